@@ -162,6 +162,7 @@ struct GemmArgs {
 
 // Number of column tiles the bf16 CE epilogue produces partials for (depends on the tile config chosen for N).
 int gemm_bf16_ce_col_tiles(int M, int N, int K);
+int gemm_cu_count();                    // compute units of the current device, at most 256
 hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t st);
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t st);
 // n weight-gradient GEMMs (A m-contiguous, B n-contiguous, plain store) in one launch where that is faster

@@ -1,108 +1,360 @@
-// fp32 GEMM for dtype MLM_F32: LDS-tiled, plain FMA, fp32 throughout.  This path exists for the
-// 1e-4 parity configuration (small shapes); the throughput path is gemm_bf16.hip.
-// Computes C[m,n] = sum_k A(m,k) B(k,n) with either operand stored k-contiguous or not, and the
-// same fused epilogues as the bf16 kernel (bias, bias+GeLU with saved pre-activation, GeLU', dlogits).
+// fp32 GEMM for dtype MLM_F32 on the fp32 matrix cores (v_mfma_f32_32x32x2_f32: 157 TFLOP/s on the whole chip, fp32
+// products and fp32 accumulation, so the precision is that of a chain of fused multiply-adds).
+// Computes C[m,n] = sum_k A(m,k) B(k,n) with either operand stored k-contiguous or not, and the same fused epilogues as
+// the bf16 kernel (bias, bias+GeLU with saved pre-activation, GeLU', dlogits).
+//
+// The order of k inside a sum is free, so the 8-deep chunk c of k is fed to four MFMAs with k = 8c + j in the lower
+// half-wave and 8c + 4 + j in the upper one (j = 0..3): a lane's four values of a k-contiguous operand are then ONE
+// 16-byte access.  The accumulator of a 32 x 32 tile holds, in lane l, column l % 32 and rows 8 (e / 4) + 4 (l / 32) +
+// e % 4, so every store covers 128 contiguous bytes of a row.
+//
+// Three kernels by the number of output tiles (launch_gemm_f32 holds the rule and the figures):
+//   * 128 x 128 tile, 4 waves of 64 x 64: operand tiles of 32 k staged through LDS (registers -> LDS, double buffered);
+//     bound by the matrix cores.
+//   * 64 x 64 tile, 8 waves: 2 x 2 waves of 32 x 32 in two groups that take the two halves of every 64-deep operand tile,
+//     so a CU that holds one tile still has two waves per SIMD to cover LDS and global latency.
+//   * 32 x 32 tile, 8 waves that split k and read their operands straight from the caches (no LDS, no barrier in the
+//     loop): for outputs of so few tiles that the serial k loop of one wave, not the matrix rate, is the time.
 #include "common.h"
 
 namespace mlm {
 
-constexpr int FT = 64;   // tile edge
-constexpr int FK = 16;   // k step
-
+// Epilogue of one accumulator element.
+struct F32Row { float coef, Mr, invS; int loc; };
 template <int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
-  __shared__ float sA[FK][FT + 4];
-  __shared__ float sB[FK][FT + 4];
+__device__ __forceinline__ F32Row f32_row(const GemmArgs& a, int m) {
+  F32Row r = {0.f, 0.f, 0.f, -1};
+  if (EPI == EPI_DLOGITS) {
+    r.coef = (a.loss_w ? a.loss_w[m] : 1.0f) / a.loss_stats[1];
+    r.Mr = a.Mrow[m];
+    r.invS = r.coef / a.Srow[m];
+    r.loc = a.targets[m] - a.v0;
+  }
+  return r;
+}
+template <int EPI>
+__device__ __forceinline__ void f32_put(const GemmArgs& a, const F32Row& r, int m, int n, float bias, float v) {
+  float* C = (float*)a.C + (size_t)m * a.ldc + n;
+  if (EPI == EPI_STORE) {
+    *C = v + bias;
+  } else if (EPI == EPI_BIAS_GELU) {
+    v += bias;
+    ((float*)a.aux)[(size_t)m * a.ldaux + n] = v;
+    *C = gelu_fwd(v, a.gelu_tanh != 0);
+  } else if (EPI == EPI_DGELU) {
+    *C = v * gelu_bwd(((const float*)a.aux)[(size_t)m * a.ldaux + n], a.gelu_tanh != 0);
+  } else if (EPI == EPI_DLOGITS) {
+    float g = expf(v - r.Mr) * r.invS;
+    if (n == r.loc) g -= r.coef;
+    *C = g;
+  }
+}
+// One 32 x 32 accumulator tile whose first row / column is (m0, n0).
+template <int EPI>
+__device__ __forceinline__ void f32_store_tile(const GemmArgs& a, const floatx16& acc, int m0, int n0, int lane) {
+  const int n = n0 + (lane & 31), lh = lane >> 5;
+  if (n >= a.N) return;
+  const float bias = ((EPI == EPI_STORE || EPI == EPI_BIAS_GELU) && a.bias) ? ((const float*)a.bias)[n] : 0.f;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int m = m0 + 8 * (e >> 2) + 4 * lh + (e & 3);
+    if (m < a.M) f32_put<EPI>(a, f32_row<EPI>(a, m), m, n, bias, acc[e]);
+  }
+}
+
+// ---- operand tile of ROWS x KT staged through LDS by NT threads ----------------------------------------------------
+// KC (k-contiguous in memory): LDS [row][KT + 4]; a fragment is one 16-byte read, rows 4 KT + 16 bytes apart fall on
+// different bank groups.  Otherwise: LDS [k][ROWS + 8]; a fragment is four 4-byte reads, the two half-waves read k-rows
+// four apart, which the 8-float pad puts 32 banks apart.
+template <bool KC, int ROWS, int KT, int NT>
+struct F32Tile {
+  static constexpr int LD = KC ? KT + 4 : ROWS + 8;
+  static constexpr int FLOATS = KC ? ROWS * LD : KT * LD;
+  static constexpr int PER = ROWS * KT / 4 / NT;             // float4 per thread
+  static_assert(ROWS * KT % (4 * NT) == 0, "tile does not divide over the threads");
+  float4 reg[PER];
+  __device__ __forceinline__ void load(const float* __restrict__ P, int ld, int row0, int nrows, int k0, int K, int tid) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int v = tid + i * NT;
+      int row, k;
+      if (KC) { row = row0 + v / (KT / 4); k = k0 + (v % (KT / 4)) * 4; }
+      else    { row = row0 + (v % (ROWS / 4)) * 4; k = k0 + v / (ROWS / 4); }
+      // rows past the end repeat the last ones (their results are not stored); k past the end counts as zero.  Row counts,
+      // and K of a k-contiguous operand, are multiples of 8: a group of four is inside or outside as a whole.
+      const float* p = KC ? P + (size_t)min(row, nrows - 1) * ld + min(k, K - 4)
+                          : P + (size_t)min(k, K - 1) * ld + min(row, nrows - 4);
+      const float4 x = *reinterpret_cast<const float4*>(p);
+      reg[i] = k < K ? x : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
+  __device__ __forceinline__ void store(float* s, int tid) const {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int v = tid + i * NT;
+      float* d = KC ? s + (v / (KT / 4)) * LD + (v % (KT / 4)) * 4 : s + (v / (ROWS / 4)) * LD + (v % (ROWS / 4)) * 4;
+      *reinterpret_cast<float4*>(d) = reg[i];
+    }
+  }
+  // the four MFMA operands of chunk c (8 k) for the 32 rows from r0
+  __device__ static __forceinline__ void frag(const float* s, int r0, int c, int lane, float (&f)[4]) {
+    const int row = r0 + (lane & 31), k = 8 * c + 4 * (lane >> 5);
+    if (KC) {
+      const float4 v = *reinterpret_cast<const float4*>(s + row * LD + k);
+      f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) f[j] = s[(k + j) * LD + row];
+    }
+  }
+};
+
+// BM x BN tile; WM x WN waves of (BM / WM) x (BN / WN), KS groups of them that share every KT-deep operand tile along k.
+template <bool A_KC, bool B_KC, int EPI, int BM, int BN, int WM, int WN, int KS, int KT>
+__global__ __launch_bounds__(64 * WM * WN * KS) void gemm_f32_tile_kernel(GemmArgs a) {
+  constexpr int NT = 64 * WM * WN * KS, TM = BM / WM / 32, TN = BN / WN / 32, NC = KT / 8 / KS;
+  typedef F32Tile<A_KC, BM, KT, NT> TA;
+  typedef F32Tile<B_KC, BN, KT, NT> TB;
+  constexpr int STAGE = TA::FLOATS + TB::FLOATS;
+  extern __shared__ __attribute__((aligned(16))) float lds_f32[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int grp = wave / (WM * WN), w = wave % (WM * WN);
+  const int wm0 = (w / WN) * (BM / WM), wn0 = (w % WN) * (BN / WN);
+  const int tiles_m = (a.M + BM - 1) / BM;
+  const int m0 = (blockIdx.x % tiles_m) * BM, n0 = (blockIdx.x / tiles_m) * BN;
   const float* A = (const float*)a.A;
   const float* B = (const float*)a.B;
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * FT, n0 = blockIdx.x * FT;
-  float acc[4][4];
+  floatx16 acc[TM][TN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  for (int k0 = 0; k0 < a.K; k0 += FK) {
+  // Tile kt + 1 waits in registers while the first half of tile kt is multiplied, is written to the other LDS buffer in
+  // the middle of it (free since the last barrier) and tile kt + 2 is requested right then: a request has a whole tile's
+  // time to arrive, and neither the LDS writes nor the wait for memory sit next to the barrier, where all waves stop.
+  TA ta;
+  TB tb;
+  const int nk = (a.K + KT - 1) / KT;
+  auto request = [&](int kt) {
+    ta.load(A, a.lda, m0, a.M, kt * KT, a.K, tid);
+    tb.load(B, a.ldb, n0, a.N, kt * KT, a.K, tid);
+  };
+  auto write = [&](int kt) {
+    float* d = lds_f32 + (kt & 1) * STAGE;
+    ta.store(d, tid);
+    tb.store(d + TA::FLOATS, tid);
+  };
+  request(0);
+  write(0);
+  if (nk > 1) request(1);
+  __syncthreads();
+  for (int kt = 0; kt < nk; ++kt) {
+    const float* sA = lds_f32 + (kt & 1) * STAGE;
+    const float* sB = sA + TA::FLOATS;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = tid + i * 256;
-      int m, k;
-      if (a.a_kc) { k = e & 15; m = e >> 4; } else { m = e & 63; k = e >> 6; }
-      float v = 0.f;
-      if (m0 + m < a.M && k0 + k < a.K)
-        v = a.a_kc ? A[(size_t)(m0 + m) * a.lda + k0 + k] : A[(size_t)(k0 + k) * a.lda + m0 + m];
-      sA[k][m] = v;
-      int n;
-      if (a.b_kc) { k = e & 15; n = e >> 4; } else { n = e & 63; k = e >> 6; }
-      v = 0.f;
-      if (n0 + n < a.N && k0 + k < a.K)
-        v = a.b_kc ? B[(size_t)(n0 + n) * a.ldb + k0 + k] : B[(size_t)(k0 + k) * a.ldb + n0 + n];
-      sB[k][n] = v;
-    }
-    __syncthreads();
+    for (int c = 0; c < NC; ++c) {
+      float fa[TM][4], fb[TN][4];
 #pragma unroll
-    for (int k = 0; k < FK; ++k) {
-      float av[4], bv[4];
+      for (int i = 0; i < TM; ++i) TA::frag(sA, wm0 + i * 32, grp * NC + c, lane, fa[i]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) { av[i] = sA[k][ty * 4 + i]; bv[i] = sB[k][tx * 4 + i]; }
+      for (int j = 0; j < TN; ++j) TB::frag(sB, wn0 + j * 32, grp * NC + c, lane, fb[j]);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][q], fb[j][q], acc[i][j], 0, 0, 0);
+      if (c == NC / 2 - 1 && kt + 1 < nk) {
+        write(kt + 1);
+        if (kt + 2 < nk) request(kt + 2);
+      }
     }
     __syncthreads();
   }
-
-  float* C = (float*)a.C;
-  const float* bias = (const float*)a.bias;
+  if (KS > 1) {
+    // the groups' sums meet in LDS ([group - 1][wave][value][lane]) and are added in group order
+    float* park = lds_f32 + w * (TM * TN * 16 * 64) + lane;
+    constexpr int GS = WM * WN * TM * TN * 16 * 64;
+    if (grp > 0) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i;
-    if (m >= a.M) continue;
-    float coef = 0.f, Mr = 0.f, invS = 0.f;
-    int loc = -1;
-    if (EPI == EPI_DLOGITS) {
-      coef = (a.loss_w ? a.loss_w[m] : 1.0f) / a.loss_stats[1];
-      Mr = a.Mrow[m];
-      invS = coef / a.Srow[m];
-      loc = a.targets[m] - a.v0;
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) park[(grp - 1) * GS + ((i * TN + j) * 16 + e) * 64] = acc[i][j][e];
     }
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int g = 0; g < KS - 1; ++g)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) acc[i][j][e] += park[g * GS + ((i * TN + j) * 16 + e) * 64];
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) f32_store_tile<EPI>(a, acc[i][j], m0 + wm0 + i * 32, n0 + wn0 + j * 32, lane);
+}
+
+// 32 x 32 tile, 8 waves: wave w sums the w-th eighth of k (in 8-deep chunks) and the eight partial tiles are added in LDS,
+// in wave order.
+constexpr int kF32SplitWaves = 8;
+constexpr int kF32SplitStep = 4;        // chunks of 8 k per step: 32 k, a full 128-byte line of a k-contiguous row
+
+// (a k-contiguous operand has K a multiple of 8; K of the weight gradient counts tokens and can be any number: its last
+// chunk is filled up with zeros)
+template <bool KC>
+__device__ __forceinline__ void f32_frag_global(const float* __restrict__ P, int ld, int row, int k, int K, float (&f)[4]) {
+  if (KC) {
+    const float4 v = *reinterpret_cast<const float4*>(P + (size_t)row * ld + k);
+    f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+  } else {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n >= a.N) continue;
-      float v = acc[i][j];
-      if (EPI == EPI_STORE) {
-        if (bias) v += bias[n];
-        C[(size_t)m * a.ldc + n] = v;
-      } else if (EPI == EPI_BIAS_GELU) {
-        if (bias) v += bias[n];
-        ((float*)a.aux)[(size_t)m * a.ldaux + n] = v;
-        C[(size_t)m * a.ldc + n] = gelu_fwd(v, a.gelu_tanh != 0);
-      } else if (EPI == EPI_DGELU) {
-        const float g = ((const float*)a.aux)[(size_t)m * a.ldaux + n];
-        C[(size_t)m * a.ldc + n] = v * gelu_bwd(g, a.gelu_tanh != 0);
-      } else if (EPI == EPI_DLOGITS) {
-        float g = expf(v - Mr) * invS;
-        if (n == loc) g -= coef;
-        C[(size_t)m * a.ldc + n] = g;
-      }
+      f[j] = P[(size_t)min(k + j, K - 1) * ld + row];
+      f[j] = k + j < K ? f[j] : 0.f;
     }
   }
 }
 
-hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t st) {
-  dim3 grid((a.N + FT - 1) / FT, (a.M + FT - 1) / FT), block(256);
-  switch (a.epi) {
-    case EPI_STORE: hipLaunchKernelGGL((gemm_f32_kernel<EPI_STORE>), grid, block, 0, st, a); break;
-    case EPI_BIAS_GELU: hipLaunchKernelGGL((gemm_f32_kernel<EPI_BIAS_GELU>), grid, block, 0, st, a); break;
-    case EPI_DGELU: hipLaunchKernelGGL((gemm_f32_kernel<EPI_DGELU>), grid, block, 0, st, a); break;
-    case EPI_DLOGITS: hipLaunchKernelGGL((gemm_f32_kernel<EPI_DLOGITS>), grid, block, 0, st, a); break;
-    default: return hipErrorInvalidValue;
+template <bool A_KC, bool B_KC, int EPI>
+__global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_kernel(GemmArgs a) {
+  constexpr int NWV = kF32SplitWaves, ST = kF32SplitStep;
+  __shared__ float park[NWV][16][64];
+  const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tiles_m = (a.M + 31) / 32;
+  const int m0 = (blockIdx.x % tiles_m) * 32, n0 = (blockIdx.x / tiles_m) * 32;
+  const float* A = (const float*)a.A;
+  const float* B = (const float*)a.B;
+  const int rowA = min(m0 + l32, a.M - 1), rowB = min(n0 + l32, a.N - 1);
+  const int nchunk = (a.K + 7) / 8;
+  const int c0 = (int)((long)nchunk * wave / NWV), c1 = (int)((long)nchunk * (wave + 1) / NWV);
+  floatx16 acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  float fa[2][ST][4], fb[2][ST][4];
+  auto load = [&](int buf, int c) {
+#pragma unroll
+    for (int q = 0; q < ST; ++q) {
+      const int k = 8 * min(c + q, nchunk - 1) + 4 * lh;         // past this wave's range: read, not multiplied
+      f32_frag_global<A_KC>(A, a.lda, rowA, k, a.K, fa[buf][q]);
+      f32_frag_global<B_KC>(B, a.ldb, rowB, k, a.K, fb[buf][q]);
+    }
+  };
+  auto multiply = [&](int buf, int c) {
+#pragma unroll
+    for (int q = 0; q < ST; ++q)
+      if (c + q < c1) {                                          // wave-uniform
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[buf][q][j], fb[buf][q][j], acc, 0, 0, 0);
+      }
+  };
+  if (c0 < c1) {
+    load(0, c0);
+    for (int c = c0; c < c1; c += 2 * ST) {
+      load(1, c + ST);
+      multiply(0, c);
+      load(0, c + 2 * ST);
+      multiply(1, c + ST);
+    }
   }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) park[wave][e][lane] = acc[e];
+  __syncthreads();
+  // wave w finishes the tile's values e = 2 w, 2 w + 1
+  const int n = n0 + l32;
+  if (n >= a.N) return;
+  const float bias = ((EPI == EPI_STORE || EPI == EPI_BIAS_GELU) && a.bias) ? ((const float*)a.bias)[n] : 0.f;
+#pragma unroll
+  for (int q = 0; q < 16 / NWV; ++q) {
+    const int e = wave * (16 / NWV) + q;
+    float v = 0.f;
+#pragma unroll
+    for (int p = 0; p < NWV; ++p) v += park[p][e][lane];
+    const int m = m0 + 8 * (e >> 2) + 4 * lh + (e & 3);
+    if (m < a.M) f32_put<EPI>(a, f32_row<EPI>(a, m), m, n, bias, v);
+  }
+}
+
+template <bool A_KC, bool B_KC, int EPI, int BM, int BN, int WM, int WN, int KS, int KT>
+static hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t st) {
+  constexpr int NT = 64 * WM * WN * KS;
+  constexpr size_t kStages = 2 * (size_t)(F32Tile<A_KC, BM, KT, NT>::FLOATS + F32Tile<B_KC, BN, KT, NT>::FLOATS) * 4;
+  constexpr size_t kPark = (size_t)(KS - 1) * BM * BN * 4;
+  constexpr size_t kLds = kStages > kPark ? kStages : kPark;
+  static_assert(kLds <= 160 * 1024, "LDS budget");
+  auto kern = gemm_f32_tile_kernel<A_KC, B_KC, EPI, BM, BN, WM, WN, KS, KT>;
+  static LdsAttrOnce attr;
+  if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
+  const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
+  hipLaunchKernelGGL(kern, dim3(tiles), dim3(NT), kLds, st, a);
   return hipGetLastError();
+}
+
+// Which kernel: the smallest of three time estimates in microseconds, fitted to measured calls of the three on MI355X
+// (2048^3 and 4096^3, 1024 x {1024 .. 8192} x {1024 .. 8192}, 512 x 1536 x 512, 256 x 256 x {128 .. 512}, 800 x 1152 x 288).
+//   * split kernel: a start-up, the serial eighth of k, and 52 TFLOP/s once the chip is full (its operands come through
+//     the caches once per 32 x 32 tile);
+//   * tile kernels: start-up plus rounds of two workgroups per CU; a last round with at most one workgroup per CU costs
+//     a little more than half.  64 x 64: 37 us per round and 1024 k, 21 us with one workgroup per CU; 128 x 128: 132 / 73.
+// 1024^3: 48 us (split), 30 us (64), 85 us (128); 4096^3: 2540 / 1160-1210 / 1050-1110 us (130 TFLOP/s, the matrix cores'
+// peak is 157); 256 x 256 x 512: < 10 / 15 / 46 us.  (One 64 x 64-tile kernel on the vector ALUs, 15.7 TFLOP/s at most, took
+// 200 us for 1024^3 and 60 us for 256 x 256 x 512 before.)
+static int f32_pick(int M, int N, int K) {
+  auto tiles = [&](int b) { return (double)((M + b - 1) / b) * ((N + b - 1) / b); };
+  const int cus = gemm_cu_count();
+  auto rounds = [&](int b, double two, double one) {
+    const double t = tiles(b), full = (double)(long)(t / (2 * cus)), rem = t - full * 2 * cus;
+    return full * two + (rem > cus ? two : rem > 0 ? one : 0.0);
+  };
+  const double k = K / 1024.0;
+  const double split = 3.0 + 6.0 * k + 2.0 * M * N * K / 52e6;
+  const double t64 = 4.0 + rounds(64, 37.0, 21.0) * k, t128 = 3.0 + rounds(128, 132.0, 73.0) * k;
+  if (split <= t64 && split <= t128) return 32;
+  return t64 <= t128 ? 64 : 128;
+}
+
+template <bool A_KC, bool B_KC, int EPI>
+static hipError_t launch_f32_layout(const GemmArgs& a, hipStream_t st) {
+  switch (f32_pick(a.M, a.N, a.K)) {
+    case 32: {
+      const int tiles = ((a.M + 31) / 32) * ((a.N + 31) / 32);
+      hipLaunchKernelGGL((gemm_f32_split_kernel<A_KC, B_KC, EPI>), dim3(tiles), dim3(64 * kF32SplitWaves), 0, st, a);
+      return hipGetLastError();
+    }
+    case 64: return launch_f32_tile<A_KC, B_KC, EPI, 64, 64, 2, 2, 2, 64>(a, st);
+    default: return launch_f32_tile<A_KC, B_KC, EPI, 128, 128, 2, 2, 1, 32>(a, st);
+  }
+}
+
+hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t st) {
+  if (a.a_kc && !a.b_kc) {
+    switch (a.epi) {
+      case EPI_STORE: return launch_f32_layout<true, false, EPI_STORE>(a, st);
+      case EPI_BIAS_GELU: return launch_f32_layout<true, false, EPI_BIAS_GELU>(a, st);
+      case EPI_DLOGITS: return launch_f32_layout<true, false, EPI_DLOGITS>(a, st);
+      default: return hipErrorInvalidValue;
+    }
+  }
+  if (a.a_kc && a.b_kc) {
+    switch (a.epi) {
+      case EPI_STORE: return launch_f32_layout<true, true, EPI_STORE>(a, st);
+      case EPI_DGELU: return launch_f32_layout<true, true, EPI_DGELU>(a, st);
+      default: return hipErrorInvalidValue;
+    }
+  }
+  if (!a.a_kc && !a.b_kc && a.epi == EPI_STORE) return launch_f32_layout<false, false, EPI_STORE>(a, st);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace mlm
