@@ -463,8 +463,7 @@ static int attn_shard_bwd_impl(const mlm_dims* dims, const void* dx1, const void
   if (!defer) MLM_TRY_HIP(run_gemm(dt, gemm_wgrad(L.Hl, dims->H, L.T, ctx_r, dx1, dWo_r), st, sk));
   MLM_TRY_HIP(run_gemm(dt, gemm_dgrad(L.T, L.Hl, dims->H, dx1, Wo_r, dctx), st, sk));
   // attention core
-  // bf16: the dQ kernel computes delta itself (and stores it for the dK/dV kernel)
-  if (dt != MLM_BF16) MLM_TRY_HIP(launch_attn_delta(dt, L.T, L.hl, L.d, dims->b, dims->s, ctx_r, dctx, delta, st));
+  // the dQ kernels compute delta = rowsum(dctx o ctx) themselves and store it for the dK/dV kernels
   AttnArgs a;
   memset(&a, 0, sizeof(a));
   a.b = dims->b; a.s = dims->s; a.hl = L.hl; a.d = L.d; a.causal = dims->causal; a.key_len = key_len;

@@ -1,8 +1,22 @@
-// fp32 attention for dtype MLM_F32 (the 1e-4 parity path; small shapes).  Streaming-softmax
-// forward and a two-kernel backward (dQ per query row, dK/dV per key row) that recompute the
-// probabilities from the saved log-sum-exp, so nothing of size s x s is ever stored and no
-// atomics are needed (results are deterministic).  One thread owns one row; K/V (or Q/dO)
-// tiles are staged through LDS and read as broadcasts.
+// fp32 attention for dtype MLM_F32 on the fp32 matrix cores (v_mfma_f32_32x32x2_f32): streaming-softmax forward and a
+// two-kernel backward (dQ per query block, dK/dV per key block) that recompute the probabilities from the saved
+// log-sum-exp, so nothing of size s x s is ever stored and no atomics are needed (results are deterministic).
+//
+// A workgroup owns 32 rows (queries in forward and dQ, keys in dK/dV) of one (batch, head); its four waves take the
+// 32-row tiles of the other sequence axis in turn (wave w: tiles w, w + 4, ...) and their partial results are merged
+// through LDS in wave order: splitting the streamed axis over the waves shortens the serial chain, and a sequence of 128
+// tokens, four tiles long, still keeps all four waves busy.  Bound by the matrix cores' fp32 rate and, below a few tiles
+// per wave, by the chain of one tile.  Two sequences of 512 tokens, 16 heads of 64, causal: forward 32 us, dQ 50, dK/dV 87
+// (739 / 721 + 7 for delta / 1134 with one thread per row on the vector ALUs); two of 128 tokens, 2 heads: 8 / 11 / 14 us
+// (192 / 190 + 6 / 305).
+//
+// Scores are computed so that a lane's 16 accumulator values belong to ONE owned row, column l % 32 of the 32 x 32 tile,
+// and to the streamed rows 8 (e / 4) + 4 (l / 32) + e % 4: row statistics are per-lane scalars plus one cross-half
+// exchange, and value e is already the second product's operand for the pair of streamed rows {8 (e / 4) + e % 4, + 4} --
+// the probabilities never leave their registers.  Operands come straight from the caches: 16-byte reads of a row where
+// the head dimension is contracted (the order of a contraction is free, so the 8-deep chunk c feeds four MFMAs with
+// elements 8 c + j / 8 c + 4 + j in the half-waves), 128-byte coalesced reads where the sequence is.
+//
 // Masking follows the integer predicate allowed(i,j) = (j < key_len[b]) && (!causal || j <= i);
 // excluded keys contribute exactly zero.
 // Dropout of the probabilities (a.drop.enabled): the forward kernel draws the keep decision of element
@@ -13,218 +27,302 @@
 
 namespace mlm {
 
-constexpr int AF_TILE = 32;
+constexpr int AF_ROWS = 32;          // owned rows per workgroup and rows per streamed tile
+constexpr int AF_WAVES = 4;
+
+template <int D> struct AfShape {
+  static constexpr int NC = D / 8;               // 8-deep chunks of the head dimension
+  static constexpr int DT = (D + 31) / 32;       // 32-column tiles of it (the last one may hang over D)
+};
+
+// This lane's share (elements 8 c + 4 lh .. + 3 of every chunk c) of one row of the head.
+template <int D>
+__device__ __forceinline__ void af_load_row(const float* __restrict__ row, int lh, float (&f)[D / 2]) {
+#pragma unroll
+  for (int c = 0; c < D / 8; ++c) {
+    const float4 v = *reinterpret_cast<const float4*>(row + 8 * c + 4 * lh);
+    f[4 * c] = v.x; f[4 * c + 1] = v.y; f[4 * c + 2] = v.z; f[4 * c + 3] = v.w;
+  }
+}
+// acc[streamed row][owned row] = sum over the head dimension of streamed[row] . owned (registers)
+template <int D>
+__device__ __forceinline__ floatx16 af_scores(const float* __restrict__ row, int lh, const float (&own)[D / 2]) {
+  floatx16 acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+#pragma unroll
+  for (int c = 0; c < D / 8; ++c) {
+    const float4 v = *reinterpret_cast<const float4*>(row + 8 * c + 4 * lh);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v.x, own[4 * c], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v.y, own[4 * c + 1], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v.z, own[4 * c + 2], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v.w, own[4 * c + 3], acc, 0, 0, 0);
+  }
+  return acc;
+}
+// out[dt][head column][owned row] += sum over the tile's streamed rows of M[row][column] w[row][owned row]; M: element
+// (0, 0) of the matrix, rows beyond nrows - 1 repeat the last one (their weights are zero).
+template <int D>
+__device__ __forceinline__ void af_accumulate(const float* __restrict__ M, int ld, int r0, int nrows, int lane,
+                                              const floatx16& w, floatx16 (&out)[AfShape<D>::DT]) {
+  const int l32 = lane & 31, lh = lane >> 5;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int r = min(r0 + 8 * (e >> 2) + 4 * lh + (e & 3), nrows - 1);
+    const float* p = M + (size_t)r * ld + l32;
+#pragma unroll
+    for (int dt = 0; dt < AfShape<D>::DT; ++dt) {
+      const bool in = D % 32 == 0 || dt * 32 + l32 < D;
+      const float v = in ? p[dt * 32] : 0.f;
+      out[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, w[e], out[dt], 0, 0, 0);
+    }
+  }
+}
+// The waves' accumulators parked in LDS ([wave][value][lane]: conflict-free)
+template <int NV> __device__ __forceinline__ float* af_park(float* lds, int wave, int lane) { return lds + (size_t)wave * NV * 64 + lane; }
 
 template <int D>
-__global__ __launch_bounds__(64) void attn_fwd_f32_kernel(AttnArgs a) {
-  extern __shared__ float lds[];
-  float* sK = lds;                      // [AF_TILE][D]
-  float* sV = lds + AF_TILE * D;        // [AF_TILE][D]
-  const int lane = threadIdx.x;
-  const int i = blockIdx.x * 64 + lane;
+__global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_fwd_f32_kernel(AttnArgs a) {
+  constexpr int DT = AfShape<D>::DT, NV = DT * 16 + 2;
+  extern __shared__ __attribute__((aligned(16))) float lds_af[];
+  const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int qb = gridDim.x - 1 - blockIdx.x;             // longest (causal) blocks first
   const int hd = blockIdx.y, bi = blockIdx.z;
   const int ld = 3 * a.hl * D;
-  const float* qkv = (const float*)a.qkv;
-  const size_t tok0 = (size_t)bi * a.s;
+  const float* base = (const float*)a.qkv + (size_t)bi * a.s * ld;
   const int klen = attn_key_len(a.key_len, bi, a.s);
-  const bool active = i < a.s;
+  const int q0 = qb * AF_ROWS, qi = q0 + l32;
   const float scale = 1.0f / sqrtf((float)D);
-  float q[D], o[D];
+  float q[D / 2];
+  af_load_row<D>(base + (size_t)min(qi, a.s - 1) * ld + hd * D, lh, q);
+  floatx16 o[DT];
 #pragma unroll
-  for (int c = 0; c < D; ++c) {
-    q[c] = active ? qkv[(tok0 + i) * ld + hd * D + c] : 0.f;
-    o[c] = 0.f;
-  }
-  float m = -INFINITY, l = 0.f;
-  int kend = klen;
-  if (a.causal) kend = min(kend, min(a.s, blockIdx.x * 64 + 64));
-  const size_t row = ((size_t)bi * a.hl + hd) * a.s + (active ? i : 0);   // row of the [b, hl, s, s] probability tensor
-  for (int k0 = 0; k0 < kend; k0 += AF_TILE) {
-    for (int e = lane; e < AF_TILE * D; e += 64) {
-      const int j = e / D, c = e % D;
-      const bool ok = k0 + j < a.s;
-      sK[e] = ok ? qkv[(tok0 + k0 + j) * ld + (a.hl + hd) * D + c] : 0.f;
-      sV[e] = ok ? qkv[(tok0 + k0 + j) * ld + (2 * a.hl + hd) * D + c] : 0.f;
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) o[dt][e] = 0.f;
+  float m = -INFINITY, l = 0.f;                          // l: this half-wave's keys only
+  int kv_end = klen;
+  if (a.causal) kv_end = min(kv_end, min(a.s, q0 + AF_ROWS));
+  const size_t prow = ((size_t)bi * a.hl + hd) * a.s + min(qi, a.s - 1);   // row of the [b, hl, s, s] probability tensor
+  const float* K = base + (a.hl + hd) * D;
+  const float* V = base + (2 * a.hl + hd) * D;
+  for (int k0 = wave * AF_ROWS; k0 < kv_end; k0 += AF_WAVES * AF_ROWS) {
+    floatx16 s = af_scores<D>(K + (size_t)min(k0 + l32, a.s - 1) * ld, lh, q);
+    float mt = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int key = k0 + 8 * (e >> 2) + 4 * lh + (e & 3);
+      s[e] = (key >= klen || (a.causal && key > qi)) ? -INFINITY : s[e] * scale;
+      mt = fmaxf(mt, s[e]);
     }
-    __syncthreads();
-    if (active) {
-      uint32_t bits = 0xFFFFFFFFu;                  // keep bits of keys k0 .. k0 + 31
-      if (a.drop.enabled) {
-        bits = 0;
+    // key k0 is allowed for every query of the block (k0 < kv_end, and a causal tile never starts right of the block's
+    // first query), so the maximum is finite
+    const float mn = fmaxf(m, fmaxf(mt, __shfl_xor(mt, 32, 64)));
+    const float corr = expf(m - mn);
+    float ls = 0.f;
 #pragma unroll
-        for (int g = 0; g < AF_TILE / 4; ++g) bits |= drop_keep4(a.drop, (row * a.s + k0 + 4 * g) >> 2) << (4 * g);
-        a.keep_bits[row * a.keep_pitch + k0 / 32] = bits;
-      }
-      for (int j = 0; j < AF_TILE; ++j) {
-        const int key = k0 + j;
-        if (key >= klen || (a.causal && key > i)) continue;
-        float sc = 0.f;
-#pragma unroll
-        for (int c = 0; c < D; ++c) sc = fmaf(q[c], sK[j * D + c], sc);
-        sc *= scale;
-        const float mn = fmaxf(m, sc);
-        const float corr = expf(m - mn);
-        const float p = expf(sc - mn);
-        l = l * corr + p;
-        const float pd = ((bits >> j) & 1u) ? p : 0.f;
-#pragma unroll
-        for (int c = 0; c < D; ++c) o[c] = o[c] * corr + pd * sV[j * D + c];
-        m = mn;
-      }
+    for (int e = 0; e < 16; ++e) {
+      s[e] = expf(s[e] - mn);
+      ls += s[e];
     }
-    __syncthreads();
-  }
-  if (active) {
-    const float inv = a.drop.scale / l;
-    float* ctx = (float*)a.ctx;
+    l = l * corr + ls;
+    m = mn;
 #pragma unroll
-    for (int c = 0; c < D; ++c) ctx[(tok0 + i) * (a.hl * D) + hd * D + c] = o[c] * inv;
-    a.lse[((size_t)bi * a.hl + hd) * a.s + i] = m + logf(l);
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) o[dt][e] *= corr;
+    if (a.drop.enabled) {
+      uint32_t word = 0;                                 // this half-wave's 16 of the tile's 32 keep bits
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const uint32_t k4 = drop_keep4(a.drop, (prow * a.s + k0 + 8 * g + 4 * lh) >> 2);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[4 * g + e] = ((k4 >> e) & 1u) ? s[4 * g + e] : 0.f;
+        word |= k4 << (8 * g + 4 * lh);
+      }
+      word |= __shfl_xor(word, 32, 64);
+      if (lh == 0 && qi < a.s) a.keep_bits[prow * a.keep_pitch + (k0 >> 5)] = word;
+    }
+    af_accumulate<D>(V, ld, k0, a.s, lane, s, o);
+  }
+  float* park = af_park<NV>(lds_af, wave, lane);
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) park[(dt * 16 + e) * 64] = o[dt][e];
+  park[DT * 16 * 64] = m;
+  park[(DT * 16 + 1) * 64] = l;
+  __syncthreads();
+  // every wave forms the merged statistics of all rows and finishes DT of the 4 DT groups of four head columns
+  float M = -INFINITY, L = 0.f, c[AF_WAVES];
+#pragma unroll
+  for (int w = 0; w < AF_WAVES; ++w) M = fmaxf(M, af_park<NV>(lds_af, w, lane)[DT * 16 * 64]);   // wave 0 has tile 0: finite
+#pragma unroll
+  for (int w = 0; w < AF_WAVES; ++w) {
+    c[w] = expf(af_park<NV>(lds_af, w, lane)[DT * 16 * 64] - M);
+    L += c[w] * (af_park<NV>(lds_af, w, lane)[(DT * 16 + 1) * 64] + af_park<NV>(lds_af, w, lane ^ 32)[(DT * 16 + 1) * 64]);
+  }
+  if (qi >= a.s) return;
+  const float inv = a.drop.scale / L;
+  float* crow = (float*)a.ctx + ((size_t)bi * a.s + qi) * (a.hl * D) + hd * D;
+#pragma unroll
+  for (int i = 0; i < DT; ++i) {
+    const int grp = wave * DT + i, dt = grp >> 2, g = grp & 3;
+    const int col = dt * 32 + 8 * g + 4 * lh;
+    float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int w = 0; w < AF_WAVES; ++w) {
+      const float* p = af_park<NV>(lds_af, w, lane) + (dt * 16 + 4 * g) * 64;
+      r.x += p[0] * c[w]; r.y += p[64] * c[w]; r.z += p[128] * c[w]; r.w += p[192] * c[w];
+    }
+    if (col < D) *reinterpret_cast<float4*>(crow + col) = make_float4(r.x * inv, r.y * inv, r.z * inv, r.w * inv);
+  }
+  if (wave == 0 && lh == 0) a.lse[((size_t)bi * a.hl + hd) * a.s + qi] = M + logf(L);
+}
+
+// dQ_i = scale * sum_j dS_ij K_j,  dS_ij = P_ij (dO_i . V_j - delta_i),  P_ij = exp(scale q_i.k_j - lse_i);
+// delta_i = dO_i . O_i is formed here from rows the lanes hold and left in the workspace for the dK/dV kernel.
+template <int D>
+__global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dq_f32_kernel(AttnArgs a) {
+  constexpr int DT = AfShape<D>::DT, NV = DT * 16;
+  extern __shared__ __attribute__((aligned(16))) float lds_af[];
+  const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int qb = gridDim.x - 1 - blockIdx.x;
+  const int hd = blockIdx.y, bi = blockIdx.z;
+  const int ld = 3 * a.hl * D, ldo = a.hl * D;
+  const float* base = (const float*)a.qkv + (size_t)bi * a.s * ld;
+  const int klen = attn_key_len(a.key_len, bi, a.s);
+  const int q0 = qb * AF_ROWS, qi = q0 + l32, qc = min(qi, a.s - 1);
+  const float scale = 1.0f / sqrtf((float)D);
+  float q[D / 2], dov[D / 2];
+  af_load_row<D>(base + (size_t)qc * ld + hd * D, lh, q);
+  af_load_row<D>((const float*)a.dctx + ((size_t)bi * a.s + qc) * ldo + hd * D, lh, dov);
+  float dl = 0.f;
+  {
+    float ov[D / 2];
+    af_load_row<D>((const float*)a.ctx + ((size_t)bi * a.s + qc) * ldo + hd * D, lh, ov);
+#pragma unroll
+    for (int c = 0; c < D / 2; ++c) dl = fmaf(ov[c], dov[c], dl);
+    dl += __shfl_xor(dl, 32, 64);
+  }
+  const size_t row = ((size_t)bi * a.hl + hd) * a.s + qc;
+  const float lse = a.lse[row];
+  if (wave == 0 && lh == 0 && qi < a.s) a.delta[row] = dl;
+  floatx16 dq[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) dq[dt][e] = 0.f;
+  int kv_end = klen;
+  if (a.causal) kv_end = min(kv_end, min(a.s, q0 + AF_ROWS));
+  const float* K = base + (a.hl + hd) * D;
+  const float* V = base + (2 * a.hl + hd) * D;
+  for (int k0 = wave * AF_ROWS; k0 < kv_end; k0 += AF_WAVES * AF_ROWS) {
+    const int kr = min(k0 + l32, a.s - 1);
+    floatx16 s = af_scores<D>(K + (size_t)kr * ld, lh, q);
+    const floatx16 dp = af_scores<D>(V + (size_t)kr * ld, lh, dov);
+    const uint32_t bits = a.drop.enabled ? a.keep_bits[row * a.keep_pitch + (k0 >> 5)] >> (4 * lh) : 0xFFFFFFFFu;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int key = k0 + 8 * (e >> 2) + 4 * lh + (e & 3);
+      const bool off = key >= klen || (a.causal && key > qi);
+      const float p = off ? 0.f : expf(s[e] * scale - lse);
+      // gradient w.r.t. the undropped probability
+      const float g = ((bits >> (8 * (e >> 2) + (e & 3))) & 1u) ? dp[e] * a.drop.scale : 0.f;
+      s[e] = p * (g - dl);
+    }
+    af_accumulate<D>(K, ld, k0, a.s, lane, s, dq);
+  }
+  float* park = af_park<NV>(lds_af, wave, lane);
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) park[(dt * 16 + e) * 64] = dq[dt][e];
+  __syncthreads();
+  if (qi >= a.s) return;
+  float* orow = (float*)a.dqkv + ((size_t)bi * a.s + qi) * ld + hd * D;
+#pragma unroll
+  for (int i = 0; i < DT; ++i) {
+    const int grp = wave * DT + i, dt = grp >> 2, g = grp & 3;
+    const int col = dt * 32 + 8 * g + 4 * lh;
+    float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int w = 0; w < AF_WAVES; ++w) {
+      const float* p = af_park<NV>(lds_af, w, lane) + (dt * 16 + 4 * g) * 64;
+      r.x += p[0]; r.y += p[64]; r.z += p[128]; r.w += p[192];
+    }
+    if (col < D) *reinterpret_cast<float4*>(orow + col) = make_float4(r.x * scale, r.y * scale, r.z * scale, r.w * scale);
   }
 }
 
-// dQ_i = scale * sum_j dS_ij K_j,  dS_ij = P_ij (dO_i . V_j - delta_i),  P_ij = exp(scale q_i.k_j - lse_i)
+// dV_j = sum_i P_ij dO_i,  dK_j = scale * sum_i dS_ij Q_i
 template <int D>
-__global__ __launch_bounds__(64) void attn_bwd_dq_f32_kernel(AttnArgs a) {
-  extern __shared__ float lds[];
-  float* sK = lds;
-  float* sV = lds + AF_TILE * D;
-  float* sdO = lds + 2 * AF_TILE * D;   // [64][D+1] this block's dO rows
-  const int lane = threadIdx.x;
-  const int i = blockIdx.x * 64 + lane;
+__global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dkv_f32_kernel(AttnArgs a) {
+  constexpr int DT = AfShape<D>::DT, NV = 2 * DT * 16;
+  extern __shared__ __attribute__((aligned(16))) float lds_af[];
+  const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int hd = blockIdx.y, bi = blockIdx.z;
-  const int ld = 3 * a.hl * D;
-  const float* qkv = (const float*)a.qkv;
-  const float* dctx = (const float*)a.dctx;
-  const size_t tok0 = (size_t)bi * a.s;
+  const int ld = 3 * a.hl * D, ldo = a.hl * D;
+  const float* base = (const float*)a.qkv + (size_t)bi * a.s * ld;
+  const float* dO = (const float*)a.dctx + (size_t)bi * a.s * ldo + hd * D;
+  const float* Q = base + hd * D;
   const int klen = attn_key_len(a.key_len, bi, a.s);
-  const bool active = i < a.s;
+  const int kb0 = blockIdx.x * AF_ROWS, kj = kb0 + l32, kc = min(kj, a.s - 1);
   const float scale = 1.0f / sqrtf((float)D);
-  float q[D], dq[D];
+  float kf[D / 2], vf[D / 2];
+  af_load_row<D>(base + (size_t)kc * ld + (a.hl + hd) * D, lh, kf);
+  af_load_row<D>(base + (size_t)kc * ld + (2 * a.hl + hd) * D, lh, vf);
+  floatx16 dk[DT], dv[DT];
 #pragma unroll
-  for (int c = 0; c < D; ++c) {
-    q[c] = active ? qkv[(tok0 + i) * ld + hd * D + c] : 0.f;
-    sdO[lane * (D + 1) + c] = active ? dctx[(tok0 + i) * (a.hl * D) + hd * D + c] : 0.f;
-    dq[c] = 0.f;
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) { dk[dt][e] = 0.f; dv[dt][e] = 0.f; }
+  const size_t row0 = ((size_t)bi * a.hl + hd) * a.s;
+  // key blocks of padding only get zeros; a causal block starts at its own first query
+  const int q_begin = kb0 >= klen ? a.s : (a.causal ? kb0 : 0);
+  for (int q0 = q_begin + wave * AF_ROWS; q0 < a.s; q0 += AF_WAVES * AF_ROWS) {
+    const int qr = min(q0 + l32, a.s - 1);
+    floatx16 s = af_scores<D>(Q + (size_t)qr * ld, lh, kf);          // [query][key]
+    floatx16 dp = af_scores<D>(dO + (size_t)qr * ldo, lh, vf);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int i = q0 + 8 * (e >> 2) + 4 * lh + (e & 3), ic = min(i, a.s - 1);
+      const bool off = kj >= klen || i >= a.s || (a.causal && kj > i);
+      const float p = off ? 0.f : expf(s[e] * scale - a.lse[row0 + ic]);
+      float keep = 1.0f;
+      if (a.drop.enabled)
+        keep = ((a.keep_bits[(row0 + ic) * a.keep_pitch + (kb0 >> 5)] >> l32) & 1u) ? a.drop.scale : 0.f;
+      s[e] = p * keep;
+      dp[e] = p * (dp[e] * keep - a.delta[row0 + ic]);
+    }
+    af_accumulate<D>(dO, ldo, q0, a.s, lane, s, dv);
+    af_accumulate<D>(Q, ld, q0, a.s, lane, dp, dk);
   }
-  const float lse = active ? a.lse[((size_t)bi * a.hl + hd) * a.s + i] : 0.f;
-  const float dl = active ? a.delta[((size_t)bi * a.hl + hd) * a.s + i] : 0.f;
-  const size_t row = ((size_t)bi * a.hl + hd) * a.s + (active ? i : 0);
-  int kend = klen;
-  if (a.causal) kend = min(kend, min(a.s, blockIdx.x * 64 + 64));
-  for (int k0 = 0; k0 < kend; k0 += AF_TILE) {
-    for (int e = lane; e < AF_TILE * D; e += 64) {
-      const int j = e / D, c = e % D;
-      const bool ok = k0 + j < a.s;
-      sK[e] = ok ? qkv[(tok0 + k0 + j) * ld + (a.hl + hd) * D + c] : 0.f;
-      sV[e] = ok ? qkv[(tok0 + k0 + j) * ld + (2 * a.hl + hd) * D + c] : 0.f;
+  float* park = af_park<NV>(lds_af, wave, lane);
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      park[(dt * 16 + e) * 64] = dk[dt][e] * scale;
+      park[((DT + dt) * 16 + e) * 64] = dv[dt][e];
     }
-    __syncthreads();
-    if (active) {
-      const uint32_t bits = a.drop.enabled ? a.keep_bits[row * a.keep_pitch + k0 / 32] : 0xFFFFFFFFu;
-      for (int j = 0; j < AF_TILE; ++j) {
-        const int key = k0 + j;
-        if (key >= klen || (a.causal && key > i)) continue;
-        float sc = 0.f, dp = 0.f;
+  __syncthreads();
+  if (kj >= a.s) return;
+  float* krow = (float*)a.dqkv + ((size_t)bi * a.s + kj) * ld + (a.hl + hd) * D;
 #pragma unroll
-        for (int c = 0; c < D; ++c) {
-          sc = fmaf(q[c], sK[j * D + c], sc);
-          dp = fmaf(sdO[lane * (D + 1) + c], sV[j * D + c], dp);
-        }
-        dp = ((bits >> j) & 1u) ? dp * a.drop.scale : 0.f;     // gradient w.r.t. the undropped probability
-        const float p = expf(sc * scale - lse);
-        const float ds = p * (dp - dl);
+  for (int i = 0; i < 2 * DT; ++i) {
+    const int grp = wave * 2 * DT + i, t = grp >> 2, g = grp & 3;     // t < DT: dK tile t, else dV tile t - DT
+    const int col = (t % DT) * 32 + 8 * g + 4 * lh;
+    float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-        for (int c = 0; c < D; ++c) dq[c] = fmaf(ds, sK[j * D + c], dq[c]);
-      }
+    for (int w = 0; w < AF_WAVES; ++w) {
+      const float* p = af_park<NV>(lds_af, w, lane) + (t * 16 + 4 * g) * 64;
+      r.x += p[0]; r.y += p[64]; r.z += p[128]; r.w += p[192];
     }
-    __syncthreads();
-  }
-  if (active) {
-    float* dqkv = (float*)a.dqkv;
-#pragma unroll
-    for (int c = 0; c < D; ++c) dqkv[(tok0 + i) * ld + hd * D + c] = dq[c] * scale;
-  }
-}
-
-// dV_j = sum_i P_ij dO_i,  dK_j = scale * sum_i dS_ij Q_i   (one thread per key row j)
-template <int D>
-__global__ __launch_bounds__(64) void attn_bwd_dkv_f32_kernel(AttnArgs a) {
-  extern __shared__ float lds[];
-  float* sQ = lds;                          // [AF_TILE][D]
-  float* sdO = lds + AF_TILE * D;           // [AF_TILE][D]
-  float* sKj = lds + 2 * AF_TILE * D;       // [64][D+1] this block's K rows
-  float* sVj = sKj + 64 * (D + 1);          // [64][D+1]
-  float* sLse = sVj + 64 * (D + 1);         // [AF_TILE]
-  float* sDl = sLse + AF_TILE;              // [AF_TILE]
-  const int lane = threadIdx.x;
-  const int j = blockIdx.x * 64 + lane;
-  const int hd = blockIdx.y, bi = blockIdx.z;
-  const int ld = 3 * a.hl * D;
-  const float* qkv = (const float*)a.qkv;
-  const float* dctx = (const float*)a.dctx;
-  const size_t tok0 = (size_t)bi * a.s;
-  const int klen = attn_key_len(a.key_len, bi, a.s);
-  const bool active = j < a.s && j < klen;
-  const float scale = 1.0f / sqrtf((float)D);
-  float dk[D], dv[D];
-#pragma unroll
-  for (int c = 0; c < D; ++c) {
-    const bool ok = j < a.s;
-    sKj[lane * (D + 1) + c] = ok ? qkv[(tok0 + j) * ld + (a.hl + hd) * D + c] : 0.f;
-    sVj[lane * (D + 1) + c] = ok ? qkv[(tok0 + j) * ld + (2 * a.hl + hd) * D + c] : 0.f;
-    dk[c] = 0.f;
-    dv[c] = 0.f;
-  }
-  const int ibeg = a.causal ? (blockIdx.x * 64) / AF_TILE * AF_TILE : 0;
-  for (int i0 = ibeg; i0 < a.s; i0 += AF_TILE) {
-    for (int e = lane; e < AF_TILE * D; e += 64) {
-      const int ii = e / D, c = e % D;
-      const bool ok = i0 + ii < a.s;
-      sQ[e] = ok ? qkv[(tok0 + i0 + ii) * ld + hd * D + c] : 0.f;
-      sdO[e] = ok ? dctx[(tok0 + i0 + ii) * (a.hl * D) + hd * D + c] : 0.f;
-    }
-    if (lane < AF_TILE) {
-      const bool ok = i0 + lane < a.s;
-      sLse[lane] = ok ? a.lse[((size_t)bi * a.hl + hd) * a.s + i0 + lane] : 0.f;
-      sDl[lane] = ok ? a.delta[((size_t)bi * a.hl + hd) * a.s + i0 + lane] : 0.f;
-    }
-    __syncthreads();
-    if (active) {
-      for (int ii = 0; ii < AF_TILE; ++ii) {
-        const int i = i0 + ii;
-        if (i >= a.s || (a.causal && j > i)) continue;
-        float sc = 0.f, dp = 0.f;
-#pragma unroll
-        for (int c = 0; c < D; ++c) {
-          sc = fmaf(sQ[ii * D + c], sKj[lane * (D + 1) + c], sc);
-          dp = fmaf(sdO[ii * D + c], sVj[lane * (D + 1) + c], dp);
-        }
-        const float p = expf(sc * scale - sLse[ii]);
-        float keep = 1.0f;
-        if (a.drop.enabled) {
-          const size_t row = ((size_t)bi * a.hl + hd) * a.s + i;
-          keep = ((a.keep_bits[row * a.keep_pitch + (j >> 5)] >> (j & 31)) & 1u) ? a.drop.scale : 0.f;
-        }
-        dp *= keep;
-        const float ds = p * (dp - sDl[ii]);
-        const float pd = p * keep;
-#pragma unroll
-        for (int c = 0; c < D; ++c) {
-          dv[c] = fmaf(pd, sdO[ii * D + c], dv[c]);
-          dk[c] = fmaf(ds, sQ[ii * D + c], dk[c]);
-        }
-      }
-    }
-    __syncthreads();
-  }
-  if (j < a.s) {
-    float* dqkv = (float*)a.dqkv;
-#pragma unroll
-    for (int c = 0; c < D; ++c) {
-      dqkv[(tok0 + j) * ld + (a.hl + hd) * D + c] = dk[c] * scale;
-      dqkv[(tok0 + j) * ld + (2 * a.hl + hd) * D + c] = dv[c];
-    }
+    if (col < D) *reinterpret_cast<float4*>(krow + (t < DT ? 0 : a.hl * D) + col) = r;
   }
 }
 
@@ -238,11 +336,16 @@ bool attn_f32_supported(int d) { return d > 0 && d % 16 == 0 && d <= 128; }
     default: return hipErrorInvalidValue;                                                            \
   }
 
+// values per lane that a wave parks -> bytes of LDS of the workgroup
+static constexpr size_t af_lds(int values) { return (size_t)AF_WAVES * values * 64 * sizeof(float); }
+
 hipError_t launch_attn_fwd_f32(const AttnArgs& a, hipStream_t st) {
-  dim3 grid((a.s + 63) / 64, a.hl, a.b), block(64);
+  const dim3 grid((a.s + AF_ROWS - 1) / AF_ROWS, a.hl, a.b), block(64 * AF_WAVES);
 #define MLM_AF_FWD(DD)                                                                               \
   {                                                                                                  \
-    const size_t lds = (size_t)2 * AF_TILE * DD * sizeof(float);                                     \
+    constexpr size_t lds = af_lds(AfShape<DD>::DT * 16 + 2);                                         \
+    static LdsAttrOnce attr;                                                                         \
+    if (hipError_t e = attr.ensure((const void*)attn_fwd_f32_kernel<DD>, (int)lds); e != hipSuccess) return e; \
     hipLaunchKernelGGL((attn_fwd_f32_kernel<DD>), grid, block, lds, st, a);                          \
   }
   MLM_AF_SWITCH(MLM_AF_FWD)
@@ -251,17 +354,15 @@ hipError_t launch_attn_fwd_f32(const AttnArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_attn_bwd_f32(const AttnArgs& a, hipStream_t st) {
-  dim3 grid((a.s + 63) / 64, a.hl, a.b), block(64);
+  const dim3 grid((a.s + AF_ROWS - 1) / AF_ROWS, a.hl, a.b), block(64 * AF_WAVES);
 #define MLM_AF_BWD(DD)                                                                               \
   {                                                                                                  \
-    const size_t lds1 = ((size_t)2 * AF_TILE * DD + 64 * (DD + 1)) * sizeof(float);                  \
+    constexpr size_t lds1 = af_lds(AfShape<DD>::DT * 16), lds2 = af_lds(2 * AfShape<DD>::DT * 16);   \
+    static_assert(lds2 <= 160 * 1024, "LDS budget");                                                 \
+    static LdsAttrOnce attr1, attr2;                                                                 \
+    if (hipError_t e = attr1.ensure((const void*)attn_bwd_dq_f32_kernel<DD>, (int)lds1); e != hipSuccess) return e; \
+    if (hipError_t e = attr2.ensure((const void*)attn_bwd_dkv_f32_kernel<DD>, (int)lds2); e != hipSuccess) return e; \
     hipLaunchKernelGGL((attn_bwd_dq_f32_kernel<DD>), grid, block, lds1, st, a);                      \
-    const size_t lds2 = ((size_t)2 * AF_TILE * DD + 2 * 64 * (DD + 1) + 2 * AF_TILE) * sizeof(float); \
-    if (lds2 > 64 * 1024) {                                                                          \
-      hipError_t e = hipFuncSetAttribute((const void*)attn_bwd_dkv_f32_kernel<DD>,                   \
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds2);     \
-      if (e != hipSuccess) return e;                                                                 \
-    }                                                                                                \
     hipLaunchKernelGGL((attn_bwd_dkv_f32_kernel<DD>), grid, block, lds2, st, a);                     \
   }
   MLM_AF_SWITCH(MLM_AF_BWD)

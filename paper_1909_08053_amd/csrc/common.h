@@ -264,7 +264,5 @@ hipError_t launch_embed_bwd(int dtype, int T, int H, int Vl, int v0, const int32
                             const void* dz, void* dE, hipStream_t st);
 hipError_t launch_embed_bwd_replicated(int dtype, int b, int s, int H, const void* dx0, void* dz0, void* dpos,
                                        const mlm_dropout* drop, hipStream_t st);
-hipError_t launch_attn_delta(int dtype, int T, int hl, int d, int b, int s, const void* ctx, const void* dctx,
-                             float* delta, hipStream_t st);
 
 }  // namespace mlm

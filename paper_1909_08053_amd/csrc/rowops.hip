@@ -996,40 +996,6 @@ hipError_t launch_rows_scatter(int dtype, int n, int rows, int H, const int32_t*
   return hipGetLastError();
 }
 
-// delta[b, head, i] = sum_c dctx[t, head*d + c] * ctx[t, head*d + c]  (row sum of dP o P in the softmax gradient)
-template <typename T>
-__global__ __launch_bounds__(256) void attn_delta_kernel(int Tn, int hl, int d, int s, const T* __restrict__ ctx,
-                                                         const T* __restrict__ dctx, float* __restrict__ delta) {
-  constexpr int VN = Vec16<T>::N;
-  const int idx = blockIdx.x * 256 + threadIdx.x;   // (t, head)
-  if (idx >= Tn * hl) return;
-  const int t = idx / hl, hd = idx % hl;
-  const size_t off = (size_t)t * hl * d + (size_t)hd * d;
-  float acc = 0.f;
-  for (int c = 0; c < d; c += VN) {
-    Vec16<T> a, g;
-    a.load(ctx + off + c);
-    g.load(dctx + off + c);
-#pragma unroll
-    for (int e = 0; e < VN; ++e) acc += a.get(e) * g.get(e);
-  }
-  const int bi = t / s, i = t % s;
-  delta[((size_t)bi * hl + hd) * s + i] = acc;
-}
-
-hipError_t launch_attn_delta(int dtype, int T, int hl, int d, int b, int s, const void* ctx, const void* dctx,
-                             float* delta, hipStream_t st) {
-  (void)b;
-  dim3 grid((T * hl + 255) / 256);
-  if (dtype == MLM_BF16)
-    hipLaunchKernelGGL((attn_delta_kernel<bf16>), grid, dim3(256), 0, st, T, hl, d, s, (const bf16*)ctx,
-                       (const bf16*)dctx, delta);
-  else
-    hipLaunchKernelGGL((attn_delta_kernel<float>), grid, dim3(256), 0, st, T, hl, d, s, (const float*)ctx,
-                       (const float*)dctx, delta);
-  return hipGetLastError();
-}
-
 // ------------------------------------------------------------------------------ column sums without a workspace
 // For callers that cannot allocate (code under graph capture, serving loops): the chunk partials of the column sum
 // live in a file-scope device array instead of a caller workspace.  Every GPU holds its own copy of the array at its
