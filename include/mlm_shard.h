@@ -37,11 +37,9 @@
  *     kernel and device, whether its dynamic-LDS attribute has been set; (b) the
  *     address of mlm_colsum_noalloc's static scratch per device; (c) per host thread,
  *     the list that mlm_deferred_sums_begin opens and mlm_deferred_sums_flush closes;
- *     (d) five tuning
+ *     (d) two tuning
  *     overrides that are read from the environment ONCE per process, at the first
- *     bf16 GEMM: MLM_GEMM_V2=0 (register-staged kernel instead of the direct-to-LDS
- *     one), MLM_GEMM_TILE=0|1|2 (tile of the register-staged kernel), MLM_GEMM_WAVES=4|8,
- *     MLM_GEMM_BN=192|256 (tile width where both exist), MLM_GEMM_GROUP=0 (weight
+ *     bf16 GEMM: MLM_GEMM_BN=192|256 (tile width where both exist), MLM_GEMM_GROUP=0 (weight
  *     gradients launched one by one).  They choose between kernels that compute the
  *     same sums in a different order and exist for A/B measurements; unset, the
  *     library chooses by its cost model.  Calls may come from several host threads.

@@ -5,16 +5,9 @@
 namespace mlm {
 
 hipError_t launch_gemm_bf16_dgrad(const GemmArgs& a, hipStream_t st) {
-  if (gemm_use_v2(a)) {
-    switch (a.epi) {
-      case EPI_STORE: return launch_gemm_bf16_v2<true, true, EPI_STORE>(a, a.splitk_ws, st);
-      case EPI_DGELU: return launch_gemm_bf16_v2<true, true, EPI_DGELU>(a, a.splitk_ws, st);
-      default: return hipErrorInvalidValue;
-    }
-  }
   switch (a.epi) {
-    case EPI_STORE: return launch_gemm_bf16_layout<true, true, EPI_STORE>(a, st);
-    case EPI_DGELU: return launch_gemm_bf16_layout<true, true, EPI_DGELU>(a, st);
+    case EPI_STORE: return launch_gemm_bf16_v2<true, true, EPI_STORE>(a, a.splitk_ws, st);
+    case EPI_DGELU: return launch_gemm_bf16_v2<true, true, EPI_DGELU>(a, a.splitk_ws, st);
     default: return hipErrorInvalidValue;
   }
 }

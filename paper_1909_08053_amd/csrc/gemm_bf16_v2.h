@@ -12,12 +12,11 @@
 //     slice are pulled into registers while the slice before it is multiplied, so its stage is re-armed while it is
 //     still being multiplied: three slices are in flight and one is landed, about 3500 MFMA clocks of prefetch
 //     distance, one barrier per slice.
-//   * v_mfma_f32_16x16x32_bf16 in the 8-wave variants: the same peak rate as the 32 x 32 x 16 shape, but a higher
-//     sustained rate on real (normally distributed) operands, where the chip's power limit sets the clock.
-// Requirements: K % 32 == 0 and K >= 64 (the dispatcher falls back to the register-staged kernel otherwise).  k is
-// walked in pairs of 32-deep slices; when K is an odd multiple of 32 the LAST pair starts at K - 64, i.e. it overlaps
-// the pair before it by one slice, and the MFMAs of its first (already counted) slice are skipped: every copy stays
-// inside the operand and the instruction stream of the steady state is unchanged.
+//   * v_mfma_f32_16x16x32_bf16: the same peak rate as the 32 x 32 x 16 shape, but a higher sustained rate on real
+//     (normally distributed) operands, where the chip's power limit sets the clock: 2.04 PFLOP/s against 1.77 with the
+//     matrix pipe alone, 1.60 against 1.45 with this loop's fragment reads and copies around it.
+// k is walked in pairs of 32-deep slices.  K need not be a multiple of anything: the 16-byte units of the last pair that
+// lie past K are fetched from sixteen zero bytes (one compare and select per copy, compiled in for such K only).
 //
 // Tail split: when the tile count does not fill a whole number of rounds of the 256 CUs, the tiles of the last
 // partial round are split along k into f pieces (f = floor(256 / remainder)); each piece writes an fp32 partial
@@ -31,26 +30,18 @@
 
 namespace mlm {
 
-// MFMA shape of the main loop: 16 (v_mfma_f32_16x16x32_bf16) unless the library is built with
-// -DMLM_GEMM_MFMA_SHAPE=32 (v_mfma_f32_32x32x16_bf16, the earlier loop, kept for comparison builds).
-#ifndef MLM_GEMM_MFMA_SHAPE
-#define MLM_GEMM_MFMA_SHAPE 16
-#endif
-constexpr int V2_MF = MLM_GEMM_MFMA_SHAPE;
-// The 4-wave variant (128 x 128 per wave, 256 accumulator registers) keeps the 32 x 32 x 16 shape: with 64 separate
-// 16 x 16 accumulators the compiler spills over a thousand registers, and the measured gain of the shape is half as
-// large there (fewer fragment reads per MFMA to begin with).
-template <int NW> constexpr int v2_mf() { return NW == 4 ? 32 : V2_MF; }
 constexpr int V2_B = 256;                   // block tile edge (M and N)
 constexpr int V2_BK = 32;                   // k per stage
 constexpr int V2_STAGES = 4;
+constexpr int V2_NW = 8;                    // waves per workgroup, two per SIMD
+template <int BN> constexpr int v2_waves_m() { return BN == V2_B ? 2 : 4; }
+inline int v2_slices(int K) { return 2 * ((K + 2 * V2_BK - 1) / (2 * V2_BK)); }   // 32-deep slices walked: whole pairs
 constexpr int V2_OP_BYTES = V2_B * V2_BK * 2;          // 16 KB per operand per stage
 constexpr int V2_REGION_BYTES = V2_STAGES * V2_OP_BYTES;   // 64 KB ring per operand: A's ring, then B's ring
 constexpr size_t V2_LDS_BYTES = (size_t)2 * V2_REGION_BYTES;          // 128 KB
-constexpr int V2_MAX_CUS = 256;              // bound of the tail-split workspace: at most this many fp32 partial tiles
-// Compute units of the current device (tiles that run concurrently: one 128-KB workgroup per unit), capped at
-// V2_MAX_CUS; asked from the runtime once per device.
-int gemm_cu_count();
+
+// What a copy reads for the 16-byte units past K.
+static __device__ const uint4 v2_zero16 = {0u, 0u, 0u, 0u};
 
 // Bank swizzle of the [k][row] tile layout (XOR on the 16-byte unit index of a 512-byte k-row).  A transposing read
 // is served in two passes of 32 lanes; a pass reads 64 contiguous bytes (four units) of each of four consecutive
@@ -59,7 +50,7 @@ int gemm_cu_count();
 // LDS bank-conflict counter: an earlier swizzle that only spread the rows over 128 bytes showed 50 % conflict cycles).
 // The 16 x 16 x 32 MFMA's operand puts k = 8 g .. 8 g + 7 into lane group g = lane / 16, so a pass of its transposing
 // read covers k-rows 0 .. 3 (or 4 .. 7) AND 8 .. 11 (12 .. 15), 32 bytes of each: bit 3 of k moves a row by another 32
-// bytes.  With this term both MFMA shapes read conflict-free (simulated for both).
+// bytes.  With this term the reads are conflict-free (simulated).
 __device__ __forceinline__ int v2_mn_swizzle(int k) { return ((k & 3) << 2) | (((k >> 3) & 1) << 1); }
 
 // LDS position (16-byte unit inside the k-row) of logical row-chunk u of k-row k, and its inverse, for a [k][ROWS]
@@ -91,7 +82,9 @@ __device__ __forceinline__ int v2_kc_swizzle(int row) { return (((row >> 1) & 1)
 //    slice by slice, costs twice the cache-line requests and was measured 40 % slower on the copy side).  A pair
 //    takes 2 QPW copies per wave and is fetched once every two slices.
 //  * operand contiguous along m / n (MN): a slice is [32 k][256 rows] = 512 bytes per k, QPW copies per slice.
-template <bool KC, int NP_, int ROWS = V2_B>
+// RAG (K is no multiple of 64): units past K are read from v2_zero16.  A template parameter: the compare and select per
+// copy cost 2 % of a large GEMM.
+template <bool KC, int NP_, bool RAG, int ROWS = V2_B>
 struct V2Src {
   static constexpr int NP = NP_;       // KC: 1-KB copies per wave and PAIR (rows / (8 waves)); MN: per wave and slice
   // MN: a slice is ROWS / 16 one-KB copies; where that is no multiple of the wave count (192 rows: 12 copies, 8
@@ -99,14 +92,17 @@ struct V2Src {
   // copy count -- and with it the vmcnt bookkeeping -- uniform)
   static constexpr int LAST = KC ? (1 << 20) : ROWS / 16 - 1;
   const bf16* p[NP];
+  int kofs[NP];    // k of this lane's unit inside the pair (KC) / slice (MN)
+  int kleft;       // K - k_begin: units with k >= kleft are zeros
   size_t step;     // elements to advance per 32-deep k-slice
-  __device__ __forceinline__ void init(const bf16* P, int ld, int row0, int nrows, int k_begin, int wave, int lane) {
+  __device__ __forceinline__ void init(const bf16* P, int ld, int row0, int nrows, int k_begin, int K, int wave, int lane) {
+    kleft = K - k_begin;
     if (KC) {
 #pragma unroll
       for (int q = 0; q < NP; ++q) {
         const int row = (wave * NP + q) * 8 + (lane >> 3);
-        const int u = (lane & 7) ^ v2_kc_swizzle(row);
-        p[q] = P + (size_t)min(row0 + row, nrows - 1) * ld + k_begin + u * 8;
+        kofs[q] = ((lane & 7) ^ v2_kc_swizzle(row)) * 8;
+        p[q] = P + (size_t)min(row0 + row, nrows - 1) * ld + k_begin + kofs[q];
       }
       step = V2_BK;
     } else {
@@ -116,6 +112,7 @@ struct V2Src {
         const int g = 64 * min(wave * NP + q, LAST) + lane;      // linear 16-byte unit of the slice buffer
         const int k = g / (ROWS / 8);
         const int u = v2_mn_chunk<ROWS>(g % (ROWS / 8), k);
+        kofs[q] = k;
         p[q] = P + (size_t)(k_begin + k) * ld + min(row0 + u * 8, nrows - 8);
       }
       step = (size_t)V2_BK * ld;
@@ -124,39 +121,15 @@ struct V2Src {
   // dst: LDS byte address of the pair's (KC) / slice's (MN) buffer; ks: first 32-deep k-slice of the pair / the slice,
   // relative to k_begin; wave_u: wave index as a uniform (SGPR) value
   __device__ __forceinline__ void issue_one(uint32_t dst, int wave_u, int ks, int q) const {
-    dma16(p[q] + (ptrdiff_t)ks * (ptrdiff_t)step, dst + min(wave_u * NP + q, LAST) * 1024);
+    const bf16* src = p[q] + (ptrdiff_t)ks * (ptrdiff_t)step;
+    if (RAG) src = ks * V2_BK + kofs[q] < kleft ? src : reinterpret_cast<const bf16*>(&v2_zero16);
+    dma16(src, dst + min(wave_u * NP + q, LAST) * 1024);
   }
   __device__ __forceinline__ void issue(uint32_t dst, int wave_u, int ks) const {
 #pragma unroll
     for (int q = 0; q < NP; ++q) issue_one(dst, wave_u, ks, q);
   }
 };
-
-// Operand registers (8 consecutive k of one row/column per lane) for the 32-row MFMA tile starting at row `r0`,
-// k-step ks (0 / 1) of the slice in ring stage `stage` of the operand ring at `ring`.
-template <bool KC, int ROWS = V2_B>           // ROWS: rows of the operand's tile
-__device__ __forceinline__ bf16x8 v2_frag(const unsigned char* ring, int stage, int r0, int ks, int lane) {
-  constexpr int OPB = ROWS * V2_BK * 2;       // bytes of one k-slice of the operand
-  const int l32 = lane & 31, lh = lane >> 5;
-  if (KC) {
-    const int row = r0 + l32;
-    const int u = (stage & 1) * 4 + ks * 2 + lh;
-    return *reinterpret_cast<const bf16x8*>(ring + (stage >> 1) * (2 * OPB) + row * 128 +
-                                            ((u ^ v2_kc_swizzle(row)) << 4));
-  } else {
-    const unsigned char* op_base = ring + stage * OPB;
-    const int g = lane >> 4, i16 = lane & 15;
-    const int u = (r0 >> 3) + 2 * (g & 1) + ((i16 & 3) >> 1);
-    v4s_t h[2];
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int k = ks * 16 + 8 * (g >> 1) + 4 * r + (i16 >> 2);
-      h[r] = lds_read_tr16(op_base + k * (ROWS * 2) + (v2_mn_pos<ROWS>(u, k) * 16) + (i16 & 1) * 8);
-    }
-    const v8s_t v = __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_bit_cast(bf16x8, v);
-  }
-}
 
 // Operand registers of the 16 x 16 x 32 MFMA for the 16-row tile starting at row `r0`: lane l holds k = 8 (l / 16) ..
 // + 7 (the whole 32-deep slice is one MFMA deep) of row r0 + l % 16.
@@ -197,13 +170,13 @@ struct V2Plan {
 // in 0.88 of the time, so it wins where it saves a round or fills one and loses on long-k shapes whose last round
 // can be split instead.  The fix-up kernel reads the pieces mostly out of the last-level cache.
 inline double v2_tile_fixed(int bn) { return bn == V2_B ? 9.2 : 8.0; }
-inline double v2_slice_cost(int bn, bool /*b_mn*/) { return bn == V2_B ? 0.67 : 0.59; }
+inline double v2_slice_cost(int bn) { return bn == V2_B ? 0.67 : 0.59; }
 inline double v2_fixup_cost(double traffic_us) { return 3.0 + 0.6 * traffic_us; }
 
 // Decide whether, and how far, to split the last partial round along k.  Cost model in microseconds: a tile costs
 // its fixed part + the per-slice cost of its k-slices; the pieces write fp32 partial tiles at ~5 TB/s and the fix-up
 // kernel reads them back.
-inline V2Plan v2_plan(int M, int N, int K, bool allow_split, int bn = V2_B, bool b_mn = false) {
+inline V2Plan v2_plan(int M, int N, int K, bool allow_split, int bn = V2_B) {
   const int V2_CUS = gemm_cu_count();
   V2Plan p;
   p.bn = bn;
@@ -211,8 +184,8 @@ inline V2Plan v2_plan(int M, int N, int K, bool allow_split, int bn = V2_B, bool
   p.tiles_n = (N + bn - 1) / bn;
   const int tiles = p.tiles_m * p.tiles_n;
   const int rem = tiles % V2_CUS;
-  const int nk = 2 * ((K / V2_BK + 1) / 2);           // slices walked: pairs of 32 (an odd count repeats one slice)
-  const double fixed = v2_tile_fixed(bn), per_slice = v2_slice_cost(bn, b_mn);
+  const int nk = v2_slices(K);
+  const double fixed = v2_tile_fixed(bn), per_slice = v2_slice_cost(bn);
   int split = 1;
   double tail = rem ? fixed + per_slice * nk : 0.0;   // unsplit tail round
   if (allow_split && rem != 0 && rem * 2 <= V2_CUS) {
@@ -232,22 +205,17 @@ inline V2Plan v2_plan(int M, int N, int K, bool allow_split, int bn = V2_B, bool
   return p;
 }
 
-// NW = waves per workgroup: 4 (2 x 2 waves of 128 x 128) or 8 (2 x 4 waves of 128 x 64, two waves per SIMD).
-// One work item (pid) of one GEMM: the body of the kernels below.
-// BN = 256: 2 x (NW / 2) waves of 128 x (512 / NW).  BN = 192 (8 waves, k-contiguous B only): 4 x 2 waves of 64 x 96 --
-// a tile count of 32 x (N / 192) fills the 256 CUs where N / 256 column tiles leave a quarter of them idle
-// (N = 1536: 256 tiles instead of 192) or a half-empty second round (N = 3072: 512 instead of 384).
-// MF = MFMA shape: 16 (v_mfma_f32_16x16x32_bf16, the default) or 32 (v_mfma_f32_32x32x16_bf16, kept for comparison).
-// Same wave tiles, same LDS traffic and the same peak rate, but on normally distributed operands the 16 x 16 x 32
-// shape sustains 2.04 PFLOP/s against 1.77 with the matrix pipe alone, 1.60 against 1.45 with this loop's fragment
-// reads and copies around it (256 x 256 tile, 8 waves; measured with a stand-alone loop of the same structure).
-template <bool A_KC, bool B_KC, int EPI, int NW, int BN = V2_B, int MF = 16>
+// One work item (pid) of one GEMM: the body of the kernels below.  8 waves, two per SIMD.
+// BN = 256: 2 x 4 waves of 128 x 64.  BN = 192: 4 x 2 waves of 64 x 96 -- a tile count of 32 x (N / 192) fills the 256 CUs
+// where N / 256 column tiles leave a quarter of them idle (N = 1536: 256 tiles instead of 192) or a half-empty second
+// round (N = 3072: 512 instead of 384).
+template <bool A_KC, bool B_KC, int EPI, int BN, bool RAG>
 __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Plan& plan, float* splitk_ws, int pid,
                                                   unsigned char* lds_raw) {
-  static_assert(BN == V2_B || (BN == 192 && NW == 8), "narrow tile: 8 waves");
-  static_assert(MF == 16 || MF == 32, "MFMA shape");
-  constexpr int WAVES_M = BN == V2_B ? 2 : 4, WAVES_N = NW / WAVES_M;
-  constexpr int WM = V2_B / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
+  static_assert(BN == V2_B || BN == 192, "tile widths");
+  constexpr int NW = V2_NW;
+  constexpr int WAVES_M = v2_waves_m<BN>(), WAVES_N = NW / WAVES_M;
+  constexpr int WM = V2_B / WAVES_M, WN = BN / WAVES_N;
   constexpr int OPB_B = BN * V2_BK * 2;                        // bytes of one k-slice of the B operand
   // 1-KB copies per wave: per pair of slices for a k-contiguous operand, per slice otherwise
   constexpr int NPA = A_KC ? V2_B / (8 * NW) : 16 / NW, NPB = B_KC ? BN / (8 * NW) : (BN / 16 + NW - 1) / NW;
@@ -268,22 +236,15 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
   // share an XCD (congruent mod 8) share tile rows, so each XCD's L2 sees few distinct operand panels.
   const int tile_m = vt % plan.tiles_m, tile_n = vt / plan.tiles_m;
   const int m0 = tile_m * V2_B, n0 = tile_n * BN;
-  const int ns_total = a.K / V2_BK;                  // 32-deep k-slices of the problem
-  const int np_total = (ns_total + 1) / 2;           // k is walked in pairs of slices
+  const int np_total = (a.K + 2 * V2_BK - 1) / (2 * V2_BK);   // pairs of 32-deep slices of the problem
   const int kt_begin = 2 * (int)((long)np_total * piece / npieces);
   const int kt_end = 2 * (int)((long)np_total * (piece + 1) / npieces);
   const int nk = kt_end - kt_begin;                  // even, >= 2
-  // Odd slice count: the last pair of the problem starts one slice early (at K - 64) and its first slice, which the
-  // pair before it has already multiplied, is skipped.  shift = 1 for the piece that holds that pair.
-  const int shift = (kt_end > ns_total) ? 1 : 0;
-  // first k-slice (relative to kt_begin) of walked slice kt / of walked pair pr
-  auto slice_of = [&](int kt) { return kt - (kt >= nk - 2 ? shift : 0); };
-  auto pair_of = [&](int pr) { return 2 * pr - (pr == nk / 2 - 1 ? shift : 0); };
 
-  V2Src<A_KC, NPA> sa;
-  V2Src<B_KC, NPB, BN> sb;
-  sa.init((const bf16*)a.A, a.lda, m0, a.M, kt_begin * V2_BK, wave, lane);
-  sb.init((const bf16*)a.B, a.ldb, n0, a.N, kt_begin * V2_BK, wave, lane);
+  V2Src<A_KC, NPA, RAG> sa;
+  V2Src<B_KC, NPB, RAG, BN> sb;
+  sa.init((const bf16*)a.A, a.lda, m0, a.M, kt_begin * V2_BK, a.K, wave, lane);
+  sb.init((const bf16*)a.B, a.ldb, n0, a.N, kt_begin * V2_BK, a.K, wave, lane);
 
   const uint32_t ldsA = lds_offset_of(lds_raw), ldsB = ldsA + V2_REGION_BYTES;
   const unsigned char* ringA = lds_raw;
@@ -296,16 +257,15 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
   const int last_pair = nk / 2 - 1, last_slice = nk - 1;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    if (A_KC) sa.issue(ldsA + h * 2 * V2_OP_BYTES, wave_u, pair_of(min(h, last_pair)));
-    if (B_KC) sb.issue(ldsB + h * 2 * OPB_B, wave_u, pair_of(min(h, last_pair)));
+    if (A_KC) sa.issue(ldsA + h * 2 * V2_OP_BYTES, wave_u, 2 * min(h, last_pair));
+    if (B_KC) sb.issue(ldsB + h * 2 * OPB_B, wave_u, 2 * min(h, last_pair));
 #pragma unroll
     for (int s = 2 * h; s < 2 * h + 2; ++s) {
-      if (!A_KC) sa.issue(ldsA + s * V2_OP_BYTES, wave_u, slice_of(min(s, last_slice)));
-      if (!B_KC) sb.issue(ldsB + s * OPB_B, wave_u, slice_of(min(s, last_slice)));
+      if (!A_KC) sa.issue(ldsA + s * V2_OP_BYTES, wave_u, min(s, last_slice));
+      if (!B_KC) sb.issue(ldsB + s * OPB_B, wave_u, min(s, last_slice));
     }
   }
-  // The operand registers of what is multiplied next are read from LDS while the matrix cores work (32 x 32 x 16
-  // shape: by half-slices of 16 k; 16 x 16 x 32 shape: by whole slices, see there).  The slice hand-over sits inside
+  // The operand registers of what is multiplied next are read from LDS while the matrix cores work.  The slice hand-over sits inside
   // slice kt: wait for the copies of slice kt+1, barrier, then re-arm what slice kt leaves behind (its operands are all
   // in registers by then): an MN operand's stage gets slice kt+4; a KC operand's pair-stage is free after the ODD
   // slice of the pair and then gets the pair two ahead.  Copies are ISSUED ONE AT A TIME BETWEEN MFMAs: back-to-back 1-KB copies fill
@@ -320,75 +280,74 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
   constexpr int EV = C_SLICE, OD = C_PAIR + C_SLICE;
   constexpr int W_INIT = 3 * C_SLICE + C_PAIR, W_EVEN = EV + OD, W_ODD = NKC > 0 ? 2 * EV : EV + OD;
   (void)NMN;
-  if constexpr (MF == 32) {
-    floatx16 acc[TN][TM];
+  // ---- 16 x 16 x 32 MFMAs: one MFMA spans the slice's 32 k, so a wave holds the fragments of ONE slice: NA of A, NB
+  // of B.  MFMA order: A fragment outer, B fragment inner.  A fragment j is replaced by the next slice's behind
+  // its last MFMA (j, NB - 1) and is next used about NMF - NB MFMAs later; the B fragments are double-buffered (the slice's
+  // parity picks the set) and the next slice's are read right after the hand-over.  The hand-over (wait for the
+  // copies of slice kt + 1, barrier) sits after MFMA HO, ahead of the first read of slice kt + 1; the copies that
+  // re-arm slice kt's stage (all of its fragments were in registers before the slice began) follow it, one at a
+  // time between the MFMAs.  Measured on the benchmark step: HO = 0 .. 2 within noise of each other, later
+  // hand-overs slower (HO = 15: +0.5 %); B fragment outer with in-place replacement of both operands (A fragments
+  // then have NA MFMAs between read and use) the same step time, 1 % slower on the logits GEMM.
+  constexpr int NA = WM / 16, NB = WN / 16, NMF = NA * NB;
+  constexpr int HO = 1;
+  static_assert(HO + 1 + NB <= NMF, "the next slice's B fragments are read in this slice");
+  floatx4 acc[NB][NA];
 #pragma unroll
-    for (int i = 0; i < TN; ++i)
+  for (int i = 0; i < NB; ++i)
 #pragma unroll
-      for (int j = 0; j < TM; ++j)
+    for (int j = 0; j < NA; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
+  bf16x8 fa[NA], fb[2][NB];
+  wait_vmcnt<W_INIT>();                  // slice 0 landed
+  __builtin_amdgcn_s_barrier();
+#pragma unroll
+  for (int j = 0; j < NA; ++j) fa[j] = v2_frag16<A_KC>(ringA, 0, wm0 + j * 16, lane);
+#pragma unroll
+  for (int i = 0; i < NB; ++i) fb[0][i] = v2_frag16<B_KC, BN>(ringB, 0, wn0 + i * 16, lane);
 
-    constexpr int NMF = TN * TM;           // MFMAs per half-slice per wave
-    static_assert(NMF > TM + TN, "one fragment read after each MFMA but the first must cover all fragments");
-    bf16x8 fa0[TM], fb0[TN], fa1[TM], fb1[TN];
-    wait_vmcnt<W_INIT>();                  // slice 0 landed
-    __builtin_amdgcn_s_barrier();
+  // one 32-deep slice; PAR = parity of kt (compile time: it fixes the ring stage bits and the copy schedule)
+  auto slice = [&](auto par_c, int kt) {
+    constexpr int PAR = decltype(par_c)::value;
+    const int stage = kt & (V2_STAGES - 1), nstage = (kt + 1) & (V2_STAGES - 1);
+    constexpr int NC = PAR == 0 ? EV : OD;                 // copies to issue in this slice
+    constexpr int NAFTER = NMF - HO - 1;                   // MFMAs after the hand-over
+    const int pair_idx = 2 * min((kt + 3) >> 1, last_pair);   // PAR == 1: the pair two ahead of this slice's pair
+    const uint32_t pair_sel = (uint32_t)(((kt + 3) >> 1) & 1);
+    const uint32_t pair_off_a = pair_sel * (2 * V2_OP_BYTES), pair_off_b = pair_sel * (2 * OPB_B);
+    const int slice_idx = min(kt + V2_STAGES, last_slice);
+    const uint32_t slice_off_a = (uint32_t)stage * V2_OP_BYTES, slice_off_b = (uint32_t)stage * OPB_B;
 #pragma unroll
-    for (int j = 0; j < TM; ++j) fa0[j] = v2_frag<A_KC>(ringA, 0, wm0 + j * 32, 0, lane);
-#pragma unroll
-    for (int i = 0; i < TN; ++i) fb0[i] = v2_frag<B_KC, BN>(ringB, 0, wn0 + i * 32, 0, lane);
-
-    // one 32-deep slice; PAR = parity of kt (compile time: it fixes the ring stage bits and the copy schedule);
-    // live: false for the slice that repeats one multiplied already (odd slice count): everything but its MFMAs runs.
-    // It is a compile-time true in the steady-state loop and a wave-uniform flag (scalar branches) in the peeled last pair.
-    auto slice = [&](auto par_c, auto live, int kt) {
-      constexpr int PAR = decltype(par_c)::value;
-      const int stage = kt & (V2_STAGES - 1);
-      // First half.  Order pinned with scheduling barriers: one MFMA first (its operands were read half a slice ago,
-      // so the loop-top wait is free), then ONE fragment read of the second half's operands after each MFMA.  Spread
-      // like this the reads never queue up in the LDS pipe (all eight waves reach this point together after the
-      // barrier), and the MFMAs in between cover their latency.  (Left alone, the scheduler bunches the reads and
-      // either hoists them above the loop-top wait or sinks them to the barrier; both expose their full latency.)
-#pragma unroll
-      for (int idx = 0; idx < NMF; ++idx) {
-        if (live) acc[idx / TM][idx % TM] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb0[idx / TM], fa0[idx % TM], acc[idx / TM][idx % TM], 0, 0, 0);
-        if (idx >= 1 && idx - 1 < TM + TN) {
-          const int q = idx - 1;
-          __builtin_amdgcn_sched_barrier(0);
-          if (q < TM) fa1[q] = v2_frag<A_KC>(ringA, stage, wm0 + q * 32, 1, lane);
-          else fb1[q - TM] = v2_frag<B_KC, BN>(ringB, stage, wn0 + (q - TM) * 32, 1, lane);
-          __builtin_amdgcn_sched_barrier(0);
-        }
+    for (int idx = 0; idx < NMF; ++idx) {
+      const int i = idx % NB, j = idx / NB;
+      constexpr int CUR = PAR, NXT = 1 - PAR;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[CUR][i], fa[j], acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (idx == HO) {
+        wait_vmcnt<PAR == 0 ? W_EVEN : W_ODD>();   // this wave's copies of slice kt+1 have landed
+        // this wave's LDS reads of slice kt's stage (the last fragments, read at the end of slice kt - 1) have returned ...
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0) only
+        // ... so after this bare s_barrier (no memory fence: a fence would also wait for the copies in flight)
+        // everyone's part of slice kt+1 is in LDS and nobody reads slice kt's stage any more.
+        __builtin_amdgcn_s_barrier();
       }
-      __builtin_amdgcn_sched_barrier(0);     // ... and the MFMAs ahead of the hand-over
-      wait_vmcnt<PAR == 0 ? W_EVEN : W_ODD>();   // this wave's copies of slice kt+1 have landed
-      // this wave's LDS reads of slice kt (second-half operands, issued above) have returned ...
-      __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0) only
-      // ... so after this bare s_barrier (no memory fence: a fence would also wait for the copies in flight)
-      // everyone's part of slice kt+1 is in LDS and nobody reads slice kt's stage any more.
-      __builtin_amdgcn_s_barrier();
-      // Second half: after each MFMA one fragment read of slice kt+1's first-half operands, and the copies that
-      // re-arm the freed stage(s) spread evenly between the MFMAs.
-      const int nstage = (kt + 1) & (V2_STAGES - 1);
-      constexpr int NC = PAR == 0 ? EV : OD;                 // copies to issue in this half
-      const int pair_idx = pair_of(min((kt + 3) >> 1, last_pair));   // PAR == 1: the pair two ahead of this slice's pair
-      const uint32_t pair_sel = (uint32_t)(((kt + 3) >> 1) & 1);
-      const uint32_t pair_off_a = pair_sel * (2 * V2_OP_BYTES), pair_off_b = pair_sel * (2 * OPB_B);
-      const int slice_idx = slice_of(min(kt + V2_STAGES, last_slice));
-      const uint32_t slice_off_a = (uint32_t)stage * V2_OP_BYTES, slice_off_b = (uint32_t)stage * OPB_B;
+      if (idx > HO) {
+        // fragments of slice kt + 1 into the registers that slice kt has finished with
 #pragma unroll
-      for (int idx = 0; idx < NMF; ++idx) {
-        if (live) acc[idx / TM][idx % TM] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb1[idx / TM], fa1[idx % TM], acc[idx / TM][idx % TM], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        if (idx < TM + TN) {
-          const int q = idx;
-          if (q < TM) fa0[q] = v2_frag<A_KC>(ringA, nstage, wm0 + q * 32, 0, lane);
-          else fb0[q - TM] = v2_frag<B_KC, BN>(ringB, nstage, wn0 + (q - TM) * 32, 0, lane);
+        for (int q = 0; q < NB; ++q)
+          if (idx == HO + 1 + q) fb[NXT][q] = v2_frag16<B_KC, BN>(ringB, nstage, wn0 + q * 16, lane);
+#pragma unroll
+        for (int q = 0; q < NA; ++q) {
+          // one MFMA after the fragment's last one (q, NB - 1) -- directly behind it the read needs wait states, the
+          // MFMA still reads the registers -- but inside the slice and not before the hand-over
+          const int last = q * NB + NB < NMF - 1 ? q * NB + NB : NMF - 1;
+          const int at = last > HO ? last : HO + 1;
+          if (idx == at) fa[q] = v2_frag16<A_KC>(ringA, nstage, wm0 + q * 16, lane);
         }
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-          if ((c * NMF) / (NC > 0 ? NC : 1) != idx) continue;   // copy c goes after MFMA (c NMF) / NC
+          if (HO + 1 + (c * NAFTER) / (NC > 0 ? NC : 1) != idx) continue;   // copy c goes after MFMA HO + 1 + (c NAFTER) / NC
           // order: A's pair, B's pair (odd slices only), then A's slice, B's slice
           int r = c;
           constexpr int KA = (PAR == 1 && A_KC) ? NPA : 0, KB = (PAR == 1 && B_KC) ? NPB : 0;
@@ -401,158 +360,42 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
           r -= MA;
           sb.issue_one(ldsB + slice_off_b, wave_u, slice_idx, r);
         }
-        __builtin_amdgcn_sched_barrier(0);
       }
-    };
-    typedef std::integral_constant<int, 0> c0_t;
-    typedef std::integral_constant<int, 1> c1_t;
-    for (int kt = 0; kt < nk - 2; kt += 2) {
-      slice(c0_t{}, std::true_type{}, kt);
-      slice(c1_t{}, std::true_type{}, kt + 1);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    slice(c0_t{}, shift == 0, nk - 2);                  // odd slice count: this one repeats slice nk - 3, copies only
-    slice(c1_t{}, std::true_type{}, nk - 1);
-    // The ring is kept full to the end, so copies of the (clamped) last slice are still in flight here.  They were
-    // issued from inline assembly, which the compiler's wait-count tracking does not see: wait for them explicitly
-    // before the epilogue reuses the ring's memory for its staging strips.
-    wait_vmcnt<0>();
-    __syncthreads();
-
-    if (npieces > 1) {
-      // fp32 partial tile: piece-major [tail tile][piece][256][BN]
-      const int l32 = lane & 31, lh = lane >> 5;
-      float* dst = splitk_ws + ((size_t)(vt - plan.full_tiles) * plan.split + piece) * (V2_B * BN);
-#pragma unroll
-      for (int j = 0; j < TM; ++j)
-#pragma unroll
-        for (int i = 0; i < TN; ++i)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            float4 v = make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
-            *reinterpret_cast<float4*>(dst + (wm0 + j * 32 + l32) * BN + wn0 + i * 32 + 8 * g + 4 * lh) = v;
-          }
-      return;
-    }
-    gemm_epilogue<V2_B, BN, WAVES_M, WAVES_N, EPI>(a, acc, lds_raw, m0, n0, tile_n);
-  } else {
-    // ---- 16 x 16 x 32 MFMAs: one MFMA spans the slice's 32 k, so a wave holds the fragments of ONE slice: NA of A, NB
-    // of B.  MFMA order: A fragment outer, B fragment inner.  A fragment j is replaced by the next slice's behind
-    // its last MFMA (j, NB - 1) and is next used about NMF - NB MFMAs later; the B fragments are double-buffered (the slice's
-    // parity picks the set) and the next slice's are read right after the hand-over.  The hand-over (wait for the
-    // copies of slice kt + 1, barrier) sits after MFMA HO, ahead of the first read of slice kt + 1; the copies that
-    // re-arm slice kt's stage (all of its fragments were in registers before the slice began) follow it, one at a
-    // time between the MFMAs.  Measured on the benchmark step: HO = 0 .. 2 within noise of each other, later
-    // hand-overs slower (HO = 15: +0.5 %); B fragment outer with in-place replacement of both operands (A fragments
-    // then have NA MFMAs between read and use) the same step time, 1 % slower on the logits GEMM.
-    constexpr int NA = WM / 16, NB = WN / 16, NMF = NA * NB;
-    constexpr int HO = 1;
-    static_assert(HO + 1 + NB <= NMF, "the next slice's B fragments are read in this slice");
-    floatx4 acc[NB][NA];
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-      for (int j = 0; j < NA; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
-    bf16x8 fa[NA], fb[2][NB];
-    wait_vmcnt<W_INIT>();                  // slice 0 landed
-    __builtin_amdgcn_s_barrier();
-#pragma unroll
-    for (int j = 0; j < NA; ++j) fa[j] = v2_frag16<A_KC>(ringA, 0, wm0 + j * 16, lane);
-#pragma unroll
-    for (int i = 0; i < NB; ++i) fb[0][i] = v2_frag16<B_KC, BN>(ringB, 0, wn0 + i * 16, lane);
-
-    // one 32-deep slice; PAR = parity of kt (compile time: it fixes the ring stage bits and the copy schedule);
-    // live: false for the slice that repeats one multiplied already (odd slice count): everything but its MFMAs runs.
-    auto slice = [&](auto par_c, auto live, int kt) {
-      constexpr int PAR = decltype(par_c)::value;
-      const int stage = kt & (V2_STAGES - 1), nstage = (kt + 1) & (V2_STAGES - 1);
-      constexpr int NC = PAR == 0 ? EV : OD;                 // copies to issue in this slice
-      constexpr int NAFTER = NMF - HO - 1;                   // MFMAs after the hand-over
-      const int pair_idx = pair_of(min((kt + 3) >> 1, last_pair));   // PAR == 1: the pair two ahead of this slice's pair
-      const uint32_t pair_sel = (uint32_t)(((kt + 3) >> 1) & 1);
-      const uint32_t pair_off_a = pair_sel * (2 * V2_OP_BYTES), pair_off_b = pair_sel * (2 * OPB_B);
-      const int slice_idx = slice_of(min(kt + V2_STAGES, last_slice));
-      const uint32_t slice_off_a = (uint32_t)stage * V2_OP_BYTES, slice_off_b = (uint32_t)stage * OPB_B;
-#pragma unroll
-      for (int idx = 0; idx < NMF; ++idx) {
-        const int i = idx % NB, j = idx / NB;
-        constexpr int CUR = PAR, NXT = 1 - PAR;
-        if (live) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[CUR][i], fa[j], acc[i][j], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        if (idx == HO) {
-          wait_vmcnt<PAR == 0 ? W_EVEN : W_ODD>();   // this wave's copies of slice kt+1 have landed
-          // this wave's LDS reads of slice kt's stage (the last fragments, read at the end of slice kt - 1) have returned ...
-          __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0) only
-          // ... so after this bare s_barrier (no memory fence: a fence would also wait for the copies in flight)
-          // everyone's part of slice kt+1 is in LDS and nobody reads slice kt's stage any more.
-          __builtin_amdgcn_s_barrier();
-        }
-        if (idx > HO) {
-          // fragments of slice kt + 1 into the registers that slice kt has finished with
-#pragma unroll
-          for (int q = 0; q < NB; ++q)
-            if (idx == HO + 1 + q) fb[NXT][q] = v2_frag16<B_KC, BN>(ringB, nstage, wn0 + q * 16, lane);
-#pragma unroll
-          for (int q = 0; q < NA; ++q) {
-            // one MFMA after the fragment's last one (q, NB - 1) -- directly behind it the read needs wait states, the
-            // MFMA still reads the registers -- but inside the slice and not before the hand-over
-            const int last = q * NB + NB < NMF - 1 ? q * NB + NB : NMF - 1;
-            const int at = last > HO ? last : HO + 1;
-            if (idx == at) fa[q] = v2_frag16<A_KC>(ringA, nstage, wm0 + q * 16, lane);
-          }
-#pragma unroll
-          for (int c = 0; c < NC; ++c) {
-            if (HO + 1 + (c * NAFTER) / (NC > 0 ? NC : 1) != idx) continue;   // copy c goes after MFMA HO + 1 + (c NAFTER) / NC
-            // order: A's pair, B's pair (odd slices only), then A's slice, B's slice
-            int r = c;
-            constexpr int KA = (PAR == 1 && A_KC) ? NPA : 0, KB = (PAR == 1 && B_KC) ? NPB : 0;
-            constexpr int MA = A_KC ? 0 : NPA;
-            if (r < KA) { sa.issue_one(ldsA + pair_off_a, wave_u, pair_idx, r); continue; }
-            r -= KA;
-            if (r < KB) { sb.issue_one(ldsB + pair_off_b, wave_u, pair_idx, r); continue; }
-            r -= KB;
-            if (r < MA) { sa.issue_one(ldsA + slice_off_a, wave_u, slice_idx, r); continue; }
-            r -= MA;
-            sb.issue_one(ldsB + slice_off_b, wave_u, slice_idx, r);
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    };
-    typedef std::integral_constant<int, 0> c0_t;
-    typedef std::integral_constant<int, 1> c1_t;
-    for (int kt = 0; kt < nk - 2; kt += 2) {
-      slice(c0_t{}, std::true_type{}, kt);
-      slice(c1_t{}, std::true_type{}, kt + 1);
-    }
-    slice(c0_t{}, shift == 0, nk - 2);                  // odd slice count: this one repeats slice nk - 3, copies only
-    slice(c1_t{}, std::true_type{}, nk - 1);
-    // copies of the (clamped) last slices are still in flight and target the ring the epilogue reuses
-    wait_vmcnt<0>();
-    __syncthreads();
-
-    if (npieces > 1) {
-      // fp32 partial tile: piece-major [tail tile][piece][256][BN]
-      const int l16 = lane & 15, lg = lane >> 4;
-      float* dst = splitk_ws + ((size_t)(vt - plan.full_tiles) * plan.split + piece) * (V2_B * BN);
-#pragma unroll
-      for (int j = 0; j < NA; ++j)
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-          const float4 v = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-          *reinterpret_cast<float4*>(dst + (wm0 + j * 16 + l16) * BN + wn0 + i * 16 + 4 * lg) = v;
-        }
-      return;
-    }
-    gemm_epilogue<V2_B, BN, WAVES_M, WAVES_N, EPI>(a, acc, lds_raw, m0, n0, tile_n);
+  };
+  typedef std::integral_constant<int, 0> c0_t;
+  typedef std::integral_constant<int, 1> c1_t;
+  // (no slice is peeled off: with a second copy of the two bodies the register allocator rotates accumulators through the
+  // fragments' registers, and the loop then holds 7-16 wait states for the fragment reads that overwrite them)
+  for (int kt = 0; kt < nk; kt += 2) {
+    slice(c0_t{}, kt);
+    slice(c1_t{}, kt + 1);
   }
+  // copies of the (clamped) last slices are still in flight and target the ring the epilogue reuses
+  wait_vmcnt<0>();
+  __syncthreads();
+
+  if (npieces > 1) {
+    // fp32 partial tile: piece-major [tail tile][piece][256][BN]
+    const int l16 = lane & 15, lg = lane >> 4;
+    float* dst = splitk_ws + ((size_t)(vt - plan.full_tiles) * plan.split + piece) * (V2_B * BN);
+#pragma unroll
+    for (int j = 0; j < NA; ++j)
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const float4 v = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+        *reinterpret_cast<float4*>(dst + (wm0 + j * 16 + l16) * BN + wn0 + i * 16 + 4 * lg) = v;
+      }
+    return;
+  }
+  gemm_epilogue<V2_B, BN, WAVES_M, WAVES_N, EPI>(a, acc, lds_raw, m0, n0, tile_n);
 }
 
-template <bool A_KC, bool B_KC, int EPI, int NW, int BN = V2_B>
-__global__ __launch_bounds__(NW * 64) void gemm_bf16_v2_kernel(GemmArgs a, V2Plan plan, float* splitk_ws) {
+template <bool A_KC, bool B_KC, int EPI, int BN, bool RAG>
+__global__ __launch_bounds__(V2_NW * 64) void gemm_bf16_v2_kernel(GemmArgs a, V2Plan plan, float* splitk_ws) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  gemm_v2_work_item<A_KC, B_KC, EPI, NW, BN, v2_mf<NW>()>(a, plan, splitk_ws, blockIdx.x, lds_raw);
+  gemm_v2_work_item<A_KC, B_KC, EPI, BN, RAG>(a, plan, splitk_ws, blockIdx.x, lds_raw);
 }
 
 // Several independent GEMMs of one operand layout in ONE launch (plain-store epilogue, no k-split): the tiles of
@@ -567,8 +410,8 @@ struct GemmGroup {
   V2Plan plan[kMaxGroup];
 };
 
-template <bool A_KC, bool B_KC, int NW>
-__global__ __launch_bounds__(NW * 64) void gemm_bf16_v2_group_kernel(GemmGroup g) {
+template <bool A_KC, bool B_KC, bool RAG>
+__global__ __launch_bounds__(V2_NW * 64) void gemm_bf16_v2_group_kernel(GemmGroup g) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   const int pid = blockIdx.x;
   // the problem index is uniform over the workgroup: select its arguments with scalar compares
@@ -581,7 +424,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_v2_group_kernel(GemmGroup g
 #pragma unroll
   for (int i = 1; i < kMaxGroup; ++i)
     if (q == i) { a = g.args[i]; plan = g.plan[i]; first = g.tile_begin[i]; }
-  gemm_v2_work_item<A_KC, B_KC, EPI_STORE, NW, V2_B, v2_mf<NW>()>(a, plan, nullptr, pid - first, lds_raw);
+  gemm_v2_work_item<A_KC, B_KC, EPI_STORE, V2_B, RAG>(a, plan, nullptr, pid - first, lds_raw);
 }
 
 // Tail tiles: sum the k-pieces in piece order (deterministic) and apply the epilogue to the fp32 sums.  A wave owns
@@ -682,23 +525,19 @@ __global__ __launch_bounds__(256) void gemm_v2_fixup_kernel(GemmArgs a, V2Plan p
   }
 }
 
-inline size_t v2_splitk_ws_bytes() { return (size_t)V2_MAX_CUS * V2_B * V2_B * sizeof(float); }   // 64 MB upper bound
-
-int gemm_v2_waves(bool a_kc, bool b_kc);   // 4 or 8 waves per workgroup for this operand layout
-
-template <bool A_KC, bool B_KC, int EPI, int NW, int BN = V2_B>
-hipError_t launch_gemm_bf16_v2_nw(const GemmArgs& a, float* splitk_ws, hipStream_t st) {
-  auto kern = gemm_bf16_v2_kernel<A_KC, B_KC, EPI, NW, BN>;
-  // the ring (128 KB) or, with 8 waves, the epilogue's staging strips (2 per wave) + reduction area, whichever is larger
-  constexpr int WAVES_M = BN == V2_B ? 2 : 4;
-  constexpr size_t kEpi = GemmTile<V2_B, BN, WAVES_M, NW / WAVES_M>::LDS_EPI;
+template <bool A_KC, bool B_KC, int EPI, int BN, bool RAG>
+hipError_t launch_gemm_bf16_v2_bn(const GemmArgs& a, float* splitk_ws, hipStream_t st) {
+  auto kern = gemm_bf16_v2_kernel<A_KC, B_KC, EPI, BN, RAG>;
+  // the ring (128 KB) or the epilogue's staging strips (2 per wave) + reduction area, whichever is larger
+  constexpr int WAVES_M = v2_waves_m<BN>();
+  constexpr size_t kEpi = GemmTile<V2_B, BN, WAVES_M, V2_NW / WAVES_M>::LDS_EPI;
   constexpr size_t kLds = V2_LDS_BYTES > kEpi ? V2_LDS_BYTES : kEpi;
   static_assert(kLds <= 160 * 1024, "LDS budget");
   static LdsAttrOnce attr;         // per instantiation and device
   if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
-  const V2Plan plan = v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, BN, !B_KC);
+  const V2Plan plan = v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, BN);
   const int grid = plan.full_tiles + plan.tail_tiles * plan.split;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(NW * 64), kLds, st, a, plan, splitk_ws);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(V2_NW * 64), kLds, st, a, plan, splitk_ws);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (plan.tail_tiles) {
@@ -712,10 +551,10 @@ hipError_t launch_gemm_bf16_v2_nw(const GemmArgs& a, float* splitk_ws, hipStream
 // Tiles (work items without a k-split) of one problem.
 inline int v2_tiles(const GemmArgs& a) { return ((a.M + V2_B - 1) / V2_B) * ((a.N + V2_B - 1) / V2_B); }
 
-template <bool A_KC, bool B_KC, int NW>
-hipError_t launch_gemm_bf16_v2_group_nw(const GemmArgs* probs, int n, hipStream_t st) {
-  auto kern = gemm_bf16_v2_group_kernel<A_KC, B_KC, NW>;
-  constexpr size_t kEpi = GemmTile<V2_B, V2_B, 2, NW / 2>::LDS_EPI;
+template <bool A_KC, bool B_KC, bool RAG>
+hipError_t launch_gemm_bf16_v2_group(const GemmArgs* probs, int n, hipStream_t st) {
+  auto kern = gemm_bf16_v2_group_kernel<A_KC, B_KC, RAG>;
+  constexpr size_t kEpi = GemmTile<V2_B, V2_B, v2_waves_m<V2_B>(), V2_NW / v2_waves_m<V2_B>()>::LDS_EPI;
   constexpr size_t kLds = V2_LDS_BYTES > kEpi ? V2_LDS_BYTES : kEpi;
   static LdsAttrOnce attr;
   if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
@@ -730,28 +569,36 @@ hipError_t launch_gemm_bf16_v2_group_nw(const GemmArgs* probs, int n, hipStream_
     total += g.plan[q].full_tiles;
   }
   for (int q = n; q <= kMaxGroup; ++q) g.tile_begin[q] = total;
-  hipLaunchKernelGGL(kern, dim3(total), dim3(NW * 64), kLds, st, g);
+  hipLaunchKernelGGL(kern, dim3(total), dim3(V2_NW * 64), kLds, st, g);
   return hipGetLastError();
 }
 
 int gemm_v2_forced_bn();                    // MLM_GEMM_BN=192|256 forces a tile width where both exist, else 0
 
+template <bool A_KC, bool B_KC, int EPI, bool RAG>
+hipError_t launch_gemm_bf16_v2_rag(const GemmArgs& a, float* splitk_ws, hipStream_t st) {
+  // both tile widths exist for the input-gradient layout and for the plain / bias + GeLU forward GEMMs: take the one the
+  // cost model prices lower for this shape
+  constexpr bool kHasNarrow = A_KC && (B_KC || EPI == EPI_STORE || EPI == EPI_BIAS_GELU);
+  if constexpr (kHasNarrow) {
+    const int forced = gemm_v2_forced_bn();
+    const bool narrow = forced ? forced == 192
+                               : v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, 192).cost <
+                                     v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, V2_B).cost;
+    if (narrow) return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, 192, RAG>(a, splitk_ws, st);
+  }
+  return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_B, RAG>(a, splitk_ws, st);
+}
+
 template <bool A_KC, bool B_KC, int EPI>
 hipError_t launch_gemm_bf16_v2(const GemmArgs& a, float* splitk_ws, hipStream_t st) {
-  if (gemm_v2_waves(A_KC, B_KC) == 8) {
-    // both tile widths exist for the input-gradient layout and for the plain / bias + GeLU forward GEMMs: take the
-    // one the cost model prices lower for this shape
-    constexpr bool kHasNarrow = A_KC && (B_KC || EPI == EPI_STORE || EPI == EPI_BIAS_GELU);
-    if (kHasNarrow) {
-      const int forced = gemm_v2_forced_bn();
-      const bool narrow = forced ? forced == 192
-                                 : v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, 192, !B_KC).cost <
-                                       v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, V2_B, !B_KC).cost;
-      if (narrow) return launch_gemm_bf16_v2_nw<A_KC, B_KC, EPI, 8, kHasNarrow ? 192 : V2_B>(a, splitk_ws, st);
-    }
-    return launch_gemm_bf16_v2_nw<A_KC, B_KC, EPI, 8>(a, splitk_ws, st);
-  }
-  return launch_gemm_bf16_v2_nw<A_KC, B_KC, EPI, 4>(a, splitk_ws, st);
+  return a.K % (2 * V2_BK) ? launch_gemm_bf16_v2_rag<A_KC, B_KC, EPI, true>(a, splitk_ws, st)
+                           : launch_gemm_bf16_v2_rag<A_KC, B_KC, EPI, false>(a, splitk_ws, st);
 }
+
+// One translation unit per operand layout (keeps compile times parallel).
+hipError_t launch_gemm_bf16_fwd(const GemmArgs& a, hipStream_t st);     // A k-contiguous, B n-contiguous
+hipError_t launch_gemm_bf16_dgrad(const GemmArgs& a, hipStream_t st);   // both k-contiguous
+hipError_t launch_gemm_bf16_wgrad(const GemmArgs& a, hipStream_t st);   // A m-contiguous, B n-contiguous
 
 }  // namespace mlm
