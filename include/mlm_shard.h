@@ -132,7 +132,8 @@ MLM_API int mlm_layernorm_fwd(const mlm_dims* dims, const void* x, const void* g
  *   dx = residual_grad + d(LN)/dx applied to dy      (residual_grad may be NULL = 0)
  *   dgamma = sum_t dy * xhat,  dbeta = sum_t dy       ([H] dtype outputs)
  * dy, x, residual_grad, dx: [T,H] dtype (dx may alias residual_grad or dy).
- * ws: MLM_WS_LAYERNORM_BWD bytes. */
+ * ws: MLM_WS_LAYERNORM_BWD bytes (down to ceil(b s / 32) * 3 H floats are accepted: fewer workgroups
+ * then run, and the column sums are added in another order). */
 MLM_API int mlm_layernorm_bwd(const mlm_dims* dims, const void* dy, const void* x, const void* gamma,
                       const float* mean, const float* rstd, const void* residual_grad,
                       void* dx, void* dgamma, void* dbeta, void* ws, size_t ws_bytes, void* stream);

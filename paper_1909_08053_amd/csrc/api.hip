@@ -57,7 +57,7 @@ size_t ws_bytes_for(const mlm_dims* dm, const Local& L, int which) {
   const size_t sk = dm->dtype == MLM_BF16 ? kSplitKBytes : 0;
   switch (which) {
     case MLM_WS_LAYERNORM_BWD:
-      return align256(((T + kLnBwdRowsPerBlock - 1) / kLnBwdRowsPerBlock) * 3 * (size_t)dm->H * 4);
+      return align256((size_t)ln_bwd_blocks(dm->dtype, L.T, dm->H) * 3 * dm->H * 4);
     case MLM_WS_ATTN_FWD: return sk;
     case MLM_WS_ATTN_BWD:
       return align256(T * L.Hl * L.esz) + align256(T * 3 * L.Hl * L.esz) +
@@ -74,6 +74,11 @@ size_t ws_bytes_for(const mlm_dims* dm, const Local& L, int which) {
     case MLM_WS_VOCAB_CE_BWD: return align256(T * L.Vl * L.esz) + sk;
     default: return 0;
   }
+}
+
+// the smallest workspace a layer-norm backward accepts (the query asks for more where more workgroups help)
+size_t ln_bwd_min_ws(const mlm_dims* dm, const Local& L) {
+  return align256((size_t)ln_bwd_min_blocks(L.T) * 3 * dm->H * 4);
 }
 
 inline int hip_status(hipError_t e) { return e == hipSuccess ? MLM_OK : MLM_E_HIP; }
@@ -174,9 +179,9 @@ MLM_API int mlm_layernorm_bwd(const mlm_dims* dims, const void* dy, const void* 
       (residual_grad && !aligned16(residual_grad)))
     return MLM_E_ALIGN;
   if ((rc = ln_supported(dims))) return rc;
-  if (ws_bytes < ws_bytes_for(dims, L, MLM_WS_LAYERNORM_BWD)) return MLM_E_WORKSPACE;
+  if (ws_bytes < ln_bwd_min_ws(dims, L)) return MLM_E_WORKSPACE;
   return hip_status(launch_layernorm_bwd(dims->dtype, L.T, dims->H, dy, x, gamma, mean, rstd, residual_grad, dx,
-                                         dgamma, dbeta, (float*)ws, (hipStream_t)stream));
+                                         dgamma, dbeta, (float*)ws, ws_bytes, (hipStream_t)stream));
 }
 
 MLM_API int mlm_combine(const mlm_dims* dims, const void* const* partials, int32_t n_partials, const void* bias,
@@ -276,10 +281,10 @@ static int combine_layernorm_bwd_impl(const mlm_dims* dims, const void* const* p
       (residual_grad && !aligned16(residual_grad)) || (dy_out && !aligned16(dy_out)))
     return MLM_E_ALIGN;
   if ((rc = ln_supported(dims))) return rc;
-  if (ws_bytes < ws_bytes_for(dims, L, MLM_WS_LAYERNORM_BWD)) return MLM_E_WORKSPACE;
+  if (ws_bytes < ln_bwd_min_ws(dims, L)) return MLM_E_WORKSPACE;
   return hip_status(launch_combine_layernorm_bwd(dims->dtype, L.T, dims->H, partials, n_partials, x, gamma, mean, rstd,
                                                  residual_grad, dy_out, dx, dgamma, dbeta, dx_colsum, (float*)ws,
-                                                 drop, dz_out, (hipStream_t)stream));
+                                                 ws_bytes, drop, dz_out, (hipStream_t)stream));
 }
 
 MLM_API int mlm_combine_layernorm_bwd(const mlm_dims* dims, const void* const* partials, int32_t n_partials,
@@ -324,7 +329,7 @@ MLM_API int mlm_colsum_noalloc(const mlm_dims* dims, const void* dy, void* dbias
 // two bias column sums inside the attention and MLP calls and two stand-alone [T,H] column sums
 static size_t deferred_sums_bytes_for(const mlm_dims* dm, const Local& L) {
   const size_t T = (size_t)L.T;
-  const size_t ln = align256(((T + kLnBwdRowsPerBlock - 1) / kLnBwdRowsPerBlock) * 3 * (size_t)dm->H * 4);
+  const size_t ln = align256((size_t)ln_bwd_blocks(dm->dtype, L.T, dm->H) * 3 * dm->H * 4);
   const size_t chunks = (T + kColsumRowsPerBlock - 1) / kColsumRowsPerBlock;
   return 4 * ln + align256(chunks * 3 * L.Hl * 4) + align256(chunks * L.Fl * 4) + 2 * align256(chunks * dm->H * 4);
 }

@@ -207,28 +207,32 @@ hipError_t launch_attn_fwd_f32(const AttnArgs& a, hipStream_t st);
 hipError_t launch_attn_bwd_f32(const AttnArgs& a, hipStream_t st);
 
 // ---- row / elementwise kernels (rowops.hip); dtype = MLM_F32 / MLM_BF16 ----------
-constexpr int kLnBwdRowsPerBlock = 32;
+constexpr int kLnBwdRowsPerBlock = 32;      // at most; ln_bwd_blocks deals fewer where that leaves compute units idle
 constexpr int kColsumRowsPerBlock = 64;
 constexpr int kMaxPartials = 16;
 
 hipError_t launch_layernorm_fwd(int dtype, int T, int H, float eps, const void* x, const void* gamma,
                                 const void* beta, void* y, float* mean, float* rstd, hipStream_t st);
-// ws: [ceil(T/kLnBwdRowsPerBlock)][2][H] float (the workspace query reserves 3 parts)
+// Number of workgroups (= block partials) of a layer-norm backward over T rows, and the fewest it can run with.
+int ln_bwd_blocks(int dtype, int T, int H);
+inline int ln_bwd_min_blocks(int T) { return (T + kLnBwdRowsPerBlock - 1) / kLnBwdRowsPerBlock; }
+// ws: [ln_bwd_blocks][2][H] float (the workspace query reserves 3 parts); with less room, down to ln_bwd_min_blocks
+// partials of 3 parts, fewer workgroups run
 hipError_t launch_layernorm_bwd(int dtype, int T, int H, const void* dy, const void* x, const void* gamma,
                                 const float* mean, const float* rstd, const void* residual_grad, void* dx,
-                                void* dgamma, void* dbeta, float* ws, hipStream_t st);
+                                void* dgamma, void* dbeta, float* ws, size_t ws_bytes, hipStream_t st);
 // Fused forms: the layer norm reads sum(partials) (+ bias + residual) instead of a stored tensor.
 hipError_t launch_combine_layernorm_fwd(int dtype, int T, int H, float eps, const void* const* partials, int n,
                                         const void* bias, const void* residual, void* x_out, const void* gamma,
                                         const void* beta, void* y, float* mean, float* rstd, const mlm_dropout* drop,
                                         hipStream_t st);
-// ws: [ceil(T/kLnBwdRowsPerBlock)][3][H] float; dy_out and dx_colsum may be NULL.  With drop and dz_out the kernel
+// ws: [ln_bwd_blocks][3][H] float (less room as above); dy_out and dx_colsum may be NULL.  With drop and dz_out the kernel
 // also emits dz_out = dropout-mask(dx) / (1 - p) and dx_colsum sums dz_out's columns instead of dx's.
 hipError_t launch_combine_layernorm_bwd(int dtype, int T, int H, const void* const* partials, int n, const void* x,
                                         const void* gamma, const float* mean, const float* rstd,
                                         const void* residual_grad, void* dy_out, void* dx, void* dgamma, void* dbeta,
-                                        void* dx_colsum, float* ws, const mlm_dropout* drop, void* dz_out,
-                                        hipStream_t st);
+                                        void* dx_colsum, float* ws, size_t ws_bytes, const mlm_dropout* drop,
+                                        void* dz_out, hipStream_t st);
 // out = residual + dropout(sum partials + bias[t mod bias_rows])
 hipError_t launch_combine(int dtype, int T, int H, const void* const* partials, int n, const void* bias,
                           int bias_rows, const void* residual, void* out, const mlm_dropout* drop, hipStream_t st);

@@ -3,6 +3,7 @@
 // partial merges (Section 3 of the paper: replicated LN/residual, g/f reductions, loss fused
 // with the vocabulary-parallel logits).  One wavefront (64 lanes) owns one token row; row
 // statistics are wave-level shuffles, HBM access is 16-byte vectors, coalesced along H.
+#include <algorithm>
 #include <mutex>
 #include "common.h"
 #include "rng.h"
@@ -193,8 +194,8 @@ hipError_t launch_combine_layernorm_fwd(int dtype, int T, int H, float eps, cons
 }
 
 // ------------------------------------------------------------------------------ layer norm backward
-// Block = one wave per 64 vectors of a row; the grid has one block per
-// kLnBwdRowsPerBlock rows and the rows are dealt to the blocks in batches of kLnBwdBatch, round-robin.  A lane owns
+// Block = one wave per 64 vectors of a row; the rows are dealt to the blocks (ln_bwd_blocks of them) in batches of
+// kLnBwdBatch, round-robin.  A lane owns
 // ONE 16-byte vector of columns in every row, so its dgamma / dbeta (/ dx column-sum) partials are a handful of
 // registers and several waves fit on a SIMD (a wave-per-row layout needs the partials of the whole row per lane:
 // ~150 registers, one wave per SIMD, and ran at half the HBM rate).  The row statistics s1 = mean(dy gamma),
@@ -508,18 +509,38 @@ hipError_t deferred_sums_flush(hipStream_t st) {
   return hipGetLastError();
 }
 
+// bf16 rows of up to 3072 columns (a multiple of 4) take the 8-byte form: twice the waves per row, at most 12
+static bool ln_bwd_narrow(int esz, int H) { return esz == 2 && H % 4 == 0 && H / 4 <= 768; }
+static int ln_bwd_waves(int esz, int H) {
+  const int vn = (ln_bwd_narrow(esz, H) ? 8 : 16) / esz;
+  return (H / vn + 63) / 64;
+}
+
+// A block works through its batches one after the other (3-4 us each), so the rows go to as many blocks as the chip
+// holds at once: one per compute unit, two where a row is at most 6 waves (more partials than that cost the finishing
+// reduction more than they give).  Eight batches per block is the most: at 8192 x 3072 four take 47.9 us and eight 39.3,
+// the call's time with the finishing reduction.  Eight per block at every size, which leaves compute units idle below
+// 8192 rows, against this rule: bf16 400 x 192 19.6 -> 12.5 us, 1024 x 1920 25.2 -> 12.4, 3000 x 1536 26.5 -> 19.5,
+// 4096 x 2560 32.2 -> 24.9, 8192 x 1536 29.7 -> 28.7; fp32 128 x 256 20.1 -> 12.2, 1024 x 1024 23.3 -> 12.3.
+int ln_bwd_blocks(int dtype, int T, int H) {
+  const int nbatch = (T + kLnBwdBatch - 1) / kLnBwdBatch;
+  const int slots = ln_bwd_waves(dtype == MLM_BF16 ? 2 : 4, H) <= 6 ? 512 : 256;
+  const int per = std::min((nbatch + slots - 1) / slots, kLnBwdRowsPerBlock / kLnBwdBatch);
+  return (nbatch + per - 1) / per;
+}
+
 template <typename T>
 static hipError_t ln_bwd_dispatch(int rows, int H, const void* dy, const void* x, const void* gamma,
                                   const float* mean, const float* rstd, const void* residual, void* dx,
-                                  void* dgamma, void* dbeta, float* ws, const PartialPtrs* pp, int n, void* dy_out,
-                                  void* dx_colsum, const DropArgs& drop, void* dz_out, hipStream_t st) {
-  // bf16 rows of up to 3072 columns (a multiple of 4) take the 8-byte form: twice the waves per row, at most 12
+                                  void* dgamma, void* dbeta, float* ws, size_t ws_bytes, const PartialPtrs* pp, int n,
+                                  void* dy_out, void* dx_colsum, const DropArgs& drop, void* dz_out, hipStream_t st) {
   constexpr bool kNarrow = sizeof(T) == 2;
-  const bool narrow = kNarrow && H % 4 == 0 && H / 4 <= 768;
-  const int vn = narrow ? 8 / (int)sizeof(T) : Vec16<T>::N;
-  const int nwaves = (H / vn + 63) / 64;
+  const bool narrow = ln_bwd_narrow(sizeof(T), H);
+  const int nwaves = ln_bwd_waves(sizeof(T), H);
   if (nwaves < 1 || nwaves > (narrow ? 12 : 8)) return hipErrorInvalidValue;
-  const int nblk = (rows + kLnBwdRowsPerBlock - 1) / kLnBwdRowsPerBlock;
+  const size_t room = ws_bytes / ((size_t)3 * H * sizeof(float));
+  if (room < (size_t)ln_bwd_min_blocks(rows)) return hipErrorInvalidValue;
+  const int nblk = (int)std::min((size_t)ln_bwd_blocks(sizeof(T) == 2 ? MLM_BF16 : MLM_F32, rows, H), room);
   PartialPtrs none;
   for (int k = 0; k < kMaxPartials; ++k) none.p[k] = nullptr;
   const int np = (pp && dx_colsum) ? 3 : 2;
@@ -556,28 +577,27 @@ static hipError_t ln_bwd_dispatch(int rows, int H, const void* dy, const void* x
 
 hipError_t launch_layernorm_bwd(int dtype, int T, int H, const void* dy, const void* x, const void* gamma,
                                 const float* mean, const float* rstd, const void* residual_grad, void* dx,
-                                void* dgamma, void* dbeta, float* ws, hipStream_t st) {
+                                void* dgamma, void* dbeta, float* ws, size_t ws_bytes, hipStream_t st) {
   const DropArgs nd = make_drop_args(nullptr);
   return dtype == MLM_BF16
-             ? ln_bwd_dispatch<bf16>(T, H, dy, x, gamma, mean, rstd, residual_grad, dx, dgamma, dbeta, ws, nullptr, 0,
+             ? ln_bwd_dispatch<bf16>(T, H, dy, x, gamma, mean, rstd, residual_grad, dx, dgamma, dbeta, ws, ws_bytes, nullptr, 0,
                                      nullptr, nullptr, nd, nullptr, st)
-             : ln_bwd_dispatch<float>(T, H, dy, x, gamma, mean, rstd, residual_grad, dx, dgamma, dbeta, ws, nullptr, 0,
+             : ln_bwd_dispatch<float>(T, H, dy, x, gamma, mean, rstd, residual_grad, dx, dgamma, dbeta, ws, ws_bytes, nullptr, 0,
                                       nullptr, nullptr, nd, nullptr, st);
 }
 
-// ws: [ceil(T/kLnBwdRowsPerBlock)][3][H] float
 hipError_t launch_combine_layernorm_bwd(int dtype, int T, int H, const void* const* partials, int n, const void* x,
                                         const void* gamma, const float* mean, const float* rstd,
                                         const void* residual_grad, void* dy_out, void* dx, void* dgamma, void* dbeta,
-                                        void* dx_colsum, float* ws, const mlm_dropout* drop, void* dz_out,
-                                        hipStream_t st) {
+                                        void* dx_colsum, float* ws, size_t ws_bytes, const mlm_dropout* drop,
+                                        void* dz_out, hipStream_t st) {
   PartialPtrs pp;
   for (int k = 0; k < kMaxPartials; ++k) pp.p[k] = k < n ? partials[k] : nullptr;
   const DropArgs da = make_drop_args(drop);
   return dtype == MLM_BF16
-             ? ln_bwd_dispatch<bf16>(T, H, nullptr, x, gamma, mean, rstd, residual_grad, dx, dgamma, dbeta, ws, &pp, n,
+             ? ln_bwd_dispatch<bf16>(T, H, nullptr, x, gamma, mean, rstd, residual_grad, dx, dgamma, dbeta, ws, ws_bytes, &pp, n,
                                      dy_out, dx_colsum, da, dz_out, st)
-             : ln_bwd_dispatch<float>(T, H, nullptr, x, gamma, mean, rstd, residual_grad, dx, dgamma, dbeta, ws, &pp, n,
+             : ln_bwd_dispatch<float>(T, H, nullptr, x, gamma, mean, rstd, residual_grad, dx, dgamma, dbeta, ws, ws_bytes, &pp, n,
                                       dy_out, dx_colsum, da, dz_out, st);
 }
 
