@@ -17,7 +17,8 @@ struct GemmTile {
   static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   static constexpr int TM = WM / 32, TN = WN / 32;
   static constexpr int STRIP = 32 * 68 * 2;                        // bf16-sized elements of one epilogue strip (32 x 68 floats)
-  static constexpr size_t LDS_EPI = (size_t)2 * WAVES_M * WAVES_N * STRIP * 2 + (size_t)2 * WAVES_N * BM * 4;
+  static constexpr int NSTRIP = TM * ((TN + 1) / 2) > 1 ? 2 : 1;   // strips per wave (one if the wave tile is one strip)
+  static constexpr size_t LDS_EPI = (size_t)NSTRIP * WAVES_M * WAVES_N * STRIP * 2 + (size_t)2 * WAVES_N * BM * 4;
 };
 
 // ---------------------------------------------------------------------------------------------- epilogue
@@ -139,7 +140,7 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs& a, Acc& acc,
   const bf16* bias = (const bf16*)a.bias;
 
   if (EPI == EPI_CE) {
-    float* red_m = reinterpret_cast<float*>(lds_raw + (size_t)2 * WAVES_M * WAVES_N * Tcfg::STRIP * 2);
+    float* red_m = reinterpret_cast<float*>(lds_raw + (size_t)Tcfg::NSTRIP * WAVES_M * WAVES_N * Tcfg::STRIP * 2);
     float* red_s = red_m + WAVES_N * BM;
     float* rm = red_m + (wave % WAVES_N) * BM + wm0;
     float* rs = red_s + (wave % WAVES_N) * BM + wm0;
@@ -177,8 +178,8 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs& a, Acc& acc,
     // Nothing but the rounding happens between accumulator and memory: round first and stage bf16 strips (half the
     // LDS traffic of the fp32 strips, no conversion at read-back).  Row stride 72 elements keeps rows 16-byte aligned.
     constexpr int SWB = 72;
-    static_assert(2 * 32 * SWB <= Tcfg::STRIP * 2, "bf16 strips fit in the wave's staging area");
-    bf16* bstrip0 = lds + (size_t)wave * 2 * Tcfg::STRIP;
+    static_assert(2 * 32 * SWB <= Tcfg::NSTRIP * Tcfg::STRIP * 2, "bf16 strips fit in the wave's staging area");
+    bf16* bstrip0 = lds + (size_t)wave * Tcfg::NSTRIP * Tcfg::STRIP;
 #pragma unroll
     for (int step = 0; step <= NSTEP; ++step) {
       if (step < NSTEP) {
@@ -207,7 +208,7 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs& a, Acc& acc,
   }
   constexpr int SW = 64 + 4;                                   // strip row stride in floats (272 B)
   static_assert(32 * SW * 4 <= Tcfg::STRIP * 2, "strip does not fit");
-  float* strip0 = reinterpret_cast<float*>(lds + (size_t)wave * 2 * Tcfg::STRIP);
+  float* strip0 = reinterpret_cast<float*>(lds + (size_t)wave * Tcfg::NSTRIP * Tcfg::STRIP);
 
 #pragma unroll
   for (int step = 0; step <= NSTEP; ++step) {

@@ -9,7 +9,7 @@ int gemm_v2_forced_bn() {
   if (forced < 0) {
     const char* e = getenv("MLM_GEMM_BN");
     const int v = e ? atoi(e) : 0;
-    forced = (v == 192 || v == 256) ? v : 0;
+    forced = (v == 128 || v == 192 || v == 256) ? v : 0;
   }
   return forced;
 }
@@ -29,9 +29,10 @@ int gemm_cu_count() {
   return n;
 }
 
+// (the cross-entropy GEMM always gets split-k scratch)
 int gemm_bf16_ce_col_tiles(int M, int N, int K) {
-  (void)M; (void)K;
-  return (N + V2_B - 1) / V2_B;
+  const int bn = v2_pick_bn<true, false, EPI_CE>(M, N, K, true);
+  return (N + bn - 1) / bn;
 }
 
 hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t st) {

@@ -32,13 +32,20 @@ namespace mlm {
 
 constexpr int V2_B = 256;                   // block tile edge (M and N)
 constexpr int V2_BK = 32;                   // k per stage
-constexpr int V2_STAGES = 4;
-constexpr int V2_NW = 8;                    // waves per workgroup, two per SIMD
-template <int BN> constexpr int v2_waves_m() { return BN == V2_B ? 2 : 4; }
+constexpr int V2_SMALL = 128;               // block tile edge of the small tile
+// rows of the block tile by its width
+template <int BN> constexpr int v2_bm() { return BN == V2_SMALL ? V2_SMALL : V2_B; }
+// DEEP: the small tile in a launch of at most one workgroup per compute unit.  It has to hide its latencies by itself, so it
+// runs 8 waves (two per SIMD) of 32 x 64 and, where a pair of slices arrives at once (a k-contiguous operand), keeps eight
+// slices in its ring; in larger launches two workgroups share a compute unit, and 4 waves of 64 x 64 read a third less from
+// LDS.  Measured, 96 slices: 4 / 8 waves on 256 tiles 44.7 / 33.1 us, on 512 tiles 49.1 / 51 us; 8 against 4 slices in the
+// ring 31.1 / 35.4 us (both operands k-contiguous), 32.5 / 33.1 (one), and 37 / 33.5 (none, 128 slices).
+template <int BN, bool DEEP> constexpr int v2_waves_m() { return BN == 192 || DEEP ? 4 : 2; }
+template <int BN, bool DEEP> constexpr int v2_nw() { return BN == V2_SMALL && !DEEP ? 4 : 8; }
 inline int v2_slices(int K) { return 2 * ((K + 2 * V2_BK - 1) / (2 * V2_BK)); }   // 32-deep slices walked: whole pairs
-constexpr int V2_OP_BYTES = V2_B * V2_BK * 2;          // 16 KB per operand per stage
-constexpr int V2_REGION_BYTES = V2_STAGES * V2_OP_BYTES;   // 64 KB ring per operand: A's ring, then B's ring
-constexpr size_t V2_LDS_BYTES = (size_t)2 * V2_REGION_BYTES;          // 128 KB
+template <bool A_KC, bool B_KC, bool DEEP> constexpr int v2_stages() { return DEEP && (A_KC || B_KC) ? 8 : 4; }
+// A's ring, then B's ring: 128 KB for a 256 x 256 tile, 64 KB (128 KB DEEP) for a 128 x 128 one
+constexpr size_t v2_ring_bytes(int bm, int bn, int stages) { return (size_t)stages * V2_BK * 2 * (bm + bn); }
 
 // What a copy reads for the 16-byte units past K.
 static __device__ const uint4 v2_zero16 = {0u, 0u, 0u, 0u};
@@ -61,12 +68,12 @@ __device__ __forceinline__ int v2_mn_swizzle(int k) { return ((k & 3) << 2) | ((
 // (192 rows, 16 x 16 x 32 reads: two more units for bit 3 of k, as above)
 __device__ __forceinline__ int v2_mn_rot192(int k) { return (((k >> 1) & 1) << 2) + (((k >> 3) & 1) << 1); }
 template <int ROWS> __device__ __forceinline__ int v2_mn_pos(int u, int k) {
-  if (ROWS == V2_B) return u ^ v2_mn_swizzle(k);
+  if (ROWS != 192) return u ^ v2_mn_swizzle(k);
   const int t = u + v2_mn_rot192(k);
   return t >= ROWS / 8 ? t - ROWS / 8 : t;
 }
 template <int ROWS> __device__ __forceinline__ int v2_mn_chunk(int pos, int k) {
-  if (ROWS == V2_B) return pos ^ v2_mn_swizzle(k);
+  if (ROWS != 192) return pos ^ v2_mn_swizzle(k);
   const int t = pos - v2_mn_rot192(k);
   return t < 0 ? t + ROWS / 8 : t;
 }
@@ -84,7 +91,7 @@ __device__ __forceinline__ int v2_kc_swizzle(int row) { return (((row >> 1) & 1)
 //  * operand contiguous along m / n (MN): a slice is [32 k][256 rows] = 512 bytes per k, QPW copies per slice.
 // RAG (K is no multiple of 64): units past K are read from v2_zero16.  A template parameter: the compare and select per
 // copy cost 2 % of a large GEMM.
-template <bool KC, int NP_, bool RAG, int ROWS = V2_B>
+template <bool KC, int NP_, bool RAG, int ROWS>
 struct V2Src {
   static constexpr int NP = NP_;       // KC: 1-KB copies per wave and PAIR (rows / (8 waves)); MN: per wave and slice
   // MN: a slice is ROWS / 16 one-KB copies; where that is no multiple of the wave count (192 rows: 12 copies, 8
@@ -133,7 +140,7 @@ struct V2Src {
 
 // Operand registers of the 16 x 16 x 32 MFMA for the 16-row tile starting at row `r0`: lane l holds k = 8 (l / 16) ..
 // + 7 (the whole 32-deep slice is one MFMA deep) of row r0 + l % 16.
-template <bool KC, int ROWS = V2_B>
+template <bool KC, int ROWS>
 __device__ __forceinline__ bf16x8 v2_frag16(const unsigned char* ring, int stage, int r0, int lane) {
   constexpr int OPB = ROWS * V2_BK * 2;       // bytes of one k-slice of the operand
   const int l16 = lane & 15, lg = lane >> 4;
@@ -160,8 +167,10 @@ __device__ __forceinline__ bf16x8 v2_frag16(const unsigned char* ring, int stage
 
 struct V2Plan {
   int tiles_m, tiles_n, full_tiles, tail_tiles, split;   // grid = full_tiles + tail_tiles * split
-  int bn;                                                 // tile width (256, or 192 for the narrow-tile variant)
+  int bm, bn;                                             // tile: 256 x 256, 256 x 192 or 128 x 128
   double cost;                                            // estimated kernel time in microseconds (host side only)
+  int grid() const { return full_tiles + tail_tiles * split; }
+  bool deep() const { return bn == 128 && grid() <= gemm_cu_count(); }   // one workgroup per compute unit: eight-slice ring
 };
 
 // Cost-model constants (microseconds, fitted to rocprofv3 kernel durations of unsplit two-round launches at two
@@ -169,56 +178,68 @@ struct V2Plan {
 // 256 x 256 tile and for the 256 x 192 tile (either B layout).  The narrow tile does 3/4 of the MFMA work per slice
 // in 0.88 of the time, so it wins where it saves a round or fills one and loses on long-k shapes whose last round
 // can be split instead.  The fix-up kernel reads the pieces mostly out of the last-level cache.
-inline double v2_tile_fixed(int bn) { return bn == V2_B ? 9.2 : 8.0; }
-inline double v2_slice_cost(int bn) { return bn == V2_B ? 0.67 : 0.59; }
+// The small tile has two: `alone` with at most one workgroup per compute unit in the launch, else for two that share one
+// (fitted to 120 .. 512 tiles of 24 .. 256 slices).
+inline double v2_tile_cost(int bn, int nk, bool alone) {
+  if (bn == V2_SMALL) return alone ? 4.5 + 0.24 * nk : 6.0 + 0.43 * nk;
+  return bn == V2_B ? 9.2 + 0.67 * nk : 8.0 + 0.59 * nk;
+}
 inline double v2_fixup_cost(double traffic_us) { return 3.0 + 0.6 * traffic_us; }
 
 // Decide whether, and how far, to split the last partial round along k.  Cost model in microseconds: a tile costs
 // its fixed part + the per-slice cost of its k-slices; the pieces write fp32 partial tiles at ~5 TB/s and the fix-up
 // kernel reads them back.
 inline V2Plan v2_plan(int M, int N, int K, bool allow_split, int bn = V2_B) {
-  const int V2_CUS = gemm_cu_count();
+  const int cus = gemm_cu_count();
   V2Plan p;
+  p.bm = bn == V2_SMALL ? V2_SMALL : V2_B;
   p.bn = bn;
-  p.tiles_m = (M + V2_B - 1) / V2_B;
+  p.tiles_m = (M + p.bm - 1) / p.bm;
   p.tiles_n = (N + bn - 1) / bn;
   const int tiles = p.tiles_m * p.tiles_n;
-  const int rem = tiles % V2_CUS;
+  const int per_round = bn == V2_SMALL ? 2 * cus : cus;     // two workgroups of the small tile share a compute unit
+  const int rem = tiles % per_round;
   const int nk = v2_slices(K);
-  const double fixed = v2_tile_fixed(bn), per_slice = v2_slice_cost(bn);
   int split = 1;
-  double tail = rem ? fixed + per_slice * nk : 0.0;   // unsplit tail round
-  if (allow_split && rem != 0 && rem * 2 <= V2_CUS) {
-    int smax = V2_CUS / rem;
+  const bool alone = tiles <= cus;
+  double tail = rem ? v2_tile_cost(bn, nk, alone) : 0.0;   // unsplit tail round
+  if (allow_split && rem != 0 && rem * 2 <= cus) {
+    int smax = cus / rem;
     if (smax > 16) smax = 16;
     for (int sp = 2; sp <= smax; ++sp) {
       if (nk / sp < 8) break;                         // keep at least 8 k-slices per piece
-      const double traffic = (double)rem * sp * (V2_B * (double)bn * 4.0) / 5.0e6;
-      const double t = fixed + per_slice * ((nk + sp - 1) / sp) + traffic + v2_fixup_cost(traffic);
+      const double traffic = (double)rem * sp * (p.bm * (double)bn * 4.0) / 5.0e6;
+      const double t = v2_tile_cost(bn, (nk + sp - 1) / sp, alone) + traffic + v2_fixup_cost(traffic);
       if (t < tail) { tail = t; split = sp; }
     }
   }
   p.split = split;
   p.tail_tiles = split > 1 ? rem : 0;
   p.full_tiles = tiles - p.tail_tiles;
-  p.cost = (tiles / V2_CUS) * (fixed + per_slice * nk) + tail;
+  p.cost = (tiles / per_round) * v2_tile_cost(bn, nk, false) + tail;
   return p;
 }
 
-// One work item (pid) of one GEMM: the body of the kernels below.  8 waves, two per SIMD.
+// One work item (pid) of one GEMM: the body of the kernels below.
 // BN = 256: 2 x 4 waves of 128 x 64.  BN = 192: 4 x 2 waves of 64 x 96 -- a tile count of 32 x (N / 192) fills the 256 CUs
 // where N / 256 column tiles leave a quarter of them idle (N = 1536: 256 tiles instead of 192) or a half-empty second
 // round (N = 3072: 512 instead of 384).
-template <bool A_KC, bool B_KC, int EPI, int BN, bool RAG>
+// BN = 128: a 128 x 128 tile for outputs of too few large tiles.  Per flop it reads twice the operand bytes and more of LDS
+// (two workgroups per compute unit: 0.215 us per tile and 32-deep slice, where a quarter of the 256 x 256 tile's is 0.17),
+// but a launch of at most two tiles per compute unit neither leaves units idle nor splits k over fp32 partial tiles.
+// Library call, forward layout, best large tile against it: 1024 x 1920 x 960 18.7 -> 10.6 us, 1024 x 3840 x 1920
+// 33.7 -> 21.2, 3000 x 1152 x 1536 27.5 -> 16.7, 4096 x 2048 x 768 20.3 -> 16.9; 4096 x 4096 x 768 stays (27 against 31).
+// Grouped weight gradients of 228 such tiles (8192 tokens, 1536 wide, split eight ways): 152 us in eight launches -> 81.
+template <bool A_KC, bool B_KC, int EPI, int BN, bool RAG, bool DEEP>
 __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Plan& plan, float* splitk_ws, int pid,
                                                   unsigned char* lds_raw) {
-  static_assert(BN == V2_B || BN == 192, "tile widths");
-  constexpr int NW = V2_NW;
-  constexpr int WAVES_M = v2_waves_m<BN>(), WAVES_N = NW / WAVES_M;
-  constexpr int WM = V2_B / WAVES_M, WN = BN / WAVES_N;
-  constexpr int OPB_B = BN * V2_BK * 2;                        // bytes of one k-slice of the B operand
+  static_assert(BN == V2_B || BN == 192 || BN == V2_SMALL, "tile widths");
+  constexpr int NW = v2_nw<BN, DEEP>(), BM = v2_bm<BN>(), ST = v2_stages<A_KC, B_KC, DEEP>();
+  constexpr int WAVES_M = v2_waves_m<BN, DEEP>(), WAVES_N = NW / WAVES_M;
+  constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
+  constexpr int OPB_A = BM * V2_BK * 2, OPB_B = BN * V2_BK * 2;   // bytes of one k-slice of either operand
   // 1-KB copies per wave: per pair of slices for a k-contiguous operand, per slice otherwise
-  constexpr int NPA = A_KC ? V2_B / (8 * NW) : 16 / NW, NPB = B_KC ? BN / (8 * NW) : (BN / 16 + NW - 1) / NW;
+  constexpr int NPA = A_KC ? BM / (8 * NW) : BM / 16 / NW, NPB = B_KC ? BN / (8 * NW) : (BN / 16 + NW - 1) / NW;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
 
@@ -235,20 +256,20 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
   // Plain order, tile row fastest: the 256 concurrent tiles form 8 tile-columns of 32 tile-rows, and the ids that
   // share an XCD (congruent mod 8) share tile rows, so each XCD's L2 sees few distinct operand panels.
   const int tile_m = vt % plan.tiles_m, tile_n = vt / plan.tiles_m;
-  const int m0 = tile_m * V2_B, n0 = tile_n * BN;
+  const int m0 = tile_m * BM, n0 = tile_n * BN;
   const int np_total = (a.K + 2 * V2_BK - 1) / (2 * V2_BK);   // pairs of 32-deep slices of the problem
   const int kt_begin = 2 * (int)((long)np_total * piece / npieces);
   const int kt_end = 2 * (int)((long)np_total * (piece + 1) / npieces);
   const int nk = kt_end - kt_begin;                  // even, >= 2
 
-  V2Src<A_KC, NPA, RAG> sa;
+  V2Src<A_KC, NPA, RAG, BM> sa;
   V2Src<B_KC, NPB, RAG, BN> sb;
   sa.init((const bf16*)a.A, a.lda, m0, a.M, kt_begin * V2_BK, a.K, wave, lane);
   sb.init((const bf16*)a.B, a.ldb, n0, a.N, kt_begin * V2_BK, a.K, wave, lane);
 
-  const uint32_t ldsA = lds_offset_of(lds_raw), ldsB = ldsA + V2_REGION_BYTES;
+  const uint32_t ldsA = lds_offset_of(lds_raw), ldsB = ldsA + ST * OPB_A;
   const unsigned char* ringA = lds_raw;
-  const unsigned char* ringB = lds_raw + V2_REGION_BYTES;
+  const unsigned char* ringB = lds_raw + ST * OPB_A;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   constexpr int NKC = (A_KC ? 1 : 0) + (B_KC ? 1 : 0), NMN = 2 - NKC;
   // Four slices are always in flight or landed; past the end of k the last pair / slice is fetched again into a
@@ -256,12 +277,12 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
   // the initial fill = the order the steady state would have produced: pair 0, slices 0 1, pair 1, slices 2 3.
   const int last_pair = nk / 2 - 1, last_slice = nk - 1;
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    if (A_KC) sa.issue(ldsA + h * 2 * V2_OP_BYTES, wave_u, 2 * min(h, last_pair));
+  for (int h = 0; h < ST / 2; ++h) {
+    if (A_KC) sa.issue(ldsA + h * 2 * OPB_A, wave_u, 2 * min(h, last_pair));
     if (B_KC) sb.issue(ldsB + h * 2 * OPB_B, wave_u, 2 * min(h, last_pair));
 #pragma unroll
     for (int s = 2 * h; s < 2 * h + 2; ++s) {
-      if (!A_KC) sa.issue(ldsA + s * V2_OP_BYTES, wave_u, min(s, last_slice));
+      if (!A_KC) sa.issue(ldsA + s * OPB_A, wave_u, min(s, last_slice));
       if (!B_KC) sb.issue(ldsB + s * OPB_B, wave_u, min(s, last_slice));
     }
   }
@@ -273,12 +294,14 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
   //
   // Copies per wave issued at the hand-over of an even slice: EV = NMN QPW; of an odd slice: OD = NKC 2 QPW + NMN QPW
   // (pairs first).  Copies return in order, so "slice kt+1 has landed" is a bound on the copies still outstanding:
-  //   even kt: everything up to the hand-over of kt-3 must be done           -> at most EV + OD = 4 QPW outstanding
-  //   odd kt:  the pair issued first at the hand-over of kt-2 must be done   -> at most 2 EV outstanding (if NKC > 0)
+  //   even kt: everything up to the hand-over of kt+1-ST must be done        -> ST - 2 hand-overs outstanding
+  //   odd kt:  the pair issued first at the hand-over of kt+2-ST must be done -> that hand-over's slice and ST - 3 more
   constexpr int C_SLICE = (A_KC ? 0 : NPA) + (B_KC ? 0 : NPB);     // copies per wave that re-arm a slice stage
   constexpr int C_PAIR = (A_KC ? NPA : 0) + (B_KC ? NPB : 0);      // copies per wave that re-arm a pair stage
   constexpr int EV = C_SLICE, OD = C_PAIR + C_SLICE;
-  constexpr int W_INIT = 3 * C_SLICE + C_PAIR, W_EVEN = EV + OD, W_ODD = NKC > 0 ? 2 * EV : EV + OD;
+  constexpr int W_INIT = (ST - 1) * C_SLICE + (ST / 2 - 1) * C_PAIR, W_EVEN = (ST / 2 - 1) * (EV + OD);
+  constexpr int W_ODD = NKC > 0 ? (ST / 2) * EV + (ST / 2 - 2) * OD : W_EVEN;
+  static_assert(W_INIT < 64 && W_EVEN < 64, "vmcnt holds six bits");
   (void)NMN;
   // ---- 16 x 16 x 32 MFMAs: one MFMA spans the slice's 32 k, so a wave holds the fragments of ONE slice: NA of A, NB
   // of B.  MFMA order: A fragment outer, B fragment inner.  A fragment j is replaced by the next slice's behind
@@ -303,21 +326,21 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
   wait_vmcnt<W_INIT>();                  // slice 0 landed
   __builtin_amdgcn_s_barrier();
 #pragma unroll
-  for (int j = 0; j < NA; ++j) fa[j] = v2_frag16<A_KC>(ringA, 0, wm0 + j * 16, lane);
+  for (int j = 0; j < NA; ++j) fa[j] = v2_frag16<A_KC, BM>(ringA, 0, wm0 + j * 16, lane);
 #pragma unroll
   for (int i = 0; i < NB; ++i) fb[0][i] = v2_frag16<B_KC, BN>(ringB, 0, wn0 + i * 16, lane);
 
   // one 32-deep slice; PAR = parity of kt (compile time: it fixes the ring stage bits and the copy schedule)
   auto slice = [&](auto par_c, int kt) {
     constexpr int PAR = decltype(par_c)::value;
-    const int stage = kt & (V2_STAGES - 1), nstage = (kt + 1) & (V2_STAGES - 1);
+    const int stage = kt & (ST - 1), nstage = (kt + 1) & (ST - 1);
     constexpr int NC = PAR == 0 ? EV : OD;                 // copies to issue in this slice
     constexpr int NAFTER = NMF - HO - 1;                   // MFMAs after the hand-over
-    const int pair_idx = 2 * min((kt + 3) >> 1, last_pair);   // PAR == 1: the pair two ahead of this slice's pair
-    const uint32_t pair_sel = (uint32_t)(((kt + 3) >> 1) & 1);
-    const uint32_t pair_off_a = pair_sel * (2 * V2_OP_BYTES), pair_off_b = pair_sel * (2 * OPB_B);
-    const int slice_idx = min(kt + V2_STAGES, last_slice);
-    const uint32_t slice_off_a = (uint32_t)stage * V2_OP_BYTES, slice_off_b = (uint32_t)stage * OPB_B;
+    const int pair_idx = 2 * min((kt + ST - 1) >> 1, last_pair);   // PAR == 1: the pair ST / 2 ahead of this slice's pair
+    const uint32_t pair_sel = (uint32_t)(((kt + ST - 1) >> 1) & (ST / 2 - 1));
+    const uint32_t pair_off_a = pair_sel * (2 * OPB_A), pair_off_b = pair_sel * (2 * OPB_B);
+    const int slice_idx = min(kt + ST, last_slice);
+    const uint32_t slice_off_a = (uint32_t)stage * OPB_A, slice_off_b = (uint32_t)stage * OPB_B;
 #pragma unroll
     for (int idx = 0; idx < NMF; ++idx) {
       const int i = idx % NB, j = idx / NB;
@@ -343,7 +366,7 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
           // MFMA still reads the registers -- but inside the slice and not before the hand-over
           const int last = q * NB + NB < NMF - 1 ? q * NB + NB : NMF - 1;
           const int at = last > HO ? last : HO + 1;
-          if (idx == at) fa[q] = v2_frag16<A_KC>(ringA, nstage, wm0 + q * 16, lane);
+          if (idx == at) fa[q] = v2_frag16<A_KC, BM>(ringA, nstage, wm0 + q * 16, lane);
         }
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
@@ -377,9 +400,9 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
   __syncthreads();
 
   if (npieces > 1) {
-    // fp32 partial tile: piece-major [tail tile][piece][256][BN]
+    // fp32 partial tile: piece-major [tail tile][piece][BM][BN]
     const int l16 = lane & 15, lg = lane >> 4;
-    float* dst = splitk_ws + ((size_t)(vt - plan.full_tiles) * plan.split + piece) * (V2_B * BN);
+    float* dst = splitk_ws + ((size_t)(vt - plan.full_tiles) * plan.split + piece) * (BM * BN);
 #pragma unroll
     for (int j = 0; j < NA; ++j)
 #pragma unroll
@@ -389,13 +412,14 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
       }
     return;
   }
-  gemm_epilogue<V2_B, BN, WAVES_M, WAVES_N, EPI>(a, acc, lds_raw, m0, n0, tile_n);
+  gemm_epilogue<BM, BN, WAVES_M, WAVES_N, EPI>(a, acc, lds_raw, m0, n0, tile_n);
 }
 
-template <bool A_KC, bool B_KC, int EPI, int BN, bool RAG>
-__global__ __launch_bounds__(V2_NW * 64) void gemm_bf16_v2_kernel(GemmArgs a, V2Plan plan, float* splitk_ws) {
+// (two workgroups of the small tile fit a compute unit)
+template <bool A_KC, bool B_KC, int EPI, int BN, bool RAG, bool DEEP>
+__global__ __launch_bounds__((v2_nw<BN, DEEP>() * 64), 2) void gemm_bf16_v2_kernel(GemmArgs a, V2Plan plan, float* splitk_ws) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  gemm_v2_work_item<A_KC, B_KC, EPI, BN, RAG>(a, plan, splitk_ws, blockIdx.x, lds_raw);
+  gemm_v2_work_item<A_KC, B_KC, EPI, BN, RAG, DEEP>(a, plan, splitk_ws, blockIdx.x, lds_raw);
 }
 
 // Several independent GEMMs of one operand layout in ONE launch (plain-store epilogue, no k-split): the tiles of
@@ -410,8 +434,8 @@ struct GemmGroup {
   V2Plan plan[kMaxGroup];
 };
 
-template <bool A_KC, bool B_KC, bool RAG>
-__global__ __launch_bounds__(V2_NW * 64) void gemm_bf16_v2_group_kernel(GemmGroup g) {
+template <bool A_KC, bool B_KC, int BN, bool RAG, bool DEEP>
+__global__ __launch_bounds__((v2_nw<BN, DEEP>() * 64), 2) void gemm_bf16_v2_group_kernel(GemmGroup g) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   const int pid = blockIdx.x;
   // the problem index is uniform over the workgroup: select its arguments with scalar compares
@@ -424,26 +448,26 @@ __global__ __launch_bounds__(V2_NW * 64) void gemm_bf16_v2_group_kernel(GemmGrou
 #pragma unroll
   for (int i = 1; i < kMaxGroup; ++i)
     if (q == i) { a = g.args[i]; plan = g.plan[i]; first = g.tile_begin[i]; }
-  gemm_v2_work_item<A_KC, B_KC, EPI_STORE, V2_B, RAG>(a, plan, nullptr, pid - first, lds_raw);
+  gemm_v2_work_item<A_KC, B_KC, EPI_STORE, BN, RAG, DEEP>(a, plan, nullptr, pid - first, lds_raw);
 }
 
 // Tail tiles: sum the k-pieces in piece order (deterministic) and apply the epilogue to the fp32 sums.  A wave owns
 // whole 256-column tile rows (a lane: 4 consecutive columns), so the row statistics of the cross-entropy epilogue are
-// one wave reduction.  Grid: (256 / kFixRows row groups, tail tiles), 4 waves, kFixRows / 4 rows per wave.
+// one wave reduction.  Grid: (bm / kFixRows row groups, tail tiles), 4 waves, kFixRows / 4 rows per wave.
 constexpr int kFixRows = 8;
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_v2_fixup_kernel(GemmArgs a, V2Plan plan, const float* __restrict__ ws) {
   const int t = blockIdx.y;                          // tail tile
   const int vt = plan.full_tiles + t;
   const int tile_n = vt / plan.tiles_m;
-  const int bn = plan.bn;                             // tile width: a partial tile is [256][bn] floats
-  const int m0 = (vt % plan.tiles_m) * V2_B, n0 = tile_n * bn;
+  const int bm = plan.bm, bn = plan.bn;               // a partial tile is [bm][bn] floats
+  const int m0 = (vt % plan.tiles_m) * bm, n0 = tile_n * bn;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = n0 + lane * 4;
   const bool col_ok = n < a.N && lane * 4 < bn;       // N is a multiple of 8: a 4-column group is all in or all out
   const int nc = col_ok ? n : 0;
   const int lcol = lane * 4 < bn ? lane * 4 : 0;
-  const float* base = ws + (size_t)t * plan.split * (V2_B * bn) + lcol;
+  const float* base = ws + (size_t)t * plan.split * (bm * bn) + lcol;
   float bv[4] = {0.f, 0.f, 0.f, 0.f};
   if ((EPI == EPI_STORE || EPI == EPI_BIAS_GELU) && a.bias != nullptr) {
     const bf16x4 b = *reinterpret_cast<const bf16x4*>((const bf16*)a.bias + nc);
@@ -458,7 +482,7 @@ __global__ __launch_bounds__(256) void gemm_v2_fixup_kernel(GemmArgs a, V2Plan p
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[i][e] = bv[e];
     for (int p = 0; p < plan.split; ++p) {
-      const float4 x = *reinterpret_cast<const float4*>(base + (size_t)p * (V2_B * bn) + r * bn);
+      const float4 x = *reinterpret_cast<const float4*>(base + (size_t)p * (bm * bn) + r * bn);
       v[i][0] += x.x; v[i][1] += x.y; v[i][2] += x.z; v[i][3] += x.w;
     }
   }
@@ -525,23 +549,27 @@ __global__ __launch_bounds__(256) void gemm_v2_fixup_kernel(GemmArgs a, V2Plan p
   }
 }
 
-template <bool A_KC, bool B_KC, int EPI, int BN, bool RAG>
+// the rings or the epilogue's staging strips + reduction area, whichever is larger
+template <bool A_KC, bool B_KC, int BN, bool DEEP> constexpr size_t v2_lds_bytes() {
+  constexpr int WAVES_M = v2_waves_m<BN, DEEP>();
+  constexpr size_t kEpi = GemmTile<v2_bm<BN>(), BN, WAVES_M, v2_nw<BN, DEEP>() / WAVES_M>::LDS_EPI;
+  constexpr size_t kRing = v2_ring_bytes(v2_bm<BN>(), BN, v2_stages<A_KC, B_KC, DEEP>()), kLds = kRing > kEpi ? kRing : kEpi;
+  static_assert(kLds <= (BN == V2_SMALL && !DEEP ? 80 : 160) * 1024, "LDS budget");
+  return kLds;
+}
+
+template <bool A_KC, bool B_KC, int EPI, int BN, bool RAG, bool DEEP = false>
 hipError_t launch_gemm_bf16_v2_bn(const GemmArgs& a, float* splitk_ws, hipStream_t st) {
-  auto kern = gemm_bf16_v2_kernel<A_KC, B_KC, EPI, BN, RAG>;
-  // the ring (128 KB) or the epilogue's staging strips (2 per wave) + reduction area, whichever is larger
-  constexpr int WAVES_M = v2_waves_m<BN>();
-  constexpr size_t kEpi = GemmTile<V2_B, BN, WAVES_M, V2_NW / WAVES_M>::LDS_EPI;
-  constexpr size_t kLds = V2_LDS_BYTES > kEpi ? V2_LDS_BYTES : kEpi;
-  static_assert(kLds <= 160 * 1024, "LDS budget");
+  auto kern = gemm_bf16_v2_kernel<A_KC, B_KC, EPI, BN, RAG, DEEP>;
+  constexpr size_t kLds = v2_lds_bytes<A_KC, B_KC, BN, DEEP>();
   static LdsAttrOnce attr;         // per instantiation and device
   if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
   const V2Plan plan = v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, BN);
-  const int grid = plan.full_tiles + plan.tail_tiles * plan.split;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(V2_NW * 64), kLds, st, a, plan, splitk_ws);
+  hipLaunchKernelGGL(kern, dim3(plan.grid()), dim3(v2_nw<BN, DEEP>() * 64), kLds, st, a, plan, splitk_ws);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (plan.tail_tiles) {
-    hipLaunchKernelGGL((gemm_v2_fixup_kernel<EPI>), dim3(V2_B / kFixRows, plan.tail_tiles), dim3(256), 0, st, a, plan,
+    hipLaunchKernelGGL((gemm_v2_fixup_kernel<EPI>), dim3(plan.bm / kFixRows, plan.tail_tiles), dim3(256), 0, st, a, plan,
                        splitk_ws);
     e = hipGetLastError();
   }
@@ -549,13 +577,12 @@ hipError_t launch_gemm_bf16_v2_bn(const GemmArgs& a, float* splitk_ws, hipStream
 }
 
 // Tiles (work items without a k-split) of one problem.
-inline int v2_tiles(const GemmArgs& a) { return ((a.M + V2_B - 1) / V2_B) * ((a.N + V2_B - 1) / V2_B); }
+inline int v2_tiles(const GemmArgs& a, int bm, int bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); }
 
-template <bool A_KC, bool B_KC, bool RAG>
+template <bool A_KC, bool B_KC, int BN, bool RAG, bool DEEP>
 hipError_t launch_gemm_bf16_v2_group(const GemmArgs* probs, int n, hipStream_t st) {
-  auto kern = gemm_bf16_v2_group_kernel<A_KC, B_KC, RAG>;
-  constexpr size_t kEpi = GemmTile<V2_B, V2_B, v2_waves_m<V2_B>(), V2_NW / v2_waves_m<V2_B>()>::LDS_EPI;
-  constexpr size_t kLds = V2_LDS_BYTES > kEpi ? V2_LDS_BYTES : kEpi;
+  auto kern = gemm_bf16_v2_group_kernel<A_KC, B_KC, BN, RAG, DEEP>;
+  constexpr size_t kLds = v2_lds_bytes<A_KC, B_KC, BN, DEEP>();
   static LdsAttrOnce attr;
   if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
   GemmGroup g;
@@ -564,29 +591,48 @@ hipError_t launch_gemm_bf16_v2_group(const GemmArgs* probs, int n, hipStream_t s
   int total = 0;
   for (int q = 0; q < n; ++q) {
     g.args[q] = probs[q];
-    g.plan[q] = v2_plan(probs[q].M, probs[q].N, probs[q].K, false);
+    g.plan[q] = v2_plan(probs[q].M, probs[q].N, probs[q].K, false, BN);
     g.tile_begin[q] = total;
     total += g.plan[q].full_tiles;
   }
   for (int q = n; q <= kMaxGroup; ++q) g.tile_begin[q] = total;
-  hipLaunchKernelGGL(kern, dim3(total), dim3(V2_NW * 64), kLds, st, g);
+  hipLaunchKernelGGL(kern, dim3(total), dim3(v2_nw<BN, DEEP>() * 64), kLds, st, g);
   return hipGetLastError();
 }
 
-int gemm_v2_forced_bn();                    // MLM_GEMM_BN=192|256 forces a tile width where both exist, else 0
+int gemm_v2_forced_bn();                    // MLM_GEMM_BN=128|192|256 forces a tile width where both exist, else 0
+
+// The 192-wide tile exists for all but the cross-entropy epilogues, the small tile for every epilogue but the one that
+// recomputes the logits: take the one the cost model prices lowest for this shape.
+template <bool A_KC, bool B_KC, int EPI> constexpr bool v2_has_narrow() {
+  return B_KC || EPI == EPI_STORE || EPI == EPI_BIAS_GELU;
+}
+template <int EPI> constexpr bool v2_has_small() { return EPI != EPI_DLOGITS; }
+template <bool A_KC, bool B_KC, int EPI>
+int v2_pick_bn(int M, int N, int K, bool allow_split) {
+  const int forced = gemm_v2_forced_bn();
+  if (forced == V2_B || (forced == 192 && v2_has_narrow<A_KC, B_KC, EPI>()) || (forced == V2_SMALL && v2_has_small<EPI>()))
+    return forced;
+  int best = V2_B;
+  double cost = v2_plan(M, N, K, allow_split, V2_B).cost;
+  for (int bn : {192, V2_SMALL}) {
+    if (bn == 192 ? !v2_has_narrow<A_KC, B_KC, EPI>() : !v2_has_small<EPI>()) continue;
+    const double c = v2_plan(M, N, K, allow_split, bn).cost;
+    if (c < cost) { cost = c; best = bn; }
+  }
+  return best;
+}
 
 template <bool A_KC, bool B_KC, int EPI, bool RAG>
 hipError_t launch_gemm_bf16_v2_rag(const GemmArgs& a, float* splitk_ws, hipStream_t st) {
-  // both tile widths exist for the input-gradient layout and for the plain / bias + GeLU forward GEMMs: take the one the
-  // cost model prices lower for this shape
-  constexpr bool kHasNarrow = A_KC && (B_KC || EPI == EPI_STORE || EPI == EPI_BIAS_GELU);
-  if constexpr (kHasNarrow) {
-    const int forced = gemm_v2_forced_bn();
-    const bool narrow = forced ? forced == 192
-                               : v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, 192).cost <
-                                     v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, V2_B).cost;
-    if (narrow) return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, 192, RAG>(a, splitk_ws, st);
-  }
+  const int bn = v2_pick_bn<A_KC, B_KC, EPI>(a.M, a.N, a.K, splitk_ws != nullptr);
+  if constexpr (v2_has_narrow<A_KC, B_KC, EPI>())
+    if (bn == 192) return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, 192, RAG>(a, splitk_ws, st);
+  if constexpr (v2_has_small<EPI>())
+    if (bn == V2_SMALL)
+      return v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, V2_SMALL).deep()
+                 ? launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_SMALL, RAG, true>(a, splitk_ws, st)
+                 : launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_SMALL, RAG>(a, splitk_ws, st);
   return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_B, RAG>(a, splitk_ws, st);
 }
 

@@ -10,41 +10,44 @@ hipError_t launch_gemm_bf16_wgrad(const GemmArgs& a, hipStream_t st) {
   return launch_gemm_bf16_v2<false, false, EPI_STORE>(a, a.splitk_ws, st);
 }
 
-// Estimated time (microseconds, the cost model of v2_plan) of one weight-gradient GEMM launched on its own with the
-// tail split, and of a set of them launched as one group without a split.
-static double wgrad_cost_alone(const GemmArgs& a) {
-  const V2Plan p = v2_plan(a.M, a.N, a.K, true);
-  const int V2_CUS = gemm_cu_count();
-  const int nk = v2_slices(a.K);
-  const int rounds_full = (p.full_tiles + V2_CUS - 1) / V2_CUS;
-  const double fixed = v2_tile_fixed(V2_B), per_slice = v2_slice_cost(V2_B);
-  double t = rounds_full * (fixed + per_slice * nk);
-  if (p.tail_tiles) {
-    const double traffic = (double)p.tail_tiles * p.split * (V2_B * V2_B * 4.0) / 5.0e6;
-    t += fixed + per_slice * ((nk + p.split - 1) / p.split) + traffic + v2_fixup_cost(traffic);
-  }
-  return t + 2.0;     // launch + drain of the GEMM kernel itself
+// Estimated time (microseconds) of the tiles of all problems in one launch without a k-split.
+static double group_cost(const GemmArgs* probs, int n, int bn) {
+  const int bm = bn == V2_SMALL ? V2_SMALL : V2_B, cus = gemm_cu_count(), per_round = bn == V2_SMALL ? 2 * cus : cus;
+  int tiles = 0;
+  for (int q = 0; q < n; ++q) tiles += v2_tiles(probs[q], bm, bn);
+  const int nk = v2_slices(probs[0].K), rem = tiles % per_round;
+  return (tiles / per_round) * v2_tile_cost(bn, nk, false) + (rem ? v2_tile_cost(bn, nk, tiles <= cus) : 0.0);
 }
 
-// The weight gradients of a layer shard (same operand layout, same k = tokens).  One grouped launch when the cost
-// model says the shared last round beats the separate launches with their k-splits; separate launches otherwise.
+// The weight gradients of a layer shard (same operand layout, same k = tokens).  One grouped launch, in the tile size that
+// fills the chip better, when the cost model says the shared last round beats the separate launches with their
+// k-splits; separate launches otherwise.
 hipError_t launch_gemm_bf16_wgrad_group(const GemmArgs* probs, int n, float* splitk_ws, hipStream_t st) {
   bool groupable = n >= 2 && n <= kMaxGroup;
   double alone = 0.0;
-  int tiles = 0;
   for (int q = 0; q < n && groupable; ++q) {
     groupable = probs[q].epi == EPI_STORE && probs[q].bias == nullptr && probs[q].K == probs[0].K;
-    alone += wgrad_cost_alone(probs[q]);
-    tiles += v2_tiles(probs[q]);
+    const int M = probs[q].M, N = probs[q].N, K = probs[q].K;
+    alone += v2_plan(M, N, K, true, v2_pick_bn<false, false, EPI_STORE>(M, N, K, true)).cost + 2.0;   // + launch and drain
   }
   if (groupable) {
-    const int nk = v2_slices(probs[0].K);
-    const int V2_CUS = gemm_cu_count();
-    const double grouped = ((tiles + V2_CUS - 1) / V2_CUS) * (v2_tile_fixed(V2_B) + v2_slice_cost(V2_B) * nk) + 2.0;
+    const double big = group_cost(probs, n, V2_B), small = group_cost(probs, n, V2_SMALL);
+    const int forced = gemm_v2_forced_bn();
+    const bool use_small = forced ? forced == V2_SMALL : small < big;
     static const bool off = [] { const char* e = getenv("MLM_GEMM_GROUP"); return e && atoi(e) == 0; }();
-    if (!off && grouped < alone)
-      return probs[0].K % (2 * V2_BK) ? launch_gemm_bf16_v2_group<false, false, true>(probs, n, st)
-                                      : launch_gemm_bf16_v2_group<false, false, false>(probs, n, st);
+    if (!off && (use_small ? small : big) + 2.0 < alone) {
+      const bool rag = probs[0].K % (2 * V2_BK) != 0;
+      int tiles = 0;
+      for (int q = 0; q < n; ++q) tiles += v2_tiles(probs[q], V2_SMALL, V2_SMALL);
+      if (use_small && tiles <= gemm_cu_count())
+        return rag ? launch_gemm_bf16_v2_group<false, false, V2_SMALL, true, true>(probs, n, st)
+                   : launch_gemm_bf16_v2_group<false, false, V2_SMALL, false, true>(probs, n, st);
+      if (use_small)
+        return rag ? launch_gemm_bf16_v2_group<false, false, V2_SMALL, true, false>(probs, n, st)
+                   : launch_gemm_bf16_v2_group<false, false, V2_SMALL, false, false>(probs, n, st);
+      return rag ? launch_gemm_bf16_v2_group<false, false, V2_B, true, false>(probs, n, st)
+                 : launch_gemm_bf16_v2_group<false, false, V2_B, false, false>(probs, n, st);
+    }
   }
   for (int q = 0; q < n; ++q) {
     GemmArgs a = probs[q];
