@@ -124,14 +124,27 @@ struct ATileSrc {
 // Workgroup = 128 queries of one (batch, head), 4 waves of 32 queries.  K and V tiles of 64 keys stream through a
 // three-stage LDS ring filled by DMA two tiles ahead; per tile: S^T = K Q^T (12 MFMAs at d = 96), online softmax in
 // registers, O^T += V^T P^T with V read through the transposing LDS loads (12 MFMAs).  One barrier per tile.
-// Forward and dQ run TWO wave groups (8 waves) per 128 owned rows: group g takes the streamed tiles 2j + g, each
-// group has its own DMA ring, and the groups' partial results are merged through LDS at the end.  That halves the
-// serial chain of the longest (causal) blocks and puts two waves on every SIMD, so one wave's exp2 / VALU work
-// overlaps the other's MFMAs.  Ring stages per group: 3, or 2 at d = 128 (LDS budget).  d = 192 keeps ONE group: its
-// 24-KB tiles leave no LDS for a second ring, and its accumulators need more than the 256 registers per lane that
-// two waves per SIMD allow.
-template <int D> constexpr int attn_groups() { return D > 128 ? 1 : 2; }
-template <int D> constexpr int group_stages() { return D == 128 ? 2 : 3; }
+// How the waves of a forward / dQ workgroup divide its rows and the streamed tiles: RW waves along the rows (32 each), KG
+// waves along the 64 keys of a tile, NG groups of RW x KG = 4 waves that take every NG-th tile through a DMA ring of their
+// own.  The partial results of the KG NG waves that own the same rows are merged through LDS at the end.
+//   WIDE  (4 x 1 x 1): no merge, and two workgroups fit a compute unit (d <= 128), so that one's first copies and last
+//         stores run under the other's steps: for launches of more than one workgroup per compute unit.
+//   PAIR  (4 x 1 x 2): halves the serial chain of the longest (causal) blocks and puts two waves on every SIMD where a
+//         compute unit has one workgroup.  d = 192 has no LDS for the second ring.
+//   SPLIT (2 x 2 x NG): 64 rows per workgroup, for launches that leave compute units without one; each wave multiplies
+//         half of a tile.
+enum AttnMode { ATTN_WIDE, ATTN_PAIR, ATTN_SPLIT };
+template <int D, int MODE> struct AttnSplit {
+  static constexpr int RW = MODE == ATTN_SPLIT ? 2 : 4, KG = ANW / RW;
+  static constexpr int NG = MODE == ATTN_WIDE || D > 128 ? 1 : 2;
+  static constexpr int NST = D == 128 ? 2 : 3;                       // ring stages per group (LDS budget)
+  static constexpr int NT = NG * ANT, G = KG * NG;                   // threads; waves that share a row
+  static constexpr int MINW = NG == 2 || (MODE == ATTN_WIDE && D <= 128) ? 2 : 1;   // waves per SIMD the registers must allow
+  static constexpr size_t RING = (size_t)NG * NST * 2 * ATILE * D * 2;
+  static constexpr size_t PARK = (size_t)(G - 1) * RW * (D / 2 + 2) * 64 * 4;
+  static constexpr size_t LDS = RING > PARK ? RING : PARK;
+  static_assert(LDS <= 160 * 1024, "LDS budget");
+};
 template <int D> constexpr int dkv_dsplit() { return D >= 128 ? 2 : 1; }
 // dK/dV: two wave groups (alternate query tiles, merged through LDS at the end) for the head sizes whose registers
 // allow two waves per SIMD once the wave's own K / V rows are kept in LDS instead of registers; ring stages per group
@@ -142,17 +155,19 @@ template <int D> constexpr bool dkv_own_lds() { return D <= 96; }    // d = 128:
 
 // (two waves per SIMD requested: with at most 256 registers per lane the MFMA accumulators live in ordinary VGPRs, so
 // the softmax arithmetic needs no accumulator-register moves)
-template <int D, bool DROP>
-__global__ __launch_bounds__(attn_groups<D>() * ANT) void attn_fwd_bf16_kernel(AttnArgs a) {
+template <int D, bool DROP, int MODE>
+__global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW)) void attn_fwd_bf16_kernel(AttnArgs a) {
   typedef ATile<D> TL;
-  constexpr int BQ = 32 * ANW, STAGE = 2 * TL::BYTES, LPT = 2 * TL::QPW;   // LPT: copies per tile and wave (K + V)
-  constexpr int NST = group_stages<D>(), NG = attn_groups<D>();
+  typedef AttnSplit<D, MODE> SP;
+  constexpr int RW = SP::RW, KG = SP::KG, NK = 2 / KG;               // NK: 32-key halves of a tile per wave
+  constexpr int BQ = 32 * RW, STAGE = 2 * TL::BYTES, LPT = 2 * TL::QPW;   // LPT: copies per tile and wave (K + V)
+  constexpr int NST = SP::NST, NG = SP::NG;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
   // wave-uniform values must be known as such: the mask test below is a scalar branch
-  const int grp = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);    // wave group: 0 takes the even tiles, 1 the odd tiles
-  const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);   // wave inside its group: 32 queries
-  const int wave_u = wave;
+  const int grp = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);    // wave group: takes the tiles NG j + grp
+  const int wave_u = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);   // wave inside its group (copies a quarter of a tile)
+  const int wave = wave_u % RW, kh = wave_u / RW;  // its 32 queries, and its 32 keys of a tile (KG = 2)
   const int nqb = (a.s + BQ - 1) / BQ;
   const AttnBlock blk = attn_block(nqb, a.hl, a.b);
   if (!blk.valid) return;
@@ -183,7 +198,7 @@ __global__ __launch_bounds__(attn_groups<D>() * ANT) void attn_fwd_bf16_kernel(A
   const bf16* Kb = base + (a.hl + hd) * D;
   const bf16* Vb = base + (2 * a.hl + hd) * D;
   ATileSrc<D> src;
-  src.init(wave, lane);
+  src.init(wave_u, lane);
   unsigned char* ring = lds_raw + grp * (NST * STAGE);   // this group's ring
   const uint32_t lds0 = lds_offset_of(ring);
   const int njt = (nt + NG - 1) / NG;              // steps: group g handles tile NG j + g in step j (if it exists)
@@ -198,7 +213,7 @@ __global__ __launch_bounds__(attn_groups<D>() * ANT) void attn_fwd_bf16_kernel(A
   int stage = 0;
   for (int j = 0; j < njt; ++j) {
     const int t = NG * j + grp;
-    const int k0 = t * ATILE;
+    const int k0 = t * ATILE, kw0 = k0 + (KG == 2 ? 32 * kh : 0);    // the tile's first key, this wave's first key
     wait_vmcnt<LPT*(NST - 2)>();                   // this wave's copies of step j have landed; step j + 1 may be in flight
     __builtin_amdgcn_s_barrier();                 // everyone's have; and everyone is done with step j - 1
     // The copies that re-arm the stage of step j - 1 (= stage of step j + NST - 1) are NOT issued here in one burst:
@@ -214,16 +229,18 @@ __global__ __launch_bounds__(attn_groups<D>() * ANT) void attn_fwd_bf16_kernel(A
     const unsigned char* sV = sK + TL::BYTES;
     stage = stage == NST - 1 ? 0 : stage + 1;
     constexpr bool SPREAD = D <= 96;
-    const bool live = t < nt && !(a.causal && k0 > qw0 + 31);   // else: no such tile / entirely above this wave's diagonal (wave-uniform)
+    // else: no such tile / all padding / entirely above this wave's diagonal (wave-uniform); key kw0 of a live tile is
+    // allowed for every query of the wave
+    const bool live = t < nt && kw0 < klen && !(a.causal && kw0 > qw0 + 31);
     if (!SPREAD || !live) {
       src.issue(Kb, ld, tc_next, a.s, dstK, wave_u);
       src.issue(Vb, ld, tc_next, a.s, dstV, wave_u);
     }
     if (!live) continue;
-    floatx16 sacc[2];
+    floatx16 sacc[NK];
     float lsum_t = 0.f;
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
+    for (int kt = 0; kt < NK; ++kt)
 #pragma unroll
       for (int e = 0; e < 16; ++e) sacc[kt][e] = 0.f;
     // the two 32-key halves are independent accumulation chains: alternate them so that a dependent MFMA never
@@ -231,31 +248,31 @@ __global__ __launch_bounds__(attn_groups<D>() * ANT) void attn_fwd_bf16_kernel(A
 #pragma unroll
     for (int ks = 0; ks < D / 16; ++ks)
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-        sacc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_kc(sK, kt * 32, ks, lane), qf[ks], sacc[kt], 0, 0, 0);
+      for (int kt = 0; kt < NK; ++kt)
+        sacc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_kc(sK, (KG == 2 ? kh : kt) * 32, ks, lane), qf[ks], sacc[kt], 0, 0, 0);
     // raw scores s; probabilities p = exp2(s * sc - max) with the scale folded into one fma per element
-    const bool need_mask = (a.causal && k0 + ATILE - 1 > qw0) || (k0 + ATILE > klen);   // wave-uniform
+    const bool need_mask = (a.causal && kw0 + 32 * NK - 1 > qw0) || (kw0 + 32 * NK > klen);   // wave-uniform
     float mt = -INFINITY;
     if (need_mask) {
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
+      for (int kt = 0; kt < NK; ++kt)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          const int key = k0 + kt * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
+          const int key = kw0 + kt * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
           const bool off = key >= klen || (a.causal && key > qi);
           sacc[kt][e] = off ? -INFINITY : sacc[kt][e];
           mt = fmaxf(mt, sacc[kt][e]);
         }
     } else {
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
+      for (int kt = 0; kt < NK; ++kt)
 #pragma unroll
         for (int e = 0; e < 16; ++e) mt = fmaxf(mt, sacc[kt][e]);
     }
     mt = fmaxf(mt, __shfl_xor(mt, 32, 64)) * sc;
     const float mn = fmaxf(m, mt);               // finite from the first tile on: key 0 is allowed for every query
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
+    for (int kt = 0; kt < NK; ++kt)
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const float p = __builtin_amdgcn_exp2f(fmaf(sacc[kt][e], sc, -mn));
@@ -263,8 +280,8 @@ __global__ __launch_bounds__(attn_groups<D>() * ANT) void attn_fwd_bf16_kernel(A
         lsum_t += p;
         if (SPREAD) {
 #pragma unroll
-          for (int c = 0; c < LPT; ++c)                    // copy c after element (32 c + 16) / LPT of the 32
-            if (kt * 16 + e == (32 * c + 16) / LPT) {
+          for (int c = 0; c < LPT; ++c)                    // copy c after element (16 NK c + 8 NK) / LPT of the 16 NK
+            if (kt * 16 + e == (16 * NK * c + 8 * NK) / LPT) {
               if (c < TL::QPW) src.issue_one(Kb, ld, tc_next, a.s, dstK, wave_u, c);
               else src.issue_one(Vb, ld, tc_next, a.s, dstV, wave_u, c - TL::QPW);
             }
@@ -283,52 +300,59 @@ __global__ __launch_bounds__(attn_groups<D>() * ANT) void attn_fwd_bf16_kernel(A
     lsum += lsum_t;
     if (DROP) {
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-        uint32_t word = 0;                       // this lane's 16 of the 32 keep bits of keys k0 + 32 kt ..
+      for (int kt = 0; kt < NK; ++kt) {
+        uint32_t word = 0;                       // this lane's 16 of the 32 keep bits of keys kw0 + 32 kt ..
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const uint32_t k4 = drop_keep4(a.drop, (prow * a.s + k0 + kt * 32 + 8 * g + 4 * lh) >> 2);
+          const uint32_t k4 = drop_keep4(a.drop, (prow * a.s + kw0 + kt * 32 + 8 * g + 4 * lh) >> 2);
 #pragma unroll
           for (int e = 0; e < 4; ++e) sacc[kt][4 * g + e] = ((k4 >> e) & 1u) ? sacc[kt][4 * g + e] : 0.f;
           word |= k4 << (8 * g + 4 * lh);
         }
         word |= __shfl_xor(word, 32, 64);        // the other half-wave holds the other 16 bits
-        if (lh == kt && qi < a.s) a.keep_bits[prow * a.keep_pitch + (k0 >> 5) + kt] = word;
+        if (lh == kt && qi < a.s) a.keep_bits[prow * a.keep_pitch + (kw0 >> 5) + kt] = word;
       }
     }
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+    for (int c = 0; c < 2 * NK; ++c) {
       const bf16x8 pf = pack8(sacc[c >> 1], 8 * (c & 1));
 #pragma unroll
       for (int dt = 0; dt < D / 32; ++dt)
-        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_tr(sV, c, dt * 32, lane), pf, o[dt], 0, 0, 0);
+        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_tr(sV, (KG == 2 ? 2 * kh : 0) + c, dt * 32, lane), pf, o[dt], 0, 0, 0);
     }
   }
   wait_vmcnt<0>();                                // copies still in flight target this workgroup's LDS
-  // merge the two groups' (m, l, O): group 1 parks its values in LDS ([wave][value][lane]: conflict-free)
-  if (NG == 2) {
+  // merge the (m, l, O) of the waves that own the same rows: all but the first park theirs in LDS ([value][lane] per wave:
+  // conflict-free)
+  if (SP::G > 1) {
     __syncthreads();
     constexpr int NR = D / 2 + 2;
+    const int part = kh + KG * grp;
     float* park = reinterpret_cast<float*>(lds_raw) + (size_t)wave * NR * 64 + lane;
-    if (grp == 1) {
+    constexpr int PSTEP = RW * NR * 64;
+    if (part > 0) {
+      float* dst = park + (part - 1) * PSTEP;
 #pragma unroll
       for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) park[(dt * 16 + e) * 64] = o[dt][e];
-      park[(D / 2) * 64] = m;
-      park[(D / 2 + 1) * 64] = lsum;
+        for (int e = 0; e < 16; ++e) dst[(dt * 16 + e) * 64] = o[dt][e];
+      dst[(D / 2) * 64] = m;
+      dst[(D / 2 + 1) * 64] = lsum;
     }
     __syncthreads();
-    if (grp == 1) return;
-    const float m1 = park[(D / 2) * 64], l1 = park[(D / 2 + 1) * 64];
-    const float mn = fmaxf(m, m1);                // group 0 always has tile 0: finite
-    const float c0 = __builtin_amdgcn_exp2f(m - mn), c1 = __builtin_amdgcn_exp2f(m1 - mn);
-    lsum = lsum * c0 + l1 * c1;
+    if (part > 0) return;
 #pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt)
+    for (int p = 0; p < SP::G - 1; ++p, park += PSTEP) {
+      const float m1 = park[(D / 2) * 64], l1 = park[(D / 2 + 1) * 64];
+      const float mn = fmaxf(m, m1);              // part 0 always has key 0: finite
+      const float c0 = __builtin_amdgcn_exp2f(m - mn), c1 = __builtin_amdgcn_exp2f(m1 - mn);
+      lsum = lsum * c0 + l1 * c1;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) o[dt][e] = o[dt][e] * c0 + park[(dt * 16 + e) * 64] * c1;
-    m = mn;
+      for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[dt][e] = o[dt][e] * c0 + park[(dt * 16 + e) * 64] * c1;
+      m = mn;
+    }
   }
   lsum += __shfl_xor(lsum, 32, 64);
   if (qi < a.s) {
@@ -352,14 +376,18 @@ __global__ __launch_bounds__(attn_groups<D>() * ANT) void attn_fwd_bf16_kernel(A
 // P = exp2(S sc - lse), dS = P o (dP - delta), dQ^T += K^T dS^T with K read a second time through the transposing
 // loads.  delta_i = sum_d dO_id O_id is computed here from the rows the lanes already hold and stored for the
 // dK/dV kernel, which runs after this one.
-template <int D, bool DROP>
-__global__ __launch_bounds__(attn_groups<D>() * ANT) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
+template <int D, bool DROP, int MODE>
+__global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW)) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
   typedef ATile<D> TL;
-  constexpr int BQ = 32 * ANW, STAGE = 2 * TL::BYTES, LPT = 2 * TL::QPW, NST = group_stages<D>(), NG = attn_groups<D>();
+  typedef AttnSplit<D, MODE> SP;
+  constexpr int RW = SP::RW, KG = SP::KG, NK = 2 / KG;
+  constexpr int BQ = 32 * RW, STAGE = 2 * TL::BYTES, LPT = 2 * TL::QPW, NST = SP::NST, NG = SP::NG;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
-  const int grp = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);   // wave group: even / odd tiles
-  const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);   // wave inside its group (uniform: scalar mask branches)
+  const int grp = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);   // wave group: takes the tiles NG j + grp
+  const int wave_u = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);   // wave inside its group (uniform: scalar mask branches)
+  const int wave = wave_u % RW, kh = wave_u / RW;  // its 32 queries, and its 32 keys of a tile (KG = 2)
+  const int part = kh + KG * grp;
   const int nqb = (a.s + BQ - 1) / BQ;
   const AttnBlock blk = attn_block(nqb, a.hl, a.b);
   if (!blk.valid) return;
@@ -389,7 +417,7 @@ __global__ __launch_bounds__(attn_groups<D>() * ANT) void attn_bwd_dq_bf16_kerne
   }
   const float lse2 = a.lse[((size_t)bi * a.hl + hd) * a.s + qc] * kLog2e;
   const uint32_t* kbrow = DROP ? a.keep_bits + (((size_t)bi * a.hl + hd) * a.s + qc) * a.keep_pitch : nullptr;
-  if (grp == 0 && lh == 0 && qi < a.s) {          // for the dK/dV kernel: [0] delta, [1] log-sum-exp in log2 units
+  if (part == 0 && lh == 0 && qi < a.s) {          // for the dK/dV kernel: [0] delta, [1] log-sum-exp in log2 units
     a.delta[((size_t)bi * a.hl + hd) * a.s + qi] = dl;
     a.delta[(size_t)a.b * a.hl * a.s + ((size_t)bi * a.hl + hd) * a.s + qi] = lse2;
   }
@@ -406,20 +434,20 @@ __global__ __launch_bounds__(attn_groups<D>() * ANT) void attn_bwd_dq_bf16_kerne
   const bf16* Kb = base + (a.hl + hd) * D;
   const bf16* Vb = base + (2 * a.hl + hd) * D;
   ATileSrc<D> src;
-  src.init(wave, lane);
+  src.init(wave_u, lane);
   unsigned char* ring = lds_raw + grp * (NST * STAGE);
   const uint32_t lds0 = lds_offset_of(ring);
   const int njt = (nt + NG - 1) / NG;
 #pragma unroll
   for (int t = 0; t < NST - 1; ++t) {
     const int tc = min(NG * t + grp, nt - 1) * ATILE;
-    src.issue(Kb, ld, tc, a.s, lds0 + t * STAGE, wave);
-    src.issue(Vb, ld, tc, a.s, lds0 + t * STAGE + TL::BYTES, wave);
+    src.issue(Kb, ld, tc, a.s, lds0 + t * STAGE, wave_u);
+    src.issue(Vb, ld, tc, a.s, lds0 + t * STAGE + TL::BYTES, wave_u);
   }
   int stage = 0;
   for (int j = 0; j < njt; ++j) {
     const int t = NG * j + grp;
-    const int k0 = t * ATILE;
+    const int k0 = t * ATILE, kw0 = k0 + (KG == 2 ? 32 * kh : 0);
     wait_vmcnt<LPT*(NST - 2)>();
     __builtin_amdgcn_s_barrier();
     // the copies that re-arm the stage of step j - 1 are issued one at a time inside the element-wise pass below
@@ -428,43 +456,44 @@ __global__ __launch_bounds__(attn_groups<D>() * ANT) void attn_bwd_dq_bf16_kerne
     const int pst = stage == 0 ? NST - 1 : stage - 1;
     const int tc_next = min(t + NG * (NST - 1), nt - 1) * ATILE;
     const uint32_t dstK = lds0 + pst * STAGE, dstV = dstK + TL::BYTES;
-    auto copy_after = [&](int el) {                  // el: element index 0..31 of the pass (compile time after unrolling)
+    auto copy_after = [&](int el) {                  // el: element index 0 .. 16 NK - 1 of the pass (compile time after unrolling)
 #pragma unroll
       for (int c = 0; c < LPT; ++c)
-        if (el == (32 * c + 16) / LPT) {
-          if (c < TL::QPW) src.issue_one(Kb, ld, tc_next, a.s, dstK, wave, c);
-          else src.issue_one(Vb, ld, tc_next, a.s, dstV, wave, c - TL::QPW);
+        if (el == (16 * NK * c + 8 * NK) / LPT) {
+          if (c < TL::QPW) src.issue_one(Kb, ld, tc_next, a.s, dstK, wave_u, c);
+          else src.issue_one(Vb, ld, tc_next, a.s, dstV, wave_u, c - TL::QPW);
         }
     };
     const unsigned char* sK = ring + stage * STAGE;
     const unsigned char* sV = sK + TL::BYTES;
     stage = stage == NST - 1 ? 0 : stage + 1;
-    const bool live = t < nt && !(a.causal && k0 > qw0 + 31);
+    const bool live = t < nt && kw0 < klen && !(a.causal && kw0 > qw0 + 31);
     if (!SPREAD || !live) {
-      src.issue(Kb, ld, tc_next, a.s, dstK, wave);
-      src.issue(Vb, ld, tc_next, a.s, dstV, wave);
+      src.issue(Kb, ld, tc_next, a.s, dstK, wave_u);
+      src.issue(Vb, ld, tc_next, a.s, dstV, wave_u);
     }
     if (!live) continue;
-    uint2 kw = make_uint2(0xFFFFFFFFu, 0xFFFFFFFFu);          // keep bits of this query row, keys k0 .. k0 + 63
-    if (DROP) kw = *reinterpret_cast<const uint2*>(kbrow + (k0 >> 5));
-    floatx16 sacc[2], pacc[2];
+    uint2 kw = make_uint2(0xFFFFFFFFu, 0xFFFFFFFFu);          // keep bits of this query row, this wave's keys
+    if (DROP && KG == 1) kw = *reinterpret_cast<const uint2*>(kbrow + (k0 >> 5));
+    if (DROP && KG == 2) kw.x = kbrow[kw0 >> 5];
+    floatx16 sacc[NK], pacc[NK];
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
+    for (int kt = 0; kt < NK; ++kt)
 #pragma unroll
       for (int e = 0; e < 16; ++e) { sacc[kt][e] = 0.f; pacc[kt][e] = 0.f; }
     // four independent accumulation chains, interleaved
 #pragma unroll
     for (int ks = 0; ks < D / 16; ++ks)
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-        sacc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_kc(sK, kt * 32, ks, lane), qf[ks], sacc[kt], 0, 0, 0);   // S^T[key][query]
-        pacc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_kc(sV, kt * 32, ks, lane), dof[ks], pacc[kt], 0, 0, 0);  // dP^T[key][query]
+      for (int kt = 0; kt < NK; ++kt) {
+        sacc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_kc(sK, (KG == 2 ? kh : kt) * 32, ks, lane), qf[ks], sacc[kt], 0, 0, 0);   // S^T[key][query]
+        pacc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_kc(sV, (KG == 2 ? kh : kt) * 32, ks, lane), dof[ks], pacc[kt], 0, 0, 0);  // dP^T[key][query]
       }
-    const bool need_mask = (a.causal && k0 + ATILE - 1 > qw0) || (k0 + ATILE > klen);   // wave-uniform
+    const bool need_mask = (a.causal && kw0 + 32 * NK - 1 > qw0) || (kw0 + 32 * NK > klen);   // wave-uniform
     if (DROP) {
       // gradient w.r.t. the undropped probability: keep o dP / (1 - p)
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
+      for (int kt = 0; kt < NK; ++kt) {
         const uint32_t w = (kt == 0 ? kw.x : kw.y) >> (4 * lh);
 #pragma unroll
         for (int e = 0; e < 16; ++e)
@@ -473,10 +502,10 @@ __global__ __launch_bounds__(attn_groups<D>() * ANT) void attn_bwd_dq_bf16_kerne
     }
     if (need_mask) {
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
+      for (int kt = 0; kt < NK; ++kt)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          const int key = k0 + kt * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
+          const int key = kw0 + kt * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
           const bool off = key >= klen || (a.causal && key > qi);
           const float p = off ? 0.f : __builtin_amdgcn_exp2f(fmaf(sacc[kt][e], sc, -lse2));
           sacc[kt][e] = p * (pacc[kt][e] - dl);     // dS^T
@@ -484,7 +513,7 @@ __global__ __launch_bounds__(attn_groups<D>() * ANT) void attn_bwd_dq_bf16_kerne
         }
     } else {
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
+      for (int kt = 0; kt < NK; ++kt)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           sacc[kt][e] = __builtin_amdgcn_exp2f(fmaf(sacc[kt][e], sc, -lse2)) * (pacc[kt][e] - dl);
@@ -492,30 +521,35 @@ __global__ __launch_bounds__(attn_groups<D>() * ANT) void attn_bwd_dq_bf16_kerne
         }
     }
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+    for (int c = 0; c < 2 * NK; ++c) {
       const bf16x8 dsf = pack8(sacc[c >> 1], 8 * (c & 1));
 #pragma unroll
       for (int dt = 0; dt < D / 32; ++dt)
-        dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_tr(sK, c, dt * 32, lane), dsf, dq[dt], 0, 0, 0);   // dQ^T[dcol][query]
+        dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_tr(sK, (KG == 2 ? 2 * kh : 0) + c, dt * 32, lane), dsf, dq[dt], 0, 0, 0);   // dQ^T[dcol][query]
     }
   }
   wait_vmcnt<0>();
-  // dQ = group 0's sum + group 1's sum (group 1 parks its accumulators in LDS: [wave][value][lane])
-  if (NG == 2) {
+  // dQ = the sum over the waves that own the same rows, in a fixed order (all but the first park their accumulators in
+  // LDS: [value][lane] per wave)
+  if (SP::G > 1) {
     __syncthreads();
     float* park = reinterpret_cast<float*>(lds_raw) + (size_t)wave * (D / 2) * 64 + lane;
-    if (grp == 1) {
+    constexpr int PSTEP = RW * (D / 2) * 64;
+    if (part > 0) {
+      float* dst = park + (part - 1) * PSTEP;
 #pragma unroll
       for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) park[(dt * 16 + e) * 64] = dq[dt][e];
+        for (int e = 0; e < 16; ++e) dst[(dt * 16 + e) * 64] = dq[dt][e];
     }
     __syncthreads();
-    if (grp == 1) return;
+    if (part > 0) return;
 #pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt)
+    for (int p = 0; p < SP::G - 1; ++p, park += PSTEP)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) dq[dt][e] += park[(dt * 16 + e) * 64];
+      for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) dq[dt][e] += park[(dt * 16 + e) * 64];
   }
   if (qi < a.s) {
     bf16* orow = (bf16*)a.dqkv + ((size_t)bi * a.s + qi) * ld + hd * D;
@@ -751,17 +785,55 @@ __global__ __launch_bounds__(dkv_groups<D>() * ANT) void attn_bwd_dkv_bf16_kerne
 // ------------------------------------------------------------------------------------------ launchers
 bool attn_bf16_supported(int d) { return d == 64 || d == 96 || d == 128 || d == 192; }
 
+// By the number of 128-row workgroups.  Forward / dQ kernels measured as WIDE, PAIR, SPLIT (us, causal, s = 1024 unless
+// noted): d = 96: 80 workgroups 22.9 / 25.2, 21.1 / 24.5, 18.6 / 19.3; 128 23.2 / 26.8, 22.6 / 25.7, 18.3 / 20.5; 256
+// 25.5 / 28.7, 23.8 / 29.1, 32.3 / 34.9; 384 37.6 / 42.4, 37.3 / 45.4, 43.7 / 48.9; 1024 65 / 77, 83 / 102, 109 / 124.
+// d = 64: 144 19.7 / 20.8, 16.7 / 19.9, 18.9 / 21.3; 320 of s = 512 without a mask 16.8 / 20.1, 21.4 / 25.6, 25.6 / 28.6.
+// d = 128: 64 25.3 / 36.9, 23.8 / 30.6, 20.6 / 24.5; 192 27.0 / 38.8, 25.6 / 32.8, 31.0 / 38.6; 768 62 / 85, 72 / 97, 97 / 122.
+// d = 192: 128 42.4 / 55.9, -, 34.7 / 39.1; 512 86 / 115, -, 108 / 125.
+template <int D>
+static AttnMode attn_mode(const AttnArgs& a) {
+  const int wgs = (a.s + 127) / 128 * a.hl * a.b, cus = gemm_cu_count();
+  if (2 * wgs <= cus) return ATTN_SPLIT;
+  return D > 128 || wgs > cus ? ATTN_WIDE : ATTN_PAIR;
+}
+
+template <int D, bool DROP, int MODE>
+static hipError_t launch_fwd_m(const AttnArgs& a, hipStream_t st) {
+  typedef AttnSplit<D, MODE> SP;
+  static LdsAttrOnce attr;
+  if (SP::LDS > 64 * 1024)
+    if (hipError_t e = attr.ensure((const void*)attn_fwd_bf16_kernel<D, DROP, MODE>, (int)SP::LDS); e != hipSuccess) return e;
+  const dim3 grid = attn_grid((a.s + 32 * SP::RW - 1) / (32 * SP::RW), a.hl, a.b);
+  hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, DROP, MODE>), grid, dim3(SP::NT), SP::LDS, st, a);
+  return hipGetLastError();
+}
+
+template <int D, bool DROP, int MODE>
+static hipError_t launch_dq_m(const AttnArgs& a, hipStream_t st) {
+  typedef AttnSplit<D, MODE> SP;
+  static LdsAttrOnce attr;
+  if (SP::LDS > 64 * 1024)
+    if (hipError_t e = attr.ensure((const void*)attn_bwd_dq_bf16_kernel<D, DROP, MODE>, (int)SP::LDS); e != hipSuccess) return e;
+  const dim3 grid = attn_grid((a.s + 32 * SP::RW - 1) / (32 * SP::RW), a.hl, a.b);
+  hipLaunchKernelGGL((attn_bwd_dq_bf16_kernel<D, DROP, MODE>), grid, dim3(SP::NT), SP::LDS, st, a);
+  return hipGetLastError();
+}
+
 template <int D, bool DROP>
 static hipError_t launch_fwd_dd(const AttnArgs& a, hipStream_t st) {
-  const size_t lds = (size_t)attn_groups<D>() * group_stages<D>() * 2 * ATile<D>::BYTES;
-  if (lds > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute((const void*)attn_fwd_bf16_kernel<D, DROP>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  const dim3 grid = attn_grid((a.s + 32 * ANW - 1) / (32 * ANW), a.hl, a.b);
-  hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, DROP>), grid, dim3(attn_groups<D>() * ANT), lds, st, a);
-  return hipGetLastError();
+  const AttnMode m = attn_mode<D>(a);
+  if constexpr (D <= 128)
+    if (m == ATTN_PAIR) return launch_fwd_m<D, DROP, ATTN_PAIR>(a, st);
+  return m == ATTN_SPLIT ? launch_fwd_m<D, DROP, ATTN_SPLIT>(a, st) : launch_fwd_m<D, DROP, ATTN_WIDE>(a, st);
+}
+
+template <int D, bool DROP>
+static hipError_t launch_dq_dd(const AttnArgs& a, hipStream_t st) {
+  const AttnMode m = attn_mode<D>(a);
+  if constexpr (D <= 128)
+    if (m == ATTN_PAIR) return launch_dq_m<D, DROP, ATTN_PAIR>(a, st);
+  return m == ATTN_SPLIT ? launch_dq_m<D, DROP, ATTN_SPLIT>(a, st) : launch_dq_m<D, DROP, ATTN_WIDE>(a, st);
 }
 
 template <int D>
@@ -772,16 +844,7 @@ static hipError_t launch_fwd_d(const AttnArgs& a, hipStream_t st) {
 template <int D, bool DROP>
 static hipError_t launch_bwd_dd(const AttnArgs& a, hipStream_t st) {
   const int nblk = (a.s + 32 * ANW - 1) / (32 * ANW);
-  const dim3 grid = attn_grid(nblk, a.hl, a.b);
-  const size_t lds_q = (size_t)attn_groups<D>() * group_stages<D>() * 2 * ATile<D>::BYTES;
-  hipError_t e;
-  if (lds_q > 64 * 1024) {
-    e = hipFuncSetAttribute((const void*)attn_bwd_dq_bf16_kernel<D, DROP>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lds_q);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL((attn_bwd_dq_bf16_kernel<D, DROP>), grid, dim3(attn_groups<D>() * ANT), lds_q, st, a);
-  e = hipGetLastError();
+  hipError_t e = launch_dq_dd<D, DROP>(a, st);
   if (e != hipSuccess) return e;
   constexpr int NGK = dkv_groups<D>(), NSK = dkv_stages<D>();
   constexpr size_t kStageKv = 2 * ATile<D>::BYTES + 2 * ATILE * 4;
@@ -791,11 +854,9 @@ static hipError_t launch_bwd_dd(const AttnArgs& a, hipStream_t st) {
   static_assert((size_t)NGK * NSK * (kStageKv + ATILE * 16) + kOwn <= 160 * 1024 && kPark <= 160 * 1024, "LDS budget");
   size_t lds_kv = (size_t)NGK * NSK * (kStageKv + (DROP ? ATILE * 16 : 0)) + kOwn;
   if (lds_kv < kPark) lds_kv = kPark;
-  if (lds_kv > 64 * 1024) {
-    e = hipFuncSetAttribute((const void*)attn_bwd_dkv_bf16_kernel<D, DROP>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lds_kv);
-    if (e != hipSuccess) return e;
-  }
+  static LdsAttrOnce attr;
+  if (lds_kv > 64 * 1024)
+    if (e = attr.ensure((const void*)attn_bwd_dkv_bf16_kernel<D, DROP>, (int)lds_kv); e != hipSuccess) return e;
   const dim3 grid_kv = attn_grid(nblk * dkv_dsplit<D>(), a.hl, a.b);
   hipLaunchKernelGGL((attn_bwd_dkv_bf16_kernel<D, DROP>), grid_kv, dim3(NGK * ANT), lds_kv, st, a);
   return hipGetLastError();
