@@ -14,35 +14,41 @@ namespace mlm {
 // rank(t) = #{t' : key[t'] < key[t]} + #{t' < t : key[t'] == key[t]}.
 // The T x T comparisons are split over blockIdx.y: block (x, y) counts, for its 256 tokens, the tokens t' of slice y
 // that precede them, and writes the partial count; embed_scatter_kernel adds the slices' counts (integers: exact in
-// any order) and scatters.  Keys are staged through LDS and compared four per LDS read.
-constexpr int kRankChunk = 1024;
+// any order) and scatters.  Keys are staged through LDS in chunks of 256 and compared four per LDS read.  A chunk other
+// than the block's own lies wholly before or after its tokens, so ties there need no look at the index: two vector
+// operations per comparison (8192 tokens: 31 -> 11 us with the index compared everywhere and 1024-token slices before).
+constexpr int kRankChunk = 256;
 
 __device__ __forceinline__ int embed_key(const int32_t* ids, int i, int v0, int Vl) {
   const int loc = ids[i] - v0;
   return (loc >= 0 && loc < Vl) ? loc : Vl;
 }
 
-__global__ __launch_bounds__(256) void embed_rank_kernel(int T, int nslice, const int32_t* __restrict__ ids, int v0,
-                                                         int Vl, int32_t* __restrict__ partial) {
+__global__ __launch_bounds__(kRankChunk) void embed_rank_kernel(int T, int nslice, const int32_t* __restrict__ ids, int v0,
+                                                                int Vl, int32_t* __restrict__ partial) {
   __shared__ __attribute__((aligned(16))) int32_t sk[kRankChunk];
-  const int t = blockIdx.x * 256 + threadIdx.x;
+  const int t0 = blockIdx.x * kRankChunk, t = t0 + threadIdx.x;
   const int my = t < T ? embed_key(ids, t, v0, Vl) : 0;
   // slice y covers chunks y, y + nslice, ... of kRankChunk tokens
   int rank = 0;
   for (int c0 = blockIdx.y * kRankChunk; c0 < T; c0 += nslice * kRankChunk) {
     __syncthreads();
-    for (int i = threadIdx.x; i < kRankChunk; i += 256)
-      sk[i] = c0 + i < T ? embed_key(ids, c0 + i, v0, Vl) : 0x7FFFFFFF;      // padding sorts after everything
+    const int i0 = c0 + threadIdx.x;
+    sk[threadIdx.x] = i0 < T ? embed_key(ids, i0, v0, Vl) : 0x7FFFFFFF;      // padding sorts after everything
     __syncthreads();
-    // tokens before t in index order win ties: in this chunk those are the first (t - c0) entries
-    const int before = min(max(t - c0, 0), kRankChunk);
-#pragma unroll 4
-    for (int i = 0; i < kRankChunk; i += 4) {
-      const int4 k = *reinterpret_cast<const int4*>(&sk[i]);
-      rank += (k.x < my || (k.x == my && i + 0 < before)) ? 1 : 0;
-      rank += (k.y < my || (k.y == my && i + 1 < before)) ? 1 : 0;
-      rank += (k.z < my || (k.z == my && i + 2 < before)) ? 1 : 0;
-      rank += (k.w < my || (k.w == my && i + 3 < before)) ? 1 : 0;
+    if (c0 != t0) {
+      const int lim = c0 < t0 ? my + 1 : my;          // tokens before t in index order win ties
+#pragma unroll 8
+      for (int i = 0; i < kRankChunk; i += 4) {
+        const int4 k = *reinterpret_cast<const int4*>(&sk[i]);
+        rank += k.x < lim ? 1 : 0;
+        rank += k.y < lim ? 1 : 0;
+        rank += k.z < lim ? 1 : 0;
+        rank += k.w < lim ? 1 : 0;
+      }
+    } else {
+#pragma unroll 8
+      for (int i = 0; i < kRankChunk; ++i) rank += sk[i] < my + (i < (int)threadIdx.x ? 1 : 0) ? 1 : 0;
     }
   }
   if (t < T) partial[(size_t)blockIdx.y * T + t] = rank;
@@ -57,47 +63,116 @@ __global__ __launch_bounds__(256) void embed_scatter_kernel(int T, int nslice, c
   perm[rank] = t;
 }
 
-// One wave per (sorted position, group of 64 rows of E_r): lane h reads E_r[h0 + h, loc] and the wave writes 64
-// consecutive elements of the token's row of the partial (zeros for a token outside the shard).  blockIdx.x (the
-// sorted positions) varies fastest, so the blocks in flight together share a row group -- 64 rows of E_r, which
-// stay in the L2 -- and walk its columns in increasing order.
+// Gather and its gradient work on tiles of 64 sorted positions x 64 rows of E_r, transposed through LDS: on the E_r side a
+// lane is a position, so a wave reads (or updates) 64 nearby columns of one row, and on the token side 16-byte vectors (or
+// lanes) run along the row of the partial (or dz0).  With a wave per position and row group, 98304 workgroups at 8192 tokens
+// x 3072 were bound by their launches and by 2-byte stores: 53 us forward and 65 us backward on one shard of eight, 26 and 39 now.
+constexpr int kEmbTile = 64;
+// (row stride of the LDS tile: an odd number of 32-bit words)
+template <typename T> constexpr int emb_stride() { return kEmbTile + 4 / (int)sizeof(T); }
+
+// out[t, :] = E_r[:, loc(t)], or zeros for a token outside the shard.  The positions of a tile that lie outside come last,
+// so a tile whose first one does is all zeros.
 template <typename T>
 __global__ __launch_bounds__(256) void embed_fwd_kernel(int Tn, int H, int Vl, int v0, const int32_t* __restrict__ ids,
                                                         const int32_t* __restrict__ perm, const T* __restrict__ E,
                                                         T* __restrict__ out) {
-  const int lane = threadIdx.x & 63;
-  const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int h = blockIdx.y * 64 + lane;
-  if (k >= Tn || h >= H) return;
-  const int t = perm[k];
-  const int loc = ids[t] - v0;
-  const bool inside = loc >= 0 && loc < Vl;           // wave-uniform
-  out[(size_t)t * H + h] = inside ? E[(size_t)h * Vl + loc] : from_f32<T>(0.f);
+  constexpr int S = emb_stride<T>(), VN = Vec16<T>::N, SEG = kEmbTile / VN;
+  __shared__ __attribute__((aligned(16))) T tile[kEmbTile * S];
+  __shared__ int stok[kEmbTile], sloc[kEmbTile];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int k0 = blockIdx.x * kEmbTile, h0 = blockIdx.y * kEmbTile;
+  if (threadIdx.x < kEmbTile) {
+    const int k = k0 + lane, t = perm[min(k, Tn - 1)], loc = ids[t] - v0;
+    stok[lane] = k < Tn ? t : -1;
+    sloc[lane] = k < Tn && loc >= 0 && loc < Vl ? loc : -1;
+  }
+  __syncthreads();
+  const bool some = sloc[0] >= 0;                     // block-uniform
+  if (some) {
+    const int loc = sloc[lane];
+    T v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int h = h0 + wave * 16 + i;
+      v[i] = loc >= 0 && h < H ? E[(size_t)h * Vl + loc] : from_f32<T>(0.f);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) tile[lane * S + wave * 16 + i] = v[i];
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < kEmbTile / (256 / SEG); ++i) {
+    const int p = i * (256 / SEG) + threadIdx.x / SEG, c = (threadIdx.x % SEG) * VN;
+    const int t = stok[p];
+    if (t < 0 || h0 + c >= H) continue;               // H is a multiple of 8: a vector is all in or all out
+    uint4 w = make_uint4(0u, 0u, 0u, 0u);
+    if (some) {
+      const uint32_t* src = reinterpret_cast<const uint32_t*>(&tile[p * S + c]);
+      w = make_uint4(src[0], src[1], src[2], src[3]);
+    }
+    *reinterpret_cast<uint4*>(out + (size_t)t * H + h0 + c) = w;
+  }
 }
 
-// One wave per (sorted position, group of 64 rows of dE_r); the wave at the head of a run of equal local ids sums the
-// run's rows of dz0 in token order (fp32) and adds the sum to column `loc` of dE_r.  Element-sized accesses:
-// neighbouring columns belong to other waves.
+// dE_r[:, loc] += the sum of the rows of dz0 whose token has local id loc, in token order (fp32).  The wave whose 16
+// positions hold the head of a run of equal ids sums all of it, the part behind its positions one row at a time.
+// Element-sized accesses to dE_r: neighbouring columns belong to other lanes and workgroups.
 template <typename T>
 __global__ __launch_bounds__(256) void embed_bwd_kernel(int Tn, int H, int Vl, int v0, const int32_t* __restrict__ ids,
                                                         const int32_t* __restrict__ perm, const T* __restrict__ dz,
                                                         T* __restrict__ dE) {
-  const int lane = threadIdx.x & 63;
-  const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int h = blockIdx.y * 64 + lane;
-  if (k >= Tn) return;
-  const int loc = ids[perm[k]] - v0;
-  if (loc < 0 || loc >= Vl) return;                   // outside the shard (wave-uniform)
-  if (k > 0 && ids[perm[k - 1]] - v0 == loc) return;  // not the head of its run
-  float acc = 0.f;
-  for (int kk = k; kk < Tn; ++kk) {
-    const int t = perm[kk];
-    if (ids[t] - v0 != loc) break;                    // end of the run (wave-uniform)
-    if (h < H) acc += to_f32(dz[(size_t)t * H + h]);
+  __shared__ float tile[kEmbTile * (kEmbTile + 1)];
+  __shared__ int stok[kEmbTile], sloc[kEmbTile + 1];  // sloc[i + 1]: position k0 + i; sloc[0]: the one before
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int k0 = blockIdx.x * kEmbTile, h0 = blockIdx.y * kEmbTile, h = h0 + lane, hc = min(h, H - 1);
+  if (threadIdx.x <= kEmbTile) {
+    const int k = k0 + (int)threadIdx.x - 1;
+    const int t = k >= 0 && k < Tn ? perm[k] : -1, loc = t >= 0 ? ids[t] - v0 : -1;
+    sloc[threadIdx.x] = loc >= 0 && loc < Vl ? loc : -1;
+    if (threadIdx.x > 0) stok[threadIdx.x - 1] = t;
   }
-  if (h < H) {
-    T* p = dE + (size_t)h * Vl + loc;
-    *p = from_f32<T>(to_f32(*p) + acc);
+  __syncthreads();
+  if (sloc[1] < 0) return;                            // sorted: the whole tile is outside the shard (block-uniform)
+  const int p0 = wave * 16;
+  float v[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int t = stok[p0 + i];
+    v[i] = sloc[p0 + i + 1] >= 0 ? to_f32(dz[(size_t)t * H + hc]) : 0.f;
+  }
+  float acc = 0.f;
+  int head = -1;                                      // position (in the tile) of the run being summed; wave-uniform
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int loc = sloc[p0 + i + 1];
+    if (loc < 0 || loc != sloc[p0 + i]) {             // a new run, or the end of the shard's tokens
+      if (head >= 0) tile[head * (kEmbTile + 1) + lane] = acc;
+      head = loc >= 0 ? p0 + i : -1;
+      acc = v[i];
+    } else {
+      acc += v[i];                                    // (of a run that an earlier wave sums: head is -1)
+    }
+  }
+  if (head >= 0) {
+    const int loc = sloc[head + 1];
+    for (int kk = k0 + p0 + 16; kk < Tn; ++kk) {
+      const int t = perm[kk];
+      if (ids[t] - v0 != loc) break;                  // end of the run (wave-uniform)
+      acc += to_f32(dz[(size_t)t * H + hc]);
+    }
+    tile[head * (kEmbTile + 1) + lane] = acc;
+  }
+  __syncthreads();
+  const int loc = sloc[lane + 1];
+  if (loc < 0 || loc == sloc[lane]) return;           // outside, or not the head of its run
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int r = wave * 16 + i;
+    if (h0 + r < H) {
+      T* p = dE + (size_t)(h0 + r) * Vl + loc;
+      *p = from_f32<T>(to_f32(*p) + tile[lane * (kEmbTile + 1) + r]);
+    }
   }
 }
 
@@ -144,7 +219,7 @@ hipError_t launch_embed_fwd(int dtype, int T, int H, int Vl, int v0, const int32
   int nslice = (T + kRankChunk - 1) / kRankChunk;
   nslice = nslice < 1 ? 1 : (nslice > 16 ? 16 : nslice);
   if (nslice > H * esz / 4) nslice = H * esz / 4;
-  hipLaunchKernelGGL(embed_rank_kernel, dim3((T + 255) / 256, nslice), dim3(256), 0, st, T, nslice, ids, v0, Vl,
+  hipLaunchKernelGGL(embed_rank_kernel, dim3((T + kRankChunk - 1) / kRankChunk, nslice), dim3(kRankChunk), 0, st, T, nslice, ids, v0, Vl,
                      (int32_t*)partial);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -152,7 +227,7 @@ hipError_t launch_embed_fwd(int dtype, int T, int H, int Vl, int v0, const int32
                      perm);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  dim3 grid((T + 3) / 4, (H + 63) / 64);
+  dim3 grid((T + kEmbTile - 1) / kEmbTile, (H + kEmbTile - 1) / kEmbTile);
   if (dtype == MLM_BF16)
     hipLaunchKernelGGL((embed_fwd_kernel<bf16>), grid, dim3(256), 0, st, T, H, Vl, v0, ids, perm, (const bf16*)E,
                        (bf16*)partial);
@@ -164,7 +239,7 @@ hipError_t launch_embed_fwd(int dtype, int T, int H, int Vl, int v0, const int32
 
 hipError_t launch_embed_bwd(int dtype, int T, int H, int Vl, int v0, const int32_t* ids, const int32_t* perm,
                             const void* dz, void* dE, hipStream_t st) {
-  dim3 grid((T + 3) / 4, (H + 63) / 64);
+  dim3 grid((T + kEmbTile - 1) / kEmbTile, (H + kEmbTile - 1) / kEmbTile);
   if (dtype == MLM_BF16)
     hipLaunchKernelGGL((embed_bwd_kernel<bf16>), grid, dim3(256), 0, st, T, H, Vl, v0, ids, perm, (const bf16*)dz,
                        (bf16*)dE);
