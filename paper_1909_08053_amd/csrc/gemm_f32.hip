@@ -3,18 +3,21 @@
 // Computes C[m,n] = sum_k A(m,k) B(k,n) with either operand stored k-contiguous or not, and the same fused epilogues as
 // the bf16 kernel (bias, bias+GeLU with saved pre-activation, GeLU', dlogits).
 //
-// The order of k inside a sum is free, so the 8-deep chunk c of k is fed to four MFMAs with k = 8c + j in the lower
-// half-wave and 8c + 4 + j in the upper one (j = 0..3): a lane's four values of a k-contiguous operand are then ONE
-// 16-byte access.  The accumulator of a 32 x 32 tile holds, in lane l, column l % 32 and rows 8 (e / 4) + 4 (l / 32) +
-// e % 4, so every store covers 128 contiguous bytes of a row.
+// The order of k inside a sum is free.  The tile kernels use 16 x 16 x 4 MFMAs: the 16-deep chunk c of k is fed to four of
+// them with k = 16c + 4g + j in lane group g = lane / 16 (j = 0..3), so a lane's four values of a k-contiguous operand are ONE
+// 16-byte access; the B tile is the first operand, so a lane holds four consecutive columns of one row of the result.  The
+// split kernel uses 32 x 32 x 2 ones with k = 8c + j in the lower half-wave and 8c + 4 + j in the upper one; its accumulator
+// holds, in lane l, column l % 32 and rows 8 (e / 4) + 4 (l / 32) + e % 4.
 //
 // Three kernels by the number of output tiles (launch_gemm_f32 holds the rule and the figures):
 //   * 128 x 128 tile, 4 waves of 64 x 64: operand tiles of 32 k staged through LDS (registers -> LDS, double buffered);
-//     bound by the matrix cores.
+//     bound by the matrix cores (86 % of their cycles at 4096^3).
 //   * 64 x 64 tile, 8 waves: 2 x 2 waves of 32 x 32 in two groups that take the two halves of every 64-deep operand tile,
 //     so a CU that holds one tile still has two waves per SIMD to cover LDS and global latency.
 //   * 32 x 32 tile, 8 waves that split k and read their operands straight from the caches (no LDS, no barrier in the
 //     loop): for outputs of so few tiles that the serial k loop of one wave, not the matrix rate, is the time.
+#include <type_traits>
+#include <utility>
 #include "common.h"
 
 namespace mlm {
@@ -49,56 +52,86 @@ __device__ __forceinline__ void f32_put(const GemmArgs& a, const F32Row& r, int 
     *C = g;
   }
 }
-// One 32 x 32 accumulator tile whose first row / column is (m0, n0).
+// One 16 x 16 accumulator tile whose first row / column is (m0, n0): a lane holds four consecutive columns of one row.
 template <int EPI>
-__device__ __forceinline__ void f32_store_tile(const GemmArgs& a, const floatx16& acc, int m0, int n0, int lane) {
-  const int n = n0 + (lane & 31), lh = lane >> 5;
-  if (n >= a.N) return;
-  const float bias = ((EPI == EPI_STORE || EPI == EPI_BIAS_GELU) && a.bias) ? ((const float*)a.bias)[n] : 0.f;
+__device__ __forceinline__ void f32_store_tile(const GemmArgs& a, const floatx4& acc, int m0, int n0, int lane) {
+  const int m = m0 + (lane & 15), n = n0 + 4 * (lane >> 4);
+  if (m >= a.M || n >= a.N) return;                   // N is a multiple of 8: four columns are all in or all out
+  float* C = (float*)a.C + (size_t)m * a.ldc + n;
+  float v[4] = {acc[0], acc[1], acc[2], acc[3]};
+  if ((EPI == EPI_STORE || EPI == EPI_BIAS_GELU) && a.bias) {
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int m = m0 + 8 * (e >> 2) + 4 * lh + (e & 3);
-    if (m < a.M) f32_put<EPI>(a, f32_row<EPI>(a, m), m, n, bias, acc[e]);
+    for (int e = 0; e < 4; ++e) v[e] += ((const float*)a.bias)[n + e];
   }
+  if (EPI == EPI_BIAS_GELU) {
+    *reinterpret_cast<float4*>((float*)a.aux + (size_t)m * a.ldaux + n) = make_float4(v[0], v[1], v[2], v[3]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = gelu_fwd(v[e], a.gelu_tanh != 0);
+  } else if (EPI == EPI_DGELU) {
+    const float4 g = *reinterpret_cast<const float4*>((const float*)a.aux + (size_t)m * a.ldaux + n);
+    const float gv[4] = {g.x, g.y, g.z, g.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] *= gelu_bwd(gv[e], a.gelu_tanh != 0);
+  } else if (EPI == EPI_DLOGITS) {
+    const F32Row r = f32_row<EPI>(a, m);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = expf(v[e] - r.Mr) * r.invS;
+      if (n + e == r.loc) v[e] -= r.coef;
+    }
+  }
+  *reinterpret_cast<float4*>(C) = make_float4(v[0], v[1], v[2], v[3]);
 }
 
 // ---- operand tile of ROWS x KT staged through LDS by NT threads ----------------------------------------------------
 // KC (k-contiguous in memory): LDS [row][KT + 4]; a fragment is one 16-byte read, rows 4 KT + 16 bytes apart fall on
-// different bank groups.  Otherwise: LDS [k][ROWS + 8]; a fragment is four 4-byte reads, the two half-waves read k-rows
-// four apart, which the 8-float pad puts 32 banks apart.
+// different bank groups.  Otherwise: LDS [k][ROWS + 4]; a fragment is four 4-byte reads, the four groups of 16 lanes read
+// k-rows four apart, which the 4-float pad puts 16 banks apart.
 template <bool KC, int ROWS, int KT, int NT>
 struct F32Tile {
-  static constexpr int LD = KC ? KT + 4 : ROWS + 8;
+  static constexpr int LD = KC ? KT + 4 : ROWS + 4;
   static constexpr int FLOATS = KC ? ROWS * LD : KT * LD;
   static constexpr int PER = ROWS * KT / 4 / NT;             // float4 per thread
   static_assert(ROWS * KT % (4 * NT) == 0, "tile does not divide over the threads");
   float4 reg[PER];
-  __device__ __forceinline__ void load(const float* __restrict__ P, int ld, int row0, int nrows, int k0, int K, int tid) {
+  uint32_t ofs[PER];           // bytes from the tile's first element to this thread's i-th vector (at most 128 rows apart)
+  // where thread tid's i-th vector lies in the tile
+  __device__ static __forceinline__ int row_of(int i, int tid) {
+    const int v = tid + i * NT;
+    return KC ? v / (KT / 4) : (v % (ROWS / 4)) * 4;
+  }
+  __device__ static __forceinline__ int k_of(int i, int tid) {
+    const int v = tid + i * NT;
+    return KC ? (v % (KT / 4)) * 4 : v / (ROWS / 4);
+  }
+  __device__ __forceinline__ void init(int ld, int row0, int nrows, int tid) {
+    // rows past the end repeat the last ones (their results are not stored); row counts, and K of a k-contiguous operand,
+    // are multiples of 8: a group of four is inside or outside as a whole
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int v = tid + i * NT;
-      int row, k;
-      if (KC) { row = row0 + v / (KT / 4); k = k0 + (v % (KT / 4)) * 4; }
-      else    { row = row0 + (v % (ROWS / 4)) * 4; k = k0 + v / (ROWS / 4); }
-      // rows past the end repeat the last ones (their results are not stored); k past the end counts as zero.  Row counts,
-      // and K of a k-contiguous operand, are multiples of 8: a group of four is inside or outside as a whole.
-      const float* p = KC ? P + (size_t)min(row, nrows - 1) * ld + min(k, K - 4)
-                          : P + (size_t)min(k, K - 1) * ld + min(row, nrows - 4);
-      const float4 x = *reinterpret_cast<const float4*>(p);
-      reg[i] = k < K ? x : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int i = 0; i < PER; ++i)
+      ofs[i] = 4u * (KC ? (uint32_t)min(row_of(i, tid), nrows - 1 - row0) * ld + k_of(i, tid)
+                        : (uint32_t)k_of(i, tid) * ld + min(row_of(i, tid), nrows - 4 - row0));
+  }
+  // tile: its first element (wave-uniform, so a whole tile inside [0, K) costs no address arithmetic per load); kleft = K
+  // minus its first k: k past the end counts as zero
+  template <bool WHOLE>
+  __device__ __forceinline__ void load_one(const float* __restrict__ tile, int ld, int kleft, int tid, int i) {
+    if (WHOLE) {
+      reg[i] = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(tile) + ofs[i]);
+    } else {
+      const int k = k_of(i, tid);
+      const bool in = k < kleft;
+      const float* base = in ? tile : tile - (KC ? (size_t)k : (size_t)k * ld);      // not inside: the vector's k = 0
+      const float4 x = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(base) + ofs[i]);
+      reg[i] = in ? x : make_float4(0.f, 0.f, 0.f, 0.f);
     }
   }
-  __device__ __forceinline__ void store(float* s, int tid) const {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int v = tid + i * NT;
-      float* d = KC ? s + (v / (KT / 4)) * LD + (v % (KT / 4)) * 4 : s + (v / (ROWS / 4)) * LD + (v % (ROWS / 4)) * 4;
-      *reinterpret_cast<float4*>(d) = reg[i];
-    }
+  __device__ __forceinline__ void store_one(float* s, int tid, int i) const {
+    *reinterpret_cast<float4*>(s + (KC ? row_of(i, tid) * LD + k_of(i, tid) : k_of(i, tid) * LD + row_of(i, tid))) = reg[i];
   }
-  // the four MFMA operands of chunk c (8 k) for the 32 rows from r0
+  // the four MFMA operands of chunk c (16 k) for the 16 rows from r0
   __device__ static __forceinline__ void frag(const float* s, int r0, int c, int lane, float (&f)[4]) {
-    const int row = r0 + (lane & 31), k = 8 * c + 4 * (lane >> 5);
+    const int row = r0 + (lane & 15), k = 16 * c + 4 * (lane >> 4);
     if (KC) {
       const float4 v = *reinterpret_cast<const float4*>(s + row * LD + k);
       f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
@@ -109,10 +142,15 @@ struct F32Tile {
   }
 };
 
+template <typename F, int... N>
+__device__ __forceinline__ void f32_static_for(F&& f, std::integer_sequence<int, N...>) {
+  (f(std::integral_constant<int, N>{}), ...);
+}
+
 // BM x BN tile; WM x WN waves of (BM / WM) x (BN / WN), KS groups of them that share every KT-deep operand tile along k.
 template <bool A_KC, bool B_KC, int EPI, int BM, int BN, int WM, int WN, int KS, int KT>
-__global__ __launch_bounds__(64 * WM * WN * KS) void gemm_f32_tile_kernel(GemmArgs a) {
-  constexpr int NT = 64 * WM * WN * KS, TM = BM / WM / 32, TN = BN / WN / 32, NC = KT / 8 / KS;
+__global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_kernel(GemmArgs a) {
+  constexpr int NT = 64 * WM * WN * KS, TM = BM / WM / 16, TN = BN / WN / 16, NC = KT / 16 / KS;
   typedef F32Tile<A_KC, BM, KT, NT> TA;
   typedef F32Tile<B_KC, BN, KT, NT> TB;
   constexpr int STAGE = TA::FLOATS + TB::FLOATS;
@@ -124,68 +162,103 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_f32_tile_kernel(GemmAr
   const int m0 = (blockIdx.x % tiles_m) * BM, n0 = (blockIdx.x / tiles_m) * BN;
   const float* A = (const float*)a.A;
   const float* B = (const float*)a.B;
-  floatx16 acc[TM][TN];
+  floatx4 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
 
   // Tile kt + 1 waits in registers while the first half of tile kt is multiplied, is written to the other LDS buffer in
-  // the middle of it (free since the last barrier) and tile kt + 2 is requested right then: a request has a whole tile's
-  // time to arrive, and neither the LDS writes nor the wait for memory sit next to the barrier, where all waves stop.
+  // the middle of it (free since the last barrier) and tile kt + 2 is requested vector by vector behind the writes: a
+  // request has a whole tile's time to arrive.  Fragments are read one chunk ahead; for the first chunk of tile kt + 1 the
+  // barrier sits behind the first MFMA of the last chunk of tile kt, whose fragments are in registers by then.  All of this is
+  // issued one operation at a time between the MFMAs: issued in bursts, with the address arithmetic of the loads, it left the
+  // pipe idle for 1500 of 5600 cycles per tile.  1024 x 4096 x 1024 91 -> 84 us, with 16 x 16 x 4 instead of 32 x 32 x 2
+  // MFMAs (which also make the stores 16 bytes) 79; 4096^3 1074 -> 1011 -> 997; 1024^3 (64 x 64 tile) 28.8 -> 26.1 -> 23.5.
   TA ta;
   TB tb;
+  ta.init(a.lda, m0, a.M, tid);
+  tb.init(a.ldb, n0, a.N, tid);
+  const float* tileA = A + (A_KC ? (size_t)m0 * a.lda : (size_t)m0);
+  const float* tileB = B + (B_KC ? (size_t)n0 * a.ldb : (size_t)n0);
   const int nk = (a.K + KT - 1) / KT;
-  auto request = [&](int kt) {
-    ta.load(A, a.lda, m0, a.M, kt * KT, a.K, tid);
-    tb.load(B, a.ldb, n0, a.N, kt * KT, a.K, tid);
+  constexpr int NV = TA::PER + TB::PER;             // vectors per thread and tile
+  auto request_one = [&](auto whole, int kt, int v) {
+    constexpr bool W = decltype(whole)::value;
+    if (v < TA::PER) ta.template load_one<W>(tileA + (size_t)kt * KT * (A_KC ? 1 : a.lda), a.lda, a.K - kt * KT, tid, v);
+    else tb.template load_one<W>(tileB + (size_t)kt * KT * (B_KC ? 1 : a.ldb), a.ldb, a.K - kt * KT, tid, v - TA::PER);
   };
-  auto write = [&](int kt) {
+  auto write_one = [&](int kt, int v) {
     float* d = lds_f32 + (kt & 1) * STAGE;
-    ta.store(d, tid);
-    tb.store(d + TA::FLOATS, tid);
+    if (v < TA::PER) ta.store_one(d, tid, v);
+    else tb.store_one(d + TA::FLOATS, tid, v - TA::PER);
   };
-  request(0);
-  write(0);
-  if (nk > 1) request(1);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
+  float fa[2][TM][4], fb[2][TN][4];
+  auto fragment = [&](int buf, int kt, int c, int f) {
     const float* sA = lds_f32 + (kt & 1) * STAGE;
-    const float* sB = sA + TA::FLOATS;
+    if (f < TM) TA::frag(sA, wm0 + f * 16, grp * NC + c, lane, fa[buf][f < TM ? f : 0]);
+    else TB::frag(sA + TA::FLOATS, wn0 + (f - TM) * 16, grp * NC + c, lane, fb[buf][f < TM ? 0 : f - TM]);
+  };
+  constexpr int NF = TM + TN, NMF = 4 * TM * TN;
+  static_assert(NC % 2 == 0 && NC >= 2 && NF <= NMF, "chunk c of every tile is in buffer c & 1");
+  typedef std::integral_constant<bool, true> yes_t;
+  typedef std::integral_constant<bool, false> no_t;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) request_one(no_t{}, 0, v);
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    write_one(0, v);
+    if (nk > 1) request_one(no_t{}, 1, v);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int f = 0; f < NF; ++f) fragment(0, 0, 0, f);
+  // NEXT: there is a tile kt + 1; WHOLE: and a tile kt + 2 that lies inside [0, K)
+  auto multiply = [&](auto has_next, auto whole, int kt) {
+    constexpr bool NEXT = decltype(has_next)::value, WHOLE = decltype(whole)::value;
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-      float fa[TM][4], fb[TN][4];
+      f32_static_for([&](auto n_c) {                  // (a loop of this length is past the compiler's unrolling limit)
+        constexpr int n = decltype(n_c)::value, q = n / (TM * TN), i = n / TN % TM, j = n % TN;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[c & 1][j][q], fa[c & 1][i][q], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (NEXT && c == NC - 1 && n == 0) __syncthreads();
+        if (n < NF) {
+          if (c + 1 < NC) fragment((c + 1) & 1, kt, c + 1, n);
+          else if (NEXT) fragment(0, kt + 1, 0, n);
+        }
+        if (NEXT && c == NC / 2 - 1) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i) TA::frag(sA, wm0 + i * 32, grp * NC + c, lane, fa[i]);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) TB::frag(sB, wn0 + j * 32, grp * NC + c, lane, fb[j]);
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][q], fb[j][q], acc[i][j], 0, 0, 0);
-      if (c == NC / 2 - 1 && kt + 1 < nk) {
-        write(kt + 1);
-        if (kt + 2 < nk) request(kt + 2);
-      }
+          for (int v = 0; v < NV; ++v)
+            if (v * NMF / NV == n) {
+              write_one(kt + 1, v);
+              if (WHOLE) request_one(yes_t{}, kt + 2, v);
+              else if (kt + 2 < nk) request_one(no_t{}, kt + 2, v);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }, std::make_integer_sequence<int, NMF>{});
     }
-    __syncthreads();
-  }
+  };
+  const int nwhole = a.K / KT;
+  int kt = 0;
+  for (; kt + 2 < nwhole; ++kt) multiply(yes_t{}, yes_t{}, kt);
+  for (; kt + 1 < nk; ++kt) multiply(yes_t{}, no_t{}, kt);
+  multiply(no_t{}, no_t{}, kt);
+  if (KS > 1) __syncthreads();
   if (KS > 1) {
     // the groups' sums meet in LDS ([group - 1][wave][value][lane]) and are added in group order
-    float* park = lds_f32 + w * (TM * TN * 16 * 64) + lane;
-    constexpr int GS = WM * WN * TM * TN * 16 * 64;
+    float* park = lds_f32 + w * (TM * TN * 4 * 64) + lane;
+    constexpr int GS = WM * WN * TM * TN * 4 * 64;
     if (grp > 0) {
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) park[(grp - 1) * GS + ((i * TN + j) * 16 + e) * 64] = acc[i][j][e];
+          for (int e = 0; e < 4; ++e) park[(grp - 1) * GS + ((i * TN + j) * 4 + e) * 64] = acc[i][j][e];
     }
     __syncthreads();
     if (grp > 0) return;
@@ -196,12 +269,12 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void gemm_f32_tile_kernel(GemmAr
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) acc[i][j][e] += park[g * GS + ((i * TN + j) * 16 + e) * 64];
+          for (int e = 0; e < 4; ++e) acc[i][j][e] += park[g * GS + ((i * TN + j) * 4 + e) * 64];
   }
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) f32_store_tile<EPI>(a, acc[i][j], m0 + wm0 + i * 32, n0 + wn0 + j * 32, lane);
+    for (int j = 0; j < TN; ++j) f32_store_tile<EPI>(a, acc[i][j], m0 + wm0 + i * 16, n0 + wn0 + j * 16, lane);
 }
 
 // 32 x 32 tile, 8 waves: wave w sums the w-th eighth of k (in 8-deep chunks) and the eight partial tiles are added in LDS,
@@ -306,9 +379,9 @@ static hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t st) {
 //   * split kernel: a start-up, the serial eighth of k, and 52 TFLOP/s once the chip is full (its operands come through
 //     the caches once per 32 x 32 tile);
 //   * tile kernels: start-up plus rounds of two workgroups per CU; a last round with at most one workgroup per CU costs
-//     a little more than half.  64 x 64: 37 us per round and 1024 k, 21 us with one workgroup per CU; 128 x 128: 132 / 73.
-// 1024^3: 48 us (split), 30 us (64), 85 us (128); 4096^3: 2540 / 1160-1210 / 1050-1110 us (130 TFLOP/s, the matrix cores'
-// peak is 157); 256 x 256 x 512: < 10 / 15 / 46 us.  (One 64 x 64-tile kernel on the vector ALUs, 15.7 TFLOP/s at most, took
+//     a little more than half.  64 x 64: 31.5 us per round and 1024 k, 17.3 us with one workgroup per CU; 128 x 128: 119 / 63.
+// 1024^3: 48 us (split), 23 us (64); 4096^3: 2540 (split), 985-1000 us (128: 139 TFLOP/s, the matrix cores' peak is 157);
+// 256 x 256 x 512: < 10 us (split).  (One 64 x 64-tile kernel on the vector ALUs, 15.7 TFLOP/s at most, took
 // 200 us for 1024^3 and 60 us for 256 x 256 x 512 before.)
 static int f32_pick(int M, int N, int K) {
   auto tiles = [&](int b) { return (double)((M + b - 1) / b) * ((N + b - 1) / b); };
@@ -319,7 +392,7 @@ static int f32_pick(int M, int N, int K) {
   };
   const double k = K / 1024.0;
   const double split = 3.0 + 6.0 * k + 2.0 * M * N * K / 52e6;
-  const double t64 = 4.0 + rounds(64, 37.0, 21.0) * k, t128 = 3.0 + rounds(128, 132.0, 73.0) * k;
+  const double t64 = 4.0 + rounds(64, 31.5, 17.3) * k, t128 = 3.0 + rounds(128, 119.0, 63.0) * k;
   if (split <= t64 && split <= t128) return 32;
   return t64 <= t128 ? 64 : 128;
 }
