@@ -603,8 +603,7 @@ MLM_API int mlm_layer_shard_wgrads(const mlm_dims* dims, const void* u, const vo
   GemmArgs g[4] = {gemm_wgrad(L.Fl, dims->H, L.T, y_r, dz2, dB_r), gemm_wgrad(dims->H, L.Fl, L.T, u2, dg_r, dA_r),
                    gemm_wgrad(dims->H, 3 * L.Hl, L.T, u, dqkv_r, dWqkv_r), gemm_wgrad(L.Hl, dims->H, L.T, ctx_r, dz1, dWo_r)};
   if (dims->dtype == MLM_BF16) return hip_status(launch_gemm_bf16_wgrad_group(g, 4, (float*)ws, st));
-  for (int q = 0; q < 4; ++q) MLM_TRY_HIP(launch_gemm_f32(g[q], st));
-  return MLM_OK;
+  return hip_status(launch_gemm_f32_wgrads(g, 4, st));
 }
 
 MLM_API int mlm_vocab_ce_shard_fwd(const mlm_dims* dims, const void* hf, const void* E_r, const int32_t* targets, float* m_r,

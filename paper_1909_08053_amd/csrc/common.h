@@ -165,6 +165,7 @@ int gemm_bf16_ce_col_tiles(int M, int N, int K);
 int gemm_cu_count();                    // compute units of the current device, at most 256
 hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t st);
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t st);
+hipError_t launch_gemm_f32_wgrads(const GemmArgs* probs, int n, hipStream_t st);
 // n weight-gradient GEMMs (A m-contiguous, B n-contiguous, plain store) in one launch where that is faster
 hipError_t launch_gemm_bf16_wgrad_group(const GemmArgs* probs, int n, float* splitk_ws, hipStream_t st);
 

@@ -16,6 +16,7 @@
 //     so a CU that holds one tile still has two waves per SIMD to cover LDS and global latency.
 //   * 32 x 32 tile, 8 waves that split k and read their operands straight from the caches (no LDS, no barrier in the
 //     loop): for outputs of so few tiles that the serial k loop of one wave, not the matrix rate, is the time.
+#include <string.h>
 #include <type_traits>
 #include <utility>
 #include "common.h"
@@ -299,13 +300,13 @@ __device__ __forceinline__ void f32_frag_global(const float* __restrict__ P, int
 }
 
 template <bool A_KC, bool B_KC, int EPI>
-__global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_kernel(GemmArgs a) {
+__device__ __forceinline__ void f32_split_tile(const GemmArgs& a, int tile) {
   constexpr int NWV = kF32SplitWaves, ST = kF32SplitStep;
   __shared__ float park[NWV][16][64];
   const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tiles_m = (a.M + 31) / 32;
-  const int m0 = (blockIdx.x % tiles_m) * 32, n0 = (blockIdx.x / tiles_m) * 32;
+  const int m0 = (tile % tiles_m) * 32, n0 = (tile / tiles_m) * 32;
   const float* A = (const float*)a.A;
   const float* B = (const float*)a.B;
   const int rowA = min(m0 + l32, a.M - 1), rowB = min(n0 + l32, a.N - 1);
@@ -359,6 +360,28 @@ __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_kernel(Gem
   }
 }
 
+template <bool A_KC, bool B_KC, int EPI>
+__global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_kernel(GemmArgs a) {
+  f32_split_tile<A_KC, B_KC, EPI>(a, blockIdx.x);
+}
+
+// The tiles of several weight gradients in one launch: such a GEMM takes 6 us whatever its size, and nothing waits for the
+// four of a layer shard one by one (four launches of 256 x {256, 512} x 256: 24 -> 11 us in one).
+constexpr int kF32Group = 4;
+struct F32Group {
+  GemmArgs a[kF32Group];
+  int tile_begin[kF32Group];           // first tile of each problem (past the grid for problems that do not exist)
+};
+__global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_group_kernel(F32Group g) {
+  const int id = blockIdx.x;
+  GemmArgs a = g.a[0];
+  int first = 0;
+#pragma unroll
+  for (int q = 1; q < kF32Group; ++q)
+    if (id >= g.tile_begin[q]) { a = g.a[q]; first = g.tile_begin[q]; }     // workgroup-uniform
+  f32_split_tile<false, false, EPI_STORE>(a, id - first);
+}
+
 template <bool A_KC, bool B_KC, int EPI, int BM, int BN, int WM, int WN, int KS, int KT>
 static hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t st) {
   constexpr int NT = 64 * WM * WN * KS;
@@ -408,6 +431,29 @@ static hipError_t launch_f32_layout(const GemmArgs& a, hipStream_t st) {
     case 64: return launch_f32_tile<A_KC, B_KC, EPI, 64, 64, 2, 2, 2, 64>(a, st);
     default: return launch_f32_tile<A_KC, B_KC, EPI, 128, 128, 2, 2, 1, 32>(a, st);
   }
+}
+
+// Weight gradients (both operands k-major, plain store) that all take the split kernel go out as one launch, others one by one.
+hipError_t launch_gemm_f32_wgrads(const GemmArgs* probs, int n, hipStream_t st) {
+  bool together = n >= 2 && n <= kF32Group;
+  for (int q = 0; q < n && together; ++q)
+    together = !probs[q].a_kc && !probs[q].b_kc && probs[q].epi == EPI_STORE && f32_pick(probs[q].M, probs[q].N, probs[q].K) == 32;
+  if (!together) {
+    for (int q = 0; q < n; ++q)
+      if (hipError_t e = launch_gemm_f32(probs[q], st); e != hipSuccess) return e;
+    return hipSuccess;
+  }
+  F32Group g;
+  memset(&g, 0, sizeof(g));
+  int total = 0;
+  for (int q = 0; q < n; ++q) {
+    g.a[q] = probs[q];
+    g.tile_begin[q] = total;
+    total += ((probs[q].M + 31) / 32) * ((probs[q].N + 31) / 32);
+  }
+  for (int q = n; q < kF32Group; ++q) g.tile_begin[q] = total;
+  hipLaunchKernelGGL(gemm_f32_split_group_kernel, dim3(total), dim3(64 * kF32SplitWaves), 0, st, g);
+  return hipGetLastError();
 }
 
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t st) {
