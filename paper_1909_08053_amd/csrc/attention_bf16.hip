@@ -577,13 +577,16 @@ __global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW
 // 128 K and V rows are copied to LDS once and their fragments are read per use.
 // Larger heads keep one group (their accumulators alone need more registers) and split the D columns of dK / dV over
 // two workgroups instead.
-template <int D, bool DROP>
+// SPLIT: 64 keys per workgroup, and two waves of each group share a tile's 64 queries: for launches that leave compute units
+// without a workgroup.  128 workgroups of 128 keys, d = 96: 29.1 -> 21.7 us; 64 of d = 128 31.8 -> 24.5; 64 of d = 64
+// (s = 512) 15.0 -> 11.1.
+template <int D, bool DROP, bool SPLIT>
 __global__ __launch_bounds__(dkv_groups<D>() * ANT) void attn_bwd_dkv_bf16_kernel(AttnArgs a) {
   typedef ATile<D> TL;
-  constexpr int BKB = 32 * ANW, VEC = 2 * ATILE * 4;          // VEC: bytes of the lse + delta vectors of a tile
+  constexpr int RW = SPLIT ? 2 : ANW, KG = ANW / RW, BKB = 32 * RW, VEC = 2 * ATILE * 4;          // VEC: bytes of the lse + delta vectors of a tile
   constexpr int KBB = DROP ? ATILE * 16 : 0;                  // keep bits of the tile: 64 queries x 128 keys
   constexpr int STAGE = 2 * TL::BYTES + VEC + KBB, LPT = 2 * TL::QPW + 1 + (DROP ? 1 : 0);
-  constexpr int NG = dkv_groups<D>(), NST = dkv_stages<D>();
+  constexpr int NG = dkv_groups<D>(), NST = dkv_stages<D>(), G = KG * NG;
   constexpr bool OWN_LDS = NG == 2 && dkv_own_lds<D>();        // own K / V rows in LDS (after the rings)
   // Large heads: the dK / dV accumulators of all D columns plus the owned K / V rows do not fit the register file
   // (they spilled: 2.3x / 5.6x the d = 96 time at d = 128 / 192).  Two workgroups then share a key block, each
@@ -594,8 +597,9 @@ __global__ __launch_bounds__(dkv_groups<D>() * ANT) void attn_bwd_dkv_bf16_kerne
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
   // known wave-uniform: mask tests become scalar branches
   const int grp = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);   // wave group: even / odd query tiles
-  const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);         // wave inside its group: 32 keys
-  const AttnBlock blk = attn_block(((a.s + 32 * ANW - 1) / (32 * ANW)) * DS, a.hl, a.b);
+  const int wave_u = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);       // wave inside its group (copies a quarter of a tile)
+  const int wave = wave_u % RW, qh = wave_u / RW;  // its 32 keys, and its 32 queries of a tile (KG = 2)
+  const AttnBlock blk = attn_block(((a.s + BKB - 1) / BKB) * DS, a.hl, a.b);
   if (!blk.valid) return;
   const int kb = blk.xb / DS;                      // key block; for causal, block 0 has the most queries: first
   const int dh0 = (blk.xb % DS) * DH;              // first of this workgroup's dK / dV columns
@@ -606,20 +610,20 @@ __global__ __launch_bounds__(dkv_groups<D>() * ANT) void attn_bwd_dkv_bf16_kerne
   const int kb0 = kb * BKB, kw0 = kb0 + wave * 32, kj = kw0 + l32;
   const int kc = min(kj, a.s - 1);
   ATileSrc<D> src;
-  src.init(wave, lane);
+  src.init(wave_u, lane);
   const uint32_t lds0 = lds_offset_of(lds_raw);
 
-  // the block's own K and V rows: registers (one group) or two 64-row tiles each in LDS (two groups; rows past the
+  // the block's own K and V rows: registers (one group) or BKB / 64 64-row tiles each in LDS (two groups; rows past the
   // end of the sequence repeat the last row, exactly as the register path clamps them)
   bf16x8 kf[OWN_LDS ? 1 : D / 16], vf[OWN_LDS ? 1 : D / 16];
   const unsigned char* ownK = lds_raw + NG * NST * STAGE;
-  const unsigned char* ownV = ownK + 2 * TL::BYTES;
+  const unsigned char* ownV = ownK + (BKB / ATILE) * TL::BYTES;
   if (OWN_LDS) {
-    // group 0 copies the K rows, group 1 the V rows (two tiles of 64 rows each)
+    // group 0 copies the K rows, group 1 the V rows
     const bf16* P = base + ((grp == 0 ? a.hl : 2 * a.hl) + hd) * D;
-    const uint32_t dst = lds0 + NG * NST * STAGE + grp * 2 * TL::BYTES;
-    src.issue(P, ld, kb0, a.s, dst, wave);
-    src.issue(P, ld, kb0 + ATILE, a.s, dst + TL::BYTES, wave);
+    const uint32_t dst = lds0 + NG * NST * STAGE + grp * (BKB / ATILE) * TL::BYTES;
+    src.issue(P, ld, kb0, a.s, dst, wave_u);
+    if (BKB > ATILE) src.issue(P, ld, kb0 + ATILE, a.s, dst + TL::BYTES, wave_u);
   } else {
     const bf16* krow = base + (size_t)kc * ld + (a.hl + hd) * D;
     const bf16* vrow = base + (size_t)kc * ld + (2 * a.hl + hd) * D;
@@ -649,21 +653,21 @@ __global__ __launch_bounds__(dkv_groups<D>() * ANT) void attn_bwd_dkv_bf16_kerne
   const bf16* dOb = (const bf16*)a.dctx + (size_t)bi * a.s * ldo + hd * D;
   // per-query vectors in the workspace: [0] delta, [1] log-sum-exp in log2 units (both written by the dQ kernel)
   const size_t nrow_all = (size_t)a.b * a.hl * a.s;
-  const float* vec_b = ((wave & 1) ? a.delta + nrow_all : a.delta) + ((size_t)bi * a.hl + hd) * a.s;
+  const float* vec_b = ((wave_u & 1) ? a.delta + nrow_all : a.delta) + ((size_t)bi * a.hl + hd) * a.s;
   unsigned char* ring = lds_raw + grp * (NST * STAGE);        // this group's ring
   const uint32_t ring0 = lds0 + grp * (NST * STAGE);
   auto issue_tile = [&](int t, int st) {          // tile index relative to qt0 (clamped), ring stage
     const int r0 = (qt0 + min(t, nt - 1)) * ATILE;
     const uint32_t sb = ring0 + st * STAGE;
-    src.issue(Qb, ld, r0, a.s, sb, wave);
-    src.issue(dOb, ldo, r0, a.s, sb + TL::BYTES, wave);
+    src.issue(Qb, ld, r0, a.s, sb, wave_u);
+    src.issue(dOb, ldo, r0, a.s, sb + TL::BYTES, wave_u);
     // waves 0, 2 copy the delta vector, waves 1, 3 the log-sum-exp vector (same data twice: uniform copy counts)
-    dma4(vec_b + min(r0 + lane, a.s - 1), sb + 2 * TL::BYTES + (wave & 1) * (ATILE * 4));
+    dma4(vec_b + min(r0 + lane, a.s - 1), sb + 2 * TL::BYTES + (wave_u & 1) * (ATILE * 4));
     if (DROP) {
-      // lane t copies the four words of query r0 + t that cover this block's 128 keys (every wave copies the same
-      // kilobyte: uniform copy counts)
+      // lane t copies the four words of query r0 + t that cover this block's keys (and, of 64 keys, the other half of
+      // their 128: a row holds whole groups of four words); every wave copies the same kilobyte: uniform copy counts
       const uint32_t* src_bits = a.keep_bits + (((size_t)bi * a.hl + hd) * a.s + min(r0 + lane, a.s - 1)) * a.keep_pitch +
-                                 (kb0 >> 5);
+                                 ((kb0 >> 5) & ~3);
       dma16(reinterpret_cast<const bf16*>(src_bits), sb + 2 * TL::BYTES + VEC);
     }
   };
@@ -687,10 +691,12 @@ __global__ __launch_bounds__(dkv_groups<D>() * ANT) void attn_bwd_dkv_bf16_kerne
     const float* sLse = sDl + ATILE;
     const uint32_t* sBits = reinterpret_cast<const uint32_t*>(sLse + ATILE);   // [64 queries][4 words]
     stage = stage == NST - 1 ? 0 : stage + 1;
-    if (t >= nt || (a.causal && q0 + ATILE - 1 < kw0)) continue;   // no such tile / every query precedes this wave's keys
+    const int ql = q0 + (KG == 2 ? 32 * qh + 31 : ATILE - 1);      // this wave's last query of the tile
+    if (t >= nt || (a.causal && ql < kw0)) continue;               // no such tile / every query precedes this wave's keys
     const bool need_mask = (a.causal && q0 < kw0 + 31) || (kw0 + 32 > klen) || (q0 + ATILE > a.s);   // wave-uniform
 #pragma unroll
-    for (int qs = 0; qs < 2; ++qs) {
+    for (int qi = 0; qi < 2 / KG; ++qi) {
+      const int qs = KG == 2 ? qh : qi;
       floatx16 sacc, pacc;
 #pragma unroll
       for (int e = 0; e < 16; ++e) { sacc[e] = 0.f; pacc[e] = 0.f; }
@@ -716,7 +722,7 @@ __global__ __launch_bounds__(dkv_groups<D>() * ANT) void attn_bwd_dkv_bf16_kerne
             p = (kj >= klen || q >= a.s || (a.causal && kj > q)) ? 0.f : p;
           }
           if (DROP) {
-            const bool keep = (sBits[(qoff + e) * 4 + wave] >> l32) & 1u;
+            const bool keep = (sBits[(qoff + e) * 4 + (SPLIT ? (kb0 >> 5) & 3 : 0) + wave] >> l32) & 1u;
             sacc[4 * g + e] = keep ? p * a.drop.scale : 0.f;                                       // dropped P (for dV)
             pacc[4 * g + e] = p * ((keep ? pacc[4 * g + e] * a.drop.scale : 0.f) - dv4[e]);        // dS
           } else {
@@ -739,29 +745,34 @@ __global__ __launch_bounds__(dkv_groups<D>() * ANT) void attn_bwd_dkv_bf16_kerne
     }
   }
   wait_vmcnt<0>();
-  // dK, dV = group 0's sums + group 1's sums (group 1 parks its accumulators in LDS: [wave][value][lane])
-  if (NG == 2) {
+  // dK, dV = the sums over the waves that own the same keys, in a fixed order (all but the first park their accumulators in
+  // LDS: [value][lane] per wave)
+  if (G > 1) {
     __syncthreads();
-    constexpr int NV = 2 * (DH / 32) * 16;
+    constexpr int NV = 2 * (DH / 32) * 16, PSTEP = RW * NV * 64;
+    const int part = qh + KG * grp;
     float* park = reinterpret_cast<float*>(lds_raw) + (size_t)wave * NV * 64 + lane;
-    if (grp == 1) {
+    if (part > 0) {
+      float* dst = park + (part - 1) * PSTEP;
 #pragma unroll
       for (int dt = 0; dt < DH / 32; ++dt)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          park[(dt * 16 + e) * 64] = dk[dt][e];
-          park[((DH / 32 + dt) * 16 + e) * 64] = dv[dt][e];
+          dst[(dt * 16 + e) * 64] = dk[dt][e];
+          dst[((DH / 32 + dt) * 16 + e) * 64] = dv[dt][e];
         }
     }
     __syncthreads();
-    if (grp == 1) return;
+    if (part > 0) return;
 #pragma unroll
-    for (int dt = 0; dt < DH / 32; ++dt)
+    for (int p = 0; p < G - 1; ++p, park += PSTEP)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        dk[dt][e] += park[(dt * 16 + e) * 64];
-        dv[dt][e] += park[((DH / 32 + dt) * 16 + e) * 64];
-      }
+      for (int dt = 0; dt < DH / 32; ++dt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          dk[dt][e] += park[(dt * 16 + e) * 64];
+          dv[dt][e] += park[((DH / 32 + dt) * 16 + e) * 64];
+        }
   }
   if (kj < a.s) {
     bf16* krow = (bf16*)a.dqkv + ((size_t)bi * a.s + kj) * ld + (a.hl + hd) * D;
@@ -841,25 +852,31 @@ static hipError_t launch_fwd_d(const AttnArgs& a, hipStream_t st) {
   return a.drop.enabled ? launch_fwd_dd<D, true>(a, st) : launch_fwd_dd<D, false>(a, st);
 }
 
+template <int D, bool DROP, bool SPLIT>
+static hipError_t launch_dkv(const AttnArgs& a, hipStream_t st) {
+  constexpr int RW = SPLIT ? 2 : ANW, NG = dkv_groups<D>(), G = NG * ANW / RW;
+  constexpr size_t kStage = 2 * ATile<D>::BYTES + 2 * ATILE * 4 + (DROP ? ATILE * 16 : 0);
+  // rings and the owned K / V rows (two groups); at the end the parked accumulators
+  constexpr size_t kOwn = (NG == 2 && dkv_own_lds<D>()) ? RW * ATile<D>::BYTES : 0;
+  constexpr size_t kRing = (size_t)NG * dkv_stages<D>() * kStage + kOwn;
+  constexpr size_t kPark = (size_t)(G - 1) * RW * 2 * (D / dkv_dsplit<D>() / 32) * 16 * 64 * 4;
+  constexpr size_t kLds = kRing > kPark ? kRing : kPark;
+  static_assert(kLds <= 160 * 1024, "LDS budget");
+  static LdsAttrOnce attr;
+  if (kLds > 64 * 1024)
+    if (hipError_t e = attr.ensure((const void*)attn_bwd_dkv_bf16_kernel<D, DROP, SPLIT>, (int)kLds); e != hipSuccess) return e;
+  const dim3 grid = attn_grid((a.s + 32 * RW - 1) / (32 * RW) * dkv_dsplit<D>(), a.hl, a.b);
+  hipLaunchKernelGGL((attn_bwd_dkv_bf16_kernel<D, DROP, SPLIT>), grid, dim3(NG * ANT), kLds, st, a);
+  return hipGetLastError();
+}
+
 template <int D, bool DROP>
 static hipError_t launch_bwd_dd(const AttnArgs& a, hipStream_t st) {
-  const int nblk = (a.s + 32 * ANW - 1) / (32 * ANW);
-  hipError_t e = launch_dq_dd<D, DROP>(a, st);
-  if (e != hipSuccess) return e;
-  constexpr int NGK = dkv_groups<D>(), NSK = dkv_stages<D>();
-  constexpr size_t kStageKv = 2 * ATile<D>::BYTES + 2 * ATILE * 4;
-  // rings, the owned K / V rows (two groups), and at the end the parked accumulators of group 1
-  constexpr size_t kOwn = (NGK == 2 && dkv_own_lds<D>()) ? 4 * ATile<D>::BYTES : 0;
-  constexpr size_t kPark = NGK == 2 ? (size_t)ANW * 2 * (D / dkv_dsplit<D>() / 32) * 16 * 64 * 4 : 0;
-  static_assert((size_t)NGK * NSK * (kStageKv + ATILE * 16) + kOwn <= 160 * 1024 && kPark <= 160 * 1024, "LDS budget");
-  size_t lds_kv = (size_t)NGK * NSK * (kStageKv + (DROP ? ATILE * 16 : 0)) + kOwn;
-  if (lds_kv < kPark) lds_kv = kPark;
-  static LdsAttrOnce attr;
-  if (lds_kv > 64 * 1024)
-    if (e = attr.ensure((const void*)attn_bwd_dkv_bf16_kernel<D, DROP>, (int)lds_kv); e != hipSuccess) return e;
-  const dim3 grid_kv = attn_grid(nblk * dkv_dsplit<D>(), a.hl, a.b);
-  hipLaunchKernelGGL((attn_bwd_dkv_bf16_kernel<D, DROP>), grid_kv, dim3(NGK * ANT), lds_kv, st, a);
-  return hipGetLastError();
+  if (hipError_t e = launch_dq_dd<D, DROP>(a, st); e != hipSuccess) return e;
+  // 64-key workgroups where 128-key ones would leave half of the compute units idle (d = 192 needs one wave per SIMD)
+  if constexpr (D <= 128)
+    if (2 * dkv_dsplit<D>() * ((a.s + 127) / 128) * a.hl * a.b <= gemm_cu_count()) return launch_dkv<D, DROP, true>(a, st);
+  return launch_dkv<D, DROP, false>(a, st);
 }
 
 template <int D>
