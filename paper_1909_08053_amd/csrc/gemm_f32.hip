@@ -95,7 +95,7 @@ struct F32Tile {
   static constexpr int PER = ROWS * KT / 4 / NT;             // float4 per thread
   static_assert(ROWS * KT % (4 * NT) == 0, "tile does not divide over the threads");
   float4 reg[PER];
-  uint32_t ofs[PER];           // bytes from the tile's first element to this thread's i-th vector (at most 128 rows apart)
+  uint32_t ofs[PER];           // bytes from the tile's first element to this thread's i-th vector (kF32MaxK128 bounds them)
   // where thread tid's i-th vector lies in the tile
   __device__ static __forceinline__ int row_of(int i, int tid) {
     const int v = tid + i * NT;
@@ -406,6 +406,9 @@ static hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t st) {
 // 1024^3: 48 us (split), 23 us (64); 4096^3: 2540 (split), 985-1000 us (128: 139 TFLOP/s, the matrix cores' peak is 157);
 // 256 x 256 x 512: < 10 us (split).  (One 64 x 64-tile kernel on the vector ALUs, 15.7 TFLOP/s at most, took
 // 200 us for 1024^3 and 60 us for 256 x 256 x 512 before.)
+// (A tile's lane offsets are 32-bit byte counts: 127 rows of a k-contiguous operand stay below 4 GiB up to this K, 63 rows up
+// to the 2^24 that mlm_gemm accepts.)
+constexpr int kF32MaxK128 = 1 << 23;
 static int f32_pick(int M, int N, int K) {
   auto tiles = [&](int b) { return (double)((M + b - 1) / b) * ((N + b - 1) / b); };
   const int cus = gemm_cu_count();
@@ -417,6 +420,7 @@ static int f32_pick(int M, int N, int K) {
   const double split = 3.0 + 6.0 * k + 2.0 * M * N * K / 52e6;
   const double t64 = 4.0 + rounds(64, 31.5, 17.3) * k, t128 = 3.0 + rounds(128, 119.0, 63.0) * k;
   if (split <= t64 && split <= t128) return 32;
+  if (K > kF32MaxK128) return 64;
   return t64 <= t128 ? 64 : 128;
 }
 
