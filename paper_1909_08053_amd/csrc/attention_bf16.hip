@@ -804,7 +804,7 @@ bool attn_bf16_supported(int d) { return d == 64 || d == 96 || d == 128 || d == 
 // d = 192: 128 42.4 / 55.9, -, 34.7 / 39.1; 512 86 / 115, -, 108 / 125.
 template <int D>
 static AttnMode attn_mode(const AttnArgs& a) {
-  const int wgs = (a.s + 127) / 128 * a.hl * a.b, cus = gemm_cu_count();
+  const long wgs = (long)((a.s + 127) / 128) * a.hl * a.b, cus = gemm_cu_count();
   if (2 * wgs <= cus) return ATTN_SPLIT;
   return D > 128 || wgs > cus ? ATTN_WIDE : ATTN_PAIR;
 }
@@ -875,7 +875,7 @@ static hipError_t launch_bwd_dd(const AttnArgs& a, hipStream_t st) {
   if (hipError_t e = launch_dq_dd<D, DROP>(a, st); e != hipSuccess) return e;
   // 64-key workgroups where 128-key ones would leave half of the compute units idle (d = 192 needs one wave per SIMD)
   if constexpr (D <= 128)
-    if (2 * dkv_dsplit<D>() * ((a.s + 127) / 128) * a.hl * a.b <= gemm_cu_count()) return launch_dkv<D, DROP, true>(a, st);
+    if (2L * dkv_dsplit<D>() * ((a.s + 127) / 128) * a.hl * a.b <= gemm_cu_count()) return launch_dkv<D, DROP, true>(a, st);
   return launch_dkv<D, DROP, false>(a, st);
 }
 
