@@ -228,7 +228,8 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dq_f32_kernel(AttnA
     for (int e = 0; e < 16; ++e) {
       const int key = k0 + 8 * (e >> 2) + 4 * lh + (e & 3);
       const bool off = key >= klen || (a.causal && key > qi);
-      const float p = off ? 0.f : expf(s[e] * scale - lse);
+      const float pe = expf(s[e] * scale - lse);
+      const float p = off ? 0.f : pe;
       // gradient w.r.t. the undropped probability
       const float g = ((bits >> (8 * (e >> 2) + (e & 3))) & 1u) ? dp[e] * a.drop.scale : 0.f;
       s[e] = p * (g - dl);
@@ -285,18 +286,33 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dkv_f32_kernel(Attn
   const int q_begin = kb0 >= klen ? a.s : (a.causal ? kb0 : 0);
   for (int q0 = q_begin + wave * AF_ROWS; q0 < a.s; q0 += AF_WAVES * AF_ROWS) {
     const int qr = min(q0 + l32, a.s - 1);
+    // the tile's per-query values are requested ahead of the scores, and the mask selects the finished probability: with
+    // the loads behind the mask they were taken one by one inside branches (fp32 layer step 1342 -> 1314 us)
+    float lse[16], del[16];
+    uint32_t bits[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int ic = min(q0 + 8 * (e >> 2) + 4 * lh + (e & 3), a.s - 1);
+      lse[e] = a.lse[row0 + ic];
+      del[e] = a.delta[row0 + ic];
+    }
+    if (a.drop.enabled) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        bits[e] = a.keep_bits[(row0 + min(q0 + 8 * (e >> 2) + 4 * lh + (e & 3), a.s - 1)) * a.keep_pitch + (kb0 >> 5)];
+    }
     floatx16 s = af_scores<D>(Q + (size_t)qr * ld, lh, kf);          // [query][key]
     floatx16 dp = af_scores<D>(dO + (size_t)qr * ldo, lh, vf);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const int i = q0 + 8 * (e >> 2) + 4 * lh + (e & 3), ic = min(i, a.s - 1);
+      const int i = q0 + 8 * (e >> 2) + 4 * lh + (e & 3);
       const bool off = kj >= klen || i >= a.s || (a.causal && kj > i);
-      const float p = off ? 0.f : expf(s[e] * scale - a.lse[row0 + ic]);
+      const float pe = expf(s[e] * scale - lse[e]);
+      const float p = off ? 0.f : pe;
       float keep = 1.0f;
-      if (a.drop.enabled)
-        keep = ((a.keep_bits[(row0 + ic) * a.keep_pitch + (kb0 >> 5)] >> l32) & 1u) ? a.drop.scale : 0.f;
+      if (a.drop.enabled) keep = ((bits[e] >> l32) & 1u) ? a.drop.scale : 0.f;
       s[e] = p * keep;
-      dp[e] = p * (dp[e] * keep - a.delta[row0 + ic]);
+      dp[e] = p * (dp[e] * keep - del[e]);
     }
     af_accumulate<D>(dO, ldo, q0, a.s, lane, s, dv);
     af_accumulate<D>(Q, ld, q0, a.s, lane, dp, dk);
