@@ -78,6 +78,58 @@ __device__ __forceinline__ void af_accumulate(const float* __restrict__ M, int l
     }
   }
 }
+// af_accumulate for a tile in which, if `edge`, some pairs are excluded (off(e): this lane's pair e is).  An excluded pair's weight is
+// zero, but zero times Inf or NaN is NaN and the matrix cores multiply every pair: a lane that is left with a sum that is not
+// finite adds the tile again pair by pair, the allowed ones only.  (Looking at the sums costs a layer of two
+// sequences of 512 tokens, 16 heads of 64, 5 us of 1324; looking at the rows beforehand, a trip to memory ahead of every such
+// tile, cost it 40.)
+template <int D, typename Off>
+__device__ __forceinline__ void af_accumulate_masked(const float* __restrict__ M, int ld, int r0, int nrows, int lane,
+                                                     const floatx16& w, bool edge, Off off, floatx16 (&out)[AfShape<D>::DT]) {
+  floatx16 before[AfShape<D>::DT];
+#pragma unroll
+  for (int dt = 0; dt < AfShape<D>::DT; ++dt) before[dt] = out[dt];
+  af_accumulate<D>(M, ld, r0, nrows, lane, w, out);
+  if (!edge) return;
+  float x[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int dt = 0; dt < AfShape<D>::DT; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) x[e & 3] = fmaf(0.f, out[dt][e], x[e & 3]);       // 0, or NaN
+  const float xs = (x[0] + x[1]) + (x[2] + x[3]);
+  const bool again = xs != xs;
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(again) == 0, 1)) return;
+  uint32_t allow = 0;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) allow |= off(e) ? 0u : 1u << e;
+#pragma unroll
+  for (int dt = 0; dt < AfShape<D>::DT; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) out[dt][e] = again ? before[dt][e] : out[dt][e];
+  const int l32 = lane & 31, lh = lane >> 5;
+#pragma unroll 1
+  for (int r = 0; r < AF_ROWS; ++r) {
+    const int e = 4 * (r >> 3) + (r & 3), src = l32 + 32 * ((r >> 2) & 1);    // where the weight of streamed row r is
+    float we = w[0];
+#pragma unroll
+    for (int q = 1; q < 16; ++q) we = q == e ? w[q] : we;
+    we = __shfl(we, src, 64);
+    const bool on = (__shfl(allow, src, 64) >> e) & 1u;
+    if (!on || !again) continue;                       // (an allowed row lies inside the sequence)
+    const float* p = M + (size_t)(r0 + r) * ld + 4 * lh;
+#pragma unroll
+    for (int dt = 0; dt < AfShape<D>::DT; ++dt)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        if (dt * 32 + 8 * g >= D) continue;
+        const float4 v = *reinterpret_cast<const float4*>(p + dt * 32 + 8 * g);
+        out[dt][4 * g] = fmaf(v.x, we, out[dt][4 * g]);
+        out[dt][4 * g + 1] = fmaf(v.y, we, out[dt][4 * g + 1]);
+        out[dt][4 * g + 2] = fmaf(v.z, we, out[dt][4 * g + 2]);
+        out[dt][4 * g + 3] = fmaf(v.w, we, out[dt][4 * g + 3]);
+      }
+  }
+}
 // The waves' accumulators parked in LDS ([wave][value][lane]: conflict-free)
 template <int NV> __device__ __forceinline__ float* af_park(float* lds, int wave, int lane) { return lds + (size_t)wave * NV * 64 + lane; }
 
@@ -110,10 +162,13 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_fwd_f32_kernel(AttnArgs
   for (int k0 = wave * AF_ROWS; k0 < kv_end; k0 += AF_WAVES * AF_ROWS) {
     floatx16 s = af_scores<D>(K + (size_t)min(k0 + l32, a.s - 1) * ld, lh, q);
     float mt = -INFINITY;
+    auto off = [&](int e) {
+      const int key = k0 + 8 * (e >> 2) + 4 * lh + (e & 3);
+      return key >= klen || (a.causal && key > qi);
+    };
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const int key = k0 + 8 * (e >> 2) + 4 * lh + (e & 3);
-      s[e] = (key >= klen || (a.causal && key > qi)) ? -INFINITY : s[e] * scale;
+      s[e] = off(e) ? -INFINITY : s[e] * scale;
       mt = fmaxf(mt, s[e]);
     }
     // key k0 is allowed for every query of the block (k0 < kv_end, and a causal tile never starts right of the block's
@@ -144,7 +199,8 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_fwd_f32_kernel(AttnArgs
       word |= __shfl_xor(word, 32, 64);
       if (lh == 0 && qi < a.s) a.keep_bits[prow * a.keep_pitch + (k0 >> 5)] = word;
     }
-    af_accumulate<D>(V, ld, k0, a.s, lane, s, o);
+    const bool edge = k0 + AF_ROWS > klen || (a.causal && k0 + AF_ROWS - 1 > q0);      // wave-uniform
+    af_accumulate_masked<D>(V, ld, k0, a.s, lane, s, edge, off, o);
   }
   float* park = af_park<NV>(lds_af, wave, lane);
 #pragma unroll
@@ -224,17 +280,20 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dq_f32_kernel(AttnA
     floatx16 s = af_scores<D>(K + (size_t)kr * ld, lh, q);
     const floatx16 dp = af_scores<D>(V + (size_t)kr * ld, lh, dov);
     const uint32_t bits = a.drop.enabled ? a.keep_bits[row * a.keep_pitch + (k0 >> 5)] >> (4 * lh) : 0xFFFFFFFFu;
+    auto off = [&](int e) {
+      const int key = k0 + 8 * (e >> 2) + 4 * lh + (e & 3);
+      return key >= klen || (a.causal && key > qi);
+    };
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const int key = k0 + 8 * (e >> 2) + 4 * lh + (e & 3);
-      const bool off = key >= klen || (a.causal && key > qi);
-      const float pe = expf(s[e] * scale - lse);
-      const float p = off ? 0.f : pe;
+      const float p = expf(s[e] * scale - lse);
       // gradient w.r.t. the undropped probability
       const float g = ((bits >> (8 * (e >> 2) + (e & 3))) & 1u) ? dp[e] * a.drop.scale : 0.f;
-      s[e] = p * (g - dl);
+      const float ds = p * (g - dl);
+      s[e] = off(e) ? 0.f : ds;
     }
-    af_accumulate<D>(K, ld, k0, a.s, lane, s, dq);
+    const bool edge = k0 + AF_ROWS > klen || (a.causal && k0 + AF_ROWS - 1 > q0);      // wave-uniform
+    af_accumulate_masked<D>(K, ld, k0, a.s, lane, s, edge, off, dq);
   }
   float* park = af_park<NV>(lds_af, wave, lane);
 #pragma unroll
@@ -303,19 +362,22 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dkv_f32_kernel(Attn
     }
     floatx16 s = af_scores<D>(Q + (size_t)qr * ld, lh, kf);          // [query][key]
     floatx16 dp = af_scores<D>(dO + (size_t)qr * ldo, lh, vf);
+    auto off = [&](int e) {
+      const int i = q0 + 8 * (e >> 2) + 4 * lh + (e & 3);
+      return kj >= klen || i >= a.s || (a.causal && kj > i);
+    };
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const int i = q0 + 8 * (e >> 2) + 4 * lh + (e & 3);
-      const bool off = kj >= klen || i >= a.s || (a.causal && kj > i);
-      const float pe = expf(s[e] * scale - lse[e]);
-      const float p = off ? 0.f : pe;
+      const float p = expf(s[e] * scale - lse[e]);
       float keep = 1.0f;
       if (a.drop.enabled) keep = ((bits[e] >> l32) & 1u) ? a.drop.scale : 0.f;
-      s[e] = p * keep;
-      dp[e] = p * (dp[e] * keep - del[e]);
+      const float pd = p * keep, ds = p * (dp[e] * keep - del[e]);
+      s[e] = off(e) ? 0.f : pd;
+      dp[e] = off(e) ? 0.f : ds;
     }
-    af_accumulate<D>(dO, ldo, q0, a.s, lane, s, dv);
-    af_accumulate<D>(Q, ld, q0, a.s, lane, dp, dk);
+    const bool edge = kb0 + AF_ROWS > klen || q0 + AF_ROWS > a.s || (a.causal && kb0 + AF_ROWS - 1 > q0);   // wave-uniform
+    af_accumulate_masked<D>(dO, ldo, q0, a.s, lane, s, edge, off, dv);
+    af_accumulate_masked<D>(Q, ld, q0, a.s, lane, dp, edge, off, dk);
   }
   float* park = af_park<NV>(lds_af, wave, lane);
 #pragma unroll
