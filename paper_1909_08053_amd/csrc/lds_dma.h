@@ -12,13 +12,14 @@ typedef short v8s_t __attribute__((ext_vector_type(8)));
 // One wave-wide 16-byte-per-lane copy HBM -> LDS: lane t's 16 bytes land at lds_addr + 16 t (lds_addr is the
 // wave-uniform LDS byte address, passed in M0).  Written as inline assembly so that the compiler's conservative
 // "LDS DMA may alias any LDS read" rule does not turn every fragment read into s_waitcnt vmcnt(0); completion is
-// tracked by hand with wait_vmcnt<> below.
+// tracked by hand with wait_vmcnt<> below.  (s_nop: the wait state that gfx950 wants between a scalar write of M0 and a copy
+// into LDS; the compiler keeps it only between instructions of its own)
 __device__ __forceinline__ void dma16(const bf16* g, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(g) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(g) : "memory");
 }
 // Same with 4 bytes per lane: lane t's dword lands at lds_addr + 4 t (one 256-byte vector per wave instruction).
 __device__ __forceinline__ void dma4(const float* g, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_addr), "v"(g) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_addr), "v"(g) : "memory");
 }
 __device__ __forceinline__ uint32_t lds_offset_of(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)p;
