@@ -183,9 +183,18 @@ struct V2Plan {
 // in 0.88 of the time, so it wins where it saves a round or fills one and loses on long-k shapes whose last round
 // can be split instead.  The fix-up kernel reads the pieces mostly out of the last-level cache.
 // The small tile has two: `alone` with at most one workgroup per compute unit in the launch, else for two that share one
-// (fitted to 120 .. 512 tiles of 24 .. 256 slices).
-inline double v2_tile_cost(int bn, int nk, bool alone) {
-  if (bn == V2_SMALL) return alone ? 4.5 + 0.24 * nk : 6.0 + 0.43 * nk;
+// (fitted to 60 .. 2600 tiles of 48 .. 256 slices).  Two that share one are bound by what their XCD's L2 has to fetch: ids go
+// to the eight XCDs in turn and the tile row is the fast index, so with an odd number of tile rows every XCD works on all of
+// them, and with few rows on many columns.  128 against 256 and 192 wide, weight-gradient layout, 8192 deep: 1920 x 12800 (15
+// tile rows) 591 / 347 / 419 us, 8064 x 1024 (63 rows) 173 / 153 / 137, 1024 x 7680 (8 rows) 169 / 155 / 138; but 2048 x 3840
+// (16 rows) 126 / 154 / 136.  With the row count left out of the model, 172 of 1985 shapes took the small tile where the
+// large one it would take otherwise is 3 .. 76 % faster; with it none does by more than 3 %.
+inline double v2_small_slice(int tiles_m, int tiles) {
+  if (tiles_m % 2 || tiles_m <= 10) return 0.72;
+  return tiles > 2 * gemm_cu_count() ? 0.46 : 0.43;
+}
+inline double v2_tile_cost(int bn, int nk, bool alone, double small_slice) {
+  if (bn == V2_SMALL) return alone ? 4.5 + 0.24 * nk : 6.0 + small_slice * nk;
   return bn == V2_B ? 9.2 + 0.67 * nk : 8.0 + 0.59 * nk;
 }
 inline double v2_fixup_cost(double traffic_us) { return 3.0 + 0.6 * traffic_us; }
@@ -206,21 +215,22 @@ inline V2Plan v2_plan(int M, int N, int K, bool allow_split, int bn = V2_B) {
   const int nk = v2_slices(K);
   int split = 1;
   const bool alone = tiles <= cus;
-  double tail = rem ? v2_tile_cost(bn, nk, alone) : 0.0;   // unsplit tail round
+  const double ss = v2_small_slice(p.tiles_m, tiles);
+  double tail = rem ? v2_tile_cost(bn, nk, alone, ss) : 0.0;   // unsplit tail round
   if (allow_split && rem != 0 && rem * 2 <= cus) {
     int smax = cus / rem;
     if (smax > 16) smax = 16;
     for (int sp = 2; sp <= smax; ++sp) {
       if (nk / sp < 8) break;                         // keep at least 8 k-slices per piece
       const double traffic = (double)rem * sp * (p.bm * (double)bn * 4.0) / 5.0e6;
-      const double t = v2_tile_cost(bn, (nk + sp - 1) / sp, alone) + traffic + v2_fixup_cost(traffic);
+      const double t = v2_tile_cost(bn, (nk + sp - 1) / sp, alone, ss) + traffic + v2_fixup_cost(traffic);
       if (t < tail) { tail = t; split = sp; }
     }
   }
   p.split = split;
   p.tail_tiles = split > 1 ? rem : 0;
   p.full_tiles = tiles - p.tail_tiles;
-  p.cost = (tiles / per_round) * v2_tile_cost(bn, nk, false) + tail;
+  p.cost = (tiles / per_round) * v2_tile_cost(bn, nk, false, ss) + tail;
   return p;
 }
 
@@ -582,6 +592,18 @@ hipError_t launch_gemm_bf16_v2_bn(const GemmArgs& a, float* splitk_ws, hipStream
 
 // Tiles (work items without a k-split) of one problem.
 inline int v2_tiles(const GemmArgs& a, int bm, int bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); }
+
+// Estimated time (microseconds) of the tiles of all problems in one launch without a k-split.  The last round of the small
+// tile, where it leaves compute units with one workgroup, runs at that one's pace (1200 tiles of 128 slices, 2.34 rounds: 155 us).
+inline double v2_group_cost(const GemmArgs* probs, int n, int bn) {
+  const int bm = bn == V2_SMALL ? V2_SMALL : V2_B, cus = gemm_cu_count(), per_round = bn == V2_SMALL ? 2 * cus : cus;
+  int tiles = 0;
+  for (int q = 0; q < n; ++q) tiles += v2_tiles(probs[q], bm, bn);
+  double ss = 0.0;                     // mean over the tiles
+  for (int q = 0; q < n; ++q) ss += v2_small_slice((probs[q].M + bm - 1) / bm, tiles) * v2_tiles(probs[q], bm, bn) / tiles;
+  const int nk = v2_slices(probs[0].K), rem = tiles % per_round;
+  return (tiles / per_round) * v2_tile_cost(bn, nk, false, ss) + (rem ? v2_tile_cost(bn, nk, rem <= cus, ss) : 0.0);
+}
 
 template <bool A_KC, bool B_KC, int BN, bool RAG, bool DEEP>
 hipError_t launch_gemm_bf16_v2_group(const GemmArgs* probs, int n, hipStream_t st) {

@@ -10,15 +10,6 @@ hipError_t launch_gemm_bf16_wgrad(const GemmArgs& a, hipStream_t st) {
   return launch_gemm_bf16_v2<false, false, EPI_STORE>(a, a.splitk_ws, st);
 }
 
-// Estimated time (microseconds) of the tiles of all problems in one launch without a k-split.
-static double group_cost(const GemmArgs* probs, int n, int bn) {
-  const int bm = bn == V2_SMALL ? V2_SMALL : V2_B, cus = gemm_cu_count(), per_round = bn == V2_SMALL ? 2 * cus : cus;
-  int tiles = 0;
-  for (int q = 0; q < n; ++q) tiles += v2_tiles(probs[q], bm, bn);
-  const int nk = v2_slices(probs[0].K), rem = tiles % per_round;
-  return (tiles / per_round) * v2_tile_cost(bn, nk, false) + (rem ? v2_tile_cost(bn, nk, tiles <= cus) : 0.0);
-}
-
 // The weight gradients of a layer shard (same operand layout, same k = tokens).  One grouped launch, in the tile size that
 // fills the chip better, when the cost model says the shared last round beats the separate launches with their
 // k-splits; separate launches otherwise.
@@ -31,7 +22,7 @@ hipError_t launch_gemm_bf16_wgrad_group(const GemmArgs* probs, int n, float* spl
     alone += v2_plan(M, N, K, true, v2_pick_bn<false, false, EPI_STORE>(M, N, K, true)).cost + 2.0;   // + launch and drain
   }
   if (groupable) {
-    const double big = group_cost(probs, n, V2_B), small = group_cost(probs, n, V2_SMALL);
+    const double big = v2_group_cost(probs, n, V2_B), small = v2_group_cost(probs, n, V2_SMALL);
     const int forced = gemm_v2_forced_bn();
     const bool use_small = forced ? forced == V2_SMALL : small < big;
     static const bool off = [] { const char* e = getenv("MLM_GEMM_GROUP"); return e && atoi(e) == 0; }();

@@ -1,0 +1,71 @@
+"""Tile choice of the bf16 GEMM (no GPU needed: the plan is host arithmetic), against shapes whose three tiles were measured."""
+import subprocess
+
+import pytest
+
+from paper_1909_08053_amd import build as BLD
+
+MAIN = """#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+#include "gemm_bf16_v2.h"
+namespace mlm {
+int gemm_cu_count() { return 256; }
+int gemm_v2_forced_bn() { return 0; }
+}
+using namespace mlm;
+int main(int argc, char** argv) {          // "layout M N K" -> tile width; "g T H p" -> tile width of the grouped launch
+  char kind[8];
+  int x, y, z;
+  while (scanf("%7s %d %d %d", kind, &x, &y, &z) == 4) {
+    if (kind[0] == 'g') {
+      const int T = x, H = y, Hl = y / z, Fl = 4 * y / z;
+      GemmArgs a[4];
+      memset(a, 0, sizeof(a));
+      const int mn[4][2] = {{Fl, H}, {H, Fl}, {H, 3 * Hl}, {Hl, H}};
+      for (int q = 0; q < 4; ++q) { a[q].M = mn[q][0]; a[q].N = mn[q][1]; a[q].K = T; }
+      printf("%d\\n", v2_group_cost(a, 4, V2_SMALL) < v2_group_cost(a, 4, V2_B) ? V2_SMALL : V2_B);
+    } else if (!strcmp(kind, "fwd")) printf("%d\\n", v2_pick_bn<true, false, EPI_STORE>(x, y, z, false));
+    else if (!strcmp(kind, "dgrad")) printf("%d\\n", v2_pick_bn<true, true, EPI_STORE>(x, y, z, false));
+    else printf("%d\\n", v2_pick_bn<false, false, EPI_STORE>(x, y, z, false));
+  }
+  return 0;
+}
+"""
+
+# layout, M, N, K and the microseconds measured for the 128-, 192- and 256-wide tile
+MEASURED = [
+    ("wgrad", 1920, 25600, 8192, 1321, 743, 719), ("fwd", 1920, 12800, 6144, 410, 314, 259), ("wgrad", 3200, 7680, 8192, 599, 421, 341),
+    ("wgrad", 1920, 12800, 8192, 591, 419, 347), ("fwd", 3200, 7680, 6144, 406, 313, 256), ("dgrad", 8064, 1024, 6144, 125, 88, 112),
+    ("fwd", 8064, 1024, 1536, 37, 31, 36), ("fwd", 768, 10240, 6144, 117, 96, 108), ("dgrad", 1024, 7680, 6144, 109, 98, 109),
+    ("wgrad", 8064, 1024, 8192, 173, 137, 153), ("fwd", 896, 7552, 6144, 130, 101, 115), ("wgrad", 3968, 2048, 8192, 191, 132, 151),
+    # where the small tile is the better one it stays
+    ("wgrad", 2048, 3840, 8192, 126, 136, 154), ("wgrad", 2560, 2560, 4096, 57, 68, 81), ("wgrad", 960, 1920, 8192, 65, 115, 140),
+    ("fwd", 4096, 1920, 2560, 39, 42, 49), ("dgrad", 2048, 3072, 1024, 18.9, 20.4, 22.7),
+]
+# tokens, width, ways of the split and the microseconds of the grouped weight gradients of a layer shard, 128- and 256-wide tile
+GROUPS = [(8192, 1920, 2, 473, 361), (5000, 1920, 2, 285, 230), (8192, 1536, 1, 520, 379), (8192, 2304, 4, 310, 259),
+          (8192, 3072, 8, 259, 195), (4096, 3072, 4, 214, 187), (4096, 2560, 4, 155, 173), (8192, 1536, 8, 78, 147),
+          (3000, 1536, 4, 53, 67), (8192, 1536, 4, 149, 154)]
+
+
+@pytest.fixture(scope="module")
+def picks(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    src, exe = d / "plan.hip", d / "plan"
+    src.write_text(MAIN)
+    subprocess.run([BLD._hipcc(), *BLD.FLAGS, str(src), "-o", str(exe)], check=True, capture_output=True, timeout=180)
+    lines = [f"{m[0]} {m[1]} {m[2]} {m[3]}" for m in MEASURED] + [f"g {g[0]} {g[1]} {g[2]}" for g in GROUPS]
+    out = subprocess.run([str(exe)], input="\n".join(lines), text=True, check=True, capture_output=True, timeout=60).stdout.split()
+    return [int(x) for x in out]
+
+
+def test_chosen_tile_is_within_five_percent_of_the_best(picks):
+    for m, bn in zip(MEASURED, picks):
+        us = dict(zip((128, 192, 256), m[4:]))
+        assert us[bn] <= 1.05 * min(us.values()), (m, bn)
+
+
+def test_grouped_weight_gradients_take_the_better_tile(picks):
+    for g, bn in zip(GROUPS, picks[len(MEASURED):]):
+        assert g[3 if bn == 128 else 4] <= 1.05 * min(g[3:]), (g, bn)
