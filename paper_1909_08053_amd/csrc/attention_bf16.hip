@@ -20,6 +20,7 @@
 // log-sum-exp stay those of the undropped scores.  The backward kernels read the saved bits instead of running the
 // generator again: dQ loads its query row's two words per tile, dK/dV gets the tile's 64 x 128-bit block through the
 // DMA ring.  delta = rowsum(dO o O) needs no change: O already contains the dropout.
+#include "attention_modes.h"
 #include "lds_dma.h"
 #include "rng.h"
 
@@ -128,12 +129,12 @@ struct ATileSrc {
 // waves along the 64 keys of a tile, NG groups of RW x KG = 4 waves that take every NG-th tile through a DMA ring of their
 // own.  The partial results of the KG NG waves that own the same rows are merged through LDS at the end.
 //   WIDE  (4 x 1 x 1): no merge, and two workgroups fit a compute unit (d <= 128), so that one's first copies and last
-//         stores run under the other's steps: for launches of more than one workgroup per compute unit.
+//         stores run under the other's steps.
 //   PAIR  (4 x 1 x 2): halves the serial chain of the longest (causal) blocks and puts two waves on every SIMD where a
 //         compute unit has one workgroup.  d = 192 has no LDS for the second ring.
 //   SPLIT (2 x 2 x NG): 64 rows per workgroup, for launches that leave compute units without one; each wave multiplies
 //         half of a tile.
-enum AttnMode { ATTN_WIDE, ATTN_PAIR, ATTN_SPLIT };
+// (attention_modes.h holds the rule and the figures)
 template <int D, int MODE> struct AttnSplit {
   static constexpr int RW = MODE == ATTN_SPLIT ? 2 : 4, KG = ANW / RW;
   static constexpr int NG = MODE == ATTN_WIDE || D > 128 ? 1 : 2;
@@ -577,9 +578,7 @@ __global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW
 // 128 K and V rows are copied to LDS once and their fragments are read per use.
 // Larger heads keep one group (their accumulators alone need more registers) and split the D columns of dK / dV over
 // two workgroups instead.
-// SPLIT: 64 keys per workgroup, and two waves of each group share a tile's 64 queries: for launches that leave compute units
-// without a workgroup.  128 workgroups of 128 keys, d = 96: 29.1 -> 21.7 us; 64 of d = 128 31.8 -> 24.5; 64 of d = 64
-// (s = 512) 15.0 -> 11.1.
+// SPLIT: 64 keys per workgroup, and two waves of each group share a tile's 64 queries (attn_dkv_split: when).
 template <int D, bool DROP, bool SPLIT>
 __global__ __launch_bounds__(dkv_groups<D>() * ANT) void attn_bwd_dkv_bf16_kernel(AttnArgs a) {
   typedef ATile<D> TL;
@@ -796,19 +795,6 @@ __global__ __launch_bounds__(dkv_groups<D>() * ANT) void attn_bwd_dkv_bf16_kerne
 // ------------------------------------------------------------------------------------------ launchers
 bool attn_bf16_supported(int d) { return d == 64 || d == 96 || d == 128 || d == 192; }
 
-// By the number of 128-row workgroups.  Forward / dQ kernels measured as WIDE, PAIR, SPLIT (us, causal, s = 1024 unless
-// noted): d = 96: 80 workgroups 22.9 / 25.2, 21.1 / 24.5, 18.6 / 19.3; 128 23.2 / 26.8, 22.6 / 25.7, 18.3 / 20.5; 256
-// 25.5 / 28.7, 23.8 / 29.1, 32.3 / 34.9; 384 37.6 / 42.4, 37.3 / 45.4, 43.7 / 48.9; 1024 65 / 77, 83 / 102, 109 / 124.
-// d = 64: 144 19.7 / 20.8, 16.7 / 19.9, 18.9 / 21.3; 320 of s = 512 without a mask 16.8 / 20.1, 21.4 / 25.6, 25.6 / 28.6.
-// d = 128: 64 25.3 / 36.9, 23.8 / 30.6, 20.6 / 24.5; 192 27.0 / 38.8, 25.6 / 32.8, 31.0 / 38.6; 768 62 / 85, 72 / 97, 97 / 122.
-// d = 192: 128 42.4 / 55.9, -, 34.7 / 39.1; 512 86 / 115, -, 108 / 125.
-template <int D>
-static AttnMode attn_mode(const AttnArgs& a) {
-  const long wgs = (long)((a.s + 127) / 128) * a.hl * a.b, cus = gemm_cu_count();
-  if (2 * wgs <= cus) return ATTN_SPLIT;
-  return D > 128 || wgs > cus ? ATTN_WIDE : ATTN_PAIR;
-}
-
 template <int D, bool DROP, int MODE>
 static hipError_t launch_fwd_m(const AttnArgs& a, hipStream_t st) {
   typedef AttnSplit<D, MODE> SP;
@@ -833,7 +819,7 @@ static hipError_t launch_dq_m(const AttnArgs& a, hipStream_t st) {
 
 template <int D, bool DROP>
 static hipError_t launch_fwd_dd(const AttnArgs& a, hipStream_t st) {
-  const AttnMode m = attn_mode<D>(a);
+  const AttnMode m = attn_mode(a.s, a.hl * a.b, a.causal != 0, D);
   if constexpr (D <= 128)
     if (m == ATTN_PAIR) return launch_fwd_m<D, DROP, ATTN_PAIR>(a, st);
   return m == ATTN_SPLIT ? launch_fwd_m<D, DROP, ATTN_SPLIT>(a, st) : launch_fwd_m<D, DROP, ATTN_WIDE>(a, st);
@@ -841,7 +827,7 @@ static hipError_t launch_fwd_dd(const AttnArgs& a, hipStream_t st) {
 
 template <int D, bool DROP>
 static hipError_t launch_dq_dd(const AttnArgs& a, hipStream_t st) {
-  const AttnMode m = attn_mode<D>(a);
+  const AttnMode m = attn_mode(a.s, a.hl * a.b, a.causal != 0, D);
   if constexpr (D <= 128)
     if (m == ATTN_PAIR) return launch_dq_m<D, DROP, ATTN_PAIR>(a, st);
   return m == ATTN_SPLIT ? launch_dq_m<D, DROP, ATTN_SPLIT>(a, st) : launch_dq_m<D, DROP, ATTN_WIDE>(a, st);
@@ -873,9 +859,8 @@ static hipError_t launch_dkv(const AttnArgs& a, hipStream_t st) {
 template <int D, bool DROP>
 static hipError_t launch_bwd_dd(const AttnArgs& a, hipStream_t st) {
   if (hipError_t e = launch_dq_dd<D, DROP>(a, st); e != hipSuccess) return e;
-  // 64-key workgroups where 128-key ones would leave half of the compute units idle (d = 192 needs one wave per SIMD)
   if constexpr (D <= 128)
-    if (2L * dkv_dsplit<D>() * ((a.s + 127) / 128) * a.hl * a.b <= gemm_cu_count()) return launch_dkv<D, DROP, true>(a, st);
+    if (attn_dkv_split(a.s, a.hl * a.b, a.causal != 0, D, dkv_dsplit<D>())) return launch_dkv<D, DROP, true>(a, st);
   return launch_dkv<D, DROP, false>(a, st);
 }
 

@@ -1,0 +1,44 @@
+// How the bf16 attention kernels divide a launch into workgroups (the kernels: attention_bf16.hip).  Host arithmetic only.
+#pragma once
+
+namespace mlm {
+
+int gemm_cu_count();                    // compute units of the current device, at most 256
+
+// Forward and dQ: WIDE and PAIR take 128 rows of one (batch, head) pair per workgroup, SPLIT 64.
+enum AttnMode { ATTN_WIDE, ATTN_PAIR, ATTN_SPLIT };
+
+// All workgroups of a (batch, head) pair run on one XCD (an eighth of the compute units), and the eight XCDs take the pairs in
+// turn: what decides is the number of 128-row workgroups of the busiest XCD next to their number overall.  Measured as WIDE,
+// PAIR, SPLIT (us, forward + dQ, compute units 256, s x pairs):
+//   SPLIT while its workgroups, twice as many, fit the compute units overall and on the XCD; causal ones, of which the short
+//   ones make room for the long ones, up to two per unit there.  d = 96: 1024 x 8 causal 47, 44, 34; 3072 x 4 causal 120, 103,
+//   77, but full 125, 110, 145; 4096 x 4 full 170, 152, 197; 768 x 20 full 39, 39, 57.  d = 128: 8192 x 1 causal 434, 328, 458.
+//   PAIR up to one workgroup per compute unit: a causal chain of steps halved.  And beyond, causal, while the busiest XCD has
+//   one or two pairs and two workgroups per unit, or three pairs and one and a half: its longest chain alone is then the
+//   launch's time.  d = 96: 4096 x 16 causal 243, 180; 2048 x 24 causal 126, 107; 8192 x 8 causal 381, 324.
+//   WIDE for the rest.  d = 96: 1024 x 64 causal 76, 91; 2048 x 32 causal 132, 135; 4096 x 20 causal 270, 300; full 1024 x 128
+//   166, 193, 8192 x 8 570, 586.
+// (PAIR does not exist for d = 192: WIDE in its place.)
+inline AttnMode attn_mode(int s, int pairs, bool causal, int d) {
+  const long cus = gemm_cu_count(), xcd_cus = cus / 8, blocks = (s + 127) / 128, wgs = blocks * pairs;
+  const long xcd_pairs = (pairs + 7) / 8, xcd_wgs = xcd_pairs * blocks;
+  if (2 * wgs <= cus && 2 * xcd_wgs <= (causal ? 2 : 1) * xcd_cus) return ATTN_SPLIT;
+  if (d > 128) return ATTN_WIDE;
+  if (wgs <= cus) return ATTN_PAIR;
+  if (causal && (xcd_pairs <= 2 ? xcd_wgs <= 2 * xcd_cus : xcd_pairs == 3 && 2 * xcd_wgs <= 3 * xcd_cus)) return ATTN_PAIR;
+  return ATTN_WIDE;
+}
+
+// dK / dV: 64-key workgroups (else 128-key ones) under the same condition; `parts` workgroups share a key block (large heads).
+// us, 128 / 64 keys: d = 96 1024 x 8 causal 27.6 / 19.4, 3072 x 4 causal 69 / 47, but full 74 / 91; 768 x 20 full 24 / 33; d = 64
+// 512 x 16 causal 14.3 / 10.2; d = 128 2048 x 1 causal 50 / 45, full 53 / 71, 4096 x 1 causal 112 / 147.  (d = 192 needs one
+// wave per SIMD.)
+inline bool attn_dkv_split(int s, int pairs, bool causal, int d, int parts) {
+  if (d > 128) return false;
+  const long cus = gemm_cu_count(), wgs = (long)parts * ((s + 127) / 128) * pairs;
+  const long xcd_wgs = (long)parts * ((s + 127) / 128) * ((pairs + 7) / 8);
+  return 2 * wgs <= cus && 2 * xcd_wgs <= (causal ? 2 : 1) * (cus / 8);
+}
+
+}  // namespace mlm
