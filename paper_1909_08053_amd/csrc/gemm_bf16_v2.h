@@ -187,11 +187,11 @@ struct V2Plan {
 // to the eight XCDs in turn and the tile row is the fast index, so with an odd number of tile rows every XCD works on all of
 // them, and with few rows on many columns.  128 against 256 and 192 wide, weight-gradient layout, 8192 deep: 1920 x 12800 (15
 // tile rows) 591 / 347 / 419 us, 8064 x 1024 (63 rows) 173 / 153 / 137, 1024 x 7680 (8 rows) 169 / 155 / 138; but 2048 x 3840
-// (16 rows) 126 / 154 / 136.  With the row count left out of the model, 172 of 1985 shapes took the small tile where the
+// (16 rows) 126 / 154 / 136, and 3840 x 1920 (30 rows) 152 / 139 with a k-split of the large tile's 120.  With the row count left out of the model, 172 of 1985 shapes took the small tile where the
 // large one it would take otherwise is 3 .. 76 % faster; with it none does by more than 3 %.
-inline double v2_small_slice(int tiles_m, int tiles) {
+inline double v2_small_slice(int tiles_m) {
   if (tiles_m % 2 || tiles_m <= 10) return 0.72;
-  return tiles > 2 * gemm_cu_count() ? 0.46 : 0.43;
+  return 0.46;
 }
 inline double v2_tile_cost(int bn, int nk, bool alone, double small_slice) {
   if (bn == V2_SMALL) return alone ? 4.5 + 0.24 * nk : 6.0 + small_slice * nk;
@@ -215,7 +215,7 @@ inline V2Plan v2_plan(int M, int N, int K, bool allow_split, int bn = V2_B) {
   const int nk = v2_slices(K);
   int split = 1;
   const bool alone = tiles <= cus;
-  const double ss = v2_small_slice(p.tiles_m, tiles);
+  const double ss = v2_small_slice(p.tiles_m);
   double tail = rem ? v2_tile_cost(bn, nk, alone, ss) : 0.0;   // unsplit tail round
   if (allow_split && rem != 0 && rem * 2 <= cus) {
     int smax = cus / rem;
@@ -600,7 +600,7 @@ inline double v2_group_cost(const GemmArgs* probs, int n, int bn) {
   int tiles = 0;
   for (int q = 0; q < n; ++q) tiles += v2_tiles(probs[q], bm, bn);
   double ss = 0.0;                     // mean over the tiles
-  for (int q = 0; q < n; ++q) ss += v2_small_slice((probs[q].M + bm - 1) / bm, tiles) * v2_tiles(probs[q], bm, bn) / tiles;
+  for (int q = 0; q < n; ++q) ss += v2_small_slice((probs[q].M + bm - 1) / bm) * v2_tiles(probs[q], bm, bn) / tiles;
   const int nk = v2_slices(probs[0].K), rem = tiles % per_round;
   return (tiles / per_round) * v2_tile_cost(bn, nk, false, ss) + (rem ? v2_tile_cost(bn, nk, rem <= cus, ss) : 0.0);
 }

@@ -27,18 +27,21 @@ int main(int argc, char** argv) {          // "layout M N K" -> tile width; "g T
       printf("%d\\n", v2_group_cost(a, 4, V2_SMALL) < v2_group_cost(a, 4, V2_B) ? V2_SMALL : V2_B);
     } else if (!strcmp(kind, "fwd")) printf("%d\\n", v2_pick_bn<true, false, EPI_STORE>(x, y, z, false));
     else if (!strcmp(kind, "dgrad")) printf("%d\\n", v2_pick_bn<true, true, EPI_STORE>(x, y, z, false));
-    else printf("%d\\n", v2_pick_bn<false, false, EPI_STORE>(x, y, z, false));
+    else printf("%d\\n", v2_pick_bn<false, false, EPI_STORE>(x, y, z, kind[5] == 's'));   // "wgrads": with a k-split
   }
   return 0;
 }
 """
 
-# layout, M, N, K and the microseconds measured for the 128-, 192- and 256-wide tile
+# layout, M, N, K and the microseconds measured for the 128-, 192- and 256-wide tile (192 with a k-split not measured apart:
+# the 128-wide tile's)
 MEASURED = [
     ("wgrad", 1920, 25600, 8192, 1321, 743, 719), ("fwd", 1920, 12800, 6144, 410, 314, 259), ("wgrad", 3200, 7680, 8192, 599, 421, 341),
     ("wgrad", 1920, 12800, 8192, 591, 419, 347), ("fwd", 3200, 7680, 6144, 406, 313, 256), ("dgrad", 8064, 1024, 6144, 125, 88, 112),
     ("fwd", 8064, 1024, 1536, 37, 31, 36), ("fwd", 768, 10240, 6144, 117, 96, 108), ("dgrad", 1024, 7680, 6144, 109, 98, 109),
     ("wgrad", 8064, 1024, 8192, 173, 137, 153), ("fwd", 896, 7552, 6144, 130, 101, 115), ("wgrad", 3968, 2048, 8192, 191, 132, 151),
+    # with a k-split and its fix-up (256 wide: 240 half-length pieces)
+    ("wgrads", 3840, 1920, 8192, 152, 152, 139), ("wgrads", 1920, 3840, 8192, 162, 162, 142),
     # where the small tile is the better one it stays
     ("wgrad", 2048, 3840, 8192, 126, 136, 154), ("wgrad", 2560, 2560, 4096, 57, 68, 81), ("wgrad", 960, 1920, 8192, 65, 115, 140),
     ("fwd", 4096, 1920, 2560, 39, 42, 49), ("dgrad", 2048, 3072, 1024, 18.9, 20.4, 22.7),
