@@ -66,7 +66,7 @@ __global__ __launch_bounds__(256) void embed_scatter_kernel(int T, int nslice, c
 // Gather and its gradient work on tiles of 64 sorted positions x 64 rows of E_r, transposed through LDS: on the E_r side a
 // lane is a position, so a wave reads (or updates) 64 nearby columns of one row, and on the token side 16-byte vectors (or
 // lanes) run along the row of the partial (or dz0).  With a wave per position and row group, 98304 workgroups at 8192 tokens
-// x 3072 were bound by their launches and by 2-byte stores: 53 us forward and 65 us backward on one shard of eight, 26 and 39 now.
+// x 3072 were bound by their launches and by 2-byte stores: 53 us forward and 65 us backward on one shard of eight, 26 and 23 now.
 constexpr int kEmbTile = 64;
 // (row stride of the LDS tile: an odd number of 32-bit words)
 template <typename T> constexpr int emb_stride() { return kEmbTile + 4 / (int)sizeof(T); }
@@ -116,17 +116,21 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(int Tn, int H, int Vl, i
 }
 
 // dE_r[:, loc] += the sum of the rows of dz0 whose token has local id loc, in token order (fp32).  The wave whose 16
-// positions hold the head of a run of equal ids sums all of it, the part behind its positions one row at a time.
-// Element-sized accesses to dE_r: neighbouring columns belong to other lanes and workgroups.
-template <typename T>
-__global__ __launch_bounds__(256) void embed_bwd_kernel(int Tn, int H, int Vl, int v0, const int32_t* __restrict__ ids,
+// positions hold the head of a run of equal ids sums all of it, sixteen rows at a time: their loads are in flight together (one
+// row after the other, three dependent trips to memory each, 8192 equal tokens took 4.4 ms).
+// Element-sized accesses to dE_r: neighbouring columns belong to other lanes and workgroups.  NWV waves = 16 NWV positions per
+// workgroup: four, or one where that leaves compute units idle -- every lane of an access to dE_r may touch another line, and
+// the lines of a few workgroups queue on their compute units (200 tokens x 320, 1024 columns, 7.9 us, 6.1 with one).
+template <typename T, int NWV>
+__global__ __launch_bounds__(64 * NWV) void embed_bwd_kernel(int Tn, int H, int Vl, int v0, const int32_t* __restrict__ ids,
                                                         const int32_t* __restrict__ perm, const T* __restrict__ dz,
                                                         T* __restrict__ dE) {
-  __shared__ float tile[kEmbTile * (kEmbTile + 1)];
-  __shared__ int stok[kEmbTile], sloc[kEmbTile + 1];  // sloc[i + 1]: position k0 + i; sloc[0]: the one before
+  constexpr int NP = 16 * NWV;                        // positions
+  __shared__ float tile[NP * (kEmbTile + 1)];
+  __shared__ int stok[NP + 1], sloc[NP + 2];          // sloc[i + 1]: position k0 + i, from the one before the tile to the one behind
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int k0 = blockIdx.x * kEmbTile, h0 = blockIdx.y * kEmbTile, h = h0 + lane, hc = min(h, H - 1);
-  if (threadIdx.x <= kEmbTile) {
+  const int k0 = blockIdx.x * NP, h0 = blockIdx.y * kEmbTile, h = h0 + lane, hc = min(h, H - 1);
+  if (threadIdx.x <= NP + 1) {
     const int k = k0 + (int)threadIdx.x - 1;
     const int t = k >= 0 && k < Tn ? perm[k] : -1, loc = t >= 0 ? ids[t] - v0 : -1;
     sloc[threadIdx.x] = loc >= 0 && loc < Vl ? loc : -1;
@@ -134,19 +138,18 @@ __global__ __launch_bounds__(256) void embed_bwd_kernel(int Tn, int H, int Vl, i
   }
   __syncthreads();
   if (sloc[1] < 0) return;                            // sorted: the whole tile is outside the shard (block-uniform)
-  const int p0 = wave * 16;
+  const int p0 = __builtin_amdgcn_readfirstlane(wave) * 16;
+  // lane i: local id of position p0 + i - 1 and token of position p0 + i; read back as scalars
+  const int lloc = sloc[min(p0 + lane, NP + 1)], ltok = max(stok[min(p0 + lane, NP)], 0);
   float v[16];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int t = stok[p0 + i];
-    v[i] = sloc[p0 + i + 1] >= 0 ? to_f32(dz[(size_t)t * H + hc]) : 0.f;
-  }
+  for (int i = 0; i < 16; ++i) v[i] = to_f32(dz[(size_t)__builtin_amdgcn_readlane(ltok, i) * H + hc]);
   float acc = 0.f;
-  int head = -1;                                      // position (in the tile) of the run being summed; wave-uniform
+  int head = -1;                                      // position (in the tile) of the run being summed
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
-    const int loc = sloc[p0 + i + 1];
-    if (loc < 0 || loc != sloc[p0 + i]) {             // a new run, or the end of the shard's tokens
+    const int prev = __builtin_amdgcn_readlane(lloc, i), loc = __builtin_amdgcn_readlane(lloc, i + 1);
+    if (loc < 0 || loc != prev) {                     // a new run, or the end of the shard's tokens
       if (head >= 0) tile[head * (kEmbTile + 1) + lane] = acc;
       head = loc >= 0 ? p0 + i : -1;
       acc = v[i];
@@ -155,24 +158,35 @@ __global__ __launch_bounds__(256) void embed_bwd_kernel(int Tn, int H, int Vl, i
     }
   }
   if (head >= 0) {
-    const int loc = sloc[head + 1];
-    for (int kk = k0 + p0 + 16; kk < Tn; ++kk) {
-      const int t = perm[kk];
-      if (ids[t] - v0 != loc) break;                  // end of the run (wave-uniform)
-      acc += to_f32(dz[(size_t)t * H + hc]);
+    const int loc = __builtin_amdgcn_readlane(lloc, 16);
+    // (most runs end inside the wave's positions)
+    for (int kk = __builtin_amdgcn_readlane(lloc, 17) == loc ? k0 + p0 + 16 : Tn; kk < Tn; kk += 16) {
+      const int k = kk + (lane & 15), tk = k < Tn ? perm[k] : -1;
+      const bool same = tk >= 0 && ids[tk] - v0 == loc;
+      // positions of the run among these sixteen: sorted, so the first n (wave-uniform)
+      const int n = __builtin_ctz(~((uint32_t)__builtin_amdgcn_ballot_w64(same) & 0xFFFFu));
+      if (n == 0) break;
+      const int first = __builtin_amdgcn_readfirstlane(tk);      // (before the selection: every lane takes part)
+      const int tok = same ? tk : first;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) v[i] = to_f32(dz[(size_t)__builtin_amdgcn_readlane(tok, i) * H + hc]);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc = i < n ? acc + v[i] : acc;
+      if (n < 16) break;
     }
     tile[head * (kEmbTile + 1) + lane] = acc;
   }
   __syncthreads();
-  const int loc = sloc[lane + 1];
-  if (loc < 0 || loc == sloc[lane]) return;           // outside, or not the head of its run
+  const int p = threadIdx.x % NP, r0 = threadIdx.x / NP * 16;       // this lane's position, the first of its rows
+  const int loc = sloc[p + 1];
+  if (loc < 0 || loc == sloc[p]) return;              // outside, or not the head of its run
+  T was[16];                                          // (all read before the first is written)
+#pragma unroll
+  for (int i = 0; i < 16; ++i) was[i] = dE[(size_t)min(h0 + r0 + i, H - 1) * Vl + loc];
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
-    const int r = wave * 16 + i;
-    if (h0 + r < H) {
-      T* p = dE + (size_t)(h0 + r) * Vl + loc;
-      *p = from_f32<T>(to_f32(*p) + tile[lane * (kEmbTile + 1) + r]);
-    }
+    const int r = r0 + i;
+    if (h0 + r < H) dE[(size_t)(h0 + r) * Vl + loc] = from_f32<T>(to_f32(was[i]) + tile[p * (kEmbTile + 1) + r]);
   }
 }
 
@@ -237,16 +251,21 @@ hipError_t launch_embed_fwd(int dtype, int T, int H, int Vl, int v0, const int32
   return hipGetLastError();
 }
 
+template <typename T>
+static hipError_t embed_bwd_dispatch(int Tn, int H, int Vl, int v0, const int32_t* ids, const int32_t* perm, const T* dz, T* dE,
+                                     hipStream_t st) {
+  const int rows = (H + kEmbTile - 1) / kEmbTile;
+  if ((Tn + 63) / 64 * rows < gemm_cu_count())
+    hipLaunchKernelGGL((embed_bwd_kernel<T, 1>), dim3((Tn + 15) / 16, rows), dim3(64), 0, st, Tn, H, Vl, v0, ids, perm, dz, dE);
+  else
+    hipLaunchKernelGGL((embed_bwd_kernel<T, 4>), dim3((Tn + 63) / 64, rows), dim3(256), 0, st, Tn, H, Vl, v0, ids, perm, dz, dE);
+  return hipGetLastError();
+}
+
 hipError_t launch_embed_bwd(int dtype, int T, int H, int Vl, int v0, const int32_t* ids, const int32_t* perm,
                             const void* dz, void* dE, hipStream_t st) {
-  dim3 grid((T + kEmbTile - 1) / kEmbTile, (H + kEmbTile - 1) / kEmbTile);
-  if (dtype == MLM_BF16)
-    hipLaunchKernelGGL((embed_bwd_kernel<bf16>), grid, dim3(256), 0, st, T, H, Vl, v0, ids, perm, (const bf16*)dz,
-                       (bf16*)dE);
-  else
-    hipLaunchKernelGGL((embed_bwd_kernel<float>), grid, dim3(256), 0, st, T, H, Vl, v0, ids, perm, (const float*)dz,
-                       (float*)dE);
-  return hipGetLastError();
+  return dtype == MLM_BF16 ? embed_bwd_dispatch<bf16>(T, H, Vl, v0, ids, perm, (const bf16*)dz, (bf16*)dE, st)
+                           : embed_bwd_dispatch<float>(T, H, Vl, v0, ids, perm, (const float*)dz, (float*)dE, st);
 }
 
 hipError_t launch_embed_bwd_replicated(int dtype, int b, int s, int H, const void* dx0, void* dz0, void* dpos,

@@ -11,7 +11,9 @@ DEV = "cuda:0"
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 @pytest.mark.parametrize("T,H,Vl,distinct", [(1, 16, 8, 8), (64, 64, 64, 1), (257, 80, 40, 2),
-                                                (1000, 144, 512, 1024), (700, 64, 24, 30)])
+                                                (1000, 144, 512, 1024), (700, 64, 24, 30),
+                                                # gradient with four waves per workgroup: 65 x 17 and 47 x 8 tiles
+                                                (4100, 1040, 64, 3), (3000, 512, 704, 1400)])
 def test_embedding_tiles(dtype, T, H, Vl, distinct):
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     p, r = 2, 1                                       # the shard owns ids [Vl, 2 Vl)
