@@ -238,7 +238,7 @@ def main():
             traffic = None
     roofline = {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                 "frac": achieved / PEAK_BF16_TFLOPS, "traffic": traffic, "traffic_source": traffic_src,
-                "kernel": "gemm_bf16_v2_kernel<true,false,EPI_CE,256,false,false> (logits GEMM + cross-entropy partials), timed as "
+                "kernel": "gemm_bf16_v2_kernel<true,false,EPI_CE,256,0,false> (logits GEMM + cross-entropy partials), timed as "
                           "the whole mlm_vocab_ce_shard_fwd call: + gemm_v2_fixup_kernel<EPI_CE> + ce_tile_merge_kernel",
                 "kernel_ms": k_ms, "launches_in_bracket": 3, "flops_per_launch": logits_flops}
 

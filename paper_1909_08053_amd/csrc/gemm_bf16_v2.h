@@ -16,7 +16,8 @@
 //     (normally distributed) operands, where the chip's power limit sets the clock: 2.04 PFLOP/s against 1.77 with the
 //     matrix pipe alone, 1.60 against 1.45 with this loop's fragment reads and copies around it.
 // k is walked in pairs of 32-deep slices.  K need not be a multiple of anything: the 16-byte units of the last pair that
-// lie past K are fetched from sixteen zero bytes (one compare and select per copy, compiled in for such K only).
+// lie past K are fetched from sixteen zero bytes (one compare and select per copy, compiled in for such K only), or, K being
+// an odd multiple of 32, the last pair starts one slice early and multiplies that slice as zeros.
 //
 // Tail split: when the tile count does not fill a whole number of rounds of the 256 CUs, the tiles of the last
 // partial round are split along k into f pieces (f = floor(256 / remainder)); each piece writes an fp32 partial
@@ -43,6 +44,13 @@ template <int BN> constexpr int v2_bm() { return BN == V2_SMALL ? V2_SMALL : V2_
 template <int BN, bool DEEP> constexpr int v2_waves_m() { return BN == 192 || DEEP ? 4 : 2; }
 template <int BN, bool DEEP> constexpr int v2_nw() { return BN == V2_SMALL && !DEEP ? 4 : 8; }
 inline int v2_slices(int K) { return 2 * ((K + 2 * V2_BK - 1) / (2 * V2_BK)); }   // 32-deep slices walked: whole pairs
+// How K ends: KE_PAIR on a whole pair of slices; KE_SLICE on the first slice of a pair (K an odd multiple of 32; the large tiles'
+// kernels: with KE_ANY they are 4-8 % slower at 8192 x 3072 x 1568, and KE_PAIR's with this form's arithmetic 0.7-1 %); KE_ANY.
+enum { KE_PAIR, KE_SLICE, KE_ANY };
+template <int BN> int v2_k_end(int K) {
+  if (K % (2 * V2_BK) == 0) return KE_PAIR;
+  return BN != V2_SMALL && K % V2_BK == 0 && K >= 2 * V2_BK ? KE_SLICE : KE_ANY;
+}
 template <bool A_KC, bool B_KC, bool DEEP> constexpr int v2_stages() { return DEEP && (A_KC || B_KC) ? 8 : 4; }
 // A's ring, then B's ring: 128 KB for a 256 x 256 tile, 64 KB (128 KB DEEP) for a 128 x 128 one
 constexpr size_t v2_ring_bytes(int bm, int bn, int stages) { return (size_t)stages * V2_BK * 2 * (bm + bn); }
@@ -93,9 +101,9 @@ __device__ __forceinline__ int v2_kc_swizzle(int row) { return (row >> 1) & 7; }
 //    slice by slice, costs twice the cache-line requests and was measured 40 % slower on the copy side).  A pair
 //    takes 2 QPW copies per wave and is fetched once every two slices.
 //  * operand contiguous along m / n (MN): a slice is [32 k][256 rows] = 512 bytes per k, QPW copies per slice.
-// RAG (K is no multiple of 64): units past K are read from v2_zero16.  A template parameter: the compare and select per
-// copy cost 2 % of a large GEMM.
-template <bool KC, int NP_, bool RAG, int ROWS>
+// ANY_K (KE_ANY): units past K are read from v2_zero16.  A template parameter: the compare and select per copy cost 2-4 % of a
+// large GEMM.
+template <bool KC, int NP_, bool ANY_K, int ROWS>
 struct V2Src {
   static constexpr int NP = NP_;       // KC: 1-KB copies per wave and PAIR (rows / (8 waves)); MN: per wave and slice
   // MN: a slice is ROWS / 16 one-KB copies; where that is no multiple of the wave count (192 rows: 12 copies, 8
@@ -133,7 +141,7 @@ struct V2Src {
   // relative to k_begin; wave_u: wave index as a uniform (SGPR) value
   __device__ __forceinline__ void issue_one(uint32_t dst, int wave_u, int ks, int q) const {
     const bf16* src = p[q] + (ptrdiff_t)ks * (ptrdiff_t)step;
-    if (RAG) src = ks * V2_BK + kofs[q] < kleft ? src : reinterpret_cast<const bf16*>(&v2_zero16);
+    if (ANY_K) src = ks * V2_BK + kofs[q] < kleft ? src : reinterpret_cast<const bf16*>(&v2_zero16);
     dma16(src, dst + min(wave_u * NP + q, LAST) * 1024);
   }
   __device__ __forceinline__ void issue(uint32_t dst, int wave_u, int ks) const {
@@ -244,7 +252,7 @@ inline V2Plan v2_plan(int M, int N, int K, bool allow_split, int bn = V2_B) {
 // Library call, forward layout, best large tile against it: 1024 x 1920 x 960 18.7 -> 10.6 us, 1024 x 3840 x 1920
 // 33.7 -> 21.2, 3000 x 1152 x 1536 27.5 -> 16.7, 4096 x 2048 x 768 20.3 -> 16.9; 4096 x 4096 x 768 stays (27 against 31).
 // Grouped weight gradients of 228 such tiles (8192 tokens, 1536 wide, split eight ways): 152 us in eight launches -> 81.
-template <bool A_KC, bool B_KC, int EPI, int BN, bool RAG, bool DEEP>
+template <bool A_KC, bool B_KC, int EPI, int BN, int KE, bool DEEP>
 __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Plan& plan, float* splitk_ws, int pid,
                                                   unsigned char* lds_raw) {
   static_assert(BN == V2_B || BN == 192 || BN == V2_SMALL, "tile widths");
@@ -276,8 +284,8 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
   const int kt_end = 2 * (int)((long)np_total * (piece + 1) / npieces);
   const int nk = kt_end - kt_begin;                  // even, >= 2
 
-  V2Src<A_KC, NPA, RAG, BM> sa;
-  V2Src<B_KC, NPB, RAG, BN> sb;
+  V2Src<A_KC, NPA, KE == KE_ANY, BM> sa;
+  V2Src<B_KC, NPB, KE == KE_ANY, BN> sb;
   sa.init((const bf16*)a.A, a.lda, m0, a.M, kt_begin * V2_BK, a.K, wave, lane);
   sb.init((const bf16*)a.B, a.ldb, n0, a.N, kt_begin * V2_BK, a.K, wave, lane);
 
@@ -290,14 +298,20 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
   // stage nobody reads (keeps the vmcnt bookkeeping and the instruction stream free of tail cases).  Issue order of
   // the initial fill = the order the steady state would have produced: pair 0, slices 0 1, pair 1, slices 2 3.
   const int last_pair = nk / 2 - 1, last_slice = nk - 1;
+  // KE_SLICE: the last pair starts one slice early, and its first slice, which the pair
+  // before it has multiplied already, is multiplied as zeros.  shift = 1 for the piece that holds that pair.
+  const int shift = KE == KE_SLICE && kt_end * V2_BK > a.K ? 1 : 0;
+  // first 32-deep slice of pair pr / memory slice of walked slice ks
+  auto pair_of = [&](int pr) { return 2 * pr - (pr == last_pair ? shift : 0); };
+  auto slice_of = [&](int ks) { return ks - (ks >= nk - 2 ? shift : 0); };
 #pragma unroll
   for (int h = 0; h < ST / 2; ++h) {
-    if (A_KC) sa.issue(ldsA + h * 2 * OPB_A, wave_u, 2 * min(h, last_pair));
-    if (B_KC) sb.issue(ldsB + h * 2 * OPB_B, wave_u, 2 * min(h, last_pair));
+    if (A_KC) sa.issue(ldsA + h * 2 * OPB_A, wave_u, pair_of(min(h, last_pair)));
+    if (B_KC) sb.issue(ldsB + h * 2 * OPB_B, wave_u, pair_of(min(h, last_pair)));
 #pragma unroll
     for (int s = 2 * h; s < 2 * h + 2; ++s) {
-      if (!A_KC) sa.issue(ldsA + s * OPB_A, wave_u, min(s, last_slice));
-      if (!B_KC) sb.issue(ldsB + s * OPB_B, wave_u, min(s, last_slice));
+      if (!A_KC) sa.issue(ldsA + s * OPB_A, wave_u, slice_of(min(s, last_slice)));
+      if (!B_KC) sb.issue(ldsB + s * OPB_B, wave_u, slice_of(min(s, last_slice)));
     }
   }
   // The operand registers of what is multiplied next are read from LDS while the matrix cores work.  The slice hand-over sits inside
@@ -350,10 +364,10 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
     const int stage = kt & (ST - 1), nstage = (kt + 1) & (ST - 1);
     constexpr int NC = PAR == 0 ? EV : OD;                 // copies to issue in this slice
     constexpr int NAFTER = NMF - HO - 1;                   // MFMAs after the hand-over
-    const int pair_idx = 2 * min((kt + ST - 1) >> 1, last_pair);   // PAR == 1: the pair ST / 2 ahead of this slice's pair
+    const int pair_idx = pair_of(min((kt + ST - 1) >> 1, last_pair));   // PAR == 1: the pair ST / 2 ahead of this slice's pair
     const uint32_t pair_sel = (uint32_t)(((kt + ST - 1) >> 1) & (ST / 2 - 1));
     const uint32_t pair_off_a = pair_sel * (2 * OPB_A), pair_off_b = pair_sel * (2 * OPB_B);
-    const int slice_idx = min(kt + ST, last_slice);
+    const int slice_idx = slice_of(min(kt + ST, last_slice));
     const uint32_t slice_off_a = (uint32_t)stage * OPB_A, slice_off_b = (uint32_t)stage * OPB_B;
 #pragma unroll
     for (int idx = 0; idx < NMF; ++idx) {
@@ -406,6 +420,13 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
   // (no slice is peeled off: with a second copy of the two bodies the register allocator rotates accumulators through the
   // fragments' registers, and the loop then holds 7-16 wait states for the fragment reads that overwrite them)
   for (int kt = 0; kt < nk; kt += 2) {
+    if (KE == KE_SLICE && shift && kt == nk - 2) {
+      const bf16x8 zero = {};
+#pragma unroll
+      for (int j = 0; j < NA; ++j) fa[j] = zero;
+#pragma unroll
+      for (int i = 0; i < NB; ++i) fb[0][i] = zero;
+    }
     slice(c0_t{}, kt);
     slice(c1_t{}, kt + 1);
   }
@@ -430,10 +451,10 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
 }
 
 // (two workgroups of the small tile fit a compute unit)
-template <bool A_KC, bool B_KC, int EPI, int BN, bool RAG, bool DEEP>
+template <bool A_KC, bool B_KC, int EPI, int BN, int KE, bool DEEP>
 __global__ __launch_bounds__((v2_nw<BN, DEEP>() * 64), 2) void gemm_bf16_v2_kernel(GemmArgs a, V2Plan plan, float* splitk_ws) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  gemm_v2_work_item<A_KC, B_KC, EPI, BN, RAG, DEEP>(a, plan, splitk_ws, blockIdx.x, lds_raw);
+  gemm_v2_work_item<A_KC, B_KC, EPI, BN, KE, DEEP>(a, plan, splitk_ws, blockIdx.x, lds_raw);
 }
 
 // Several independent GEMMs of one operand layout in ONE launch (plain-store epilogue, no k-split): the tiles of
@@ -448,7 +469,7 @@ struct GemmGroup {
   V2Plan plan[kMaxGroup];
 };
 
-template <bool A_KC, bool B_KC, int BN, bool RAG, bool DEEP>
+template <bool A_KC, bool B_KC, int BN, int KE, bool DEEP>
 __global__ __launch_bounds__((v2_nw<BN, DEEP>() * 64), 2) void gemm_bf16_v2_group_kernel(GemmGroup g) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   const int pid = blockIdx.x;
@@ -462,7 +483,7 @@ __global__ __launch_bounds__((v2_nw<BN, DEEP>() * 64), 2) void gemm_bf16_v2_grou
 #pragma unroll
   for (int i = 1; i < kMaxGroup; ++i)
     if (q == i) { a = g.args[i]; plan = g.plan[i]; first = g.tile_begin[i]; }
-  gemm_v2_work_item<A_KC, B_KC, EPI_STORE, BN, RAG, DEEP>(a, plan, nullptr, pid - first, lds_raw);
+  gemm_v2_work_item<A_KC, B_KC, EPI_STORE, BN, KE, DEEP>(a, plan, nullptr, pid - first, lds_raw);
 }
 
 // Tail tiles: sum the k-pieces in piece order (deterministic) and apply the epilogue to the fp32 sums.  A wave owns
@@ -572,9 +593,9 @@ template <bool A_KC, bool B_KC, int BN, bool DEEP> constexpr size_t v2_lds_bytes
   return kLds;
 }
 
-template <bool A_KC, bool B_KC, int EPI, int BN, bool RAG, bool DEEP = false>
-hipError_t launch_gemm_bf16_v2_bn(const GemmArgs& a, float* splitk_ws, hipStream_t st) {
-  auto kern = gemm_bf16_v2_kernel<A_KC, B_KC, EPI, BN, RAG, DEEP>;
+template <bool A_KC, bool B_KC, int EPI, int BN, int KE, bool DEEP>
+hipError_t launch_gemm_bf16_v2_ke(const GemmArgs& a, float* splitk_ws, hipStream_t st) {
+  auto kern = gemm_bf16_v2_kernel<A_KC, B_KC, EPI, BN, KE, DEEP>;
   constexpr size_t kLds = v2_lds_bytes<A_KC, B_KC, BN, DEEP>();
   static LdsAttrOnce attr;         // per instantiation and device
   if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
@@ -605,9 +626,9 @@ inline double v2_group_cost(const GemmArgs* probs, int n, int bn) {
   return (tiles / per_round) * v2_tile_cost(bn, nk, false, ss) + (rem ? v2_tile_cost(bn, nk, rem <= cus, ss) : 0.0);
 }
 
-template <bool A_KC, bool B_KC, int BN, bool RAG, bool DEEP>
-hipError_t launch_gemm_bf16_v2_group(const GemmArgs* probs, int n, hipStream_t st) {
-  auto kern = gemm_bf16_v2_group_kernel<A_KC, B_KC, BN, RAG, DEEP>;
+template <bool A_KC, bool B_KC, int BN, int KE, bool DEEP>
+hipError_t launch_gemm_bf16_v2_group_ke(const GemmArgs* probs, int n, hipStream_t st) {
+  auto kern = gemm_bf16_v2_group_kernel<A_KC, B_KC, BN, KE, DEEP>;
   constexpr size_t kLds = v2_lds_bytes<A_KC, B_KC, BN, DEEP>();
   static LdsAttrOnce attr;
   if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
@@ -624,6 +645,16 @@ hipError_t launch_gemm_bf16_v2_group(const GemmArgs* probs, int n, hipStream_t s
   for (int q = n; q <= kMaxGroup; ++q) g.tile_begin[q] = total;
   hipLaunchKernelGGL(kern, dim3(total), dim3(v2_nw<BN, DEEP>() * 64), kLds, st, g);
   return hipGetLastError();
+}
+
+template <bool A_KC, bool B_KC, int BN, bool DEEP>
+hipError_t launch_gemm_bf16_v2_group(const GemmArgs* probs, int n, hipStream_t st) {
+  switch (v2_k_end<BN>(probs[0].K)) {
+    case KE_PAIR: return launch_gemm_bf16_v2_group_ke<A_KC, B_KC, BN, KE_PAIR, DEEP>(probs, n, st);
+    case KE_SLICE:
+      if constexpr (BN != V2_SMALL) return launch_gemm_bf16_v2_group_ke<A_KC, B_KC, BN, KE_SLICE, DEEP>(probs, n, st);
+    default: return launch_gemm_bf16_v2_group_ke<A_KC, B_KC, BN, KE_ANY, DEEP>(probs, n, st);
+  }
 }
 
 int gemm_v2_forced_bn();                    // MLM_GEMM_BN=128|192|256 forces a tile width where both exist, else 0
@@ -649,23 +680,27 @@ int v2_pick_bn(int M, int N, int K, bool allow_split) {
   return best;
 }
 
-template <bool A_KC, bool B_KC, int EPI, bool RAG>
-hipError_t launch_gemm_bf16_v2_rag(const GemmArgs& a, float* splitk_ws, hipStream_t st) {
-  const int bn = v2_pick_bn<A_KC, B_KC, EPI>(a.M, a.N, a.K, splitk_ws != nullptr);
-  if constexpr (v2_has_narrow<A_KC, B_KC, EPI>())
-    if (bn == 192) return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, 192, RAG>(a, splitk_ws, st);
-  if constexpr (v2_has_small<EPI>())
-    if (bn == V2_SMALL)
-      return v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, V2_SMALL).deep()
-                 ? launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_SMALL, RAG, true>(a, splitk_ws, st)
-                 : launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_SMALL, RAG>(a, splitk_ws, st);
-  return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_B, RAG>(a, splitk_ws, st);
+template <bool A_KC, bool B_KC, int EPI, int BN, bool DEEP = false>
+hipError_t launch_gemm_bf16_v2_bn(const GemmArgs& a, float* splitk_ws, hipStream_t st) {
+  switch (v2_k_end<BN>(a.K)) {
+    case KE_PAIR: return launch_gemm_bf16_v2_ke<A_KC, B_KC, EPI, BN, KE_PAIR, DEEP>(a, splitk_ws, st);
+    case KE_SLICE:
+      if constexpr (BN != V2_SMALL) return launch_gemm_bf16_v2_ke<A_KC, B_KC, EPI, BN, KE_SLICE, DEEP>(a, splitk_ws, st);
+    default: return launch_gemm_bf16_v2_ke<A_KC, B_KC, EPI, BN, KE_ANY, DEEP>(a, splitk_ws, st);
+  }
 }
 
 template <bool A_KC, bool B_KC, int EPI>
 hipError_t launch_gemm_bf16_v2(const GemmArgs& a, float* splitk_ws, hipStream_t st) {
-  return a.K % (2 * V2_BK) ? launch_gemm_bf16_v2_rag<A_KC, B_KC, EPI, true>(a, splitk_ws, st)
-                           : launch_gemm_bf16_v2_rag<A_KC, B_KC, EPI, false>(a, splitk_ws, st);
+  const int bn = v2_pick_bn<A_KC, B_KC, EPI>(a.M, a.N, a.K, splitk_ws != nullptr);
+  if constexpr (v2_has_narrow<A_KC, B_KC, EPI>())
+    if (bn == 192) return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, 192>(a, splitk_ws, st);
+  if constexpr (v2_has_small<EPI>())
+    if (bn == V2_SMALL)
+      return v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, V2_SMALL).deep()
+                 ? launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_SMALL, true>(a, splitk_ws, st)
+                 : launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_SMALL>(a, splitk_ws, st);
+  return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_B>(a, splitk_ws, st);
 }
 
 // One translation unit per operand layout (keeps compile times parallel).

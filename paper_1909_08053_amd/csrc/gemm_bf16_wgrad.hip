@@ -27,17 +27,11 @@ hipError_t launch_gemm_bf16_wgrad_group(const GemmArgs* probs, int n, float* spl
     const bool use_small = forced ? forced == V2_SMALL : small < big;
     static const bool off = [] { const char* e = getenv("MLM_GEMM_GROUP"); return e && atoi(e) == 0; }();
     if (!off && (use_small ? small : big) + 2.0 < alone) {
-      const bool rag = probs[0].K % (2 * V2_BK) != 0;
       int tiles = 0;
       for (int q = 0; q < n; ++q) tiles += v2_tiles(probs[q], V2_SMALL, V2_SMALL);
-      if (use_small && tiles <= gemm_cu_count())
-        return rag ? launch_gemm_bf16_v2_group<false, false, V2_SMALL, true, true>(probs, n, st)
-                   : launch_gemm_bf16_v2_group<false, false, V2_SMALL, false, true>(probs, n, st);
-      if (use_small)
-        return rag ? launch_gemm_bf16_v2_group<false, false, V2_SMALL, true, false>(probs, n, st)
-                   : launch_gemm_bf16_v2_group<false, false, V2_SMALL, false, false>(probs, n, st);
-      return rag ? launch_gemm_bf16_v2_group<false, false, V2_B, true, false>(probs, n, st)
-                 : launch_gemm_bf16_v2_group<false, false, V2_B, false, false>(probs, n, st);
+      if (!use_small) return launch_gemm_bf16_v2_group<false, false, V2_B, false>(probs, n, st);
+      return tiles <= gemm_cu_count() ? launch_gemm_bf16_v2_group<false, false, V2_SMALL, true>(probs, n, st)
+                                      : launch_gemm_bf16_v2_group<false, false, V2_SMALL, false>(probs, n, st);
     }
   }
   for (int q = 0; q < n; ++q) {

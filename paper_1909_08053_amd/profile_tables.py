@@ -154,7 +154,7 @@ def kernels(raw):
     tf = gf / ce_us / 1e6
     rl = bench["roofline"]
     L += ["",
-          "dominant kernel: gemm_bf16_v2_kernel<true,false,EPI_CE,256,false,false> (logits GEMM 8192x3072x6400 fused with the cross-entropy "
+          "dominant kernel: gemm_bf16_v2_kernel<true,false,EPI_CE,256,0,false> (logits GEMM 8192x3072x6400 fused with the cross-entropy "
           "partials + logits store)",
           f"  rocprofv3 average duration {ce_us:.1f} us  ->  {gf / 1e9:.2f} GFLOP / {ce_us:.1f} us = {tf:.1f} TFLOP/s = "
           f"{tf / 25:.1f} % of the 2.5 PFLOP/s bf16 dense peak",
@@ -214,7 +214,7 @@ def traffic(raw):
          f"calibration: combine_kernel (three launches after the timed steps, one partial, no bias, no residual) is a plain copy of "
          f"[8192,3072] bf16 = {copy_bytes / 1e6:.2f} MB in, same out",
          f"  FETCH_SIZE reads {avg(f[comb]):.0f} KiB  -> scale {fr:.3f};  WRITE_SIZE reads {avg(w[comb]):.0f} KiB -> scale {fw:.3f}",
-         f"logits GEMM + CE partials (gemm_bf16_v2_kernel<true,false,EPI_CE,256,false,false>): FETCH_SIZE {avg(f[cek]):.0f} KiB, WRITE_SIZE "
+         f"logits GEMM + CE partials (gemm_bf16_v2_kernel<true,false,EPI_CE,256,0,false>): FETCH_SIZE {avg(f[cek]):.0f} KiB, WRITE_SIZE "
          f"{avg(w[cek]):.0f} KiB per dispatch",
          f"  scaled: {ce_f / 1e6:.1f} MB read + {ce_w / 1e6:.1f} MB written = {(ce_f + ce_w) / 1e6:.1f} MB per launch",
          f"  algorithmic (each operand once, logits once): {alg / 1e6:.1f} MB  ->  ratio {(ce_f + ce_w) / alg:.2f}"]

@@ -4,6 +4,7 @@ import subprocess
 import pytest
 
 from paper_1909_08053_amd import build as BLD
+from test_gpu_bf16_gemm_k import LARGE_TILES
 
 MAIN = """#include <stdio.h>
 #include <stdlib.h>
@@ -51,6 +52,8 @@ GROUPS = [(8192, 1920, 2, 473, 361), (5000, 1920, 2, 285, 230), (8192, 1536, 1, 
           (8192, 3072, 8, 259, 195), (4096, 3072, 4, 214, 187), (4096, 2560, 4, 155, 173), (8192, 1536, 8, 78, 147),
           (3000, 1536, 4, 53, 67), (8192, 1536, 4, 149, 154)]
 
+LAYOUTS = ("fwd", "dgrad", "wgrad")
+
 
 @pytest.fixture(scope="module")
 def picks(tmp_path_factory):
@@ -59,6 +62,7 @@ def picks(tmp_path_factory):
     src.write_text(MAIN)
     subprocess.run([BLD._hipcc(), *BLD.FLAGS, str(src), "-o", str(exe)], check=True, capture_output=True, timeout=180)
     lines = [f"{m[0]} {m[1]} {m[2]} {m[3]}" for m in MEASURED] + [f"g {g[0]} {g[1]} {g[2]}" for g in GROUPS]
+    lines += [f"{l} {M} {N} {K}" for M, N, K in LARGE_TILES[192] + LARGE_TILES[256] for l in LAYOUTS]
     out = subprocess.run([str(exe)], input="\n".join(lines), text=True, check=True, capture_output=True, timeout=60).stdout.split()
     return [int(x) for x in out]
 
@@ -70,5 +74,11 @@ def test_chosen_tile_is_within_five_percent_of_the_best(picks):
 
 
 def test_grouped_weight_gradients_take_the_better_tile(picks):
-    for g, bn in zip(GROUPS, picks[len(MEASURED):]):
+    for g, bn in zip(GROUPS, picks[len(MEASURED):len(MEASURED) + len(GROUPS)]):
         assert g[3 if bn == 128 else 4] <= 1.05 * min(g[3:]), (g, bn)
+
+
+def test_shapes_of_the_large_tiles_test_take_the_large_tiles(picks):
+    large = picks[len(MEASURED) + len(GROUPS):]
+    n = 3 * len(LARGE_TILES[192])
+    assert set(large[:n]) == {192} and set(large[n:]) == {256}, large
