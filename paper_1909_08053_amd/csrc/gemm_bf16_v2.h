@@ -22,7 +22,7 @@
 // Tail split: when the tile count does not fill a whole number of rounds of the 256 CUs, the tiles of the last
 // partial round are split along k into f pieces (f = floor(256 / remainder)); each piece writes an fp32 partial
 // tile to a workspace and gemm_v2_fixup_kernel sums the pieces in a fixed order (deterministic) and applies
-// the bias.  Only the plain-store epilogue takes part.
+// the epilogue, whichever it is.
 #pragma once
 #include "gemm_bf16.h"
 #include "lds_dma.h"
@@ -657,7 +657,7 @@ hipError_t launch_gemm_bf16_v2_group(const GemmArgs* probs, int n, hipStream_t s
   }
 }
 
-int gemm_v2_forced_bn();                    // MLM_GEMM_BN=128|192|256 forces a tile width where both exist, else 0
+int gemm_v2_forced_bn();                    // MLM_GEMM_BN=128|192|256 forces a tile width where it exists, else 0
 
 // The 192-wide tile exists for all but the cross-entropy epilogues, the small tile for every epilogue but the one that
 // recomputes the logits: take the one the cost model prices lowest for this shape.

@@ -180,9 +180,9 @@ def test_small_bf16_dropout_layers(case):
 
 
 def test_full_size_8p3b_shape_dropout_and_embedding_all_shards():
-    """The 8.3B-shaped layer (s = 1024, H = 3072, 32 heads of 96, vocabulary 51,200, 8 shards: the launch
-    configuration of the benchmark, batch 2 of 8 to bound the oracle's s x s mask and probability tensors) with
-    dropout 0.1 at every site (Section 4.2) and the input embedding, all shards, against the oracle."""
+    """The 8.3B-shaped layer (s = 1024, H = 3072, 32 heads of 96, vocabulary 51,200, 8 shards; batch 2 of the benchmark's
+    8 to bound the oracle's s x s mask and probability tensors, so attention divides its waves as it does for few
+    workgroups) with dropout 0.1 at every site (Section 4.2) and the input embedding, all shards, against the oracle."""
     cfg = synth.with_batch(synth.CONFIGS["gpt2_8p3b"], 2)
     errs = run_dropout_layer(cfg, 0.1, 0.1, scale_w=1.0, embed=True)
     print("worst max-norm relative errors:", sorted(errs, key=lambda e: -e[1])[:6])

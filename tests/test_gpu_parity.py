@@ -24,7 +24,7 @@ def _dn(t):
 # ------------------------------------------------------------------ GEMM building block
 GEMM_SHAPES = [(256, 256, 256), (512, 384, 192), (264, 136, 72), (1000, 520, 328), (128, 1152, 3072 // 4),
                (8, 8, 8), (1032, 952, 640), (72, 7648, 136),
-               # K an odd multiple of 32 (the last pair of k-slices overlaps the one before it): shortest, short, long
+               # K an odd multiple of 32 (the last pair of k-slices is half full): shortest, short, long
                (264, 200, 96), (520, 264, 160), (136, 520, 7648), (296, 392, 2016)]
 
 
@@ -352,7 +352,7 @@ def test_deferred_sums_equal_the_sums_finished_inside_each_call(variant):
         L = LayerShards(cfg, list(range(p)), DEV, deferred_sums=deferred, **kw)
         L.load_host_inputs(inp)
         if deferred and variant == "short_buffer":
-            one_ln = ((cfg.T + 31) // 32) * 3 * cfg.H * 4
+            one_ln = B.mlm_workspace_bytes(L.dims[0], B.WS_LAYERNORM_BWD)
             L.defer_ws = torch.empty(one_ln + 256, device=DEV, dtype=torch.uint8)
         for k in ("dg1", "db1", "dg2", "db2", "dgf", "dbf", "dbo", "dc"):
             L.act[k].fill_(float("nan"))
@@ -400,7 +400,7 @@ def test_grouped_weight_gradients_equal_the_separate_calls(dtype, shape):
     """Deferring the four weight gradients of a layer shard to one mlm_layer_shard_wgrads call (one grouped GEMM launch
     where the cost model picks it) changes no input gradient at all and the weight gradients only through the k-split
     summation order of the separate GEMMs (none when neither form splits)."""
-    if shape == "ragged":        # T = 528 is no multiple of 64: the GEMMs run one by one (register-staged kernel)
+    if shape == "ragged":        # T = 528 is no multiple of 64: a k that ends inside a pair of slices
         cfg = synth.small_config(dtype=dtype, b=2, s=264, H=256, h=2, F=1024, V=528, p=2)
     elif shape == "aligned":     # T = 512, 24 tiles in all: the cost model picks the single grouped launch
         cfg = synth.small_config(dtype=dtype, b=2, s=256, H=512, h=4, F=2048, V=512, p=2)
