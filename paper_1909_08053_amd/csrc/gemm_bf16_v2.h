@@ -91,8 +91,8 @@ template <int ROWS> __device__ __forceinline__ int v2_mn_chunk(int pos, int k) {
 // pass does not take 16 consecutive lanes: the first one holds lanes 0-3, 12-15 and 20-27, i.e. rows 0-3 and 12-15 of unit u
 // and rows 4-11 of unit u + 1.  With row pairs numbered in order, both sets of values are closed under that + 1 and the 16
 // lanes touch 16 different bank groups (with a value that permutes the bits of the pair number -- distinct for 16
-// consecutive lanes -- every pass met a two-way conflict: half of the LDS cycles of these reads, by the counter,
-// now 1-6 %; the 8.3B-shape step 1797 -> 1791 us: the reads were mostly hidden).
+// consecutive lanes -- every pass met a two-way conflict: half of the LDS cycles of these reads; the counter
+// now shows 1-12 % of a kernel's, epilogue included; the 8.3B-shape step 1797 -> 1791 us: the reads were mostly hidden).
 __device__ __forceinline__ int v2_kc_swizzle(int row) { return (row >> 1) & 7; }
 
 // Per-lane source pointers of one operand's DMA copies (NP 1-KB copies per wave).
