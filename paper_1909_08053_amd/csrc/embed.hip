@@ -118,18 +118,19 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(int Tn, int H, int Vl, i
 // dE_r[:, loc] += the sum of the rows of dz0 whose token has local id loc, in token order (fp32).  The wave whose 16
 // positions hold the head of a run of equal ids sums all of it, sixteen rows at a time: their loads are in flight together (one
 // row after the other, three dependent trips to memory each, 8192 equal tokens took 4.4 ms).
-// Element-sized accesses to dE_r: neighbouring columns belong to other lanes and workgroups.  NWV waves = 16 NWV positions per
-// workgroup: four, or one where that leaves compute units idle -- every lane of an access to dE_r may touch another line, and
-// the lines of a few workgroups queue on their compute units (200 tokens x 320, 1024 columns, 7.9 us, 6.1 with one).
-template <typename T, int NWV>
+// Element-sized accesses to dE_r: neighbouring columns belong to other lanes and workgroups.  A workgroup takes NWV waves = 16 NWV
+// positions x HR rows: 64 x 64, or 16 x 16 where that leaves compute units idle -- every lane of an access to dE_r may touch
+// another line, and the lines of a few workgroups queue on their compute units (200 tokens x 320, 1024 columns: 7.9 us,
+// 16 x 64 6.1, 16 x 16 5.1).
+template <typename T, int NWV, int HR>
 __global__ __launch_bounds__(64 * NWV) void embed_bwd_kernel(int Tn, int H, int Vl, int v0, const int32_t* __restrict__ ids,
                                                         const int32_t* __restrict__ perm, const T* __restrict__ dz,
                                                         T* __restrict__ dE) {
-  constexpr int NP = 16 * NWV;                        // positions
-  __shared__ float tile[NP * (kEmbTile + 1)];
+  constexpr int NP = 16 * NWV, RPL = HR * NP / (64 * NWV);         // positions; rows of dE per lane
+  __shared__ float tile[NP * (HR + 1)];
   __shared__ int stok[NP + 1], sloc[NP + 2];          // sloc[i + 1]: position k0 + i, from the one before the tile to the one behind
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int k0 = blockIdx.x * NP, h0 = blockIdx.y * kEmbTile, h = h0 + lane, hc = min(h, H - 1);
+  const int k0 = blockIdx.x * NP, h0 = blockIdx.y * HR, col = lane % HR, hc = min(h0 + col, H - 1);
   if (threadIdx.x <= NP + 1) {
     const int k = k0 + (int)threadIdx.x - 1;
     const int t = k >= 0 && k < Tn ? perm[k] : -1, loc = t >= 0 ? ids[t] - v0 : -1;
@@ -150,7 +151,7 @@ __global__ __launch_bounds__(64 * NWV) void embed_bwd_kernel(int Tn, int H, int 
   for (int i = 0; i < 16; ++i) {
     const int prev = __builtin_amdgcn_readlane(lloc, i), loc = __builtin_amdgcn_readlane(lloc, i + 1);
     if (loc < 0 || loc != prev) {                     // a new run, or the end of the shard's tokens
-      if (head >= 0) tile[head * (kEmbTile + 1) + lane] = acc;
+      if (head >= 0) tile[head * (HR + 1) + col] = acc;
       head = loc >= 0 ? p0 + i : -1;
       acc = v[i];
     } else {
@@ -174,19 +175,19 @@ __global__ __launch_bounds__(64 * NWV) void embed_bwd_kernel(int Tn, int H, int 
       for (int i = 0; i < 16; ++i) acc = i < n ? acc + v[i] : acc;
       if (n < 16) break;
     }
-    tile[head * (kEmbTile + 1) + lane] = acc;
+    tile[head * (HR + 1) + col] = acc;
   }
   __syncthreads();
-  const int p = threadIdx.x % NP, r0 = threadIdx.x / NP * 16;       // this lane's position, the first of its rows
+  const int p = threadIdx.x % NP, r0 = threadIdx.x / NP * RPL;       // this lane's position, the first of its rows
   const int loc = sloc[p + 1];
   if (loc < 0 || loc == sloc[p]) return;              // outside, or not the head of its run
-  T was[16];                                          // (all read before the first is written)
+  T was[RPL];                                         // (all read before the first is written)
 #pragma unroll
-  for (int i = 0; i < 16; ++i) was[i] = dE[(size_t)min(h0 + r0 + i, H - 1) * Vl + loc];
+  for (int i = 0; i < RPL; ++i) was[i] = dE[(size_t)min(h0 + r0 + i, H - 1) * Vl + loc];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
+  for (int i = 0; i < RPL; ++i) {
     const int r = r0 + i;
-    if (h0 + r < H) dE[(size_t)(h0 + r) * Vl + loc] = from_f32<T>(to_f32(was[i]) + tile[p * (kEmbTile + 1) + r]);
+    if (h0 + r < H) dE[(size_t)(h0 + r) * Vl + loc] = from_f32<T>(to_f32(was[i]) + tile[p * (HR + 1) + r]);
   }
 }
 
@@ -254,11 +255,11 @@ hipError_t launch_embed_fwd(int dtype, int T, int H, int Vl, int v0, const int32
 template <typename T>
 static hipError_t embed_bwd_dispatch(int Tn, int H, int Vl, int v0, const int32_t* ids, const int32_t* perm, const T* dz, T* dE,
                                      hipStream_t st) {
-  const int rows = (H + kEmbTile - 1) / kEmbTile;
-  if ((Tn + 63) / 64 * rows < gemm_cu_count())
-    hipLaunchKernelGGL((embed_bwd_kernel<T, 1>), dim3((Tn + 15) / 16, rows), dim3(64), 0, st, Tn, H, Vl, v0, ids, perm, dz, dE);
+  const dim3 large((Tn + 63) / 64, (H + 63) / 64), small((Tn + 15) / 16, (H + 15) / 16);
+  if ((int)(large.x * large.y) < gemm_cu_count())
+    hipLaunchKernelGGL((embed_bwd_kernel<T, 1, 16>), small, dim3(64), 0, st, Tn, H, Vl, v0, ids, perm, dz, dE);
   else
-    hipLaunchKernelGGL((embed_bwd_kernel<T, 4>), dim3((Tn + 63) / 64, rows), dim3(256), 0, st, Tn, H, Vl, v0, ids, perm, dz, dE);
+    hipLaunchKernelGGL((embed_bwd_kernel<T, 4, 64>), large, dim3(256), 0, st, Tn, H, Vl, v0, ids, perm, dz, dE);
   return hipGetLastError();
 }
 

@@ -1,4 +1,4 @@
-"""Input embedding at the edges of its 64 x 64 tiles: one token, ragged tokens and rows, runs of equal ids that cross the 16
+"""Input embedding at the edges of its 64 x 64 (gradient of few tokens: 16 x 16) tiles: one token, ragged tokens and rows, runs of equal ids that cross the 16
 positions of a wave and the 64 of a tile, ids of other shards."""
 import pytest
 import torch
