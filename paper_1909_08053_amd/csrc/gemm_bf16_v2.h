@@ -26,6 +26,7 @@
 #pragma once
 #include "gemm_bf16.h"
 #include "lds_dma.h"
+#include <limits.h>
 #include <string.h>
 #include <type_traits>
 
@@ -180,10 +181,101 @@ __device__ __forceinline__ bf16x8 v2_frag16(const unsigned char* ring, int stage
 struct V2Plan {
   int tiles_m, tiles_n, full_tiles, tail_tiles, split;   // grid = full_tiles + tail_tiles * split
   int bm, bn;                                             // tile: 256 x 256, 256 x 192 or 128 x 128
+  int window, strip, long_pieces;                         // walk over the tiles (v2_xcd_order, v2_tile_of; v2_set_walk)
   double cost;                                            // estimated kernel time in microseconds (host side only)
   int grid() const { return full_tiles + tail_tiles * split; }
   bool deep() const { return bn == 128 && grid() <= gemm_cu_count(); }   // one workgroup per compute unit: eight-slice ring
 };
+
+// Walk over the tiles.  Every XCD has its own L2, so the 32 tiles that its compute units work on at a time (64 of the small
+// tile) should lie close together: 4 x 8 tiles read 12 operand panels, 1 x 32 read 33.  Workgroup ids go to the XCDs in turn.
+//   strip = 0: ids straight to tiles, tile row fastest.  Good patches where the number of tile rows is a multiple of 32, and
+//   otherwise up to all tile rows or all columns for every XCD.
+//   Else v2_xcd_order: of every window of ids that is resident at a time, the ids of one XCD (congruent mod 8) take CONSECUTIVE
+//   positions of the walk of v2_tile_of: the shorter side of the output is cut into strips `strip` tiles wide (the last takes
+//   what is left); a strip is walked along the longer side, every other one backwards, a row of `strip` tiles at a time.
+__host__ __device__ inline int v2_xcd_order(int id, int total, int window) {
+  const int base = total <= window ? 0 : id / window * window;      // (a division is 0.07 us ahead of the first copy)
+  const int cnt = total - base < window ? total - base : window;
+  const int p = id - base, x = p & 7, per = cnt >> 3, more = cnt & 7;
+  return base + x * per + (x < more ? x : more) + (p >> 3);
+}
+__host__ __device__ inline void v2_tile_of(const V2Plan& p, int q, int* tile_m, int* tile_n) {
+  const bool rows = p.strip == 0 || p.tiles_m <= p.tiles_n;         // strips of tile rows, walked along the columns
+  const int cross = rows ? p.tiles_m : p.tiles_n, along = rows ? p.tiles_n : p.tiles_m;
+  const int strip = p.strip == 0 ? cross : p.strip;
+  const int s = strip >= cross ? 0 : q / (strip * along), r = q - s * (strip * along);
+  const int left = cross - s * strip, w = left < strip ? left : strip;
+  int l = r / w;
+  const int c = s * strip + r - l * w;
+  if (s & 1) l = along - 1 - l;
+  *tile_m = rows ? c : l;
+  *tile_n = rows ? l : c;
+}
+// Operand bytes (per k) of the busiest XCD, over the first two windows of ids, in strips of w.
+inline long v2_walk_cost(const V2Plan& p, int window, int w) {
+  const int tiles = p.tiles_m * p.tiles_n;
+  const bool rows = p.tiles_m <= p.tiles_n;
+  const int cross = rows ? p.tiles_m : p.tiles_n, along = rows ? p.tiles_n : p.tiles_m;
+  const int bc = rows ? p.bm : p.bn, bl = rows ? p.bn : p.bm, len = w * along;
+  long cost = 0;
+  for (int base = 0; base < tiles && base < 2 * window; base += window) {
+    const int cnt = tiles - base < window ? tiles - base : window;
+    long busiest = 0;
+    for (int x = 0; x < 8; ++x) {
+      int q = base + x * (cnt >> 3) + (x < (cnt & 7) ? x : cnt & 7);
+      const int end = q + (cnt >> 3) + (x < (cnt & 7));
+      int nc = 0, lo = along, hi = -1;                 // panels across; first and last panel along
+      while (q < end) {                                // strip by strip
+        const int s = q / len, left = cross - s * w, sw = left < w ? left : w;
+        const int stop = s * len + sw * along < end ? s * len + sw * along : end;
+        int l0 = (q - s * len) / sw, l1 = (stop - 1 - s * len) / sw;
+        nc += l1 > l0 ? sw : stop - q;
+        if (s & 1) { const int t = l0; l0 = along - 1 - l1; l1 = along - 1 - t; }
+        if (l0 < lo) lo = l0;
+        if (l1 > hi) hi = l1;
+        q = stop;
+      }
+      const long c = (long)nc * bc + (hi >= lo ? (long)(hi - lo + 1) * bl : 0);
+      if (c > busiest) busiest = c;
+    }
+    cost += busiest;
+  }
+  return cost;
+}
+// The same with ids straight to tiles: an XCD meets every (R / gcd(R, 8))-th tile row.
+inline long v2_plain_cost(const V2Plan& p, int window) {
+  const int tiles = p.tiles_m * p.tiles_n, R = p.tiles_m;
+  const int step = R % 8 == 0 ? 8 : R % 4 == 0 ? 4 : R % 2 == 0 ? 2 : 1;
+  long cost = 0;
+  for (int base = 0; base < tiles && base < 2 * window; base += window) {
+    const int cnt = tiles - base < window ? tiles - base : window, share = (cnt + 7) / 8;
+    const int nr = R / step < share ? R / step : share;
+    int nc = (cnt + R - 1) / R;                        // columns of the window; an XCD may skip some
+    if (nc > share) nc = share;
+    cost += (long)nr * p.bm + (long)nc * p.bn;
+  }
+  return cost;
+}
+// The walk of a launch: the strip width that costs least, where that is a tenth less than ids straight to tiles (equal patches
+// are better apart: 96 tiles of 6 rows 1 us).  Measured in strips, 1450 shapes of up to 600 tiles: small tile 0.90 of the time on average
+// (20 tile rows 0.98, 15 rows 0.88, 33 rows 0.83; 1920 x 4096 x 6144 131 -> 86 us), 192 wide 0.98, 256 wide 1.00.
+// long_pieces: an XCD takes the k-pieces of tail tiles part by part of k; short ones are spread over the XCDs.  36 tiles x 6 pieces of
+// 16 slices in order / spread 15.2 / 12.3 us, 96 x 2 of 32 17.7 / 14.5; 80 x 3 of 80 and 32 x 4 .. 128 x 2 large tiles of
+// 24 .. 100 about 1 % of their steps in order's favour.
+inline void v2_set_walk(V2Plan* p, int window, int K, bool strips = false) {
+  p->window = window;
+  p->long_pieces = v2_slices(K) >= (p->bn == V2_SMALL ? 48 : 16) * p->split;
+  p->strip = 0;
+  if (p->full_tiles == 0 && !p->long_pieces) return;
+  const int cross = p->tiles_m <= p->tiles_n ? p->tiles_m : p->tiles_n;
+  const long plain = v2_plain_cost(*p, window);
+  long best = strips ? LONG_MAX : plain - plain / 10;
+  for (int w = cross < 3 ? cross : 3; w <= cross && w <= 12; ++w) {
+    const long c = v2_walk_cost(*p, window, w);
+    if (c <= best) { best = c; p->strip = w; }
+  }
+}
 
 // Cost-model constants (microseconds, fitted to rocprofv3 kernel durations of unsplit two-round launches at two
 // k-lengths each on MI355X): fixed cost of a tile (fill + epilogue) and cost of one 32-deep k-slice, for the
@@ -191,12 +283,10 @@ struct V2Plan {
 // in 0.88 of the time, so it wins where it saves a round or fills one and loses on long-k shapes whose last round
 // can be split instead.  The fix-up kernel reads the pieces mostly out of the last-level cache.
 // The small tile has two: `alone` with at most one workgroup per compute unit in the launch, else for two that share one
-// (fitted to 60 .. 2600 tiles of 48 .. 256 slices).  Two that share one are bound by what their XCD's L2 has to fetch: ids go
-// to the eight XCDs in turn and the tile row is the fast index, so with an odd number of tile rows every XCD works on all of
-// them, and with few rows on many columns.  128 against 256 and 192 wide, weight-gradient layout, 8192 deep: 1920 x 12800 (15
-// tile rows) 591 / 347 / 419 us, 8064 x 1024 (63 rows) 173 / 153 / 137, 1024 x 7680 (8 rows) 169 / 155 / 138; but 2048 x 3840
-// (16 rows) 126 / 154 / 136, and 3840 x 1920 (30 rows) 152 / 139 with a k-split of the large tile's 120.  With the row count left out of the model, 172 of 1985 shapes took the small tile where the
-// large one it would take otherwise is 3 .. 76 % faster; with it none does by more than 3 %.
+// (fitted to 60 .. 2600 tiles of 48 .. 256 slices).  The dearer price of an odd number of tile rows, or of few, comes from a
+// walk that spread those over all XCDs: 1920 x 12800 x 8192 (15 tile rows) 591 us, 256-wide 347.  With v2_tile_of the cheaper
+// one fits every row count (that shape: 370 / 352), so the line is cautious: where it keeps a large tile the small one is now up
+// to 1.3 x faster (768 x 6400 x 6144: 67 / 88 us).
 inline double v2_small_slice(int tiles_m) {
   if (tiles_m % 2 || tiles_m <= 10) return 0.72;
   return 0.46;
@@ -265,19 +355,23 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
 
-  // work item: a full tile, or one k-piece of a tail tile
-  int vt, piece = 0, npieces = 1;
-  if (pid < plan.full_tiles) {
-    vt = pid;
-  } else {
-    const int t = pid - plan.full_tiles;
-    vt = plan.full_tiles + t / plan.split;
-    piece = t % plan.split;
+  // Work item: a full tile, or one k-piece of a tail tile.  An XCD takes long pieces of the same part of k and of neighbouring
+  // tiles, which share panels; short ones, whose time is the first misses', are spread (v2_set_walk).
+  int vt = pid, piece = 0, npieces = 1;
+  if (pid >= plan.full_tiles) {
+    int t = pid - plan.full_tiles;
+    if (plan.long_pieces) {
+      t = v2_xcd_order(t, plan.tail_tiles * plan.split, plan.window);
+      piece = t / plan.tail_tiles;
+      vt = plan.full_tiles + t - piece * plan.tail_tiles;
+    } else {
+      vt = plan.full_tiles + t / plan.split;
+      piece = t % plan.split;
+    }
     npieces = plan.split;
   }
-  // Plain order, tile row fastest: the 256 concurrent tiles form 8 tile-columns of 32 tile-rows, and the ids that
-  // share an XCD (congruent mod 8) share tile rows, so each XCD's L2 sees few distinct operand panels.
-  const int tile_m = vt % plan.tiles_m, tile_n = vt / plan.tiles_m;
+  int tile_m, tile_n;
+  v2_tile_of(plan, vt, &tile_m, &tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   const int np_total = (a.K + 2 * V2_BK - 1) / (2 * V2_BK);   // pairs of 32-deep slices of the problem
   const int kt_begin = 2 * (int)((long)np_total * piece / npieces);
@@ -454,7 +548,9 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
 template <bool A_KC, bool B_KC, int EPI, int BN, int KE, bool DEEP>
 __global__ __launch_bounds__((v2_nw<BN, DEEP>() * 64), 2) void gemm_bf16_v2_kernel(GemmArgs a, V2Plan plan, float* splitk_ws) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  gemm_v2_work_item<A_KC, B_KC, EPI, BN, KE, DEEP>(a, plan, splitk_ws, blockIdx.x, lds_raw);
+  const int id = blockIdx.x;
+  const int pid = plan.strip && id < plan.full_tiles ? v2_xcd_order(id, plan.full_tiles, plan.window) : id;
+  gemm_v2_work_item<A_KC, B_KC, EPI, BN, KE, DEEP>(a, plan, splitk_ws, pid, lds_raw);
 }
 
 // Several independent GEMMs of one operand layout in ONE launch (plain-store epilogue, no k-split): the tiles of
@@ -464,6 +560,7 @@ __global__ __launch_bounds__((v2_nw<BN, DEEP>() * 64), 2) void gemm_bf16_v2_kern
 constexpr int kMaxGroup = 4;
 struct GemmGroup {
   int n;
+  int xcd_order;                       // one walk through the tiles of all problems
   int tile_begin[kMaxGroup + 1];       // first work item of each problem; tile_begin[n] = grid size
   GemmArgs args[kMaxGroup];
   V2Plan plan[kMaxGroup];
@@ -472,7 +569,7 @@ struct GemmGroup {
 template <bool A_KC, bool B_KC, int BN, int KE, bool DEEP>
 __global__ __launch_bounds__((v2_nw<BN, DEEP>() * 64), 2) void gemm_bf16_v2_group_kernel(GemmGroup g) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  const int pid = blockIdx.x;
+  const int pid = g.xcd_order ? v2_xcd_order(blockIdx.x, g.tile_begin[g.n], g.plan[0].window) : blockIdx.x;
   // the problem index is uniform over the workgroup: select its arguments with scalar compares
   int q = 0;
 #pragma unroll
@@ -493,10 +590,10 @@ constexpr int kFixRows = 8;
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_v2_fixup_kernel(GemmArgs a, V2Plan plan, const float* __restrict__ ws) {
   const int t = blockIdx.y;                          // tail tile
-  const int vt = plan.full_tiles + t;
-  const int tile_n = vt / plan.tiles_m;
+  int tile_m, tile_n;
+  v2_tile_of(plan, plan.full_tiles + t, &tile_m, &tile_n);
   const int bm = plan.bm, bn = plan.bn;               // a partial tile is [bm][bn] floats
-  const int m0 = (vt % plan.tiles_m) * bm, n0 = tile_n * bn;
+  const int m0 = tile_m * bm, n0 = tile_n * bn;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = n0 + lane * 4;
   const bool col_ok = n < a.N && lane * 4 < bn;       // N is a multiple of 8: a 4-column group is all in or all out
@@ -593,13 +690,20 @@ template <bool A_KC, bool B_KC, int BN, bool DEEP> constexpr size_t v2_lds_bytes
   return kLds;
 }
 
+// Ids resident at a time, a multiple of the eight XCDs.
+template <int BN, bool DEEP> int v2_window() {
+  const int n = (BN == V2_SMALL && !DEEP ? 2 : 1) * gemm_cu_count() & ~7;
+  return n < 8 ? 8 : n;
+}
+
 template <bool A_KC, bool B_KC, int EPI, int BN, int KE, bool DEEP>
 hipError_t launch_gemm_bf16_v2_ke(const GemmArgs& a, float* splitk_ws, hipStream_t st) {
   auto kern = gemm_bf16_v2_kernel<A_KC, B_KC, EPI, BN, KE, DEEP>;
   constexpr size_t kLds = v2_lds_bytes<A_KC, B_KC, BN, DEEP>();
   static LdsAttrOnce attr;         // per instantiation and device
   if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
-  const V2Plan plan = v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, BN);
+  V2Plan plan = v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, BN);
+  v2_set_walk(&plan, v2_window<BN, DEEP>(), a.K);
   hipLaunchKernelGGL(kern, dim3(plan.grid()), dim3(v2_nw<BN, DEEP>() * 64), kLds, st, a, plan, splitk_ws);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -643,6 +747,11 @@ hipError_t launch_gemm_bf16_v2_group_ke(const GemmArgs* probs, int n, hipStream_
     total += g.plan[q].full_tiles;
   }
   for (int q = n; q <= kMaxGroup; ++q) g.tile_begin[q] = total;
+  for (int strips = 0; strips < 2; ++strips) {         // strips for all problems where one gains by them
+    for (int q = 0; q < n; ++q) v2_set_walk(&g.plan[q], v2_window<BN, DEEP>(), probs[q].K, strips != 0);
+    for (int q = 0; q < n; ++q) g.xcd_order |= g.plan[q].strip != 0;
+    if (!g.xcd_order) break;
+  }
   hipLaunchKernelGGL(kern, dim3(total), dim3(v2_nw<BN, DEEP>() * 64), kLds, st, g);
   return hipGetLastError();
 }
