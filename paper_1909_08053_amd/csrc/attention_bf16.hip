@@ -97,14 +97,18 @@ struct ATile {
   }
 };
 
-// Which 16 bytes of a tile each lane copies (fixed per lane), and the copy of one tile.
+// Which 16 bytes of a tile each lane copies (fixed per lane), and the copy of one tile.  After REP copies of a wave the lane is
+// STEP rows further down at the same unit but for the swizzle, which differs in one bit (FLIP elements): a row and a column per
+// copy would be up to 12 registers of kernels that have none left.
 template <int D>
 struct ATileSrc {
   typedef ATile<D> TL;
-  int row[TL::QPW], col[TL::QPW];
+  static constexpr int REP = TL::U % 12 == 0 ? 3 : 1, STEP = 64 * REP / TL::U, FLIP = TL::U == 16 ? 8 : 16;
+  static_assert(TL::QPW <= (TL::U == 16 ? 4 : 2) * REP, "one bit of the swizzle (two at 16 units)");
+  int row[REP], col[REP];
   __device__ __forceinline__ void init(int wave, int lane) {
 #pragma unroll
-    for (int i = 0; i < TL::QPW; ++i) {
+    for (int i = 0; i < REP; ++i) {
       const int u = 64 * (wave * TL::QPW + i) + lane;
       row[i] = u / TL::U;
       col[i] = ((u % TL::U) ^ TL::sw(row[i])) * 8;
@@ -112,12 +116,12 @@ struct ATileSrc {
   }
   // P: element (0, 0) of the streamed matrix (row stride ld); rows beyond nrows - 1 re-read the last row (callers mask)
   __device__ __forceinline__ void issue_one(const bf16* P, int ld, int row0, int nrows, uint32_t lds_tile, int wave_u, int i) const {
-    dma16(P + (size_t)min(row0 + row[i], nrows - 1) * ld + col[i], lds_tile + (wave_u * TL::QPW + i) * 1024);
+    dma16(P + (size_t)min(row0 + row[i % REP] + i / REP * STEP, nrows - 1) * ld + (col[i % REP] ^ (i / REP * FLIP)),
+          lds_tile + (wave_u * TL::QPW + i) * 1024);
   }
   __device__ __forceinline__ void issue(const bf16* P, int ld, int row0, int nrows, uint32_t lds_tile, int wave_u) const {
 #pragma unroll
-    for (int i = 0; i < TL::QPW; ++i)
-      dma16(P + (size_t)min(row0 + row[i], nrows - 1) * ld + col[i], lds_tile + (wave_u * TL::QPW + i) * 1024);
+    for (int i = 0; i < TL::QPW; ++i) issue_one(P, ld, row0, nrows, lds_tile, wave_u, i);
   }
 };
 
@@ -377,8 +381,9 @@ __global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW
 // P = exp2(S sc - lse), dS = P o (dP - delta), dQ^T += K^T dS^T with K read a second time through the transposing
 // loads.  delta_i = sum_d dO_id O_id is computed here from the rows the lanes already hold and stored for the
 // dK/dV kernel, which runs after this one.
-template <int D, bool DROP, int MODE>
-__global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW)) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
+// MERGED: part of the joint kernel below; delta comes from attn_delta_bf16_kernel.
+template <int D, bool DROP, int MODE, bool MERGED>
+__device__ __forceinline__ void attn_bwd_dq_block(const AttnArgs a, const AttnBlock blk) {
   typedef ATile<D> TL;
   typedef AttnSplit<D, MODE> SP;
   constexpr int RW = SP::RW, KG = SP::KG, NK = 2 / KG;
@@ -390,8 +395,6 @@ __global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW
   const int wave = wave_u % RW, kh = wave_u / RW;  // its 32 queries, and its 32 keys of a tile (KG = 2)
   const int part = kh + KG * grp;
   const int nqb = (a.s + BQ - 1) / BQ;
-  const AttnBlock blk = attn_block(nqb, a.hl, a.b);
-  if (!blk.valid) return;
   const int qb = nqb - 1 - blk.xb;
   const int hd = blk.hd, bi = blk.bi;
   const int ld = 3 * a.hl * D;
@@ -400,8 +403,9 @@ __global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW
   const int q0 = qb * BQ, qw0 = q0 + wave * 32, qi = qw0 + l32;
   const int qc = min(qi, a.s - 1);
 
+  const size_t vrow = ((size_t)bi * a.hl + hd) * a.s;           // of the [b, hl, s] vectors
   bf16x8 qf[D / 16], dof[D / 16];
-  float dl = 0.f;
+  float dl = MERGED ? a.delta[vrow + qc] : 0.f;
   {
     const bf16* qrow = base + (size_t)qc * ld + hd * D;
     const bf16* drow = (const bf16*)a.dctx + ((size_t)bi * a.s + qc) * (a.hl * D) + hd * D;
@@ -410,17 +414,18 @@ __global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW
     for (int ks = 0; ks < D / 16; ++ks) {
       qf[ks] = *reinterpret_cast<const bf16x8*>(qrow + ks * 16 + lh * 8);
       dof[ks] = *reinterpret_cast<const bf16x8*>(drow + ks * 16 + lh * 8);
+      if (MERGED) continue;
       const bf16x8 of = *reinterpret_cast<const bf16x8*>(orow + ks * 16 + lh * 8);
 #pragma unroll
       for (int e = 0; e < 8; ++e) dl = fmaf((float)dof[ks][e], (float)of[e], dl);
     }
-    dl += __shfl_xor(dl, 32, 64);
+    if (!MERGED) dl += __shfl_xor(dl, 32, 64);
   }
-  const float lse2 = a.lse[((size_t)bi * a.hl + hd) * a.s + qc] * kLog2e;
+  const float lse2 = a.lse[vrow + qc] * kLog2e;
   const uint32_t* kbrow = DROP ? a.keep_bits + (((size_t)bi * a.hl + hd) * a.s + qc) * a.keep_pitch : nullptr;
-  if (part == 0 && lh == 0 && qi < a.s) {          // for the dK/dV kernel: [0] delta, [1] log-sum-exp in log2 units
-    a.delta[((size_t)bi * a.hl + hd) * a.s + qi] = dl;
-    a.delta[(size_t)a.b * a.hl * a.s + ((size_t)bi * a.hl + hd) * a.s + qi] = lse2;
+  if (!MERGED && part == 0 && lh == 0 && qi < a.s) {   // for the dK/dV kernel: [0] delta, [1] log-sum-exp in log2 units
+    a.delta[vrow + qi] = dl;
+    a.delta[(size_t)a.b * a.hl * a.s + vrow + qi] = lse2;
   }
   floatx16 dq[D / 32];
 #pragma unroll
@@ -477,56 +482,66 @@ __global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW
     uint2 kw = make_uint2(0xFFFFFFFFu, 0xFFFFFFFFu);          // keep bits of this query row, this wave's keys
     if (DROP && KG == 1) kw = *reinterpret_cast<const uint2*>(kbrow + (k0 >> 5));
     if (DROP && KG == 2) kw.x = kbrow[kw0 >> 5];
-    floatx16 sacc[NK], pacc[NK];
+    // Head size 128 takes the tile's two 32-key halves one after the other: both at a time are 32 registers more than there are
+    // (8 .. 19 spilled ones).
+    constexpr int NHB = D == 128 && NK == 2 ? 2 : 1, NKB = NK / NHB;
 #pragma unroll
-    for (int kt = 0; kt < NK; ++kt)
+    for (int hb = 0; hb < NHB; ++hb) {
+      const int kh0 = kw0 + 32 * NKB * hb;           // first key of this part
+      if (NHB > 1 && (kh0 >= klen || (a.causal && kh0 > qw0 + 31))) continue;
+      floatx16 sacc[NKB], pacc[NKB];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) { sacc[kt][e] = 0.f; pacc[kt][e] = 0.f; }
-    // four independent accumulation chains, interleaved
+      for (int kt = 0; kt < NKB; ++kt)
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks)
+        for (int e = 0; e < 16; ++e) { sacc[kt][e] = 0.f; pacc[kt][e] = 0.f; }
+      // four (two) independent accumulation chains, interleaved
 #pragma unroll
-      for (int kt = 0; kt < NK; ++kt) {
-        sacc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_kc(sK, (KG == 2 ? kh : kt) * 32, ks, lane), qf[ks], sacc[kt], 0, 0, 0);   // S^T[key][query]
-        pacc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_kc(sV, (KG == 2 ? kh : kt) * 32, ks, lane), dof[ks], pacc[kt], 0, 0, 0);  // dP^T[key][query]
-      }
-    const bool need_mask = (a.causal && kw0 + 32 * NK - 1 > qw0) || (kw0 + 32 * NK > klen);   // wave-uniform
-    if (DROP) {
-      // gradient w.r.t. the undropped probability: keep o dP / (1 - p)
+      for (int ks = 0; ks < D / 16; ++ks)
 #pragma unroll
-      for (int kt = 0; kt < NK; ++kt) {
-        const uint32_t w = (kt == 0 ? kw.x : kw.y) >> (4 * lh);
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          pacc[kt][e] = ((w >> (8 * (e >> 2) + (e & 3))) & 1u) ? pacc[kt][e] * a.drop.scale : 0.f;
-      }
-    }
-    if (need_mask) {
-#pragma unroll
-      for (int kt = 0; kt < NK; ++kt)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int key = kw0 + kt * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
-          const bool off = key >= klen || (a.causal && key > qi);
-          const float p = off ? 0.f : __builtin_amdgcn_exp2f(fmaf(sacc[kt][e], sc, -lse2));
-          sacc[kt][e] = p * (pacc[kt][e] - dl);     // dS^T
-          if (SPREAD) copy_after(kt * 16 + e);
+        for (int kt = 0; kt < NKB; ++kt) {
+          const int r0 = (KG == 2 ? kh : hb * NKB + kt) * 32;
+          sacc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_kc(sK, r0, ks, lane), qf[ks], sacc[kt], 0, 0, 0);   // S^T[key][query]
+          pacc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_kc(sV, r0, ks, lane), dof[ks], pacc[kt], 0, 0, 0);  // dP^T[key][query]
         }
-    } else {
+      __builtin_amdgcn_sched_barrier(0);
+      const bool need_mask = (a.causal && kh0 + 32 * NKB - 1 > qw0) || (kh0 + 32 * NKB > klen);   // wave-uniform
+      if (DROP) {
+        // gradient w.r.t. the undropped probability: keep o dP / (1 - p)
 #pragma unroll
-      for (int kt = 0; kt < NK; ++kt)
+        for (int kt = 0; kt < NKB; ++kt) {
+          const uint32_t w = (hb * NKB + kt == 0 ? kw.x : kw.y) >> (4 * lh);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          sacc[kt][e] = __builtin_amdgcn_exp2f(fmaf(sacc[kt][e], sc, -lse2)) * (pacc[kt][e] - dl);
-          if (SPREAD) copy_after(kt * 16 + e);
+          for (int e = 0; e < 16; ++e)
+            pacc[kt][e] = ((w >> (8 * (e >> 2) + (e & 3))) & 1u) ? pacc[kt][e] * a.drop.scale : 0.f;
         }
-    }
+      }
+      if (need_mask) {
 #pragma unroll
-    for (int c = 0; c < 2 * NK; ++c) {
-      const bf16x8 dsf = pack8(sacc[c >> 1], 8 * (c & 1));
+        for (int kt = 0; kt < NKB; ++kt)
 #pragma unroll
-      for (int dt = 0; dt < D / 32; ++dt)
-        dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_tr(sK, (KG == 2 ? 2 * kh : 0) + c, dt * 32, lane), dsf, dq[dt], 0, 0, 0);   // dQ^T[dcol][query]
+          for (int e = 0; e < 16; ++e) {
+            const int key = kh0 + kt * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
+            const bool off = key >= klen || (a.causal && key > qi);
+            const float p = off ? 0.f : __builtin_amdgcn_exp2f(fmaf(sacc[kt][e], sc, -lse2));
+            sacc[kt][e] = p * (pacc[kt][e] - dl);     // dS^T
+            if (SPREAD) copy_after(kt * 16 + e);
+          }
+      } else {
+#pragma unroll
+        for (int kt = 0; kt < NKB; ++kt)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            sacc[kt][e] = __builtin_amdgcn_exp2f(fmaf(sacc[kt][e], sc, -lse2)) * (pacc[kt][e] - dl);
+            if (SPREAD) copy_after(kt * 16 + e);
+          }
+      }
+#pragma unroll
+      for (int c = 0; c < 2 * NKB; ++c) {
+        const bf16x8 dsf = pack8(sacc[c >> 1], 8 * (c & 1));
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt)
+          dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(TL::frag_tr(sK, (KG == 2 ? 2 * kh : 2 * NKB * hb) + c, dt * 32, lane), dsf, dq[dt], 0, 0, 0);   // dQ^T[dcol][query]
+      }
     }
   }
   wait_vmcnt<0>();
@@ -580,7 +595,7 @@ __global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW
 // two workgroups instead.
 // SPLIT: 64 keys per workgroup, and two waves of each group share a tile's 64 queries (attn_dkv_split: when).
 template <int D, bool DROP, bool SPLIT>
-__global__ __launch_bounds__(dkv_groups<D>() * ANT) void attn_bwd_dkv_bf16_kernel(AttnArgs a) {
+__device__ __forceinline__ void attn_bwd_dkv_block(const AttnArgs a, const AttnBlock blk) {
   typedef ATile<D> TL;
   constexpr int RW = SPLIT ? 2 : ANW, KG = ANW / RW, BKB = 32 * RW, VEC = 2 * ATILE * 4;          // VEC: bytes of the lse + delta vectors of a tile
   constexpr int KBB = DROP ? ATILE * 16 : 0;                  // keep bits of the tile: 64 queries x 128 keys
@@ -598,8 +613,6 @@ __global__ __launch_bounds__(dkv_groups<D>() * ANT) void attn_bwd_dkv_bf16_kerne
   const int grp = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);   // wave group: even / odd query tiles
   const int wave_u = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);       // wave inside its group (copies a quarter of a tile)
   const int wave = wave_u % RW, qh = wave_u / RW;  // its 32 keys, and its 32 queries of a tile (KG = 2)
-  const AttnBlock blk = attn_block(((a.s + BKB - 1) / BKB) * DS, a.hl, a.b);
-  if (!blk.valid) return;
   const int kb = blk.xb / DS;                      // key block; for causal, block 0 has the most queries: first
   const int dh0 = (blk.xb % DS) * DH;              // first of this workgroup's dK / dV columns
   const int hd = blk.hd, bi = blk.bi;
@@ -713,20 +726,26 @@ __global__ __launch_bounds__(dkv_groups<D>() * ANT) void attn_bwd_dkv_bf16_kerne
         const float4 d4 = *reinterpret_cast<const float4*>(sDl + qoff);
         const float lv4[4] = {l4.x, l4.y, l4.z, l4.w};
         const float dv4[4] = {d4.x, d4.y, d4.z, d4.w};
+        float p[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[e] = __builtin_amdgcn_exp2f(fmaf(sacc[4 * g + e], sc, -lv4[e]));
+        if (need_mask) {
+          asm volatile("");                            // (stays a scalar branch: without it every tile pays for the selects)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int q = q0 + qoff + e;
+            p[e] = (kj >= klen || q >= a.s || (a.causal && kj > q)) ? 0.f : p[e];
+          }
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          float p = __builtin_amdgcn_exp2f(fmaf(sacc[4 * g + e], sc, -lv4[e]));
-          if (need_mask) {
-            const int q = q0 + qoff + e;
-            p = (kj >= klen || q >= a.s || (a.causal && kj > q)) ? 0.f : p;
-          }
           if (DROP) {
             const bool keep = (sBits[(qoff + e) * 4 + (SPLIT ? (kb0 >> 5) & 3 : 0) + wave] >> l32) & 1u;
-            sacc[4 * g + e] = keep ? p * a.drop.scale : 0.f;                                       // dropped P (for dV)
-            pacc[4 * g + e] = p * ((keep ? pacc[4 * g + e] * a.drop.scale : 0.f) - dv4[e]);        // dS
+            sacc[4 * g + e] = keep ? p[e] * a.drop.scale : 0.f;                                       // dropped P (for dV)
+            pacc[4 * g + e] = p[e] * ((keep ? pacc[4 * g + e] * a.drop.scale : 0.f) - dv4[e]);        // dS
           } else {
-            sacc[4 * g + e] = p;                                // P
-            pacc[4 * g + e] = p * (pacc[4 * g + e] - dv4[e]);   // dS
+            sacc[4 * g + e] = p[e];                                // P
+            pacc[4 * g + e] = p[e] * (pacc[4 * g + e] - dv4[e]);   // dS
           }
         }
       }
@@ -792,6 +811,74 @@ __global__ __launch_bounds__(dkv_groups<D>() * ANT) void attn_bwd_dkv_bf16_kerne
   }
 }
 
+// The two as kernels of their own (attn_bwd_mode: when).
+template <int D, bool DROP, int MODE>
+__global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW)) void attn_bwd_dq_bf16_kernel(AttnArgs a) {
+  constexpr int BQ = 32 * AttnSplit<D, MODE>::RW;
+  const AttnBlock blk = attn_block((a.s + BQ - 1) / BQ, a.hl, a.b);
+  if (blk.valid) attn_bwd_dq_block<D, DROP, MODE, false>(a, blk);
+}
+template <int D, bool DROP, bool SPLIT>
+__global__ __launch_bounds__(dkv_groups<D>() * ANT) void attn_bwd_dkv_bf16_kernel(AttnArgs a) {
+  constexpr int BKB = SPLIT ? 64 : 128;
+  const AttnBlock blk = attn_block((a.s + BKB - 1) / BKB * dkv_dsplit<D>(), a.hl, a.b);
+  if (blk.valid) attn_bwd_dkv_block<D, DROP, SPLIT>(a, blk);
+}
+
+// ------------------------------------------------------------------------------------------ backward in one launch
+// dQ and dK/dV blocks in one grid.  Under a causal mask the blocks of either kernel differ by up to 16 x at 2048 tokens, and with
+// about one workgroup per compute unit the longest is the kernel's time while the others idle; together, the longest of both
+// kinds first, the short blocks of one fill up behind the long ones of the other.  Without a mask, two kinds that leave compute
+// units idle share them.  dK/dV then cannot wait for dQ's delta: it comes from a small kernel ahead of both.
+// Order on an XCD: groups of `pg` pairs (whose K, V, Q and dO rows its L2 holds), in a group the blocks of rank 0 of all pairs,
+// of rank 1, .., the two kinds spread evenly over the ranks.
+struct AttnJoint { int nq, nk, pg; };      // dQ and dK/dV blocks of a pair, pairs of a group
+
+template <int D, bool DROP, int MODE, bool SPLIT>
+__global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW)) void attn_bwd_bf16_kernel(AttnArgs a, AttnJoint jt) {
+  static_assert(AttnSplit<D, MODE>::NT == dkv_groups<D>() * ANT, "both kinds of block have the same number of waves");
+  const int pairs = a.hl * a.b, npx = (pairs + 7) / 8, per = jt.nq + jt.nk;
+  int r = blockIdx.x >> 3;
+  const int g = r / (jt.pg * per);
+  r -= g * jt.pg * per;
+  const int size = min(jt.pg, npx - g * jt.pg);               // (the last group may be smaller)
+  const int rank = r / size, pair = (g * jt.pg + r - rank * size) * 8 + (blockIdx.x & 7);
+  if (pair >= pairs) return;
+  const int before = rank * jt.nq / per;                       // dQ blocks among the ranks below
+  const bool is_dq = (rank + 1) * jt.nq / per > before;
+  AttnBlock blk;
+  blk.xb = is_dq ? before : rank - before;
+  blk.hd = pair % a.hl;
+  blk.bi = pair / a.hl;
+  blk.valid = true;
+  if (is_dq) attn_bwd_dq_block<D, DROP, MODE, true>(a, blk);
+  else attn_bwd_dkv_block<D, DROP, SPLIT>(a, blk);
+}
+
+// delta = rowsum(dO o O), and the log-sum-exp in log2 units: four lanes per (batch, head, query), 16-byte loads.  Bound by the
+// launch (3 us up to 8192 x 384).
+template <int D>
+__global__ __launch_bounds__(256) void attn_delta_bf16_kernel(AttnArgs a) {
+  const size_t rows = (size_t)a.b * a.hl * a.s, r = ((size_t)blockIdx.x * 256 + threadIdx.x) >> 2;
+  if (r >= rows) return;                                       // whole groups of four lanes
+  const int i = r % a.s, hd = r / a.s % a.hl, bi = r / a.s / a.hl, c = threadIdx.x & 3;
+  const size_t at = ((size_t)bi * a.s + i) * (a.hl * D) + hd * D;
+  float dl = 0.f;
+#pragma unroll
+  for (int u = 0; u < D / 32; ++u) {
+    const bf16x8 d = *reinterpret_cast<const bf16x8*>((const bf16*)a.dctx + at + 32 * u + 8 * c);
+    const bf16x8 o = *reinterpret_cast<const bf16x8*>((const bf16*)a.ctx + at + 32 * u + 8 * c);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) dl = fmaf((float)d[e], (float)o[e], dl);
+  }
+  dl += __shfl_xor(dl, 1, 64);
+  dl += __shfl_xor(dl, 2, 64);
+  if (c == 0) {
+    a.delta[r] = dl;
+    a.delta[rows + r] = a.lse[r] * kLog2e;
+  }
+}
+
 // ------------------------------------------------------------------------------------------ launchers
 bool attn_bf16_supported(int d) { return d == 64 || d == 96 || d == 128 || d == 192; }
 
@@ -806,6 +893,51 @@ static hipError_t launch_fwd_m(const AttnArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int D, bool DROP>
+static hipError_t launch_fwd_dd(const AttnArgs& a, hipStream_t st) {
+  const AttnMode m = attn_mode(a.s, a.hl * a.b, a.causal != 0, D);
+  if constexpr (D <= 128)
+    if (m == ATTN_PAIR) return launch_fwd_m<D, DROP, ATTN_PAIR>(a, st);
+  return m == ATTN_SPLIT ? launch_fwd_m<D, DROP, ATTN_SPLIT>(a, st) : launch_fwd_m<D, DROP, ATTN_WIDE>(a, st);
+}
+
+template <int D>
+static hipError_t launch_fwd_d(const AttnArgs& a, hipStream_t st) {
+  return a.drop.enabled ? launch_fwd_dd<D, true>(a, st) : launch_fwd_dd<D, false>(a, st);
+}
+
+// LDS of a dK/dV block: rings and the owned K / V rows (two groups); at the end the parked accumulators.
+template <int D, bool DROP, bool SPLIT> constexpr size_t dkv_lds_bytes() {
+  constexpr int RW = SPLIT ? 2 : ANW, NG = dkv_groups<D>(), G = NG * ANW / RW;
+  constexpr size_t kStage = 2 * ATile<D>::BYTES + 2 * ATILE * 4 + (DROP ? ATILE * 16 : 0);
+  constexpr size_t kOwn = (NG == 2 && dkv_own_lds<D>()) ? RW * ATile<D>::BYTES : 0;
+  constexpr size_t kRing = (size_t)NG * dkv_stages<D>() * kStage + kOwn;
+  constexpr size_t kPark = (size_t)(G - 1) * RW * 2 * (D / dkv_dsplit<D>() / 32) * 16 * 64 * 4;
+  return kRing > kPark ? kRing : kPark;
+}
+
+template <int D, bool DROP, int MODE, bool SPLIT>
+static hipError_t launch_bwd_joint(const AttnArgs& a, hipStream_t st) {
+  typedef AttnSplit<D, MODE> SP;
+  auto kern = attn_bwd_bf16_kernel<D, DROP, MODE, SPLIT>;
+  constexpr size_t kDkv = dkv_lds_bytes<D, DROP, SPLIT>(), kLds = SP::LDS > kDkv ? SP::LDS : kDkv;
+  static_assert(kLds <= 160 * 1024, "LDS budget");
+  static LdsAttrOnce attr;
+  if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
+  const size_t rows = (size_t)a.b * a.hl * a.s;
+  hipLaunchKernelGGL((attn_delta_bf16_kernel<D>), dim3((unsigned)((rows + 63) / 64)), dim3(256), 0, st, a);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  constexpr int BKB = SPLIT ? 64 : 128;
+  AttnJoint jt;
+  jt.nq = (a.s + 32 * SP::RW - 1) / (32 * SP::RW);
+  jt.nk = (a.s + BKB - 1) / BKB * dkv_dsplit<D>();
+  const int npx = (a.hl * a.b + 7) / 8, per = jt.nq + jt.nk;
+  jt.pg = (2 * (gemm_cu_count() / 8) + per - 1) / per;         // two workgroups per compute unit of the XCD to choose from
+  if (jt.pg > npx) jt.pg = npx;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(8 * npx * per)), dim3(SP::NT), kLds, st, a, jt);
+  return hipGetLastError();
+}
+
 template <int D, bool DROP, int MODE>
 static hipError_t launch_dq_m(const AttnArgs& a, hipStream_t st) {
   typedef AttnSplit<D, MODE> SP;
@@ -817,51 +949,37 @@ static hipError_t launch_dq_m(const AttnArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int D, bool DROP>
-static hipError_t launch_fwd_dd(const AttnArgs& a, hipStream_t st) {
-  const AttnMode m = attn_mode(a.s, a.hl * a.b, a.causal != 0, D);
-  if constexpr (D <= 128)
-    if (m == ATTN_PAIR) return launch_fwd_m<D, DROP, ATTN_PAIR>(a, st);
-  return m == ATTN_SPLIT ? launch_fwd_m<D, DROP, ATTN_SPLIT>(a, st) : launch_fwd_m<D, DROP, ATTN_WIDE>(a, st);
-}
-
-template <int D, bool DROP>
-static hipError_t launch_dq_dd(const AttnArgs& a, hipStream_t st) {
-  const AttnMode m = attn_mode(a.s, a.hl * a.b, a.causal != 0, D);
-  if constexpr (D <= 128)
-    if (m == ATTN_PAIR) return launch_dq_m<D, DROP, ATTN_PAIR>(a, st);
-  return m == ATTN_SPLIT ? launch_dq_m<D, DROP, ATTN_SPLIT>(a, st) : launch_dq_m<D, DROP, ATTN_WIDE>(a, st);
-}
-
-template <int D>
-static hipError_t launch_fwd_d(const AttnArgs& a, hipStream_t st) {
-  return a.drop.enabled ? launch_fwd_dd<D, true>(a, st) : launch_fwd_dd<D, false>(a, st);
-}
-
 template <int D, bool DROP, bool SPLIT>
 static hipError_t launch_dkv(const AttnArgs& a, hipStream_t st) {
-  constexpr int RW = SPLIT ? 2 : ANW, NG = dkv_groups<D>(), G = NG * ANW / RW;
-  constexpr size_t kStage = 2 * ATile<D>::BYTES + 2 * ATILE * 4 + (DROP ? ATILE * 16 : 0);
-  // rings and the owned K / V rows (two groups); at the end the parked accumulators
-  constexpr size_t kOwn = (NG == 2 && dkv_own_lds<D>()) ? RW * ATile<D>::BYTES : 0;
-  constexpr size_t kRing = (size_t)NG * dkv_stages<D>() * kStage + kOwn;
-  constexpr size_t kPark = (size_t)(G - 1) * RW * 2 * (D / dkv_dsplit<D>() / 32) * 16 * 64 * 4;
-  constexpr size_t kLds = kRing > kPark ? kRing : kPark;
+  constexpr int BKB = SPLIT ? 64 : 128;
+  constexpr size_t kLds = dkv_lds_bytes<D, DROP, SPLIT>();
   static_assert(kLds <= 160 * 1024, "LDS budget");
   static LdsAttrOnce attr;
   if (kLds > 64 * 1024)
     if (hipError_t e = attr.ensure((const void*)attn_bwd_dkv_bf16_kernel<D, DROP, SPLIT>, (int)kLds); e != hipSuccess) return e;
-  const dim3 grid = attn_grid((a.s + 32 * RW - 1) / (32 * RW) * dkv_dsplit<D>(), a.hl, a.b);
-  hipLaunchKernelGGL((attn_bwd_dkv_bf16_kernel<D, DROP, SPLIT>), grid, dim3(NG * ANT), kLds, st, a);
+  const dim3 grid = attn_grid((a.s + BKB - 1) / BKB * dkv_dsplit<D>(), a.hl, a.b);
+  hipLaunchKernelGGL((attn_bwd_dkv_bf16_kernel<D, DROP, SPLIT>), grid, dim3(dkv_groups<D>() * ANT), kLds, st, a);
   return hipGetLastError();
 }
 
 template <int D, bool DROP>
 static hipError_t launch_bwd_dd(const AttnArgs& a, hipStream_t st) {
-  if (hipError_t e = launch_dq_dd<D, DROP>(a, st); e != hipSuccess) return e;
-  if constexpr (D <= 128)
-    if (attn_dkv_split(a.s, a.hl * a.b, a.causal != 0, D, dkv_dsplit<D>())) return launch_dkv<D, DROP, true>(a, st);
-  return launch_dkv<D, DROP, false>(a, st);
+  const int pairs = a.hl * a.b;
+  const bool causal = a.causal != 0;
+  if constexpr (D > 128) {
+    return launch_bwd_joint<D, DROP, ATTN_WIDE, false>(a, st);
+  } else {
+    const AttnBwdMode bm = attn_bwd_mode(a.s, pairs, causal, D, dkv_dsplit<D>());
+    if (bm == ATTN_BWD_JOINT) return launch_bwd_joint<D, DROP, ATTN_PAIR, false>(a, st);
+    if (bm == ATTN_BWD_JOINT_SPLIT) return launch_bwd_joint<D, DROP, ATTN_SPLIT, true>(a, st);
+    const AttnMode m = attn_mode(a.s, pairs, causal, D);
+    hipError_t e = m == ATTN_PAIR    ? launch_dq_m<D, DROP, ATTN_PAIR>(a, st)
+                   : m == ATTN_SPLIT ? launch_dq_m<D, DROP, ATTN_SPLIT>(a, st)
+                                     : launch_dq_m<D, DROP, ATTN_WIDE>(a, st);
+    if (e != hipSuccess) return e;
+    return attn_dkv_split(a.s, pairs, causal, D, dkv_dsplit<D>()) ? launch_dkv<D, DROP, true>(a, st)
+                                                                   : launch_dkv<D, DROP, false>(a, st);
+  }
 }
 
 template <int D>

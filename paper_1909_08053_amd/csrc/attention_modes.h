@@ -41,4 +41,24 @@ inline bool attn_dkv_split(int s, int pairs, bool causal, int d, int parts) {
   return 2 * wgs <= cus && 2 * xcd_wgs <= (causal ? 2 : 1) * (cus / 8);
 }
 
+// Backward: dQ and dK / dV as two launches (divided as above), or in one (attn_bwd_bf16_kernel), in 128-row workgroups or 64-row
+// ones.  `parts` workgroups share a dK / dV block.  Of the busiest XCD's share of the 128-row workgroups of one kind, xcd_wgs:
+//   64 rows while both kinds then find a compute unit each (and an eighth more); causal, d <= 96, from 6 blocks a sequence on, up
+//   to two workgroups per unit: d = 96 1024 x 16 pairs 77 -> 70 us with the call's GEMMs, in 128 rows 72; 512 x 24 in 64 rows 53.3, 128 51.9.
+//   Causal: 128 rows, however many, since the short blocks fill up behind the long ones: d = 96 1024 x 32 pairs 82 -> 71, 1024 x
+//   64 153 -> 135, 2048 x 16 115 -> 92, 768 x 96 145 -> 140.  But not two pairs an XCD of more than one and a half blocks per
+//   unit: 4096 x 12 246 -> 255.
+//   No mask: only while the workgroups leave units idle, three quarters: d = 96 768 x 12 62 -> 56, but 2048 x 6 90 -> 98.
+//   d = 192: always (its blocks take a compute unit each): 1024 x 16 causal 188 -> 118, 2048 x 48 full 1616 -> 1211; 128 rows
+//   against 64 equal up to 8 an XCD, above 262 / 316 (1024 x 48).
+enum AttnBwdMode { ATTN_BWD_TWO, ATTN_BWD_JOINT, ATTN_BWD_JOINT_SPLIT };
+inline AttnBwdMode attn_bwd_mode(int s, int pairs, bool causal, int d, int parts) {
+  if (d > 128) return ATTN_BWD_JOINT;
+  const long xcd_cus = gemm_cu_count() / 8, blocks = (s + 127) / 128, xcd_pairs = (pairs + 7) / 8, xcd_wgs = xcd_pairs * blocks;
+  if (2 * (1 + parts) * xcd_wgs <= xcd_cus + xcd_cus / 8) return ATTN_BWD_JOINT_SPLIT;
+  if (!causal) return 4 * (1 + parts) * xcd_wgs <= 3 * xcd_cus ? ATTN_BWD_JOINT : ATTN_BWD_TWO;
+  if (parts == 1 && blocks >= 6 && 2 * xcd_wgs <= xcd_cus) return ATTN_BWD_JOINT_SPLIT;
+  return xcd_pairs <= 2 && 2 * xcd_wgs > 3 * xcd_cus ? ATTN_BWD_TWO : ATTN_BWD_JOINT;
+}
+
 }  // namespace mlm
