@@ -113,6 +113,11 @@ GemmArgs gemm_wgrad(int M, int N, int K, const void* X, const void* dY, void* dW
   return gemm_args(M, N, K, X, M, 0, dY, N, 0, dW, N);
 }
 
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return x < y + nb && y < x + na;
+}
+
 #define MLM_TRY_HIP(expr)                    \
   do {                                       \
     hipError_t e_ = (expr);                  \
@@ -676,8 +681,15 @@ MLM_API int mlm_vocab_ce_shard_bwd(const mlm_dims* dims, const void* hf, const v
     g.Mrow = M; g.Srow = S; g.loss_w = loss_w; g.loss_stats = loss_stats;
     MLM_TRY_HIP(run_gemm(dt, g, st, sk));
   }
-  MLM_TRY_HIP(run_gemm(dt, gemm_wgrad(dims->H, L.Vl, L.T, hf, dL, dE_r), st, sk));
-  MLM_TRY_HIP(run_gemm(dt, gemm_dgrad(L.T, dims->H, L.Vl, dL, E_r, dhf_partial_r), st, sk));
+  const GemmArgs gE = gemm_wgrad(dims->H, L.Vl, L.T, hf, dL, dE_r), gH = gemm_dgrad(L.T, dims->H, L.Vl, dL, E_r, dhf_partial_r);
+  // one launch for both, unless the caller's buffers make their order visible (dhf over hf)
+  const size_t bE = (size_t)dims->H * L.Vl * L.esz, bH = (size_t)L.T * dims->H * L.esz, bL = (size_t)L.T * L.Vl * L.esz;
+  const bool apart = overlap(dE_r, bE, dhf_partial_r, bH) || overlap(dE_r, bE, E_r, bE) || overlap(dE_r, bE, hf, bH) ||
+                     overlap(dE_r, bE, dL, bL) || overlap(dhf_partial_r, bH, E_r, bE) || overlap(dhf_partial_r, bH, hf, bH) ||
+                     overlap(dhf_partial_r, bH, dL, bL);
+  if (dt == MLM_BF16 && !apart) return hip_status(launch_gemm_bf16_dual(gE, gH, sk, st));
+  MLM_TRY_HIP(run_gemm(dt, gE, st, sk));
+  MLM_TRY_HIP(run_gemm(dt, gH, st, sk));
   return MLM_OK;
 }
 

@@ -169,6 +169,10 @@ hipError_t launch_gemm_f32_wgrads(const GemmArgs* probs, int n, hipStream_t st);
 // n weight-gradient GEMMs (A m-contiguous, B n-contiguous, plain store) in one launch where that is faster
 hipError_t launch_gemm_bf16_wgrad_group(const GemmArgs* probs, int n, float* splitk_ws, hipStream_t st);
 
+// A weight gradient a0 and an input gradient a1 (plain stores) that do not depend on each other, in one launch where that is
+// faster; no output may overlap an input or the other output.
+hipError_t launch_gemm_bf16_dual(const GemmArgs& a0, const GemmArgs& a1, float* splitk_ws, hipStream_t st);
+
 // ---- dropout site as the kernels see it (rng.h holds the generator) ---------------
 struct DropArgs {
   uint32_t k0, k1;          // key: the stream seed

@@ -14,6 +14,11 @@ int gemm_v2_forced_bn() {
   return forced;
 }
 
+bool gemm_v2_group_off() {
+  static const bool off = [] { const char* e = getenv("MLM_GEMM_GROUP"); return e && atoi(e) == 0; }();
+  return off;
+}
+
 // Compute units of the current device, capped at the tail-split workspace's bound; one query per device.
 int gemm_cu_count() {
   constexpr int kMaxDevices = 64, kCap = 256;

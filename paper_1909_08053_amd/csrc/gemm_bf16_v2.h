@@ -766,6 +766,7 @@ hipError_t launch_gemm_bf16_v2_group(const GemmArgs* probs, int n, hipStream_t s
   }
 }
 
+bool gemm_v2_group_off();                   // MLM_GEMM_GROUP=0: every GEMM in a launch of its own
 int gemm_v2_forced_bn();                    // MLM_GEMM_BN=128|192|256 forces a tile width where it exists, else 0
 
 // The 192-wide tile exists for all but the cross-entropy epilogues, the small tile for every epilogue but the one that
@@ -810,6 +811,61 @@ hipError_t launch_gemm_bf16_v2(const GemmArgs& a, float* splitk_ws, hipStream_t 
                  ? launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_SMALL, true>(a, splitk_ws, st)
                  : launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_SMALL>(a, splitk_ws, st);
   return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_B>(a, splitk_ws, st);
+}
+
+// End of `units` units working through n0 items of c0 and then n1 of c1 (microseconds), each taking the next item when it is done.
+inline double v2_two_batches(int units, int n0, double c0, int n1, double c1) {
+  const double t0 = (double)(n0 / units) * c0;
+  const int busy = n0 % units;                        // units that are done with the first batch c0 later than the others
+  double lo = busy ? t0 + c0 : t0, hi = t0 + c0 + c1 * (n1 / units + 2);
+  auto done = [&](double t) {
+    const double late = t - t0 - c0;
+    return (double)(units - busy) * (long)((t - t0) / c1 + 1e-6) + (late > 0 ? (double)busy * (long)(late / c1 + 1e-6) : 0.0) >= n1;
+  };
+  if (done(lo)) return lo;
+  for (int i = 0; i < 24; ++i) {
+    const double mid = 0.5 * (lo + hi);
+    if (done(mid)) hi = mid; else lo = mid;
+  }
+  return hi;
+}
+
+// How a weight gradient a0 and an input gradient a1 that do not depend on each other are launched: together in tiles of bn
+// (first_is_1: a1's tiles, the longer ones, lead), or apart (bn = 0).  Measured apart / together, the pass that forms dL included:
+// 8192 tokens x 3072 x 6400 533 / 490 us, 8192 x 1536 x 51200 2300 / 2155, 3008 x 3072 x 12800 420 / 345, 1536 x 3072 x 2048
+// 54.5 / 46.8, 6144 x 2560 x 3072 159 / 144; small tiles 320 x 1920 x 1000 24.1 / 15.4, 704 x 384 x 512 17.7 / 14.2.  Where either
+// alone fills three quarters of the units it gains nothing: 3008 x 3072 x 4096 131 / 138, 4096 x 1920 x 6400 178 / 183.
+struct V2Dual { int bn; bool first_is_1; };
+inline V2Dual v2_dual(const GemmArgs& a0, const GemmArgs& a1) {
+  V2Dual d = {0, v2_slices(a1.K) > v2_slices(a0.K)};
+  if (gemm_v2_forced_bn() || gemm_v2_group_off()) return d;
+  const int cus = gemm_cu_count(), nk0 = v2_slices(a0.K), nk1 = v2_slices(a1.K);
+  // + launch and drain.  Busy compute units clock higher while others idle, so an unsplit last round costs less than its tiles
+  // do in full ones (192 large tiles 0.89); the narrow tile falls behind at very long k (1600 slices: 1105 us, not 952).
+  auto alone = [&](const GemmArgs& a, int bn) {
+    const V2Plan p = v2_plan(a.M, a.N, a.K, true, bn);
+    const int nk = v2_slices(a.K), tiles = p.tiles_m * p.tiles_n, rem = tiles % cus;
+    double c = p.cost + 2.0;
+    if (bn != V2_SMALL && p.split == 1 && rem) c -= 0.45 * (1.0 - (double)rem / cus) * v2_tile_cost(bn, nk, false, 0.0);
+    if (bn == 192 && nk > 1024) c += 0.06 * nk * ((tiles + cus - 1) / cus);
+    return c;
+  };
+  double best = 0.98 * (alone(a0, v2_pick_bn<false, false, EPI_STORE>(a0.M, a0.N, a0.K, true)) +
+                        alone(a1, v2_pick_bn<true, true, EPI_STORE>(a1.M, a1.N, a1.K, true)));
+  auto price = [&](int bn, bool one_each) {
+    const int bm = bn == V2_SMALL ? V2_SMALL : V2_B;
+    const int n0 = ((a0.M + bm - 1) / bm) * ((a0.N + bn - 1) / bn), n1 = ((a1.M + bm - 1) / bm) * ((a1.N + bn - 1) / bn);
+    if (one_each && n0 + n1 > cus) return 1e30;
+    const double c0 = v2_tile_cost(bn, nk0, one_each, 0.46), c1 = v2_tile_cost(bn, nk1, one_each, 0.46);
+    return 2.0 + (d.first_is_1 ? v2_two_batches(cus, n1, c1, n0, c0) : v2_two_batches(cus, n0, c0, n1, c1));
+  };
+  if (a0.K % (2 * V2_BK) == 0 && a1.K % V2_BK == 0 && a1.K >= 2 * V2_BK) {
+    const double t = price(V2_B, false);
+    if (t < best) { best = t; d.bn = V2_B; }
+  }
+  const double t = price(V2_SMALL, true);
+  if (t < best) d.bn = V2_SMALL;
+  return d;
 }
 
 // One translation unit per operand layout (keeps compile times parallel).

@@ -1,6 +1,5 @@
 // bf16 GEMM instantiations for the weight-gradient layout dW = X^T dY: A(m,k) = X[k,m] (m-contiguous) and
 // B(k,n) = dY[k,n] (n-contiguous); k runs over tokens.
-#include <stdlib.h>
 #include "gemm_bf16_v2.h"
 
 namespace mlm {
@@ -25,8 +24,7 @@ hipError_t launch_gemm_bf16_wgrad_group(const GemmArgs* probs, int n, float* spl
     const double big = v2_group_cost(probs, n, V2_B), small = v2_group_cost(probs, n, V2_SMALL);
     const int forced = gemm_v2_forced_bn();
     const bool use_small = forced ? forced == V2_SMALL : small < big;
-    static const bool off = [] { const char* e = getenv("MLM_GEMM_GROUP"); return e && atoi(e) == 0; }();
-    if (!off && (use_small ? small : big) + 2.0 < alone) {
+    if (!gemm_v2_group_off() && (use_small ? small : big) + 2.0 < alone) {
       int tiles = 0;
       for (int q = 0; q < n; ++q) tiles += v2_tiles(probs[q], V2_SMALL, V2_SMALL);
       if (!use_small) return launch_gemm_bf16_v2_group<false, false, V2_B, false>(probs, n, st);
