@@ -18,15 +18,26 @@ MLM_F32, MLM_BF16 = 0, 1
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libmlm_shard.so")
 
-EXPORTS = ("mlm_shard_range", "mlm_workspace_bytes", "mlm_status_string", "mlm_layernorm_fwd", "mlm_layernorm_bwd",
-           "mlm_combine", "mlm_combine_layernorm_fwd", "mlm_combine_layernorm_bwd", "mlm_colsum", "mlm_attn_shard_fwd", "mlm_attn_shard_bwd", "mlm_mlp_shard_fwd",
-           "mlm_mlp_shard_bwd", "mlm_vocab_ce_shard_fwd", "mlm_vocab_ce_merge", "mlm_vocab_ce_shard_bwd", "mlm_gemm", "mlm_grad_sqnorm",
-           "mlm_adamw_step", "mlm_adamw_step_multi", "mlm_rng_stream_seed", "mlm_combine_dropout",
-           "mlm_combine_layernorm_fwd_dropout", "mlm_combine_layernorm_bwd_dropout", "mlm_attn_keep_words",
-           "mlm_attn_shard_fwd_dropout", "mlm_attn_shard_bwd_dropout", "mlm_embed_shard_fwd", "mlm_embed_bwd_replicated",
-           "mlm_embed_shard_bwd", "mlm_rows_gather", "mlm_rows_scatter", "mlm_mlp_shard_bwd_input",
-           "mlm_attn_shard_bwd_input", "mlm_layer_shard_wgrads", "mlm_colsum_noalloc", "mlm_deferred_sums_bytes",
-           "mlm_deferred_sums_begin", "mlm_deferred_sums_flush")
+# Argument types, one letter each: P pointer, i int32, l int64, u uint64, z size_t, f float.  They are declared once, so that
+# a call passes plain integers: wrapping every argument in a ctypes object and asking torch.cuda for the stream object was a
+# third of a step's host time (46 launches: 253-309 -> 194 us a step, and more than the GPU's 246 in bf16 at 400 tokens x 192).
+_SIGNATURES = dict(item.split("=") for item in """
+mlm_shard_range=liiPP mlm_workspace_bytes=PiP mlm_status_string=i mlm_layernorm_fwd=PPPPPPPP
+mlm_layernorm_bwd=PPPPPPPPPPPzP mlm_combine=PPiPPPP mlm_combine_layernorm_fwd=PPiPPPPPPPPP
+mlm_combine_layernorm_bwd=PPiPPPPPPPPPPPzP mlm_colsum=PPPPzP mlm_colsum_noalloc=PPPP mlm_deferred_sums_bytes=PP
+mlm_deferred_sums_begin=Pz mlm_deferred_sums_flush=P mlm_attn_shard_fwd=PPPPPPPPPPPzP mlm_attn_shard_bwd=PPPPPPPPPPPPPPzP
+mlm_mlp_shard_fwd=PPPPPPPPPzP mlm_mlp_shard_bwd=PPPPPPPPPPPPzP mlm_vocab_ce_shard_fwd=PPPPPPPPPzP
+mlm_vocab_ce_merge=PPPPiPPPPPP mlm_vocab_ce_shard_bwd=PPPPPPPPPPPPzP mlm_gemm=iiilllPPPPP mlm_grad_sqnorm=iPPiPPPzP
+mlm_adamw_step=ilPPPPPPffffffiP mlm_adamw_step_multi=iiPPPPPPPPfffffiP mlm_rng_stream_seed=uiiP
+mlm_combine_dropout=PPiPiPPPP mlm_combine_layernorm_fwd_dropout=PPiPPPPPPPPPP
+mlm_combine_layernorm_bwd_dropout=PPiPPPPPPPPPPPPPzP mlm_attn_keep_words=PP mlm_attn_shard_fwd_dropout=PPPPPPPPPPPPPzP
+mlm_attn_shard_bwd_dropout=PPPPPPPPPPPPPPPPzP mlm_embed_shard_fwd=PPPPPP mlm_embed_bwd_replicated=PPPPPP
+mlm_embed_shard_bwd=PPPPPP mlm_rows_gather=PPPiiPP mlm_rows_scatter=PPPiPP mlm_mlp_shard_bwd_input=PPPPPPPPPzP
+mlm_attn_shard_bwd_input=PPPPPPPPPPPPPPzP mlm_layer_shard_wgrads=PPPPPPPPPPPPPPzP
+""".split())
+EXPORTS = tuple(_SIGNATURES)
+_CTYPES = {"P": ctypes.c_void_p, "i": ctypes.c_int32, "l": ctypes.c_int64, "u": ctypes.c_uint64, "z": ctypes.c_size_t,
+           "f": ctypes.c_float}
 STREAM_REPLICATED, STREAM_MODEL_PARALLEL = 0, 1
 
 
@@ -53,7 +64,7 @@ def make_dropout(p: float, seed: int, offset: int) -> Dropout:
 
 
 def _d(drop: Optional[Dropout]):
-    return ctypes.byref(drop) if drop is not None else ctypes.c_void_p(0)
+    return ctypes.byref(drop) if drop is not None else None
 
 
 _lib = None
@@ -66,11 +77,10 @@ def lib() -> ctypes.CDLL:
             raise RuntimeError(f"{LIB_PATH} is not built; run `python -m paper_1909_08053_amd.build` "
                                "(there is no fallback path)")
         L = ctypes.CDLL(LIB_PATH)
-        L.mlm_status_string.restype = ctypes.c_char_p
-        L.mlm_status_string.argtypes = [ctypes.c_int]
-        for name in EXPORTS:
-            if name != "mlm_status_string":
-                getattr(L, name).restype = ctypes.c_int
+        for name, sig in _SIGNATURES.items():
+            f = getattr(L, name)
+            f.argtypes = [_CTYPES[c] for c in sig]
+            f.restype = ctypes.c_char_p if name == "mlm_status_string" else ctypes.c_int
         _lib = L
     return _lib
 
@@ -86,22 +96,24 @@ def make_dims(b, s, H, h, F, V, p, r, dtype, causal=True, gelu_tanh=True, ln_eps
 
 def _p(t: Optional[torch.Tensor]):
     if t is None:
-        return ctypes.c_void_p(0)
+        return None
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError("expected a contiguous CUDA tensor")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _st(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream().cuda_stream
-    return ctypes.c_void_p(int(stream))
+    if stream is not None:
+        return int(stream)
+    if torch.cuda.is_initialized():        # the raw handle of torch.cuda.current_stream(), without building the object
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _ws(ws: Optional[torch.Tensor]):
     if ws is None:
-        return ctypes.c_void_p(0), ctypes.c_size_t(0)
-    return _p(ws), ctypes.c_size_t(ws.numel() * ws.element_size())
+        return None, 0
+    return _p(ws), ws.numel() * ws.element_size()
 
 
 def _chk(rc: int, where: str):
@@ -111,14 +123,14 @@ def _chk(rc: int, where: str):
 
 def mlm_shard_range(n: int, p: int, r: int):
     b, e = ctypes.c_int64(0), ctypes.c_int64(0)
-    _chk(lib().mlm_shard_range(ctypes.c_int64(n), ctypes.c_int32(p), ctypes.c_int32(r), ctypes.byref(b),
+    _chk(lib().mlm_shard_range(n, p, r, ctypes.byref(b),
                                ctypes.byref(e)), "mlm_shard_range")
     return b.value, e.value
 
 
 def mlm_workspace_bytes(dims: Dims, which: int) -> int:
     n = ctypes.c_size_t(0)
-    _chk(lib().mlm_workspace_bytes(ctypes.byref(dims), ctypes.c_int32(which), ctypes.byref(n)), "mlm_workspace_bytes")
+    _chk(lib().mlm_workspace_bytes(ctypes.byref(dims), which, ctypes.byref(n)), "mlm_workspace_bytes")
     return n.value
 
 
@@ -137,7 +149,7 @@ def mlm_combine(dims, partials: Sequence[torch.Tensor], bias, residual, out, str
     arr = (ctypes.c_void_p * max(n, 1))(*[t.data_ptr() for t in partials])
     for t in partials:
         _p(t)
-    _chk(lib().mlm_combine(ctypes.byref(dims), arr, ctypes.c_int32(n), _p(bias), _p(residual), _p(out), _st(stream)),
+    _chk(lib().mlm_combine(ctypes.byref(dims), arr, n, _p(bias), _p(residual), _p(out), _st(stream)),
          "mlm_combine")
 
 
@@ -151,7 +163,7 @@ def _partial_array(partials):
 def mlm_combine_layernorm_fwd(dims, partials: Sequence[torch.Tensor], bias, residual, x_out, gamma, beta, y, mean, rstd,
                               stream=None):
     arr, n = _partial_array(partials)
-    _chk(lib().mlm_combine_layernorm_fwd(ctypes.byref(dims), arr, ctypes.c_int32(n), _p(bias), _p(residual), _p(x_out),
+    _chk(lib().mlm_combine_layernorm_fwd(ctypes.byref(dims), arr, n, _p(bias), _p(residual), _p(x_out),
                                          _p(gamma), _p(beta), _p(y), _p(mean), _p(rstd), _st(stream)),
          "mlm_combine_layernorm_fwd")
 
@@ -159,7 +171,7 @@ def mlm_combine_layernorm_fwd(dims, partials: Sequence[torch.Tensor], bias, resi
 def mlm_combine_layernorm_bwd(dims, partials: Sequence[torch.Tensor], x, gamma, mean, rstd, residual_grad, dy_out, dx,
                               dgamma, dbeta, dx_colsum, ws, stream=None):
     arr, n = _partial_array(partials)
-    _chk(lib().mlm_combine_layernorm_bwd(ctypes.byref(dims), arr, ctypes.c_int32(n), _p(x), _p(gamma), _p(mean),
+    _chk(lib().mlm_combine_layernorm_bwd(ctypes.byref(dims), arr, n, _p(x), _p(gamma), _p(mean),
                                          _p(rstd), _p(residual_grad), _p(dy_out), _p(dx), _p(dgamma), _p(dbeta),
                                          _p(dx_colsum), *_ws(ws), _st(stream)), "mlm_combine_layernorm_bwd")
 
@@ -214,7 +226,7 @@ def mlm_vocab_ce_shard_fwd(dims, hf, E_r, targets, m_r, s_r, t_r, logits_r, ws, 
 
 
 def mlm_vocab_ce_merge(dims, m, s, t, n_shards, loss_w, ce, M, S, loss_out, stream=None):
-    _chk(lib().mlm_vocab_ce_merge(ctypes.byref(dims), _p(m), _p(s), _p(t), ctypes.c_int32(n_shards), _p(loss_w),
+    _chk(lib().mlm_vocab_ce_merge(ctypes.byref(dims), _p(m), _p(s), _p(t), n_shards, _p(loss_w),
                                   _p(ce), _p(M), _p(S), _p(loss_out), _st(stream)), "mlm_vocab_ce_merge")
 
 
@@ -226,8 +238,8 @@ def mlm_vocab_ce_shard_bwd(dims, hf, E_r, targets, loss_w, M, S, loss_stats, log
 
 
 def mlm_gemm(dtype, trans_a, trans_b, M, N, K, A, B, C, bias=None, stream=None):
-    _chk(lib().mlm_gemm(ctypes.c_int32(dtype), ctypes.c_int32(trans_a), ctypes.c_int32(trans_b), ctypes.c_int64(M),
-                        ctypes.c_int64(N), ctypes.c_int64(K), _p(A), _p(B), _p(C), _p(bias), _st(stream)), "mlm_gemm")
+    _chk(lib().mlm_gemm(dtype, trans_a, trans_b, M,
+                        N, K, _p(A), _p(B), _p(C), _p(bias), _st(stream)), "mlm_gemm")
 
 
 def mlm_grad_sqnorm(dtype, grads: Sequence[torch.Tensor], other_sqnorm, sqnorm_out, ws, stream=None):
@@ -236,48 +248,46 @@ def mlm_grad_sqnorm(dtype, grads: Sequence[torch.Tensor], other_sqnorm, sqnorm_o
         _p(t)
     arr = (ctypes.c_void_p * max(n, 1))(*[t.data_ptr() for t in grads])
     cnt = (ctypes.c_int64 * max(n, 1))(*[t.numel() for t in grads])
-    _chk(lib().mlm_grad_sqnorm(ctypes.c_int32(dtype), arr, cnt, ctypes.c_int32(n), _p(other_sqnorm), _p(sqnorm_out),
+    _chk(lib().mlm_grad_sqnorm(dtype, arr, cnt, n, _p(other_sqnorm), _p(sqnorm_out),
                                *_ws(ws), _st(stream)), "mlm_grad_sqnorm")
 
 
 def mlm_adamw_step(dtype, grad, master, m, v, weight_out, total_sqnorm, max_norm, lr, beta1, beta2, eps, weight_decay,
                    step, stream=None):
-    f = ctypes.c_float
-    _chk(lib().mlm_adamw_step(ctypes.c_int32(dtype), ctypes.c_int64(grad.numel()), _p(grad), _p(master), _p(m), _p(v),
-                              _p(weight_out), _p(total_sqnorm), f(max_norm), f(lr), f(beta1), f(beta2), f(eps),
-                              f(weight_decay), ctypes.c_int32(step), _st(stream)), "mlm_adamw_step")
+    _chk(lib().mlm_adamw_step(dtype, grad.numel(), _p(grad), _p(master), _p(m), _p(v),
+                              _p(weight_out), _p(total_sqnorm), max_norm, lr, beta1, beta2, eps,
+                              weight_decay, step, _st(stream)), "mlm_adamw_step")
 
 
 def mlm_adamw_step_multi(dtype, grads, masters, ms, vs, weights_out, weight_decays, total_sqnorm, max_norm, lr, beta1,
                          beta2, eps, step, stream=None):
     n = len(grads)
-    ptrs = lambda ts: (ctypes.c_void_p * n)(*[(_p(t).value or 0) for t in ts])
+    ptrs = lambda ts: (ctypes.c_void_p * n)(*[(_p(t) or 0) for t in ts])
     cnt = (ctypes.c_int64 * n)(*[t.numel() for t in grads])
     wds = (ctypes.c_float * n)(*[float(x) for x in weight_decays])
-    f = ctypes.c_float
-    _chk(lib().mlm_adamw_step_multi(ctypes.c_int32(dtype), ctypes.c_int32(n), cnt, ptrs(grads), ptrs(masters), ptrs(ms),
-                                    ptrs(vs), ptrs(weights_out), wds, _p(total_sqnorm), f(max_norm), f(lr), f(beta1),
-                                    f(beta2), f(eps), ctypes.c_int32(step), _st(stream)), "mlm_adamw_step_multi")
+    _chk(lib().mlm_adamw_step_multi(dtype, n, cnt, ptrs(grads), ptrs(masters), ptrs(ms),
+                                    ptrs(vs), ptrs(weights_out), wds, _p(total_sqnorm), max_norm, lr, beta1,
+                                    beta2, eps, step, _st(stream)), "mlm_adamw_step_multi")
 
 
 # ---- dropout (two random streams) and the input embedding -------------------------------------------------------
 def mlm_rng_stream_seed(base_seed: int, stream: int, r: int) -> int:
     out = ctypes.c_uint64(0)
-    _chk(lib().mlm_rng_stream_seed(ctypes.c_uint64(base_seed & 0xFFFFFFFFFFFFFFFF), ctypes.c_int32(stream),
-                                   ctypes.c_int32(r), ctypes.byref(out)), "mlm_rng_stream_seed")
+    _chk(lib().mlm_rng_stream_seed(base_seed & 0xFFFFFFFFFFFFFFFF, stream,
+                                   r, ctypes.byref(out)), "mlm_rng_stream_seed")
     return out.value
 
 
 def mlm_combine_dropout(dims, partials, bias, bias_rows, drop, residual, out, stream=None):
     arr, n = _partial_array(partials)
-    _chk(lib().mlm_combine_dropout(ctypes.byref(dims), arr, ctypes.c_int32(n), _p(bias), ctypes.c_int32(bias_rows),
+    _chk(lib().mlm_combine_dropout(ctypes.byref(dims), arr, n, _p(bias), bias_rows,
                                    _d(drop), _p(residual), _p(out), _st(stream)), "mlm_combine_dropout")
 
 
 def mlm_combine_layernorm_fwd_dropout(dims, partials, bias, drop, residual, x_out, gamma, beta, y, mean, rstd,
                                       stream=None):
     arr, n = _partial_array(partials)
-    _chk(lib().mlm_combine_layernorm_fwd_dropout(ctypes.byref(dims), arr, ctypes.c_int32(n), _p(bias), _d(drop),
+    _chk(lib().mlm_combine_layernorm_fwd_dropout(ctypes.byref(dims), arr, n, _p(bias), _d(drop),
                                                  _p(residual), _p(x_out), _p(gamma), _p(beta), _p(y), _p(mean),
                                                  _p(rstd), _st(stream)), "mlm_combine_layernorm_fwd_dropout")
 
@@ -285,7 +295,7 @@ def mlm_combine_layernorm_fwd_dropout(dims, partials, bias, drop, residual, x_ou
 def mlm_combine_layernorm_bwd_dropout(dims, partials, x, gamma, mean, rstd, residual_grad, drop, dy_out, dx, dz_out,
                                       dgamma, dbeta, dx_colsum, ws, stream=None):
     arr, n = _partial_array(partials)
-    _chk(lib().mlm_combine_layernorm_bwd_dropout(ctypes.byref(dims), arr, ctypes.c_int32(n), _p(x), _p(gamma),
+    _chk(lib().mlm_combine_layernorm_bwd_dropout(ctypes.byref(dims), arr, n, _p(x), _p(gamma),
                                                  _p(mean), _p(rstd), _p(residual_grad), _d(drop), _p(dy_out), _p(dx),
                                                  _p(dz_out), _p(dgamma), _p(dbeta), _p(dx_colsum), *_ws(ws),
                                                  _st(stream)), "mlm_combine_layernorm_bwd_dropout")
@@ -328,12 +338,12 @@ def mlm_embed_shard_bwd(dims, ids, perm_r, dz0, dE_r, stream=None):
 
 
 def mlm_rows_gather(dims, x, row_idx, n, n_out, out, stream=None):
-    _chk(lib().mlm_rows_gather(ctypes.byref(dims), _p(x), _p(row_idx), ctypes.c_int32(n), ctypes.c_int32(n_out), _p(out),
+    _chk(lib().mlm_rows_gather(ctypes.byref(dims), _p(x), _p(row_idx), n, n_out, _p(out),
                                _st(stream)), "mlm_rows_gather")
 
 
 def mlm_rows_scatter(dims, y, row_idx, n, out, stream=None):
-    _chk(lib().mlm_rows_scatter(ctypes.byref(dims), _p(y), _p(row_idx), ctypes.c_int32(n), _p(out), _st(stream)),
+    _chk(lib().mlm_rows_scatter(ctypes.byref(dims), _p(y), _p(row_idx), n, _p(out), _st(stream)),
          "mlm_rows_scatter")
 
 
