@@ -687,7 +687,7 @@ MLM_API int mlm_vocab_ce_shard_bwd(const mlm_dims* dims, const void* hf, const v
   const bool apart = overlap(dE_r, bE, dhf_partial_r, bH) || overlap(dE_r, bE, E_r, bE) || overlap(dE_r, bE, hf, bH) ||
                      overlap(dE_r, bE, dL, bL) || overlap(dhf_partial_r, bH, E_r, bE) || overlap(dhf_partial_r, bH, hf, bH) ||
                      overlap(dhf_partial_r, bH, dL, bL);
-  if (dt == MLM_BF16 && !apart) return hip_status(launch_gemm_bf16_dual(gE, gH, sk, st));
+  if (!apart) return hip_status(dt == MLM_BF16 ? launch_gemm_bf16_dual(gE, gH, sk, st) : launch_gemm_f32_dual(gE, gH, st));
   MLM_TRY_HIP(run_gemm(dt, gE, st, sk));
   MLM_TRY_HIP(run_gemm(dt, gH, st, sk));
   return MLM_OK;

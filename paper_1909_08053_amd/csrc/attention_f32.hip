@@ -282,16 +282,14 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_fwd_f32_kernel(AttnArgs
 
 // dQ_i = scale * sum_j dS_ij K_j,  dS_ij = P_ij (dO_i . V_j - delta_i),  P_ij = exp(scale q_i.k_j - lse_i);
 // delta_i = dO_i . O_i is formed here from rows the lanes hold and left in the workspace for the dK/dV kernel.
-template <int D>
-__global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dq_f32_kernel(AttnArgs a, int pg) {
+// (JOINT: part of attn_bwd_f32_kernel, whose dK/dV blocks form delta themselves)
+template <int D, bool JOINT>
+__device__ __forceinline__ void attn_bwd_dq_f32_block(const AttnArgs a, const AfBlock blk) {
   constexpr int DT = AfShape<D>::DT, NV = DT * 16;
   extern __shared__ __attribute__((aligned(16))) float lds_af[];
   const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nb = (a.s + AF_ROWS - 1) / AF_ROWS;
-  const AfBlock blk = af_block(nb, a.hl, a.b, pg);
-  if (!blk.valid) return;
-  const int qb = nb - 1 - blk.xb;
+  const int qb = (a.s + AF_ROWS - 1) / AF_ROWS - 1 - blk.xb;
   const int hd = blk.hd, bi = blk.bi;
   const int ld = 3 * a.hl * D, ldo = a.hl * D;
   const float* base = (const float*)a.qkv + (size_t)bi * a.s * ld;
@@ -311,7 +309,7 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dq_f32_kernel(AttnA
   }
   const size_t row = ((size_t)bi * a.hl + hd) * a.s + qc;
   const float lse = a.lse[row];
-  if (wave == 0 && lh == 0 && qi < a.s) a.delta[row] = dl;
+  if (!JOINT && wave == 0 && lh == 0 && qi < a.s) a.delta[row] = dl;
   floatx16 dq[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
@@ -364,14 +362,29 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dq_f32_kernel(AttnA
 }
 
 // dV_j = sum_i P_ij dO_i,  dK_j = scale * sum_i dS_ij Q_i
-template <int D>
+// JOINT: dQ's blocks follow in the same launch, for calls whose blocks all find a compute unit at once (else dQ runs two workgroups
+// per unit in a launch of its own, and here only one).  Delta of a tile's queries is then formed here, from the rows of dO that
+// the scores read anyway and those of O.  Two of 128 tokens, 2 heads of 64: 23 us
+// in two launches, 14.5 in one (16.9 with O's rows requested behind the scores).
+template <int D, bool JOINT>
 __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dkv_f32_kernel(AttnArgs a, int pg) {
   constexpr int DT = AfShape<D>::DT, NV = 2 * DT * 16;
   extern __shared__ __attribute__((aligned(16))) float lds_af[];
   const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const AfBlock blk = af_block((a.s + AF_ROWS - 1) / AF_ROWS, a.hl, a.b, pg);
-  if (!blk.valid) return;
+  AfBlock blk;
+  if (JOINT) {
+    const int nb = (a.s + AF_ROWS - 1) / AF_ROWS, n = nb * a.hl * a.b, k = blockIdx.x;
+    const int id = k < n ? k : k - n, pair = id / nb, pb = pair / a.hl;
+    blk = {id - pair * nb, pair - pb * a.hl, pb, true};
+    if (k >= n) {
+      attn_bwd_dq_f32_block<D, true>(a, blk);
+      return;
+    }
+  } else {
+    blk = af_block((a.s + AF_ROWS - 1) / AF_ROWS, a.hl, a.b, pg);
+    if (!blk.valid) return;
+  }
   const int hd = blk.hd, bi = blk.bi;
   const int ld = 3 * a.hl * D, ldo = a.hl * D;
   const float* base = (const float*)a.qkv + (size_t)bi * a.s * ld;
@@ -401,7 +414,15 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dkv_f32_kernel(Attn
     for (int e = 0; e < 16; ++e) {
       const int ic = min(q0 + 8 * (e >> 2) + 4 * lh + (e & 3), a.s - 1);
       lse[e] = a.lse[row0 + ic];
-      del[e] = a.delta[row0 + ic];
+      if (!JOINT) del[e] = a.delta[row0 + ic];
+    }
+    // O's row of query q0 + l32, requested ahead of the scores too where there are registers for it
+    constexpr bool EARLY = JOINT && D <= 80;
+    const float* orow = (const float*)a.ctx + ((size_t)bi * a.s + qr) * ldo + hd * D + 4 * lh;
+    float4 ov[EARLY ? D / 8 : 1];
+    if (EARLY) {
+#pragma unroll
+      for (int c = 0; c < D / 8; ++c) ov[c] = *reinterpret_cast<const float4*>(orow + 8 * c);
     }
     if (a.drop.enabled) {
 #pragma unroll
@@ -410,6 +431,18 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dkv_f32_kernel(Attn
     }
     floatx16 s = af_scores<D>(Q + (size_t)qr * ld, lh, kf);          // [query][key]
     floatx16 dp = af_scores<D>(dO + (size_t)qr * ldo, lh, vf);
+    if (JOINT) {
+      float dl = 0.f;                                     // of query q0 + l32, in the order of the dQ kernel
+#pragma unroll
+      for (int c = 0; c < D / 8; ++c) {
+        const float4 g = *reinterpret_cast<const float4*>(dO + (size_t)qr * ldo + 8 * c + 4 * lh);
+        const float4 o = EARLY ? ov[EARLY ? c : 0] : *reinterpret_cast<const float4*>(orow + 8 * c);
+        dl = fmaf(o.x, g.x, dl); dl = fmaf(o.y, g.y, dl); dl = fmaf(o.z, g.z, dl); dl = fmaf(o.w, g.w, dl);
+      }
+      dl += __shfl_xor(dl, 32, 64);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) del[e] = __shfl(dl, 8 * (e >> 2) + 4 * lh + (e & 3), 64);
+    }
     auto off = [&](int e) {
       const int i = q0 + 8 * (e >> 2) + 4 * lh + (e & 3);
       return kj >= klen || i >= a.s || (a.causal && kj > i);
@@ -452,6 +485,11 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dkv_f32_kernel(Attn
   }
 }
 
+template <int D>
+__global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dq_f32_kernel(AttnArgs a, int pg) {
+  const AfBlock blk = af_block((a.s + AF_ROWS - 1) / AF_ROWS, a.hl, a.b, pg);
+  if (blk.valid) attn_bwd_dq_f32_block<D, false>(a, blk);
+}
 bool attn_f32_supported(int d) { return d > 0 && d % 16 == 0 && d <= 128; }
 
 #define MLM_AF_SWITCH(MACRO)                                                                         \
@@ -482,6 +520,19 @@ hipError_t launch_attn_fwd_f32(const AttnArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_attn_bwd_f32(const AttnArgs& a, hipStream_t st) {
+  const long joint = 2l * ((a.s + AF_ROWS - 1) / AF_ROWS) * a.hl * a.b;
+  if (joint <= gemm_cu_count()) {
+#define MLM_AF_JOINT(DD)                                                                             \
+  {                                                                                                  \
+    constexpr size_t lds = af_lds(2 * AfShape<DD>::DT * 16);                                         \
+    static LdsAttrOnce attr;                                                                         \
+    if (hipError_t e = attr.ensure((const void*)(attn_bwd_dkv_f32_kernel<DD, true>), (int)lds); e != hipSuccess) return e; \
+    hipLaunchKernelGGL((attn_bwd_dkv_f32_kernel<DD, true>), dim3((unsigned)joint), dim3(64 * AF_WAVES), lds, st, a, 0); \
+  }
+    MLM_AF_SWITCH(MLM_AF_JOINT)
+#undef MLM_AF_JOINT
+    return hipGetLastError();
+  }
   unsigned ngrid;
   const int pg = af_pairs(a, (a.s + AF_ROWS - 1) / AF_ROWS, &ngrid);
   const dim3 grid(ngrid), block(64 * AF_WAVES);
@@ -491,9 +542,9 @@ hipError_t launch_attn_bwd_f32(const AttnArgs& a, hipStream_t st) {
     static_assert(lds2 <= 160 * 1024, "LDS budget");                                                 \
     static LdsAttrOnce attr1, attr2;                                                                 \
     if (hipError_t e = attr1.ensure((const void*)attn_bwd_dq_f32_kernel<DD>, (int)lds1); e != hipSuccess) return e; \
-    if (hipError_t e = attr2.ensure((const void*)attn_bwd_dkv_f32_kernel<DD>, (int)lds2); e != hipSuccess) return e; \
+    if (hipError_t e = attr2.ensure((const void*)(attn_bwd_dkv_f32_kernel<DD, false>), (int)lds2); e != hipSuccess) return e; \
     hipLaunchKernelGGL((attn_bwd_dq_f32_kernel<DD>), grid, block, lds1, st, a, pg);                  \
-    hipLaunchKernelGGL((attn_bwd_dkv_f32_kernel<DD>), grid, block, lds2, st, a, pg);                 \
+    hipLaunchKernelGGL((attn_bwd_dkv_f32_kernel<DD, false>), grid, block, lds2, st, a, pg);                 \
   }
   MLM_AF_SWITCH(MLM_AF_BWD)
 #undef MLM_AF_BWD

@@ -172,6 +172,7 @@ hipError_t launch_gemm_bf16_wgrad_group(const GemmArgs* probs, int n, float* spl
 // A weight gradient a0 and an input gradient a1 (plain stores) that do not depend on each other, in one launch where that is
 // faster; no output may overlap an input or the other output.
 hipError_t launch_gemm_bf16_dual(const GemmArgs& a0, const GemmArgs& a1, float* splitk_ws, hipStream_t st);
+hipError_t launch_gemm_f32_dual(const GemmArgs& a0, const GemmArgs& a1, hipStream_t st);
 
 // ---- dropout site as the kernels see it (rng.h holds the generator) ---------------
 struct DropArgs {

