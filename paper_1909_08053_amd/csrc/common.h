@@ -165,6 +165,10 @@ int gemm_bf16_ce_col_tiles(int M, int N, int K);
 int gemm_cu_count();                    // compute units of the current device, at most 256
 hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t st);
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t st);
+// an input gradient (both operands k-contiguous, plain store) and column sums that do not depend on it
+struct ColsumJob;
+hipError_t launch_gemm_bf16_dgrad_colsum(const GemmArgs& a, const ColsumJob& j, hipStream_t st);
+hipError_t launch_gemm_f32_dgrad_colsum(const GemmArgs& a, const ColsumJob& j, hipStream_t st);
 hipError_t launch_gemm_f32_wgrads(const GemmArgs* probs, int n, hipStream_t st);
 // n weight-gradient GEMMs (A m-contiguous, B n-contiguous, plain store) in one launch where that is faster
 hipError_t launch_gemm_bf16_wgrad_group(const GemmArgs* probs, int n, float* splitk_ws, hipStream_t st);
@@ -173,6 +177,57 @@ hipError_t launch_gemm_bf16_wgrad_group(const GemmArgs* probs, int n, float* spl
 // faster; no output may overlap an input or the other output.
 hipError_t launch_gemm_bf16_dual(const GemmArgs& a0, const GemmArgs& a1, float* splitk_ws, hipStream_t st);
 hipError_t launch_gemm_f32_dual(const GemmArgs& a0, const GemmArgs& a1, hipStream_t st);
+
+// ---- column sums (bias gradients) as a part of another launch --------------------------
+// Partial column sums of x [rows, N] in chunks of kColsumRowsPerBlock rows: ws[chunk][N].  blocks = 0: no job.
+constexpr int kColsumRowsPerBlock = 64;
+struct ColsumJob {
+  const void* x;
+  float* ws;
+  int rows, N, blocks;
+};
+template <typename T> inline int colsum_blocks(int rows, int N) {
+  return ((N / Vec16<T>::N + 63) / 64) * ((rows + kColsumRowsPerBlock - 1) / kColsumRowsPerBlock);
+}
+// One block of it: 64 vector-columns x NT / 64 row-slices; the slices are summed through LDS in a fixed order.
+template <typename T, int NT> constexpr int colsum_lds_floats() { return NT / 64 * (64 * Vec16<T>::N + 1); }
+template <typename T, int NT>
+__device__ __forceinline__ void colsum_block(const ColsumJob& j, int blk, float* lds) {
+  constexpr int VN = Vec16<T>::N, NS = NT / 64, PITCH = 64 * VN + 1;
+  const int vx = threadIdx.x & 63, sl = threadIdx.x >> 6;
+  const int ncb = (j.N / VN + 63) / 64;               // column blocks (the faster index)
+  const int chunk = blk / ncb, vcol = (blk - chunk * ncb) * 64 + vx;
+  const bool ok = vcol * VN < j.N;
+  const int r0 = chunk * kColsumRowsPerBlock, r1 = min(j.rows, r0 + kColsumRowsPerBlock);
+  float acc[VN];
+#pragma unroll
+  for (int e = 0; e < VN; ++e) acc[e] = 0.f;
+  if (ok) {
+#pragma unroll 4
+    for (int r = r0 + sl; r < r1; r += NS) {
+      Vec16<T> v;
+      v.load((const T*)j.x + (size_t)r * j.N + (size_t)vcol * VN);
+#pragma unroll
+      for (int e = 0; e < VN; ++e) acc[e] += v.get(e);
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < VN; ++e) lds[sl * PITCH + e * 64 + vx] = acc[e];
+  __syncthreads();
+  if (sl == 0 && ok) {
+#pragma unroll
+    for (int e = 0; e < VN; ++e) {
+      float t[NS];
+#pragma unroll
+      for (int k = 0; k < NS; ++k) t[k] = lds[k * PITCH + e * 64 + vx];
+#pragma unroll
+      for (int w = 1; w < NS; w *= 2)
+#pragma unroll
+        for (int k = 0; k + w < NS; k += 2 * w) t[k] += t[k + w];
+      j.ws[(size_t)chunk * j.N + (size_t)vcol * VN + e] = t[0];
+    }
+  }
+}
 
 // ---- dropout site as the kernels see it (rng.h holds the generator) ---------------
 struct DropArgs {
@@ -214,7 +269,6 @@ hipError_t launch_attn_bwd_f32(const AttnArgs& a, hipStream_t st);
 
 // ---- row / elementwise kernels (rowops.hip); dtype = MLM_F32 / MLM_BF16 ----------
 constexpr int kLnBwdRowsPerBlock = 32;      // at most; ln_bwd_blocks deals fewer where that leaves compute units idle
-constexpr int kColsumRowsPerBlock = 64;
 constexpr int kMaxPartials = 16;
 
 hipError_t launch_layernorm_fwd(int dtype, int T, int H, float eps, const void* x, const void* gamma,
@@ -244,6 +298,12 @@ hipError_t launch_combine(int dtype, int T, int H, const void* const* partials, 
                           int bias_rows, const void* residual, void* out, const mlm_dropout* drop, hipStream_t st);
 // ws: [ceil(T/kColsumRowsPerBlock)][N] float
 hipError_t launch_colsum(int dtype, int T, int N, const void* dy, void* dbias, float* ws, hipStream_t st);
+// The same in two steps around a launch that takes the partial sums along: colsum_job says what to sum and where (ws, or the
+// storage of an open list of deferred sums), colsum_finish does what is left.
+struct ColsumPlan { ColsumJob job; bool deferred; };
+ColsumPlan colsum_job(int dtype, int T, int N, const void* dy, float* ws);
+hipError_t colsum_finish(int dtype, const ColsumPlan& p, void* dbias, hipStream_t st);
+hipError_t launch_colsum_partials(int dtype, const ColsumJob& j, hipStream_t st);
 // Deferred finishing sums (per host thread).  Between begin and flush, launch_layernorm_bwd,
 // launch_combine_layernorm_bwd and launch_colsum keep their block partials in `buf` and leave dgamma / dbeta /
 // dx_colsum / dbias unwritten; flush sums all of them in one launch (bit-identical to finishing inside each call).

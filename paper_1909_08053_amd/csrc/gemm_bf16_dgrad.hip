@@ -12,4 +12,8 @@ hipError_t launch_gemm_bf16_dgrad(const GemmArgs& a, hipStream_t st) {
   }
 }
 
+hipError_t launch_gemm_bf16_dgrad_colsum(const GemmArgs& a, const ColsumJob& j, hipStream_t st) {
+  return launch_gemm_bf16_v2<true, true, EPI_STORE, true>(a, a.splitk_ws, st, &j);
+}
+
 }  // namespace mlm

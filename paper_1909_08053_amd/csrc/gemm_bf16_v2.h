@@ -553,6 +553,21 @@ __global__ __launch_bounds__((v2_nw<BN, DEEP>() * 64), 2) void gemm_bf16_v2_kern
   gemm_v2_work_item<A_KC, B_KC, EPI, BN, KE, DEEP>(a, plan, splitk_ws, pid, lds_raw);
 }
 
+// An input gradient with the column sums of its left operand (a bias gradient) in the same launch: the workgroups behind the
+// tiles sum columns, on compute units that the tiles leave idle.
+template <int BN, int KE, bool DEEP>
+__global__ __launch_bounds__((v2_nw<BN, DEEP>() * 64), 2) void gemm_bf16_v2_colsum_kernel(GemmArgs a, V2Plan plan, float* splitk_ws,
+                                                                                           ColsumJob job) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+  const int id = blockIdx.x, items = plan.full_tiles + plan.tail_tiles * plan.split;
+  if (id >= items) {
+    colsum_block<bf16, v2_nw<BN, DEEP>() * 64>(job, id - items, reinterpret_cast<float*>(lds_raw));
+    return;
+  }
+  const int pid = plan.strip && id < plan.full_tiles ? v2_xcd_order(id, plan.full_tiles, plan.window) : id;
+  gemm_v2_work_item<true, true, EPI_STORE, BN, KE, DEEP>(a, plan, splitk_ws, pid, lds_raw);
+}
+
 // Several independent GEMMs of one operand layout in ONE launch (plain-store epilogue, no k-split): the tiles of
 // problem q follow those of problem q - 1 in the grid, so the launch pays the partially filled last round of the
 // 256 CUs once instead of once per GEMM.  Used for the weight gradients of a layer shard, which nothing but the
@@ -696,15 +711,22 @@ template <int BN, bool DEEP> int v2_window() {
   return n < 8 ? 8 : n;
 }
 
-template <bool A_KC, bool B_KC, int EPI, int BN, int KE, bool DEEP>
-hipError_t launch_gemm_bf16_v2_ke(const GemmArgs& a, float* splitk_ws, hipStream_t st) {
-  auto kern = gemm_bf16_v2_kernel<A_KC, B_KC, EPI, BN, KE, DEEP>;
+// JOB: gemm_bf16_v2_colsum_kernel with `job`
+template <bool A_KC, bool B_KC, int EPI, int BN, int KE, bool DEEP, bool JOB>
+hipError_t launch_gemm_bf16_v2_ke(const GemmArgs& a, float* splitk_ws, const ColsumJob* job, hipStream_t st) {
   constexpr size_t kLds = v2_lds_bytes<A_KC, B_KC, BN, DEEP>();
   static LdsAttrOnce attr;         // per instantiation and device
-  if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
   V2Plan plan = v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, BN);
   v2_set_walk(&plan, v2_window<BN, DEEP>(), a.K);
-  hipLaunchKernelGGL(kern, dim3(plan.grid()), dim3(v2_nw<BN, DEEP>() * 64), kLds, st, a, plan, splitk_ws);
+  if constexpr (JOB) {
+    auto kern = gemm_bf16_v2_colsum_kernel<BN, KE, DEEP>;
+    if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(plan.grid() + job->blocks), dim3(v2_nw<BN, DEEP>() * 64), kLds, st, a, plan, splitk_ws, *job);
+  } else {
+    auto kern = gemm_bf16_v2_kernel<A_KC, B_KC, EPI, BN, KE, DEEP>;
+    if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(plan.grid()), dim3(v2_nw<BN, DEEP>() * 64), kLds, st, a, plan, splitk_ws);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (plan.tail_tiles) {
@@ -790,27 +812,27 @@ int v2_pick_bn(int M, int N, int K, bool allow_split) {
   return best;
 }
 
-template <bool A_KC, bool B_KC, int EPI, int BN, bool DEEP = false>
-hipError_t launch_gemm_bf16_v2_bn(const GemmArgs& a, float* splitk_ws, hipStream_t st) {
+template <bool A_KC, bool B_KC, int EPI, int BN, bool DEEP, bool JOB>
+hipError_t launch_gemm_bf16_v2_bn(const GemmArgs& a, float* splitk_ws, const ColsumJob* job, hipStream_t st) {
   switch (v2_k_end<BN>(a.K)) {
-    case KE_PAIR: return launch_gemm_bf16_v2_ke<A_KC, B_KC, EPI, BN, KE_PAIR, DEEP>(a, splitk_ws, st);
+    case KE_PAIR: return launch_gemm_bf16_v2_ke<A_KC, B_KC, EPI, BN, KE_PAIR, DEEP, JOB>(a, splitk_ws, job, st);
     case KE_SLICE:
-      if constexpr (BN != V2_SMALL) return launch_gemm_bf16_v2_ke<A_KC, B_KC, EPI, BN, KE_SLICE, DEEP>(a, splitk_ws, st);
-    default: return launch_gemm_bf16_v2_ke<A_KC, B_KC, EPI, BN, KE_ANY, DEEP>(a, splitk_ws, st);
+      if constexpr (BN != V2_SMALL) return launch_gemm_bf16_v2_ke<A_KC, B_KC, EPI, BN, KE_SLICE, DEEP, JOB>(a, splitk_ws, job, st);
+    default: return launch_gemm_bf16_v2_ke<A_KC, B_KC, EPI, BN, KE_ANY, DEEP, JOB>(a, splitk_ws, job, st);
   }
 }
 
-template <bool A_KC, bool B_KC, int EPI>
-hipError_t launch_gemm_bf16_v2(const GemmArgs& a, float* splitk_ws, hipStream_t st) {
+template <bool A_KC, bool B_KC, int EPI, bool JOB = false>
+hipError_t launch_gemm_bf16_v2(const GemmArgs& a, float* splitk_ws, hipStream_t st, const ColsumJob* job = nullptr) {
   const int bn = v2_pick_bn<A_KC, B_KC, EPI>(a.M, a.N, a.K, splitk_ws != nullptr);
   if constexpr (v2_has_narrow<A_KC, B_KC, EPI>())
-    if (bn == 192) return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, 192>(a, splitk_ws, st);
+    if (bn == 192) return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, 192, false, JOB>(a, splitk_ws, job, st);
   if constexpr (v2_has_small<EPI>())
     if (bn == V2_SMALL)
       return v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, V2_SMALL).deep()
-                 ? launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_SMALL, true>(a, splitk_ws, st)
-                 : launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_SMALL>(a, splitk_ws, st);
-  return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_B>(a, splitk_ws, st);
+                 ? launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_SMALL, true, JOB>(a, splitk_ws, job, st)
+                 : launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_SMALL, false, JOB>(a, splitk_ws, job, st);
+  return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_B, false, JOB>(a, splitk_ws, job, st);
 }
 
 // End of `units` units working through n0 items of c0 and then n1 of c1 (microseconds), each taking the next item when it is done.

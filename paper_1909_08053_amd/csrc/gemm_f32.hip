@@ -391,6 +391,14 @@ __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_dual_kerne
   else f32_split_tile<true, true, EPI_STORE>(x, id - tiles_w);
 }
 
+// An input gradient and column sums beside it (the workgroups behind the tiles).
+__global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_colsum_kernel(GemmArgs a, ColsumJob job) {
+  __shared__ float red[colsum_lds_floats<float, 64 * kF32SplitWaves>()];
+  const int tiles = ((a.M + 31) / 32) * ((a.N + 31) / 32), id = blockIdx.x;
+  if (id < tiles) f32_split_tile<true, true, EPI_STORE>(a, id);
+  else colsum_block<float, 64 * kF32SplitWaves>(job, id - tiles, red);
+}
+
 template <bool A_KC, bool B_KC, int EPI, int BM, int BN, int WM, int WN, int KS, int KT>
 static hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t st) {
   constexpr int NT = 64 * WM * WN * KS;
@@ -440,6 +448,16 @@ hipError_t launch_gemm_f32_wgrads(const GemmArgs* probs, int n, hipStream_t st) 
   for (int q = n; q < kF32Group; ++q) g.tile_begin[q] = total;
   hipLaunchKernelGGL(gemm_f32_split_group_kernel, dim3(total), dim3(64 * kF32SplitWaves), 0, st, g);
   return hipGetLastError();
+}
+
+hipError_t launch_gemm_f32_dgrad_colsum(const GemmArgs& a, const ColsumJob& j, hipStream_t st) {
+  if (f32_pick(a.M, a.N, a.K) == 32) {
+    const int tiles = ((a.M + 31) / 32) * ((a.N + 31) / 32);
+    hipLaunchKernelGGL(gemm_f32_split_colsum_kernel, dim3(tiles + j.blocks), dim3(64 * kF32SplitWaves), 0, st, a, j);
+    return hipGetLastError();
+  }
+  if (hipError_t e = launch_colsum_partials(MLM_F32, j, st); e != hipSuccess) return e;
+  return launch_gemm_f32(a, st);
 }
 
 hipError_t launch_gemm_f32_dual(const GemmArgs& w, const GemmArgs& x, hipStream_t st) {

@@ -655,64 +655,43 @@ hipError_t launch_combine(int dtype, int T, int H, const void* const* partials, 
 }
 
 // ------------------------------------------------------------------------------ column sums (bias gradients)
-// Block = 64 vector-columns x 4 row-slices over kColsumRowsPerBlock rows; slices are summed through LDS in a fixed
-// order, the chunk partial goes to the workspace and reduce_cols_kernel finishes.
+// The chunk partials go to the workspace (colsum_block) and reduce_cols_kernel finishes.
 template <typename T>
-__global__ __launch_bounds__(256) void colsum_partial_kernel(int rows, int N, const T* __restrict__ dy,
-                                                             float* __restrict__ ws) {
-  constexpr int VN = Vec16<T>::N;
-  __shared__ float red[4][64 * VN + 1];
-  const int vx = threadIdx.x & 63, sl = threadIdx.x >> 6;
-  const int ncb = (N / VN + 63) / 64;                 // column blocks; grid.x = chunks x column blocks (column block fastest)
-  const int chunk = blockIdx.x / ncb;
-  const int vcol = (blockIdx.x - chunk * ncb) * 64 + vx;
-  const bool ok = vcol * VN < N;
-  const int r0 = chunk * kColsumRowsPerBlock;
-  const int r1 = min(rows, r0 + kColsumRowsPerBlock);
-  float acc[VN];
-#pragma unroll
-  for (int e = 0; e < VN; ++e) acc[e] = 0.f;
-  if (ok) {
-#pragma unroll 4
-    for (int r = r0 + sl; r < r1; r += 4) {
-      Vec16<T> v;
-      v.load(dy + (size_t)r * N + (size_t)vcol * VN);
-#pragma unroll
-      for (int e = 0; e < VN; ++e) acc[e] += v.get(e);
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < VN; ++e) red[sl][e * 64 + vx] = acc[e];
-  __syncthreads();
-  if (sl == 0 && ok) {
-#pragma unroll
-    for (int e = 0; e < VN; ++e) {
-      const float t = (red[0][e * 64 + vx] + red[1][e * 64 + vx]) + (red[2][e * 64 + vx] + red[3][e * 64 + vx]);
-      ws[(size_t)chunk * N + (size_t)vcol * VN + e] = t;
-    }
-  }
+__global__ __launch_bounds__(256) void colsum_partial_kernel(ColsumJob j) {
+  __shared__ float red[colsum_lds_floats<T, 256>()];
+  colsum_block<T, 256>(j, blockIdx.x, red);
 }
 
-static hipError_t colsum_impl(int dtype, int T, int N, const void* dy, void* dbias, float* ws, bool may_defer,
-                              hipStream_t st) {
+hipError_t launch_colsum_partials(int dtype, const ColsumJob& j, hipStream_t st) {
+  if (dtype == MLM_BF16) hipLaunchKernelGGL((colsum_partial_kernel<bf16>), dim3(j.blocks), dim3(256), 0, st, j);
+  else hipLaunchKernelGGL((colsum_partial_kernel<float>), dim3(j.blocks), dim3(256), 0, st, j);
+  return hipGetLastError();
+}
+
+static ColsumPlan colsum_plan(int dtype, int T, int N, const void* dy, float* ws, bool may_defer) {
   const int nchunk = (T + kColsumRowsPerBlock - 1) / kColsumRowsPerBlock;
   float* deferred = may_defer ? deferred_reserve((size_t)nchunk * N) : nullptr;
-  if (deferred) ws = deferred;
-  if (dtype == MLM_BF16) {
-    dim3 grid(((N / 8 + 63) / 64) * nchunk);
-    hipLaunchKernelGGL((colsum_partial_kernel<bf16>), grid, dim3(256), 0, st, T, N, (const bf16*)dy, ws);
-  } else {
-    dim3 grid(((N / 4 + 63) / 64) * nchunk);
-    hipLaunchKernelGGL((colsum_partial_kernel<float>), grid, dim3(256), 0, st, T, N, (const float*)dy, ws);
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const ColReduce fin = {ws, dbias, dbias, dbias, nchunk, N, N, dtype};
-  if (deferred) {
+  return {{dy, deferred ? deferred : ws, T, N, dtype == MLM_BF16 ? colsum_blocks<bf16>(T, N) : colsum_blocks<float>(T, N)},
+          deferred != nullptr};
+}
+
+ColsumPlan colsum_job(int dtype, int T, int N, const void* dy, float* ws) { return colsum_plan(dtype, T, N, dy, ws, true); }
+
+hipError_t colsum_finish(int dtype, const ColsumPlan& p, void* dbias, hipStream_t st) {
+  const int nchunk = (p.job.rows + kColsumRowsPerBlock - 1) / kColsumRowsPerBlock, N = p.job.N;
+  const ColReduce fin = {p.job.ws, dbias, dbias, dbias, nchunk, N, N, dtype};
+  if (p.deferred) {
     deferred_record(fin);
     return hipSuccess;
   }
   return launch_reduce_cols(fin, st);
+}
+
+static hipError_t colsum_impl(int dtype, int T, int N, const void* dy, void* dbias, float* ws, bool may_defer,
+                              hipStream_t st) {
+  const ColsumPlan p = colsum_plan(dtype, T, N, dy, ws, may_defer);
+  if (hipError_t e = launch_colsum_partials(dtype, p.job, st); e != hipSuccess) return e;
+  return colsum_finish(dtype, p, dbias, st);
 }
 
 hipError_t launch_colsum(int dtype, int T, int N, const void* dy, void* dbias, float* ws, hipStream_t st) {
