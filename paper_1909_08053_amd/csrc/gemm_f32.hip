@@ -151,7 +151,7 @@ __device__ __forceinline__ void f32_static_for(F&& f, std::integer_sequence<int,
 
 // BM x BN tile; WM x WN waves of (BM / WM) x (BN / WN), KS groups of them that share every KT-deep operand tile along k.
 template <bool A_KC, bool B_KC, int EPI, int BM, int BN, int WM, int WN, int KS, int KT>
-__global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_kernel(GemmArgs a) {
+__device__ __forceinline__ void f32_tile(const GemmArgs& a, int tile) {
   constexpr int NT = 64 * WM * WN * KS, TM = BM / WM / 16, TN = BN / WN / 16, NC = KT / 16 / KS;
   typedef F32Tile<A_KC, BM, KT, NT> TA;
   typedef F32Tile<B_KC, BN, KT, NT> TB;
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_kernel(Gem
   const int grp = wave / (WM * WN), w = wave % (WM * WN);
   const int wm0 = (w / WN) * (BM / WM), wn0 = (w % WN) * (BN / WN);
   const int tiles_m = (a.M + BM - 1) / BM;
-  const int m0 = (blockIdx.x % tiles_m) * BM, n0 = (blockIdx.x / tiles_m) * BN;
+  const int m0 = (tile % tiles_m) * BM, n0 = (tile / tiles_m) * BN;
   const float* A = (const float*)a.A;
   const float* B = (const float*)a.B;
   floatx4 acc[TM][TN];
@@ -279,6 +279,11 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_kernel(Gem
     for (int j = 0; j < TN; ++j) f32_store_tile<EPI>(a, acc[i][j], m0 + wm0 + i * 16, n0 + wn0 + j * 16, lane);
 }
 
+template <bool A_KC, bool B_KC, int EPI, int BM, int BN, int WM, int WN, int KS, int KT>
+__global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_kernel(GemmArgs a) {
+  f32_tile<A_KC, B_KC, EPI, BM, BN, WM, WN, KS, KT>(a, blockIdx.x);
+}
+
 // 32 x 32 tile, 8 waves: wave w sums the w-th eighth of k (in 8-deep chunks) and the eight partial tiles are added in LDS,
 // in wave order.
 constexpr int kF32SplitWaves = 8;
@@ -373,14 +378,25 @@ struct F32Group {
   GemmArgs a[kF32Group];
   int tile_begin[kF32Group];           // first tile of each problem (past the grid for problems that do not exist)
 };
-__global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_group_kernel(F32Group g) {
+__device__ __forceinline__ int f32_group_at(const F32Group& g, GemmArgs* a) {      // this workgroup's problem, and its tile there
   const int id = blockIdx.x;
-  GemmArgs a = g.a[0];
   int first = 0;
+  *a = g.a[0];
 #pragma unroll
   for (int q = 1; q < kF32Group; ++q)
-    if (id >= g.tile_begin[q]) { a = g.a[q]; first = g.tile_begin[q]; }     // workgroup-uniform
-  f32_split_tile<false, false, EPI_STORE>(a, id - first);
+    if (id >= g.tile_begin[q]) { *a = g.a[q]; first = g.tile_begin[q]; }     // workgroup-uniform
+  return id - first;
+}
+__global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_group_kernel(F32Group g) {
+  GemmArgs a;
+  const int tile = f32_group_at(g, &a);
+  f32_split_tile<false, false, EPI_STORE>(a, tile);
+}
+template <int BM, int BN, int WM, int WN, int KS, int KT>
+__global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_group_kernel(F32Group g) {
+  GemmArgs a;
+  const int tile = f32_group_at(g, &a);
+  f32_tile<false, false, EPI_STORE, BM, BN, WM, WN, KS, KT>(a, tile);
 }
 
 // A weight gradient (its tiles first) and an input gradient that do not depend on each other: 256 x 512 x 256 and 256 x 256 x 512
@@ -399,18 +415,34 @@ __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_colsum_ker
   else colsum_block<float, 64 * kF32SplitWaves>(job, id - tiles, red);
 }
 
-template <bool A_KC, bool B_KC, int EPI, int BM, int BN, int WM, int WN, int KS, int KT>
-static hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t st) {
+// LDS of a workgroup of f32_tile
+template <bool A_KC, bool B_KC, int BM, int BN, int WM, int WN, int KS, int KT> constexpr size_t f32_tile_lds() {
   constexpr int NT = 64 * WM * WN * KS;
   constexpr size_t kStages = 2 * (size_t)(F32Tile<A_KC, BM, KT, NT>::FLOATS + F32Tile<B_KC, BN, KT, NT>::FLOATS) * 4;
   constexpr size_t kPark = (size_t)(KS - 1) * BM * BN * 4;
   constexpr size_t kLds = kStages > kPark ? kStages : kPark;
   static_assert(kLds <= 160 * 1024, "LDS budget");
+  return kLds;
+}
+
+template <bool A_KC, bool B_KC, int EPI, int BM, int BN, int WM, int WN, int KS, int KT>
+static hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t st) {
+  constexpr size_t kLds = f32_tile_lds<A_KC, B_KC, BM, BN, WM, WN, KS, KT>();
   auto kern = gemm_f32_tile_kernel<A_KC, B_KC, EPI, BM, BN, WM, WN, KS, KT>;
   static LdsAttrOnce attr;
   if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
   const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  hipLaunchKernelGGL(kern, dim3(tiles), dim3(NT), kLds, st, a);
+  hipLaunchKernelGGL(kern, dim3(tiles), dim3(64 * WM * WN * KS), kLds, st, a);
+  return hipGetLastError();
+}
+
+template <int BM, int BN, int WM, int WN, int KS, int KT>
+static hipError_t launch_f32_tile_group(const F32Group& g, int total, hipStream_t st) {
+  constexpr size_t kLds = f32_tile_lds<false, false, BM, BN, WM, WN, KS, KT>();
+  auto kern = gemm_f32_tile_group_kernel<BM, BN, WM, WN, KS, KT>;
+  static LdsAttrOnce attr;
+  if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(total), dim3(64 * WM * WN * KS), kLds, st, g);
   return hipGetLastError();
 }
 
@@ -427,12 +459,17 @@ static hipError_t launch_f32_layout(const GemmArgs& a, hipStream_t st) {
   }
 }
 
-// Weight gradients (both operands k-major, plain store) that all take the split kernel go out as one launch, others one by one.
+// Weight gradients (both operands k-major, plain store) of one K in one launch where f32_group_pick says so, else one by one.
 hipError_t launch_gemm_f32_wgrads(const GemmArgs* probs, int n, hipStream_t st) {
   bool together = n >= 2 && n <= kF32Group;
-  for (int q = 0; q < n && together; ++q)
-    together = !probs[q].a_kc && !probs[q].b_kc && probs[q].epi == EPI_STORE && f32_pick(probs[q].M, probs[q].N, probs[q].K) == 32;
-  if (!together) {
+  int M[kF32Group], N[kF32Group];
+  for (int q = 0; q < n && together; ++q) {
+    together = !probs[q].a_kc && !probs[q].b_kc && probs[q].epi == EPI_STORE && probs[q].K == probs[0].K;
+    M[q] = probs[q].M;
+    N[q] = probs[q].N;
+  }
+  const int b = together ? f32_group_pick(M, N, n, probs[0].K) : 0;
+  if (b == 0) {
     for (int q = 0; q < n; ++q)
       if (hipError_t e = launch_gemm_f32(probs[q], st); e != hipSuccess) return e;
     return hipSuccess;
@@ -443,9 +480,11 @@ hipError_t launch_gemm_f32_wgrads(const GemmArgs* probs, int n, hipStream_t st) 
   for (int q = 0; q < n; ++q) {
     g.a[q] = probs[q];
     g.tile_begin[q] = total;
-    total += ((probs[q].M + 31) / 32) * ((probs[q].N + 31) / 32);
+    total += ((M[q] + b - 1) / b) * ((N[q] + b - 1) / b);
   }
   for (int q = n; q < kF32Group; ++q) g.tile_begin[q] = total;
+  if (b == 64) return launch_f32_tile_group<64, 64, 2, 2, 2, 64>(g, total, st);
+  if (b == 128) return launch_f32_tile_group<128, 128, 2, 2, 1, 32>(g, total, st);
   hipLaunchKernelGGL(gemm_f32_split_group_kernel, dim3(total), dim3(64 * kF32SplitWaves), 0, st, g);
   return hipGetLastError();
 }
