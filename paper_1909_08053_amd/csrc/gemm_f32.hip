@@ -407,12 +407,20 @@ __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_dual_kerne
   else f32_split_tile<true, true, EPI_STORE>(x, id - tiles_w);
 }
 
-// An input gradient and column sums beside it (the workgroups behind the tiles).
+// An input gradient and column sums beside it (the workgroups behind the tiles): a launch of 5 us saved, 1024 tokens x 1024 1270 ->
+// 1264 us a step.
 __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_colsum_kernel(GemmArgs a, ColsumJob job) {
   __shared__ float red[colsum_lds_floats<float, 64 * kF32SplitWaves>()];
   const int tiles = ((a.M + 31) / 32) * ((a.N + 31) / 32), id = blockIdx.x;
   if (id < tiles) f32_split_tile<true, true, EPI_STORE>(a, id);
   else colsum_block<float, 64 * kF32SplitWaves>(job, id - tiles, red);
+}
+template <int BM, int BN, int WM, int WN, int KS, int KT>
+__global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_colsum_kernel(GemmArgs a, ColsumJob job, int tiles) {
+  extern __shared__ __attribute__((aligned(16))) float lds_f32[];
+  const int id = blockIdx.x;
+  if (id < tiles) f32_tile<true, true, EPI_STORE, BM, BN, WM, WN, KS, KT>(a, id);
+  else colsum_block<float, 64 * WM * WN * KS>(job, id - tiles, lds_f32);
 }
 
 // LDS of a workgroup of f32_tile
@@ -433,6 +441,18 @@ static hipError_t launch_f32_tile(const GemmArgs& a, hipStream_t st) {
   if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
   const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
   hipLaunchKernelGGL(kern, dim3(tiles), dim3(64 * WM * WN * KS), kLds, st, a);
+  return hipGetLastError();
+}
+
+template <int BM, int BN, int WM, int WN, int KS, int KT>
+static hipError_t launch_f32_tile_colsum(const GemmArgs& a, const ColsumJob& j, hipStream_t st) {
+  constexpr size_t kTile = f32_tile_lds<true, true, BM, BN, WM, WN, KS, KT>();
+  constexpr size_t kSums = colsum_lds_floats<float, 64 * WM * WN * KS>() * sizeof(float), kLds = kTile > kSums ? kTile : kSums;
+  auto kern = gemm_f32_tile_colsum_kernel<BM, BN, WM, WN, KS, KT>;
+  static LdsAttrOnce attr;
+  if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
+  const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
+  hipLaunchKernelGGL(kern, dim3(tiles + j.blocks), dim3(64 * WM * WN * KS), kLds, st, a, j, tiles);
   return hipGetLastError();
 }
 
@@ -490,13 +510,15 @@ hipError_t launch_gemm_f32_wgrads(const GemmArgs* probs, int n, hipStream_t st) 
 }
 
 hipError_t launch_gemm_f32_dgrad_colsum(const GemmArgs& a, const ColsumJob& j, hipStream_t st) {
-  if (f32_pick(a.M, a.N, a.K) == 32) {
-    const int tiles = ((a.M + 31) / 32) * ((a.N + 31) / 32);
-    hipLaunchKernelGGL(gemm_f32_split_colsum_kernel, dim3(tiles + j.blocks), dim3(64 * kF32SplitWaves), 0, st, a, j);
-    return hipGetLastError();
+  switch (f32_pick(a.M, a.N, a.K)) {
+    case 32: {
+      const int tiles = ((a.M + 31) / 32) * ((a.N + 31) / 32);
+      hipLaunchKernelGGL(gemm_f32_split_colsum_kernel, dim3(tiles + j.blocks), dim3(64 * kF32SplitWaves), 0, st, a, j);
+      return hipGetLastError();
+    }
+    case 64: return launch_f32_tile_colsum<64, 64, 2, 2, 2, 64>(a, j, st);
+    default: return launch_f32_tile_colsum<128, 128, 2, 2, 1, 32>(a, j, st);
   }
-  if (hipError_t e = launch_colsum_partials(MLM_F32, j, st); e != hipSuccess) return e;
-  return launch_gemm_f32(a, st);
 }
 
 hipError_t launch_gemm_f32_dual(const GemmArgs& w, const GemmArgs& x, hipStream_t st) {
