@@ -26,6 +26,7 @@
 #pragma once
 #include "gemm_bf16.h"
 #include "lds_dma.h"
+#include "schedule.h"
 #include <limits.h>
 #include <string.h>
 #include <type_traits>
@@ -835,23 +836,6 @@ hipError_t launch_gemm_bf16_v2(const GemmArgs& a, float* splitk_ws, hipStream_t 
   return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_B, false, JOB>(a, splitk_ws, job, st);
 }
 
-// End of `units` units working through n0 items of c0 and then n1 of c1 (microseconds), each taking the next item when it is done.
-inline double v2_two_batches(int units, int n0, double c0, int n1, double c1) {
-  const double t0 = (double)(n0 / units) * c0;
-  const int busy = n0 % units;                        // units that are done with the first batch c0 later than the others
-  double lo = busy ? t0 + c0 : t0, hi = t0 + c0 + c1 * (n1 / units + 2);
-  auto done = [&](double t) {
-    const double late = t - t0 - c0;
-    return (double)(units - busy) * (long)((t - t0) / c1 + 1e-6) + (late > 0 ? (double)busy * (long)(late / c1 + 1e-6) : 0.0) >= n1;
-  };
-  if (done(lo)) return lo;
-  for (int i = 0; i < 24; ++i) {
-    const double mid = 0.5 * (lo + hi);
-    if (done(mid)) hi = mid; else lo = mid;
-  }
-  return hi;
-}
-
 // How a weight gradient a0 and an input gradient a1 that do not depend on each other are launched: together in tiles of bn
 // (first_is_1: a1's tiles, the longer ones, lead), or apart (bn = 0).  Measured apart / together, the pass that forms dL included:
 // 8192 tokens x 3072 x 6400 533 / 490 us, 8192 x 1536 x 51200 2300 / 2155, 3008 x 3072 x 12800 420 / 345, 1536 x 3072 x 2048
@@ -879,7 +863,7 @@ inline V2Dual v2_dual(const GemmArgs& a0, const GemmArgs& a1) {
     const int n0 = ((a0.M + bm - 1) / bm) * ((a0.N + bn - 1) / bn), n1 = ((a1.M + bm - 1) / bm) * ((a1.N + bn - 1) / bn);
     if (one_each && n0 + n1 > cus) return 1e30;
     const double c0 = v2_tile_cost(bn, nk0, one_each, 0.46), c1 = v2_tile_cost(bn, nk1, one_each, 0.46);
-    return 2.0 + (d.first_is_1 ? v2_two_batches(cus, n1, c1, n0, c0) : v2_two_batches(cus, n0, c0, n1, c1));
+    return 2.0 + (d.first_is_1 ? two_batches(cus, n1, c1, n0, c0) : two_batches(cus, n0, c0, n1, c1));
   };
   if (a0.K % (2 * V2_BK) == 0 && a1.K % V2_BK == 0 && a1.K >= 2 * V2_BK) {
     const double t = price(V2_B, false);

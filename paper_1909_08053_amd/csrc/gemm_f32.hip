@@ -407,6 +407,15 @@ __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_dual_kerne
   else f32_split_tile<true, true, EPI_STORE>(x, id - tiles_w);
 }
 
+// The same in 64 x 64 tiles; the longer ones lead.
+__global__ __launch_bounds__(512, 2) void gemm_f32_tile_dual_kernel(GemmArgs w, GemmArgs x) {
+  const int tiles_w = ((w.M + 63) / 64) * ((w.N + 63) / 64), tiles_x = ((x.M + 63) / 64) * ((x.N + 63) / 64);
+  const bool x_first = x.K > w.K;
+  const int id = blockIdx.x, first = x_first ? tiles_x : tiles_w, at = id < first ? id : id - first;
+  if ((id < first) == x_first) f32_tile<true, true, EPI_STORE, 64, 64, 2, 2, 2, 64>(x, at);
+  else f32_tile<false, false, EPI_STORE, 64, 64, 2, 2, 2, 64>(w, at);
+}
+
 // An input gradient and column sums beside it (the workgroups behind the tiles): a launch of 5 us saved, 1024 tokens x 1024 1270 ->
 // 1264 us a step.
 __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_colsum_kernel(GemmArgs a, ColsumJob job) {
@@ -522,13 +531,23 @@ hipError_t launch_gemm_f32_dgrad_colsum(const GemmArgs& a, const ColsumJob& j, h
 }
 
 hipError_t launch_gemm_f32_dual(const GemmArgs& w, const GemmArgs& x, hipStream_t st) {
-  auto tiles = [](const GemmArgs& a) { return ((a.M + 31) / 32) * ((a.N + 31) / 32); };
-  if (f32_pick(w.M, w.N, w.K) == 32 && f32_pick(x.M, x.N, x.K) == 32) {
-    hipLaunchKernelGGL(gemm_f32_split_dual_kernel, dim3(tiles(w) + tiles(x)), dim3(64 * kF32SplitWaves), 0, st, w, x);
-    return hipGetLastError();
+  const int b = f32_dual_pick(w.M, w.N, w.K, x.M, x.N, x.K);
+  if (b == 0) {
+    if (hipError_t e = launch_gemm_f32(w, st); e != hipSuccess) return e;
+    return launch_gemm_f32(x, st);
   }
-  if (hipError_t e = launch_gemm_f32(w, st); e != hipSuccess) return e;
-  return launch_gemm_f32(x, st);
+  auto tiles = [b](const GemmArgs& a) { return ((a.M + b - 1) / b) * ((a.N + b - 1) / b); };
+  const dim3 grid(tiles(w) + tiles(x));
+  if (b == 32) {
+    hipLaunchKernelGGL(gemm_f32_split_dual_kernel, grid, dim3(64 * kF32SplitWaves), 0, st, w, x);
+  } else {
+    constexpr size_t k0 = f32_tile_lds<false, false, 64, 64, 2, 2, 2, 64>(), k1 = f32_tile_lds<true, true, 64, 64, 2, 2, 2, 64>();
+    constexpr size_t kLds = k0 > k1 ? k0 : k1;
+    static LdsAttrOnce attr;
+    if (hipError_t e = attr.ensure((const void*)gemm_f32_tile_dual_kernel, (int)kLds); e != hipSuccess) return e;
+    hipLaunchKernelGGL(gemm_f32_tile_dual_kernel, grid, dim3(512), kLds, st, w, x);
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t st) {

@@ -1,5 +1,6 @@
 // Which of the three fp32 GEMM kernels (gemm_f32.hip) a problem takes.  Host arithmetic only.
 #pragma once
+#include "schedule.h"
 
 namespace mlm {
 
@@ -34,6 +35,29 @@ inline int f32_pick(int M, int N, int K) {
   return t64 <= t128 ? 64 : 128;
 }
 
+inline double f32_us(int M, int N, int K) {
+  const int b = f32_pick(M, N, K);
+  return b == 32 ? f32_split_us(M, N, K) : f32_tile_us(b, f32_tiles(b, M, N), K);
+}
+
+// A weight gradient (0) and an input gradient (1) that do not depend on each other: the tile of one launch for both, or 0 for two
+// launches.  32 where both take the split kernel; 64 where tiles of that size, those of longer k first, end a twentieth earlier than
+// the two.  Tokens x width x vocabulary, the pass that forms dL included, two launches / one: 512 x 1024 x 4096 115 / 93 us,
+// 600 x 768 x 6000 167 / 129, 1000 x 1536 x 3200 202 / 182, 700 x 1920 x 2560 156 / 128, 1024 x 640 x 16384 467 / 387, 900 x 384 x
+// 30592 716 / 613, 333 x 960 x 1032 36 / 33; but 1024 x 1024 x 8192, whose longer tiles are one per unit, 287 / 296.
+inline int f32_dual_pick(int M0, int N0, int K0, int M1, int N1, int K1) {
+  if (f32_pick(M0, N0, K0) == 32 && f32_pick(M1, N1, K1) == 32) return 32;
+  const bool swap = K1 > K0;                                   // l: the longer tiles, s: the others
+  const int cus = gemm_cu_count(), t0 = (int)f32_tiles(64, M0, N0), t1 = (int)f32_tiles(64, M1, N1);
+  const int nl = swap ? t1 : t0, ns = swap ? t0 : t1;
+  const double kl = (swap ? K1 : K0) / 1024.0, ks = (swap ? K0 : K1) / 1024.0;
+  const double beside = nl <= cus ? ns * ks / (2 * cus - nl) + 0.5 * ks : kl;      // k that a longer tile does with others beside it
+  const double both = 4.0 + (nl + ns <= cus ? 17.3 * kl
+                             : beside < kl  ? 31.5 * beside + 17.3 * (kl - beside)
+                                            : two_batches(2 * cus, nl, 31.5 * kl, ns, 31.5 * ks));
+  return both < 0.95 * (2.0 + f32_us(M0, N0, K0) + f32_us(M1, N1, K1)) ? 64 : 0;
+}
+
 // n weight gradients of the same K that do not depend on each other: the tile of one launch for all of them, or 0 for a launch
 // each.  32 where each of them takes the split kernel; else the tiles of all share their partly filled last round.  The four of a
 // layer shard, apart / together (tokens, width, FFN width, split): 1024, 1024, 4096, 1 225 / 208 us; the same split four ways 73 / 57;
@@ -43,9 +67,8 @@ inline int f32_group_pick(const int* M, const int* N, int n, int K) {
   double apart = 0.0, t64 = 0.0, t128 = 0.0;
   bool split = true;
   for (int q = 0; q < n; ++q) {
-    const int b = f32_pick(M[q], N[q], K);
-    split = split && b == 32;
-    apart += 2.0 + (b == 32 ? f32_split_us(M[q], N[q], K) : f32_tile_us(b, f32_tiles(b, M[q], N[q]), K));
+    split = split && f32_pick(M[q], N[q], K) == 32;
+    apart += 2.0 + f32_us(M[q], N[q], K);
     t64 += f32_tiles(64, M[q], N[q]);
     t128 += f32_tiles(128, M[q], N[q]);
   }
