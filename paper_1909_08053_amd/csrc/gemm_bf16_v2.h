@@ -578,14 +578,17 @@ struct GemmGroup {
   int n;
   int xcd_order;                       // one walk through the tiles of all problems
   int tile_begin[kMaxGroup + 1];       // first work item of each problem; tile_begin[n] = grid size
+  int full;                            // whole tiles; the work items behind them are k-pieces of the last problem's last tiles
   GemmArgs args[kMaxGroup];
   V2Plan plan[kMaxGroup];
 };
 
-template <bool A_KC, bool B_KC, int BN, int KE, bool DEEP>
-__global__ __launch_bounds__((v2_nw<BN, DEEP>() * 64), 2) void gemm_bf16_v2_group_kernel(GemmGroup g) {
+// SPLIT: with k-pieces (V2GroupSplit), whose partial tiles go to splitk_ws
+template <bool A_KC, bool B_KC, int BN, int KE, bool DEEP, bool SPLIT>
+__global__ __launch_bounds__((v2_nw<BN, DEEP>() * 64), 2) void gemm_bf16_v2_group_kernel(GemmGroup g, float* splitk_ws) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  const int pid = g.xcd_order ? v2_xcd_order(blockIdx.x, g.tile_begin[g.n], g.plan[0].window) : blockIdx.x;
+  const int id = blockIdx.x;
+  const int pid = g.xcd_order && (!SPLIT || id < g.full) ? v2_xcd_order(id, g.full, g.plan[0].window) : id;
   // the problem index is uniform over the workgroup: select its arguments with scalar compares
   int q = 0;
 #pragma unroll
@@ -596,7 +599,7 @@ __global__ __launch_bounds__((v2_nw<BN, DEEP>() * 64), 2) void gemm_bf16_v2_grou
 #pragma unroll
   for (int i = 1; i < kMaxGroup; ++i)
     if (q == i) { a = g.args[i]; plan = g.plan[i]; first = g.tile_begin[i]; }
-  gemm_v2_work_item<A_KC, B_KC, EPI_STORE, BN, KE, DEEP>(a, plan, nullptr, pid - first, lds_raw);
+  gemm_v2_work_item<A_KC, B_KC, EPI_STORE, BN, KE, DEEP>(a, plan, SPLIT ? splitk_ws : nullptr, pid - first, lds_raw);
 }
 
 // Tail tiles: sum the k-pieces in piece order (deterministic) and apply the epilogue to the fp32 sums.  A wave owns
@@ -743,19 +746,47 @@ inline int v2_tiles(const GemmArgs& a, int bm, int bn) { return ((a.M + bm - 1) 
 
 // Estimated time (microseconds) of the tiles of all problems in one launch without a k-split.  The last round of the small
 // tile, where it leaves compute units with one workgroup, runs at that one's pace (1200 tiles of 128 slices, 2.34 rounds: 155 us).
-inline double v2_group_cost(const GemmArgs* probs, int n, int bn) {
+// lowest: the small tile at its cheaper price whatever the row counts (v2_small_slice).
+inline double v2_group_cost(const GemmArgs* probs, int n, int bn, bool lowest = false) {
   const int bm = bn == V2_SMALL ? V2_SMALL : V2_B, cus = gemm_cu_count(), per_round = bn == V2_SMALL ? 2 * cus : cus;
   int tiles = 0;
   for (int q = 0; q < n; ++q) tiles += v2_tiles(probs[q], bm, bn);
   double ss = 0.0;                     // mean over the tiles
-  for (int q = 0; q < n; ++q) ss += v2_small_slice((probs[q].M + bm - 1) / bm) * v2_tiles(probs[q], bm, bn) / tiles;
+  for (int q = 0; q < n; ++q) ss += v2_small_slice(lowest ? 32 : (probs[q].M + bm - 1) / bm) * v2_tiles(probs[q], bm, bn) / tiles;
   const int nk = v2_slices(probs[0].K), rem = tiles % per_round;
   return (tiles / per_round) * v2_tile_cost(bn, nk, false, ss) + (rem ? v2_tile_cost(bn, nk, rem <= cus, ss) : 0.0);
 }
 
-template <bool A_KC, bool B_KC, int BN, int KE, bool DEEP>
-hipError_t launch_gemm_bf16_v2_group_ke(const GemmArgs* probs, int n, hipStream_t st) {
-  auto kern = gemm_bf16_v2_group_kernel<A_KC, B_KC, BN, KE, DEEP>;
+// The large tiles of all problems in one launch, the last `rem` of problem `last` (the one of most tiles) in `split` k-pieces each:
+// the same trade as in v2_plan for the partly filled last round that the problems share.  split = 0: none.
+// The four gradients of a layer shard (tokens x width, ways of the split), the better of 128- and 256-wide tiles against this:
+// 4096 x 2560, 4 176 / 162 us, 6176 x 2560, 4 253 / 214, 7000 x 2304, 3 309 / 264, 8192 x 1920, 2 347 / 328, 6000 x 1152 246 / 192, 4096 x 1056
+// 173 / 124, 8192 x 1216 333 / 260; but not where short k favours the small tile, at its cheaper price: 1536 x 1056 51 / 61, 2000 x
+// 1152 71 / 82.
+struct V2GroupSplit { int last, rem, split; double cost; };
+inline V2GroupSplit v2_group_split(const GemmArgs* probs, int n) {
+  const int cus = gemm_cu_count(), nk = v2_slices(probs[0].K);
+  V2GroupSplit g = {0, 0, 0, 1e30};
+  int tiles = 0;
+  for (int q = 0; q < n; ++q) {
+    const int t = v2_tiles(probs[q], V2_B, V2_B);
+    tiles += t;
+    if (t > v2_tiles(probs[g.last], V2_B, V2_B)) g.last = q;
+  }
+  g.rem = tiles % cus;
+  if (tiles < cus || g.rem == 0 || g.rem > v2_tiles(probs[g.last], V2_B, V2_B)) return g;
+  for (int sp = 2; sp <= 16 && sp * g.rem <= cus && nk / sp >= 8; ++sp) {
+    const double traffic = (double)g.rem * sp * (V2_B * (double)V2_B * 4.0) / 5.0e6;
+    const double t = (tiles / cus) * v2_tile_cost(V2_B, nk, false, 0.0) + v2_tile_cost(V2_B, (nk + sp - 1) / sp, false, 0.0) + traffic +
+                     v2_fixup_cost(traffic);
+    if (t < g.cost) { g.cost = t; g.split = sp; }
+  }
+  return g;
+}
+
+template <bool A_KC, bool B_KC, int BN, int KE, bool DEEP, bool SPLIT>
+hipError_t launch_gemm_bf16_v2_group_ke(const GemmArgs* probs, int n, const V2GroupSplit& sp, float* splitk_ws, hipStream_t st) {
+  auto kern = gemm_bf16_v2_group_kernel<A_KC, B_KC, BN, KE, DEEP, SPLIT>;
   constexpr size_t kLds = v2_lds_bytes<A_KC, B_KC, BN, DEEP>();
   static LdsAttrOnce attr;
   if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
@@ -764,28 +795,41 @@ hipError_t launch_gemm_bf16_v2_group_ke(const GemmArgs* probs, int n, hipStream_
   g.n = n;
   int total = 0;
   for (int q = 0; q < n; ++q) {
-    g.args[q] = probs[q];
-    g.plan[q] = v2_plan(probs[q].M, probs[q].N, probs[q].K, false, BN);
+    const GemmArgs& a = probs[!SPLIT ? q : q == n - 1 ? sp.last : q == sp.last ? n - 1 : q];       // (sp.last goes last)
+    g.args[q] = a;
+    g.plan[q] = v2_plan(a.M, a.N, a.K, false, BN);
     g.tile_begin[q] = total;
     total += g.plan[q].full_tiles;
   }
+  g.full = total;
+  if (SPLIT) {
+    V2Plan& p = g.plan[n - 1];
+    p.full_tiles -= sp.rem;
+    p.tail_tiles = sp.rem;
+    p.split = sp.split;
+    g.full -= sp.rem;
+    total = g.full + sp.rem * sp.split;
+  }
   for (int q = n; q <= kMaxGroup; ++q) g.tile_begin[q] = total;
   for (int strips = 0; strips < 2; ++strips) {         // strips for all problems where one gains by them
-    for (int q = 0; q < n; ++q) v2_set_walk(&g.plan[q], v2_window<BN, DEEP>(), probs[q].K, strips != 0);
+    for (int q = 0; q < n; ++q) v2_set_walk(&g.plan[q], v2_window<BN, DEEP>(), probs[0].K, strips != 0);
     for (int q = 0; q < n; ++q) g.xcd_order |= g.plan[q].strip != 0;
     if (!g.xcd_order) break;
   }
-  hipLaunchKernelGGL(kern, dim3(total), dim3(v2_nw<BN, DEEP>() * 64), kLds, st, g);
+  hipLaunchKernelGGL(kern, dim3(total), dim3(v2_nw<BN, DEEP>() * 64), kLds, st, g, splitk_ws);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess || !SPLIT) return e;
+  hipLaunchKernelGGL((gemm_v2_fixup_kernel<EPI_STORE>), dim3(V2_B / kFixRows, sp.rem), dim3(256), 0, st, g.args[n - 1], g.plan[n - 1],
+                     splitk_ws);
   return hipGetLastError();
 }
 
-template <bool A_KC, bool B_KC, int BN, bool DEEP>
-hipError_t launch_gemm_bf16_v2_group(const GemmArgs* probs, int n, hipStream_t st) {
+template <bool A_KC, bool B_KC, int BN, bool DEEP, bool SPLIT = false>
+hipError_t launch_gemm_bf16_v2_group(const GemmArgs* probs, int n, hipStream_t st, const V2GroupSplit& sp = {}, float* splitk_ws = nullptr) {
   switch (v2_k_end<BN>(probs[0].K)) {
-    case KE_PAIR: return launch_gemm_bf16_v2_group_ke<A_KC, B_KC, BN, KE_PAIR, DEEP>(probs, n, st);
+    case KE_PAIR: return launch_gemm_bf16_v2_group_ke<A_KC, B_KC, BN, KE_PAIR, DEEP, SPLIT>(probs, n, sp, splitk_ws, st);
     case KE_SLICE:
-      if constexpr (BN != V2_SMALL) return launch_gemm_bf16_v2_group_ke<A_KC, B_KC, BN, KE_SLICE, DEEP>(probs, n, st);
-    default: return launch_gemm_bf16_v2_group_ke<A_KC, B_KC, BN, KE_ANY, DEEP>(probs, n, st);
+      if constexpr (BN != V2_SMALL) return launch_gemm_bf16_v2_group_ke<A_KC, B_KC, BN, KE_SLICE, DEEP, SPLIT>(probs, n, sp, splitk_ws, st);
+    default: return launch_gemm_bf16_v2_group_ke<A_KC, B_KC, BN, KE_ANY, DEEP, SPLIT>(probs, n, sp, splitk_ws, st);
   }
 }
 

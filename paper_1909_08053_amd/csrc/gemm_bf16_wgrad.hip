@@ -24,6 +24,12 @@ hipError_t launch_gemm_bf16_wgrad_group(const GemmArgs* probs, int n, float* spl
     const double big = v2_group_cost(probs, n, V2_B), small = v2_group_cost(probs, n, V2_SMALL);
     const int forced = gemm_v2_forced_bn();
     const bool use_small = forced ? forced == V2_SMALL : small < big;
+    if (!gemm_v2_group_off() && !forced && splitk_ws) {
+      const V2GroupSplit sp = v2_group_split(probs, n);
+      const double whole = use_small ? v2_group_cost(probs, n, V2_SMALL, true) : big;
+      if (sp.split && sp.cost < 0.97 * whole && sp.cost + 2.0 < alone)
+        return launch_gemm_bf16_v2_group<false, false, V2_B, false, true>(probs, n, st, sp, splitk_ws);
+    }
     if (!gemm_v2_group_off() && (use_small ? small : big) + 2.0 < alone) {
       int tiles = 0;
       for (int q = 0; q < n; ++q) tiles += v2_tiles(probs[q], V2_SMALL, V2_SMALL);
