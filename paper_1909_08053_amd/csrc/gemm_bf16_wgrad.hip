@@ -11,7 +11,7 @@ hipError_t launch_gemm_bf16_wgrad(const GemmArgs& a, hipStream_t st) {
 
 // The weight gradients of a layer shard (same operand layout, same k = tokens).  One grouped launch, in the tile size that
 // fills the chip better, when the cost model says the shared last round beats the separate launches with their
-// k-splits; separate launches otherwise.
+// k-splits (v2_group_split: large tiles with that round split along k); separate launches otherwise.
 hipError_t launch_gemm_bf16_wgrad_group(const GemmArgs* probs, int n, float* splitk_ws, hipStream_t st) {
   bool groupable = n >= 2 && n <= kMaxGroup;
   double alone = 0.0;

@@ -62,18 +62,15 @@ def step_roles(cfg_dims):
         ("F11 merge of the per-tile (m, s, t)", "ce_tile_merge", "-", 0),
         ("F12 loss merge over shards", "ce_merge", "-", 0),
         ("B1  dlogits in place", "dlogits", "B", 2 * T * Vl * 2),
-        ("B1  dE = Hf^T dL 3072x8192x6400", "gemm_bf16_v2_kernel", "F", GF(T, H, Vl)),
-        ("B1  fix-up", "fixup", "-", 0),
-        ("B1  dHf partial = dL E^T 8192x6400x3072", "gemm_bf16_v2_kernel", "F", GF(T, H, Vl)),
-        ("B1  fix-up of dHf's split half round", "fixup", "-", 0),
+        ("B1  dE = Hf^T dL 3072x8192x6400, dHf partial = dL E^T 8192x6400x3072", "gemm_bf16_v2_dual_kernel", "F", 2 * GF(T, H, Vl)),
         ("B2  reduction + final layer norm backward", "ln_bwd", "B", 3 * TH),
         ("B3+B4  dG = (dX2 B^T) o GeLU' 8192x3072x1536", "gemm_bf16_v2_kernel", "F", GF(T, H, Fl)),
         ("B4  da partial sums", "colsum_partial", "B", T * Fl * 2),
         ("B5  dU2 partial = dG A^T 8192x1536x3072", "gemm_bf16_v2_kernel", "F", GF(T, Fl, H)),
         ("B6  reduction + layer norm 2 backward + residual", "ln_bwd", "B", 4 * TH),
         ("B7  dC = dX1 Wo^T 8192x3072x384", "gemm_bf16_v2_kernel", "F", GF(T, H, Hl)),
-        ("B8  attention backward dQ (+ delta)", "attn_bwd_dq", "Q", 0),
-        ("B8  attention backward dK, dV", "attn_bwd_dkv", "K", 2 * att),
+        ("B8  attention backward, delta", "attn_delta", "-", 0),
+        ("B8  attention backward dQ, dK, dV in one launch", "attn_bwd_bf16", "F", 2 * att),
         ("B9  dbqkv partial sums", "colsum_partial", "B", T * 3 * Hl * 2),
         ("B9  dU partial = dQKV Wqkv^T 8192x1152x3072", "gemm_bf16_v2_kernel", "F", GF(T, H, 3 * Hl)),
         ("B3,B5,B7,B9  dB, dA, dWqkv, dWo in one grouped launch", "group_kernel", "F",
@@ -108,12 +105,8 @@ def position_table(trace_csv, steps):
         tot += a
         label, _, kind, w = roles[k]
         rate = ""
-        if kind == "K":
-            both = a + st.mean(dur[k - 1])
-            rate = f"{w / both / 1e6:7.0f} TFLOP/s (dQ + dK/dV, {w / 1e9:.1f} GF)"
-            sums["mfma"] += a
-        elif kind in ("F", "Q"):
-            rate = f"{w / a / 1e6:7.0f} TFLOP/s" if kind == "F" else ""
+        if kind == "F":
+            rate = f"{w / a / 1e6:7.0f} TFLOP/s"
             sums["mfma"] += a
         elif kind == "B":
             rate = f"{w / a / 1e3:7.0f} GB/s"
