@@ -431,6 +431,8 @@ MLM_API int mlm_attn_shard_bwd_input(const mlm_dims* dims, const void* dx1, cons
  *   dWqkv_r = u^T dqkv_r   [H, 3 H_l]      dWo_r = ctx_r^T dz1   [H_l, H]
  *   dA_r    = u2^T dg_r    [H, F_l]        dB_r  = y_r^T dz2     [F_l, H]
  * dz1 / dz2: the [T,H] gradients the two backward calls were given as dx1 / dx2 (still intact).
+ * An output may lie over operands that only earlier products of the order dB_r, dA_r, dWqkv_r, dWo_r read (dA_r over y_r):
+ * the four then run one after the other.
  * ws: MLM_WS_MLP_BWD bytes is enough. */
 MLM_API int mlm_layer_shard_wgrads(const mlm_dims* dims, const void* u, const void* dqkv_r, const void* ctx_r,
                            const void* dz1, const void* u2, const void* dg_r, const void* y_r, const void* dz2,

@@ -130,9 +130,20 @@ GemmArgs gemm_wgrad(int M, int N, int K, const void* X, const void* dY, void* dW
   return gemm_args(M, N, K, X, M, 0, dY, N, 0, dW, N);
 }
 
-bool overlap(const void* a, size_t na, const void* b, size_t nb) {
-  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
-  return x < y + nb && y < x + na;
+// Whether a launch may work on all of these products at once: no output overlaps an operand or another output, so that their
+// order does not show.
+bool independent(const GemmArgs* g, int n, size_t esz) {
+  auto apart = [&](const void* x, size_t nx, const void* y, size_t ny) {
+    const uintptr_t a = (uintptr_t)x, b = (uintptr_t)y;
+    return a >= b + ny * esz || b >= a + nx * esz;
+  };
+  for (int q = 0; q < n; ++q)
+    for (int r = 0; r < n; ++r) {
+      const size_t mn = (size_t)g[q].M * g[q].N;
+      if (!apart(g[q].C, mn, g[r].A, (size_t)g[r].M * g[r].K) || !apart(g[q].C, mn, g[r].B, (size_t)g[r].K * g[r].N)) return false;
+      if (q != r && !apart(g[q].C, mn, g[r].C, (size_t)g[r].M * g[r].N)) return false;
+    }
+  return true;
 }
 
 #define MLM_TRY_HIP(expr)                    \
@@ -620,8 +631,12 @@ MLM_API int mlm_layer_shard_wgrads(const mlm_dims* dims, const void* u, const vo
   // k = tokens in all four: dW = X^T dY
   GemmArgs g[4] = {gemm_wgrad(L.Fl, dims->H, L.T, y_r, dz2, dB_r), gemm_wgrad(dims->H, L.Fl, L.T, u2, dg_r, dA_r),
                    gemm_wgrad(dims->H, 3 * L.Hl, L.T, u, dqkv_r, dWqkv_r), gemm_wgrad(L.Hl, dims->H, L.T, ctx_r, dz1, dWo_r)};
-  if (dims->dtype == MLM_BF16) return hip_status(launch_gemm_bf16_wgrad_group(g, 4, (float*)ws, st));
-  return hip_status(launch_gemm_f32_wgrads(g, 4, st));
+  float* sk = dims->dtype == MLM_BF16 ? (float*)ws : nullptr;
+  if (!independent(g, 4, L.esz)) {                     // in this order: dA over y_r, or dWqkv_r over dg_r, comes out right
+    for (const GemmArgs& q : g) MLM_TRY_HIP(run_gemm(dims->dtype, q, st, sk));
+    return MLM_OK;
+  }
+  return hip_status(sk ? launch_gemm_bf16_wgrad_group(g, 4, sk, st) : launch_gemm_f32_wgrads(g, 4, st));
 }
 
 MLM_API int mlm_vocab_ce_shard_fwd(const mlm_dims* dims, const void* hf, const void* E_r, const int32_t* targets, float* m_r,
@@ -694,15 +709,11 @@ MLM_API int mlm_vocab_ce_shard_bwd(const mlm_dims* dims, const void* hf, const v
     g.Mrow = M; g.Srow = S; g.loss_w = loss_w; g.loss_stats = loss_stats;
     MLM_TRY_HIP(run_gemm(dt, g, st, sk));
   }
-  const GemmArgs gE = gemm_wgrad(dims->H, L.Vl, L.T, hf, dL, dE_r), gH = gemm_dgrad(L.T, dims->H, L.Vl, dL, E_r, dhf_partial_r);
+  const GemmArgs g[2] = {gemm_wgrad(dims->H, L.Vl, L.T, hf, dL, dE_r), gemm_dgrad(L.T, dims->H, L.Vl, dL, E_r, dhf_partial_r)};
   // one launch for both, unless the caller's buffers make their order visible (dhf over hf)
-  const size_t bE = (size_t)dims->H * L.Vl * L.esz, bH = (size_t)L.T * dims->H * L.esz, bL = (size_t)L.T * L.Vl * L.esz;
-  const bool apart = overlap(dE_r, bE, dhf_partial_r, bH) || overlap(dE_r, bE, E_r, bE) || overlap(dE_r, bE, hf, bH) ||
-                     overlap(dE_r, bE, dL, bL) || overlap(dhf_partial_r, bH, E_r, bE) || overlap(dhf_partial_r, bH, hf, bH) ||
-                     overlap(dhf_partial_r, bH, dL, bL);
-  if (!apart) return hip_status(dt == MLM_BF16 ? launch_gemm_bf16_dual(gE, gH, sk, st) : launch_gemm_f32_dual(gE, gH, st));
-  MLM_TRY_HIP(run_gemm(dt, gE, st, sk));
-  MLM_TRY_HIP(run_gemm(dt, gH, st, sk));
+  if (independent(g, 2, L.esz))
+    return hip_status(dt == MLM_BF16 ? launch_gemm_bf16_dual(g[0], g[1], sk, st) : launch_gemm_f32_dual(g[0], g[1], st));
+  for (const GemmArgs& q : g) MLM_TRY_HIP(run_gemm(dt, q, st, sk));
   return MLM_OK;
 }
 
