@@ -149,8 +149,9 @@ __device__ __forceinline__ void f32_static_for(F&& f, std::integer_sequence<int,
   (f(std::integral_constant<int, N>{}), ...);
 }
 
-// BM x BN tile; WM x WN waves of (BM / WM) x (BN / WN), KS groups of them that share every KT-deep operand tile along k.
-template <bool A_KC, bool B_KC, int EPI, int BM, int BN, int WM, int WN, int KS, int KT>
+// BM x BN tile; WM x WN waves of (BM / WM) x (BN / WN), KS groups of them that share every KT-deep operand tile along k.  CH: a wave
+// keeps that many sums of an element, of every CH-th four k each, and adds them at the end: KS CH chains of K / (KS CH) products.
+template <bool A_KC, bool B_KC, int EPI, int BM, int BN, int WM, int WN, int KS, int KT, int CH = 1>
 __device__ __forceinline__ void f32_tile(const GemmArgs& a, int tile) {
   constexpr int NT = 64 * WM * WN * KS, TM = BM / WM / 16, TN = BN / WN / 16, NC = KT / 16 / KS;
   typedef F32Tile<A_KC, BM, KT, NT> TA;
@@ -164,13 +165,17 @@ __device__ __forceinline__ void f32_tile(const GemmArgs& a, int tile) {
   const int m0 = (tile % tiles_m) * BM, n0 = (tile / tiles_m) * BN;
   const float* A = (const float*)a.A;
   const float* B = (const float*)a.B;
-  floatx4 acc[TM][TN];
+  static_assert(CH == 1 || CH == 4, "the four MFMAs of a chunk");
+  floatx4 sum[CH][TM][TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int h = 0; h < CH; ++h)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[h][i][j][e] = 0.f;
+  floatx4 (&acc)[TM][TN] = sum[0];
 
   // Tile kt + 1 waits in registers while the first half of tile kt is multiplied, is written to the other LDS buffer in
   // the middle of it (free since the last barrier) and tile kt + 2 is requested vector by vector behind the writes: a
@@ -224,7 +229,7 @@ __device__ __forceinline__ void f32_tile(const GemmArgs& a, int tile) {
     for (int c = 0; c < NC; ++c) {
       f32_static_for([&](auto n_c) {                  // (a loop of this length is past the compiler's unrolling limit)
         constexpr int n = decltype(n_c)::value, q = n / (TM * TN), i = n / TN % TM, j = n % TN;
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[c & 1][j][q], fa[c & 1][i][q], acc[i][j], 0, 0, 0);
+        sum[q % CH][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[c & 1][j][q], fa[c & 1][i][q], sum[q % CH][i][j], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
         if (NEXT && c == NC - 1 && n == 0) __syncthreads();
         if (n < NF) {
@@ -249,6 +254,14 @@ __device__ __forceinline__ void f32_tile(const GemmArgs& a, int tile) {
   for (; kt + 2 < nwhole; ++kt) multiply(yes_t{}, yes_t{}, kt);
   for (; kt + 1 < nk; ++kt) multiply(yes_t{}, no_t{}, kt);
   multiply(no_t{}, no_t{}, kt);
+  if constexpr (CH == 4) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i][j][e] = (sum[0][i][j][e] + sum[1][i][j][e]) + (sum[2][i][j][e] + sum[3][i][j][e]);
+  }
   if (KS > 1) __syncthreads();
   if (KS > 1) {
     // the groups' sums meet in LDS ([group - 1][wave][value][lane]) and are added in group order
@@ -392,11 +405,11 @@ __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_group_kern
   const int tile = f32_group_at(g, &a);
   f32_split_tile<false, false, EPI_STORE>(a, tile);
 }
-template <int BM, int BN, int WM, int WN, int KS, int KT>
+template <int BM, int BN, int WM, int WN, int KS, int KT, int CH>
 __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_group_kernel(F32Group g) {
   GemmArgs a;
   const int tile = f32_group_at(g, &a);
-  f32_tile<false, false, EPI_STORE, BM, BN, WM, WN, KS, KT>(a, tile);
+  f32_tile<false, false, EPI_STORE, BM, BN, WM, WN, KS, KT, CH>(a, tile);
 }
 
 // A weight gradient (its tiles first) and an input gradient that do not depend on each other: 256 x 512 x 256 and 256 x 256 x 512
@@ -408,12 +421,13 @@ __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_dual_kerne
 }
 
 // The same in 64 x 64 tiles; the longer ones lead.
+template <int CH>
 __global__ __launch_bounds__(512, 2) void gemm_f32_tile_dual_kernel(GemmArgs w, GemmArgs x) {
   const int tiles_w = ((w.M + 63) / 64) * ((w.N + 63) / 64), tiles_x = ((x.M + 63) / 64) * ((x.N + 63) / 64);
   const bool x_first = x.K > w.K;
   const int id = blockIdx.x, first = x_first ? tiles_x : tiles_w, at = id < first ? id : id - first;
-  if ((id < first) == x_first) f32_tile<true, true, EPI_STORE, 64, 64, 2, 2, 2, 64>(x, at);
-  else f32_tile<false, false, EPI_STORE, 64, 64, 2, 2, 2, 64>(w, at);
+  if ((id < first) == x_first) f32_tile<true, true, EPI_STORE, 64, 64, 2, 2, 2, 64, CH>(x, at);
+  else f32_tile<false, false, EPI_STORE, 64, 64, 2, 2, 2, 64, CH>(w, at);
 }
 
 // An input gradient and column sums beside it (the workgroups behind the tiles): a launch of 5 us saved, 1024 tokens x 1024 1270 ->
@@ -465,10 +479,10 @@ static hipError_t launch_f32_tile_colsum(const GemmArgs& a, const ColsumJob& j, 
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WM, int WN, int KS, int KT>
+template <int BM, int BN, int WM, int WN, int KS, int KT, int CH>
 static hipError_t launch_f32_tile_group(const F32Group& g, int total, hipStream_t st) {
   constexpr size_t kLds = f32_tile_lds<false, false, BM, BN, WM, WN, KS, KT>();
-  auto kern = gemm_f32_tile_group_kernel<BM, BN, WM, WN, KS, KT>;
+  auto kern = gemm_f32_tile_group_kernel<BM, BN, WM, WN, KS, KT, CH>;
   static LdsAttrOnce attr;
   if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(total), dim3(64 * WM * WN * KS), kLds, st, g);
@@ -488,7 +502,7 @@ static hipError_t launch_f32_layout(const GemmArgs& a, hipStream_t st) {
   }
 }
 
-// Weight gradients (both operands k-major, plain store) of one K in one launch where f32_group_pick says so, else one by one.
+// Weight gradients (both operands k-major, plain store) of one K, as f32_group_plan says.
 hipError_t launch_gemm_f32_wgrads(const GemmArgs* probs, int n, hipStream_t st) {
   bool together = n >= 2 && n <= kF32Group;
   int M[kF32Group], N[kF32Group];
@@ -497,25 +511,31 @@ hipError_t launch_gemm_f32_wgrads(const GemmArgs* probs, int n, hipStream_t st) 
     M[q] = probs[q].M;
     N[q] = probs[q].N;
   }
-  const int b = together ? f32_group_pick(M, N, n, probs[0].K) : 0;
-  if (b == 0) {
-    for (int q = 0; q < n; ++q)
+  const F32GroupPlan p = together ? f32_group_plan(M, N, n, probs[0].K) : F32GroupPlan{};
+  auto launch = [&](int b, int chains, bool wide, bool narrow) {      // those that take the 128-wide tile alone, and / or the others
+    F32Group g;
+    memset(&g, 0, sizeof(g));
+    int total = 0, m = 0;
+    for (int q = 0; q < n; ++q) {
+      if (!(f32_pick(M[q], N[q], probs[q].K) == 128 ? wide : narrow)) continue;
+      g.a[m] = probs[q];
+      g.tile_begin[m++] = total;
+      total += ((M[q] + b - 1) / b) * ((N[q] + b - 1) / b);
+    }
+    for (; m < kF32Group; ++m) g.tile_begin[m] = total;
+    if (b == 128) return launch_f32_tile_group<128, 128, 2, 2, 1, 32, 1>(g, total, st);
+    if (b == 64) return chains == 8 ? launch_f32_tile_group<64, 64, 2, 2, 2, 64, 4>(g, total, st)
+                                    : launch_f32_tile_group<64, 64, 2, 2, 2, 64, 1>(g, total, st);
+    hipLaunchKernelGGL(gemm_f32_split_group_kernel, dim3(total), dim3(64 * kF32SplitWaves), 0, st, g);
+    return hipGetLastError();
+  };
+  if (p.wide_apart)
+    if (hipError_t e = launch(128, 1, true, false); e != hipSuccess) return e;
+  if (p.tile) return launch(p.tile, p.chains, !p.wide_apart, true);
+  for (int q = 0; q < n; ++q)
+    if (!p.wide_apart || f32_pick(M[q], N[q], probs[q].K) != 128)
       if (hipError_t e = launch_gemm_f32(probs[q], st); e != hipSuccess) return e;
-    return hipSuccess;
-  }
-  F32Group g;
-  memset(&g, 0, sizeof(g));
-  int total = 0;
-  for (int q = 0; q < n; ++q) {
-    g.a[q] = probs[q];
-    g.tile_begin[q] = total;
-    total += ((M[q] + b - 1) / b) * ((N[q] + b - 1) / b);
-  }
-  for (int q = n; q < kF32Group; ++q) g.tile_begin[q] = total;
-  if (b == 64) return launch_f32_tile_group<64, 64, 2, 2, 2, 64>(g, total, st);
-  if (b == 128) return launch_f32_tile_group<128, 128, 2, 2, 1, 32>(g, total, st);
-  hipLaunchKernelGGL(gemm_f32_split_group_kernel, dim3(total), dim3(64 * kF32SplitWaves), 0, st, g);
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 hipError_t launch_gemm_f32_dgrad_colsum(const GemmArgs& a, const ColsumJob& j, hipStream_t st) {
@@ -530,8 +550,19 @@ hipError_t launch_gemm_f32_dgrad_colsum(const GemmArgs& a, const ColsumJob& j, h
   }
 }
 
+template <int CH>
+static hipError_t launch_f32_tile_dual(const GemmArgs& w, const GemmArgs& x, dim3 grid, hipStream_t st) {
+  constexpr size_t k0 = f32_tile_lds<false, false, 64, 64, 2, 2, 2, 64>(), k1 = f32_tile_lds<true, true, 64, 64, 2, 2, 2, 64>();
+  constexpr size_t kLds = k0 > k1 ? k0 : k1;
+  static LdsAttrOnce attr;
+  if (hipError_t e = attr.ensure((const void*)gemm_f32_tile_dual_kernel<CH>, (int)kLds); e != hipSuccess) return e;
+  hipLaunchKernelGGL(gemm_f32_tile_dual_kernel<CH>, grid, dim3(512), kLds, st, w, x);
+  return hipGetLastError();
+}
+
 hipError_t launch_gemm_f32_dual(const GemmArgs& w, const GemmArgs& x, hipStream_t st) {
-  const int b = f32_dual_pick(w.M, w.N, w.K, x.M, x.N, x.K);
+  const F32DualPick p = f32_dual_pick(w.M, w.N, w.K, x.M, x.N, x.K);
+  const int b = p.tile;
   if (b == 0) {
     if (hipError_t e = launch_gemm_f32(w, st); e != hipSuccess) return e;
     return launch_gemm_f32(x, st);
@@ -540,14 +571,9 @@ hipError_t launch_gemm_f32_dual(const GemmArgs& w, const GemmArgs& x, hipStream_
   const dim3 grid(tiles(w) + tiles(x));
   if (b == 32) {
     hipLaunchKernelGGL(gemm_f32_split_dual_kernel, grid, dim3(64 * kF32SplitWaves), 0, st, w, x);
-  } else {
-    constexpr size_t k0 = f32_tile_lds<false, false, 64, 64, 2, 2, 2, 64>(), k1 = f32_tile_lds<true, true, 64, 64, 2, 2, 2, 64>();
-    constexpr size_t kLds = k0 > k1 ? k0 : k1;
-    static LdsAttrOnce attr;
-    if (hipError_t e = attr.ensure((const void*)gemm_f32_tile_dual_kernel, (int)kLds); e != hipSuccess) return e;
-    hipLaunchKernelGGL(gemm_f32_tile_dual_kernel, grid, dim3(512), kLds, st, w, x);
+    return hipGetLastError();
   }
-  return hipGetLastError();
+  return p.chains == 8 ? launch_f32_tile_dual<4>(w, x, grid, st) : launch_f32_tile_dual<1>(w, x, grid, st);
 }
 
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t st) {

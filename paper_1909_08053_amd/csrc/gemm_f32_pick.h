@@ -40,42 +40,81 @@ inline double f32_us(int M, int N, int K) {
   return b == 32 ? f32_split_us(M, N, K) : f32_tile_us(b, f32_tiles(b, M, N), K);
 }
 
+// Launches that hold several problems.  No result gets further from the exact one by sharing a launch, so a tile's sums are at least
+// as many chains over k as those of the kernel that its problem takes alone: eight in the split kernel, two in the 64-wide tiles, one
+// in the 128-wide ones.  (Two chains in place of eight were up to 1.9 x further off, one in place of two 1.4 x: 55 tokens x 768 x 3072,
+// 1.3e-7 against 7.5e-8.)  64-wide tiles can form eight; their workgroup then has a compute unit to itself.
+
 // A weight gradient (0) and an input gradient (1) that do not depend on each other: the tile of one launch for both, or 0 for two
-// launches.  32 where both take the split kernel; 64 where tiles of that size, those of longer k first, end a twentieth earlier than
-// the two.  Tokens x width x vocabulary, the pass that forms dL included, two launches / one: 512 x 1024 x 4096 115 / 93 us,
-// 600 x 768 x 6000 167 / 129, 1000 x 1536 x 3200 202 / 182, 700 x 1920 x 2560 156 / 128, 1024 x 640 x 16384 467 / 387, 900 x 384 x
-// 30592 716 / 613, 333 x 960 x 1032 36 / 33; but 1024 x 1024 x 8192, whose longer tiles are one per unit, 287 / 296.
-inline int f32_dual_pick(int M0, int N0, int K0, int M1, int N1, int K1) {
-  if (f32_pick(M0, N0, K0) == 32 && f32_pick(M1, N1, K1) == 32) return 32;
+// launches, and the chains of its sums.  32 where both take the split kernel; 64 where tiles of that size, those of longer k first, end
+// a twentieth earlier than the two.  Tokens x width x vocabulary, the pass that forms dL included, two launches / one: 512 x 1024 x 4096
+// 115 / 94 us, 600 x 768 x 6000 167 / 131, 1000 x 1536 x 3200 202 / 182, 700 x 1920 x 2560 155 / 129, 1024 x 640 x 16384 469 / 394, 333 x
+// 960 x 1032 36 / 33; but 1024 x 1024 x 8192, whose longer tiles are one per unit, 287 / 296.  Eight chains: 390 x 672 x 16032 421 / 278, 128 x
+// 2232 x 21512 633 / 373, 4554 x 216 x 1168 124 / 90; not where the split kernel's workgroups find a unit each, which its price
+// does not see: 805 x 200 x 3176 60 / 65, 6000 x 1024 x 256 90 / 109.
+struct F32DualPick { int tile, chains; };
+inline F32DualPick f32_dual_pick(int M0, int N0, int K0, int M1, int N1, int K1) {
+  const int b0 = f32_pick(M0, N0, K0), b1 = f32_pick(M1, N1, K1), cus = gemm_cu_count();
+  if (b0 == 32 && b1 == 32) return {32, 8};
+  const bool split = b0 == 32 || b1 == 32;
+  if (split && (b0 == 32 ? f32_tiles(32, M0, N0) : f32_tiles(32, M1, N1)) <= cus) return {0, 0};
   const bool swap = K1 > K0;                                   // l: the longer tiles, s: the others
-  const int cus = gemm_cu_count(), t0 = (int)f32_tiles(64, M0, N0), t1 = (int)f32_tiles(64, M1, N1);
+  const int t0 = (int)f32_tiles(64, M0, N0), t1 = (int)f32_tiles(64, M1, N1);
   const int nl = swap ? t1 : t0, ns = swap ? t0 : t1;
   const double kl = (swap ? K1 : K0) / 1024.0, ks = (swap ? K0 : K1) / 1024.0;
   const double beside = nl <= cus ? ns * ks / (2 * cus - nl) + 0.5 * ks : kl;      // k that a longer tile does with others beside it
-  const double both = 4.0 + (nl + ns <= cus ? 17.3 * kl
-                             : beside < kl  ? 31.5 * beside + 17.3 * (kl - beside)
-                                            : two_batches(2 * cus, nl, 31.5 * kl, ns, 31.5 * ks));
-  return both < 0.95 * (2.0 + f32_us(M0, N0, K0) + f32_us(M1, N1, K1)) ? 64 : 0;
+  const double both = 4.0 + (split || nl + ns <= cus ? two_batches(cus, nl, 17.3 * kl, ns, 17.3 * ks)
+                             : beside < kl           ? 31.5 * beside + 17.3 * (kl - beside)
+                                                     : two_batches(2 * cus, nl, 31.5 * kl, ns, 31.5 * ks));
+  if (both >= 0.95 * (2.0 + f32_us(M0, N0, K0) + f32_us(M1, N1, K1))) return {0, 0};
+  return {64, split ? 8 : 2};
 }
 
-// n weight gradients of the same K that do not depend on each other: the tile of one launch for all of them, or 0 for a launch
-// each.  32 where each of them takes the split kernel; else the tiles of all share their partly filled last round.  The four of a
-// layer shard, apart / together (tokens, width, FFN width, split): 1024, 1024, 4096, 1 225 / 208 us; the same split four ways 73 / 57;
-// 333, 768, 3072, 1 77 / 53; 900, 640, 2560, 1 126 / 85; 2048, 768, 3072, 1 315 / 240; 4096, 1024, 4096, 1 806 / 753; 33, 2048, 8192, 1
-// 92 / 77; of 21 measured none slower.
-inline int f32_group_pick(const int* M, const int* N, int n, int K) {
+// Microseconds of one launch with t tiles of b x b in it, b = 64 or 128: per round of two tiles a unit, and per k tile of it.  (Fitted to
+// the four weight gradients of 103 layer shards of 12 .. 2726 tokens and 320 .. 2048 wide: within 6 % and, 128-wide, 2 %.  At short k
+// the stores decide, which f32_tile_us leaves out.)
+inline double f32_launch_us(int b, int chains, double t, int K) {
+  const int cus = gemm_cu_count(), nk = (K + (b == 64 ? 63 : 31)) / (b == 64 ? 64 : 32);
+  const double full = (double)(long)(t / (2 * cus)), rem = t - full * 2 * cus;
+  const double two = b == 128 ? 5.1 + 3.8 * nk : chains == 8 ? 3.5 + 2.2 * nk : 1.9 + 2.1 * nk;
+  const double one = b == 128 ? 2.9 + 2.0 * nk : chains == 8 ? 2.5 + 1.0 * nk : 1.6 + 1.04 * nk;
+  return (b == 128 ? 4.2 : 3.6) + (full + (rem > cus)) * two + (rem > 0 && rem <= cus ? one : 0.0);
+}
+
+// n weight gradients of the same K that do not depend on each other: how they are launched.  The four of a layer shard, a launch each /
+// as planned (tokens, width, ways of the split): 333, 768, 1 77 / 55 us; 1024, 768, 1 167 / 129; 1024, 1024, 4 73 / 60; 40, 768, 1 33 / 23 (eight
+// chains); 59, 736, 2 35 / 14; 33, 2048, 1 92 / 77 (128-wide); 372, 1912, 1 319 / 286 and 841, 984, 1 190 / 176 (128-wide ones in a launch of their
+// own).  All in one launch of 128-wide tiles would be a little faster still (1024, 1024, 1 219 / 206, 197), and less exact.
+struct F32GroupPlan {
+  int tile;              // of one launch for all of them; 0: a launch each
+  int chains;            // of the sums in 64-wide tiles
+  bool wide_apart;       // those that take the 128-wide tile alone share a launch of their own; `tile` is the others'
+  double us;
+};
+inline F32GroupPlan f32_group_plan(const int* M, const int* N, int n, int K) {
   double apart = 0.0, t64 = 0.0, t128 = 0.0;
-  bool split = true;
+  int n32 = 0, n128 = 0, rest = 0, rM[4], rN[4];
   for (int q = 0; q < n; ++q) {
-    split = split && f32_pick(M[q], N[q], K) == 32;
-    apart += 2.0 + f32_us(M[q], N[q], K);
+    const int b = f32_pick(M[q], N[q], K);
+    apart += b == 32 ? 2.0 + f32_split_us(M[q], N[q], K) : f32_launch_us(b, b == 64 ? 2 : 1, f32_tiles(b, M[q], N[q]), K);
     t64 += f32_tiles(64, M[q], N[q]);
-    t128 += f32_tiles(128, M[q], N[q]);
+    n32 += b == 32;
+    n128 += b == 128;
+    if (b == 128) t128 += f32_tiles(128, M[q], N[q]);
+    else { rM[rest] = M[q]; rN[rest++] = N[q]; }
   }
-  if (split) return 32;
-  const double us64 = 2.0 + f32_tile_us(64, t64, K), us128 = K > kF32MaxK128 ? 1e30 : 2.0 + f32_tile_us(128, t128, K);
-  if (us64 >= apart && us128 >= apart) return 0;
-  return us64 <= us128 ? 64 : 128;
+  F32GroupPlan p = {0, 0, false, apart};
+  if (n < 2) return p;
+  if (n32 == n) return {32, 8, false, apart};
+  const int chains = n32 ? 8 : 2;
+  const double one = f32_launch_us(64, chains, t64, K), wide = f32_launch_us(128, 1, t128, K);
+  if (one < p.us) p = {64, chains, false, one};
+  if (n128 == n && wide < p.us) p = {128, 1, false, wide};
+  if (n128 && n128 < n) {
+    const F32GroupPlan r = f32_group_plan(rM, rN, rest, K);
+    if (wide + r.us < p.us) p = {r.tile, r.chains, true, wide + r.us};
+  }
+  return p;
 }
 
 }  // namespace mlm

@@ -8,8 +8,12 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-# tokens, width, vocabulary of the shard: either gradient's tiles leading, ragged edges in all three, last k tiles of 5 and of 8
-@pytest.mark.parametrize("T,H,V", [(512, 1024, 4096), (1101, 1032, 1024), (709, 1928, 2568), (1101, 1024, 1032)])
+# tokens, width, vocabulary of the shard: either gradient's tiles leading, ragged edges in all three, last k tiles of 5 and of 8; sums of
+# eight chains (the last)
+SHAPES = [(512, 1024, 4096), (1101, 1032, 1024), (709, 1928, 2568), (1101, 1024, 1032), (389, 680, 16040)]
+
+
+@pytest.mark.parametrize("T,H,V", SHAPES)
 def test_logits_gradients_in_one_launch(T, H, V):
     dm = B.make_dims(1, T, H, 1, 8, V, 1, 0, B.MLM_F32)
     g = torch.Generator(device=DEV)

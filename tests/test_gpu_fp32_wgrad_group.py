@@ -8,10 +8,13 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-# tokens, width, FFN width, ways of the split: 64-wide tiles with whole and ragged edges, a last k tile of 5, a single k tile; 128-wide
-# ones, whole and ragged; fewer tokens than a k tile
-@pytest.mark.parametrize("T,H,F,p", [(261, 512, 2048, 1), (517, 1000, 2000, 5), (64, 768, 768, 1), (33, 1032, 2056, 1), (1024, 1024, 4096, 1),
-                                     (1021, 2064, 8208, 2), (77, 1000, 4000, 1), (5, 1032, 2056, 1)])
+# tokens, width, FFN width, ways of the split: 64-wide tiles with whole and ragged edges, a last k tile of 5, a single k tile, sums of two
+# and of eight chains; 128-wide tiles, whole and ragged, for all and for some of the four; fewer tokens than a k tile
+SHAPES = [(261, 512, 2048, 1), (517, 1000, 2000, 5), (64, 768, 768, 1), (33, 1032, 2056, 1), (1024, 1024, 4096, 1), (1021, 2064, 8208, 2),
+          (77, 1000, 4000, 1), (5, 1032, 2056, 1), (77, 1032, 4104, 1), (33, 2040, 8160, 1), (72, 2048, 8192, 1), (218, 968, 3872, 1)]
+
+
+@pytest.mark.parametrize("T,H,F,p", SHAPES)
 def test_weight_gradients_in_one_launch(T, H, F, p):
     d = B.make_dims(1, T, H, H // 8, F, 8 * p, p, 0, B.MLM_F32)
     Hl, F = H // p, F // p

@@ -1,0 +1,85 @@
+"""Which products share a launch, and in which tiles (no GPU needed: the rules are host arithmetic): for the shapes of the GPU tests, whose
+names claim it, and against measured launches."""
+import subprocess
+
+import pytest
+
+import test_gpu_fp32_ce_bwd_joint as FCE
+import test_gpu_fp32_wgrad_group as FWG
+from paper_1909_08053_amd import build as BLD
+
+F32 = """#include <stdio.h>
+#include "gemm_f32_pick.h"
+int mlm::gemm_cu_count() { return 256; }
+using namespace mlm;
+int main() {                       // "w T H F p" -> tile, chains, 128-wide ones apart; "d T H V" -> tile, chains
+  char kind[4];
+  int T, H, F, p;
+  while (scanf("%3s %d %d %d", kind, &T, &H, &F) == 4) {
+    if (kind[0] == 'w') {
+      if (scanf("%d", &p) != 1) return 1;
+      const int Hl = H / p, Fl = F / p, M[4] = {Fl, H, H, Hl}, N[4] = {H, Fl, 3 * Hl, H};
+      const F32GroupPlan g = f32_group_plan(M, N, 4, T);
+      int kinds = 0;                                    // tiles that the four take alone, one bit each
+      for (int q = 0; q < 4; ++q) kinds |= f32_pick(M[q], N[q], T) / 32;
+      printf("%d %d %d %d\\n", g.tile, g.chains, g.wide_apart, kinds);
+    } else {
+      const F32DualPick d = f32_dual_pick(H, F, T, T, H, F);
+      printf("%d %d 0 0\\n", d.tile, d.chains);
+    }
+  }
+  return 0;
+}
+"""
+
+# fp32 weight gradients, tokens, width, ways of the split; us with a launch each, in one launch of 64-wide tiles with sums of as many
+# chains as needed, with the 128-wide ones in a launch of their own (all four: the same), the others in 64-wide tiles or a launch each
+F32_GROUPS = [
+    (16, 2048, 1, 66.5, 131.6, 54.1), (108, 2048, 1, 139.1, 204.8, 127.6), (1024, 2048, 1, 784.8, 921.0, 764.1), (16, 1568, 1, 54.5, 80.1, 38.4),
+    (211, 1544, 1, 163.0, 151.1, 150.2), (80, 1712, 1, 105.6, 112.3, 97.4), (841, 984, 1, 189.6, 186.6, 175.6), (204, 912, 1, 69.2, 59.4, 59.8),
+    (23, 904, 1, 29.8, 32.3, 24.8), (1147, 1104, 1, 320.1, 299.2, 295.4), (372, 1912, 1, 318.9, 310.1, 285.6), (955, 1872, 1, 709.6, 689.4, 689.9),
+    (2063, 1120, 1, 565.2, 530.6, 556.9), (68, 776, 1, 41.8, 37.2, 40.3), (37, 832, 1, 34.3, 26.2, 30.6), (14, 632, 1, 27.9, 16.1, 22.0),
+    (29, 680, 1, 30.2, 19.4, 26.6), (49, 1920, 4, 37.4, 26.8, 29.9), (27, 1464, 1, 60.2, 52.1, 53.4), (44, 1520, 2, 49.5, 41.7, 46.5),
+]
+# both fp32 gradients of the logits, tokens, width, vocabulary; us of the call in two launches, in one of 64-wide tiles
+F32_DUALS = [
+    (805, 200, 3176, 60.5, 64.7), (6097, 1968, 440, 202.5, 192.0), (613, 568, 17880, 425.3, 352.3), (390, 672, 16032, 421.1, 277.7),
+    (4554, 216, 1168, 123.9, 90.0), (128, 2232, 21512, 632.6, 372.8), (6000, 1024, 256, 90.3, 108.6), (3792, 192, 248, 46.4, 72.3),
+    (64, 1024, 30000, 317.5, 496.4), (22, 784, 38944, 422.3, 639.2), (512, 1024, 4096, 114.8, 94.4), (271, 2000, 25784, 691.6, 583.4),
+    (406, 1008, 18416, 462.3, 373.3), (593, 712, 1016, 39.7, 36.6), (1737, 1032, 4592, 316.6, 311.5), (2010, 1808, 3480, 467.6, 444.3),
+]
+
+
+@pytest.fixture(scope="module")
+def f32(tmp_path_factory):
+    d = tmp_path_factory.mktemp("f32")
+    (d / "f32.cpp").write_text(F32)
+    subprocess.run(["g++", "-std=c++17", "-I" + BLD.CSRC, str(d / "f32.cpp"), "-o", str(d / "f32")], check=True, timeout=60)
+
+    def run(lines):
+        out = subprocess.run([str(d / "f32")], input="\n".join(lines), text=True, check=True, capture_output=True, timeout=60).stdout
+        return [tuple(map(int, l.split())) for l in out.splitlines()]
+    return run
+
+
+def test_fp32_shapes_of_the_gpu_tests_share_launches(f32):
+    plans = f32(["w %d %d %d %d" % s for s in FWG.SHAPES])
+    assert {(64, 2, 0), (64, 8, 0), (128, 1, 0), (64, 2, 1), (0, 0, 1)} <= {p[:3] for p in plans}, plans
+    assert all(tile or wide for tile, _, wide, _ in plans), plans
+    duals = f32(["d %d %d %d" % s for s in FCE.SHAPES])
+    assert [d[:2] for d in duals] == [(64, 2)] * (len(duals) - 1) + [(64, 8)]
+
+
+def test_fp32_sums_keep_their_chains(f32):
+    """Two in the 64-wide tiles are enough only where nothing takes the split kernel alone; 128-wide tiles only where all do."""
+    sizes = [(T, H, 4 * H, p) for T in (5, 24, 55, 123, 333, 1024, 4096) for H in (64, 320, 768, 1032, 1536, 2048) for p in (1, 2, 4, 8)]
+    for s, (tile, chains, wide, kinds) in zip(sizes, f32(["w %d %d %d %d" % s for s in sizes])):
+        assert tile != 64 or chains == (8 if kinds & 1 else 2), s
+        assert tile != 128 or kinds == 4, s
+
+
+def test_fp32_rules_take_the_faster_form(f32):
+    for m, (tile, _, wide, _) in zip(F32_GROUPS, f32(["w %d %d %d %d" % (*m[:2], 4 * m[1], m[2]) for m in F32_GROUPS])):
+        assert m[3 + (2 if wide or tile == 128 else 1 if tile else 0)] <= 1.04 * min(m[3:]), (m, tile, wide)
+    for m, (tile, _, _, _) in zip(F32_DUALS, f32(["d %d %d %d" % m[:3] for m in F32_DUALS])):
+        assert m[4 if tile else 3] <= 1.04 * min(m[3:]), (m, tile)
