@@ -14,10 +14,10 @@ __global__ __launch_bounds__((v2_nw<BN, DEEP>() * 64), 2) void gemm_bf16_v2_dual
   const int at = id < first ? id : id - first;
   if ((id < first) == (first_is_1 != 0)) {
     const int pid = p1.strip ? v2_xcd_order(at, p1.full_tiles, p1.window) : at;
-    gemm_v2_work_item<true, true, EPI_STORE, BN, KE1, DEEP>(a1, p1, nullptr, pid, lds_raw);
+    gemm_v2_work_item<true, true, EPI_STORE, BN, KE1, DEEP, false>(a1, p1, nullptr, pid, lds_raw);
   } else {
     const int pid = p0.strip ? v2_xcd_order(at, p0.full_tiles, p0.window) : at;
-    gemm_v2_work_item<false, false, EPI_STORE, BN, KE0, DEEP>(a0, p0, nullptr, pid, lds_raw);
+    gemm_v2_work_item<false, false, EPI_STORE, BN, KE0, DEEP, false>(a0, p0, nullptr, pid, lds_raw);
   }
 }
 

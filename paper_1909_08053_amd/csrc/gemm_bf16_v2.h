@@ -196,19 +196,23 @@ struct V2Plan {
 //   positions of the walk of v2_tile_of: the shorter side of the output is cut into strips `strip` tiles wide (the last takes
 //   what is left); a strip is walked along the longer side, every other one backwards, a row of `strip` tiles at a time.
 __host__ __device__ inline int v2_xcd_order(int id, int total, int window) {
-  const int base = total <= window ? 0 : id / window * window;      // (a division is 0.07 us ahead of the first copy)
+  const int base = total <= window ? 0 : (int)((unsigned)id / (unsigned)window) * window;   // (a division is 0.07 us ahead of the first copy)
   const int cnt = total - base < window ? total - base : window;
   const int p = id - base, x = p & 7, per = cnt >> 3, more = cnt & 7;
   return base + x * per + (x < more ? x : more) + (p >> 3);
 }
 __host__ __device__ inline void v2_tile_of(const V2Plan& p, int q, int* tile_m, int* tile_n) {
-  const bool rows = p.strip == 0 || p.tiles_m <= p.tiles_n;         // strips of tile rows, walked along the columns
+  if (p.strip == 0) {
+    *tile_n = (int)((unsigned)q / (unsigned)p.tiles_m);
+    *tile_m = q - *tile_n * p.tiles_m;
+    return;
+  }
+  const bool rows = p.tiles_m <= p.tiles_n;                         // strips of tile rows, walked along the columns
   const int cross = rows ? p.tiles_m : p.tiles_n, along = rows ? p.tiles_n : p.tiles_m;
-  const int strip = p.strip == 0 ? cross : p.strip;
-  const int s = strip >= cross ? 0 : q / (strip * along), r = q - s * (strip * along);
-  const int left = cross - s * strip, w = left < strip ? left : strip;
-  int l = r / w;
-  const int c = s * strip + r - l * w;
+  const int s = p.strip >= cross ? 0 : (int)((unsigned)q / (unsigned)(p.strip * along)), r = q - s * (p.strip * along);
+  const int left = cross - s * p.strip, w = left < p.strip ? left : p.strip;
+  int l = (int)((unsigned)r / (unsigned)w);
+  const int c = s * p.strip + r - l * w;
   if (s & 1) l = along - 1 - l;
   *tile_m = rows ? c : l;
   *tile_n = rows ? l : c;
@@ -343,7 +347,9 @@ inline V2Plan v2_plan(int M, int N, int K, bool allow_split, int bn = V2_B) {
 // Library call, forward layout, best large tile against it: 1024 x 1920 x 960 18.7 -> 10.6 us, 1024 x 3840 x 1920
 // 33.7 -> 21.2, 3000 x 1152 x 1536 27.5 -> 16.7, 4096 x 2048 x 768 20.3 -> 16.9; 4096 x 4096 x 768 stays (27 against 31).
 // Grouped weight gradients of 228 such tiles (8192 tokens, 1536 wide, split eight ways): 152 us in eight launches -> 81.
-template <bool A_KC, bool B_KC, int EPI, int BN, int KE, bool DEEP>
+// PIECES: the launch may hold k-pieces.  A whole tile takes no division but the walk's: a 64-bit one for the k range of every work
+// item, and the walk in strips, were 0.1 - 0.3 us of launches of 4 - 6.
+template <bool A_KC, bool B_KC, int EPI, int BN, int KE, bool DEEP, bool PIECES = true>
 __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Plan& plan, float* splitk_ws, int pid,
                                                   unsigned char* lds_raw) {
   static_assert(BN == V2_B || BN == 192 || BN == V2_SMALL, "tile widths");
@@ -358,25 +364,26 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
 
   // Work item: a full tile, or one k-piece of a tail tile.  An XCD takes long pieces of the same part of k and of neighbouring
   // tiles, which share panels; short ones, whose time is the first misses', are spread (v2_set_walk).
-  int vt = pid, piece = 0, npieces = 1;
-  if (pid >= plan.full_tiles) {
+  const int np_total = (int)((unsigned)(a.K + 2 * V2_BK - 1) / (2 * V2_BK));   // pairs of 32-deep slices of the problem
+  int vt = pid, piece = 0, kt_begin = 0, kt_end = 2 * np_total;
+  const bool whole = !PIECES || pid < plan.full_tiles;
+  if (!whole) {
     int t = pid - plan.full_tiles;
     if (plan.long_pieces) {
       t = v2_xcd_order(t, plan.tail_tiles * plan.split, plan.window);
-      piece = t / plan.tail_tiles;
+      piece = (int)((unsigned)t / (unsigned)plan.tail_tiles);
       vt = plan.full_tiles + t - piece * plan.tail_tiles;
     } else {
-      vt = plan.full_tiles + t / plan.split;
-      piece = t % plan.split;
+      const int tail = (int)((unsigned)t / (unsigned)plan.split);
+      vt = plan.full_tiles + tail;
+      piece = t - tail * plan.split;
     }
-    npieces = plan.split;
+    kt_begin = 2 * (int)((unsigned)(np_total * piece) / (unsigned)plan.split);        // (at most 2^18 pairs, 16 pieces)
+    kt_end = 2 * (int)((unsigned)(np_total * (piece + 1)) / (unsigned)plan.split);
   }
   int tile_m, tile_n;
   v2_tile_of(plan, vt, &tile_m, &tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * BN;
-  const int np_total = (a.K + 2 * V2_BK - 1) / (2 * V2_BK);   // pairs of 32-deep slices of the problem
-  const int kt_begin = 2 * (int)((long)np_total * piece / npieces);
-  const int kt_end = 2 * (int)((long)np_total * (piece + 1) / npieces);
   const int nk = kt_end - kt_begin;                  // even, >= 2
 
   V2Src<A_KC, NPA, KE == KE_ANY, BM> sa;
@@ -529,7 +536,7 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
   wait_vmcnt<0>();
   __syncthreads();
 
-  if (npieces > 1) {
+  if (!whole) {
     // fp32 partial tile: piece-major [tail tile][piece][BM][BN]
     const int l16 = lane & 15, lg = lane >> 4;
     float* dst = splitk_ws + ((size_t)(vt - plan.full_tiles) * plan.split + piece) * (BM * BN);
@@ -575,7 +582,6 @@ __global__ __launch_bounds__((v2_nw<BN, DEEP>() * 64), 2) void gemm_bf16_v2_cols
 // optimizer waits for: four GEMMs with 72 + 72 + 24 + 60 tiles at the 8.3B-shape 1/8 shard become one round.
 constexpr int kMaxGroup = 4;
 struct GemmGroup {
-  int n;
   int xcd_order;                       // one walk through the tiles of all problems
   int tile_begin[kMaxGroup + 1];       // first work item of each problem; tile_begin[n] = grid size
   int full;                            // whole tiles; the work items behind them are k-pieces of the last problem's last tiles
@@ -592,14 +598,14 @@ __global__ __launch_bounds__((v2_nw<BN, DEEP>() * 64), 2) void gemm_bf16_v2_grou
   // the problem index is uniform over the workgroup: select its arguments with scalar compares
   int q = 0;
 #pragma unroll
-  for (int i = 1; i < kMaxGroup; ++i) q += (i < g.n && pid >= g.tile_begin[i]) ? 1 : 0;
+  for (int i = 1; i < kMaxGroup; ++i) q += pid >= g.tile_begin[i] ? 1 : 0;      // (past the grid for problems that do not exist)
   GemmArgs a = g.args[0];
   V2Plan plan = g.plan[0];
   int first = g.tile_begin[0];
 #pragma unroll
   for (int i = 1; i < kMaxGroup; ++i)
     if (q == i) { a = g.args[i]; plan = g.plan[i]; first = g.tile_begin[i]; }
-  gemm_v2_work_item<A_KC, B_KC, EPI_STORE, BN, KE, DEEP>(a, plan, SPLIT ? splitk_ws : nullptr, pid - first, lds_raw);
+  gemm_v2_work_item<A_KC, B_KC, EPI_STORE, BN, KE, DEEP, SPLIT>(a, plan, SPLIT ? splitk_ws : nullptr, pid - first, lds_raw);
 }
 
 // Tail tiles: sum the k-pieces in piece order (deterministic) and apply the epilogue to the fp32 sums.  A wave owns
@@ -792,7 +798,6 @@ hipError_t launch_gemm_bf16_v2_group_ke(const GemmArgs* probs, int n, const V2Gr
   if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
   GemmGroup g;
   memset(&g, 0, sizeof(g));
-  g.n = n;
   int total = 0;
   for (int q = 0; q < n; ++q) {
     const GemmArgs& a = probs[!SPLIT ? q : q == n - 1 ? sp.last : q == sp.last ? n - 1 : q];       // (sp.last goes last)
