@@ -263,7 +263,11 @@ inline long v2_plain_cost(const V2Plan& p, int window) {
   return cost;
 }
 // The walk of a launch: the strip width that costs least, where that is a tenth less than ids straight to tiles (equal patches
-// are better apart: 96 tiles of 6 rows 1 us).  Measured in strips, 1450 shapes of up to 600 tiles: small tile 0.90 of the time on average
+// are better apart: 96 tiles of 6 rows 1 us) and spares the busiest XCD four megabytes.  Of 329 launches that would gain the tenth, time in
+// strips by the megabytes spared: up to 0.5 1.015 (the walk's divisions), 0.5 .. 1 0.996, 1 .. 4 0.974, more 0.93; but up to 4 the call that the
+// launch is part of lost up to 9 % (520 tokens x 864 x 2000 forward 28.5 / 31.1 us, its second product reads what the strips left
+// on one XCD), one in thirty of 500 drawn calls, and with this line none.  Measured in strips, 1450 shapes of up to 600 tiles: small tile
+// 0.90 of the time on average
 // (20 tile rows 0.98, 15 rows 0.88, 33 rows 0.83; 1920 x 4096 x 6144 131 -> 86 us), 192 wide 0.98, 256 wide 1.00.
 // long_pieces: an XCD takes the k-pieces of tail tiles part by part of k; short ones are spread over the XCDs.  36 tiles x 6 pieces of
 // 16 slices in order / spread 15.2 / 12.3 us, 96 x 2 of 32 17.7 / 14.5; 80 x 3 of 80 and 32 x 4 .. 128 x 2 large tiles of
@@ -274,8 +278,8 @@ inline void v2_set_walk(V2Plan* p, int window, int K, bool strips = false) {
   p->strip = 0;
   if (p->full_tiles == 0 && !p->long_pieces) return;
   const int cross = p->tiles_m <= p->tiles_n ? p->tiles_m : p->tiles_n;
-  const long plain = v2_plain_cost(*p, window);
-  long best = strips ? LONG_MAX : plain - plain / 10;
+  const long plain = v2_plain_cost(*p, window), least = (1 << 21) / K;      // (4 MB in elements per k)
+  long best = strips ? LONG_MAX : plain - (plain / 10 > least ? plain / 10 : least);
   for (int w = cross < 3 ? cross : 3; w <= cross && w <= 12; ++w) {
     const long c = v2_walk_cost(*p, window, w);
     if (c <= best) { best = c; p->strip = w; }

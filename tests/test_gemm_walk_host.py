@@ -69,3 +69,47 @@ def test_tiles_of_an_xcd_share_panels(walk):
     cases = [(32, 25, 256), (32, 12, 256), (16, 14, 256), (4, 100, 256), (15, 50, 256), (33, 17, 256), (63, 8, 256), (20, 20, 256)]
     for c, (_, panels) in zip(cases, walk(cases)):
         assert panels <= 16, (c, panels)
+
+
+RULE = """#include <stdio.h>
+#include <string.h>
+#include "gemm_bf16_v2.h"
+namespace mlm {
+int gemm_cu_count() { return 256; }
+int gemm_v2_forced_bn() { return 0; }
+}
+using namespace mlm;
+int main() {                               // "layout M N K split" -> strips, k-pieces, part by part of k
+  char lay[8];
+  int M, N, K, sp;
+  while (scanf("%7s %d %d %d %d", lay, &M, &N, &K, &sp) == 5) {
+    const int bn = !strcmp(lay, "fwd") ? v2_pick_bn<true, false, EPI_STORE>(M, N, K, sp)
+                 : !strcmp(lay, "dgrad") ? v2_pick_bn<true, true, EPI_STORE>(M, N, K, sp) : v2_pick_bn<false, false, EPI_STORE>(M, N, K, sp);
+    V2Plan p = v2_plan(M, N, K, sp, bn);
+    v2_set_walk(&p, bn == V2_SMALL && !p.deep() ? 512 : 256, K);
+    printf("%d %d %d\\n", p.strip != 0, p.tail_tiles * p.split, p.long_pieces);
+  }
+  return 0;
+}
+"""
+
+# layout, M, N, K; us with ids straight to tiles and in strips.  The last three are the first product of a call, with the call's time.
+STRIPS = [
+    ("dgrad", 280, 5040, 1872, 20.5, 15.8), ("fwd", 360, 6440, 3968, 37.0, 29.1), ("fwd", 600, 5520, 2416, 30.8, 25.4),
+    ("fwd", 5776, 1064, 3808, 71.6, 59.3), ("dgrad", 1608, 1824, 1352, 18.1, 15.2), ("wgrad", 528, 3496, 4992, 41.8, 38.0),
+    ("wgrad", 1488, 3248, 1720, 30.1, 27.3), ("dgrad", 2416, 3616, 80, 9.0, 9.3), ("fwd", 1432, 816, 216, 5.8, 6.0),
+    ("wgrad", 928, 1208, 224, 5.2, 5.4), ("wgrad", 736, 480, 88, 4.0, 4.2), ("dgrad", 3440, 3104, 120, 9.9, 10.3),
+    ("fwd", 520, 2000, 864, 28.4, 31.1), ("fwd", 1068, 2016, 448, 24.9, 27.3), ("fwd", 2400, 1440, 480, 27.9, 29.7),
+]
+
+
+def test_walk_takes_the_faster_order(tmp_path):
+    """Short launches keep the plain order, whose tiles cost one division."""
+    (tmp_path / "rule.hip").write_text(RULE)
+    subprocess.run([BLD._hipcc(), *BLD.FLAGS, str(tmp_path / "rule.hip"), "-o", str(tmp_path / "rule")], check=True, capture_output=True,
+                   timeout=180)
+    lines = ["%s %d %d %d 0" % c[:4] for c in STRIPS]
+    out = subprocess.run([str(tmp_path / "rule")], input="\n".join(lines), text=True, check=True, capture_output=True, timeout=60).stdout
+    got = [tuple(map(int, l.split())) for l in out.splitlines()]
+    for c, (strips, _, _) in zip(STRIPS, got):
+        assert c[4 + strips] == min(c[4:]), (c, strips)
