@@ -262,6 +262,23 @@ inline long v2_plain_cost(const V2Plan& p, int window) {
   }
   return cost;
 }
+// Operand elements per k of an XCD's share of the k-pieces (the fourth's), in the order of their numbers or part by part of k.
+inline long v2_piece_cost(const V2Plan& p, bool parts) {
+  const int total = p.tail_tiles * p.split;
+  int row[64], col[64], n = 0;
+  long cost = 0;
+  for (int id = total > 3 ? 3 : 0; id < total && n < 64; id += 8, ++n) {
+    const int t = parts ? v2_xcd_order(id, total, p.window) : id, piece = parts ? t / p.tail_tiles : t % p.split;
+    int m, c;
+    v2_tile_of(p, p.full_tiles + (parts ? t % p.tail_tiles : t / p.split), &m, &c);
+    row[n] = 16 * m + piece;                         // (at most 16 pieces)
+    col[n] = 16 * c + piece;
+    bool r = true, l = true;
+    for (int i = 0; i < n; ++i) { r = r && row[i] != row[n]; l = l && col[i] != col[n]; }
+    cost += (r ? p.bm : 0) + (l ? p.bn : 0);
+  }
+  return cost;
+}
 // The walk of a launch: the strip width that costs least, where that is a tenth less than ids straight to tiles (equal patches
 // are better apart: 96 tiles of 6 rows 1 us) and spares the busiest XCD four megabytes.  Of 329 launches that would gain the tenth, time in
 // strips by the megabytes spared: up to 0.5 1.015 (the walk's divisions), 0.5 .. 1 0.996, 1 .. 4 0.974, more 0.93; but up to 4 the call that the
@@ -271,18 +288,32 @@ inline long v2_plain_cost(const V2Plan& p, int window) {
 // (20 tile rows 0.98, 15 rows 0.88, 33 rows 0.83; 1920 x 4096 x 6144 131 -> 86 us), 192 wide 0.98, 256 wide 1.00.
 // long_pieces: an XCD takes the k-pieces of tail tiles part by part of k; short ones are spread over the XCDs.  36 tiles x 6 pieces of
 // 16 slices in order / spread 15.2 / 12.3 us, 96 x 2 of 32 17.7 / 14.5; 80 x 3 of 80 and 32 x 4 .. 128 x 2 large tiles of
-// 24 .. 100 about 1 % of their steps in order's favour.
+// 24 .. 100 about 1 % of their steps in order's favour; dhf of 863 tokens x 512 x 22616, 28 x 9 pieces of 79, 98.7 -> 78.8 us of its call.  Not
+// where the spread ones, whose number shares a factor with the eight XCDs, share as many panels: 7343 x 112 x 14688, 58 tiles x 4, 161 / 175,
+// 5519 x 208 x 3160, 88 x 2, 72 / 75.  Without whole tiles the strips are the pieces' own.
 inline void v2_set_walk(V2Plan* p, int window, int K, bool strips = false) {
   p->window = window;
-  p->long_pieces = v2_slices(K) >= (p->bn == V2_SMALL ? 48 : 16) * p->split;
+  p->long_pieces = 0;
   p->strip = 0;
-  if (p->full_tiles == 0 && !p->long_pieces) return;
   const int cross = p->tiles_m <= p->tiles_n ? p->tiles_m : p->tiles_n;
-  const long plain = v2_plain_cost(*p, window), least = (1 << 21) / K;      // (4 MB in elements per k)
-  long best = strips ? LONG_MAX : plain - (plain / 10 > least ? plain / 10 : least);
-  for (int w = cross < 3 ? cross : 3; w <= cross && w <= 12; ++w) {
-    const long c = v2_walk_cost(*p, window, w);
-    if (c <= best) { best = c; p->strip = w; }
+  if (p->full_tiles) {
+    const long plain = v2_plain_cost(*p, window), least = (1 << 21) / K;      // (4 MB in elements per k)
+    long best = strips ? LONG_MAX : plain - (plain / 10 > least ? plain / 10 : least);
+    for (int w = cross < 3 ? cross : 3; w <= cross && w <= 12; ++w) {
+      const long c = v2_walk_cost(*p, window, w);
+      if (c <= best) { best = c; p->strip = w; }
+    }
+  }
+  if (p->tail_tiles == 0 || v2_slices(K) < (p->bn == V2_SMALL ? 48 : 16) * p->split) return;
+  const long spread = v2_piece_cost(*p, false);
+  long best = spread - spread / 10;
+  const int first = p->strip, last = p->full_tiles || cross > 12 ? first : cross;
+  for (int w = first;; w = w == 0 && last > 4 ? 4 : last) {        // the launch's strips; or one of 0, 4 and the whole width
+    V2Plan t = *p;
+    t.strip = w;
+    const long c = v2_piece_cost(t, true);
+    if (c <= best) { best = c; p->strip = w; p->long_pieces = 1; }
+    if (w == last) break;
   }
 }
 

@@ -101,15 +101,23 @@ STRIPS = [
     ("wgrad", 928, 1208, 224, 5.2, 5.4), ("wgrad", 736, 480, 88, 4.0, 4.2), ("dgrad", 3440, 3104, 120, 9.9, 10.3),
     ("fwd", 520, 2000, 864, 28.4, 31.1), ("fwd", 1068, 2016, 448, 24.9, 27.3), ("fwd", 2400, 1440, 480, 27.9, 29.7),
 ]
+# layout, M, N, K of products in k-pieces only; us of their call with the pieces spread over the XCDs and part by part of k
+PIECES = [
+    ("dgrad", 7343, 112, 14688, 161.0, 174.6), ("dgrad", 5519, 208, 3160, 72.1, 75.0), ("dgrad", 863, 512, 22616, 99.3, 78.8),
+    ("dgrad", 2111, 360, 27072, 167.0, 133.1), ("fwd", 1332, 680, 9184, 74.0, 62.5), ("dgrad", 1399, 432, 26168, 138.6, 120.1),
+    ("dgrad", 2230, 144, 12928, 73.6, 65.4), ("fwd", 336, 1320, 11760, 79.2, 70.8), ("dgrad", 3970, 136, 13952, 102.5, 114.0),
+]
 
 
 def test_walk_takes_the_faster_order(tmp_path):
-    """Short launches keep the plain order, whose tiles cost one division."""
+    """Short launches keep the plain order, whose tiles cost one division, and k-pieces are ordered only where that shares more panels."""
     (tmp_path / "rule.hip").write_text(RULE)
     subprocess.run([BLD._hipcc(), *BLD.FLAGS, str(tmp_path / "rule.hip"), "-o", str(tmp_path / "rule")], check=True, capture_output=True,
                    timeout=180)
-    lines = ["%s %d %d %d 0" % c[:4] for c in STRIPS]
+    lines = ["%s %d %d %d 0" % c[:4] for c in STRIPS] + ["%s %d %d %d 1" % c[:4] for c in PIECES]
     out = subprocess.run([str(tmp_path / "rule")], input="\n".join(lines), text=True, check=True, capture_output=True, timeout=60).stdout
     got = [tuple(map(int, l.split())) for l in out.splitlines()]
     for c, (strips, _, _) in zip(STRIPS, got):
         assert c[4 + strips] == min(c[4:]), (c, strips)
+    for c, (_, pieces, parts) in zip(PIECES, got[len(STRIPS):]):
+        assert pieces and c[4 + parts] == min(c[4:]), (c, pieces, parts)
