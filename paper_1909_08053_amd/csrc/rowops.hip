@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <mutex>
 #include "common.h"
+#include "schedule.h"
 #include "rng.h"
 
 namespace mlm {
@@ -887,7 +888,8 @@ hipError_t launch_ce_merge(int T, int n_shards, const float* m, const float* s, 
 }
 
 // dL = w_t / sum(w) * (exp(L - M_t) / S_t - onehot), written over the stored logits.  Bound by memory.  A thread takes up to
-// VECS vectors of a row, all requested before the first is used: four where a workgroup then holds a whole row.
+// VECS vectors of a row, all requested before the first is used: four where a workgroup then holds a whole row (dlogits_vectors).
+// A thread that has none leaves first: with its one load under a condition instead, 8192 x 30592 bf16 took 162 us, not 155.
 template <typename T, int VECS>
 __global__ __launch_bounds__(256) void dlogits_inplace_kernel(int Vl, T* logits, const int32_t* __restrict__ targets,
                                                               int v0, const float* __restrict__ M,
@@ -899,19 +901,20 @@ __global__ __launch_bounds__(256) void dlogits_inplace_kernel(int Vl, T* logits,
   const int ncb = (nv + 256 * VECS - 1) / (256 * VECS);   // grid.x = tokens x column blocks (column block fastest)
   const int t = blockIdx.x / ncb;
   const int c0 = (blockIdx.x - t * ncb) * 256 * VECS + threadIdx.x;
-  T* row = logits + (size_t)t * Vl;
-  Vec16<T> v[VECS];
-#pragma unroll
-  for (int k = 0; k < VECS; ++k)
-    if (c0 + 256 * k < nv) v[k].load(row + (size_t)(c0 + 256 * k) * VN);
+  if (c0 >= nv) return;
   const float coef = (loss_w ? loss_w[t] : 1.0f) / loss_stats[1];
   const float Mt = M[t];
   const float inv = coef / S[t];
   const int loc = targets[t] - v0;
+  T* row = logits + (size_t)t * Vl;
+  Vec16<T> v[VECS];
+#pragma unroll
+  for (int k = 0; k < VECS; ++k)
+    if (k == 0 || c0 + 256 * k < nv) v[k].load(row + (size_t)(c0 + 256 * k) * VN);
 #pragma unroll
   for (int k = 0; k < VECS; ++k) {
     const int c = c0 + 256 * k;
-    if (c >= nv) break;
+    if (k > 0 && c >= nv) break;
     Vec16<T> o;
 #pragma unroll
     for (int e = 0; e < VN; ++e) {
@@ -923,13 +926,11 @@ __global__ __launch_bounds__(256) void dlogits_inplace_kernel(int Vl, T* logits,
   }
 }
 
-// One workgroup per row up to 1024 vectors (8192 x 6400 bf16 37.2 -> 34.6 us, where every fourth workgroup had an eighth of its
-// threads at work; 1000 x 2056 7.0 -> 5.1); of longer rows a vector per thread (8192 x 51200 in fours 266 -> 279 us).
 template <typename T>
 static hipError_t launch_dlogits(int rows, int Vl, void* logits, const int32_t* targets, int v0, const float* M, const float* S,
                                  const float* loss_w, const float* loss_stats, hipStream_t st) {
   const int nv = Vl / Vec16<T>::N;
-  if (nv <= 1024)
+  if (dlogits_vectors(rows, nv, gemm_cu_count()) == 4)
     hipLaunchKernelGGL((dlogits_inplace_kernel<T, 4>), dim3(rows), dim3(256), 0, st, Vl, (T*)logits, targets, v0, M, S, loss_w, loss_stats);
   else
     hipLaunchKernelGGL((dlogits_inplace_kernel<T, 1>), dim3(((nv + 255) / 256) * rows), dim3(256), 0, st, Vl, (T*)logits, targets, v0, M, S,

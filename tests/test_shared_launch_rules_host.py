@@ -1,5 +1,5 @@
-"""Which products share a launch, and in which tiles (no GPU needed: the rules are host arithmetic): for the shapes of the GPU tests, whose
-names claim it, and against measured launches."""
+"""Which products share a launch, and in which tiles, and how the pass over stored logits is divided (no GPU needed: the rules are host
+arithmetic): for the shapes of the GPU tests, whose names claim it, and against measured launches."""
 import subprocess
 
 import pytest
@@ -83,3 +83,21 @@ def test_fp32_rules_take_the_faster_form(f32):
         assert m[3 + (2 if wide or tile == 128 else 1 if tile else 0)] <= 1.04 * min(m[3:]), (m, tile, wide)
     for m, (tile, _, _, _) in zip(F32_DUALS, f32(["d %d %d %d" % m[:3] for m in F32_DUALS])):
         assert m[4 if tile else 3] <= 1.04 * min(m[3:]), (m, tile)
+
+
+# rows, 16-byte vectors of a row of bf16 logits; us with a vector per thread and with a workgroup per row
+DLOGITS = [(16, 800, 2.56, 3.08), (40, 800, 2.60, 3.16), (64, 1024, 2.96, 3.52), (128, 800, 3.08, 3.48), (300, 800, 4.88, 5.24),
+           (512, 800, 7.08, 6.36), (1000, 257, 6.68, 5.52), (2048, 800, 13.48, 10.08), (8192, 800, 37.23, 32.32), (8192, 257, 19.32, 14.64),
+           (8192, 6400, 266.0, 279.0)]
+
+
+def test_pass_over_logits_takes_the_faster_form(tmp_path):
+    (tmp_path / "dl.cpp").write_text("""#include <stdio.h>
+#include "schedule.h"
+int main() { int t, nv; while (scanf("%d %d", &t, &nv) == 2) printf("%d\\n", mlm::dlogits_vectors(t, nv, 256)); return 0; }
+""")
+    subprocess.run(["g++", "-std=c++17", "-I" + BLD.CSRC, str(tmp_path / "dl.cpp"), "-o", str(tmp_path / "dl")], check=True, timeout=60)
+    text = "\n".join("%d %d" % m[:2] for m in DLOGITS)
+    out = subprocess.run([str(tmp_path / "dl")], input=text, text=True, check=True, capture_output=True, timeout=60).stdout.split()
+    for m, v in zip(DLOGITS, map(int, out)):
+        assert m[3 if v == 4 else 2] == min(m[2:]), (m, v)
