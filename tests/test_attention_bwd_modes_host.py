@@ -3,6 +3,7 @@ import subprocess
 
 import pytest
 
+import test_gpu_attention_bwd_two_launches as TWO
 from paper_1909_08053_amd import build as BLD
 
 MAIN = """#include <stdio.h>
@@ -11,7 +12,7 @@ int mlm::gemm_cu_count() { return 256; }
 int main() {
   int causal, d, s, pairs;
   while (scanf("%d %d %d %d", &causal, &d, &s, &pairs) == 4)
-    printf("%d\\n", (int)mlm::attn_bwd_mode(s, pairs, causal != 0, d, d >= 128 ? 2 : 1));
+    printf("%d %d\\n", (int)mlm::attn_bwd_mode(s, pairs, causal != 0, d, d >= 128 ? 2 : 1), (int)mlm::attn_mode(s, pairs, causal != 0, d));
   return 0;
 }
 """
@@ -30,11 +31,26 @@ MEASURED = [
 ]
 
 
-def test_backward_takes_the_fastest_form(tmp_path):
-    (tmp_path / "modes.cpp").write_text(MAIN)
-    subprocess.run(["g++", "-std=c++17", "-I" + BLD.CSRC, str(tmp_path / "modes.cpp"), "-o", str(tmp_path / "modes")], check=True,
-                   timeout=60)
-    lines = "\n".join(" ".join(map(str, m[:4])) for m in MEASURED)
-    out = subprocess.run([str(tmp_path / "modes")], input=lines, text=True, check=True, capture_output=True, timeout=60).stdout
-    for m, mode in zip(MEASURED, map(int, out.split())):
+@pytest.fixture(scope="module")
+def modes(tmp_path_factory):
+    d = tmp_path_factory.mktemp("modes")
+    (d / "modes.cpp").write_text(MAIN)
+    subprocess.run(["g++", "-std=c++17", "-I" + BLD.CSRC, str(d / "modes.cpp"), "-o", str(d / "modes")], check=True, timeout=60)
+
+    def run(cases):
+        lines = "\n".join(" ".join(map(str, c)) for c in cases)
+        out = subprocess.run([str(d / "modes")], input=lines, text=True, check=True, capture_output=True, timeout=60).stdout
+        return [tuple(map(int, l.split())) for l in out.splitlines()]
+    return run
+
+
+def test_backward_takes_the_fastest_form(modes):
+    for m, (mode, _) in zip(MEASURED, modes([m[:4] for m in MEASURED])):
         assert m[4 + mode] <= 1.04 * min(m[4:]), (m, mode)
+
+
+def test_long_sequences_of_the_gpu_test_take_two_launches(modes):
+    for d in (64, 96, 128):
+        got = modes([(1, d, s, b * h) for b, h, s in TWO.SHAPES])
+        assert [mode for mode, _ in got] == [0, 0], (d, got)                     # two launches
+        assert [dq for _, dq in got] == [1, 0], (d, got)                         # dQ in paired wave groups, and in single ones
