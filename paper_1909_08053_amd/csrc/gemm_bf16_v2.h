@@ -920,6 +920,30 @@ hipError_t launch_gemm_bf16_v2(const GemmArgs& a, float* splitk_ws, hipStream_t 
   return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_B, false, JOB>(a, splitk_ws, job, st);
 }
 
+// How n weight gradients (both operands k-major) are launched: together in tiles of bn, `split`: with the last round in k-pieces; apart
+// (bn = 0) where they are no group or the shared last round gains nothing over separate launches with their k-splits.
+struct V2GroupPlan { int bn; V2GroupSplit split; };
+inline V2GroupPlan v2_group_plan(const GemmArgs* probs, int n, bool have_ws) {
+  V2GroupPlan p = {0, {0, 0, 0, 1e30}};
+  if (gemm_v2_group_off() || n < 2 || n > kMaxGroup) return p;
+  double alone = 0.0;
+  for (int q = 0; q < n; ++q) {
+    const int M = probs[q].M, N = probs[q].N, K = probs[q].K;
+    if (probs[q].epi != EPI_STORE || probs[q].bias != nullptr || K != probs[0].K) return p;
+    alone += v2_plan(M, N, K, true, v2_pick_bn<false, false, EPI_STORE>(M, N, K, true)).cost + 2.0;   // + launch and drain
+  }
+  const double big = v2_group_cost(probs, n, V2_B), small = v2_group_cost(probs, n, V2_SMALL);
+  const int forced = gemm_v2_forced_bn();
+  const bool use_small = forced ? forced == V2_SMALL : small < big;
+  if (!forced && have_ws) {
+    const V2GroupSplit sp = v2_group_split(probs, n);
+    const double whole = use_small ? v2_group_cost(probs, n, V2_SMALL, true) : big;
+    if (sp.split && sp.cost < 0.97 * whole && sp.cost + 2.0 < alone) return {V2_B, sp};
+  }
+  if ((use_small ? small : big) + 2.0 < alone) p.bn = use_small ? V2_SMALL : V2_B;
+  return p;
+}
+
 // How a weight gradient a0 and an input gradient a1 that do not depend on each other are launched: together in tiles of bn
 // (first_is_1: a1's tiles, the longer ones, lead), or apart (bn = 0).  Measured apart / together, the pass that forms dL included:
 // 8192 tokens x 3072 x 6400 533 / 490 us, 8192 x 1536 x 51200 2300 / 2155, 3008 x 3072 x 12800 420 / 345, 1536 x 3072 x 2048

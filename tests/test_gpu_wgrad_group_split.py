@@ -8,12 +8,16 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-# tokens, width, ways of the split (FFN width 4 x): K ending on a pair of slices, on half a pair and anywhere; few and many pieces; ragged
-# tiles in both directions; the split problem first and in the middle of the four
-@pytest.mark.parametrize("T,H,p", [(4096, 2560, 4), (3360, 2304, 3), (3333, 2560, 4), (2016, 1056, 1), (6000, 1152, 1), (4096, 1920, 2)])
-def test_weight_gradients_with_a_split_last_round(T, H, p):
-    Hl, F = H // p, 4 * H // p
-    d = B.make_dims(1, T, H, p, 4 * H, 8 * p, p, 0, B.MLM_BF16)
+# tokens, width, ways of the split, FFN width over width: K ending on a pair of slices, on half a pair and anywhere; few and many pieces;
+# ragged tiles in both directions; the split problem first and (the last two) third of the four
+SHAPES = [(4096, 2560, 4, 4), (3360, 2304, 3, 4), (3333, 2560, 4, 4), (2016, 1056, 1, 4), (6000, 1152, 1, 4), (4096, 1920, 2, 4),
+          (3333, 2560, 2, 1), (2048, 1536, 1, 2)]
+
+
+@pytest.mark.parametrize("T,H,p,f", SHAPES)
+def test_weight_gradients_with_a_split_last_round(T, H, p, f):
+    Hl, F = H // p, f * H // p
+    d = B.make_dims(1, T, H, p, f * H, 8 * p, p, 0, B.MLM_BF16)
     g = torch.Generator(device=DEV)
     g.manual_seed(T + H)
     x = {k: torch.randn(T, n, generator=g, device=DEV).bfloat16() for k, n in

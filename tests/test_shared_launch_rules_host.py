@@ -4,8 +4,10 @@ import subprocess
 
 import pytest
 
+import test_gpu_ce_bwd_joint as BCE
 import test_gpu_fp32_ce_bwd_joint as FCE
 import test_gpu_fp32_wgrad_group as FWG
+import test_gpu_wgrad_group_split as BWG
 from paper_1909_08053_amd import build as BLD
 
 F32 = """#include <stdio.h>
@@ -101,3 +103,74 @@ int main() { int t, nv; while (scanf("%d %d", &t, &nv) == 2) printf("%d\\n", mlm
     out = subprocess.run([str(tmp_path / "dl")], input=text, text=True, check=True, capture_output=True, timeout=60).stdout.split()
     for m, v in zip(DLOGITS, map(int, out)):
         assert m[3 if v == 4 else 2] == min(m[2:]), (m, v)
+
+
+BF16 = """#include <stdio.h>
+#include <string.h>
+#include "gemm_bf16_v2.h"
+namespace mlm {
+int gemm_cu_count() { return 256; }
+int gemm_v2_forced_bn() { return 0; }
+bool gemm_v2_group_off() { return false; }
+}
+using namespace mlm;
+int main() {                       // "d T H V" -> tile, whether dhf leads; "g T H p F / H" -> tile, the split problem, its pieces
+  char kind[4];
+  int T, H, x, f;
+  while (scanf("%3s %d %d %d", kind, &T, &H, &x) == 4) {
+    GemmArgs a[4];
+    memset(a, 0, sizeof(a));
+    auto set = [&](int q, int M, int N, int K) { a[q].M = M; a[q].N = N; a[q].K = K; a[q].epi = EPI_STORE; };
+    if (kind[0] == 'd') {
+      set(0, H, x, T);
+      set(1, T, H, x);
+      const V2Dual d = v2_dual(a[0], a[1]);
+      printf("%d %d 0\\n", d.bn, d.first_is_1);
+    } else {
+      if (scanf("%d", &f) != 1) return 1;
+      const int Hl = H / x, Fl = f * H / x;
+      set(0, Fl, H, T); set(1, H, Fl, T); set(2, H, 3 * Hl, T); set(3, Hl, H, T);
+      const V2GroupPlan p = v2_group_plan(a, 4, true);
+      printf("%d %d %d\\n", p.bn, p.split.last, p.split.split);
+    }
+  }
+  return 0;
+}
+"""
+
+# both bf16 gradients of the logits, tokens, width, vocabulary; us of the call in two launches, in one
+BF16_DUALS = [
+    (8192, 3072, 6400, 490, 458), (8192, 1536, 51200, 2154, 2030), (3008, 3072, 12800, 424, 353), (1536, 3072, 2048, 53.5, 45.7),
+    (6144, 2560, 3072, 166, 145), (320, 1920, 1000, 19.3, 15.0), (704, 384, 512, 16.4, 10.9), (3008, 3072, 4096, 131, 138),
+    (4096, 1920, 6400, 182, 186), (8192, 1536, 6400, 273, 266), (8192, 1920, 25600, 1307, 1406), (4096, 2560, 7648, 276, 260),
+    (2048, 1024, 4096, 53.3, 77.6), (4096, 3072, 6400, 249, 235), (8192, 2560, 12800, 806, 842), (1024, 1536, 6400, 58.5, 112.9),
+    (512, 1536, 7648, 46.4, 154.7), (4096, 1536, 25600, 571, 634), (2048, 3072, 25600, 517, 620), (8192, 768, 3200, 101.5, 166.5),
+    (400, 768, 3000, 28.5, 34.3), (1000, 512, 1024, 30.8, 14.6), (8192, 1536, 25600, 1104, 1070), (72, 384, 1000, 16.9, 12.0),
+]
+# bf16 weight gradients of a layer shard, tokens, width, ways of the split; us in whole tiles or a launch each, with a split last round
+BF16_GROUPS = [
+    (4096, 2560, 4, 154.2, 143.0), (3360, 2304, 3, 147.7, 130.0), (6176, 2560, 4, 249.4, 212.0), (7000, 2304, 3, 298.8, 260.1),
+    (8192, 1920, 2, 351.9, 320.9), (6000, 1152, 1, 238.7, 186.0), (4096, 1056, 1, 172.0, 123.1), (8192, 1216, 1, 341.7, 263.4),
+    (1536, 1056, 1, 49.1, 61.0), (2000, 1152, 1, 68.6, 82.0),
+]
+
+
+def test_bf16_rules(tmp_path):
+    src, exe = tmp_path / "bf16.hip", tmp_path / "bf16"
+    src.write_text(BF16)
+    subprocess.run([BLD._hipcc(), *BLD.FLAGS, str(src), "-o", str(exe)], check=True, capture_output=True, timeout=180)
+    lines = ["d %d %d %d" % s for s in BCE.SHAPES] + ["g %d %d %d %d" % s for s in BWG.SHAPES]
+    lines += ["d %d %d %d" % m[:3] for m in BF16_DUALS] + ["g %d %d %d 4" % m[:3] for m in BF16_GROUPS]
+    out = subprocess.run([str(exe)], input="\n".join(lines), text=True, check=True, capture_output=True, timeout=60).stdout
+    got = [tuple(map(int, l.split())) for l in out.splitlines()]
+    take = lambda n: [got.pop(0) for _ in range(n)]
+    # the shapes of the GPU tests: small tiles, then large ones with either gradient leading; a split problem in first and middle place
+    duals = take(len(BCE.SHAPES))
+    assert [d[0] for d in duals] == [128, 128, 128, 256, 256, 256, 256] and {d[1] for d in duals[3:]} == {0, 1}, duals
+    groups = take(len(BWG.SHAPES))
+    assert all(bn == 256 and split > 1 for bn, _, split in groups), groups
+    assert {0, 2} <= {last for _, last, _ in groups} and len({split for _, _, split in groups}) > 2, groups
+    for m, (bn, _, _) in zip(BF16_DUALS, take(len(BF16_DUALS))):
+        assert m[4 if bn else 3] <= 1.04 * min(m[3:]), (m, bn)
+    for m, (_, _, split) in zip(BF16_GROUPS, take(len(BF16_GROUPS))):
+        assert m[4 if split else 3] <= 1.04 * min(m[3:]), (m, split)
