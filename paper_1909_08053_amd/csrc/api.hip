@@ -501,7 +501,7 @@ static int attn_shard_bwd_impl(const mlm_dims* dims, const void* dx1, const void
   if (!defer) MLM_TRY_HIP(run_gemm(dt, gemm_wgrad(L.Hl, dims->H, L.T, ctx_r, dx1, dWo_r), st, sk));
   MLM_TRY_HIP(run_gemm(dt, gemm_dgrad(L.T, L.Hl, dims->H, dx1, Wo_r, dctx), st, sk));
   // attention core
-  // the dQ kernels compute delta = rowsum(dctx o ctx) themselves and store it for the dK/dV kernels
+  // delta = rowsum(dctx o ctx): formed and stored by the dQ kernel, or ahead of a joint launch (bf16); a joint fp32 launch stores none
   AttnArgs a;
   memset(&a, 0, sizeof(a));
   a.b = dims->b; a.s = dims->s; a.hl = L.hl; a.d = L.d; a.causal = dims->causal; a.key_len = key_len;

@@ -1,5 +1,5 @@
 // bf16 MFMA attention over a shard's local heads (gfx950): forward with a streaming softmax, and a
-// two-kernel backward (dQ per query block; dK/dV per key block) that recomputes the probabilities from
+// backward (dQ per query block; dK/dV per key block; in one launch or two, attn_bwd_mode) that recomputes the probabilities from
 // the saved log-sum-exp.  Nothing of size s x s touches HBM and no atomics are used, so results are
 // deterministic.
 //
@@ -379,9 +379,9 @@ __global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW
 // ------------------------------------------------------------------------------------------ backward: dQ
 // Same streaming structure as the forward kernel.  Per tile: S^T = K Q^T and dP^T = V dO^T (contraction along D),
 // P = exp2(S sc - lse), dS = P o (dP - delta), dQ^T += K^T dS^T with K read a second time through the transposing
-// loads.  delta_i = sum_d dO_id O_id is computed here from the rows the lanes already hold and stored for the
-// dK/dV kernel, which runs after this one.
-// MERGED: part of the joint kernel below; delta comes from attn_delta_bf16_kernel.
+// loads.  As a kernel of its own it forms delta_i = sum_d dO_id O_id from the rows that the lanes hold anyway and stores it, with the
+// log-sum-exp in log2 units, for the dK/dV kernel, which runs after it.
+// MERGED: part of the joint kernel below; attn_delta_bf16_kernel has stored both.
 template <int D, bool DROP, int MODE, bool MERGED>
 __device__ __forceinline__ void attn_bwd_dq_block(const AttnArgs a, const AttnBlock blk) {
   typedef ATile<D> TL;
@@ -583,7 +583,8 @@ __device__ __forceinline__ void attn_bwd_dq_block(const AttnArgs a, const AttnBl
 
 // ------------------------------------------------------------------------------------------ backward: dK, dV
 // Workgroup = 128 keys of one (batch, head), a wave owns 32 keys.  Q and dO tiles of 64 queries stream through the DMA
-// ring together with the tile's log-sum-exp (log2 units) and delta vectors, which the dQ kernel left in the workspace.
+// ring together with the tile's log-sum-exp (log2 units) and delta vectors, which the dQ kernel or, in the joint launch,
+// attn_delta_bf16_kernel left in the workspace.
 // Per 32-query half tile: S = Q K^T and dP = dO V^T (contraction along D), P = exp2(S sc - lse), dS = P o (dP - delta),
 // then dV^T += dO^T P and dK^T += Q^T dS with Q and dO read a second time through the transposing loads.
 // Head sizes up to 96 run TWO wave groups (8 waves, two per SIMD): group g takes the query tiles 2 j + g through its own
@@ -593,7 +594,7 @@ __device__ __forceinline__ void attn_bwd_dq_block(const AttnArgs a, const AttnBl
 // 128 K and V rows are copied to LDS once and their fragments are read per use.
 // Larger heads keep one group (their accumulators alone need more registers) and split the D columns of dK / dV over
 // two workgroups instead.
-// SPLIT: 64 keys per workgroup, and two waves of each group share a tile's 64 queries (attn_dkv_split: when).
+// SPLIT: 64 keys per workgroup, and two waves of each group share a tile's 64 queries (attn_bwd_mode, attn_dkv_split: when).
 template <int D, bool DROP, bool SPLIT>
 __device__ __forceinline__ void attn_bwd_dkv_block(const AttnArgs a, const AttnBlock blk) {
   typedef ATile<D> TL;
@@ -663,7 +664,7 @@ __device__ __forceinline__ void attn_bwd_dkv_block(const AttnArgs a, const AttnB
   const bf16* Qb = base + hd * D;
   const int ldo = a.hl * D;
   const bf16* dOb = (const bf16*)a.dctx + (size_t)bi * a.s * ldo + hd * D;
-  // per-query vectors in the workspace: [0] delta, [1] log-sum-exp in log2 units (both written by the dQ kernel)
+  // per-query vectors in the workspace: [0] delta, [1] log-sum-exp in log2 units (by the dQ kernel or attn_delta_bf16_kernel)
   const size_t nrow_all = (size_t)a.b * a.hl * a.s;
   const float* vec_b = ((wave_u & 1) ? a.delta + nrow_all : a.delta) + ((size_t)bi * a.hl + hd) * a.s;
   unsigned char* ring = lds_raw + grp * (NST * STAGE);        // this group's ring
@@ -969,7 +970,7 @@ static hipError_t launch_bwd_dd(const AttnArgs& a, hipStream_t st) {
   if constexpr (D > 128) {
     return launch_bwd_joint<D, DROP, ATTN_WIDE, false>(a, st);
   } else {
-    const AttnBwdMode bm = attn_bwd_mode(a.s, pairs, causal, D, dkv_dsplit<D>());
+    const AttnBwdMode bm = attn_bwd_mode(a.s, pairs, causal, dkv_dsplit<D>());
     if (bm == ATTN_BWD_JOINT) return launch_bwd_joint<D, DROP, ATTN_PAIR, false>(a, st);
     if (bm == ATTN_BWD_JOINT_SPLIT) return launch_bwd_joint<D, DROP, ATTN_SPLIT, true>(a, st);
     const AttnMode m = attn_mode(a.s, pairs, causal, D);
@@ -977,8 +978,9 @@ static hipError_t launch_bwd_dd(const AttnArgs& a, hipStream_t st) {
                    : m == ATTN_SPLIT ? launch_dq_m<D, DROP, ATTN_SPLIT>(a, st)
                                      : launch_dq_m<D, DROP, ATTN_WIDE>(a, st);
     if (e != hipSuccess) return e;
-    return attn_dkv_split(a.s, pairs, causal, D, dkv_dsplit<D>()) ? launch_dkv<D, DROP, true>(a, st)
-                                                                   : launch_dkv<D, DROP, false>(a, st);
+    if constexpr (D <= 96)
+      if (!causal && attn_dkv_split(a.s, pairs)) return launch_dkv<D, DROP, true>(a, st);
+    return launch_dkv<D, DROP, false>(a, st);
   }
 }
 

@@ -1,6 +1,6 @@
 // fp32 attention for dtype MLM_F32 on the fp32 matrix cores (v_mfma_f32_32x32x2_f32): streaming-softmax forward and a
-// two-kernel backward (dQ per query block, dK/dV per key block) that recompute the probabilities from the saved
-// log-sum-exp, so nothing of size s x s is ever stored and no atomics are needed (results are deterministic).
+// backward (dQ per query block, dK/dV per key block; one launch for both while their blocks find a compute unit each) that recomputes
+// the probabilities from the saved log-sum-exp, so nothing of size s x s is ever stored and no atomics are needed (results are deterministic).
 //
 // A workgroup owns 32 rows (queries in forward and dQ, keys in dK/dV) of one (batch, head); its four waves take the
 // 32-row tiles of the other sequence axis in turn (wave w: tiles w, w + 4, ...) and their partial results are merged
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_fwd_f32_kernel(AttnArgs
 
 // dQ_i = scale * sum_j dS_ij K_j,  dS_ij = P_ij (dO_i . V_j - delta_i),  P_ij = exp(scale q_i.k_j - lse_i);
 // delta_i = dO_i . O_i is formed here from rows the lanes hold and left in the workspace for the dK/dV kernel.
-// (JOINT: part of attn_bwd_f32_kernel, whose dK/dV blocks form delta themselves)
+// (JOINT: part of attn_bwd_dkv_f32_kernel<D, true>, whose dK/dV blocks form delta themselves)
 template <int D, bool JOINT>
 __device__ __forceinline__ void attn_bwd_dq_f32_block(const AttnArgs a, const AfBlock blk) {
   constexpr int DT = AfShape<D>::DT, NV = DT * 16;

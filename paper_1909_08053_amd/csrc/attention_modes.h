@@ -30,15 +30,12 @@ inline AttnMode attn_mode(int s, int pairs, bool causal, int d) {
   return ATTN_WIDE;
 }
 
-// dK / dV: 64-key workgroups (else 128-key ones) under the same condition; `parts` workgroups share a key block (large heads).
-// us, 128 / 64 keys: d = 96 1024 x 8 causal 27.6 / 19.4, 3072 x 4 causal 69 / 47, but full 74 / 91; 768 x 20 full 24 / 33; d = 64
-// 512 x 16 causal 14.3 / 10.2; d = 128 2048 x 1 causal 50 / 45, full 53 / 71, 4096 x 1 causal 112 / 147.  (d = 192 needs one
-// wave per SIMD.)
-inline bool attn_dkv_split(int s, int pairs, bool causal, int d, int parts) {
-  if (d > 128) return false;
-  const long cus = gemm_cu_count(), wgs = (long)parts * ((s + 127) / 128) * pairs;
-  const long xcd_wgs = (long)parts * ((s + 127) / 128) * ((pairs + 7) / 8);
-  return 2 * wgs <= cus && 2 * xcd_wgs <= (causal ? 2 : 1) * (cus / 8);
+// dK / dV in a launch of its own (attn_bwd_mode), no mask, d = 64 or 96: 64-key workgroups (else 128-key ones) while twice as many fit
+// the compute units overall and on the busiest XCD.  us, 128 / 64 keys: d = 96 1024 x 8 27 / 20, 64 1024 x 16 23 / 17; but 3072 x 4 74 / 91, 768 x
+// 20 24 / 33.  (Under a causal mask and for larger heads launches that small are joint.)
+inline bool attn_dkv_split(int s, int pairs) {
+  const long cus = gemm_cu_count(), blocks = (s + 127) / 128;
+  return 2 * blocks * pairs <= cus && 2 * blocks * ((pairs + 7) / 8) <= cus / 8;
 }
 
 // Backward: dQ and dK / dV as two launches (divided as above), or in one (attn_bwd_bf16_kernel), in 128-row workgroups or 64-row
@@ -49,11 +46,10 @@ inline bool attn_dkv_split(int s, int pairs, bool causal, int d, int parts) {
 //   64 153 -> 135, 2048 x 16 115 -> 92, 768 x 96 145 -> 140.  But not two pairs an XCD of more than one and a half blocks per
 //   unit: 4096 x 12 246 -> 255.
 //   No mask: only while the workgroups leave units idle, three quarters: d = 96 768 x 12 62 -> 56, but 2048 x 6 90 -> 98.
-//   d = 192: always (its blocks take a compute unit each): 1024 x 16 causal 188 -> 118, 2048 x 48 full 1616 -> 1211; 128 rows
-//   against 64 equal up to 8 an XCD, above 262 / 316 (1024 x 48).
+// (d = 192 has the joint launch in 128-row workgroups only: its blocks take a compute unit each, and two launches were 188 us against
+// 118, 1024 x 16 causal, and 1616 against 1211, 2048 x 48 full; 64 rows equal up to 8 an XCD, above 316 / 262, 1024 x 48.)
 enum AttnBwdMode { ATTN_BWD_TWO, ATTN_BWD_JOINT, ATTN_BWD_JOINT_SPLIT };
-inline AttnBwdMode attn_bwd_mode(int s, int pairs, bool causal, int d, int parts) {
-  if (d > 128) return ATTN_BWD_JOINT;
+inline AttnBwdMode attn_bwd_mode(int s, int pairs, bool causal, int parts) {
   const long xcd_cus = gemm_cu_count() / 8, blocks = (s + 127) / 128, xcd_pairs = (pairs + 7) / 8, xcd_wgs = xcd_pairs * blocks;
   if (2 * (1 + parts) * xcd_wgs <= xcd_cus + xcd_cus / 8) return ATTN_BWD_JOINT_SPLIT;
   if (!causal) return 4 * (1 + parts) * xcd_wgs <= 3 * xcd_cus ? ATTN_BWD_JOINT : ATTN_BWD_TWO;

@@ -11,8 +11,8 @@ int mlm::gemm_cu_count() { return 256; }
 int main() {
   int causal, d, s, pairs;
   while (scanf("%d %d %d %d", &causal, &d, &s, &pairs) == 4)
-    printf("%d %d\\n", (int)mlm::attn_mode(s, pairs, causal != 0, d),
-           (int)mlm::attn_dkv_split(s, pairs, causal != 0, d, d >= 128 ? 2 : 1));
+    printf("%d %d\\n", (int)mlm::attn_mode(s, pairs, causal != 0, d), causal || d > 96 ||
+           mlm::attn_bwd_mode(s, pairs, false, 1) != mlm::ATTN_BWD_TWO ? -1 : (int)mlm::attn_dkv_split(s, pairs));   // -1: not asked
   return 0;
 }
 """
@@ -50,6 +50,8 @@ def test_forward_and_dq_take_the_fastest_division(chosen):
 
 
 def test_dkv_takes_the_better_workgroup(chosen):
-    for m, (_, split) in zip(MEASURED, chosen):
-        assert not (m[1] > 128 and split)            # 64-key workgroups do not exist there
-        assert m[7 + split] <= 1.06 * min(m[7:9]) or m[1] > 128, (m, split)
+    """Where dK / dV is a launch of its own that has both forms: without a mask, up to 96."""
+    asked = [(m, split) for m, (_, split) in zip(MEASURED, chosen) if split >= 0]
+    assert len(asked) >= 4 and {split for _, split in asked} == {0, 1}, asked
+    for m, split in asked:
+        assert m[7 + split] <= 1.06 * min(m[7:9]), (m, split)
