@@ -102,11 +102,15 @@ def _p(t: Optional[torch.Tensor]):
     return t.data_ptr()
 
 
+# The raw handle of torch.cuda.current_stream(), without building the object; a torch without these two goes through the object.
+_raw_stream, _device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+
+
 def _st(stream):
     if stream is not None:
         return int(stream)
-    if torch.cuda.is_initialized():        # the raw handle of torch.cuda.current_stream(), without building the object
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream and _device and torch.cuda.is_initialized():
+        return _raw_stream(_device())
     return torch.cuda.current_stream().cuda_stream
 
 
