@@ -873,7 +873,7 @@ hipError_t launch_gemm_bf16_v2_group(const GemmArgs* probs, int n, hipStream_t s
   }
 }
 
-bool gemm_v2_group_off();                   // MLM_GEMM_GROUP=0: every GEMM in a launch of its own
+bool gemm_v2_group_off();                   // MLM_GEMM_GROUP=0: every weight gradient of a layer shard in a launch of its own
 int gemm_v2_forced_bn();                    // MLM_GEMM_BN=128|192|256 forces a tile width where it exists, else 0
 
 // The 192-wide tile exists for all but the cross-entropy epilogues, the small tile for every epilogue but the one that
@@ -935,7 +935,7 @@ inline V2GroupPlan v2_group_plan(const GemmArgs* probs, int n, bool have_ws) {
   const double big = v2_group_cost(probs, n, V2_B), small = v2_group_cost(probs, n, V2_SMALL);
   const int forced = gemm_v2_forced_bn();
   const bool use_small = forced ? forced == V2_SMALL : small < big;
-  if (!forced && have_ws) {
+  if ((!forced || forced == V2_B) && have_ws) {
     const V2GroupSplit sp = v2_group_split(probs, n);
     const double whole = use_small ? v2_group_cost(probs, n, V2_SMALL, true) : big;
     if (sp.split && sp.cost < 0.97 * whole && sp.cost + 2.0 < alone) return {V2_B, sp};
@@ -952,7 +952,7 @@ inline V2GroupPlan v2_group_plan(const GemmArgs* probs, int n, bool have_ws) {
 struct V2Dual { int bn; bool first_is_1; };
 inline V2Dual v2_dual(const GemmArgs& a0, const GemmArgs& a1) {
   V2Dual d = {0, v2_slices(a1.K) > v2_slices(a0.K)};
-  if (gemm_v2_forced_bn() || gemm_v2_group_off()) return d;
+  const int forced = gemm_v2_forced_bn();
   const int cus = gemm_cu_count(), nk0 = v2_slices(a0.K), nk1 = v2_slices(a1.K);
   // + launch and drain.  Busy compute units clock higher while others idle, so an unsplit last round costs less than its tiles
   // do in full ones (192 large tiles 0.89); the narrow tile falls behind at very long k (1600 slices: 1105 us, not 952).
@@ -973,12 +973,11 @@ inline V2Dual v2_dual(const GemmArgs& a0, const GemmArgs& a1) {
     const double c0 = v2_tile_cost(bn, nk0, one_each, 0.46), c1 = v2_tile_cost(bn, nk1, one_each, 0.46);
     return 2.0 + (d.first_is_1 ? two_batches(cus, n1, c1, n0, c0) : two_batches(cus, n0, c0, n1, c1));
   };
-  if (a0.K % (2 * V2_BK) == 0 && a1.K % V2_BK == 0 && a1.K >= 2 * V2_BK) {
+  if ((!forced || forced == V2_B) && a0.K % (2 * V2_BK) == 0 && a1.K % V2_BK == 0 && a1.K >= 2 * V2_BK) {
     const double t = price(V2_B, false);
     if (t < best) { best = t; d.bn = V2_B; }
   }
-  const double t = price(V2_SMALL, true);
-  if (t < best) d.bn = V2_SMALL;
+  if ((!forced || forced == V2_SMALL) && price(V2_SMALL, true) < best) d.bn = V2_SMALL;
   return d;
 }
 

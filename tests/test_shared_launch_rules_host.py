@@ -109,17 +109,19 @@ BF16 = """#include <stdio.h>
 #include <string.h>
 #include "gemm_bf16_v2.h"
 namespace mlm {
+int forced = 0, off = 0;
 int gemm_cu_count() { return 256; }
-int gemm_v2_forced_bn() { return 0; }
-bool gemm_v2_group_off() { return false; }
+int gemm_v2_forced_bn() { return forced; }
+bool gemm_v2_group_off() { return off != 0; }
 }
 using namespace mlm;
-int main() {                       // "d T H V" -> tile, whether dhf leads; "g T H p F / H" -> tile, the split problem, its pieces
+int main() {                       // "o BN OFF 0" sets the overrides; "d T H V" -> tile, whether dhf leads; "g T H p F / H" -> tile, the split problem, its pieces
   char kind[4];
   int T, H, x, f;
   while (scanf("%3s %d %d %d", kind, &T, &H, &x) == 4) {
     GemmArgs a[4];
     memset(a, 0, sizeof(a));
+    if (kind[0] == 'o') { forced = T; off = H; continue; }
     auto set = [&](int q, int M, int N, int K) { a[q].M = M; a[q].N = N; a[q].K = K; a[q].epi = EPI_STORE; };
     if (kind[0] == 'd') {
       set(0, H, x, T);
@@ -155,14 +157,37 @@ BF16_GROUPS = [
 ]
 
 
-def test_bf16_rules(tmp_path):
-    src, exe = tmp_path / "bf16.hip", tmp_path / "bf16"
+@pytest.fixture(scope="module")
+def bf16(tmp_path_factory):
+    d = tmp_path_factory.mktemp("bf16")
+    src, exe = d / "bf16.hip", d / "bf16"
     src.write_text(BF16)
     subprocess.run([BLD._hipcc(), *BLD.FLAGS, str(src), "-o", str(exe)], check=True, capture_output=True, timeout=180)
+
+    def run(lines):
+        out = subprocess.run([str(exe)], input="\n".join(lines), text=True, check=True, capture_output=True, timeout=60).stdout
+        return [tuple(map(int, l.split())) for l in out.splitlines()]
+    return run
+
+
+def test_overrides_change_what_they_name(bf16):
+    """A forced tile width leaves it open which products share a launch; ungrouped weight gradients leave the logits' alone."""
+    duals, groups = ["d 8192 3072 6400", "d 200 192 520"], ["g 8192 3072 8 4", "g 4096 2560 4 4"]
+    assert [bn for bn, _, _ in bf16(duals)] == [256, 128]
+    free = bf16(groups)
+    assert [bn for bn, _, _ in free] == [256, 256] and [split > 0 for _, _, split in free] == [False, True]
+    assert [bn for bn, _, _ in bf16(["o 256 0 0"] + duals)] == [256, 0]
+    assert [bn for bn, _, _ in bf16(["o 128 0 0"] + duals)] == [0, 128]
+    assert [bn for bn, _, _ in bf16(["o 0 1 0"] + duals)] == [256, 128]
+    assert bf16(["o 256 0 0"] + groups) == free
+    assert [g[::2] for g in bf16(["o 0 1 0"] + groups)] == [(0, 0)] * 2
+    assert [split for _, _, split in bf16(["o 128 0 0"] + groups)] == [0, 0]
+
+
+def test_bf16_rules(bf16):
     lines = ["d %d %d %d" % s for s in BCE.SHAPES] + ["g %d %d %d %d" % s for s in BWG.SHAPES]
     lines += ["d %d %d %d" % m[:3] for m in BF16_DUALS] + ["g %d %d %d 4" % m[:3] for m in BF16_GROUPS]
-    out = subprocess.run([str(exe)], input="\n".join(lines), text=True, check=True, capture_output=True, timeout=60).stdout
-    got = [tuple(map(int, l.split())) for l in out.splitlines()]
+    got = bf16(lines)
     take = lambda n: [got.pop(0) for _ in range(n)]
     # the shapes of the GPU tests: small tiles, then large ones with either gradient leading; a split problem in first and middle place
     duals = take(len(BCE.SHAPES))
