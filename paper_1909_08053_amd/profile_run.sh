@@ -8,7 +8,7 @@ set -o pipefail
 cd /tmp && export TMPDIR=/tmp && cd "${GRAFT_REPO_ROOT:-$OLDPWD}" || exit 1
 O=gpurun_out/prof
 rm -rf $O && mkdir -p $O
-PARTS="${1:-all}"          # all | core | sweeps
+PARTS="${1:-all}"          # all | core | launches | sweeps
 step() { echo "== $1"; }
 
 if [ "$PARTS" = all ] || [ "$PARTS" = core ]; then
@@ -31,6 +31,14 @@ if [ "$PARTS" = all ] || [ "$PARTS" = core ]; then
   timeout -s KILL 150 rocprofv3 --pmc SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CYCLES \
         -d $O/sq -o bench --output-format csv -- \
         python3 bench.py --steps 3 --warmup 1 --no-cpu-baseline --no-call-table > $O/sq.log 2>&1 || exit 1
+fi
+
+if [ "$PARTS" = all ] || [ "$PARTS" = launches ]; then
+  for w in fp32_layer_step eval_2p5b_b1_forward ragged_bf16_step gpt2_1p2b_p8_step bert_3p9b_dropout_step train_8p3b_2_layers; do
+    step "kernel trace of $w"
+    timeout -k 10 150 rocprofv3 --kernel-trace -d $O/launches/$w -o x --output-format csv -- \
+          python3 -m paper_1909_08053_amd.sweep --workload $w --steps 20 > $O/launches_$w.log 2>&1 || exit 1
+  done
 fi
 
 if [ "$PARTS" = all ] || [ "$PARTS" = sweeps ]; then

@@ -1,7 +1,7 @@
 """Turns the raw output of profile_run.sh (rocprofv3 CSVs, benchmark JSON, sweep logs) into the text summaries under
 profiles/ and profiles/traffic.json.  No GPU needed:
 
-    python -m paper_1909_08053_amd.profile_tables <raw output directory of profile_run.sh> [core|sweeps|all]
+    python -m paper_1909_08053_amd.profile_tables <raw output directory of profile_run.sh> [core|launches|sweeps|all]
 
 Every summary starts with the command that produced its raw data.  The summaries hold measured figures and ratios
 derived from them only, no interpretation.
@@ -273,6 +273,36 @@ def microbench(raw):
     _write("mfma_lds_microbench.txt", L)
 
 
+# ---------------------------------------------------------------------------------------------- launches of the workloads
+def launches(raw, passes=20, timed=10):
+    """One line per launch of a pass (mean and minimum over the last passes), which is found as the period of the launch sequence."""
+    L = ["Launches of one pass of the workloads of perf/cases.py that have no table of their own, in order (one MI355X; mean and minimum over",
+         f"the last {timed} of {passes} passes; wgs: workgroups).",
+         f"command: {PRE}rocprofv3 --kernel-trace -d gpurun_out/prof/launches/<workload> -o x --output-format csv -- python3 -m "
+         f"paper_1909_08053_amd.sweep --workload <workload> --steps {passes}"]
+    for d in sorted(glob.glob(os.path.join(raw, "launches", "*"))):
+        rows = [r for r in csv.DictReader(open(_find(d, "", "*kernel_trace.csv"))) if "mlm" in r["Kernel_Name"]]
+        rows.sort(key=lambda r: int(r["Start_Timestamp"]))
+        grid = lambda r: int(r["Grid_Size_X"]) * int(r["Grid_Size_Y"]) // (int(r["Workgroup_Size_X"]) * int(r["Workgroup_Size_Y"]))
+        seq = [(r["Kernel_Name"], grid(r)) for r in rows]
+        n = next(p for p in range(1, len(seq) // timed + 1) if all(seq[-1 - i] == seq[-1 - i - p] for i in range((timed - 1) * p)))
+        us = lambda r: (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3
+        tail = rows[-n * timed:]
+        names = [r["Kernel_Name"] for r in tail[:n]]
+        last = next(k for k in ("adamw", "reduce_cols_batch", "ce_merge") if any(k in m for m in names))      # a pass ends with
+        first = max(i for i in range(n) if last in names[i]) + 1
+        L += ["", f"{os.path.basename(d)}: {n} launches", f"{'kernel':96s} {'wgs':>7s} {'avg us':>8s} {'min us':>8s}"]
+        tot = 0.0
+        for i in range(n):
+            col = [us(tail[(first + i) % n + k * n]) for k in range(timed)]
+            tot += st.mean(col)
+            name = re.sub(r"^_ZN3mlm\d+(\w+?_kernel)I", r"\1<", _short(tail[(first + i) % n]["Kernel_Name"]))
+            L.append(f"{name[:96]:96s} {seq[-n * timed + (first + i) % n][1]:7d} {st.mean(col):8.1f} {min(col):8.1f}")
+        span = (int(tail[-1]["End_Timestamp"]) - int(tail[0]["Start_Timestamp"])) / 1e3 / timed
+        L.append(f"{'sum of kernel durations; pass, launch to launch':96s} {'':7s} {tot:8.1f} {span:8.1f}")
+    _write("launches_of_the_measured_workloads.txt", L)
+
+
 # ---------------------------------------------------------------------------------------------- sweeps
 def _raw_lines(path):
     return [l.rstrip() for l in open(path).read().splitlines() if l.strip() and "amdgpu.ids" not in l]
@@ -335,6 +365,8 @@ def main():
         kernels(raw)
         traffic(raw)
         sq_counters(raw)
+    if part in ("all", "launches"):
+        launches(raw)
     if part in ("all", "sweeps"):
         sweeps(raw)
 

@@ -204,9 +204,20 @@ def bert_loss_rows_timing(steps, warmup, dev="cuda:0"):
         torch.cuda.empty_cache()
 
 
+def workload_passes(name, steps):
+    import torch
+    from perf import cases
+    state = cases.prepare(next(c for c in cases.listed() if c["name"] == name), 1)
+    for _ in range(steps):
+        cases.run(state)
+    torch.cuda.synchronize()
+    print(f"{name}: {steps} passes")
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--sweep", default="all", choices=["heads", "strong_1p2b", "table1", "optimizer", "dropout", "stack", "bert_rows", "all"])
+    ap.add_argument("--workload", help="run --steps passes of this workload of perf/cases.py and print their number (for a kernel trace)")
     ap.add_argument("--recompute", action="store_true",
                     help="checkpointed variant: re-run the layer's forward before its backward (activation recomputation)")
     ap.add_argument("--steps", type=int, default=20)
@@ -218,6 +229,9 @@ def main():
     if not torch.cuda.is_available():
         sys.exit("sweep: no GPU visible")
     B.lib()
+    if args.workload:
+        workload_passes(args.workload, args.steps)
+        return
     names = ["heads", "strong_1p2b", "table1"] if args.sweep == "all" else [args.sweep]
     if args.sweep == "optimizer":
         optimizer_timing(args.steps, args.warmup)
