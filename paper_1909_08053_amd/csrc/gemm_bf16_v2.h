@@ -325,8 +325,8 @@ inline void v2_set_walk(V2Plan* p, int window, int K, bool strips = false) {
 // The small tile has two: `alone` with at most one workgroup per compute unit in the launch, else for two that share one
 // (fitted to 60 .. 2600 tiles of 48 .. 256 slices).  The dearer price of an odd number of tile rows, or of few, comes from a
 // walk that spread those over all XCDs: 1920 x 12800 x 8192 (15 tile rows) 591 us, 256-wide 347.  With v2_tile_of the cheaper
-// one fits every row count (that shape: 370 / 352), so the line is cautious: where it keeps a large tile the small one is now up
-// to 1.3 x faster (768 x 6400 x 6144: 67 / 88 us).
+// one fits every row count (that shape: 373 / 350), so the line is cautious: where it keeps a large tile the small one is now up
+// to a fifth faster (768 x 6400 x 6144: 74 / 90 us).
 inline double v2_small_slice(int tiles_m) {
   if (tiles_m % 2 || tiles_m <= 10) return 0.72;
   return 0.46;
