@@ -39,8 +39,8 @@
  *     the list that mlm_deferred_sums_begin opens and mlm_deferred_sums_flush closes;
  *     (d) two tuning
  *     overrides that are read from the environment ONCE per process, at the first
- *     bf16 GEMM: MLM_GEMM_BN=128|192|256 (tile width where it exists), MLM_GEMM_GROUP=0 (weight
- *     gradients launched one by one).  They choose between kernels that compute the
+ *     bf16 GEMM: MLM_GEMM_BN=128|192|256 (tile width where it exists), MLM_GEMM_GROUP=0 (the weight
+ *     gradients of a layer shard launched one by one).  They choose between kernels that compute the
  *     same sums in a different order and exist for A/B measurements; unset, the
  *     library chooses by its cost model.  Calls may come from several host threads.
  *   - H, H/p, F/p, V/p and the head size must be multiples of 8 and pointers 16-byte
