@@ -17,7 +17,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmlm_shard.so")
 
-SOURCES = ["api.hip", "rowops.hip", "gemm_f32.hip", "attention_f32.hip", "gemm_bf16.hip",
+SOURCES = ["api.hip", "rowops.hip", "gemm_f32.hip", "gemm_f32_pieces.hip", "attention_f32.hip", "gemm_bf16.hip",
            "gemm_bf16_fwd.hip", "gemm_bf16_dgrad.hip", "gemm_bf16_wgrad.hip", "gemm_bf16_dual.hip", "attention_bf16.hip", "optimizer.hip", "embed.hip"]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",

@@ -1,5 +1,6 @@
-// fp32 GEMM for dtype MLM_F32 on the fp32 matrix cores (v_mfma_f32_32x32x2_f32: 157 TFLOP/s on the whole chip, fp32
-// products and fp32 accumulation, so the precision is that of a chain of fused multiply-adds).
+// fp32 GEMM for dtype MLM_F32.  Here on the fp32 matrix cores (v_mfma_f32_32x32x2_f32: 157 TFLOP/s on the whole chip, fp32
+// products and fp32 accumulation, so the precision is that of a chain of fused multiply-adds); outputs that fill the chip and sums
+// that are long go to gemm_f32_pieces.hip.
 // Computes C[m,n] = sum_k A(m,k) B(k,n) with either operand stored k-contiguous or not, and the same fused epilogues as
 // the bf16 kernel (bias, bias+GeLU with saved pre-activation, GeLU', dlogits).
 //
@@ -19,70 +20,15 @@
 #include <string.h>
 #include <type_traits>
 #include <utility>
-#include "common.h"
+#include "gemm_f32_common.h"
 #include "gemm_f32_pick.h"
 
 namespace mlm {
 
-// Epilogue of one accumulator element.
-struct F32Row { float coef, Mr, invS; int loc; };
-template <int EPI>
-__device__ __forceinline__ F32Row f32_row(const GemmArgs& a, int m) {
-  F32Row r = {0.f, 0.f, 0.f, -1};
-  if (EPI == EPI_DLOGITS) {
-    r.coef = (a.loss_w ? a.loss_w[m] : 1.0f) / a.loss_stats[1];
-    r.Mr = a.Mrow[m];
-    r.invS = r.coef / a.Srow[m];
-    r.loc = a.targets[m] - a.v0;
-  }
-  return r;
-}
-template <int EPI>
-__device__ __forceinline__ void f32_put(const GemmArgs& a, const F32Row& r, int m, int n, float bias, float v) {
-  float* C = (float*)a.C + (size_t)m * a.ldc + n;
-  if (EPI == EPI_STORE) {
-    *C = v + bias;
-  } else if (EPI == EPI_BIAS_GELU) {
-    v += bias;
-    ((float*)a.aux)[(size_t)m * a.ldaux + n] = v;
-    *C = gelu_fwd(v, a.gelu_tanh != 0);
-  } else if (EPI == EPI_DGELU) {
-    *C = v * gelu_bwd(((const float*)a.aux)[(size_t)m * a.ldaux + n], a.gelu_tanh != 0);
-  } else if (EPI == EPI_DLOGITS) {
-    float g = expf(v - r.Mr) * r.invS;
-    if (n == r.loc) g -= r.coef;
-    *C = g;
-  }
-}
 // One 16 x 16 accumulator tile whose first row / column is (m0, n0): a lane holds four consecutive columns of one row.
 template <int EPI>
 __device__ __forceinline__ void f32_store_tile(const GemmArgs& a, const floatx4& acc, int m0, int n0, int lane) {
-  const int m = m0 + (lane & 15), n = n0 + 4 * (lane >> 4);
-  if (m >= a.M || n >= a.N) return;                   // N is a multiple of 8: four columns are all in or all out
-  float* C = (float*)a.C + (size_t)m * a.ldc + n;
-  float v[4] = {acc[0], acc[1], acc[2], acc[3]};
-  if ((EPI == EPI_STORE || EPI == EPI_BIAS_GELU) && a.bias) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] += ((const float*)a.bias)[n + e];
-  }
-  if (EPI == EPI_BIAS_GELU) {
-    *reinterpret_cast<float4*>((float*)a.aux + (size_t)m * a.ldaux + n) = make_float4(v[0], v[1], v[2], v[3]);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = gelu_fwd(v[e], a.gelu_tanh != 0);
-  } else if (EPI == EPI_DGELU) {
-    const float4 g = *reinterpret_cast<const float4*>((const float*)a.aux + (size_t)m * a.ldaux + n);
-    const float gv[4] = {g.x, g.y, g.z, g.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] *= gelu_bwd(gv[e], a.gelu_tanh != 0);
-  } else if (EPI == EPI_DLOGITS) {
-    const F32Row r = f32_row<EPI>(a, m);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      v[e] = expf(v[e] - r.Mr) * r.invS;
-      if (n + e == r.loc) v[e] -= r.coef;
-    }
-  }
-  *reinterpret_cast<float4*>(C) = make_float4(v[0], v[1], v[2], v[3]);
+  f32_put4<EPI>(a, acc, m0 + (lane & 15), n0 + 4 * (lane >> 4));
 }
 
 // ---- operand tile of ROWS x KT staged through LDS by NT threads ----------------------------------------------------
@@ -302,22 +248,6 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_kernel(Gem
 constexpr int kF32SplitWaves = 8;
 constexpr int kF32SplitStep = 4;        // chunks of 8 k per step: 32 k, a full 128-byte line of a k-contiguous row
 
-// (a k-contiguous operand has K a multiple of 8; K of the weight gradient counts tokens and can be any number: its last
-// chunk is filled up with zeros)
-template <bool KC>
-__device__ __forceinline__ void f32_frag_global(const float* __restrict__ P, int ld, int row, int k, int K, float (&f)[4]) {
-  if (KC) {
-    const float4 v = *reinterpret_cast<const float4*>(P + (size_t)row * ld + k);
-    f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
-  } else {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      f[j] = P[(size_t)min(k + j, K - 1) * ld + row];
-      f[j] = k + j < K ? f[j] : 0.f;
-    }
-  }
-}
-
 template <bool A_KC, bool B_KC, int EPI>
 __device__ __forceinline__ void f32_split_tile(const GemmArgs& a, int tile) {
   constexpr int NWV = kF32SplitWaves, ST = kF32SplitStep;
@@ -386,29 +316,15 @@ __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_kernel(Gem
 
 // The tiles of several weight gradients in one launch: such a GEMM takes 6 us whatever its size, and nothing waits for the
 // four of a layer shard one by one (four launches of 256 x {256, 512} x 256: 24 -> 11 us in one).
-constexpr int kF32Group = 4;
-struct F32Group {
-  GemmArgs a[kF32Group];
-  int tile_begin[kF32Group];           // first tile of each problem (past the grid for problems that do not exist)
-};
-__device__ __forceinline__ int f32_group_at(const F32Group& g, GemmArgs* a) {      // this workgroup's problem, and its tile there
-  const int id = blockIdx.x;
-  int first = 0;
-  *a = g.a[0];
-#pragma unroll
-  for (int q = 1; q < kF32Group; ++q)
-    if (id >= g.tile_begin[q]) { *a = g.a[q]; first = g.tile_begin[q]; }     // workgroup-uniform
-  return id - first;
-}
 __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_group_kernel(F32Group g) {
   GemmArgs a;
-  const int tile = f32_group_at(g, &a);
+  const int tile = f32_group_at(g, blockIdx.x, &a);
   f32_split_tile<false, false, EPI_STORE>(a, tile);
 }
 template <int BM, int BN, int WM, int WN, int KS, int KT, int CH>
 __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_group_kernel(F32Group g) {
   GemmArgs a;
-  const int tile = f32_group_at(g, &a);
+  const int tile = f32_group_at(g, blockIdx.x, &a);
   f32_tile<false, false, EPI_STORE, BM, BN, WM, WN, KS, KT, CH>(a, tile);
 }
 
@@ -491,6 +407,7 @@ static hipError_t launch_f32_tile_group(const F32Group& g, int total, hipStream_
 
 template <bool A_KC, bool B_KC, int EPI>
 static hipError_t launch_f32_layout(const GemmArgs& a, hipStream_t st) {
+  if (const int bt = f32_pieces_pick(a.M, a.N, a.K)) return launch_f32_pieces(a, bt, st);
   switch (f32_pick(a.M, a.N, a.K)) {
     case 32: {
       const int tiles = ((a.M + 31) / 32) * ((a.N + 31) / 32);
@@ -502,16 +419,39 @@ static hipError_t launch_f32_layout(const GemmArgs& a, hipStream_t st) {
   }
 }
 
-// Weight gradients (both operands k-major, plain store) of one K, as f32_group_plan says.
-hipError_t launch_gemm_f32_wgrads(const GemmArgs* probs, int n, hipStream_t st) {
-  bool together = n >= 2 && n <= kF32Group;
-  int M[kF32Group], N[kF32Group];
-  for (int q = 0; q < n && together; ++q) {
-    together = !probs[q].a_kc && !probs[q].b_kc && probs[q].epi == EPI_STORE && probs[q].K == probs[0].K;
-    M[q] = probs[q].M;
-    N[q] = probs[q].N;
+// Weight gradients (both operands k-major, plain store) of one K: those in pieces share a launch per tile size, the others as
+// f32_group_plan says.
+hipError_t launch_gemm_f32_wgrads(const GemmArgs* all, int n_all, hipStream_t st) {
+  bool together = n_all >= 2 && n_all <= kF32Group;
+  for (int q = 0; q < n_all && together; ++q)
+    together = !all[q].a_kc && !all[q].b_kc && all[q].epi == EPI_STORE && all[q].K == all[0].K;
+  GemmArgs probs[kF32Group];
+  int M[kF32Group], N[kF32Group], n = 0;
+  for (int q = 0; q < n_all && !together; ++q)
+    if (hipError_t e = launch_gemm_f32(all[q], st); e != hipSuccess) return e;
+  if (!together) return hipSuccess;
+  for (int bt : {128, 64}) {
+    F32Group g;
+    memset(&g, 0, sizeof(g));
+    int m = 0, total = 0;
+    for (int q = 0; q < n_all; ++q) {
+      if (f32_pieces_pick(all[q].M, all[q].N, all[q].K) != bt) continue;
+      g.a[m] = all[q];
+      g.tile_begin[m++] = total;
+      total += ((all[q].M + bt - 1) / bt) * ((all[q].N + bt - 1) / bt);
+    }
+    if (m == 0) continue;
+    for (int q = m; q < kF32Group; ++q) g.tile_begin[q] = total;
+    if (hipError_t e = launch_f32_pieces_group(g, total, bt, st); e != hipSuccess) return e;
   }
-  const F32GroupPlan p = together ? f32_group_plan(M, N, n, probs[0].K) : F32GroupPlan{};
+  for (int q = 0; q < n_all; ++q) {
+    if (f32_pieces_pick(all[q].M, all[q].N, all[q].K)) continue;
+    M[n] = all[q].M;
+    N[n] = all[q].N;
+    probs[n++] = all[q];
+  }
+  if (n == 0) return hipSuccess;
+  const F32GroupPlan p = f32_group_plan(M, N, n, probs[0].K);
   auto launch = [&](int b, int chains, bool wide, bool narrow) {      // those that take the 128-wide tile alone, and / or the others
     F32Group g;
     memset(&g, 0, sizeof(g));
@@ -539,6 +479,7 @@ hipError_t launch_gemm_f32_wgrads(const GemmArgs* probs, int n, hipStream_t st) 
 }
 
 hipError_t launch_gemm_f32_dgrad_colsum(const GemmArgs& a, const ColsumJob& j, hipStream_t st) {
+  if (const int bt = f32_pieces_pick(a.M, a.N, a.K)) return launch_f32_pieces_colsum(a, j, bt, st);
   switch (f32_pick(a.M, a.N, a.K)) {
     case 32: {
       const int tiles = ((a.M + 31) / 32) * ((a.N + 31) / 32);
@@ -561,7 +502,8 @@ static hipError_t launch_f32_tile_dual(const GemmArgs& w, const GemmArgs& x, dim
 }
 
 hipError_t launch_gemm_f32_dual(const GemmArgs& w, const GemmArgs& x, hipStream_t st) {
-  const F32DualPick p = f32_dual_pick(w.M, w.N, w.K, x.M, x.N, x.K);
+  const bool pieces = f32_pieces_pick(w.M, w.N, w.K) || f32_pieces_pick(x.M, x.N, x.K);
+  const F32DualPick p = pieces ? F32DualPick{0, 0} : f32_dual_pick(w.M, w.N, w.K, x.M, x.N, x.K);
   const int b = p.tile;
   if (b == 0) {
     if (hipError_t e = launch_gemm_f32(w, st); e != hipSuccess) return e;

@@ -40,6 +40,45 @@ inline double f32_us(int M, int N, int K) {
   return b == 32 ? f32_split_us(M, N, K) : f32_tile_us(b, f32_tiles(b, M, N), K);
 }
 
+// Microseconds of one launch with t tiles of b x b in it, b = 64 or 128: per round of two tiles a unit, and per k tile of it.  (Fitted to
+// the four weight gradients of 103 layer shards of 12 .. 2726 tokens and 320 .. 2048 wide: within 6 % and, 128-wide, 2 %.  At short k
+// the stores decide, which f32_tile_us leaves out.)
+inline double f32_launch_us(int b, int chains, double t, int K) {
+  const int cus = gemm_cu_count(), nk = (K + (b == 64 ? 63 : 31)) / (b == 64 ? 64 : 32);
+  const double full = (double)(long)(t / (2 * cus)), rem = t - full * 2 * cus;
+  const double two = b == 128 ? 5.1 + 3.8 * nk : chains == 8 ? 3.5 + 2.2 * nk : 1.9 + 2.1 * nk;
+  const double one = b == 128 ? 2.9 + 2.0 * nk : chains == 8 ? 2.5 + 1.0 * nk : 1.6 + 1.04 * nk;
+  return (b == 128 ? 4.2 : 3.6) + (full + (rem > cus)) * two + (rem > 0 && rem <= cus ? one : 0.0);
+}
+
+// Products in pieces on the bf16 matrix cores (gemm_f32_pieces.hip), in 128-wide tiles (two a compute unit) or 64-wide ones (one, its
+// k in four chains), against the kernels above: microseconds of t tiles in one launch.  A round of 64-wide tiles, or of at most one
+// 128-wide tile a unit, takes little less where units stay idle; more 128-wide tiles share the chip's power and take their share of it.
+// Three layouts, plain stores, kernels above / 128 / 64: 1024 x 1024 x 4096 75 / 147 / 65 us, 768 x 2048 x 4096 135 / 149 / 117,
+// 1024 x 3072 x 1024 54 / 45 / 56, 1024 x 4096 x 512 39 / 29 / 45, x 1024 71 / 52 / 74, 1536 x 4096 x 1024 105 / 82 / 107,
+// 2048 x 6144 x 1024 194 / 142 / 222, 4096^3 980 / 665 / 950; but 1024 x 1024 x 256 8.4 / 15 / 9.5, 256 x 1024 x 4096 36 / 148 / 57
+// (the split kernel's workgroups find a unit each: those sizes stay with it).
+inline double f32_pieces_us(int bt, double t, int K) {
+  const int cus = gemm_cu_count();
+  const double f = t / cus;
+  if (bt == 128) {
+    const double step = f <= 1.0 ? 0.55 + (f > 0.5 ? 0.28 * (f - 0.5) : 0.0) : 0.67 * f > 1.05 ? 0.67 * f : 1.05;   // per 16 k
+    return 5.5 + 2.0 * f + step * ((K + 15) / 16);
+  }
+  const double full = (double)(long)f, rem = f - full;
+  return 2.0 + 4.2 * (full + (rem > 0.0)) + (0.925 * full + (rem > 0.0 ? 0.74 + 0.185 * rem : 0.0)) * ((K + 63) / 64);
+}
+// The tile of the product in pieces, or 0.  (At least a whole step of the 64-wide tile's: what is fetched ahead of the last step lies
+// inside [0, K); and K up to where its 32-bit lane offsets reach.)
+inline int f32_pieces_pick(int M, int N, int K) {
+  const int b = f32_pick(M, N, K);
+  if (b == 32 || K < 64 || K > kF32MaxK128) return 0;
+  const double t128 = f32_pieces_us(128, f32_tiles(128, M, N), K), t64 = f32_pieces_us(64, f32_tiles(64, M, N), K);
+  const double best = t128 < t64 ? t128 : t64;
+  if (best >= 0.97 * f32_launch_us(b, b == 64 ? 2 : 1, f32_tiles(b, M, N), K)) return 0;
+  return t128 < t64 ? 128 : 64;
+}
+
 // Launches that hold several problems.  No result gets further from the exact one by sharing a launch, so a tile's sums are at least
 // as many chains over k as those of the kernel that its problem takes alone: eight in the split kernel, two in the 64-wide tiles, one
 // in the 128-wide ones.  (Two chains in place of eight were up to 1.9 x further off, one in place of two 1.4 x: 55 tokens x 768 x 3072,
@@ -68,17 +107,6 @@ inline F32DualPick f32_dual_pick(int M0, int N0, int K0, int M1, int N1, int K1)
                                                      : two_batches(2 * cus, nl, 31.5 * kl, ns, 31.5 * ks));
   if (both >= 0.95 * (2.0 + f32_us(M0, N0, K0) + f32_us(M1, N1, K1))) return {0, 0};
   return {64, split ? 8 : 2};
-}
-
-// Microseconds of one launch with t tiles of b x b in it, b = 64 or 128: per round of two tiles a unit, and per k tile of it.  (Fitted to
-// the four weight gradients of 103 layer shards of 12 .. 2726 tokens and 320 .. 2048 wide: within 6 % and, 128-wide, 2 %.  At short k
-// the stores decide, which f32_tile_us leaves out.)
-inline double f32_launch_us(int b, int chains, double t, int K) {
-  const int cus = gemm_cu_count(), nk = (K + (b == 64 ? 63 : 31)) / (b == 64 ? 64 : 32);
-  const double full = (double)(long)(t / (2 * cus)), rem = t - full * 2 * cus;
-  const double two = b == 128 ? 5.1 + 3.8 * nk : chains == 8 ? 3.5 + 2.2 * nk : 1.9 + 2.1 * nk;
-  const double one = b == 128 ? 2.9 + 2.0 * nk : chains == 8 ? 2.5 + 1.0 * nk : 1.6 + 1.04 * nk;
-  return (b == 128 ? 4.2 : 3.6) + (full + (rem > cus)) * two + (rem > 0 && rem <= cus ? one : 0.0);
 }
 
 // n weight gradients of the same K that do not depend on each other: how they are launched.  The four of a layer shard, a launch each /
