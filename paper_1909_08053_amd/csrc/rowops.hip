@@ -5,6 +5,7 @@
 // statistics are wave-level shuffles, HBM access is 16-byte vectors, coalesced along H.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 #include "common.h"
 #include "schedule.h"
 #include "rng.h"
@@ -198,8 +199,8 @@ hipError_t launch_combine_layernorm_fwd(int dtype, int T, int H, float eps, cons
 // Block = one wave per 64 vectors of a row; the rows are dealt to the blocks (ln_bwd_blocks of them) in batches of
 // kLnBwdBatch, round-robin.  A lane owns
 // ONE 16-byte vector of columns in every row, so its dgamma / dbeta (/ dx column-sum) partials are a handful of
-// registers and several waves fit on a SIMD (a wave-per-row layout needs the partials of the whole row per lane:
-// ~150 registers, one wave per SIMD, and ran at half the HBM rate).  The row statistics s1 = mean(dy gamma),
+// registers and several waves fit on a SIMD.  (For fp32, rows over 3072 columns and few rows; else ln_bwd_rows_kernel below, which needs
+// a sixth of this form's wave reductions per element.)  The row statistics s1 = mean(dy gamma),
 // s2 = mean(dy gamma xhat) need the whole row: every wave reduces its slab, the per-wave partials meet in LDS and are
 // added in a fixed order (deterministic); one barrier per batch (the exchange buffer alternates).  Everything that needs
 // no row statistic (dgamma, dbeta) is accumulated in the pass before the barrier; the pass after it is two fused
@@ -385,6 +386,164 @@ __global__ __launch_bounds__(VB == 8 ? 768 : 512) void ln_bwd_kernel(int rows, i
   }
 }
 
+// The same with SP = 1 or 2 waves per ROW, for bf16 rows of up to 512 NV SP columns (a lane: NV vectors of eight).  A wave of its own
+// reduces a row's statistics by itself, without exchange or barrier; two exchange two sums, one barrier per row, and have the next row
+// in flight.  The column partials of the rows that a wave meets stay in its registers (8 NV of each quantity); the workgroup's eight
+// waves add theirs through LDS at the end.
+constexpr int kLnRowWaves = 8;
+template <int NV, int SP, bool FUSED, bool SUM, bool DZ>
+__global__ __launch_bounds__(64 * kLnRowWaves, 2) void ln_bwd_rows_kernel(int rows, int H, const bf16* __restrict__ dy,
+                                                                          const bf16* __restrict__ x, const bf16* __restrict__ gamma,
+                                                                          const float* __restrict__ mean, const float* __restrict__ rstd,
+                                                                          const bf16* residual, bf16* dx, float* __restrict__ ws,
+                                                                          PartialPtrs ptrs, int n, bf16* dy_out, DropArgs drop, bf16* dz_out) {
+  typedef Vec16<bf16> V;
+  constexpr int NP = SUM ? 3 : 2, RPB = kLnRowWaves / SP;               // rows of a workgroup at a time
+  extern __shared__ __attribute__((aligned(16))) float lds_rows[];      // [wave][512 NV]
+  __shared__ float red[2][kLnRowWaves][2];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nvec = H / 8;
+  const int v0 = (wave % SP) * (64 * NV) + lane;                        // this lane's first vector of a row
+  const float invH = 1.0f / (float)H;
+  V g[NV];
+  float col[NP][NV][8];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    g[i].load(gamma + (size_t)min(v0 + 64 * i, nvec - 1) * 8);
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) col[p][i][e] = 0.f;
+  }
+  struct Row { V d[NV], x[NV], res[NV]; float mu, rs; };
+  auto at = [&](int r, int i) { return (size_t)r * H + (size_t)min(v0 + 64 * i, nvec - 1) * 8; };   // (past the end: the last vector)
+  auto load_row = [&](Row& w, int r0) {
+    const int r = min(r0, rows - 1);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) w.x[i].load(x + at(r, i));
+    if (!FUSED || n == 1) {
+      const bf16* p = FUSED ? (const bf16*)ptrs.p[0] : dy;
+#pragma unroll
+      for (int i = 0; i < NV; ++i) w.d[i].load(p + at(r, i));
+    } else {                                           // fixed order k = 0..n-1, fp32, rounded once
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < n; ++k) {
+          V t;
+          t.load((const bf16*)ptrs.p[k] + at(r, i));
+#pragma unroll
+          for (int e = 0; e < 8; ++e) acc[e] += t.get(e);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w.d[i].set(e, acc[e]);
+      }
+    }
+    if (residual)
+#pragma unroll
+      for (int i = 0; i < NV; ++i) w.res[i].load(residual + at(r, i));
+    w.mu = mean[r];
+    w.rs = rstd[r];
+  };
+  auto work = [&](const Row& c, int r, int par) {
+    const float rs = c.rs, nmr = -c.mu * rs;             // xhat = x rstd - mean rstd
+    const bool mine = r < rows;                          // (wave-uniform; a row past the end takes part in the barrier only)
+    float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      if (!mine || v0 + 64 * i >= nvec) continue;
+      if (FUSED && dy_out) c.d[i].store(dy_out + at(r, i));
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float dv = c.d[i].get(e), xh = fmaf(c.x[i].get(e), rs, nmr), gg = dv * g[i].get(e);
+        s1 += gg;
+        s2 = fmaf(gg, xh, s2);
+        col[0][i][e] = fmaf(dv, xh, col[0][i][e]);
+        col[1][i][e] += dv;
+      }
+    }
+    s1 = wave_sum(s1);
+    s2 = wave_sum(s2);
+    if constexpr (SP > 1) {
+      if (lane == 0) { red[par][wave][0] = s1; red[par][wave][1] = s2; }
+      __syncthreads();
+      const int w0 = wave - wave % SP;
+      s1 = red[par][w0][0] + red[par][w0 + 1][0];
+      s2 = red[par][w0][1] + red[par][w0 + 1][1];
+    }
+    s1 *= invH;
+    s2 *= invH;
+    const float rs1 = rs * s1, rs2 = rs * s2;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      if (!mine || v0 + 64 * i >= nvec) continue;
+      V o;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float xh = fmaf(c.x[i].get(e), rs, nmr), gg = c.d[i].get(e) * g[i].get(e);
+        float v = fmaf(-xh, rs2, fmaf(gg, rs, -rs1));
+        if (residual) v += c.res[i].get(e);
+        o.set(e, v);
+        if (SUM && !DZ) col[NP - 1][i][e] += o.get(e);       // the stored (rounded) value, as a separate column sum would read it
+      }
+      o.store(dx + at(r, i));
+      if (DZ) {
+        float z[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) z[e] = o.get(e);
+        if (drop.enabled) drop_apply<8>(drop, at(r, i), z);
+        V oz;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          oz.set(e, z[e]);
+          if (SUM) col[NP - 1][i][e] += oz.get(e);
+        }
+        oz.store(dz_out + at(r, i));
+      }
+    }
+  };
+  static_assert(SP == 1 || SP == 2, "waves per row");
+  const int stride = gridDim.x * RPB;
+  if constexpr (SP == 1) {
+    for (int r = blockIdx.x * RPB + wave; r < rows; r += stride) {
+      Row c;
+      load_row(c, r);
+      work(c, r, 0);
+    }
+  } else {
+    Row cur, nxt;                                        // (copied, as above)
+    load_row(nxt, blockIdx.x * RPB + wave / SP);
+    int par = 0;
+    for (int base = blockIdx.x * RPB; base < rows; base += stride, par ^= 1) {
+      cur = nxt;
+      if (base + stride < rows) load_row(nxt, base + stride + wave / SP);
+      work(cur, base + wave / SP, par);
+    }
+  }
+  // column partials: every quantity in turn, added in the order of the waves
+  float* out = ws + (size_t)blockIdx.x * NP * H;
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    if (p) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      float* to = lds_rows + (size_t)(wave / SP) * (512 * NV * SP) + (v0 + 64 * i) * 8;
+#pragma unroll
+      for (int e = 0; e < 8; e += 4)
+        *reinterpret_cast<float4*>(to + e) = make_float4(col[p][i][e], col[p][i][e + 1], col[p][i][e + 2], col[p][i][e + 3]);
+    }
+    __syncthreads();
+    for (int c = threadIdx.x * 4; c < H; c += 64 * kLnRowWaves * 4) {
+      float4 t = *reinterpret_cast<const float4*>(lds_rows + c);
+#pragma unroll
+      for (int w = 1; w < RPB; ++w) {
+        const float4 v = *reinterpret_cast<const float4*>(lds_rows + (size_t)w * (512 * NV * SP) + c);
+        t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w;
+      }
+      *reinterpret_cast<float4*>(out + (size_t)p * H + c) = t;
+    }
+  }
+}
+
 // out[c] = sum_k ws[k][c] over nchunk row-chunks (the columns are up to three output vectors of `seg` entries): 16 float4 column groups x 16 chunk-slices per block; every slice
 // sums its chunks in order and the 16 slices are added in a fixed order (deterministic).
 template <typename T>
@@ -530,6 +689,16 @@ int ln_bwd_blocks(int dtype, int T, int H) {
   return (nbatch + per - 1) / per;
 }
 
+// Waves per row of ln_bwd_rows_kernel (bf16), 0: ln_bwd_kernel.  With three column partials / with dropout's second output, finishing
+// sums included, the other form / this one: 8192 x 3072 50.3 / 45.9, 59.8 / 55.4 us; 4096 x 2560 27.0 / 25.5, 34.1 / 31.5; 8192 x 1536
+// 32.1 / 26.9, 40.4 / 33.5; 3000 x 1536 21.0 / 17.3, 25.7 / 20.8; 16384 x 512 30.7 / 20.3, 39.9 / 25.0; 1024 x 1920 13.9 / 12.6, 15.4 / 14.9;
+// 2048 x 768 13.9 / 11.0.  A workgroup takes eight rows at a time: few rows leave units idle (333 x 1536 9.1 / 9.7, 10.3 / 11.1).  One
+// wave per row up to three vectors a lane, two beyond: 8192 x 1536 26.9 / 28.2, x 1920 32.7 / 31.5, 6000 x 2048 with dropout 39.8 / 33.1.
+static int ln_bwd_row_waves(int rows, int H) {
+  if (H > 3072 || rows < 3 * gemm_cu_count()) return 0;
+  return H <= 1536 ? 1 : 2;
+}
+
 template <typename T>
 static hipError_t ln_bwd_dispatch(int rows, int H, const void* dy, const void* x, const void* gamma,
                                   const float* mean, const float* rstd, const void* residual, void* dx,
@@ -541,12 +710,50 @@ static hipError_t ln_bwd_dispatch(int rows, int H, const void* dy, const void* x
   if (nwaves < 1 || nwaves > (narrow ? 12 : 8)) return hipErrorInvalidValue;
   const size_t room = ws_bytes / ((size_t)3 * H * sizeof(float));
   if (room < (size_t)ln_bwd_min_blocks(rows)) return hipErrorInvalidValue;
-  const int nblk = (int)std::min((size_t)ln_bwd_blocks(sizeof(T) == 2 ? MLM_BF16 : MLM_F32, rows, H), room);
+  int nblk = (int)std::min((size_t)ln_bwd_blocks(sizeof(T) == 2 ? MLM_BF16 : MLM_F32, rows, H), room);
   PartialPtrs none;
   for (int k = 0; k < kMaxPartials; ++k) none.p[k] = nullptr;
   const int np = (pp && dx_colsum) ? 3 : 2;
   float* deferred = deferred_reserve((size_t)nblk * np * H);
   if (deferred) ws = deferred;
+  auto finish = [&]() -> hipError_t {
+    const ColReduce fin = {ws, dgamma, dbeta, dx_colsum, nblk, np * H, H, sizeof(T) == 2 ? MLM_BF16 : MLM_F32};
+    if (!deferred) return launch_reduce_cols(fin, st);
+    deferred_record(fin);
+    return hipSuccess;
+  };
+  if constexpr (kNarrow) {
+    if (const int sp = ln_bwd_row_waves(rows, H)) {
+      nblk = std::min(nblk, std::min(gemm_cu_count(), (rows * sp + kLnRowWaves - 1) / kLnRowWaves));
+      auto go = [&](auto nv_c, auto sp_c) -> hipError_t {
+        constexpr int NV = decltype(nv_c)::value, SP = decltype(sp_c)::value;
+        auto run = [&](auto f, auto s, auto z) -> hipError_t {
+          constexpr size_t kLds = (size_t)kLnRowWaves * 512 * NV * 4;
+          auto kern = ln_bwd_rows_kernel<NV, SP, decltype(f)::value, decltype(s)::value, decltype(z)::value>;
+          static LdsAttrOnce attr;
+          if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
+          hipLaunchKernelGGL(kern, dim3(nblk), dim3(64 * kLnRowWaves), kLds, st, rows, H, (const bf16*)dy, (const bf16*)x,
+                             (const bf16*)gamma, mean, rstd, (const bf16*)residual, (bf16*)dx, ws, pp ? *pp : none, n, (bf16*)dy_out,
+                             drop, (bf16*)dz_out);
+          return hipGetLastError();
+        };
+        const std::true_type yes{};
+        const std::false_type no{};
+        if (pp && dx_colsum && dz_out) return run(yes, yes, yes);
+        if (pp && dz_out) return run(yes, no, yes);
+        if (pp && dx_colsum) return run(yes, yes, no);
+        if (pp) return run(yes, no, no);
+        return run(no, no, no);
+      };
+      const std::integral_constant<int, 1> one{};
+      const std::integral_constant<int, 2> two{};
+      const std::integral_constant<int, 3> three{};
+      const int nv = (H / 8 + 64 * sp - 1) / (64 * sp);
+      hipError_t e = sp == 2 ? (nv == 2 ? go(two, two) : go(three, two)) : nv == 1 ? go(one, one) : nv == 2 ? go(two, one) : go(three, one);
+      if (e != hipSuccess) return e;
+      return finish();
+    }
+  }
   dim3 grid(nblk), block(nwaves * 64);
 #define MLM_LN_BWD_VB(VBYTES, F, S, Z)                                                                      \
   hipLaunchKernelGGL((ln_bwd_kernel<T, VBYTES, F, S, Z>), grid, block, 0, st, rows, H, (const T*)dy,        \
@@ -566,14 +773,8 @@ static hipError_t ln_bwd_dispatch(int rows, int H, const void* dy, const void* x
   else MLM_LN_BWD_GO(false, false, false);
 #undef MLM_LN_BWD_GO
 #undef MLM_LN_BWD_VB
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const ColReduce fin = {ws, dgamma, dbeta, dx_colsum, nblk, np * H, H, sizeof(T) == 2 ? MLM_BF16 : MLM_F32};
-  if (deferred) {
-    deferred_record(fin);
-    return hipSuccess;
-  }
-  return launch_reduce_cols(fin, st);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  return finish();
 }
 
 hipError_t launch_layernorm_bwd(int dtype, int T, int H, const void* dy, const void* x, const void* gamma,
