@@ -125,10 +125,10 @@ __device__ __forceinline__ float gelu_fwd(float x, bool tanh_form) {
 }
 __device__ __forceinline__ float gelu_bwd(float x, bool tanh_form) {
   if (tanh_form) {
-    // d/dx [x s(2u)] = s + x s (1 - s) 2 u',  u' = sqrt(2/pi)(1 + 3 * 0.044715 x^2)
+    // d/dx [x s(2u)] = s + x (s - s^2) 2 u',  u' = sqrt(2/pi)(1 + 3 * 0.044715 x^2): ten vector operations beside the two of the sigmoid
     const float sg = gelu_sigmoid2u(x);
-    const float du2 = 2.0f * 0.7978845608028654f * fmaf(0.134145f, x * x, 1.0f);
-    return sg + x * sg * (1.0f - sg) * du2;
+    const float d0 = 2.0f * 0.7978845608028654f, d1 = d0 * 0.134145f;
+    return fmaf(x * fmaf(-sg, sg, sg), fmaf(d1, x * x, d0), sg);
   }
   return 0.5f * (1.0f + erff(x * 0.7071067811865476f)) + x * __expf(-0.5f * x * x) * 0.3989422804014327f;
 }

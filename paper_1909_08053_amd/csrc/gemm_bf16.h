@@ -127,9 +127,29 @@ __device__ __forceinline__ void acc_fill_strip(T* strip, const floatx4 (&acc)[NB
     }
 }
 
+// The saved pre-activations that a lane meets at read-back (EPI_DGELU), all requested at once.  Requested strip by strip, behind the
+// strip's writes, every strip waited for memory: the pre-activations were written a forward pass ago.
+template <int BM, int BN, int WAVES_M, int WAVES_N>
+struct EpilogueAux {
+  typedef GemmTile<BM, BN, WAVES_M, WAVES_N> Tcfg;
+  static constexpr int NH = (Tcfg::TN + 1) / 2;
+  bf16x8 v[Tcfg::TM * NH][4];
+  __device__ __forceinline__ void request(const GemmArgs& a, int m0, int n0) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int m = m0 + (wave / WAVES_N) * Tcfg::WM + (lane >> 3), n = n0 + (wave % WAVES_N) * Tcfg::WN + (lane & 7) * 8;
+#pragma unroll
+    for (int s = 0; s < Tcfg::TM * NH; ++s)
+#pragma unroll
+      for (int it = 0; it < 4; ++it) {
+        const int gm = min(m + s / NH * 32 + it * 8, a.M - 1), gn = min(n + s % NH * 64, a.N - 8);
+        v[s][it] = *reinterpret_cast<const bf16x8*>((const bf16*)a.aux + (size_t)gm * a.ldaux + gn);
+      }
+  }
+};
+
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, bool GELU_TANH, typename Acc>
-__device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs& a, Acc& acc,
-                                                   unsigned char* lds_raw, int m0, int n0, int tile_n) {
+__device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs& a, Acc& acc, unsigned char* lds_raw, int m0, int n0, int tile_n,
+                                                   const EpilogueAux<BM, BN, WAVES_M, WAVES_N>* aux) {
   typedef GemmTile<BM, BN, WAVES_M, WAVES_N> Tcfg;
   constexpr int NT = Tcfg::NT, TM = Tcfg::TM, TN = Tcfg::TN, WM = Tcfg::WM, WN = Tcfg::WN;
   bf16* lds = reinterpret_cast<bf16*>(lds_raw);
@@ -257,7 +277,7 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs& a, Acc& acc,
           }
           if (ok) *reinterpret_cast<bf16x8*>((bf16*)a.aux + (size_t)gm * a.ldaux + gn) = pre;
         } else if (EPI == EPI_DGELU) {
-          const bf16x8 g8 = *reinterpret_cast<const bf16x8*>((const bf16*)a.aux + (size_t)gmc * a.ldaux + gnc);
+          const bf16x8 g8 = aux->v[ps][it];
 #pragma unroll
           for (int e = 0; e < 8; ++e) o[e] = (bf16)(v[e] * gelu_bwd((float)g8[e], GELU_TANH));
         } else if (EPI == EPI_DLOGITS) {
@@ -281,14 +301,14 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs& a, Acc& acc,
 
 // acc: floatx4 [BN / WAVES_N / 16][BM / WAVES_M / 16]
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, typename Acc>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, Acc& acc,
-                                              unsigned char* lds_raw, int m0, int n0, int tile_n) {
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, Acc& acc, unsigned char* lds_raw, int m0, int n0, int tile_n,
+                                              const EpilogueAux<BM, BN, WAVES_M, WAVES_N>* aux) {
   if (EPI == EPI_BIAS_GELU || EPI == EPI_DGELU) {
     // the GeLU form is a launch-wide constant: branch once, not per element
-    if (a.gelu_tanh) gemm_epilogue_impl<BM, BN, WAVES_M, WAVES_N, EPI, true>(a, acc, lds_raw, m0, n0, tile_n);
-    else gemm_epilogue_impl<BM, BN, WAVES_M, WAVES_N, EPI, false>(a, acc, lds_raw, m0, n0, tile_n);
+    if (a.gelu_tanh) gemm_epilogue_impl<BM, BN, WAVES_M, WAVES_N, EPI, true>(a, acc, lds_raw, m0, n0, tile_n, aux);
+    else gemm_epilogue_impl<BM, BN, WAVES_M, WAVES_N, EPI, false>(a, acc, lds_raw, m0, n0, tile_n, aux);
   } else {
-    gemm_epilogue_impl<BM, BN, WAVES_M, WAVES_N, EPI, true>(a, acc, lds_raw, m0, n0, tile_n);
+    gemm_epilogue_impl<BM, BN, WAVES_M, WAVES_N, EPI, true>(a, acc, lds_raw, m0, n0, tile_n, aux);
   }
 }
 

@@ -567,6 +567,8 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
     slice(c0_t{}, kt);
     slice(c1_t{}, kt + 1);
   }
+  EpilogueAux<BM, BN, WAVES_M, WAVES_N> aux;
+  if (EPI == EPI_DGELU && whole) aux.request(a, m0, n0);
   // copies of the (clamped) last slices are still in flight and target the ring the epilogue reuses
   wait_vmcnt<0>();
   __syncthreads();
@@ -584,7 +586,7 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
       }
     return;
   }
-  gemm_epilogue<BM, BN, WAVES_M, WAVES_N, EPI>(a, acc, lds_raw, m0, n0, tile_n);
+  gemm_epilogue<BM, BN, WAVES_M, WAVES_N, EPI>(a, acc, lds_raw, m0, n0, tile_n, &aux);
 }
 
 // (two workgroups of the small tile fit a compute unit)
