@@ -63,16 +63,24 @@ __device__ __forceinline__ uint32_t drop_keep4(const DropArgs& d, uint64_t blk) 
          (w.w[3] >= d.thr ? 8u : 0u);
 }
 
-// Inverted dropout of the N consecutive elements starting at element index e0 (a multiple of 4; N = 4 or 8).
+// Keep mask of the N consecutive elements starting at element index e0 (a multiple of 4; N = 4 or 8), bit i = element e0 + i.
+template <int N>
+__device__ __forceinline__ uint32_t drop_keep(const DropArgs& d, uint64_t e0) {
+  static_assert(N % 4 == 0, "whole blocks");
+  uint32_t k = 0;
+#pragma unroll
+  for (int b = 0; b < N / 4; ++b) k |= drop_keep4(d, (e0 >> 2) + b) << (4 * b);
+  return k;
+}
+template <int N>
+__device__ __forceinline__ void drop_select(const DropArgs& d, uint32_t keep, float (&v)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = ((keep >> i) & 1u) ? v[i] * d.scale : 0.f;
+}
+// Inverted dropout of these elements.
 template <int N>
 __device__ __forceinline__ void drop_apply(const DropArgs& d, uint64_t e0, float (&v)[N]) {
-  static_assert(N % 4 == 0, "whole blocks");
-#pragma unroll
-  for (int b = 0; b < N / 4; ++b) {
-    const uint32_t k = drop_keep4(d, (e0 >> 2) + b);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[4 * b + i] = ((k >> i) & 1u) ? v[4 * b + i] * d.scale : 0.f;
-  }
+  drop_select<N>(d, drop_keep<N>(d, e0), v);
 }
 
 }  // namespace mlm
