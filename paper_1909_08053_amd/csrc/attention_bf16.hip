@@ -172,7 +172,11 @@ __global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW
   // wave-uniform values must be known as such: the mask test below is a scalar branch
   const int grp = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);    // wave group: takes the tiles NG j + grp
   const int wave_u = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);   // wave inside its group (copies a quarter of a tile)
-  const int wave = wave_u % RW, kh = wave_u / RW;  // its 32 queries, and its 32 keys of a tile (KG = 2)
+  // Fold (attn_fwd_fold): the workgroup's rows are the x-th half block from the end and the x-th from the start, so that every workgroup
+  // has the same number of tiles to multiply; the waves that share a SIMD, one of each group, have late and early rows.
+  constexpr int CH = BQ / 2, RC = RW / 2;
+  const bool fold = NG == 2 && a.fold;
+  const int wave = (wave_u % RW) ^ (fold ? RC * grp : 0), kh = wave_u / RW;  // its 32 queries, and its 32 keys of a tile (KG = 2)
   const int nqb = (a.s + BQ - 1) / BQ;
   const AttnBlock blk = attn_block(nqb, a.hl, a.b);
   if (!blk.valid) return;
@@ -181,7 +185,11 @@ __global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW
   const int ld = 3 * a.hl * D;
   const bf16* base = (const bf16*)a.qkv + (size_t)bi * a.s * ld;
   const int klen = attn_key_len(a.key_len, bi, a.s);
-  const int q0 = qb * BQ, qw0 = q0 + wave * 32, qi = qw0 + l32;
+  const int late = (a.s + CH - 1) / CH - 1 - blk.xb;        // the half blocks are `late` and xb, of which there is one if they are the same
+  const bool twice = fold && wave < RC && late == blk.xb;
+  const int q_end = fold ? CH * (late + 1) : qb * BQ + BQ;
+  const int qw0 = fold ? CH * (wave < RC ? blk.xb : late) + 32 * (wave % RC) : qb * BQ + wave * 32;
+  const int qi = twice ? a.s : qw0 + l32;                   // (rows from s on are not stored)
 
   bf16x8 qf[D / 16];
   {
@@ -197,7 +205,7 @@ __global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW
   float m = -INFINITY, lsum = 0.f;
   const size_t prow = ((size_t)bi * a.hl + hd) * a.s + min(qi, a.s - 1);   // row of the [b, hl, s, s] probabilities
   int kv_end = klen;
-  if (a.causal) kv_end = min(kv_end, q0 + BQ);
+  if (a.causal) kv_end = min(kv_end, q_end);
   const int nt = (kv_end + ATILE - 1) / ATILE;
   const float sc = kLog2e / sqrtf((float)D);
   const bf16* Kb = base + (a.hl + hd) * D;
@@ -236,7 +244,7 @@ __global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW
     constexpr bool SPREAD = D <= 96;
     // else: no such tile / all padding / entirely above this wave's diagonal (wave-uniform); key kw0 of a live tile is
     // allowed for every query of the wave
-    const bool live = t < nt && kw0 < klen && !(a.causal && kw0 > qw0 + 31);
+    const bool live = t < nt && kw0 < klen && !(a.causal && kw0 > qw0 + 31) && !twice;
     if (!SPREAD || !live) {
       src.issue(Kb, ld, tc_next, a.s, dstK, wave_u);
       src.issue(Vb, ld, tc_next, a.s, dstV, wave_u);
@@ -895,8 +903,10 @@ static hipError_t launch_fwd_m(const AttnArgs& a, hipStream_t st) {
 }
 
 template <int D, bool DROP>
-static hipError_t launch_fwd_dd(const AttnArgs& a, hipStream_t st) {
-  const AttnMode m = attn_mode(a.s, a.hl * a.b, a.causal != 0, D);
+static hipError_t launch_fwd_dd(const AttnArgs& args, hipStream_t st) {
+  const AttnMode m = attn_mode(args.s, args.hl * args.b, args.causal != 0, D);
+  AttnArgs a = args;
+  a.fold = a.causal && attn_fwd_fold(m, a.s, a.hl * a.b);
   if constexpr (D <= 128)
     if (m == ATTN_PAIR) return launch_fwd_m<D, DROP, ATTN_PAIR>(a, st);
   return m == ATTN_SPLIT ? launch_fwd_m<D, DROP, ATTN_SPLIT>(a, st) : launch_fwd_m<D, DROP, ATTN_WIDE>(a, st);

@@ -30,6 +30,17 @@ inline AttnMode attn_mode(int s, int pairs, bool causal, int d) {
   return ATTN_WIDE;
 }
 
+// Forward under a causal mask, PAIR and SPLIT: half a block of rows from either end of the sequence per workgroup, which all have the same
+// work then, where every workgroup of the busiest XCD has a compute unit from the start and the longest one would be the launch's time
+// (us, blocks / folded; s x pairs).  d = 96: 1024 x 32 23.6 / 21.3, with dropout 38.4 / 31.8; 1000 x 16 17.6 / 16.6, 512 x 64 16.2 / 15.5; d = 64:
+// 1024 x 32 20.4 / 16.5; d = 128, dropout: 512 x 16 17.5 / 15.4.  Where workgroups queue, the short ones fill up behind the long ones by
+// themselves, and half of a folded one's waves wait: d = 96 4096 x 16 91 / 101, 2048 x 24 53 / 57, 8192 x 8 161 / 184, d = 64 3072 x 4 31 / 42.
+// Few tiles: d = 64 200 x 12 6.3 / 7.3, d = 96 320 x 6 11.4 / 12.0.  (Head size 192 has one group: its waves do not share a SIMD.)
+inline bool attn_fwd_fold(AttnMode m, int s, int pairs) {
+  const long rows = m == ATTN_SPLIT ? 64 : 128;
+  return m != ATTN_WIDE && s >= 512 && (pairs + 7) / 8 * ((s + rows - 1) / rows) <= gemm_cu_count() / 8;
+}
+
 // dK / dV in a launch of its own (attn_bwd_mode), no mask, d = 64 or 96: 64-key workgroups (else 128-key ones) while twice as many fit
 // the compute units overall and on the busiest XCD.  us, 128 / 64 keys: d = 96 1024 x 8 27 / 20, 64 1024 x 16 23 / 17; but 3072 x 4 74 / 91, 768 x
 // 20 24 / 33.  (Under a causal mask and for larger heads launches that small are joint.)
