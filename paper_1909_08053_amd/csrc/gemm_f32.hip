@@ -244,7 +244,12 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_kernel(Gem
 }
 
 // 32 x 32 tile, 8 waves: wave w sums the w-th eighth of k (in 8-deep chunks) and the eight partial tiles are added in LDS,
-// in wave order.
+// in wave order.  With K = 256 it is one trip to memory, the reduction and the launch: what is asked for and never used, each
+// operation ahead of the first request and each instruction to be fetched counts.  A step is requested only where there is one, and
+// a chunk's address is the lane's plus a wave-uniform offset: against steps requested ahead whether or not the range has them, at
+// addresses computed chunk by chunk, 96 tiles of K = 256 6.6 -> 4.8 us, 32 of K = 768 with both operands k-contiguous 8.6 -> 5.0, the
+// four weight gradients below 10.4 -> 7.2 (a step of 256 tokens 265 -> 228 us).  Four steps in flight instead of two (212
+// registers, twice the code) 237; from K = 1024 on it is the matrix operations, 3.7 us of one tile's on one compute unit.
 constexpr int kF32SplitWaves = 8;
 constexpr int kF32SplitStep = 4;        // chunks of 8 k per step: 32 k, a full 128-byte line of a k-contiguous row
 
@@ -265,31 +270,50 @@ __device__ __forceinline__ void f32_split_tile(const GemmArgs& a, int tile) {
 #pragma unroll
   for (int e = 0; e < 16; ++e) acc[e] = 0.f;
   float fa[2][ST][4], fb[2][ST][4];
-  auto load = [&](int buf, int c) {
+  auto steps = [&](auto load) {
+    auto multiply = [&](int buf, int n) {
 #pragma unroll
-    for (int q = 0; q < ST; ++q) {
-      const int k = 8 * min(c + q, nchunk - 1) + 4 * lh;         // past this wave's range: read, not multiplied
-      f32_frag_global<A_KC>(A, a.lda, rowA, k, a.K, fa[buf][q]);
-      f32_frag_global<B_KC>(B, a.ldb, rowB, k, a.K, fb[buf][q]);
-    }
-  };
-  auto multiply = [&](int buf, int c) {
+      for (int q = 0; q < ST; ++q)
+        if (q < n) {                                             // wave-uniform
 #pragma unroll
-    for (int q = 0; q < ST; ++q)
-      if (c + q < c1) {                                          // wave-uniform
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[buf][q][j], fb[buf][q][j], acc, 0, 0, 0);
-      }
-  };
-  if (c0 < c1) {
-    load(0, c0);
-    for (int c = c0; c < c1; c += 2 * ST) {
+          for (int j = 0; j < 4; ++j)
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[buf][q][j], fb[buf][q][j], acc, 0, 0, 0);
+        }
+    };
+    int c = c0;
+    load(0, c);
+    for (; c + 2 * ST < c1; c += 2 * ST) {
       load(1, c + ST);
-      multiply(0, c);
+      multiply(0, ST);
       load(0, c + 2 * ST);
-      multiply(1, c + ST);
+      multiply(1, ST);
     }
+    // (one or two steps are left, the first of them requested; a short k has no others, and nothing past it is requested)
+    const bool two = c + ST < c1;
+    if (two) load(1, c + ST);
+    multiply(0, c1 - c);
+    if (two) multiply(1, c1 - c - ST);
+  };
+  // (chunks past this wave's range: its last one again, not multiplied)
+  if (c0 < c1 && (A_KC || B_KC || 8 * c1 <= a.K)) {
+    const F32Lane<A_KC> la(A, a.lda, rowA, lh);
+    const F32Lane<B_KC> lb(B, a.ldb, rowB, lh);
+    steps([&](int buf, int c) {
+#pragma unroll
+      for (int q = 0; q < ST; ++q) {
+        la.load(min(c + q, c1 - 1), fa[buf][q]);
+        lb.load(min(c + q, c1 - 1), fb[buf][q]);
+      }
+    });
+  } else if (c0 < c1) {
+    steps([&](int buf, int c) {
+#pragma unroll
+      for (int q = 0; q < ST; ++q) {
+        const int k = 8 * min(c + q, c1 - 1) + 4 * lh;
+        f32_frag_global<A_KC>(A, a.lda, rowA, k, a.K, fa[buf][q]);
+        f32_frag_global<B_KC>(B, a.ldb, rowB, k, a.K, fb[buf][q]);
+      }
+    });
   }
 #pragma unroll
   for (int e = 0; e < 16; ++e) park[wave][e][lane] = acc[e];
@@ -315,7 +339,7 @@ __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_kernel(Gem
 }
 
 // The tiles of several weight gradients in one launch: such a GEMM takes 6 us whatever its size, and nothing waits for the
-// four of a layer shard one by one (four launches of 256 x {256, 512} x 256: 24 -> 11 us in one).
+// four of a layer shard one by one (four launches of 256 x {256, 512} x 256: 24 -> 11 us in one, 7.2 now).
 __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_group_kernel(F32Group g) {
   GemmArgs a;
   const int tile = f32_group_at(g, blockIdx.x, &a);
