@@ -8,7 +8,11 @@
 // tokens, four tiles long, still keeps all four waves busy.  Bound by the matrix cores' fp32 rate and, below a few tiles
 // per wave, by the chain of one tile.  Two sequences of 512 tokens, 16 heads of 64, causal: forward 26 us, dQ 36, dK/dV 47
 // (739 / 721 + 7 for delta / 1134 with one thread per row on the vector ALUs); two of 128 tokens, 2 heads: 8 / 11 / 14 us
-// (192 / 190 + 6 / 305).
+// (192 / 190 + 6 / 305).  A tile's values are requested in runs, the rows ahead of the scores and the columns ahead of the
+// exponentials, in the registers that the rows leave; the next tile's rows ahead of the forward's second product.  Before, with the
+// order left to the compiler -> now: 2048 tokens, 8 heads of 64: forward 83 -> 78, dQ 127 -> 115, dK/dV 140 -> 137; four sequences of
+// 256, 8 heads of 80, no mask, dropout: 28.8 -> 15.3, 24.1 -> 23.4, 33 -> 26.4; 512, 8 heads of 128: 32 -> 29.7, both backward 81 -> 74; two
+// of 128, 4 heads of 64: 9.0 -> 8.2, both 15.6 -> 14.6; two of 512, 8 heads of 96: 27.4 -> 25.0, dQ 35.9 -> 37.2 (the one loss).
 //
 // Scores are computed so that a lane's 16 accumulator values belong to ONE owned row, column l % 32 of the 32 x 32 tile,
 // and to the streamed rows 8 (e / 4) + 4 (l / 32) + e % 4: row statistics are per-lane scalars plus one cross-half
@@ -84,68 +88,76 @@ __device__ __forceinline__ void af_load_row(const float* __restrict__ row, int l
     f[4 * c] = v.x; f[4 * c + 1] = v.y; f[4 * c + 2] = v.z; f[4 * c + 3] = v.w;
   }
 }
-// acc[streamed row][owned row] = sum over the head dimension of streamed[row] . owned (registers)
+// The streamed tile's rows from r0 on in the two forms that the products take, each as one run of requests ahead of what multiplies it
+// (left to itself the compiler requests a value or two when the last ones have been used).  M: element (0, 0) of the matrix; rows
+// beyond nrows - 1 repeat the last one (their weights are zero); r0 is wave-uniform, and a lane adds 32 bits to a scalar address.
 template <int D>
-__device__ __forceinline__ floatx16 af_scores(const float* __restrict__ row, int lh, const float (&own)[D / 2]) {
+__device__ __forceinline__ void af_tile_rows(const float* __restrict__ M, int ld, int r0, int nrows, int l32, int lh, float (&f)[D / 2]) {
+  af_load_row<D>(M + (size_t)r0 * ld + (uint32_t)min(l32, nrows - 1 - r0) * (uint32_t)ld, lh, f);
+}
+template <int D>
+__device__ __forceinline__ void af_tile_columns(const float* __restrict__ M, int ld, int r0, int nrows, int l32, int lh,
+                                                float (&f)[16][AfShape<D>::DT]) {
+  const char* tile = reinterpret_cast<const char*>(M + (size_t)r0 * ld);
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const uint32_t r = 4u * (uint32_t)ld * (uint32_t)min(8 * (e >> 2) + 4 * lh + (e & 3), nrows - 1 - r0);
+#pragma unroll
+    for (int dt = 0; dt < AfShape<D>::DT; ++dt)          // (columns past the head's: its last one again, never stored)
+      f[e][dt] = *reinterpret_cast<const float*>(tile + (r + 4u * (uint32_t)min(dt * 32 + l32, D - 1)));
+  }
+}
+// acc[streamed row][owned row] = sum over the head dimension of streamed[row] . owned
+template <int D>
+__device__ __forceinline__ floatx16 af_scores(const float (&row)[D / 2], const float (&own)[D / 2]) {
   floatx16 acc;
 #pragma unroll
   for (int e = 0; e < 16; ++e) acc[e] = 0.f;
 #pragma unroll
-  for (int c = 0; c < D / 8; ++c) {
-    const float4 v = *reinterpret_cast<const float4*>(row + 8 * c + 4 * lh);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v.x, own[4 * c], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v.y, own[4 * c + 1], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v.z, own[4 * c + 2], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v.w, own[4 * c + 3], acc, 0, 0, 0);
-  }
+  for (int c = 0; c < D / 2; ++c) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(row[c], own[c], acc, 0, 0, 0);
   return acc;
 }
-// out[dt][head column][owned row] += sum over the tile's streamed rows of M[row][column] w[row][owned row]; M: element
-// (0, 0) of the matrix, rows beyond nrows - 1 repeat the last one (their weights are zero).
+// out[dt][head column][owned row] += sum over the tile's streamed rows of M[row][column] w[row][owned row]
 template <int D>
-__device__ __forceinline__ void af_accumulate(const float* __restrict__ M, int ld, int r0, int nrows, int lane,
-                                              const floatx16& w, floatx16 (&out)[AfShape<D>::DT]) {
-  const int l32 = lane & 31, lh = lane >> 5;
+__device__ __forceinline__ void af_accumulate(const float (&M)[16][AfShape<D>::DT], const floatx16& w, floatx16 (&out)[AfShape<D>::DT]) {
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int r = min(r0 + 8 * (e >> 2) + 4 * lh + (e & 3), nrows - 1);
-    const float* p = M + (size_t)r * ld + l32;
+  for (int e = 0; e < 16; ++e)
 #pragma unroll
-    for (int dt = 0; dt < AfShape<D>::DT; ++dt) {
-      const bool in = D % 32 == 0 || dt * 32 + l32 < D;
-      const float v = in ? p[dt * 32] : 0.f;
-      out[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, w[e], out[dt], 0, 0, 0);
-    }
-  }
+    for (int dt = 0; dt < AfShape<D>::DT; ++dt) out[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(M[e][dt], w[e], out[dt], 0, 0, 0);
 }
+// The waves' accumulators parked in LDS ([wave][value][lane]: conflict-free)
+template <int NV> __device__ __forceinline__ float* af_park(float* lds, int wave, int lane) { return lds + (size_t)wave * NV * 64 + lane; }
 // af_accumulate for a tile in which, if `edge`, some pairs are excluded (off(e): this lane's pair e is).  An excluded pair's weight is
-// zero, but zero times Inf or NaN is NaN and the matrix cores multiply every pair: a lane that is left with a sum that is not
-// finite adds the tile again pair by pair, the allowed ones only.  (Looking at the sums costs a layer of two
-// sequences of 512 tokens, 16 heads of 64, 5 us of 1324; looking at the rows beforehand, a trip to memory ahead of every such
-// tile, cost it 40.)
+// zero, but zero times Inf or NaN is NaN and the matrix cores multiply every pair: a tile that holds such a value is added pair by
+// pair, the allowed ones only.  (Looking at the values costs nothing new now that the tile is in registers; looking at the sums
+// behind the products, with a copy of what they were before, took 32 registers and as many moves at a head of 64.)
 template <int D, typename Off>
-__device__ __forceinline__ void af_accumulate_masked(const float* __restrict__ M, int ld, int r0, int nrows, int lane,
-                                                     const floatx16& w, bool edge, Off off, floatx16 (&out)[AfShape<D>::DT]) {
-  floatx16 before[AfShape<D>::DT];
+__device__ __forceinline__ void af_accumulate_masked(const float* __restrict__ M, int ld, int r0, int lane,
+                                                     const float (&columns)[16][AfShape<D>::DT], const floatx16& w, bool edge, Off off,
+                                                     float* park, floatx16 (&out)[AfShape<D>::DT]) {
+  bool finite = true;
+  if (edge) {
+    float x[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int dt = 0; dt < AfShape<D>::DT; ++dt) before[dt] = out[dt];
-  af_accumulate<D>(M, ld, r0, nrows, lane, w, out);
-  if (!edge) return;
-  float x[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int dt = 0; dt < AfShape<D>::DT; ++dt)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) x[e & 3] = fmaf(0.f, columns[e][dt], x[e & 3]);       // 0, or NaN
+    const float xs = (x[0] + x[1]) + (x[2] + x[3]);
+    finite = __builtin_amdgcn_ballot_w64(xs != xs) == 0;
+  }
+  if (__builtin_expect(finite, 1)) {
+    af_accumulate<D>(columns, w, out);
+    return;
+  }
+  // (the sums wait in this lane's own part of LDS, which nothing else uses before the end: in registers, this loop is what decides how
+  // many the kernel takes)
 #pragma unroll
   for (int dt = 0; dt < AfShape<D>::DT; ++dt)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) x[e & 3] = fmaf(0.f, out[dt][e], x[e & 3]);       // 0, or NaN
-  const float xs = (x[0] + x[1]) + (x[2] + x[3]);
-  const bool again = xs != xs;
-  if (__builtin_expect(__builtin_amdgcn_ballot_w64(again) == 0, 1)) return;
+    for (int e = 0; e < 16; ++e) park[(dt * 16 + e) * 64] = out[dt][e];
   uint32_t allow = 0;
 #pragma unroll
   for (int e = 0; e < 16; ++e) allow |= off(e) ? 0u : 1u << e;
-#pragma unroll
-  for (int dt = 0; dt < AfShape<D>::DT; ++dt)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) out[dt][e] = again ? before[dt][e] : out[dt][e];
   const int l32 = lane & 31, lh = lane >> 5;
 #pragma unroll 1
   for (int r = 0; r < AF_ROWS; ++r) {
@@ -155,26 +167,21 @@ __device__ __forceinline__ void af_accumulate_masked(const float* __restrict__ M
     for (int q = 1; q < 16; ++q) we = q == e ? w[q] : we;
     we = __shfl(we, src, 64);
     const bool on = (__shfl(allow, src, 64) >> e) & 1u;
-    if (!on || !again) continue;                       // (an allowed row lies inside the sequence)
+    if (!on) continue;                                 // (an allowed row lies inside the sequence)
     const float* p = M + (size_t)(r0 + r) * ld + 4 * lh;
+#pragma unroll 1
+    for (int g = 0; g < D / 8; ++g)
 #pragma unroll
-    for (int dt = 0; dt < AfShape<D>::DT; ++dt)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        if (dt * 32 + 8 * g >= D) continue;
-        const float4 v = *reinterpret_cast<const float4*>(p + dt * 32 + 8 * g);
-        out[dt][4 * g] = fmaf(v.x, we, out[dt][4 * g]);
-        out[dt][4 * g + 1] = fmaf(v.y, we, out[dt][4 * g + 1]);
-        out[dt][4 * g + 2] = fmaf(v.z, we, out[dt][4 * g + 2]);
-        out[dt][4 * g + 3] = fmaf(v.w, we, out[dt][4 * g + 3]);
-      }
+      for (int i = 0; i < 4; ++i) park[(4 * g + i) * 64] = fmaf(p[8 * g + i], we, park[(4 * g + i) * 64]);
   }
+#pragma unroll
+  for (int dt = 0; dt < AfShape<D>::DT; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) out[dt][e] = park[(dt * 16 + e) * 64];
 }
-// The waves' accumulators parked in LDS ([wave][value][lane]: conflict-free)
-template <int NV> __device__ __forceinline__ float* af_park(float* lds, int wave, int lane) { return lds + (size_t)wave * NV * 64 + lane; }
 
 template <int D>
-__global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_fwd_f32_kernel(AttnArgs a, int pg) {
+__global__ __launch_bounds__(64 * AF_WAVES, D <= 64 ? 2 : 1) void attn_fwd_f32_kernel(AttnArgs a, int pg) {
   constexpr int DT = AfShape<D>::DT, NV = DT * 16 + 2;
   extern __shared__ __attribute__((aligned(16))) float lds_af[];
   const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
@@ -202,8 +209,13 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_fwd_f32_kernel(AttnArgs
   const size_t prow = ((size_t)bi * a.hl + hd) * a.s + min(qi, a.s - 1);   // row of the [b, hl, s, s] probability tensor
   const float* K = base + (a.hl + hd) * D;
   const float* V = base + (2 * a.hl + hd) * D;
+  float* park = af_park<NV>(lds_af, wave, lane);
+  float kr[D / 2], vc[16][DT];
+  if (wave * AF_ROWS < kv_end) af_tile_rows<D>(K, ld, wave * AF_ROWS, a.s, l32, lh, kr);
   for (int k0 = wave * AF_ROWS; k0 < kv_end; k0 += AF_WAVES * AF_ROWS) {
-    floatx16 s = af_scores<D>(K + (size_t)min(k0 + l32, a.s - 1) * ld, lh, q);
+    floatx16 s = af_scores<D>(kr, q);
+    af_tile_columns<D>(V, ld, k0, a.s, l32, lh, vc);      // (in the registers of K's rows)
+    __builtin_amdgcn_sched_barrier(0);
     float mt = -INFINITY;
     auto off = [&](int e) {
       const int key = k0 + 8 * (e >> 2) + 4 * lh + (e & 3);
@@ -243,9 +255,10 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_fwd_f32_kernel(AttnArgs
       if (lh == 0 && qi < a.s) a.keep_bits[prow * a.keep_pitch + (k0 >> 5)] = word;
     }
     const bool edge = k0 + AF_ROWS > klen || (a.causal && k0 + AF_ROWS - 1 > q0);      // wave-uniform
-    af_accumulate_masked<D>(V, ld, k0, a.s, lane, s, edge, off, o);
+    if (k0 + AF_WAVES * AF_ROWS < kv_end) af_tile_rows<D>(K, ld, k0 + AF_WAVES * AF_ROWS, a.s, l32, lh, kr);
+    __builtin_amdgcn_sched_barrier(0);
+    af_accumulate_masked<D>(V, ld, k0, lane, vc, s, edge, off, park, o);
   }
-  float* park = af_park<NV>(lds_af, wave, lane);
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -319,11 +332,20 @@ __device__ __forceinline__ void attn_bwd_dq_f32_block(const AttnArgs a, const Af
   if (a.causal) kv_end = min(kv_end, min(a.s, q0 + AF_ROWS));
   const float* K = base + (a.hl + hd) * D;
   const float* V = base + (2 * a.hl + hd) * D;
+  float* park = af_park<NV>(lds_af, wave, lane);
   for (int k0 = wave * AF_ROWS; k0 < kv_end; k0 += AF_WAVES * AF_ROWS) {
-    const int kr = min(k0 + l32, a.s - 1);
-    floatx16 s = af_scores<D>(K + (size_t)kr * ld, lh, q);
-    const floatx16 dp = af_scores<D>(V + (size_t)kr * ld, lh, dov);
+    float kr[D / 2], vr[D / 2], kc[16][DT];
+    af_tile_rows<D>(K, ld, k0, a.s, l32, lh, kr);
+    af_tile_rows<D>(V, ld, k0, a.s, l32, lh, vr);
     const uint32_t bits = a.drop.enabled ? a.keep_bits[row * a.keep_pitch + (k0 >> 5)] >> (4 * lh) : 0xFFFFFFFFu;
+    constexpr bool STAGED = D <= 80;
+    if (STAGED) __builtin_amdgcn_sched_barrier(0);
+    floatx16 s = af_scores<D>(kr, q);
+    if (STAGED) {
+      af_tile_columns<D>(K, ld, k0, a.s, l32, lh, kc);    // (in the registers of the rows)
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const floatx16 dp = af_scores<D>(vr, dov);
     auto off = [&](int e) {
       const int key = k0 + 8 * (e >> 2) + 4 * lh + (e & 3);
       return key >= klen || (a.causal && key > qi);
@@ -337,9 +359,9 @@ __device__ __forceinline__ void attn_bwd_dq_f32_block(const AttnArgs a, const Af
       s[e] = off(e) ? 0.f : ds;
     }
     const bool edge = k0 + AF_ROWS > klen || (a.causal && k0 + AF_ROWS - 1 > q0);      // wave-uniform
-    af_accumulate_masked<D>(K, ld, k0, a.s, lane, s, edge, off, dq);
+    if (!STAGED) af_tile_columns<D>(K, ld, k0, a.s, l32, lh, kc);
+    af_accumulate_masked<D>(K, ld, k0, lane, kc, s, edge, off, park, dq);
   }
-  float* park = af_park<NV>(lds_af, wave, lane);
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -404,6 +426,7 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dkv_f32_kernel(Attn
   const size_t row0 = ((size_t)bi * a.hl + hd) * a.s;
   // key blocks of padding only get zeros; a causal block starts at its own first query
   const int q_begin = kb0 >= klen ? a.s : (a.causal ? kb0 : 0);
+  float* park = af_park<NV>(lds_af, wave, lane);
   for (int q0 = q_begin + wave * AF_ROWS; q0 < a.s; q0 += AF_WAVES * AF_ROWS) {
     const int qr = min(q0 + l32, a.s - 1);
     // the tile's per-query values are requested ahead of the scores, and the mask selects the finished probability: with
@@ -429,20 +452,31 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dkv_f32_kernel(Attn
       for (int e = 0; e < 16; ++e)
         bits[e] = a.keep_bits[(row0 + min(q0 + 8 * (e >> 2) + 4 * lh + (e & 3), a.s - 1)) * a.keep_pitch + (kb0 >> 5)];
     }
-    floatx16 s = af_scores<D>(Q + (size_t)qr * ld, lh, kf);          // [query][key]
-    floatx16 dp = af_scores<D>(dO + (size_t)qr * ldo, lh, vf);
+    constexpr bool STAGED = D <= 96;                      // above, the rows do not fit beside four accumulators: taken as they are needed
+    auto requested = [] {
+      if (STAGED) __builtin_amdgcn_sched_barrier(0);
+    };
+    float qf[D / 2], gf[D / 2], qc[16][DT], gc[16][DT];
+    af_tile_rows<D>(Q, ld, q0, a.s, l32, lh, qf);
+    af_tile_rows<D>(dO, ldo, q0, a.s, l32, lh, gf);
+    requested();
+    floatx16 s = af_scores<D>(qf, kf);                    // [query][key]
+    if (STAGED) af_tile_columns<D>(dO, ldo, q0, a.s, l32, lh, gc);       // (in the registers of Q's rows)
+    requested();
+    floatx16 dp = af_scores<D>(gf, vf);
     if (JOINT) {
       float dl = 0.f;                                     // of query q0 + l32, in the order of the dQ kernel
 #pragma unroll
       for (int c = 0; c < D / 8; ++c) {
-        const float4 g = *reinterpret_cast<const float4*>(dO + (size_t)qr * ldo + 8 * c + 4 * lh);
         const float4 o = EARLY ? ov[EARLY ? c : 0] : *reinterpret_cast<const float4*>(orow + 8 * c);
-        dl = fmaf(o.x, g.x, dl); dl = fmaf(o.y, g.y, dl); dl = fmaf(o.z, g.z, dl); dl = fmaf(o.w, g.w, dl);
+        dl = fmaf(o.x, gf[4 * c], dl); dl = fmaf(o.y, gf[4 * c + 1], dl); dl = fmaf(o.z, gf[4 * c + 2], dl); dl = fmaf(o.w, gf[4 * c + 3], dl);
       }
       dl += __shfl_xor(dl, 32, 64);
 #pragma unroll
       for (int e = 0; e < 16; ++e) del[e] = __shfl(dl, 8 * (e >> 2) + 4 * lh + (e & 3), 64);
     }
+    if (STAGED) af_tile_columns<D>(Q, ld, q0, a.s, l32, lh, qc);
+    requested();
     auto off = [&](int e) {
       const int i = q0 + 8 * (e >> 2) + 4 * lh + (e & 3);
       return kj >= klen || i >= a.s || (a.causal && kj > i);
@@ -457,10 +491,11 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dkv_f32_kernel(Attn
       dp[e] = off(e) ? 0.f : ds;
     }
     const bool edge = kb0 + AF_ROWS > klen || q0 + AF_ROWS > a.s || (a.causal && kb0 + AF_ROWS - 1 > q0);   // wave-uniform
-    af_accumulate_masked<D>(dO, ldo, q0, a.s, lane, s, edge, off, dv);
-    af_accumulate_masked<D>(Q, ld, q0, a.s, lane, dp, edge, off, dk);
+    if (!STAGED) af_tile_columns<D>(dO, ldo, q0, a.s, l32, lh, gc);
+    af_accumulate_masked<D>(dO, ldo, q0, lane, gc, s, edge, off, park, dv);
+    if (!STAGED) af_tile_columns<D>(Q, ld, q0, a.s, l32, lh, qc);
+    af_accumulate_masked<D>(Q, ld, q0, lane, qc, dp, edge, off, park, dk);
   }
-  float* park = af_park<NV>(lds_af, wave, lane);
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -486,7 +521,7 @@ __global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dkv_f32_kernel(Attn
 }
 
 template <int D>
-__global__ __launch_bounds__(64 * AF_WAVES, 1) void attn_bwd_dq_f32_kernel(AttnArgs a, int pg) {
+__global__ __launch_bounds__(64 * AF_WAVES, D <= 64 ? 2 : 1) void attn_bwd_dq_f32_kernel(AttnArgs a, int pg) {
   const AfBlock blk = af_block((a.s + AF_ROWS - 1) / AF_ROWS, a.hl, a.b, pg);
   if (blk.valid) attn_bwd_dq_f32_block<D, false>(a, blk);
 }
