@@ -243,32 +243,35 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_kernel(Gem
   f32_tile<A_KC, B_KC, EPI, BM, BN, WM, WN, KS, KT>(a, blockIdx.x);
 }
 
-// 32 x 32 tile, 8 waves: wave w sums the w-th eighth of k (in 8-deep chunks) and the eight partial tiles are added in LDS,
+// 32 x 32 or 16 x 16 tile, 8 waves: wave w sums the w-th eighth of k (in chunks of 8 or 16) and the eight partial tiles are added in LDS,
 // in wave order.  With K = 256 it is one trip to memory, the reduction and the launch: what is asked for and never used, each
 // operation ahead of the first request and each instruction to be fetched counts.  A step is requested only where there is one, and
 // a chunk's address is the lane's plus a wave-uniform offset: against steps requested ahead whether or not the range has them, at
 // addresses computed chunk by chunk, 96 tiles of K = 256 6.6 -> 4.8 us, 32 of K = 768 with both operands k-contiguous 8.6 -> 5.0, the
 // four weight gradients below 10.4 -> 7.2 (a step of 256 tokens 265 -> 228 us).  Four steps in flight instead of two (212
-// registers, twice the code) 237; from K = 1024 on it is the matrix operations, 3.7 us of one tile's on one compute unit.
+// registers, twice the code) 237.  From K = 512 on it is the matrix operations, 3.7 us per 1024 k of a tile on its compute unit: tiles of 16 x 16
+// where there are units for them (f32_split_tile_of; 64 tiles of K = 1024 6.7 -> 4.1 us, beside column sums 7.4 -> 4.9; 228 -> 209).
 constexpr int kF32SplitWaves = 8;
-constexpr int kF32SplitStep = 4;        // chunks of 8 k per step: 32 k, a full 128-byte line of a k-contiguous row
+constexpr int kF32SplitStep = 4;        // chunks of 8 (16) k per step: 32 (64) k, whole 128-byte lines of a k-contiguous row
 
-template <bool A_KC, bool B_KC, int EPI>
+template <bool A_KC, bool B_KC, int EPI, int TS = 32>
 __device__ __forceinline__ void f32_split_tile(const GemmArgs& a, int tile) {
-  constexpr int NWV = kF32SplitWaves, ST = kF32SplitStep;
-  __shared__ float park[NWV][16][64];
-  const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
+  // TS = 16: 16 x 16 tile, chunks of 16 k of which K is a multiple (f32_split_tile_of)
+  constexpr int NWV = kF32SplitWaves, CK = 256 / TS, ST = kF32SplitStep, NE = TS * TS / 64;
+  using acc_t = std::conditional_t<TS == 32, floatx16, floatx4>;
+  __shared__ float park[NWV][NE][64];
+  const int lane = threadIdx.x & 63, l32 = lane % TS, lh = lane / TS;      // (a lane's row; its four k of a chunk)
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int tiles_m = (a.M + 31) / 32;
-  const int m0 = (tile % tiles_m) * 32, n0 = (tile / tiles_m) * 32;
+  const int tiles_m = (a.M + TS - 1) / TS;
+  const int m0 = (tile % tiles_m) * TS, n0 = (tile / tiles_m) * TS;
   const float* A = (const float*)a.A;
   const float* B = (const float*)a.B;
   const int rowA = min(m0 + l32, a.M - 1), rowB = min(n0 + l32, a.N - 1);
-  const int nchunk = (a.K + 7) / 8;
+  const int nchunk = (a.K + CK - 1) / CK;
   const int c0 = (int)((long)nchunk * wave / NWV), c1 = (int)((long)nchunk * (wave + 1) / NWV);
-  floatx16 acc;
+  acc_t acc;
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  for (int e = 0; e < NE; ++e) acc[e] = 0.f;
   float fa[2][ST][4], fb[2][ST][4];
   auto steps = [&](auto load) {
     auto multiply = [&](int buf, int n) {
@@ -277,7 +280,8 @@ __device__ __forceinline__ void f32_split_tile(const GemmArgs& a, int tile) {
         if (q < n) {                                             // wave-uniform
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[buf][q][j], fb[buf][q][j], acc, 0, 0, 0);
+            if constexpr (TS == 32) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[buf][q][j], fb[buf][q][j], acc, 0, 0, 0);
+            else acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[buf][q][j], fb[buf][q][j], acc, 0, 0, 0);
         }
     };
     int c = c0;
@@ -295,14 +299,14 @@ __device__ __forceinline__ void f32_split_tile(const GemmArgs& a, int tile) {
     if (two) multiply(1, c1 - c - ST);
   };
   // (chunks past this wave's range: its last one again, not multiplied)
-  if (c0 < c1 && (A_KC || B_KC || 8 * c1 <= a.K)) {
+  if (c0 < c1 && (A_KC || B_KC || TS == 16 || 8 * c1 <= a.K)) {
     const F32Lane<A_KC> la(A, a.lda, rowA, lh);
     const F32Lane<B_KC> lb(B, a.ldb, rowB, lh);
     steps([&](int buf, int c) {
 #pragma unroll
       for (int q = 0; q < ST; ++q) {
-        la.load(min(c + q, c1 - 1), fa[buf][q]);
-        lb.load(min(c + q, c1 - 1), fb[buf][q]);
+        la.load(CK * min(c + q, c1 - 1), fa[buf][q]);
+        lb.load(CK * min(c + q, c1 - 1), fb[buf][q]);
       }
     });
   } else if (c0 < c1) {
@@ -316,15 +320,16 @@ __device__ __forceinline__ void f32_split_tile(const GemmArgs& a, int tile) {
     });
   }
 #pragma unroll
-  for (int e = 0; e < 16; ++e) park[wave][e][lane] = acc[e];
+  for (int e = 0; e < NE; ++e) park[wave][e][lane] = acc[e];
   __syncthreads();
-  // wave w finishes the tile's values e = 2 w, 2 w + 1
+  // wave w finishes the tile's values e = 2 w, 2 w + 1 (e = w of the four of a 16 x 16 tile)
+  constexpr int PER = NE >= NWV ? NE / NWV : 1;
   const int n = n0 + l32;
-  if (n >= a.N) return;
+  if (n >= a.N || wave * PER >= NE) return;
   const float bias = ((EPI == EPI_STORE || EPI == EPI_BIAS_GELU) && a.bias) ? ((const float*)a.bias)[n] : 0.f;
 #pragma unroll
-  for (int q = 0; q < 16 / NWV; ++q) {
-    const int e = wave * (16 / NWV) + q;
+  for (int q = 0; q < PER; ++q) {
+    const int e = wave * PER + q;
     float v = 0.f;
 #pragma unroll
     for (int p = 0; p < NWV; ++p) v += park[p][e][lane];
@@ -333,9 +338,9 @@ __device__ __forceinline__ void f32_split_tile(const GemmArgs& a, int tile) {
   }
 }
 
-template <bool A_KC, bool B_KC, int EPI>
+template <bool A_KC, bool B_KC, int EPI, int TS>
 __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_kernel(GemmArgs a) {
-  f32_split_tile<A_KC, B_KC, EPI>(a, blockIdx.x);
+  f32_split_tile<A_KC, B_KC, EPI, TS>(a, blockIdx.x);
 }
 
 // The tiles of several weight gradients in one launch: such a GEMM takes 6 us whatever its size, and nothing waits for the
@@ -354,10 +359,11 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_group_kern
 
 // A weight gradient (its tiles first) and an input gradient that do not depend on each other: 256 x 512 x 256 and 256 x 256 x 512
 // take 8.2 us together, 14 in two launches.
+template <int TS>
 __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_dual_kernel(GemmArgs w, GemmArgs x) {
   const int tiles_w = ((w.M + 31) / 32) * ((w.N + 31) / 32), id = blockIdx.x;
   if (id < tiles_w) f32_split_tile<false, false, EPI_STORE>(w, id);
-  else f32_split_tile<true, true, EPI_STORE>(x, id - tiles_w);
+  else f32_split_tile<true, true, EPI_STORE, TS>(x, id - tiles_w);
 }
 
 // The same in 64 x 64 tiles; the longer ones lead.
@@ -372,10 +378,11 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_tile_dual_kernel(GemmArgs w, 
 
 // An input gradient and column sums beside it (the workgroups behind the tiles): a launch of 5 us saved, 1024 tokens x 1024 1270 ->
 // 1264 us a step.
+template <int TS>
 __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_colsum_kernel(GemmArgs a, ColsumJob job) {
   __shared__ float red[colsum_lds_floats<float, 64 * kF32SplitWaves>()];
-  const int tiles = ((a.M + 31) / 32) * ((a.N + 31) / 32), id = blockIdx.x;
-  if (id < tiles) f32_split_tile<true, true, EPI_STORE>(a, id);
+  const int tiles = ((a.M + TS - 1) / TS) * ((a.N + TS - 1) / TS), id = blockIdx.x;
+  if (id < tiles) f32_split_tile<true, true, EPI_STORE, TS>(a, id);
   else colsum_block<float, 64 * kF32SplitWaves>(job, id - tiles, red);
 }
 template <int BM, int BN, int WM, int WN, int KS, int KT>
@@ -434,8 +441,10 @@ static hipError_t launch_f32_layout(const GemmArgs& a, hipStream_t st) {
   if (const int bt = f32_pieces_pick(a.M, a.N, a.K)) return launch_f32_pieces(a, bt, st);
   switch (f32_pick(a.M, a.N, a.K)) {
     case 32: {
-      const int tiles = ((a.M + 31) / 32) * ((a.N + 31) / 32);
-      hipLaunchKernelGGL((gemm_f32_split_kernel<A_KC, B_KC, EPI>), dim3(tiles), dim3(64 * kF32SplitWaves), 0, st, a);
+      const int ts = f32_split_tile_of(a.M, a.N, a.K);
+      const dim3 tiles(((a.M + ts - 1) / ts) * ((a.N + ts - 1) / ts)), block(64 * kF32SplitWaves);
+      if (ts == 16) hipLaunchKernelGGL((gemm_f32_split_kernel<A_KC, B_KC, EPI, 16>), tiles, block, 0, st, a);
+      else hipLaunchKernelGGL((gemm_f32_split_kernel<A_KC, B_KC, EPI, 32>), tiles, block, 0, st, a);
       return hipGetLastError();
     }
     case 64: return launch_f32_tile<A_KC, B_KC, EPI, 64, 64, 2, 2, 2, 64>(a, st);
@@ -506,8 +515,10 @@ hipError_t launch_gemm_f32_dgrad_colsum(const GemmArgs& a, const ColsumJob& j, h
   if (const int bt = f32_pieces_pick(a.M, a.N, a.K)) return launch_f32_pieces_colsum(a, j, bt, st);
   switch (f32_pick(a.M, a.N, a.K)) {
     case 32: {
-      const int tiles = ((a.M + 31) / 32) * ((a.N + 31) / 32);
-      hipLaunchKernelGGL(gemm_f32_split_colsum_kernel, dim3(tiles + j.blocks), dim3(64 * kF32SplitWaves), 0, st, a, j);
+      const int ts = f32_split_tile_of(a.M, a.N, a.K);
+      const dim3 grid(((a.M + ts - 1) / ts) * ((a.N + ts - 1) / ts) + j.blocks), block(64 * kF32SplitWaves);
+      if (ts == 16) hipLaunchKernelGGL(gemm_f32_split_colsum_kernel<16>, grid, block, 0, st, a, j);
+      else hipLaunchKernelGGL(gemm_f32_split_colsum_kernel<32>, grid, block, 0, st, a, j);
       return hipGetLastError();
     }
     case 64: return launch_f32_tile_colsum<64, 64, 2, 2, 2, 64>(a, j, st);
@@ -536,7 +547,10 @@ hipError_t launch_gemm_f32_dual(const GemmArgs& w, const GemmArgs& x, hipStream_
   auto tiles = [b](const GemmArgs& a) { return ((a.M + b - 1) / b) * ((a.N + b - 1) / b); };
   const dim3 grid(tiles(w) + tiles(x));
   if (b == 32) {
-    hipLaunchKernelGGL(gemm_f32_split_dual_kernel, grid, dim3(64 * kF32SplitWaves), 0, st, w, x);
+    const int ts = f32_split_tile_of(x.M, x.N, x.K);
+    const dim3 both(tiles(w) + ((x.M + ts - 1) / ts) * ((x.N + ts - 1) / ts));
+    if (ts == 16) hipLaunchKernelGGL(gemm_f32_split_dual_kernel<16>, both, dim3(64 * kF32SplitWaves), 0, st, w, x);
+    else hipLaunchKernelGGL(gemm_f32_split_dual_kernel<32>, both, dim3(64 * kF32SplitWaves), 0, st, w, x);
     return hipGetLastError();
   }
   return p.chains == 8 ? launch_f32_tile_dual<4>(w, x, grid, st) : launch_f32_tile_dual<1>(w, x, grid, st);

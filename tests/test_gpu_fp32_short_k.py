@@ -3,6 +3,8 @@ import pytest
 import torch
 
 from paper_1909_08053_amd import binding as B
+from paper_1909_08053_amd import synth
+from test_gpu_parity import run_layer_parity
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -10,6 +12,10 @@ DEV = "cuda:0"
 # (M, N, K).  Eight waves share a tile's chunks of 8 k, four chunks a step: waves with none, with one chunk, with a whole step, with
 # one and with two steps, of which the last is not whole, with an odd and an even number of whole ones, with more than two
 SPLIT = [(40, 72, K) for K in (8, 56, 72, 256, 296, 512, 520, 768, 1024, 1096, 1544)]
+# (where 16 x 16 tiles find a compute unit each and K is a multiple of 128, or two a unit and K is one of 16 from 512 on, those: the
+# same, with chunks of 16 k, and either side of the rule)
+SPLIT += [(M, N, K) for M, N in ((16, 8), (24, 264)) for K in (112, 128, 256, 512, 528, 640, 1040, 1552, 2064)]
+SPLIT += [(256, 256, 128), (264, 256, 256), (256, 512, 496), (256, 512, 512), (264, 512, 512)]
 # the 64- and 128-tile kernels below the shortest k that is multiplied in pieces
 TILES = [(1000, 1016, 56), (1032, 2048, 48), (4096, 4088, 56), (4088, 4096, 8)]
 
@@ -60,3 +66,13 @@ def test_weight_gradients_over_any_number_of_tokens(T):
     for got, ref, bound, n in ((dE, hf.double().t() @ dL, hf.double().abs().t() @ err, T), (dhf, dL @ E.double().t(), err @ E.double().abs().t(), V)):
         mag = hf.double().abs().t() @ dL.abs() if got is dE else dL.abs() @ E.double().abs().t()
         assert bool(((got.double() - ref).abs() <= bound + (n + 4) * u * mag + 1e-12).all())
+
+
+# narrow layers over many tokens: the fused epilogues of the 64- and 128-tile kernels at such k
+LAYERS = {64: dict(b=1, s=1000, H=48, h=3, F=1024, V=1024), 128: dict(b=3, s=667, H=32, h=2, F=4096, V=4096)}
+
+
+@pytest.mark.parametrize("tile", sorted(LAYERS))
+@pytest.mark.parametrize("store_logits", [True, False])
+def test_layer_on_the_tile_kernels(tile, store_logits):
+    run_layer_parity(synth.small_config(name=f"narrow{tile}", dtype="fp32", p=1, **LAYERS[tile]), store_logits=store_logits, scale_w=2.0)
