@@ -11,7 +11,8 @@
 // Bound by the chip's power: at 4096^3 the clock falls to 1.65 GHz, where the matrix pipe is busy 70 % of the cycles, 207 TFLOP/s = 1.24
 // PFLOP/s of bf16 products, what the bf16 kernels reach (fp32 matrix cores: 139).  A value is split once per workgroup, on its way from
 // registers to LDS (22 vector operations per four values, spread between the MFMAs).  Two waves per SIMD: one alone issues these
-// operations at half rate and took 217 TFLOP/s to 1.15 times as long at one workgroup per compute unit.  v_mfma_f32_32x32x16 rather
+// operations at half rate (four waves of 64 x 64 over 32 k a step, one workgroup per compute unit: no faster at 4096^3, and 130 us
+// instead of 92 at 1024 x 8192 x 1024).  v_mfma_f32_32x32x16 rather
 // than 16x16x32: half as many MFMAs to issue, and half of the operand registers, without which two waves do not fit beside 128 sums.
 //   * 128 x 128 tile, 4 waves of 64 x 64, 16 k a step, two workgroups per compute unit.
 //   * 64 x 64 tile for outputs of few tiles: 8 waves, 64 k a step, of which a group of two waves takes 16.  Twice the splitting per flop.
