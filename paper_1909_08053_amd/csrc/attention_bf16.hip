@@ -160,7 +160,7 @@ template <int D> constexpr bool dkv_own_lds() { return D <= 96; }    // d = 128:
 
 // (two waves per SIMD requested: with at most 256 registers per lane the MFMA accumulators live in ordinary VGPRs, so
 // the softmax arithmetic needs no accumulator-register moves)
-template <int D, bool DROP, int MODE>
+template <int D, bool DROP, int MODE, bool FOLD>
 __global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW)) void attn_fwd_bf16_kernel(AttnArgs a) {
   typedef ATile<D> TL;
   typedef AttnSplit<D, MODE> SP;
@@ -172,11 +172,11 @@ __global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW
   // wave-uniform values must be known as such: the mask test below is a scalar branch
   const int grp = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);    // wave group: takes the tiles NG j + grp
   const int wave_u = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);   // wave inside its group (copies a quarter of a tile)
-  // Fold (attn_fwd_fold): the workgroup's rows are the x-th half block from the end and the x-th from the start, so that every workgroup
+  // FOLD (attn_fwd_fold): the workgroup's rows are the x-th half block from the end and the x-th from the start, so that every workgroup
   // has the same number of tiles to multiply; the waves that share a SIMD, one of each group, have late and early rows.
   constexpr int CH = BQ / 2, RC = RW / 2;
-  const bool fold = NG == 2 && a.fold;
-  const int wave = (wave_u % RW) ^ (fold ? RC * grp : 0), kh = wave_u / RW;  // its 32 queries, and its 32 keys of a tile (KG = 2)
+  static_assert(!FOLD || NG == 2, "both groups of waves");
+  const int wave = (wave_u % RW) ^ (FOLD ? RC * grp : 0), kh = wave_u / RW;  // its 32 queries, and its 32 keys of a tile (KG = 2)
   const int nqb = (a.s + BQ - 1) / BQ;
   const AttnBlock blk = attn_block(nqb, a.hl, a.b);
   if (!blk.valid) return;
@@ -186,9 +186,9 @@ __global__ __launch_bounds__((AttnSplit<D, MODE>::NT), (AttnSplit<D, MODE>::MINW
   const bf16* base = (const bf16*)a.qkv + (size_t)bi * a.s * ld;
   const int klen = attn_key_len(a.key_len, bi, a.s);
   const int late = (a.s + CH - 1) / CH - 1 - blk.xb;        // the half blocks are `late` and xb, of which there is one if they are the same
-  const bool twice = fold && wave < RC && late == blk.xb;
-  const int q_end = fold ? CH * (late + 1) : qb * BQ + BQ;
-  const int qw0 = fold ? CH * (wave < RC ? blk.xb : late) + 32 * (wave % RC) : qb * BQ + wave * 32;
+  const bool twice = FOLD && wave < RC && late == blk.xb;
+  const int q_end = FOLD ? CH * (late + 1) : qb * BQ + BQ;
+  const int qw0 = FOLD ? CH * (wave < RC ? blk.xb : late) + 32 * (wave % RC) : qb * BQ + wave * 32;
   const int qi = twice ? a.s : qw0 + l32;                   // (rows from s on are not stored)
 
   bf16x8 qf[D / 16];
@@ -891,25 +891,28 @@ __global__ __launch_bounds__(256) void attn_delta_bf16_kernel(AttnArgs a) {
 // ------------------------------------------------------------------------------------------ launchers
 bool attn_bf16_supported(int d) { return d == 64 || d == 96 || d == 128 || d == 192; }
 
-template <int D, bool DROP, int MODE>
+template <int D, bool DROP, int MODE, bool FOLD>
 static hipError_t launch_fwd_m(const AttnArgs& a, hipStream_t st) {
   typedef AttnSplit<D, MODE> SP;
+  auto kern = attn_fwd_bf16_kernel<D, DROP, MODE, FOLD>;
   static LdsAttrOnce attr;
   if (SP::LDS > 64 * 1024)
-    if (hipError_t e = attr.ensure((const void*)attn_fwd_bf16_kernel<D, DROP, MODE>, (int)SP::LDS); e != hipSuccess) return e;
+    if (hipError_t e = attr.ensure((const void*)kern, (int)SP::LDS); e != hipSuccess) return e;
   const dim3 grid = attn_grid((a.s + 32 * SP::RW - 1) / (32 * SP::RW), a.hl, a.b);
-  hipLaunchKernelGGL((attn_fwd_bf16_kernel<D, DROP, MODE>), grid, dim3(SP::NT), SP::LDS, st, a);
+  hipLaunchKernelGGL(kern, grid, dim3(SP::NT), SP::LDS, st, a);
   return hipGetLastError();
 }
 
+// (kernels of their own: with the fold a run-time switch, blocks took 8.2 us for 7.5 at 4 heads of 96, 200 tokens)
 template <int D, bool DROP>
-static hipError_t launch_fwd_dd(const AttnArgs& args, hipStream_t st) {
-  const AttnMode m = attn_mode(args.s, args.hl * args.b, args.causal != 0, D);
-  AttnArgs a = args;
-  a.fold = a.causal && attn_fwd_fold(m, a.s, a.hl * a.b);
-  if constexpr (D <= 128)
-    if (m == ATTN_PAIR) return launch_fwd_m<D, DROP, ATTN_PAIR>(a, st);
-  return m == ATTN_SPLIT ? launch_fwd_m<D, DROP, ATTN_SPLIT>(a, st) : launch_fwd_m<D, DROP, ATTN_WIDE>(a, st);
+static hipError_t launch_fwd_dd(const AttnArgs& a, hipStream_t st) {
+  const AttnMode m = attn_mode(a.s, a.hl * a.b, a.causal != 0, D);
+  const bool fold = a.causal && attn_fwd_fold(m, a.s, a.hl * a.b);
+  if constexpr (D <= 128) {
+    if (m == ATTN_PAIR) return fold ? launch_fwd_m<D, DROP, ATTN_PAIR, true>(a, st) : launch_fwd_m<D, DROP, ATTN_PAIR, false>(a, st);
+    if (m == ATTN_SPLIT && fold) return launch_fwd_m<D, DROP, ATTN_SPLIT, true>(a, st);
+  }
+  return m == ATTN_SPLIT ? launch_fwd_m<D, DROP, ATTN_SPLIT, false>(a, st) : launch_fwd_m<D, DROP, ATTN_WIDE, false>(a, st);
 }
 
 template <int D>

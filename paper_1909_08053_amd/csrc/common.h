@@ -253,7 +253,6 @@ struct AttnArgs {
   DropArgs drop;            // enabled = 0: no dropout
   uint32_t* keep_bits;      // [b, hl, s, keep_pitch] words; bit (j % 32) of word j / 32 of row (b, head, i): key j kept
   int keep_pitch;           // words per query row: 4 ceil(s / 128)
-  int fold;                 // bf16 forward, causal: a workgroup takes half a block from either end (set by its launcher)
 };
 // Number of visible keys of batch row bi: key_len lives in device memory and cannot be validated by the host, so every
 // kernel clamps it to [1, s] (0 or a negative length would index tiles before the buffer, a length above s keys that do
