@@ -651,17 +651,19 @@ MLM_API int mlm_vocab_ce_shard_fwd(const mlm_dims* dims, const void* hf, const v
   const int v0 = dims->r * L.Vl;
   if (dims->dtype == MLM_BF16) {
     const size_t T = (size_t)L.T;
-    const size_t ntile_max = ((size_t)L.Vl + 127) / 128;
+    // column tiles of 128 and more leave the whole k-split scratch behind the partials; twice as many (at most 4096 tiles of 32 or 64
+    // rows and 64 columns) take a part of it, which nothing else uses then
+    const int ntiles = gemm_bf16_ce_col_tiles(L.T, L.Vl, dims->H);
+    const size_t ntile_128 = ((size_t)L.Vl + 127) / 128, part = align256((ntiles > (int)ntile_128 ? ntiles : ntile_128) * T * 4);
     char* w = (char*)ws;
-    float* part_m = (float*)w;    w += align256(ntile_max * T * 4);
-    float* part_s = (float*)w;    w += align256(ntile_max * T * 4);
+    float* part_m = (float*)w;    w += part;
+    float* part_s = (float*)w;    w += part;
     float* t_ws = (float*)w;      w += align256(T * 4);
     GemmArgs g = gemm_fwd(L.T, L.Vl, dims->H, hf, E_r, logits_r);
     g.splitk_ws = (float*)w;
     g.epi = EPI_CE;
     g.targets = targets; g.v0 = v0;
     g.part_m = part_m; g.part_s = part_s; g.t_out = t_ws;
-    const int ntiles = gemm_bf16_ce_col_tiles(g.M, g.N, g.K);
     MLM_TRY_HIP(launch_gemm_bf16(g, st));
     MLM_TRY_HIP(launch_ce_tile_merge(L.T, ntiles, part_m, part_s, t_ws, targets, v0, v0 + L.Vl, m_r, s_r, t_r, st));
   } else {

@@ -1,6 +1,6 @@
 // Dispatcher of the bf16 MFMA GEMM: operand layout -> translation unit.
 #include <stdlib.h>
-#include "gemm_bf16_v2.h"
+#include "gemm_bf16_split.h"
 
 namespace mlm {
 
@@ -36,6 +36,7 @@ int gemm_cu_count() {
 
 // (the cross-entropy GEMM always gets split-k scratch)
 int gemm_bf16_ce_col_tiles(int M, int N, int K) {
+  if (split_pick_alone<true, false, EPI_CE>(M, N, K, true).form) return (N + 63) / 64;      // (its forms are 64 columns wide)
   const int bn = v2_pick_bn<true, false, EPI_CE>(M, N, K, true);
   return (N + bn - 1) / bn;
 }

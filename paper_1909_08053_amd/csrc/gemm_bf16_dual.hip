@@ -1,7 +1,7 @@
 // The two gradients of the vocabulary-parallel logits in one launch: dE = hf^T dL (weight-gradient layout) and dhf = dL E^T
 // (input-gradient layout).  Neither reads the other's result, and each alone leaves a partly filled last round of tiles that its
 // launch pays for by idle compute units or by fp32 partial tiles and a fix-up pass.
-#include "gemm_bf16_v2.h"
+#include "gemm_bf16_split.h"
 
 namespace mlm {
 
@@ -35,8 +35,21 @@ static hipError_t launch_dual(const GemmArgs& a0, const GemmArgs& a1, bool first
   return hipGetLastError();
 }
 
+template <int TM, int TN>
+static hipError_t launch_split_dual(const GemmArgs& a0, const GemmArgs& a1, int form, hipStream_t st) {
+  static LdsAttrOnce attr;
+  const int n0 = split_tiles(form, a0.M, a0.N), n1 = split_tiles(form, a1.M, a1.N);
+  return launch_split(&attr, gemm_bf16_split_dual_kernel<TM, TN>, split_lds_bytes<TM, TN>(), n0 + n1, st, a0, a1, a1.K > a0.K ? n1 : n0);
+}
+
 hipError_t launch_gemm_bf16_dual(const GemmArgs& a0, const GemmArgs& a1, float* splitk_ws, hipStream_t st) {
   const V2Dual d = v2_dual(a0, a1);
+  switch (split_dual_pick(a0, a1, d)) {
+    case SPLIT_64: return launch_split_dual<64, 64>(a0, a1, SPLIT_64, st);
+    case SPLIT_32X64: return launch_split_dual<32, 64>(a0, a1, SPLIT_32X64, st);
+    case SPLIT_32: return launch_split_dual<32, 32>(a0, a1, SPLIT_32, st);
+    default: break;
+  }
   if (d.bn == V2_SMALL) return launch_dual<V2_SMALL, KE_ANY, KE_ANY, true>(a0, a1, d.first_is_1, st);
   if (d.bn == V2_B)
     return v2_k_end<V2_B>(a1.K) == KE_PAIR ? launch_dual<V2_B, KE_PAIR, KE_PAIR, false>(a0, a1, d.first_is_1, st)
