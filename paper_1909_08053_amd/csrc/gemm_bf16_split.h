@@ -393,8 +393,8 @@ inline double split_us(int kind, int form, int tiles, int nk, double work) {
   return q[0] + q[1] * serial + (q[2] * serial + q[3]) * more + q[4] * work / cus;
 }
 // Slices as dear as these many where every row of a k-contiguous operand (there are kc) starts at the same place of a 128-byte line: the
-// sixteen rows of a request then meet in one bank of the vector cache (3000 x 384 x 1536 in 64 x 64 26 us, 3000 x 384 x 1528 19; neither
-// another deal of the slices nor requests of whole lines changes that).
+// sixteen rows of a request then seem to meet in one bank of the vector cache (1068 x 848 x 832 in 64 x 64 9.2 us, x 848 7.8; neither
+// another deal of the slices, other first slices for every tile nor requests of whole lines changed that).
 inline double split_slow(int kc, int K) { return K % 64 ? 1.0 : kc == 2 ? 1.4 : kc == 1 ? 1.1 : 1.0; }
 inline double split_us(int form, int M, int N, int K, int kc) {
   const int t = split_tiles(form, M, N), nk = (K + 31) / 32;
@@ -414,8 +414,8 @@ inline double v2_few_us(const V2Plan& p, int K) {
 // The form that is fastest by these prices, and its price (form SPLIT_NONE, price `than`: none beats that by an eighth).  wide: only forms of
 // 64 columns (the cross-entropy partials' column tiles).  Large tiles / these, us: fwd 400 x 288 x 192 4.5 / 2.7, 123 x 1888 x 1888 15.9 / 7.2, 1024 x
 // 1920 x 960 stays (10.3 / 16.3), dgrad 400 x 192 x 512 6.0 / 3.9, 915 x 928 x 464 8.3 / 6.1, 1068 x 848 x 848 12.1 / 7.8, wgrad 192 x 512 x 400 6.2 /
-// 3.1, 688 x 168 x 2166 15.6 / 8.6.  Of 900 drawn products 630 take one of these and the mean time falls to 0.67; seven are more than 3 %
-// slower, up to 1.5 x at 282 tiles of 48 slices that a compute unit more or less decides.
+// 3.1, 688 x 168 x 2166 15.6 / 8.6.  Of 1000 drawn products 716 take one of these and the mean time falls to 0.665 (0.656 with the best choice
+// every time); four are more than 3 % slower, 976 x 1304 x 86 most, 4.3 / 5.5.
 constexpr double kSplitMargin = 0.88;
 constexpr int kSplitMaxTiles = 4096;
 struct SplitPick { int form; double us; };

@@ -395,57 +395,70 @@ __global__ __launch_bounds__(VB == 8 ? 768 : 512) void ln_bwd_kernel(int rows, i
   }
 }
 
-// The same with SP = 1 or 2 waves per ROW, for bf16 rows of up to 512 NV SP columns (a lane: NV vectors of eight).  A wave of its own
-// reduces a row's statistics by itself, without exchange or barrier; two exchange two sums, one barrier per row, and have the next row
-// in flight.  The column partials of the rows that a wave meets stay in its registers (8 NV of each quantity); the workgroup's eight
-// waves add theirs through LDS at the end.
-constexpr int kLnRowWaves = 8;
-template <int NV, int SP, bool FUSED, bool SUM, bool DZ>
-__global__ __launch_bounds__(64 * kLnRowWaves, 2) void ln_bwd_rows_kernel(int rows, int H, const bf16* __restrict__ dy,
-                                                                          const bf16* __restrict__ x, const bf16* __restrict__ gamma,
-                                                                          const float* __restrict__ mean, const float* __restrict__ rstd,
-                                                                          const bf16* residual, bf16* dx, float* __restrict__ ws,
-                                                                          PartialPtrs ptrs, int n, bf16* dy_out, DropArgs drop, bf16* dz_out) {
-  typedef Vec16<bf16> V;
-  constexpr int NP = SUM ? 3 : 2, RPB = kLnRowWaves / SP;               // rows of a workgroup at a time
-  extern __shared__ __attribute__((aligned(16))) float lds_rows[];      // [wave][512 NV]
-  __shared__ float red[2][kLnRowWaves][2];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nvec = H / 8;
+// The same with SP = 1 or 2 waves per ROW, for rows of up to 64 NV SP vectors (a lane: NV vectors of eight bf16 or four fp32 values).  A
+// wave of its own reduces a row's statistics by itself, without exchange or barrier; two exchange two sums, one barrier per row, and have
+// the next row in flight.  The column partials of the rows that a wave meets stay in its registers; the workgroup's W waves add theirs
+// through LDS at the end.
+template <typename T, int NV, int SP, int W, bool FUSED, bool SUM, bool DZ>
+__global__ __launch_bounds__(64 * W, 2) void ln_bwd_rows_kernel(int rows, int H, const T* __restrict__ dy, const T* __restrict__ x,
+                                                                const T* __restrict__ gamma, const float* __restrict__ mean,
+                                                                const float* __restrict__ rstd, const T* residual, T* dx,
+                                                                float* __restrict__ ws, PartialPtrs ptrs, int n, T* dy_out,
+                                                                DropArgs drop, T* dz_out) {
+  typedef Vec16<T> V;
+  constexpr int VN = V::N, NP = SUM ? 3 : 2, RPB = W / SP;              // rows of a workgroup at a time
+  extern __shared__ __attribute__((aligned(16))) float lds_rows[];      // [wave][64 NV vectors]
+  __shared__ float red[2][W][2];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nvec = H / VN;
   const int v0 = (wave % SP) * (64 * NV) + lane;                        // this lane's first vector of a row
   const float invH = 1.0f / (float)H;
   V g[NV];
-  float col[NP][NV][8];
+  float col[NP][NV][VN];
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
-    g[i].load(gamma + (size_t)min(v0 + 64 * i, nvec - 1) * 8);
+    g[i].load(gamma + (size_t)min(v0 + 64 * i, nvec - 1) * VN);
 #pragma unroll
     for (int p = 0; p < NP; ++p)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) col[p][i][e] = 0.f;
+      for (int e = 0; e < VN; ++e) col[p][i][e] = 0.f;
   }
   struct Row { V d[NV], x[NV], res[NV]; float mu, rs; };
-  auto at = [&](int r, int i) { return (size_t)r * H + (size_t)min(v0 + 64 * i, nvec - 1) * 8; };   // (past the end: the last vector)
+  auto at = [&](int r, int i) { return (size_t)r * H + (size_t)min(v0 + 64 * i, nvec - 1) * VN; };   // (past the end: the last vector)
   auto load_row = [&](Row& w, int r0) {
     const int r = min(r0, rows - 1);
 #pragma unroll
     for (int i = 0; i < NV; ++i) w.x[i].load(x + at(r, i));
     if (!FUSED || n == 1) {
-      const bf16* p = FUSED ? (const bf16*)ptrs.p[0] : dy;
+      const T* p = FUSED ? (const T*)ptrs.p[0] : dy;
 #pragma unroll
       for (int i = 0; i < NV; ++i) w.d[i].load(p + at(r, i));
-    } else {                                           // fixed order k = 0..n-1, fp32, rounded once
+    } else {                                           // fixed order k = 0..n-1, fp32, rounded once; two under way at a time
+      float acc[NV][VN];
 #pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        for (int k = 0; k < n; ++k) {
-          V t;
-          t.load((const bf16*)ptrs.p[k] + at(r, i));
+      for (int i = 0; i < NV; ++i)
 #pragma unroll
-          for (int e = 0; e < 8; ++e) acc[e] += t.get(e);
-        }
+        for (int e = 0; e < VN; ++e) acc[i][e] = 0.f;
+      for (int k = 0; k < n; k += 2) {
+        V t[2][NV];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) w.d[i].set(e, acc[e]);
+        for (int i = 0; i < NV; ++i) t[0][i].load((const T*)ptrs.p[k] + at(r, i));
+        if (k + 1 < n)
+#pragma unroll
+          for (int i = 0; i < NV; ++i) t[1][i].load((const T*)ptrs.p[k + 1] + at(r, i));
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+          for (int e = 0; e < VN; ++e) acc[i][e] += t[0][i].get(e);
+        if (k + 1 < n)
+#pragma unroll
+          for (int i = 0; i < NV; ++i)
+#pragma unroll
+            for (int e = 0; e < VN; ++e) acc[i][e] += t[1][i].get(e);
       }
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+#pragma unroll
+        for (int e = 0; e < VN; ++e) w.d[i].set(e, acc[i][e]);
     }
     if (residual)
 #pragma unroll
@@ -462,7 +475,7 @@ __global__ __launch_bounds__(64 * kLnRowWaves, 2) void ln_bwd_rows_kernel(int ro
       if (!mine || v0 + 64 * i >= nvec) continue;
       if (FUSED && dy_out) c.d[i].store(dy_out + at(r, i));
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
+      for (int e = 0; e < VN; ++e) {
         const float dv = c.d[i].get(e), xh = fmaf(c.x[i].get(e), rs, nmr), gg = dv * g[i].get(e);
         s1 += gg;
         s2 = fmaf(gg, xh, s2);
@@ -487,7 +500,7 @@ __global__ __launch_bounds__(64 * kLnRowWaves, 2) void ln_bwd_rows_kernel(int ro
       if (!mine || v0 + 64 * i >= nvec) continue;
       V o;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
+      for (int e = 0; e < VN; ++e) {
         const float xh = fmaf(c.x[i].get(e), rs, nmr), gg = c.d[i].get(e) * g[i].get(e);
         float v = fmaf(-xh, rs2, fmaf(gg, rs, -rs1));
         if (residual) v += c.res[i].get(e);
@@ -496,13 +509,13 @@ __global__ __launch_bounds__(64 * kLnRowWaves, 2) void ln_bwd_rows_kernel(int ro
       }
       o.store(dx + at(r, i));
       if (DZ) {
-        float z[8];
+        float z[VN];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) z[e] = o.get(e);
-        if (drop.enabled) drop_apply<8>(drop, at(r, i), z);
+        for (int e = 0; e < VN; ++e) z[e] = o.get(e);
+        if (drop.enabled) drop_apply<VN>(drop, at(r, i), z);
         V oz;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
+        for (int e = 0; e < VN; ++e) {
           oz.set(e, z[e]);
           if (SUM) col[NP - 1][i][e] += oz.get(e);
         }
@@ -535,17 +548,17 @@ __global__ __launch_bounds__(64 * kLnRowWaves, 2) void ln_bwd_rows_kernel(int ro
     if (p) __syncthreads();
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-      float* to = lds_rows + (size_t)(wave / SP) * (512 * NV * SP) + (v0 + 64 * i) * 8;
+      float* to = lds_rows + (size_t)(wave / SP) * (64 * VN * NV * SP) + (v0 + 64 * i) * VN;
 #pragma unroll
-      for (int e = 0; e < 8; e += 4)
+      for (int e = 0; e < VN; e += 4)
         *reinterpret_cast<float4*>(to + e) = make_float4(col[p][i][e], col[p][i][e + 1], col[p][i][e + 2], col[p][i][e + 3]);
     }
     __syncthreads();
-    for (int c = threadIdx.x * 4; c < H; c += 64 * kLnRowWaves * 4) {
+    for (int c = threadIdx.x * 4; c < H; c += 64 * W * 4) {
       float4 t = *reinterpret_cast<const float4*>(lds_rows + c);
 #pragma unroll
       for (int w = 1; w < RPB; ++w) {
-        const float4 v = *reinterpret_cast<const float4*>(lds_rows + (size_t)w * (512 * NV * SP) + c);
+        const float4 v = *reinterpret_cast<const float4*>(lds_rows + (size_t)w * (64 * VN * NV * SP) + c);
         t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w;
       }
       *reinterpret_cast<float4*>(out + (size_t)p * H + c) = t;
@@ -698,14 +711,22 @@ int ln_bwd_blocks(int dtype, int T, int H) {
   return (nbatch + per - 1) / per;
 }
 
-// Waves per row of ln_bwd_rows_kernel (bf16), 0: ln_bwd_kernel.  With three column partials / with dropout's second output, finishing
-// sums included, the other form / this one: 8192 x 3072 50.3 / 45.9, 59.8 / 55.4 us; 4096 x 2560 27.0 / 25.5, 34.1 / 31.5; 8192 x 1536
-// 32.1 / 26.9, 40.4 / 33.5; 3000 x 1536 21.0 / 17.3, 25.7 / 20.8; 16384 x 512 30.7 / 20.3, 39.9 / 25.0; 1024 x 1920 13.9 / 12.6, 15.4 / 14.9;
-// 2048 x 768 13.9 / 11.0.  A workgroup takes eight rows at a time: few rows leave units idle (333 x 1536 9.1 / 9.7, 10.3 / 11.1).  One
+// Which form: waves per row of ln_bwd_rows_kernel (0: ln_bwd_kernel) and the waves of a workgroup.
+// Many bf16 rows of up to 3072 columns, eight waves.  With three column partials / with dropout's second output, finishing sums included,
+// ln_bwd_kernel / this: 8192 x 3072 50.3 / 45.9, 59.8 / 55.4 us; 4096 x 2560 27.0 / 25.5, 34.1 / 31.5; 8192 x 1536 32.1 / 26.9, 40.4 / 33.5; 3000 x
+// 1536 21.0 / 17.3, 25.7 / 20.8; 16384 x 512 30.7 / 20.3, 39.9 / 25.0; 1024 x 1920 13.9 / 12.6, 15.4 / 14.9; 2048 x 768 13.9 / 11.0.  One
 // wave per row up to three vectors a lane, two beyond: 8192 x 1536 26.9 / 28.2, x 1920 32.7 / 31.5, 6000 x 2048 with dropout 39.8 / 33.1.
-static int ln_bwd_row_waves(int rows, int H) {
-  if (H > 3072 || rows < 3 * gemm_cu_count()) return 0;
-  return H <= 1536 ? 1 : 2;
+// Fewer rows, and fp32: four rows a workgroup (eight leave units idle there: 333 x 1536 9.1 / 9.7), whose statistics need no exchange and no
+// barrier and whose partials are requested two at a time.  One partial / two, without the finishing sums: bf16 400 x 192 4.5 / 5.6 us -> 3.8 / 4.1,
+// 256 x 512 4.7 / 5.8 -> 3.8 / 4.1, 333 x 1536 6.2 / 7.7 -> 6.3 / 6.6, 760 x 3072 10.8 / 12.6 -> 10.3 / 11.1; fp32 256 x 256 4.4 / 5.4 -> 3.3 / 3.5, 1024 x
+// 1024 7.8 / 9.1 -> 7.1 / 7.5, 4096 x 512 10.8 / 15.1 -> 9.2 / 10.4.  Not for many fp32 rows of two waves (4096 x 1024 with dropout 19.5 / 20.8).
+struct LnRowForm { int per_row, waves; };
+static LnRowForm ln_bwd_row_form(int esz, int rows, int H) {
+  const int vecs = H * esz / 16, sp = vecs <= 192 ? 1 : 2;
+  if (vecs > 384) return {0, 0};
+  if (esz == 2 && rows >= 3 * gemm_cu_count()) return {sp, 8};
+  if (esz == 4 && sp == 2 && rows > 8 * gemm_cu_count()) return {0, 0};
+  return {sp, 4 * sp};
 }
 
 template <typename T>
@@ -731,37 +752,40 @@ static hipError_t ln_bwd_dispatch(int rows, int H, const void* dy, const void* x
     deferred_record(fin);
     return hipSuccess;
   };
-  if constexpr (kNarrow) {
-    if (const int sp = ln_bwd_row_waves(rows, H)) {
-      nblk = std::min(nblk, std::min(gemm_cu_count(), (rows * sp + kLnRowWaves - 1) / kLnRowWaves));
-      auto go = [&](auto nv_c, auto sp_c) -> hipError_t {
-        constexpr int NV = decltype(nv_c)::value, SP = decltype(sp_c)::value;
-        auto run = [&](auto f, auto s, auto z) -> hipError_t {
-          constexpr size_t kLds = (size_t)kLnRowWaves * 512 * NV * 4;
-          auto kern = ln_bwd_rows_kernel<NV, SP, decltype(f)::value, decltype(s)::value, decltype(z)::value>;
-          static LdsAttrOnce attr;
-          if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
-          hipLaunchKernelGGL(kern, dim3(nblk), dim3(64 * kLnRowWaves), kLds, st, rows, H, (const bf16*)dy, (const bf16*)x,
-                             (const bf16*)gamma, mean, rstd, (const bf16*)residual, (bf16*)dx, ws, pp ? *pp : none, n, (bf16*)dy_out,
-                             drop, (bf16*)dz_out);
-          return hipGetLastError();
-        };
-        const std::true_type yes{};
-        const std::false_type no{};
-        if (pp && dx_colsum && dz_out) return run(yes, yes, yes);
-        if (pp && dz_out) return run(yes, no, yes);
-        if (pp && dx_colsum) return run(yes, yes, no);
-        if (pp) return run(yes, no, no);
-        return run(no, no, no);
+  if (const LnRowForm f = ln_bwd_row_form(sizeof(T), rows, H); f.per_row) {
+    nblk = std::min(nblk, (rows * f.per_row + f.waves - 1) / f.waves);
+    if (kNarrow) nblk = std::min(nblk, gemm_cu_count());          // (a workgroup or less a compute unit: the finishing sums read every partial)
+    auto go = [&](auto nv_c, auto sp_c, auto w_c) -> hipError_t {
+      constexpr int NV = decltype(nv_c)::value, SP = decltype(sp_c)::value, W = decltype(w_c)::value;
+      auto run = [&](auto fu, auto su, auto z) -> hipError_t {
+        constexpr size_t kLds = (size_t)W * 64 * Vec16<T>::N * NV * 4;
+        auto kern = ln_bwd_rows_kernel<T, NV, SP, W, decltype(fu)::value, decltype(su)::value, decltype(z)::value>;
+        static LdsAttrOnce attr;
+        if (hipError_t e = attr.ensure((const void*)kern, (int)kLds); e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, dim3(nblk), dim3(64 * W), kLds, st, rows, H, (const T*)dy, (const T*)x, (const T*)gamma, mean, rstd,
+                           (const T*)residual, (T*)dx, ws, pp ? *pp : none, n, (T*)dy_out, drop, (T*)dz_out);
+        return hipGetLastError();
       };
-      const std::integral_constant<int, 1> one{};
-      const std::integral_constant<int, 2> two{};
-      const std::integral_constant<int, 3> three{};
-      const int nv = (H / 8 + 64 * sp - 1) / (64 * sp);
-      hipError_t e = sp == 2 ? (nv == 2 ? go(two, two) : go(three, two)) : nv == 1 ? go(one, one) : nv == 2 ? go(two, one) : go(three, one);
-      if (e != hipSuccess) return e;
-      return finish();
-    }
+      const std::true_type yes{};
+      const std::false_type no{};
+      if (pp && dx_colsum && dz_out) return run(yes, yes, yes);
+      if (pp && dz_out) return run(yes, no, yes);
+      if (pp && dx_colsum) return run(yes, yes, no);
+      if (pp) return run(yes, no, no);
+      return run(no, no, no);
+    };
+    const std::integral_constant<int, 1> one{};
+    const std::integral_constant<int, 2> two{};
+    const std::integral_constant<int, 3> three{};
+    const std::integral_constant<int, 4> four{};
+    const std::integral_constant<int, 8> eight{};
+    const int sp = f.per_row, nv = (H / Vec16<T>::N + 64 * sp - 1) / (64 * sp);
+    hipError_t e = hipErrorInvalidValue;
+    if (sp == 2) e = nv == 2 ? go(two, two, eight) : go(three, two, eight);
+    else if (f.waves == 4) e = nv == 1 ? go(one, one, four) : nv == 2 ? go(two, one, four) : go(three, one, four);
+    else if constexpr (kNarrow) e = nv == 1 ? go(one, one, eight) : nv == 2 ? go(two, one, eight) : go(three, one, eight);
+    if (e != hipSuccess) return e;
+    return finish();
   }
   dim3 grid(nblk), block(nwaves * 64);
 #define MLM_LN_BWD_VB(VBYTES, F, S, Z)                                                                      \
