@@ -19,8 +19,7 @@ MLM_F32, MLM_BF16 = 0, 1
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libmlm_shard.so")
 
 # Argument types, one letter each: P pointer, i int32, l int64, u uint64, z size_t, f float.  They are declared once, so that
-# a call passes plain integers: wrapping every argument in a ctypes object and asking torch.cuda for the stream object was a
-# third of a step's host time (46 launches: 253-309 -> 194 us a step, and more than the GPU's 246 in bf16 at 400 tokens x 192).
+# a call passes plain integers.
 _SIGNATURES = dict(item.split("=") for item in """
 mlm_shard_range=liiPP mlm_workspace_bytes=PiP mlm_status_string=i mlm_layernorm_fwd=PPPPPPPP
 mlm_layernorm_bwd=PPPPPPPPPPPzP mlm_combine=PPiPPPP mlm_combine_layernorm_fwd=PPiPPPPPPPPP
@@ -125,6 +124,53 @@ def _chk(rc: int, where: str):
         raise MlmError(rc, where)
 
 
+def _marshalled(name: str):
+    """The entry point as the native module has it: (tensors, structures, lists of tensors, ..., stream) -> status.  A list stands for an
+    array and the count behind it, a tensor ahead of a size for both."""
+    sig = _SIGNATURES[name]
+
+    def f(*args):
+        out, it, nbytes, count = [], iter(args), 0, None
+        for at, kind in enumerate(sig):
+            if kind == "z":
+                out.append(nbytes)
+                continue
+            if kind == "i" and count is not None:
+                out.append(count)
+                count = None
+                continue
+            a = next(it)
+            if kind == "P" and at == len(sig) - 1:
+                a = _st(a)
+            elif isinstance(a, ctypes.Structure):
+                a = ctypes.byref(a)
+            elif isinstance(a, (list, tuple)):
+                count, a = len(a), (ctypes.c_void_p * max(len(a), 1))(*[_p(t) for t in a])
+            elif kind == "P":
+                a, nbytes = _ws(a)
+            out.append(a)
+        return getattr(lib(), name)(*out)
+    return f
+
+
+class _Marshalled:
+    """Every entry point through ctypes, for a torch that the native module does not load into."""
+    def __getattr__(self, name):
+        f = _marshalled(name)
+        setattr(self, name, f)
+        return f
+
+
+# Arguments are marshalled natively (csrc/py_call.cpp): in Python that was 69 of 178 us of the host time of a step of 40 launches, now 149 us in
+# all (bf16, 400 tokens x 192, two shards; the GPU needs 161).
+try:
+    if not os.path.exists(LIB_PATH):
+        raise ImportError(LIB_PATH)
+    from . import _mlm_call as _call
+except ImportError:
+    _call = _Marshalled()
+
+
 def mlm_shard_range(n: int, p: int, r: int):
     b, e = ctypes.c_int64(0), ctypes.c_int64(0)
     _chk(lib().mlm_shard_range(n, p, r, ctypes.byref(b),
@@ -139,53 +185,36 @@ def mlm_workspace_bytes(dims: Dims, which: int) -> int:
 
 
 def mlm_layernorm_fwd(dims, x, gamma, beta, y, mean, rstd, stream=None):
-    _chk(lib().mlm_layernorm_fwd(ctypes.byref(dims), _p(x), _p(gamma), _p(beta), _p(y), _p(mean), _p(rstd),
-                                 _st(stream)), "mlm_layernorm_fwd")
+    _chk(_call.mlm_layernorm_fwd(dims, x, gamma, beta, y, mean, rstd, stream), "mlm_layernorm_fwd")
 
 
 def mlm_layernorm_bwd(dims, dy, x, gamma, mean, rstd, residual_grad, dx, dgamma, dbeta, ws, stream=None):
-    _chk(lib().mlm_layernorm_bwd(ctypes.byref(dims), _p(dy), _p(x), _p(gamma), _p(mean), _p(rstd), _p(residual_grad),
-                                 _p(dx), _p(dgamma), _p(dbeta), *_ws(ws), _st(stream)), "mlm_layernorm_bwd")
+    _chk(_call.mlm_layernorm_bwd(dims, dy, x, gamma, mean, rstd, residual_grad, dx, dgamma, dbeta, ws, stream),
+         "mlm_layernorm_bwd")
 
 
 def mlm_combine(dims, partials: Sequence[torch.Tensor], bias, residual, out, stream=None):
-    n = len(partials)
-    arr = (ctypes.c_void_p * max(n, 1))(*[t.data_ptr() for t in partials])
-    for t in partials:
-        _p(t)
-    _chk(lib().mlm_combine(ctypes.byref(dims), arr, n, _p(bias), _p(residual), _p(out), _st(stream)),
-         "mlm_combine")
-
-
-def _partial_array(partials):
-    n = len(partials)
-    for t in partials:
-        _p(t)
-    return (ctypes.c_void_p * max(n, 1))(*[t.data_ptr() for t in partials]), n
+    _chk(_call.mlm_combine(dims, partials, bias, residual, out, stream), "mlm_combine")
 
 
 def mlm_combine_layernorm_fwd(dims, partials: Sequence[torch.Tensor], bias, residual, x_out, gamma, beta, y, mean, rstd,
                               stream=None):
-    arr, n = _partial_array(partials)
-    _chk(lib().mlm_combine_layernorm_fwd(ctypes.byref(dims), arr, n, _p(bias), _p(residual), _p(x_out),
-                                         _p(gamma), _p(beta), _p(y), _p(mean), _p(rstd), _st(stream)),
+    _chk(_call.mlm_combine_layernorm_fwd(dims, partials, bias, residual, x_out, gamma, beta, y, mean, rstd, stream),
          "mlm_combine_layernorm_fwd")
 
 
 def mlm_combine_layernorm_bwd(dims, partials: Sequence[torch.Tensor], x, gamma, mean, rstd, residual_grad, dy_out, dx,
                               dgamma, dbeta, dx_colsum, ws, stream=None):
-    arr, n = _partial_array(partials)
-    _chk(lib().mlm_combine_layernorm_bwd(ctypes.byref(dims), arr, n, _p(x), _p(gamma), _p(mean),
-                                         _p(rstd), _p(residual_grad), _p(dy_out), _p(dx), _p(dgamma), _p(dbeta),
-                                         _p(dx_colsum), *_ws(ws), _st(stream)), "mlm_combine_layernorm_bwd")
+    _chk(_call.mlm_combine_layernorm_bwd(dims, partials, x, gamma, mean, rstd, residual_grad, dy_out, dx, dgamma, dbeta,
+                                         dx_colsum, ws, stream), "mlm_combine_layernorm_bwd")
 
 
 def mlm_colsum(dims, dy, dbias, ws, stream=None):
-    _chk(lib().mlm_colsum(ctypes.byref(dims), _p(dy), _p(dbias), *_ws(ws), _st(stream)), "mlm_colsum")
+    _chk(_call.mlm_colsum(dims, dy, dbias, ws, stream), "mlm_colsum")
 
 
 def mlm_colsum_noalloc(dims, dy, dbias, stream=None):
-    _chk(lib().mlm_colsum_noalloc(ctypes.byref(dims), _p(dy), _p(dbias), _st(stream)), "mlm_colsum_noalloc")
+    _chk(_call.mlm_colsum_noalloc(dims, dy, dbias, stream), "mlm_colsum_noalloc")
 
 
 def mlm_deferred_sums_bytes(dims) -> int:
@@ -195,50 +224,46 @@ def mlm_deferred_sums_bytes(dims) -> int:
 
 
 def mlm_deferred_sums_begin(buf):
-    _chk(lib().mlm_deferred_sums_begin(*_ws(buf)), "mlm_deferred_sums_begin")
+    _chk(_call.mlm_deferred_sums_begin(buf), "mlm_deferred_sums_begin")
 
 
 def mlm_deferred_sums_flush(stream=None):
-    _chk(lib().mlm_deferred_sums_flush(_st(stream)), "mlm_deferred_sums_flush")
+    _chk(_call.mlm_deferred_sums_flush(stream), "mlm_deferred_sums_flush")
 
 
 def mlm_attn_shard_fwd(dims, u, Wqkv_r, bqkv_r, Wo_r, key_len, qkv_r, ctx_r, lse_r, partial_r, ws=None, stream=None):
-    _chk(lib().mlm_attn_shard_fwd(ctypes.byref(dims), _p(u), _p(Wqkv_r), _p(bqkv_r), _p(Wo_r), _p(key_len), _p(qkv_r),
-                                  _p(ctx_r), _p(lse_r), _p(partial_r), *_ws(ws), _st(stream)), "mlm_attn_shard_fwd")
+    _chk(_call.mlm_attn_shard_fwd(dims, u, Wqkv_r, bqkv_r, Wo_r, key_len, qkv_r, ctx_r, lse_r, partial_r, ws, stream),
+         "mlm_attn_shard_fwd")
 
 
 def mlm_attn_shard_bwd(dims, dx1, u, Wqkv_r, Wo_r, key_len, qkv_r, ctx_r, lse_r, dWqkv_r, dbqkv_r, dWo_r,
                        du_partial_r, ws, stream=None):
-    _chk(lib().mlm_attn_shard_bwd(ctypes.byref(dims), _p(dx1), _p(u), _p(Wqkv_r), _p(Wo_r), _p(key_len), _p(qkv_r),
-                                  _p(ctx_r), _p(lse_r), _p(dWqkv_r), _p(dbqkv_r), _p(dWo_r), _p(du_partial_r),
-                                  *_ws(ws), _st(stream)), "mlm_attn_shard_bwd")
+    _chk(_call.mlm_attn_shard_bwd(dims, dx1, u, Wqkv_r, Wo_r, key_len, qkv_r, ctx_r, lse_r, dWqkv_r, dbqkv_r, dWo_r,
+                                  du_partial_r, ws, stream), "mlm_attn_shard_bwd")
 
 
 def mlm_mlp_shard_fwd(dims, u2, A_r, a_r, B_r, g_r, y_r, partial_r, ws=None, stream=None):
-    _chk(lib().mlm_mlp_shard_fwd(ctypes.byref(dims), _p(u2), _p(A_r), _p(a_r), _p(B_r), _p(g_r), _p(y_r),
-                                 _p(partial_r), *_ws(ws), _st(stream)), "mlm_mlp_shard_fwd")
+    _chk(_call.mlm_mlp_shard_fwd(dims, u2, A_r, a_r, B_r, g_r, y_r, partial_r, ws, stream), "mlm_mlp_shard_fwd")
 
 
 def mlm_mlp_shard_bwd(dims, dx2, u2, A_r, B_r, g_r, y_r, dA_r, da_r, dB_r, du2_partial_r, ws, stream=None):
-    _chk(lib().mlm_mlp_shard_bwd(ctypes.byref(dims), _p(dx2), _p(u2), _p(A_r), _p(B_r), _p(g_r), _p(y_r), _p(dA_r),
-                                 _p(da_r), _p(dB_r), _p(du2_partial_r), *_ws(ws), _st(stream)), "mlm_mlp_shard_bwd")
+    _chk(_call.mlm_mlp_shard_bwd(dims, dx2, u2, A_r, B_r, g_r, y_r, dA_r, da_r, dB_r, du2_partial_r, ws, stream),
+         "mlm_mlp_shard_bwd")
 
 
 def mlm_vocab_ce_shard_fwd(dims, hf, E_r, targets, m_r, s_r, t_r, logits_r, ws, stream=None):
-    _chk(lib().mlm_vocab_ce_shard_fwd(ctypes.byref(dims), _p(hf), _p(E_r), _p(targets), _p(m_r), _p(s_r), _p(t_r),
-                                      _p(logits_r), *_ws(ws), _st(stream)), "mlm_vocab_ce_shard_fwd")
+    _chk(_call.mlm_vocab_ce_shard_fwd(dims, hf, E_r, targets, m_r, s_r, t_r, logits_r, ws, stream),
+         "mlm_vocab_ce_shard_fwd")
 
 
 def mlm_vocab_ce_merge(dims, m, s, t, n_shards, loss_w, ce, M, S, loss_out, stream=None):
-    _chk(lib().mlm_vocab_ce_merge(ctypes.byref(dims), _p(m), _p(s), _p(t), n_shards, _p(loss_w),
-                                  _p(ce), _p(M), _p(S), _p(loss_out), _st(stream)), "mlm_vocab_ce_merge")
+    _chk(_call.mlm_vocab_ce_merge(dims, m, s, t, n_shards, loss_w, ce, M, S, loss_out, stream), "mlm_vocab_ce_merge")
 
 
 def mlm_vocab_ce_shard_bwd(dims, hf, E_r, targets, loss_w, M, S, loss_stats, logits_r, dE_r, dhf_partial_r, ws,
                            stream=None):
-    _chk(lib().mlm_vocab_ce_shard_bwd(ctypes.byref(dims), _p(hf), _p(E_r), _p(targets), _p(loss_w), _p(M), _p(S),
-                                      _p(loss_stats), _p(logits_r), _p(dE_r), _p(dhf_partial_r), *_ws(ws),
-                                      _st(stream)), "mlm_vocab_ce_shard_bwd")
+    _chk(_call.mlm_vocab_ce_shard_bwd(dims, hf, E_r, targets, loss_w, M, S, loss_stats, logits_r, dE_r, dhf_partial_r,
+                                      ws, stream), "mlm_vocab_ce_shard_bwd")
 
 
 def mlm_gemm(dtype, trans_a, trans_b, M, N, K, A, B, C, bias=None, stream=None):
@@ -283,26 +308,20 @@ def mlm_rng_stream_seed(base_seed: int, stream: int, r: int) -> int:
 
 
 def mlm_combine_dropout(dims, partials, bias, bias_rows, drop, residual, out, stream=None):
-    arr, n = _partial_array(partials)
-    _chk(lib().mlm_combine_dropout(ctypes.byref(dims), arr, n, _p(bias), bias_rows,
-                                   _d(drop), _p(residual), _p(out), _st(stream)), "mlm_combine_dropout")
+    _chk(_call.mlm_combine_dropout(dims, partials, bias, bias_rows, drop, residual, out, stream), "mlm_combine_dropout")
 
 
 def mlm_combine_layernorm_fwd_dropout(dims, partials, bias, drop, residual, x_out, gamma, beta, y, mean, rstd,
                                       stream=None):
-    arr, n = _partial_array(partials)
-    _chk(lib().mlm_combine_layernorm_fwd_dropout(ctypes.byref(dims), arr, n, _p(bias), _d(drop),
-                                                 _p(residual), _p(x_out), _p(gamma), _p(beta), _p(y), _p(mean),
-                                                 _p(rstd), _st(stream)), "mlm_combine_layernorm_fwd_dropout")
+    _chk(_call.mlm_combine_layernorm_fwd_dropout(dims, partials, bias, drop, residual, x_out, gamma, beta, y, mean,
+                                                 rstd, stream), "mlm_combine_layernorm_fwd_dropout")
 
 
 def mlm_combine_layernorm_bwd_dropout(dims, partials, x, gamma, mean, rstd, residual_grad, drop, dy_out, dx, dz_out,
                                       dgamma, dbeta, dx_colsum, ws, stream=None):
-    arr, n = _partial_array(partials)
-    _chk(lib().mlm_combine_layernorm_bwd_dropout(ctypes.byref(dims), arr, n, _p(x), _p(gamma),
-                                                 _p(mean), _p(rstd), _p(residual_grad), _d(drop), _p(dy_out), _p(dx),
-                                                 _p(dz_out), _p(dgamma), _p(dbeta), _p(dx_colsum), *_ws(ws),
-                                                 _st(stream)), "mlm_combine_layernorm_bwd_dropout")
+    _chk(_call.mlm_combine_layernorm_bwd_dropout(dims, partials, x, gamma, mean, rstd, residual_grad, drop, dy_out, dx,
+                                                 dz_out, dgamma, dbeta, dx_colsum, ws, stream),
+         "mlm_combine_layernorm_bwd_dropout")
 
 
 def mlm_attn_keep_words(dims) -> int:
@@ -313,58 +332,49 @@ def mlm_attn_keep_words(dims) -> int:
 
 def mlm_attn_shard_fwd_dropout(dims, u, Wqkv_r, bqkv_r, Wo_r, key_len, drop, qkv_r, ctx_r, lse_r, keep_bits_r,
                                partial_r, ws=None, stream=None):
-    _chk(lib().mlm_attn_shard_fwd_dropout(ctypes.byref(dims), _p(u), _p(Wqkv_r), _p(bqkv_r), _p(Wo_r), _p(key_len),
-                                          _d(drop), _p(qkv_r), _p(ctx_r), _p(lse_r), _p(keep_bits_r), _p(partial_r),
-                                          *_ws(ws), _st(stream)), "mlm_attn_shard_fwd_dropout")
+    _chk(_call.mlm_attn_shard_fwd_dropout(dims, u, Wqkv_r, bqkv_r, Wo_r, key_len, drop, qkv_r, ctx_r, lse_r,
+                                          keep_bits_r, partial_r, ws, stream), "mlm_attn_shard_fwd_dropout")
 
 
 def mlm_attn_shard_bwd_dropout(dims, dx1, u, Wqkv_r, Wo_r, key_len, drop, qkv_r, ctx_r, lse_r, keep_bits_r, dWqkv_r,
                                dbqkv_r, dWo_r, du_partial_r, ws, stream=None):
-    _chk(lib().mlm_attn_shard_bwd_dropout(ctypes.byref(dims), _p(dx1), _p(u), _p(Wqkv_r), _p(Wo_r), _p(key_len),
-                                          _d(drop), _p(qkv_r), _p(ctx_r), _p(lse_r), _p(keep_bits_r), _p(dWqkv_r),
-                                          _p(dbqkv_r), _p(dWo_r), _p(du_partial_r), *_ws(ws), _st(stream)),
+    _chk(_call.mlm_attn_shard_bwd_dropout(dims, dx1, u, Wqkv_r, Wo_r, key_len, drop, qkv_r, ctx_r, lse_r, keep_bits_r,
+                                          dWqkv_r, dbqkv_r, dWo_r, du_partial_r, ws, stream),
          "mlm_attn_shard_bwd_dropout")
 
 
 def mlm_embed_shard_fwd(dims, ids, E_r, perm_r, partial_r, stream=None):
-    _chk(lib().mlm_embed_shard_fwd(ctypes.byref(dims), _p(ids), _p(E_r), _p(perm_r), _p(partial_r), _st(stream)),
-         "mlm_embed_shard_fwd")
+    _chk(_call.mlm_embed_shard_fwd(dims, ids, E_r, perm_r, partial_r, stream), "mlm_embed_shard_fwd")
 
 
 def mlm_embed_bwd_replicated(dims, dx0, drop, dz0, dpos, stream=None):
-    _chk(lib().mlm_embed_bwd_replicated(ctypes.byref(dims), _p(dx0), _d(drop), _p(dz0), _p(dpos), _st(stream)),
-         "mlm_embed_bwd_replicated")
+    _chk(_call.mlm_embed_bwd_replicated(dims, dx0, drop, dz0, dpos, stream), "mlm_embed_bwd_replicated")
 
 
 def mlm_embed_shard_bwd(dims, ids, perm_r, dz0, dE_r, stream=None):
-    _chk(lib().mlm_embed_shard_bwd(ctypes.byref(dims), _p(ids), _p(perm_r), _p(dz0), _p(dE_r), _st(stream)),
-         "mlm_embed_shard_bwd")
+    _chk(_call.mlm_embed_shard_bwd(dims, ids, perm_r, dz0, dE_r, stream), "mlm_embed_shard_bwd")
 
 
 def mlm_rows_gather(dims, x, row_idx, n, n_out, out, stream=None):
-    _chk(lib().mlm_rows_gather(ctypes.byref(dims), _p(x), _p(row_idx), n, n_out, _p(out),
-                               _st(stream)), "mlm_rows_gather")
+    _chk(_call.mlm_rows_gather(dims, x, row_idx, n, n_out, out, stream), "mlm_rows_gather")
 
 
 def mlm_rows_scatter(dims, y, row_idx, n, out, stream=None):
-    _chk(lib().mlm_rows_scatter(ctypes.byref(dims), _p(y), _p(row_idx), n, _p(out), _st(stream)),
-         "mlm_rows_scatter")
+    _chk(_call.mlm_rows_scatter(dims, y, row_idx, n, out, stream), "mlm_rows_scatter")
 
 
 # ---- backward with the weight gradients deferred to one grouped launch -------------------------------------------
 def mlm_mlp_shard_bwd_input(dims, dx2, A_r, B_r, g_r, dg_r, da_r, du2_partial_r, ws, stream=None):
-    _chk(lib().mlm_mlp_shard_bwd_input(ctypes.byref(dims), _p(dx2), _p(A_r), _p(B_r), _p(g_r), _p(dg_r), _p(da_r),
-                                       _p(du2_partial_r), *_ws(ws), _st(stream)), "mlm_mlp_shard_bwd_input")
+    _chk(_call.mlm_mlp_shard_bwd_input(dims, dx2, A_r, B_r, g_r, dg_r, da_r, du2_partial_r, ws, stream),
+         "mlm_mlp_shard_bwd_input")
 
 
 def mlm_attn_shard_bwd_input(dims, dx1, Wqkv_r, Wo_r, key_len, drop, qkv_r, ctx_r, lse_r, keep_bits_r, dqkv_r, dbqkv_r,
                              du_partial_r, ws, stream=None):
-    _chk(lib().mlm_attn_shard_bwd_input(ctypes.byref(dims), _p(dx1), _p(Wqkv_r), _p(Wo_r), _p(key_len), _d(drop),
-                                        _p(qkv_r), _p(ctx_r), _p(lse_r), _p(keep_bits_r), _p(dqkv_r), _p(dbqkv_r),
-                                        _p(du_partial_r), *_ws(ws), _st(stream)), "mlm_attn_shard_bwd_input")
+    _chk(_call.mlm_attn_shard_bwd_input(dims, dx1, Wqkv_r, Wo_r, key_len, drop, qkv_r, ctx_r, lse_r, keep_bits_r,
+                                        dqkv_r, dbqkv_r, du_partial_r, ws, stream), "mlm_attn_shard_bwd_input")
 
 
 def mlm_layer_shard_wgrads(dims, u, dqkv_r, ctx_r, dz1, u2, dg_r, y_r, dz2, dWqkv_r, dWo_r, dA_r, dB_r, ws, stream=None):
-    _chk(lib().mlm_layer_shard_wgrads(ctypes.byref(dims), _p(u), _p(dqkv_r), _p(ctx_r), _p(dz1), _p(u2), _p(dg_r),
-                                      _p(y_r), _p(dz2), _p(dWqkv_r), _p(dWo_r), _p(dA_r), _p(dB_r), *_ws(ws),
-                                      _st(stream)), "mlm_layer_shard_wgrads")
+    _chk(_call.mlm_layer_shard_wgrads(dims, u, dqkv_r, ctx_r, dz1, u2, dg_r, y_r, dz2, dWqkv_r, dWo_r, dA_r, dB_r, ws, stream),
+         "mlm_layer_shard_wgrads")

@@ -44,6 +44,25 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _module() -> str:
+    """The CPython module that marshals the hot calls' arguments; host code against torch's headers, linked to the library beside it."""
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    root = os.path.dirname(torch.__file__)
+    out = os.path.join(HERE, "_mlm_call.so")
+    inc = [f"-I{d}" for d in [os.path.join(ROOT, "include"), sysconfig.get_paths()["include"], *cpp_extension.include_paths(),
+                               os.path.join(cpp_extension.ROCM_HOME or "/opt/rocm", "include")]]
+    cmd = [_hipcc(), "--offload-arch=gfx950", "-x", "c++", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM", "-O2", "-std=c++17", "-fPIC", "-shared",
+           "-fvisibility=hidden", "-w", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *inc,
+           os.path.join(CSRC, "py_call.cpp"), "-o", out, f"-L{HERE}", "-l:libmlm_shard.so", "-Wl,-rpath,$ORIGIN", f"-L{root}/lib",
+           "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("py_call.cpp failed:\n" + r.stderr)
+    return out
+
+
 def build(jobs: int = 8, verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
@@ -52,6 +71,7 @@ def build(jobs: int = 8, verbose: bool = True) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
+    _module()
     if verbose:
         print(f"built {LIB} ({os.path.getsize(LIB) / 1e6:.1f} MB)")
     return LIB
