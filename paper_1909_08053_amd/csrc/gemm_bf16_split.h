@@ -1,13 +1,12 @@
 // bf16 GEMM for outputs of few tiles (gfx950): C[m,n] = sum_k A(m,k) B(k,n) in tiles of 64 x 64, 32 x 64 or 32 x 32, whose
 // k is dealt to the eight waves of a workgroup in 32-deep slices.
 //   * Such a product is bound by latency, not by bytes or flops: the 128 x 128 tile leaves most compute units idle there, and
-//     its ring of slices, its barriers and its epilogue are a chain of 5 us before anything is stored.  Here every wave loads
-//     the fragments of its own slices straight into registers (no LDS, no barrier in the loop, two slices in flight a wave and
-//     sixteen a compute unit), and the eight partial sums of an output meet once, in LDS.
-//   * A k-contiguous operand is a fragment as it lies in memory: lane l takes the 16 bytes k = 8 (l / 16) .. + 7 of row l % 16.
-//     An operand contiguous along m / n is transposed in registers: lane l loads four (two) neighbouring columns of the eight
-//     k-rows 8 (l / 16) .. + 7 -- 16 lanes a full 128-byte line (half of one) -- and one byte permute per register pairs two
-//     k-rows; its 16 x 16 tiles then hold columns 4 c + f (2 c + f), f the tile's number, and the store undoes that order for nothing.
+//     its ring of slices, its barriers and its epilogue are a chain of 5 us before anything is stored.  Here a wave copies its own slices
+//     into LDS that nobody else reads (two ahead, no barrier in the loop), and the eight partial sums of an output meet once, in LDS.
+//   * Larger ones are bound by what a compute unit takes in, 55-60 GB/s of slices (a 64 x 64 tile 8 KB a slice), whatever is under way:
+//     three slices ahead in place of two changed nothing.  Fragments loaded straight into registers had reached 45, and 30 where both
+//     operands are k-contiguous (3000 x 384 x 1536 26 us, 15 now; 400 x 288 x 192 2.7 both ways): sixteen neighbouring lanes ask for
+//     sixteen rows there, the copies four lanes for 64 bytes of one.
 //   * Sums: eight chains over k, added in pairs; no result is further from the exact one than in the large tiles' single chain.
 #pragma once
 #include "gemm_bf16_v2.h"
@@ -16,89 +15,63 @@ namespace mlm {
 
 constexpr int kSplitWaves = 8;
 
-// The fragments of one operand's ROWS rows (64 or 32) in one 32-deep slice.
+// One operand's ROWS rows (64 or 32) of 32-deep slices: copies of a slice into the wave's own stretch of LDS (1 KB each, lane t's 16 bytes at
+// 16 t), and its fragments from there.  LDS positions are permuted on the global side so that both kinds of fragment read are free of
+// bank conflicts (a pass of a 16-byte read takes lanes 0-3, 12-15 and 20-27 or the others of its 32; one of a transposing read k-rows 0-3 and
+// 8-11, 32 bytes each, or 4-7 and 12-15).
 template <bool KC, int ROWS> struct SplitOperand;
 
+// k-contiguous: 16 rows of 64 bytes a copy, so that four neighbouring lanes ask for one stretch of memory (loaded straight into registers a
+// fragment asks for sixteen rows with sixteen neighbouring lanes: a quarter as many bytes a cycle).
 template <int ROWS> struct SplitOperand<true, ROWS> {
-  static constexpr int NF = ROWS / 16;
-  struct Raw { bf16x8 v[NF]; };
+  static constexpr int NC = ROWS / 16, NF = ROWS / 16;
   const char* base;                    // the tile's first row (uniform)
-  uint32_t off[NF];                    // bytes from there to this lane's unit of slice 0; below 4 GiB: 63 rows of at most 2^24 k
-  uint32_t unit;                       // 16 (lane / 16)
+  uint32_t off[NC];                    // bytes from there to this lane's unit of slice 0; below 4 GiB: 63 rows of at most 2^24 k
+  int unit;                            // its place in the slice, in elements of k
+  static __device__ __forceinline__ int sw(int row) { return -(row >> 2) & 3; }
   __device__ __forceinline__ void init(const void* P, int ld, int row0, int nrows, int lane) {
     base = (const char*)P + (size_t)row0 * ld * 2;
-    unit = (lane >> 4) * 16;
+    unit = ((lane & 3) ^ sw(lane >> 2)) * 8;
 #pragma unroll
-    for (int f = 0; f < NF; ++f) off[f] = (uint32_t)(min(row0 + 16 * f + (lane & 15), nrows - 1) - row0) * (uint32_t)ld * 2 + unit;
+    for (int c = 0; c < NC; ++c) off[c] = (uint32_t)(min(row0 + 16 * c + (lane >> 2), nrows - 1) - row0) * (uint32_t)ld * 2 + unit * 2;
   }
-  __device__ __forceinline__ void load(Raw& r, int s) const {
-    const char* p = base + (size_t)s * 64;
-#pragma unroll
-    for (int f = 0; f < NF; ++f) r.v[f] = *reinterpret_cast<const bf16x8*>(p + off[f]);
-  }
-  // slice s holds kleft < 32 of k, a multiple of 8: units past it are zeros
-  __device__ __forceinline__ void load_end(Raw& r, int s, int kleft) const {
-    const char* p = base + (size_t)s * 64;
-    const bool in = (int)unit < kleft * 2;
-#pragma unroll
-    for (int f = 0; f < NF; ++f) {
-      const bf16x8 v = *reinterpret_cast<const bf16x8*>(p + (in ? off[f] : off[f] - unit));
-      const bf16x8 zero = {};
-      r.v[f] = in ? v : zero;
-    }
-  }
-  __device__ __forceinline__ void frags(const Raw& r, bf16x8 (&f)[NF]) const {
-#pragma unroll
-    for (int i = 0; i < NF; ++i) f[i] = r.v[i];
+  __device__ __forceinline__ const char* at(int s, int c, int) const { return base + (size_t)s * 64 + off[c]; }
+  __device__ __forceinline__ int k_of(int) const { return unit; }
+  static __device__ __forceinline__ bf16x8 frag(const unsigned char* ring, int f, int lane) {
+    const int row = lane & 15;
+    return *reinterpret_cast<const bf16x8*>(ring + f * 1024 + row * 64 + (((lane >> 4) ^ sw(row)) << 4));
   }
 };
 
+// Contiguous along m / n: 8 (16) k-rows of 128 (64) bytes a copy; transposed by the fragment read.
 template <int ROWS> struct SplitOperand<false, ROWS> {
-  static constexpr int NF = ROWS / 16, NW = NF / 2;      // words (of two columns) a lane loads of a k-row
-  struct Raw { uint32_t w[8][NW]; };
+  static constexpr int U = ROWS / 8, KR = 64 / U, NC = 32 / KR, NF = ROWS / 16;      // units of a k-row, k-rows of a copy
   const char* base;                    // the tile's first column (uniform)
-  uint32_t col, off;                   // bytes to this lane's columns; and to its first k-row of slice 0
-  int ld;
+  uint32_t off[2];                     // bytes to this lane's unit of an even / odd copy
+  int ld, row;                         // its k-row in the copy
+  static __device__ __forceinline__ int sw(int k) { return (U == 8 ? (((k >> 1) & 1) | (((k >> 3) & 1) << 1)) : ((k >> 3) & 1)) << 1; }
   __device__ __forceinline__ void init(const void* P, int ld_, int row0, int nrows, int lane) {
     ld = ld_;
     base = (const char*)P + (size_t)row0 * 2;
-    col = (uint32_t)(min(row0 + NF * (lane & 15), nrows - NF) - row0) * 2;      // (nrows, a multiple of 8, is past row0)
-    off = (uint32_t)(lane >> 4) * 8u * (uint32_t)ld * 2 + col;
-  }
-  static __device__ __forceinline__ void get(uint32_t (&w)[NW], const char* p) {
-    if constexpr (NW == 2) {
-      const uint2 v = *reinterpret_cast<const uint2*>(p);
-      w[0] = v.x; w[1] = v.y;
-    } else {
-      w[0] = *reinterpret_cast<const uint32_t*>(p);
+    row = lane / U;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int u = (lane & (U - 1)) ^ sw(KR * c + row);
+      off[c] = (uint32_t)row * (uint32_t)ld * 2 + (uint32_t)(min(row0 + u * 8, nrows - 8) - row0) * 2;
     }
   }
-  __device__ __forceinline__ void load(Raw& r, int s) const {
-    const char* p = base + (size_t)s * 64 * ld;
+  __device__ __forceinline__ const char* at(int s, int c, int) const { return base + (size_t)(s * 32 + c * KR) * 2 * ld + off[c & 1]; }
+  __device__ __forceinline__ int k_of(int c) const { return c * KR + row; }
+  static __device__ __forceinline__ bf16x8 frag(const unsigned char* ring, int f, int lane) {
+    const int l16 = lane & 15, lg = lane >> 4, u = 2 * f + ((l16 & 3) >> 1);
+    v4s_t h[2];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) get(r.w[j], p + (size_t)j * 2 * ld + off);
-  }
-  __device__ __forceinline__ void load_end(Raw& r, int s, int kleft) const {
-    const char* p = base + (size_t)s * 64 * ld;
-    const int k0 = (threadIdx.x >> 4 & 3) * 8;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      get(r.w[j], p + (size_t)((uint32_t)min(k0 + j, kleft - 1) * (uint32_t)ld * 2 + col));
-#pragma unroll
-      for (int q = 0; q < NW; ++q) r.w[j][q] = k0 + j < kleft ? r.w[j][q] : 0u;
+    for (int r = 0; r < 2; ++r) {
+      const int k = 8 * lg + 4 * r + (l16 >> 2);
+      h[r] = lds_read_tr16(ring + k * (ROWS * 2) + ((u ^ sw(k)) << 4) + (l16 & 1) * 8);
     }
-  }
-  __device__ __forceinline__ void frags(const Raw& r, bf16x8 (&f)[NF]) const {
-#pragma unroll
-    for (int i = 0; i < NF; ++i) {
-      uint4 v;
-      const uint32_t sel = i & 1 ? 0x07060302u : 0x05040100u;         // the high or the low halves of two k-rows
-      v.x = __builtin_amdgcn_perm(r.w[1][i >> 1], r.w[0][i >> 1], sel);
-      v.y = __builtin_amdgcn_perm(r.w[3][i >> 1], r.w[2][i >> 1], sel);
-      v.z = __builtin_amdgcn_perm(r.w[5][i >> 1], r.w[4][i >> 1], sel);
-      v.w = __builtin_amdgcn_perm(r.w[7][i >> 1], r.w[6][i >> 1], sel);
-      f[i] = __builtin_bit_cast(bf16x8, v);
-    }
+    const v8s_t v = __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8, v);
   }
 };
 
@@ -118,7 +91,10 @@ template <int N> __device__ __forceinline__ float split_sum(float v) {
   return v;
 }
 
-template <int TM, int TN> constexpr size_t split_lds_bytes() { return (size_t)kSplitWaves * TM * TN * 4; }
+// two stages of a slice for every wave, or the partial tiles
+template <int TM, int TN> constexpr size_t split_lds_bytes() {
+  return (size_t)kSplitWaves * (TM * TN * 4 > 2 * (TM + TN) * 64 ? TM * TN * 4 : 2 * (TM + TN) * 64);
+}
 
 // One tile.  Enters and leaves without a barrier of its own outside; uses split_lds_bytes<TM, TN>() of LDS.
 template <bool A_KC, bool B_KC, int EPI, int TM, int TN>
@@ -132,8 +108,6 @@ __device__ __forceinline__ void gemm_split_tile(const GemmArgs& a, int tile_m, i
   SplitOperand<B_KC, TN> B;
   A.init(a.A, a.lda, m0, a.M, lane);
   B.init(a.B, a.ldb, n0, a.N, lane);
-  typename SplitOperand<A_KC, TM>::Raw ra[2];
-  typename SplitOperand<B_KC, TN>::Raw rb[2];
   floatx4 acc[NB][NA];
 #pragma unroll
   for (int i = 0; i < NB; ++i)
@@ -152,74 +126,64 @@ __device__ __forceinline__ void gemm_split_tile(const GemmArgs& a, int tile_m, i
   if (EPI == EPI_DGELU) pre = *reinterpret_cast<const OutVec*>((const bf16*)a.aux + (size_t)gmc * a.ldaux + gnc);
   if (EPI == EPI_CE) target = a.targets[gmc] - a.v0 - gn;
 
-  // slices wave, wave + 8, ...; the last one of k may hold less than 32.  Both forms of a load are as many requests, so that what
-  // is outstanding at a product is known whichever ran.
+  // slices wave, wave + 8, ... through two stages of the wave's own LDS; nobody else reads them, so there is no barrier.  The last slice of k
+  // may hold less than 32: units past it are copied from sixteen zero bytes.
+  constexpr int BYTES_A = TM * 64, STAGE = (TM + TN) * 64, CPS = SplitOperand<A_KC, TM>::NC + SplitOperand<B_KC, TN>::NC;
   const int kleft = a.K & 31, slices = (a.K + 31) >> 5, last = kleft ? slices - 1 : -1;
   const int n = slices > wave ? (slices - wave + KW - 1) / KW : 0;
-  auto load = [&](int set, int i) {
+  unsigned char* ring = lds_raw + wave * (2 * STAGE);
+  const uint32_t ring0 = lds_offset_of(ring);
+  auto issue = [&](int i) {
     const int s = wave + i * KW;
-    if (s == last) {
-      A.load_end(ra[set], s, kleft);
-      B.load_end(rb[set], s, kleft);
-    } else {
-      A.load(ra[set], s);
-      B.load(rb[set], s);
-    }
+    const uint32_t dst = ring0 + (i & 1) * STAGE;
+    const bool end = s == last;
+    auto copies = [&](const auto& op, uint32_t to) {
+#pragma unroll
+      for (int c = 0; c < std::decay_t<decltype(op)>::NC; ++c) {
+        const bf16* src = reinterpret_cast<const bf16*>(op.at(s, c, 0));
+        if (end) src = op.k_of(c) < kleft ? src : reinterpret_cast<const bf16*>(&v2_zero16);
+        dma16(src, to + c * 1024);
+      }
+    };
+    copies(A, dst);
+    copies(B, dst + BYTES_A);
   };
-  auto mul = [&](int set) {
+  if (n > 0) issue(0);
+  if (n > 1) issue(1);
+  for (int i = 0; i < n; ++i) {
+    if (i + 1 < n) wait_vmcnt<CPS>();
+    else wait_vmcnt<0>();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");                     // (no fragment is read ahead of the wait)
+    const unsigned char* st = ring + (i & 1) * STAGE;
     bf16x8 fa[NA], fb[NB];
-    A.frags(ra[set], fa);
-    B.frags(rb[set], fb);
+#pragma unroll
+    for (int j = 0; j < NA; ++j) fa[j] = SplitOperand<A_KC, TM>::frag(st, j, lane);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) fb[j] = SplitOperand<B_KC, TN>::frag(st + BYTES_A, j, lane);
+    if (i + 2 < n) {
+      __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0): the stage's fragments are in registers
+      __builtin_amdgcn_sched_barrier(0);
+      issue(i + 2);
+    }
 #pragma unroll
     for (int j = 0; j < NA; ++j)
 #pragma unroll
-      for (int i = 0; i < NB; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[i], fa[j], acc[i][j], 0, 0, 0);
-  };
-  if (n == 1) {
-    load(0, 0);
-    mul(0);
-  } else if (n > 1) {
-    load(0, 0);
-    load(1, 1);
-    int i = 0;
-    for (; i + 3 < n; i += 2) {
-      mul(0);
-      load(0, i + 2);
-      mul(1);
-      load(1, i + 3);
-    }
-    mul(0);
-    const bool three = i + 2 < n;
-    if (three) load(0, i + 2);
-    mul(1);
-    if (three) mul(0);
+      for (int q = 0; q < NB; ++q) acc[q][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[q], fa[j], acc[q][j], 0, 0, 0);
   }
+  asm volatile("" ::: "memory");
 
   // partial tiles: [wave][row][chunks of four columns], a row's chunks XORed with the row so that the eight lanes of a pass of
-  // writes meet different banks (their rows are neighbours, or four / two apart where A is transposed in registers)
+  // writes meet different banks.  A wave's lies over its own stages (64 x 64) or other waves' (then all wait for each other first).
   float* lds = reinterpret_cast<float*>(lds_raw);
-  constexpr int CH = TN / 4, RS = A_KC ? 0 : (NA == 4 ? 2 : 1);
-  auto chunk_at = [&](int w, int row, int c) { return lds + ((size_t)w * TM + row) * TN + ((c ^ ((row >> RS) & (CH - 1) & 7)) * 4); };
+  constexpr int CH = TN / 4;
+  if constexpr (TM * TN * 4 != 2 * STAGE) __syncthreads();
+  auto chunk_at = [&](int w, int row, int c) { return lds + ((size_t)w * TM + row) * TN + ((c ^ (row & (CH - 1) & 7)) * 4); };
 #pragma unroll
-  for (int j = 0; j < NA; ++j) {
-    const int row = A_KC ? 16 * j + l16 : NA * l16 + j;
-    if constexpr (B_KC) {
+  for (int j = 0; j < NA; ++j)
 #pragma unroll
-      for (int i = 0; i < NB; ++i)
-        *reinterpret_cast<float4*>(chunk_at(wave, row, 4 * i + lg)) = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-    } else if constexpr (NB == 4) {
-      // tile i holds columns 4 c + i, c = 4 lg + e: one e of the four tiles is a chunk
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        *reinterpret_cast<float4*>(chunk_at(wave, row, 4 * lg + e)) = make_float4(acc[0][j][e], acc[1][j][e], acc[2][j][e], acc[3][j][e]);
-    } else {
-      // columns 2 c + i: two e of the two tiles
-#pragma unroll
-      for (int e = 0; e < 4; e += 2)
-        *reinterpret_cast<float4*>(chunk_at(wave, row, 2 * lg + e / 2)) =
-            make_float4(acc[0][j][e], acc[1][j][e], acc[0][j][e + 1], acc[1][j][e + 1]);
-    }
-  }
+    for (int i = 0; i < NB; ++i)
+      *reinterpret_cast<float4*>(chunk_at(wave, 16 * j + l16, 4 * i + lg)) = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
   __syncthreads();
   float v[VEC], p[KW][VEC];
 #pragma unroll
@@ -380,26 +344,21 @@ inline int split_tiles(int form, int M, int N) {
 // Microseconds of a launch of `tiles` tiles, the longest of `nk` slices and all together of `work` = sum of tiles x slices: a start, the
 // longest wave's slices, further rounds of the chip (a workgroup of the larger two forms a compute unit, two of the smallest), and the
 // operands' way through the caches.  Fitted to 1000 products of the three layouts (64 .. 8192 x 16 .. 6600 x 24 .. 8352), 300 groups of the
-// weight gradients of a layer shard and 290 pairs of the logits' gradients; standard deviation 7-11 %.
+// weight gradients of a layer shard and 290 pairs of the logits' gradients; standard deviation 7-10 %.
 enum { SPLIT_ALONE = 0, SPLIT_GROUP, SPLIT_DUAL };
 inline double split_us(int kind, int form, int tiles, int nk, double work) {
   static const double c[3][3][5] = {            // start, per serial slice, per serial slice of a further round, per further round, work
-      {{2.42, 0.99, 0.70, 1.48, 0.069}, {1.95, 0.79, 0.30, 0.39, 0.054}, {1.95, 0.46, 0.06, 0.50, 0.063}},
-      {{2.80, 1.05, 0.50, 2.67, 0.060}, {2.04, 0.88, 0.03, 0.68, 0.089}, {2.32, 0.49, 0.00, 1.12, 0.071}},
-      {{2.37, 1.09, 0.25, 0.00, 0.087}, {2.09, 0.82, 0.04, 0.20, 0.080}, {2.17, 0.45, 0.00, 0.32, 0.062}}};
+      {{2.59, 0.80, 0.42, 1.94, 0.065}, {2.20, 0.59, 0.24, 1.41, 0.051}, {2.10, 0.38, 0.00, 1.06, 0.052}},
+      {{2.79, 0.88, 0.33, 2.57, 0.063}, {2.45, 0.75, 0.22, 1.66, 0.054}, {2.50, 0.41, 0.00, 1.10, 0.073}},
+      {{2.73, 0.67, 0.13, 0.63, 0.093}, {2.49, 0.40, 0.00, 0.85, 0.091}, {2.30, 0.31, 0.00, 0.57, 0.058}}};
   const double* q = c[kind][form - SPLIT_64];
   const int cus = gemm_cu_count(), per = form == SPLIT_32 ? 2 * cus : cus, serial = (nk + kSplitWaves - 1) / kSplitWaves;
   const int more = (tiles + per - 1) / per - 1;
   return q[0] + q[1] * serial + (q[2] * serial + q[3]) * more + q[4] * work / cus;
 }
-// Slices as dear as these many where every row of a k-contiguous operand (there are kc) starts at the same place of a 128-byte line: the
-// sixteen rows of a request then seem to meet in one bank of the vector cache (1068 x 848 x 832 in 64 x 64 9.2 us, x 848 7.8; neither
-// another deal of the slices, other first slices for every tile nor requests of whole lines changed that).
-inline double split_slow(int kc, int K) { return K % 64 ? 1.0 : kc == 2 ? 1.4 : kc == 1 ? 1.1 : 1.0; }
-inline double split_us(int form, int M, int N, int K, int kc) {
+inline double split_us(int form, int M, int N, int K) {
   const int t = split_tiles(form, M, N), nk = (K + 31) / 32;
-  const double start = 2.0;
-  return start + split_slow(kc, K) * (split_us(SPLIT_ALONE, form, t, nk, (double)t * nk) - start);
+  return split_us(SPLIT_ALONE, form, t, nk, (double)t * nk);
 }
 // Microseconds of t 128-wide tiles of all problems of a launch, at most one a compute unit, the longest of nk slices
 inline double v2_few_us(int t, int nk) { return 3.0 + 0.245 * nk + 3.2 * t / gemm_cu_count(); }
@@ -411,20 +370,21 @@ inline double v2_few_us(const V2Plan& p, int K) {
   if (p.bn == V2_SMALL && p.full_tiles == 0) return 10.5 + 0.05 * nk / p.split + 11.0 * p.tail_tiles * p.split / cus;
   return p.cost;
 }
-// The form that is fastest by these prices, and its price (form SPLIT_NONE, price `than`: none beats that by an eighth).  wide: only forms of
-// 64 columns (the cross-entropy partials' column tiles).  Large tiles / these, us: fwd 400 x 288 x 192 4.5 / 2.7, 123 x 1888 x 1888 15.9 / 7.2, 1024 x
-// 1920 x 960 stays (10.3 / 16.3), dgrad 400 x 192 x 512 6.0 / 3.9, 915 x 928 x 464 8.3 / 6.1, 1068 x 848 x 848 12.1 / 7.8, wgrad 192 x 512 x 400 6.2 /
-// 3.1, 688 x 168 x 2166 15.6 / 8.6.  Of 1000 drawn products 716 take one of these and the mean time falls to 0.665 (0.656 with the best choice
-// every time); four are more than 3 % slower, 976 x 1304 x 86 most, 4.3 / 5.5.
-constexpr double kSplitMargin = 0.88;
+// The form that is fastest by these prices, and its price (form SPLIT_NONE, price `than`: none beats that by a twelfth).  wide: only forms of
+// 64 columns (the cross-entropy partials' column tiles).  Large tiles / 64 x 64 / 32 x 64 / 32 x 32, us: fwd 400 x 288 x 192 4.5 / 3.6 / 3.1 / 2.8, 123 x 1888 x
+// 1920 15.4 / 10.2 / 8.2 / 6.8, 273 x 2776 x 2776 22.0 / 16.4 / 22.5 / 28; dgrad 400 x 192 x 512 6.0 / 4.3 / 3.4 / 2.9, 915 x 928 x 448 6.4 / 5.4 / 6.7 / 6.9,
+// 2048 x 512 x 512 6.7 / 5.4 / 6.8 / 7.0; wgrad 192 x 512 x 400 6.1 / 4.3 / 3.6 / 3.1, 688 x 168 x 2166 15.5 / 12 / 10 / 8.5; fwd 1024 x 1920 x 960 stays, 10.3 / 12.2.
+// Of 1000 drawn products 742 take one of these and the mean time falls to 0.642 (0.635 with the best choice every time); five are more than 3 %
+// slower, 624 x 416 x 4059 most, 19.5 / 23.7.
+constexpr double kSplitMargin = 0.92;
 constexpr int kSplitMaxTiles = 4096;
 struct SplitPick { int form; double us; };
-inline SplitPick split_pick(int M, int N, int K, int kc, double than, bool wide = false) {
+inline SplitPick split_pick(int M, int N, int K, double than, bool wide = false) {
   SplitPick best = {SPLIT_NONE, kSplitMargin * than};
   if (gemm_v2_forced_bn()) return {SPLIT_NONE, than};
   for (int form = SPLIT_64; form <= (wide ? SPLIT_32X64 : SPLIT_32); ++form) {
     if (split_tiles(form, M, N) > kSplitMaxTiles) continue;
-    const double us = split_us(form, M, N, K, kc);
+    const double us = split_us(form, M, N, K);
     if (us < best.us) best = {form, us};
   }
   if (best.form == SPLIT_NONE) best.us = than;
@@ -434,12 +394,12 @@ inline SplitPick split_pick(int M, int N, int K, int kc, double than, bool wide 
 template <bool A_KC, bool B_KC, int EPI>
 SplitPick split_pick_alone(int M, int N, int K, bool allow_split) {
   const V2Plan p = v2_plan(M, N, K, allow_split, v2_pick_bn<A_KC, B_KC, EPI>(M, N, K, allow_split));
-  return split_pick(M, N, K, (A_KC ? 1 : 0) + (B_KC ? 1 : 0), v2_few_us(p, K), EPI == EPI_CE);
+  return split_pick(M, N, K, v2_few_us(p, K), EPI == EPI_CE);
 }
 
 // Weight gradients of one K in one launch of these tiles, against the launch or launches of the plan p.  (Only where 128-wide tiles would
-// find a compute unit each: beyond, these lose.)  T x H split p ways, large tiles / 64 x 64 / 32 x 64 / 32 x 32, us: 380 x 352, 4 6.7 / 5.7 / 5.5 / 5.0, 92 x
-// 640, 8 4.4 / 3.9 / 3.6 / 4.3, 2092 x 320, 4 19 / 13 / 11.5 / 14; 48 x 672, 4 4.1 / 5.9 / 4.8 / 6.1 stays.
+// find a compute unit each: beyond, these lose.)  T x H split p ways, large tiles / 64 x 64 / 32 x 64 / 32 x 32, us: 95 x 384, 4 4.4 / 3.7 / 3.4 / 3.6, 1954
+// x 288, 4 18.5 / 12.1 / 10.5 / 9.3; 247 x 896, 8 6.1 / 7.8 / 8.8 / 8.1 stays.
 inline int split_group_pick(const GemmArgs* probs, int n, const V2GroupPlan& p) {
   if (gemm_v2_group_off() || gemm_v2_forced_bn() || n < 2 || n > kMaxGroup) return SPLIT_NONE;
   const int nk = (probs[0].K + 31) / 32;
@@ -466,8 +426,8 @@ inline int split_group_pick(const GemmArgs* probs, int n, const V2GroupPlan& p) 
 }
 
 // A weight gradient a0 and an input gradient a1 in one launch of these tiles, against the launch or launches of d.  T x H x V, as they were / the
-// three forms, us: 316 x 704 x 448 6.4 / 6.1 / 5.7 / 4.8, 2486 x 152 x 4200 42 / 29 / 37 / 41, 144 x 1280 x 2896 24 / 20 / 21 / 20; 442 x 768 x 6384 35 / 41 /
-// 49 / 48 stays.
+// three forms, us: 176 x 896 x 656 8.6 / 5.0 / 5.7 / 5.8, 3218 x 768 x 392 24 / 16 / 22 / 24, 338 x 560 x 3728 25 / 21 / 19 / 19; 442 x 768 x 6384 35 / 37 / 46 /
+// 47 stays.
 inline int split_dual_pick(const GemmArgs& a0, const GemmArgs& a1, const V2Dual& d) {
   if (gemm_v2_forced_bn() || d.bn == V2_B) return SPLIT_NONE;
   const int nk0 = (a0.K + 31) / 32, nk1 = (a1.K + 31) / 32, nk = nk0 > nk1 ? nk0 : nk1;
@@ -480,7 +440,7 @@ inline int split_dual_pick(const GemmArgs& a0, const GemmArgs& a1, const V2Dual&
   for (int form = SPLIT_64; form <= SPLIT_32; ++form) {
     const int t0 = split_tiles(form, a0.M, a0.N), t1 = split_tiles(form, a1.M, a1.N);
     if (t0 + t1 > kSplitMaxTiles) continue;
-    const double t = split_us(SPLIT_DUAL, form, t0 + t1, nk, (double)t0 * nk0 + (double)t1 * nk1 * split_slow(2, a1.K));
+    const double t = split_us(SPLIT_DUAL, form, t0 + t1, nk, (double)t0 * nk0 + (double)t1 * nk1);
     if (t < us) { us = t; best = form; }
   }
   return best;
