@@ -21,6 +21,7 @@
 #include <type_traits>
 #include <utility>
 #include "gemm_f32_common.h"
+#include "lds_dma.h"
 #include "gemm_f32_pick.h"
 
 namespace mlm {
@@ -244,94 +245,149 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_kernel(Gem
 }
 
 // 32 x 32 or 16 x 16 tile, 8 waves: wave w sums the w-th eighth of k (in chunks of 8 or 16) and the eight partial tiles are added in LDS,
-// in wave order.  With K = 256 it is one trip to memory, the reduction and the launch: what is asked for and never used, each
-// operation ahead of the first request and each instruction to be fetched counts.  A step is requested only where there is one, and
-// a chunk's address is the lane's plus a wave-uniform offset: against steps requested ahead whether or not the range has them, at
-// addresses computed chunk by chunk, 96 tiles of K = 256 6.6 -> 4.8 us, 32 of K = 768 with both operands k-contiguous 8.6 -> 5.0, the
-// four weight gradients below 10.4 -> 7.2 (a step of 256 tokens 265 -> 228 us).  Four steps in flight instead of two (212
-// registers, twice the code) 237.  From K = 512 on it is the matrix operations, 3.7 us per 1024 k of a tile on its compute unit: tiles of 16 x 16
-// where there are units for them (f32_split_tile_of; 64 tiles of K = 1024 6.7 -> 4.1 us, beside column sums 7.4 -> 4.9; 228 -> 209).
+// in wave order.  A wave copies its eighth, 16 k at a time, into LDS that only it reads, ahead of the products and without a barrier.
+// What bounds it is the intake of operands (a 32 x 32 tile asks for 16 flops a byte), and at few tiles the serial eighth of k.  A copy takes
+// 16 rows of 64 bytes, or whole k-rows: fragments loaded straight to registers have neighbouring lanes in different rows of a k-contiguous
+// operand, one cache line each (us, registers / LDS: 408 x 56 x 7744 with both k-contiguous 29.4 / 21.4, 256 x 512 x 2048 16.6 / 12.0; with one 15.2 /
+// 14.4; k-major 752 x 168 x 4504 34.5 / 26.6, 256 x 512 x 256 3.6 / 3.9; 69 products of 32 .. 32112 wide 8 % less in the mean, no sum changed).
+// Stages: two of a 32 x 32 tile leave room for two workgroups a unit; three or four, one workgroup, 2-6 % slower in the mean (504 x 1072 x 48
+// 4.8 / 6.3 / 6.2, 792 x 72 x 552 6.6 / 7.4 / 7.5, at best 5 % faster at 744 x 1040 x 696).  Four of a 16 x 16 tile: two cost 13 % at 160 x 104 x 7176.
 constexpr int kF32SplitWaves = 8;
-constexpr int kF32SplitStep = 4;        // chunks of 8 (16) k per step: 32 (64) k, whole 128-byte lines of a k-contiguous row
 
+// One operand's 16 k of a 32 (16) row tile: copies of 1 KB (lane t's 16 bytes at 16 t) and the fragments from there, four k of a row per lane and
+// chunk.  LDS positions are permuted on the global side, so that no read meets bank conflicts.
+template <bool KC, int TS> struct F32SplitOperand;
+template <int TS> struct F32SplitOperand<true, TS> {
+  static constexpr int NC = TS / 16;             // a copy: 16 rows of 64 bytes
+  const char* base;                              // the tile's first row (uniform)
+  uint32_t off[NC];                              // bytes from there (at most 31 rows of 2^24 floats)
+  int unit;                                      // this lane's first k of the 16
+  static __device__ __forceinline__ int sw(int row) { return -(row >> 2) & 3; }
+  __device__ __forceinline__ void init(const void* P, int ld, int row0, int nrows, int lane) {
+    base = (const char*)P + (size_t)row0 * ld * 4;
+    unit = ((lane & 3) ^ sw(lane >> 2)) * 4;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) off[c] = 4u * ((uint32_t)(min(row0 + 16 * c + (lane >> 2), nrows - 1) - row0) * (uint32_t)ld + unit);
+  }
+  __device__ __forceinline__ const char* at(int k, int c) const { return base + (size_t)k * 4 + off[c]; }
+  __device__ __forceinline__ int k_of(int) const { return unit; }
+  // k = CK q + 4 lh .. + 3 of row l (CK = 8, 16)
+  static __device__ __forceinline__ void frag(const unsigned char* lds, int q, int l, int lh, float (&f)[4]) {
+    const float4 v = *reinterpret_cast<const float4*>(lds + l * 64 + ((((256 / TS / 4) * q + lh) ^ sw(l & 15)) << 4));
+    f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+  }
+};
+template <int TS> struct F32SplitOperand<false, TS> {
+  static constexpr int U = TS / 4, KR = 64 / U, NC = 16 / KR;      // 16-byte units of a k-row, k-rows of a copy
+  const char* base;
+  uint32_t off[NC];
+  int kk[NC];                                    // this lane's k of the 16
+  // LDS row of k: the four (two) lane groups of a read, four k apart, meet different banks
+  static __device__ __forceinline__ int row_of(int k) { return k ^ ((k >> 2) & (TS == 32 ? 1 : 3)); }
+  int ld;
+  __device__ __forceinline__ void init(const void* P, int ld_, int row0, int nrows, int lane) {
+    ld = ld_;
+    base = (const char*)P + (size_t)row0 * 4;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      kk[c] = row_of(c * KR + lane / U);
+      off[c] = 4u * ((uint32_t)kk[c] * (uint32_t)ld + (min(row0 + lane % U * 4, nrows - 4) - row0));
+    }
+  }
+  __device__ __forceinline__ const char* at(int k, int c) const { return base + (size_t)k * ld * 4 + off[c]; }
+  __device__ __forceinline__ int k_of(int c) const { return kk[c]; }
+  static __device__ __forceinline__ void frag(const unsigned char* lds, int q, int l, int lh, float (&f)[4]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) f[j] = *reinterpret_cast<const float*>(lds + row_of((256 / TS) * q + 4 * lh + j) * (TS * 4) + l * 4);
+  }
+};
+// What a copy reads for k past the wave's last.
+static __device__ const uint4 f32_zero16 = {0u, 0u, 0u, 0u};
+
+template <int TS> constexpr int f32_split_stages() { return TS == 16 ? 4 : 2; }
+template <int TS> constexpr size_t f32_split_lds() { return (size_t)kF32SplitWaves * f32_split_stages<TS>() * TS * 128; }
 template <bool A_KC, bool B_KC, int EPI, int TS = 32>
 __device__ __forceinline__ void f32_split_tile(const GemmArgs& a, int tile) {
   // TS = 16: 16 x 16 tile, chunks of 16 k of which K is a multiple (f32_split_tile_of)
-  constexpr int NWV = kF32SplitWaves, CK = 256 / TS, ST = kF32SplitStep, NE = TS * TS / 64;
+  constexpr int NWV = kF32SplitWaves, CK = 256 / TS, NE = TS * TS / 64, ST = f32_split_stages<TS>();
   using acc_t = std::conditional_t<TS == 32, floatx16, floatx4>;
-  __shared__ float park[NWV][NE][64];
+  typedef F32SplitOperand<A_KC, TS> OA;
+  typedef F32SplitOperand<B_KC, TS> OB;
+  constexpr int STAGE = TS * 128, CPS = OA::NC + OB::NC;           // 16 k of both operands; copies
+  extern __shared__ __attribute__((aligned(16))) float lds_f32[];
   const int lane = threadIdx.x & 63, l32 = lane % TS, lh = lane / TS;      // (a lane's row; its four k of a chunk)
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tiles_m = (a.M + TS - 1) / TS;
   const int m0 = (tile % tiles_m) * TS, n0 = (tile / tiles_m) * TS;
-  const float* A = (const float*)a.A;
-  const float* B = (const float*)a.B;
-  const int rowA = min(m0 + l32, a.M - 1), rowB = min(n0 + l32, a.N - 1);
   const int nchunk = (a.K + CK - 1) / CK;
-  const int c0 = (int)((long)nchunk * wave / NWV), c1 = (int)((long)nchunk * (wave + 1) / NWV);
+  const int k0 = CK * (int)((long)nchunk * wave / NWV), k1 = min(CK * (int)((long)nchunk * (wave + 1) / NWV), a.K);
+  const int nk = (k1 - k0 + 15) >> 4;                              // (0: a wave without a chunk)
+  OA oa;
+  OB ob;
+  oa.init(a.A, a.lda, m0, a.M, lane);
+  ob.init(a.B, a.ldb, n0, a.N, lane);
+  unsigned char* ring = reinterpret_cast<unsigned char*>(lds_f32) + wave * (ST * STAGE);
+  const uint32_t ring0 = lds_offset_of(ring);
+  auto issue = [&](int i, int stage) {
+    const int k = k0 + 16 * i, left = k1 - k;
+    auto copies = [&](const auto& op, uint32_t to) {
+#pragma unroll
+      for (int c = 0; c < std::decay_t<decltype(op)>::NC; ++c) {
+        const bf16* src = reinterpret_cast<const bf16*>(op.at(k, c));
+        if (left < 16) src = op.k_of(c) < left ? src : reinterpret_cast<const bf16*>(&f32_zero16);
+        dma16(src, to + c * 1024);
+      }
+    };
+    copies(oa, ring0 + stage * STAGE);
+    copies(ob, ring0 + stage * STAGE + OA::NC * 1024);
+  };
   acc_t acc;
 #pragma unroll
   for (int e = 0; e < NE; ++e) acc[e] = 0.f;
-  float fa[2][ST][4], fb[2][ST][4];
-  // Only A k-contiguous: a step takes 128 bytes of each of A's 32 rows in four requests, and the lines of the eight waves' steps are the whole
-  // L1 cache, so the four go out in a run, behind B's.  (A test per chunk, true in the loop, keeps the compiler from spreading them between
-  // the products.)  Chunk by chunk / in a run: 160 x 104 x 7176 69 / 54 us, 1176 x 72 x 3800 40 / 32, 208 x 1056 x 2200 25 / 21, 384 x 232 x 1176 13.2 /
-  // 11.6, 256^3 4.3 both.  The other layouts take a step chunk by chunk: both operands k-major 160 x 104 x 7176 52 / 59, 752 x 168 x 4504 35 / 40.
-  constexpr bool MIXED = A_KC && !B_KC;
-  // The chunks that lie inside [0, K): all but the last one of a weight gradient, whose k counts tokens
-  const int cw = A_KC || B_KC || TS == 16 ? c1 : min(c1, a.K / CK);
-  auto steps = [&](auto load) {
-    auto multiply = [&](int buf, int n) {
 #pragma unroll
-      for (int q = 0; q < ST; ++q)
-        if (q < n) {                                             // wave-uniform
+  for (int i = 0; i < ST; ++i)
+    if (i < nk) issue(i, i);
+  int stage = 0;
+  for (int i = 0; i < nk; ++i) {
+    // (copies return in order: those of the stages behind this one may be under way)
+    const int behind = nk - 1 - i;
+    if (behind >= ST - 1) wait_vmcnt<(ST - 1) * CPS>();
+    else if (ST > 3 && behind == 2) wait_vmcnt<2 * CPS>();
+    else if (ST > 2 && behind == 1) wait_vmcnt<CPS>();
+    else wait_vmcnt<0>();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");                                 // (no fragment is read ahead of the wait)
+    const unsigned char* st = ring + stage * STAGE;
+    float fa[16 / CK][4], fb[16 / CK][4];
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if constexpr (TS == 32) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[buf][q][j], fb[buf][q][j], acc, 0, 0, 0);
-            else acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[buf][q][j], fb[buf][q][j], acc, 0, 0, 0);
-        }
-    };
-    int c = c0;
-    load(0, c);
-    for (; c + 2 * ST < cw; c += 2 * ST) {
-      load(1, c + ST);
-      multiply(0, MIXED ? cw - c : ST);
-      load(0, c + 2 * ST);
-      multiply(1, MIXED ? cw - c - ST : ST);
+    for (int q = 0; q < 16 / CK; ++q) {
+      OA::frag(st, q, l32, lh, fa[q]);
+      OB::frag(st + OA::NC * 1024, q, l32, lh, fb[q]);
     }
-    // (one or two steps are left, the first of them requested; a short k has no others, and nothing past it is requested)
-    const bool two = c + ST < cw;
-    if (two) load(1, c + ST);
-    multiply(0, cw - c);
-    if (two) multiply(1, cw - c - ST);
-  };
-  // (chunks past this wave's range: its last one again, not multiplied)
-  if (c0 < cw) {
-    const F32Lane<A_KC> la(A, a.lda, rowA, lh);
-    const F32Lane<B_KC> lb(B, a.ldb, rowB, lh);
-    steps([&](int buf, int c) {
-      if (MIXED) {
-#pragma unroll
-        for (int q = 0; q < ST; ++q) lb.load(CK * min(c + q, cw - 1), fb[buf][q]);
-      }
-#pragma unroll
-      for (int q = 0; q < ST; ++q) {
-        la.load(CK * min(c + q, cw - 1), fa[buf][q]);
-        if (!MIXED) lb.load(CK * min(c + q, cw - 1), fb[buf][q]);
-      }
-    });
-  }
-  if constexpr (!A_KC && !B_KC && TS == 32) {
-    // (by itself: the wave that has it took all of its chunks row by row before, 720 x 80 over 4063 tokens in four times the time of 4064)
-    if (cw < c1) {
-      f32_frag_global<A_KC>(A, a.lda, rowA, CK * cw + 4 * lh, a.K, fa[0][0]);
-      f32_frag_global<B_KC>(B, a.ldb, rowB, CK * cw + 4 * lh, a.K, fb[0][0]);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[0][0][j], fb[0][0][j], acc, 0, 0, 0);
+    if (behind >= ST) {
+      __builtin_amdgcn_s_waitcnt(0xC07F);                          // lgkmcnt(0): the stage's fragments are in registers
+      __builtin_amdgcn_sched_barrier(0);
+      issue(i + ST, stage);
     }
-  }
+    stage = stage == ST - 1 ? 0 : stage + 1;
 #pragma unroll
-  for (int e = 0; e < NE; ++e) park[wave][e][lane] = acc[e];
+    for (int q = 0; q < 16 / CK; ++q)
+      if (q == 0 || k1 - k0 - 16 * i > 8) {                        // wave-uniform
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if constexpr (TS == 32) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[q][j], fb[q][j], acc, 0, 0, 0);
+          else acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[q][j], fb[q][j], acc, 0, 0, 0);
+      }
+  }
+  asm volatile("" ::: "memory");
+  // parked over the wave's own stages, nobody else's: [value][lane]
+  constexpr int RING = ST * STAGE / 4;
+  static_assert(NE * 64 <= RING, "a partial tile fits the stages");
+  {
+    float* park = lds_f32 + wave * RING + lane;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) park[e * 64] = acc[e];
+  }
   __syncthreads();
   // wave w finishes the tile's values e = 2 w, 2 w + 1 (e = w of the four of a 16 x 16 tile)
   constexpr int PER = NE >= NWV ? NE / NWV : 1;
@@ -343,7 +399,7 @@ __device__ __forceinline__ void f32_split_tile(const GemmArgs& a, int tile) {
     const int e = wave * PER + q;
     float v = 0.f;
 #pragma unroll
-    for (int p = 0; p < NWV; ++p) v += park[p][e][lane];
+    for (int p = 0; p < NWV; ++p) v += lds_f32[p * RING + e * 64 + lane];
     const int m = m0 + 8 * (e >> 2) + 4 * lh + (e & 3);
     if (m < a.M) f32_put<EPI>(a, f32_row<EPI>(a, m), m, n, bias, v);
   }
@@ -354,8 +410,8 @@ __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_kernel(Gem
   f32_split_tile<A_KC, B_KC, EPI, TS>(a, blockIdx.x);
 }
 
-// The tiles of several weight gradients in one launch: such a GEMM takes 6 us whatever its size, and nothing waits for the
-// four of a layer shard one by one (four launches of 256 x {256, 512} x 256: 24 -> 11 us in one, 7.2 now).
+// The tiles of several weight gradients in one launch: such a GEMM takes 3-6 us whatever its size, and nothing waits for the
+// four of a layer shard one by one (four launches of 256 x {256, 512} x 256: 24 -> 11 us in one, 6.9 now).
 __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_group_kernel(F32Group g) {
   GemmArgs a;
   const int tile = f32_group_at(g, blockIdx.x, &a);
@@ -369,7 +425,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_group_kern
 }
 
 // A weight gradient (its tiles first) and an input gradient that do not depend on each other: 256 x 512 x 256 and 256 x 256 x 512
-// take 8.2 us together, 14 in two launches.
+// take 5.9 us together.  (From registers 8.2, and 14 in two launches.)
 template <int TS>
 __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_dual_kernel(GemmArgs w, GemmArgs x) {
   const int tiles_w = ((w.M + 31) / 32) * ((w.N + 31) / 32), id = blockIdx.x;
@@ -391,10 +447,11 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_tile_dual_kernel(GemmArgs w, 
 // 1264 us a step.
 template <int TS>
 __global__ __launch_bounds__(64 * kF32SplitWaves) void gemm_f32_split_colsum_kernel(GemmArgs a, ColsumJob job) {
-  __shared__ float red[colsum_lds_floats<float, 64 * kF32SplitWaves>()];
+  extern __shared__ __attribute__((aligned(16))) float lds_f32[];
+  static_assert(colsum_lds_floats<float, 64 * kF32SplitWaves>() * sizeof(float) <= f32_split_lds<TS>(), "column sums' LDS");
   const int tiles = ((a.M + TS - 1) / TS) * ((a.N + TS - 1) / TS), id = blockIdx.x;
   if (id < tiles) f32_split_tile<true, true, EPI_STORE, TS>(a, id);
-  else colsum_block<float, 64 * kF32SplitWaves>(job, id - tiles, red);
+  else colsum_block<float, 64 * kF32SplitWaves>(job, id - tiles, lds_f32);
 }
 template <int BM, int BN, int WM, int WN, int KS, int KT>
 __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_colsum_kernel(GemmArgs a, ColsumJob job, int tiles) {
@@ -402,6 +459,30 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_colsum_ker
   const int id = blockIdx.x;
   if (id < tiles) f32_tile<true, true, EPI_STORE, BM, BN, WM, WN, KS, KT>(a, id);
   else colsum_block<float, 64 * WM * WN * KS>(job, id - tiles, lds_f32);
+}
+
+// Launch of a kernel of f32_split_tile
+template <int TS, typename Kernel, typename... Args>
+static hipError_t launch_f32_split(LdsAttrOnce* attr, Kernel kern, dim3 grid, hipStream_t st, const Args&... args) {
+  if (f32_split_lds<TS>() > 64 * 1024)
+    if (hipError_t e = attr->ensure((const void*)kern, (int)f32_split_lds<TS>()); e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, grid, dim3(64 * kF32SplitWaves), (f32_split_lds<TS>()), st, args...);
+  return hipGetLastError();
+}
+template <bool A_KC, bool B_KC, int EPI, int TS>
+static hipError_t launch_f32_split_alone(const GemmArgs& a, hipStream_t st) {
+  static LdsAttrOnce attr;
+  return launch_f32_split<TS>(&attr, gemm_f32_split_kernel<A_KC, B_KC, EPI, TS>, dim3(((a.M + TS - 1) / TS) * ((a.N + TS - 1) / TS)), st, a);
+}
+template <int TS>
+static hipError_t launch_f32_split_colsum(const GemmArgs& a, const ColsumJob& j, hipStream_t st) {
+  static LdsAttrOnce attr;
+  return launch_f32_split<TS>(&attr, gemm_f32_split_colsum_kernel<TS>, dim3(((a.M + TS - 1) / TS) * ((a.N + TS - 1) / TS) + j.blocks), st, a, j);
+}
+template <int TS>
+static hipError_t launch_f32_split_dual(const GemmArgs& w, const GemmArgs& x, int tiles_w, hipStream_t st) {
+  static LdsAttrOnce attr;
+  return launch_f32_split<32>(&attr, gemm_f32_split_dual_kernel<TS>, dim3(tiles_w + ((x.M + TS - 1) / TS) * ((x.N + TS - 1) / TS)), st, w, x);
 }
 
 // LDS of a workgroup of f32_tile
@@ -451,13 +532,9 @@ template <bool A_KC, bool B_KC, int EPI>
 static hipError_t launch_f32_layout(const GemmArgs& a, hipStream_t st) {
   if (const int bt = f32_pieces_pick(a.M, a.N, a.K)) return launch_f32_pieces(a, bt, st);
   switch (f32_pick(a.M, a.N, a.K)) {
-    case 32: {
-      const int ts = f32_split_tile_of(a.M, a.N, a.K);
-      const dim3 tiles(((a.M + ts - 1) / ts) * ((a.N + ts - 1) / ts)), block(64 * kF32SplitWaves);
-      if (ts == 16) hipLaunchKernelGGL((gemm_f32_split_kernel<A_KC, B_KC, EPI, 16>), tiles, block, 0, st, a);
-      else hipLaunchKernelGGL((gemm_f32_split_kernel<A_KC, B_KC, EPI, 32>), tiles, block, 0, st, a);
-      return hipGetLastError();
-    }
+    case 32:
+      return f32_split_tile_of(a.M, a.N, a.K) == 16 ? launch_f32_split_alone<A_KC, B_KC, EPI, 16>(a, st)
+                                                    : launch_f32_split_alone<A_KC, B_KC, EPI, 32>(a, st);
     case 64: return launch_f32_tile<A_KC, B_KC, EPI, 64, 64, 2, 2, 2, 64>(a, st);
     default: return launch_f32_tile<A_KC, B_KC, EPI, 128, 128, 2, 2, 1, 32>(a, st);
   }
@@ -515,8 +592,8 @@ hipError_t launch_gemm_f32_wgrads(const GemmArgs* all, int n_all, hipStream_t st
     if (b == 128) return launch_f32_tile_group<128, 128, 2, 2, 1, 32, 1>(g, total, st);
     if (b == 64) return chains == 8 ? launch_f32_tile_group<64, 64, 2, 2, 2, 64, 4>(g, total, st)
                                     : launch_f32_tile_group<64, 64, 2, 2, 2, 64, 1>(g, total, st);
-    hipLaunchKernelGGL(gemm_f32_split_group_kernel, dim3(total), dim3(64 * kF32SplitWaves), 0, st, g);
-    return hipGetLastError();
+    static LdsAttrOnce attr;
+    return launch_f32_split<32>(&attr, gemm_f32_split_group_kernel, dim3(total), st, g);
   };
   if (p.wide_apart)
     if (hipError_t e = launch(128, 1, true, false); e != hipSuccess) return e;
@@ -530,13 +607,7 @@ hipError_t launch_gemm_f32_wgrads(const GemmArgs* all, int n_all, hipStream_t st
 hipError_t launch_gemm_f32_dgrad_colsum(const GemmArgs& a, const ColsumJob& j, hipStream_t st) {
   if (const int bt = f32_pieces_pick(a.M, a.N, a.K)) return launch_f32_pieces_colsum(a, j, bt, st);
   switch (f32_pick(a.M, a.N, a.K)) {
-    case 32: {
-      const int ts = f32_split_tile_of(a.M, a.N, a.K);
-      const dim3 grid(((a.M + ts - 1) / ts) * ((a.N + ts - 1) / ts) + j.blocks), block(64 * kF32SplitWaves);
-      if (ts == 16) hipLaunchKernelGGL(gemm_f32_split_colsum_kernel<16>, grid, block, 0, st, a, j);
-      else hipLaunchKernelGGL(gemm_f32_split_colsum_kernel<32>, grid, block, 0, st, a, j);
-      return hipGetLastError();
-    }
+    case 32: return f32_split_tile_of(a.M, a.N, a.K) == 16 ? launch_f32_split_colsum<16>(a, j, st) : launch_f32_split_colsum<32>(a, j, st);
     case 64: return launch_f32_tile_colsum<64, 64, 2, 2, 2, 64>(a, j, st);
     default: return launch_f32_tile_colsum<128, 128, 2, 2, 1, 32>(a, j, st);
   }
@@ -563,11 +634,7 @@ hipError_t launch_gemm_f32_dual(const GemmArgs& w, const GemmArgs& x, hipStream_
   auto tiles = [b](const GemmArgs& a) { return ((a.M + b - 1) / b) * ((a.N + b - 1) / b); };
   const dim3 grid(tiles(w) + tiles(x));
   if (b == 32) {
-    const int ts = f32_split_tile_of(x.M, x.N, x.K);
-    const dim3 both(tiles(w) + ((x.M + ts - 1) / ts) * ((x.N + ts - 1) / ts));
-    if (ts == 16) hipLaunchKernelGGL(gemm_f32_split_dual_kernel<16>, both, dim3(64 * kF32SplitWaves), 0, st, w, x);
-    else hipLaunchKernelGGL(gemm_f32_split_dual_kernel<32>, both, dim3(64 * kF32SplitWaves), 0, st, w, x);
-    return hipGetLastError();
+    return f32_split_tile_of(x.M, x.N, x.K) == 16 ? launch_f32_split_dual<16>(w, x, tiles(w), st) : launch_f32_split_dual<32>(w, x, tiles(w), st);
   }
   return p.chains == 8 ? launch_f32_tile_dual<4>(w, x, grid, st) : launch_f32_tile_dual<1>(w, x, grid, st);
 }

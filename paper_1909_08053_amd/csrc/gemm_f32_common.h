@@ -80,32 +80,6 @@ __device__ __forceinline__ void f32_frag_global(const float* __restrict__ P, int
   }
 }
 
-// The same for chunks that lie inside [0, K): four k, from k0 + 4 lh on, of one row.  What differs between lanes is computed once; a
-// chunk, whose first k is k0, adds a wave-uniform offset.
-template <bool KC> struct F32Lane;
-template <> struct F32Lane<true> {
-  const float* p;
-  __device__ __forceinline__ F32Lane(const float* P, int ld, int row, int lh) : p(P + (size_t)row * ld + 4 * lh) {}
-  __device__ __forceinline__ void load(int k0, float (&f)[4]) const {
-    const float4 v = *reinterpret_cast<const float4*>(p + k0);
-    f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
-  }
-};
-template <> struct F32Lane<false> {
-  const float* P;
-  size_t ld;
-  uint32_t ofs[4];                       // bytes from the chunk's first k (at most fifteen k of at most 2^24 floats)
-  __device__ __forceinline__ F32Lane(const float* P_, int ld_, int row, int lh) : P(P_), ld(ld_) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) ofs[j] = 4u * ((uint32_t)(4 * lh + j) * ld_ + row);
-  }
-  __device__ __forceinline__ void load(int k0, float (&f)[4]) const {
-    const char* chunk = reinterpret_cast<const char*>(P + (size_t)k0 * ld);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) f[j] = *reinterpret_cast<const float*>(chunk + ofs[j]);
-  }
-};
-
 // The problems of a launch that holds several.
 constexpr int kF32Group = 4;
 struct F32Group {

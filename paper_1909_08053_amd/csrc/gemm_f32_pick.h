@@ -29,8 +29,8 @@ inline double f32_tile_us(int b, double t, int K) {
 }
 inline double f32_split_us(int M, int N, int K) { return 3.0 + 6.0 * (K / 1024.0) + 2.0 * M * N * K / 52e6; }
 // Tile of the split kernel.  The matrix operations of a 32 x 32 tile take one compute unit 3.7 us per 1024 k, and few such tiles leave units
-// idle: 16 x 16 where those find a unit each (256 x 256, 32 / 16: K = 128 4.0 / 3.6 us, 1024 6.7 / 4.2; below 128 k nothing to
-// gain), or, at longer k, two a unit (256 x 512: K = 512 7.2 / 5.7 us, 1024 11.5 / 9.0, 2048 19.8 / 15.6, but 256 4.7 / 5.3: twice the
+// idle: 16 x 16 where those find a unit each (256 x 256, 32 / 16: K = 128 3.1 / 2.5 us, 1024 9.5 / 5.4; below 128 k nothing to
+// gain), or, at longer k, two a unit (256 x 512: K = 512 6.3 / 5.2 us, 1024 9.7 / 8.0, 2048 15.9 / 13.2, 256 3.8 / 3.8: twice the
 // operands are fetched).  A 16 x 16 tile sums in chunks of 16 k, in eight chains like the other; short k only where they are of one
 // length (a longest chain of 32 k in place of 24 at K = 192 is 4 % further off; from 512 k on uneven ones differ by 0.4 % at most).
 inline int f32_split_tile_of(int M, int N, int K) {
