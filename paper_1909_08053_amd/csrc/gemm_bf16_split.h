@@ -394,7 +394,9 @@ inline SplitPick split_pick(int M, int N, int K, double than, bool wide = false)
 template <bool A_KC, bool B_KC, int EPI>
 SplitPick split_pick_alone(int M, int N, int K, bool allow_split) {
   const V2Plan p = v2_plan(M, N, K, allow_split, v2_pick_bn<A_KC, B_KC, EPI>(M, N, K, allow_split));
-  return split_pick(M, N, K, v2_few_us(p, K), EPI == EPI_CE);
+  double us = v2_few_us(p, K);
+  if (v2_has_middle<A_KC, B_KC, EPI>() && v2_middle(M, N, K)) us = v2_middle_plan(M, N, K).cost;
+  return split_pick(M, N, K, us, EPI == EPI_CE);
 }
 
 // Weight gradients of one K in one launch of these tiles, against the launch or launches of the plan p.  (Only where 128-wide tiles would

@@ -36,8 +36,8 @@ namespace mlm {
 constexpr int V2_B = 256;                   // block tile edge (M and N)
 constexpr int V2_BK = 32;                   // k per stage
 constexpr int V2_SMALL = 128;               // block tile edge of the small tile
-// rows of the block tile by its width
-template <int BN> constexpr int v2_bm() { return BN == V2_SMALL ? V2_SMALL : V2_B; }
+// rows of the block tile by its width (192 and DEEP: the middle tile, 128 x 192)
+template <int BN, bool DEEP> constexpr int v2_bm() { return BN == V2_SMALL || (BN == 192 && DEEP) ? V2_SMALL : V2_B; }
 // DEEP: the small tile in a launch of at most one workgroup per compute unit.  It has to hide its latencies by itself, so it
 // runs 8 waves (two per SIMD) of 32 x 64 and, where a pair of slices arrives at once (a k-contiguous operand), keeps eight
 // slices in its ring; in larger launches two workgroups share a compute unit, and 4 waves of 64 x 64 read a third less from
@@ -49,10 +49,13 @@ inline int v2_slices(int K) { return 2 * ((K + 2 * V2_BK - 1) / (2 * V2_BK)); } 
 // How K ends: KE_PAIR on a whole pair of slices; KE_SLICE on the first slice of a pair (K an odd multiple of 32; the large tiles'
 // kernels: with KE_ANY they are 4-8 % slower at 8192 x 3072 x 1568, and KE_PAIR's with this form's arithmetic 0.7-1 %); KE_ANY.
 enum { KE_PAIR, KE_SLICE, KE_ANY };
-template <int BN> int v2_k_end(int K) {
+template <int BN, bool DEEP = false> int v2_k_end(int K) {
   if (K % (2 * V2_BK) == 0) return KE_PAIR;
-  return BN != V2_SMALL && K % V2_BK == 0 && K >= 2 * V2_BK ? KE_SLICE : KE_ANY;
+  return BN != V2_SMALL && !DEEP && K % V2_BK == 0 && K >= 2 * V2_BK ? KE_SLICE : KE_ANY;
 }
+// an n-contiguous B of 192 columns is copied pair by pair like a k-contiguous operand: 24 copies among eight waves, where a slice's 12 are two a
+// wave, a quarter of them twice
+template <int BN, bool DEEP> constexpr bool v2_pair_b() { return BN == 192 && DEEP; }
 template <bool A_KC, bool B_KC, bool DEEP> constexpr int v2_stages() { return DEEP && (A_KC || B_KC) ? 8 : 4; }
 // A's ring, then B's ring: 128 KB for a 256 x 256 tile, 64 KB (128 KB DEEP) for a 128 x 128 one
 constexpr size_t v2_ring_bytes(int bm, int bn, int stages) { return (size_t)stages * V2_BK * 2 * (bm + bn); }
@@ -105,15 +108,16 @@ __device__ __forceinline__ int v2_kc_swizzle(int row) { return (row >> 1) & 7; }
 //  * operand contiguous along m / n (MN): a slice is [32 k][256 rows] = 512 bytes per k, QPW copies per slice.
 // ANY_K (KE_ANY): units past K are read from v2_zero16.  A template parameter: the compare and select per copy cost 2-4 % of a
 // large GEMM.
-template <bool KC, int NP_, bool ANY_K, int ROWS>
+// PR: copied pair by pair, as every KC operand is.
+template <bool KC, bool PR, int NP_, bool ANY_K, int ROWS>
 struct V2Src {
-  static constexpr int NP = NP_;       // KC: 1-KB copies per wave and PAIR (rows / (8 waves)); MN: per wave and slice
+  static constexpr int NP = NP_;       // PR: 1-KB copies per wave and PAIR (rows / (8 waves)); else per wave and slice
   // MN: a slice is ROWS / 16 one-KB copies; where that is no multiple of the wave count (192 rows: 12 copies, 8
   // waves x 2) the surplus copies repeat the last one (same source, same destination: harmless, keeps the per-wave
   // copy count -- and with it the vmcnt bookkeeping -- uniform)
-  static constexpr int LAST = KC ? (1 << 20) : ROWS / 16 - 1;
+  static constexpr int LAST = PR ? (1 << 20) : ROWS / 16 - 1;
   const bf16* p[NP];
-  int kofs[NP];    // k of this lane's unit inside the pair (KC) / slice (MN)
+  int kofs[NP];    // k of this lane's unit inside the pair (PR) / slice
   int kleft;       // K - k_begin: units with k >= kleft are zeros
   size_t step;     // elements to advance per 32-deep k-slice
   __device__ __forceinline__ void init(const bf16* P, int ld, int row0, int nrows, int k_begin, int K, int wave, int lane) {
@@ -131,7 +135,7 @@ struct V2Src {
 #pragma unroll
       for (int q = 0; q < NP; ++q) {
         const int g = 64 * min(wave * NP + q, LAST) + lane;      // linear 16-byte unit of the slice buffer
-        const int k = g / (ROWS / 8);
+        const int k = g / (ROWS / 8);                            // (PR: the pair's two buffers follow one another)
         const int u = v2_mn_chunk<ROWS>(g % (ROWS / 8), k);
         kofs[q] = k;
         p[q] = P + (size_t)(k_begin + k) * ld + min(row0 + u * 8, nrows - 8);
@@ -181,7 +185,7 @@ __device__ __forceinline__ bf16x8 v2_frag16(const unsigned char* ring, int stage
 
 struct V2Plan {
   int tiles_m, tiles_n, full_tiles, tail_tiles, split;   // grid = full_tiles + tail_tiles * split
-  int bm, bn;                                             // tile: 256 x 256, 256 x 192 or 128 x 128
+  int bm, bn;                                             // tile: 256 x 256, 256 x 192, 128 x 192 or 128 x 128
   int window, strip, long_pieces;                         // walk over the tiles (v2_xcd_order, v2_tile_of; v2_set_walk)
   double cost;                                            // estimated kernel time in microseconds (host side only)
   int grid() const { return full_tiles + tail_tiles * split; }
@@ -337,6 +341,8 @@ inline double v2_tile_cost(int bn, int nk, bool alone, double small_slice) {
 }
 inline double v2_fixup_cost(double traffic_us) { return 3.0 + 0.6 * traffic_us; }
 
+int gemm_v2_forced_bn();                    // MLM_GEMM_BN=128|192|256 forces a tile width where it exists, else 0
+
 // Decide whether, and how far, to split the last partial round along k.  Cost model in microseconds: a tile costs
 // its fixed part + the per-slice cost of its k-slices; the pieces write fp32 partial tiles at ~5 TB/s and the fix-up
 // kernel reads them back.
@@ -372,6 +378,31 @@ inline V2Plan v2_plan(int M, int N, int K, bool allow_split, int bn = V2_B) {
   return p;
 }
 
+// The middle tile, 128 x 192 in eight waves of 32 x 96 with an eight-slice ring, one workgroup per compute unit: where it gives every unit
+// at most one tile and the small tile would give some units two, the others one or none at that one's pace.  Small (or what the plan
+// took) / middle, us: fwd 3000 x 1536 x 1536 23.1 / 21.3, 8192 x 768 x 1536 24.6 / 23.1, 8192 x 576 x 1536 22.4 / 20.4, 7168 x 640 x 2560 33.3 / 30.1,
+// 2352 x 1792 x 1728 29.9 / 20.8, 3448 x 1216 x 10944 197 / 114; dgrad 3000 x 1536 x 1536 22.0 / 19.7, 6152 x 696 x 648 20.2 / 15.2, 4416 x 1200 x 3304 71 / 55; of 64 such
+// products of K = 192 on one is 1 % slower, the mean 1.17 (of 36 of K = 3352 .. 15864 1.40, the least 1.04); the ring's fill decides below (5256 x 1016 x 48 6.8 / 7.3, 28 of 40 .. 184 0.93 .. 1.05).  Not beyond one tile a unit (4096 x 1920 x 2560, 320 tiles, 40 / 59; 8192 x 3072 x 1536, 1024, 73 / 93), and
+// where the small tile has one a unit as well that is shorter (1024 x 3840 x 1920 19.5 / 23.4).  Per 32-deep slice 0.33 us, 60 GB/s of operands
+// a unit.
+inline int v2_middle_tiles(int M, int N) { return ((M + V2_SMALL - 1) / V2_SMALL) * ((N + 191) / 192); }
+inline bool v2_middle(int M, int N, int K) {
+  const int cus = gemm_cu_count();
+  return K >= 192 && !gemm_v2_forced_bn() && v2_middle_tiles(M, N) <= cus && ((M + V2_SMALL - 1) / V2_SMALL) * ((N + V2_SMALL - 1) / V2_SMALL) > cus;
+}
+inline V2Plan v2_middle_plan(int M, int N, int K) {
+  const int tm = (M + V2_SMALL - 1) / V2_SMALL, tn = (N + 191) / 192;
+  V2Plan p = {};
+  p.tiles_m = tm;
+  p.tiles_n = tn;
+  p.full_tiles = tm * tn;
+  p.split = 1;
+  p.bm = V2_SMALL;
+  p.bn = 192;
+  p.cost = 6.0 + 0.33 * v2_slices(K);
+  return p;
+}
+
 // One work item (pid) of one GEMM: the body of the kernels below.
 // BN = 256: 2 x 4 waves of 128 x 64.  BN = 192: 4 x 2 waves of 64 x 96 -- a tile count of 32 x (N / 192) fills the 256 CUs
 // where N / 256 column tiles leave a quarter of them idle (N = 1536: 256 tiles instead of 192) or a half-empty second
@@ -388,12 +419,13 @@ template <bool A_KC, bool B_KC, int EPI, int BN, int KE, bool DEEP, bool PIECES 
 __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Plan& plan, float* splitk_ws, int pid,
                                                   unsigned char* lds_raw) {
   static_assert(BN == V2_B || BN == 192 || BN == V2_SMALL, "tile widths");
-  constexpr int NW = v2_nw<BN, DEEP>(), BM = v2_bm<BN>(), ST = v2_stages<A_KC, B_KC, DEEP>();
+  constexpr int NW = v2_nw<BN, DEEP>(), BM = v2_bm<BN, DEEP>(), ST = v2_stages<A_KC, B_KC, DEEP>();
   constexpr int WAVES_M = v2_waves_m<BN, DEEP>(), WAVES_N = NW / WAVES_M;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   constexpr int OPB_A = BM * V2_BK * 2, OPB_B = BN * V2_BK * 2;   // bytes of one k-slice of either operand
+  constexpr bool A_PR = A_KC, B_PR = B_KC || v2_pair_b<BN, DEEP>();
   // 1-KB copies per wave: per pair of slices for a k-contiguous operand, per slice otherwise
-  constexpr int NPA = A_KC ? BM / (8 * NW) : BM / 16 / NW, NPB = B_KC ? BN / (8 * NW) : (BN / 16 + NW - 1) / NW;
+  constexpr int NPA = A_PR ? BM / (8 * NW) : BM / 16 / NW, NPB = B_PR ? BN / (8 * NW) : (BN / 16 + NW - 1) / NW;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
 
@@ -421,8 +453,8 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   const int nk = kt_end - kt_begin;                  // even, >= 2
 
-  V2Src<A_KC, NPA, KE == KE_ANY, BM> sa;
-  V2Src<B_KC, NPB, KE == KE_ANY, BN> sb;
+  V2Src<A_KC, A_PR, NPA, KE == KE_ANY, BM> sa;
+  V2Src<B_KC, B_PR, NPB, KE == KE_ANY, BN> sb;
   sa.init((const bf16*)a.A, a.lda, m0, a.M, kt_begin * V2_BK, a.K, wave, lane);
   sb.init((const bf16*)a.B, a.ldb, n0, a.N, kt_begin * V2_BK, a.K, wave, lane);
 
@@ -430,7 +462,7 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
   const unsigned char* ringA = lds_raw;
   const unsigned char* ringB = lds_raw + ST * OPB_A;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  constexpr int NKC = (A_KC ? 1 : 0) + (B_KC ? 1 : 0), NMN = 2 - NKC;
+  constexpr int NKC = (A_PR ? 1 : 0) + (B_PR ? 1 : 0), NMN = 2 - NKC;
   // Four slices are always in flight or landed; past the end of k the last pair / slice is fetched again into a
   // stage nobody reads (keeps the vmcnt bookkeeping and the instruction stream free of tail cases).  Issue order of
   // the initial fill = the order the steady state would have produced: pair 0, slices 0 1, pair 1, slices 2 3.
@@ -443,12 +475,12 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
   auto slice_of = [&](int ks) { return ks - (ks >= nk - 2 ? shift : 0); };
 #pragma unroll
   for (int h = 0; h < ST / 2; ++h) {
-    if (A_KC) sa.issue(ldsA + h * 2 * OPB_A, wave_u, pair_of(min(h, last_pair)));
-    if (B_KC) sb.issue(ldsB + h * 2 * OPB_B, wave_u, pair_of(min(h, last_pair)));
+    if (A_PR) sa.issue(ldsA + h * 2 * OPB_A, wave_u, pair_of(min(h, last_pair)));
+    if (B_PR) sb.issue(ldsB + h * 2 * OPB_B, wave_u, pair_of(min(h, last_pair)));
 #pragma unroll
     for (int s = 2 * h; s < 2 * h + 2; ++s) {
-      if (!A_KC) sa.issue(ldsA + s * OPB_A, wave_u, slice_of(min(s, last_slice)));
-      if (!B_KC) sb.issue(ldsB + s * OPB_B, wave_u, slice_of(min(s, last_slice)));
+      if (!A_PR) sa.issue(ldsA + s * OPB_A, wave_u, slice_of(min(s, last_slice)));
+      if (!B_PR) sb.issue(ldsB + s * OPB_B, wave_u, slice_of(min(s, last_slice)));
     }
   }
   // The operand registers of what is multiplied next are read from LDS while the matrix cores work.  The slice hand-over sits inside
@@ -461,8 +493,8 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
   // (pairs first).  Copies return in order, so "slice kt+1 has landed" is a bound on the copies still outstanding:
   //   even kt: everything up to the hand-over of kt+1-ST must be done        -> ST - 2 hand-overs outstanding
   //   odd kt:  the pair issued first at the hand-over of kt+2-ST must be done -> that hand-over's slice and ST - 3 more
-  constexpr int C_SLICE = (A_KC ? 0 : NPA) + (B_KC ? 0 : NPB);     // copies per wave that re-arm a slice stage
-  constexpr int C_PAIR = (A_KC ? NPA : 0) + (B_KC ? NPB : 0);      // copies per wave that re-arm a pair stage
+  constexpr int C_SLICE = (A_PR ? 0 : NPA) + (B_PR ? 0 : NPB);     // copies per wave that re-arm a slice stage
+  constexpr int C_PAIR = (A_PR ? NPA : 0) + (B_PR ? NPB : 0);      // copies per wave that re-arm a pair stage
   constexpr int EV = C_SLICE, OD = C_PAIR + C_SLICE;
   constexpr int W_INIT = (ST - 1) * C_SLICE + (ST / 2 - 1) * C_PAIR, W_EVEN = (ST / 2 - 1) * (EV + OD);
   constexpr int W_ODD = NKC > 0 ? (ST / 2) * EV + (ST / 2 - 2) * OD : W_EVEN;
@@ -538,8 +570,8 @@ __device__ __forceinline__ void gemm_v2_work_item(const GemmArgs& a, const V2Pla
           if (HO + 1 + (c * NAFTER) / (NC > 0 ? NC : 1) != idx) continue;   // copy c goes after MFMA HO + 1 + (c NAFTER) / NC
           // order: A's pair, B's pair (odd slices only), then A's slice, B's slice
           int r = c;
-          constexpr int KA = (PAR == 1 && A_KC) ? NPA : 0, KB = (PAR == 1 && B_KC) ? NPB : 0;
-          constexpr int MA = A_KC ? 0 : NPA;
+          constexpr int KA = (PAR == 1 && A_PR) ? NPA : 0, KB = (PAR == 1 && B_PR) ? NPB : 0;
+          constexpr int MA = A_PR ? 0 : NPA;
           if (r < KA) { sa.issue_one(ldsA + pair_off_a, wave_u, pair_idx, r); continue; }
           r -= KA;
           if (r < KB) { sb.issue_one(ldsB + pair_off_b, wave_u, pair_idx, r); continue; }
@@ -746,8 +778,8 @@ __global__ __launch_bounds__(256) void gemm_v2_fixup_kernel(GemmArgs a, V2Plan p
 // the rings or the epilogue's staging strips + reduction area, whichever is larger
 template <bool A_KC, bool B_KC, int BN, bool DEEP> constexpr size_t v2_lds_bytes() {
   constexpr int WAVES_M = v2_waves_m<BN, DEEP>();
-  constexpr size_t kEpi = GemmTile<v2_bm<BN>(), BN, WAVES_M, v2_nw<BN, DEEP>() / WAVES_M>::LDS_EPI;
-  constexpr size_t kRing = v2_ring_bytes(v2_bm<BN>(), BN, v2_stages<A_KC, B_KC, DEEP>()), kLds = kRing > kEpi ? kRing : kEpi;
+  constexpr size_t kEpi = GemmTile<v2_bm<BN, DEEP>(), BN, WAVES_M, v2_nw<BN, DEEP>() / WAVES_M>::LDS_EPI;
+  constexpr size_t kRing = v2_ring_bytes(v2_bm<BN, DEEP>(), BN, v2_stages<A_KC, B_KC, DEEP>()), kLds = kRing > kEpi ? kRing : kEpi;
   static_assert(kLds <= (BN == V2_SMALL && !DEEP ? 80 : 160) * 1024, "LDS budget");
   return kLds;
 }
@@ -763,7 +795,7 @@ template <bool A_KC, bool B_KC, int EPI, int BN, int KE, bool DEEP, bool JOB>
 hipError_t launch_gemm_bf16_v2_ke(const GemmArgs& a, float* splitk_ws, const ColsumJob* job, hipStream_t st) {
   constexpr size_t kLds = v2_lds_bytes<A_KC, B_KC, BN, DEEP>();
   static LdsAttrOnce attr;         // per instantiation and device
-  V2Plan plan = v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, BN);
+  V2Plan plan = BN == 192 && DEEP ? v2_middle_plan(a.M, a.N, a.K) : v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, BN);
   v2_set_walk(&plan, v2_window<BN, DEEP>(), a.K);
   if constexpr (JOB) {
     auto kern = gemm_bf16_v2_colsum_kernel<BN, KE, DEEP>;
@@ -876,13 +908,14 @@ hipError_t launch_gemm_bf16_v2_group(const GemmArgs* probs, int n, hipStream_t s
 }
 
 bool gemm_v2_group_off();                   // MLM_GEMM_GROUP=0: every weight gradient of a layer shard in a launch of its own
-int gemm_v2_forced_bn();                    // MLM_GEMM_BN=128|192|256 forces a tile width where it exists, else 0
 
 // The 192-wide tile exists for all but the cross-entropy epilogues, the small tile for every epilogue but the one that
 // recomputes the logits: take the one the cost model prices lowest for this shape.
 template <bool A_KC, bool B_KC, int EPI> constexpr bool v2_has_narrow() {
   return B_KC || EPI == EPI_STORE || EPI == EPI_BIAS_GELU;
 }
+// The middle tile exists for forward and input-gradient products with the 192-wide one.
+template <bool A_KC, bool B_KC, int EPI> constexpr bool v2_has_middle() { return A_KC && v2_has_narrow<A_KC, B_KC, EPI>(); }
 template <int EPI> constexpr bool v2_has_small() { return EPI != EPI_DLOGITS; }
 template <bool A_KC, bool B_KC, int EPI>
 int v2_pick_bn(int M, int N, int K, bool allow_split) {
@@ -901,10 +934,10 @@ int v2_pick_bn(int M, int N, int K, bool allow_split) {
 
 template <bool A_KC, bool B_KC, int EPI, int BN, bool DEEP, bool JOB>
 hipError_t launch_gemm_bf16_v2_bn(const GemmArgs& a, float* splitk_ws, const ColsumJob* job, hipStream_t st) {
-  switch (v2_k_end<BN>(a.K)) {
+  switch (v2_k_end<BN, DEEP>(a.K)) {
     case KE_PAIR: return launch_gemm_bf16_v2_ke<A_KC, B_KC, EPI, BN, KE_PAIR, DEEP, JOB>(a, splitk_ws, job, st);
     case KE_SLICE:
-      if constexpr (BN != V2_SMALL) return launch_gemm_bf16_v2_ke<A_KC, B_KC, EPI, BN, KE_SLICE, DEEP, JOB>(a, splitk_ws, job, st);
+      if constexpr (BN != V2_SMALL && !DEEP) return launch_gemm_bf16_v2_ke<A_KC, B_KC, EPI, BN, KE_SLICE, DEEP, JOB>(a, splitk_ws, job, st);
     default: return launch_gemm_bf16_v2_ke<A_KC, B_KC, EPI, BN, KE_ANY, DEEP, JOB>(a, splitk_ws, job, st);
   }
 }
@@ -912,6 +945,8 @@ hipError_t launch_gemm_bf16_v2_bn(const GemmArgs& a, float* splitk_ws, const Col
 template <bool A_KC, bool B_KC, int EPI, bool JOB = false>
 hipError_t launch_gemm_bf16_v2(const GemmArgs& a, float* splitk_ws, hipStream_t st, const ColsumJob* job = nullptr) {
   const int bn = v2_pick_bn<A_KC, B_KC, EPI>(a.M, a.N, a.K, splitk_ws != nullptr);
+  if constexpr (v2_has_middle<A_KC, B_KC, EPI>())
+    if (v2_middle(a.M, a.N, a.K)) return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, 192, true, JOB>(a, splitk_ws, job, st);
   if constexpr (v2_has_narrow<A_KC, B_KC, EPI>())
     if (bn == 192) return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, 192, false, JOB>(a, splitk_ws, job, st);
   if constexpr (v2_has_small<EPI>())

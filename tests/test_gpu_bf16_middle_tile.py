@@ -1,0 +1,50 @@
+"""bf16 products in 128 x 192 tiles, at most one a compute unit: remainders of k around pairs of slices and the eight-slice ring, ragged tiles at
+every edge, both layouts, every epilogue and the column sums beside."""
+import pytest
+import torch
+
+from paper_1909_08053_amd import binding as B
+from paper_1909_08053_amd import synth
+from test_gpu_parity import run_layer_parity
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+# more than 256 tiles of 128 x 128, at most 256 of 128 x 192: whole tiles (256 of them), a last column tile of 8, 64 and 184 columns, of one row
+# and of 120; rows in one tile row, columns in two tile columns
+MN = [(8192, 768), (3000, 1544), (5256, 952), (4360, 1240), (120, 33016), (16384, 264)]
+KS = [192, 200, 224, 248, 256, 264, 320, 504, 520, 1032]
+
+
+@pytest.mark.parametrize("tb", [0, 1])
+@pytest.mark.parametrize("M,N,K", [(M, N, K) for M, N in MN for K in ((192, 264) if M * N > 2 ** 22 else KS[:4])] + [(3000, 1544, K) for K in KS[4:]])
+def test_bf16_middle_tile(tb, M, N, K):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M + K)
+
+    def operand(rows, cols):
+        # what lies behind the operand in memory must never enter a sum
+        t = torch.full((rows + 64, cols), float("nan"), device=DEV, dtype=torch.bfloat16)
+        t[:rows] = torch.randn(rows, cols, generator=g, device=DEV).to(torch.bfloat16)
+        return t[:rows]
+
+    A, W = operand(M, K), operand(N, K) if tb else operand(K, N)
+    bias = torch.randn(N, generator=g, device=DEV).to(torch.bfloat16)
+    C = torch.full((M + 1, N), float("nan"), device=DEV, dtype=torch.bfloat16)
+    a, w = A.double(), (W.t() if tb else W).double()
+    for b in (None, bias):
+        B.mlm_gemm(B.MLM_BF16, 0, tb, M, N, K, A, W, C[:M], b)
+        ref, mag = a @ w, a.abs() @ w.abs()
+        if b is not None:
+            ref, mag = ref + b.double(), mag + b.double().abs()
+        # fp32 accumulation of exact products in any order, then one rounding to bf16 (u = 2^-8)
+        bound = 2.0 ** -8 * ref.abs() + (K + 2) * 2.0 ** -24 * mag
+        assert bool((C[:M].double() - ref).abs().le(bound * 1.01).all())
+        assert bool(C[M].isnan().all())
+
+
+# bias + GeLU, GeLU' and the column sums beside: the widths of the shard's four products take the tile by turns
+@pytest.mark.parametrize("b,s,H,h,V,causal", [(2, 1100, 512, 8, 528, True), (2, 724, 768, 8, 528, False), (64, 133, 512, 8, 264, True)])
+def test_bf16_layer_in_middle_tiles(b, s, H, h, V, causal):
+    run_layer_parity(synth.small_config(name=f"middle{b * s}_{H}", dtype="bf16", b=b, s=s, H=H, h=h, F=4 * H, V=V, p=1, causal=causal,
+                                        masked_lm=not causal), scale_w=3.0)
