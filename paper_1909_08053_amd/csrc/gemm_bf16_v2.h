@@ -378,17 +378,20 @@ inline V2Plan v2_plan(int M, int N, int K, bool allow_split, int bn = V2_B) {
   return p;
 }
 
-// The middle tile, 128 x 192 in eight waves of 32 x 96 with an eight-slice ring, one workgroup per compute unit: where it gives every unit
+// The middle tile, 128 x 192 in eight waves of 32 x 96 with an eight-slice ring (four for a weight gradient), one workgroup per compute unit: where it gives every unit
 // at most one tile and the small tile would give some units two, the others one or none at that one's pace.  Small (or what the plan
 // took) / middle, us: fwd 3000 x 1536 x 1536 23.1 / 21.3, 8192 x 768 x 1536 24.6 / 23.1, 8192 x 576 x 1536 22.4 / 20.4, 7168 x 640 x 2560 33.3 / 30.1,
-// 2352 x 1792 x 1728 29.9 / 20.8, 3448 x 1216 x 10944 197 / 114; dgrad 3000 x 1536 x 1536 22.0 / 19.7, 6152 x 696 x 648 20.2 / 15.2, 4416 x 1200 x 3304 71 / 55; of 64 such
+// 2352 x 1792 x 1728 29.9 / 20.8, 3448 x 1216 x 10944 197 / 114; wgrad 992 x 4144 x 1800 36.2 /
+// 26.5, 2640 x 2088 x 2480 48.3 / 35.1 (50 of them 1.19 in the mean, one slower, 880 x 5512 x 7616 114 / 124; four slices in the ring: eight are 6 % slower up to
+// 4000 k, 5-15 % faster from 5500 on); dgrad 3000 x 1536 x 1536 22.0 / 19.7, 6152 x 696 x 648 20.2 / 15.2, 4416 x 1200 x 3304 71 / 55; of 64 such
 // products of K = 192 on one is 1 % slower, the mean 1.17 (of 36 of K = 3352 .. 15864 1.40, the least 1.04); the ring's fill decides below (5256 x 1016 x 48 6.8 / 7.3, 28 of 40 .. 184 0.93 .. 1.05).  Not beyond one tile a unit (4096 x 1920 x 2560, 320 tiles, 40 / 59; 8192 x 3072 x 1536, 1024, 73 / 93), and
 // where the small tile has one a unit as well that is shorter (1024 x 3840 x 1920 19.5 / 23.4).  Per 32-deep slice 0.33 us, 60 GB/s of operands
 // a unit.
 inline int v2_middle_tiles(int M, int N) { return ((M + V2_SMALL - 1) / V2_SMALL) * ((N + 191) / 192); }
+inline int v2_small_tiles(int M, int N) { return ((M + V2_SMALL - 1) / V2_SMALL) * ((N + V2_SMALL - 1) / V2_SMALL); }
 inline bool v2_middle(int M, int N, int K) {
   const int cus = gemm_cu_count();
-  return K >= 192 && !gemm_v2_forced_bn() && v2_middle_tiles(M, N) <= cus && ((M + V2_SMALL - 1) / V2_SMALL) * ((N + V2_SMALL - 1) / V2_SMALL) > cus;
+  return K >= 192 && !gemm_v2_forced_bn() && v2_middle_tiles(M, N) <= cus && v2_small_tiles(M, N) > cus;
 }
 inline V2Plan v2_middle_plan(int M, int N, int K) {
   const int tm = (M + V2_SMALL - 1) / V2_SMALL, tn = (N + 191) / 192;
@@ -871,7 +874,7 @@ hipError_t launch_gemm_bf16_v2_group_ke(const GemmArgs* probs, int n, const V2Gr
   for (int q = 0; q < n; ++q) {
     const GemmArgs& a = probs[!SPLIT ? q : q == n - 1 ? sp.last : q == sp.last ? n - 1 : q];       // (sp.last goes last)
     g.args[q] = a;
-    g.plan[q] = v2_plan(a.M, a.N, a.K, false, BN);
+    g.plan[q] = BN == 192 && DEEP ? v2_middle_plan(a.M, a.N, a.K) : v2_plan(a.M, a.N, a.K, false, BN);
     g.tile_begin[q] = total;
     total += g.plan[q].full_tiles;
   }
@@ -899,10 +902,10 @@ hipError_t launch_gemm_bf16_v2_group_ke(const GemmArgs* probs, int n, const V2Gr
 
 template <bool A_KC, bool B_KC, int BN, bool DEEP, bool SPLIT = false>
 hipError_t launch_gemm_bf16_v2_group(const GemmArgs* probs, int n, hipStream_t st, const V2GroupSplit& sp = {}, float* splitk_ws = nullptr) {
-  switch (v2_k_end<BN>(probs[0].K)) {
+  switch (v2_k_end<BN, DEEP>(probs[0].K)) {
     case KE_PAIR: return launch_gemm_bf16_v2_group_ke<A_KC, B_KC, BN, KE_PAIR, DEEP, SPLIT>(probs, n, sp, splitk_ws, st);
     case KE_SLICE:
-      if constexpr (BN != V2_SMALL) return launch_gemm_bf16_v2_group_ke<A_KC, B_KC, BN, KE_SLICE, DEEP, SPLIT>(probs, n, sp, splitk_ws, st);
+      if constexpr (BN != V2_SMALL && !DEEP) return launch_gemm_bf16_v2_group_ke<A_KC, B_KC, BN, KE_SLICE, DEEP, SPLIT>(probs, n, sp, splitk_ws, st);
     default: return launch_gemm_bf16_v2_group_ke<A_KC, B_KC, BN, KE_ANY, DEEP, SPLIT>(probs, n, sp, splitk_ws, st);
   }
 }
@@ -914,8 +917,8 @@ bool gemm_v2_group_off();                   // MLM_GEMM_GROUP=0: every weight gr
 template <bool A_KC, bool B_KC, int EPI> constexpr bool v2_has_narrow() {
   return B_KC || EPI == EPI_STORE || EPI == EPI_BIAS_GELU;
 }
-// The middle tile exists for forward and input-gradient products with the 192-wide one.
-template <bool A_KC, bool B_KC, int EPI> constexpr bool v2_has_middle() { return A_KC && v2_has_narrow<A_KC, B_KC, EPI>(); }
+// The middle tile exists with the 192-wide one.
+template <bool A_KC, bool B_KC, int EPI> constexpr bool v2_has_middle() { return v2_has_narrow<A_KC, B_KC, EPI>(); }
 template <int EPI> constexpr bool v2_has_small() { return EPI != EPI_DLOGITS; }
 template <bool A_KC, bool B_KC, int EPI>
 int v2_pick_bn(int M, int N, int K, bool allow_split) {
@@ -979,6 +982,20 @@ inline V2GroupPlan v2_group_plan(const GemmArgs* probs, int n, bool have_ws) {
   }
   if ((use_small ? small : big) + 2.0 < alone) p.bn = use_small ? V2_SMALL : V2_B;
   return p;
+}
+
+// n weight gradients in one launch of middle tiles, by the rule of a single product (v2_middle).
+// Gradients of a layer shard, T x H split p ways, as it was / so, us: 432 x 576 14.0 / 12.6, 960 x 576 22.6 / 18.8, 1376 x 640 30.4 / 26.2, 2436 x 1280, 4
+// 55.1 / 40.5, 5472 x 576 115 / 71, 6412 x 576 124 / 79; 40 drawn ones of 192 tokens on 1.14 times as fast in the mean, the worst 9.4 / 9.4 (196 x 576).
+inline bool v2_group_middle(const GemmArgs* probs, int n) {
+  if (gemm_v2_group_off() || gemm_v2_forced_bn() || n < 2 || n > kMaxGroup || probs[0].K < 192) return false;
+  int middle = 0, small = 0;
+  for (int q = 0; q < n; ++q) {
+    if (probs[q].epi != EPI_STORE || probs[q].bias != nullptr || probs[q].K != probs[0].K) return false;
+    middle += v2_middle_tiles(probs[q].M, probs[q].N);
+    small += v2_small_tiles(probs[q].M, probs[q].N);
+  }
+  return small > gemm_cu_count() && middle <= gemm_cu_count();
 }
 
 // How a weight gradient a0 and an input gradient a1 that do not depend on each other are launched: together in tiles of bn

@@ -24,8 +24,9 @@ static hipError_t launch_split_group(const GemmArgs* probs, int n, int form, hip
   return launch_split(&attr, gemm_bf16_split_group_kernel<TM, TN>, split_lds_bytes<TM, TN>(), total, st, g);
 }
 
-// The weight gradients of a layer shard (same operand layout, same k = tokens), as split_group_pick and v2_group_plan say.
+// The weight gradients of a layer shard (same operand layout, same k = tokens), as v2_group_middle, split_group_pick and v2_group_plan say.
 hipError_t launch_gemm_bf16_wgrad_group(const GemmArgs* probs, int n, float* splitk_ws, hipStream_t st) {
+  if (v2_group_middle(probs, n)) return launch_gemm_bf16_v2_group<false, false, 192, true>(probs, n, st);
   const V2GroupPlan p = v2_group_plan(probs, n, splitk_ws != nullptr);
   switch (split_group_pick(probs, n, p)) {
     case SPLIT_64: return launch_split_group<64, 64>(probs, n, SPLIT_64, st);

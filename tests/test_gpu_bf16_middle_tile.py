@@ -1,5 +1,5 @@
 """bf16 products in 128 x 192 tiles, at most one a compute unit: remainders of k around pairs of slices and the eight-slice ring, ragged tiles at
-every edge, both layouts, every epilogue and the column sums beside."""
+every edge, all layouts, every epilogue and the column sums beside; the four weight gradients of a shard in one launch, of token counts that are no multiple of anything."""
 import pytest
 import torch
 
@@ -16,9 +16,10 @@ MN = [(8192, 768), (3000, 1544), (5256, 952), (4360, 1240), (120, 33016), (16384
 KS = [192, 200, 224, 248, 256, 264, 320, 504, 520, 1032]
 
 
-@pytest.mark.parametrize("tb", [0, 1])
+@pytest.mark.parametrize("layout", [(0, 0), (0, 1), (1, 0)])
 @pytest.mark.parametrize("M,N,K", [(M, N, K) for M, N in MN for K in ((192, 264) if M * N > 2 ** 22 else KS[:4])] + [(3000, 1544, K) for K in KS[4:]])
-def test_bf16_middle_tile(tb, M, N, K):
+def test_bf16_middle_tile(layout, M, N, K):
+    ta, tb = layout
     g = torch.Generator(device=DEV)
     g.manual_seed(M + K)
 
@@ -28,12 +29,13 @@ def test_bf16_middle_tile(tb, M, N, K):
         t[:rows] = torch.randn(rows, cols, generator=g, device=DEV).to(torch.bfloat16)
         return t[:rows]
 
-    A, W = operand(M, K), operand(N, K) if tb else operand(K, N)
+    A = operand(K, M) if ta else operand(M, K)
+    W = operand(N, K) if tb else operand(K, N)
     bias = torch.randn(N, generator=g, device=DEV).to(torch.bfloat16)
     C = torch.full((M + 1, N), float("nan"), device=DEV, dtype=torch.bfloat16)
-    a, w = A.double(), (W.t() if tb else W).double()
+    a, w = (A.t() if ta else A).double(), (W.t() if tb else W).double()
     for b in (None, bias):
-        B.mlm_gemm(B.MLM_BF16, 0, tb, M, N, K, A, W, C[:M], b)
+        B.mlm_gemm(B.MLM_BF16, ta, tb, M, N, K, A, W, C[:M], b)
         ref, mag = a @ w, a.abs() @ w.abs()
         if b is not None:
             ref, mag = ref + b.double(), mag + b.double().abs()
@@ -43,8 +45,9 @@ def test_bf16_middle_tile(tb, M, N, K):
         assert bool(C[M].isnan().all())
 
 
-# bias + GeLU, GeLU' and the column sums beside: the widths of the shard's four products take the tile by turns
-@pytest.mark.parametrize("b,s,H,h,V,causal", [(2, 1100, 512, 8, 528, True), (2, 724, 768, 8, 528, False), (64, 133, 512, 8, 264, True)])
+# bias + GeLU, GeLU' and the column sums beside: the shard's four products and their weight gradients take the tile by turns
+@pytest.mark.parametrize("b,s,H,h,V,causal", [(2, 1100, 512, 8, 528, True), (2, 724, 768, 8, 528, False), (64, 133, 512, 8, 264, True), (1, 193, 576, 6, 264, True),
+                                                  (3, 211, 640, 5, 264, False), (7, 257, 576, 9, 264, True)])
 def test_bf16_layer_in_middle_tiles(b, s, H, h, V, causal):
     run_layer_parity(synth.small_config(name=f"middle{b * s}_{H}", dtype="bf16", b=b, s=s, H=H, h=h, F=4 * H, V=V, p=1, causal=causal,
                                         masked_lm=not causal), scale_w=3.0)
