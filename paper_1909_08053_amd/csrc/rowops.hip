@@ -940,16 +940,32 @@ __global__ __launch_bounds__(256) void ce_tile_merge_kernel(int T, int ntiles, c
                                                             const float* __restrict__ t_ws,
                                                             const int32_t* __restrict__ targets, int v0, int v1,
                                                             float* m_r, float* s_r, float* t_r) {
-  // 32 tokens x 8 tile-slices per block; each slice merges its tiles online, slices are merged in a fixed order.
+  // 32 tokens x 8 tile-slices per block; each slice merges its tiles online, eight at a time (their loads in flight together; one at a time, a round
+  // trip to memory each, 8192 tokens x 200 tiles took 16.8 us, now 7.5 - 8, 1024 x 100 7.1, now 4.8), slices are merged in a fixed order.
+  constexpr int U = 8;
   __shared__ float sm[8][33], ss[8][33];
   const int tx = threadIdx.x & 31, sl = threadIdx.x >> 5;
   const int t = blockIdx.x * 32 + tx;
   float M = -INFINITY, S = 0.f;
   if (t < T) {
-    for (int k = sl; k < ntiles; k += 8) {
-      const float mk = part_m[(size_t)k * T + t], sk = part_s[(size_t)k * T + t];
-      const float Mn = fmaxf(M, mk);
-      if (Mn > -INFINITY) S = S * __expf(M - Mn) + sk * __expf(mk - Mn);
+    for (int k0 = sl; k0 < ntiles; k0 += 8 * U) {
+      float mk[U], sk[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = k0 + 8 * u;
+        const size_t at = (size_t)min(k, ntiles - 1) * T + t;
+        mk[u] = part_m[at];
+        sk[u] = part_s[at];
+        if (k >= ntiles) { mk[u] = -INFINITY; sk[u] = 0.f; }
+      }
+      float Mn = M;
+#pragma unroll
+      for (int u = 0; u < U; ++u) Mn = fmaxf(Mn, mk[u]);
+      if (Mn > -INFINITY) {
+        S *= __expf(M - Mn);
+#pragma unroll
+        for (int u = 0; u < U; ++u) S += sk[u] * __expf(mk[u] - Mn);
+      }
       M = Mn;
     }
   }
@@ -979,7 +995,10 @@ hipError_t launch_ce_tile_merge(int T, int ntiles, const float* part_m, const fl
   return hipGetLastError();
 }
 
-// fp32 path: row partials straight from stored logits, one block per token.
+// fp32 path: row partials straight from stored logits, one block per token.  Bound by memory: a thread asks for the first KEEP
+// vectors of its share at once and keeps them between the two passes (1024 rows of 8192 16.9 -> 10.8 us, a float at a time and twice before; the
+// rows alone take 7).  Of longer rows the rest is read twice.
+template <int KEEP>
 __global__ __launch_bounds__(256) void ce_rows_f32_kernel(int Vl, const float* __restrict__ logits,
                                                           const int32_t* __restrict__ targets, int v0,
                                                           float* m_r, float* s_r, float* t_r) {
@@ -987,14 +1006,30 @@ __global__ __launch_bounds__(256) void ce_rows_f32_kernel(int Vl, const float* _
   const int t = blockIdx.x;
   const float* row = logits + (size_t)t * Vl;
   float mx = -INFINITY;
-  for (int j = threadIdx.x; j < Vl; j += 256) mx = fmaxf(mx, row[j]);
+  float4 v[KEEP];
+#pragma unroll
+  for (int k = 0; k < KEEP; ++k) {
+    const int j = 4 * (256 * k + (int)threadIdx.x);
+    v[k] = *reinterpret_cast<const float4*>(row + min(j, Vl - 4));           // (Vl is a multiple of 8)
+    if (j >= Vl) v[k] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+  }
+#pragma unroll
+  for (int k = 0; k < KEEP; ++k) mx = fmaxf(mx, fmaxf(fmaxf(v[k].x, v[k].y), fmaxf(v[k].z, v[k].w)));
+  for (int j = 4 * (256 * KEEP + (int)threadIdx.x); j < Vl; j += 1024) {
+    const float4 x = *reinterpret_cast<const float4*>(row + j);
+    mx = fmaxf(mx, fmaxf(fmaxf(x.x, x.y), fmaxf(x.z, x.w)));
+  }
   mx = wave_max(mx);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
   __syncthreads();
   mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
   __syncthreads();
   float se = 0.f;
-  for (int j = threadIdx.x; j < Vl; j += 256) se += expf(row[j] - mx);
+  auto add = [&](const float4& x) { se += (expf(x.x - mx) + expf(x.y - mx)) + (expf(x.z - mx) + expf(x.w - mx)); };
+#pragma unroll
+  for (int k = 0; k < KEEP; ++k)
+    if (4 * (256 * k + (int)threadIdx.x) < Vl) add(v[k]);
+  for (int j = 4 * (256 * KEEP + (int)threadIdx.x); j < Vl; j += 1024) add(*reinterpret_cast<const float4*>(row + j));
   se = wave_sum(se);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = se;
   __syncthreads();
@@ -1008,7 +1043,8 @@ __global__ __launch_bounds__(256) void ce_rows_f32_kernel(int Vl, const float* _
 
 hipError_t launch_ce_rows_f32(int T, int Vl, const float* logits, const int32_t* targets, int v0, float* m_r,
                               float* s_r, float* t_r, hipStream_t st) {
-  hipLaunchKernelGGL(ce_rows_f32_kernel, dim3(T), dim3(256), 0, st, Vl, logits, targets, v0, m_r, s_r, t_r);
+  auto kern = Vl <= 1024 * 4 ? ce_rows_f32_kernel<4> : ce_rows_f32_kernel<8>;
+  hipLaunchKernelGGL(kern, dim3(T), dim3(256), 0, st, Vl, logits, targets, v0, m_r, s_r, t_r);
   return hipGetLastError();
 }
 
