@@ -110,6 +110,10 @@ __device__ __forceinline__ float wave_max(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, a), 63));
 }
 
+// What a row's logits are taken relative to in its sum of exponentials: their maximum, or 0 where that is -inf.  An -inf logit then adds exp(-inf) = 0
+// there too, where -inf - -inf would be NaN, and a NaN logit still shows in the sum.
+__device__ __forceinline__ float ce_base(float max) { return max > -INFINITY ? max : 0.f; }
+
 // GeLU and its derivative.  tanh form: 0.5 x (1 + tanh(u)) = x sigmoid(2u) with u = sqrt(2/pi)(x + 0.044715 x^3);
 // exact form: x Phi(x).  The sigmoid is one exp2 and one reciprocal; it saturates cleanly (exp2 -> 0 or inf).
 __device__ __forceinline__ float gelu_sigmoid2u(float x) {

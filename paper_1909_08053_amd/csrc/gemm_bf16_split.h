@@ -236,7 +236,7 @@ __device__ __forceinline__ void gemm_split_tile(const GemmArgs& a, int tile_m, i
       for (int e = 0; e < VEC; ++e) mx = fmaxf(mx, v[e]);
     }
     mx = split_max<TPR>(mx);
-    const float mxl = mx * 1.4426950408889634f;
+    const float mxl = ce_base(mx) * 1.4426950408889634f;
     if (gn < a.N) {
 #pragma unroll
       for (int e = 0; e < VEC; ++e) se += __builtin_amdgcn_exp2f(fmaf(v[e], 1.4426950408889634f, -mxl));

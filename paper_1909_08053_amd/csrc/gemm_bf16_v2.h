@@ -741,7 +741,7 @@ __global__ __launch_bounds__(256) void gemm_v2_fixup_kernel(GemmArgs a, V2Plan p
       float mx = -INFINITY;
       if (ok) mx = fmaxf(fmaxf(v[i][0], v[i][1]), fmaxf(v[i][2], v[i][3]));
       mx = wave_max(mx);
-      const float mxl = mx * 1.4426950408889634f;
+      const float mxl = ce_base(mx) * 1.4426950408889634f;
       float se = 0.f;
       if (ok) {
 #pragma unroll

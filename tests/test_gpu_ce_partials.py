@@ -42,3 +42,44 @@ def test_partials(dtype, T, V):
         want = torch.where(on, ref.gather(1, (targets.long() - V).clamp(min=0)[:, None])[:, 0], torch.zeros((), device=DEV, dtype=torch.double))
         assert bool((t[:T].double() - want).abs().le(eps).all())
         assert bool(m[T].isnan() and s[T].isnan() and t[T].isnan())
+
+
+LOWEST = {B.MLM_BF16: -3.3895313892515355e38, B.MLM_F32: -3.4028234663852886e38}
+# tokens, columns, width: 64 x 64 and 32 x 64 tiles whose k is dealt to the waves, 128 x 128 tiles (one and two a compute unit, k whole and in
+# pieces), 256 x 256 (k whole and in pieces); fp32 rows shorter and longer than what a thread keeps
+MINUS_INF = [(B.MLM_BF16, 40, 8784, 1608), (B.MLM_BF16, 400, 1024, 192), (B.MLM_BF16, 33, 1032, 128), (B.MLM_BF16, 80, 10144, 80),
+             (B.MLM_BF16, 272, 12008, 144), (B.MLM_BF16, 224, 5536, 2032), (B.MLM_BF16, 264, 25608, 128), (B.MLM_BF16, 488, 8240, 1616),
+             (B.MLM_F32, 33, 1024, 128), (B.MLM_F32, 65, 8712, 128)]
+
+
+def minus_inf_case(dtype, T, V, H):
+    """Every third row overflows to -inf in all columns but the first quarter, every other third in none; V a whole number of tiles or not."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(T + V)
+    td = torch.bfloat16 if dtype == B.MLM_BF16 else torch.float32
+    hf = (torch.randn(T, H, generator=g, device=DEV)).to(td)
+    E = torch.randn(H, V, generator=g, device=DEV).to(td)
+    hf[:, :2] = 0
+    hf[::3, 0] = 4.0
+    E[:2] = 0
+    E[0, V // 4:] = LOWEST[dtype]
+    targets = torch.randint(0, V, (T,), generator=g, device=DEV, dtype=torch.int32)
+    dims = B.make_dims(1, T, H, 1, 4 * H, V, 1, 0, dtype, True)
+    out = [torch.full((T,), float("nan"), device=DEV) for _ in range(3)]
+    logits = torch.empty(T, V, device=DEV, dtype=td)
+    ws = torch.empty(B.mlm_workspace_bytes(dims, B.WS_VOCAB_CE_FWD), dtype=torch.uint8, device=DEV)
+    return hf, E, lambda: (B.mlm_vocab_ce_shard_fwd(dims, hf, E, targets, *out, logits, ws), *out, logits)[1:]
+
+
+@pytest.mark.parametrize("dtype,T,V,H", MINUS_INF)
+def test_logits_at_minus_infinity(dtype, T, V, H):
+    hf, E, run = minus_inf_case(dtype, T, V, H)
+    m, s, t, logits = run()
+    ref = hf.double() @ E.double()
+    ref[ref < -3.5e38] = float("-inf")
+    assert bool((logits[::3, V // 4:] == float("-inf")).all() and logits[::3, :V // 4].isfinite().all() and logits[1::3].isfinite().all())
+    u, small = 2.0 ** -24, E.double()
+    small[0] = 0                                                               # (no part of a finite logit)
+    eps = (2 * H + 8) * u * (hf.double().abs() @ small.abs()).max(1).values + 4 * u * ref[ref.isfinite()].abs().max() + 1e-6
+    assert bool((m.double() - ref.max(1).values).abs().le(eps).all())
+    assert bool((m.double() + s.double().log() - torch.logsumexp(ref, 1)).abs().le(2 * eps + (V / 256 + 300) * u + 3e-6).all())
