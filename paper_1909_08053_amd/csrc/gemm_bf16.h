@@ -61,7 +61,7 @@ __device__ __forceinline__ void ce_tile_stats(const GemmArgs& a, const floatx4 (
   for (int j = 0; j < NA; ++j) mx[j] = fmaxf(mx[j], __shfl_xor(mx[j], 32, 64));
 #pragma unroll
   for (int j = 0; j < NA; ++j) {
-    const float mxl = mx[j] * 1.4426950408889634f;
+    const float mxl = ce_base(mx[j]) * 1.4426950408889634f;
     se[j] = 0.f;
     tv[j] = 0.f;
 #pragma unroll
@@ -175,12 +175,10 @@ __device__ __forceinline__ void gemm_epilogue_impl(const GemmArgs& a, Acc& acc, 
         float M = -INFINITY;
 #pragma unroll
         for (int w = 0; w < WAVES_N; ++w) M = fmaxf(M, red_m[w * BM + rloc]);
+        const float base = ce_base(M);
         float S = 0.f;
 #pragma unroll
-        for (int w = 0; w < WAVES_N; ++w) {
-          const float mw = red_m[w * BM + rloc];
-          if (mw > -INFINITY) S += red_s[w * BM + rloc] * __expf(mw - M);
-        }
+        for (int w = 0; w < WAVES_N; ++w) S += red_s[w * BM + rloc] * __expf(red_m[w * BM + rloc] - base);
         a.part_m[(size_t)tile_n * a.M + row] = M;
         a.part_s[(size_t)tile_n * a.M + row] = S;
       }

@@ -961,11 +961,10 @@ __global__ __launch_bounds__(256) void ce_tile_merge_kernel(int T, int ntiles, c
       float Mn = M;
 #pragma unroll
       for (int u = 0; u < U; ++u) Mn = fmaxf(Mn, mk[u]);
-      if (Mn > -INFINITY) {
-        S *= __expf(M - Mn);
+      const float base = ce_base(Mn);
+      S *= __expf(M - base);
 #pragma unroll
-        for (int u = 0; u < U; ++u) S += sk[u] * __expf(mk[u] - Mn);
-      }
+      for (int u = 0; u < U; ++u) S += sk[u] * __expf(mk[u] - base);
       M = Mn;
     }
   }
@@ -976,10 +975,10 @@ __global__ __launch_bounds__(256) void ce_tile_merge_kernel(int T, int ntiles, c
     float Mt = -INFINITY;
 #pragma unroll
     for (int k = 0; k < 8; ++k) Mt = fmaxf(Mt, sm[k][tx]);
+    const float base = ce_base(Mt);
     float St = 0.f;
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
-      if (sm[k][tx] > -INFINITY) St += ss[k][tx] * __expf(sm[k][tx] - Mt);
+    for (int k = 0; k < 8; ++k) St += ss[k][tx] * __expf(sm[k][tx] - base);
     m_r[t] = Mt;
     s_r[t] = St;
     const int tg = targets[t];

@@ -83,3 +83,11 @@ def test_logits_at_minus_infinity(dtype, T, V, H):
     eps = (2 * H + 8) * u * (hf.double().abs() @ small.abs()).max(1).values + 4 * u * ref[ref.isfinite()].abs().max() + 1e-6
     assert bool((m.double() - ref.max(1).values).abs().le(eps).all())
     assert bool((m.double() + s.double().log() - torch.logsumexp(ref, 1)).abs().le(2 * eps + (V / 256 + 300) * u + 3e-6).all())
+
+
+@pytest.mark.parametrize("dtype,T,V,H", MINUS_INF)
+def test_a_nan_among_logits_at_minus_infinity_shows(dtype, T, V, H):
+    hf, E, run = minus_inf_case(dtype, T, V, H)
+    E[1, V // 2 + 5] = float("nan")                                            # one column of every row
+    m, s, _, _ = run()
+    assert bool(s.isnan().all() and not m[1::3].isnan().any())
