@@ -1024,7 +1024,8 @@ __global__ __launch_bounds__(256) void ce_rows_f32_kernel(int Vl, const float* _
   mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
   __syncthreads();
   float se = 0.f;
-  auto add = [&](const float4& x) { se += (expf(x.x - mx) + expf(x.y - mx)) + (expf(x.z - mx) + expf(x.w - mx)); };
+  const float base = ce_base(mx);
+  auto add = [&](const float4& x) { se += (expf(x.x - base) + expf(x.y - base)) + (expf(x.z - base) + expf(x.w - base)); };
 #pragma unroll
   for (int k = 0; k < KEEP; ++k)
     if (4 * (256 * k + (int)threadIdx.x) < Vl) add(v[k]);

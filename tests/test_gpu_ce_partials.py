@@ -91,3 +91,12 @@ def test_a_nan_among_logits_at_minus_infinity_shows(dtype, T, V, H):
     E[1, V // 2 + 5] = float("nan")                                            # one column of every row
     m, s, _, _ = run()
     assert bool(s.isnan().all() and not m[1::3].isnan().any())
+
+
+@pytest.mark.parametrize("dtype,T,V,H", MINUS_INF)
+def test_a_shard_at_minus_infinity(dtype, T, V, H):
+    """All of a row's logits in the shard: its sum is 0, so that the merge with another shard's finite logits stays exact."""
+    hf, E, run = minus_inf_case(dtype, T, V, H)
+    E[0] = LOWEST[dtype]
+    m, s, _, _ = run()
+    assert bool((m[::3] == float("-inf")).all() and (s[::3] == 0).all() and m[1::3].isfinite().all() and (s[1::3] > 0).all())
