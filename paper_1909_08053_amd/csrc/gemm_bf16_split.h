@@ -393,9 +393,8 @@ inline SplitPick split_pick(int M, int N, int K, double than, bool wide = false)
 // ... of a single product
 template <bool A_KC, bool B_KC, int EPI>
 SplitPick split_pick_alone(int M, int N, int K, bool allow_split) {
-  const V2Plan p = v2_plan(M, N, K, allow_split, v2_pick_bn<A_KC, B_KC, EPI>(M, N, K, allow_split));
-  double us = v2_few_us(p, K);
-  if (v2_has_middle<A_KC, B_KC, EPI>() && v2_middle(M, N, K)) us = v2_middle_plan(M, N, K).cost;
+  const V2Choice c = v2_choose<A_KC, B_KC, EPI>(M, N, K, allow_split);
+  const double us = c.middle ? c.us : v2_few_us(c.plan, K);
   return split_pick(M, N, K, us, EPI == EPI_CE);
 }
 

@@ -321,6 +321,11 @@ inline void v2_set_walk(V2Plan* p, int window, int K, bool strips = false) {
   }
 }
 
+inline bool v2_in_strips(V2Plan p, int window, int K) {
+  v2_set_walk(&p, window, K);
+  return p.strip != 0;
+}
+
 // Cost-model constants (microseconds, fitted to rocprofv3 kernel durations of unsplit two-round launches at two
 // k-lengths each on MI355X): fixed cost of a tile (fill + epilogue) and cost of one 32-deep k-slice, for the
 // 256 x 256 tile and for the 256 x 192 tile (either B layout).  The narrow tile does 3/4 of the MFMA work per slice
@@ -378,22 +383,17 @@ inline V2Plan v2_plan(int M, int N, int K, bool allow_split, int bn = V2_B) {
   return p;
 }
 
-// The middle tile, 128 x 192 in eight waves of 32 x 96 with an eight-slice ring (four for a weight gradient), one workgroup per compute unit: where it gives every unit
-// at most one tile and the small tile would give some units two, the others one or none at that one's pace.  Small (or what the plan
-// took) / middle, us: fwd 3000 x 1536 x 1536 23.1 / 21.3, 8192 x 768 x 1536 24.6 / 23.1, 8192 x 576 x 1536 22.4 / 20.4, 7168 x 640 x 2560 33.3 / 30.1,
-// 2352 x 1792 x 1728 29.9 / 20.8, 3448 x 1216 x 10944 197 / 114; wgrad 992 x 4144 x 1800 36.2 /
-// 26.5, 2640 x 2088 x 2480 48.3 / 35.1 (50 of them 1.19 in the mean, one slower, 880 x 5512 x 7616 114 / 124; four slices in the ring: eight are 6 % slower up to
-// 4000 k, 5-15 % faster from 5500 on); dgrad 3000 x 1536 x 1536 22.0 / 19.7, 6152 x 696 x 648 20.2 / 15.2, 4416 x 1200 x 3304 71 / 55; of 64 such
-// products of K = 192 on one is 1 % slower, the mean 1.17 (of 36 of K = 3352 .. 15864 1.40, the least 1.04); the ring's fill decides below (5256 x 1016 x 48 6.8 / 7.3, 28 of 40 .. 184 0.93 .. 1.05).  Not beyond one tile a unit (4096 x 1920 x 2560, 320 tiles, 40 / 59; 8192 x 3072 x 1536, 1024, 73 / 93), and
-// where the small tile has one a unit as well that is shorter (1024 x 3840 x 1920 19.5 / 23.4).  Per 32-deep slice 0.33 us, 60 GB/s of operands
-// a unit.
+// The middle tile, 128 x 192 in eight waves of 32 x 96 with an eight-slice ring (four for a weight gradient: eight are 6 % slower up to 4000 k,
+// 5-15 % faster from 5500 on), one workgroup per compute unit: where it gives every unit at most one tile and the small tile would give some units
+// two, the others one or none at that one's pace (v2_choose).  Not beyond one tile a unit (4096 x 1920 x 2560, 320 tiles, 40 / 59; 8192 x 3072 x 1536,
+// 1024, 73 / 93), and where the small tile has one a unit as well that is shorter (1024 x 3840 x 1920 19.5 / 23.4).
 inline int v2_middle_tiles(int M, int N) { return ((M + V2_SMALL - 1) / V2_SMALL) * ((N + 191) / 192); }
 inline int v2_small_tiles(int M, int N) { return ((M + V2_SMALL - 1) / V2_SMALL) * ((N + V2_SMALL - 1) / V2_SMALL); }
-inline bool v2_middle(int M, int N, int K) {
+inline bool v2_middle_fits(int M, int N) {
   const int cus = gemm_cu_count();
-  return K >= 192 && !gemm_v2_forced_bn() && v2_middle_tiles(M, N) <= cus && v2_small_tiles(M, N) > cus;
+  return !gemm_v2_forced_bn() && v2_middle_tiles(M, N) <= cus && v2_small_tiles(M, N) > cus;
 }
-inline V2Plan v2_middle_plan(int M, int N, int K) {
+inline V2Plan v2_middle_plan(int M, int N) {
   const int tm = (M + V2_SMALL - 1) / V2_SMALL, tn = (N + 191) / 192;
   V2Plan p = {};
   p.tiles_m = tm;
@@ -402,7 +402,6 @@ inline V2Plan v2_middle_plan(int M, int N, int K) {
   p.split = 1;
   p.bm = V2_SMALL;
   p.bn = 192;
-  p.cost = 6.0 + 0.33 * v2_slices(K);
   return p;
 }
 
@@ -798,7 +797,7 @@ template <bool A_KC, bool B_KC, int EPI, int BN, int KE, bool DEEP, bool JOB>
 hipError_t launch_gemm_bf16_v2_ke(const GemmArgs& a, float* splitk_ws, const ColsumJob* job, hipStream_t st) {
   constexpr size_t kLds = v2_lds_bytes<A_KC, B_KC, BN, DEEP>();
   static LdsAttrOnce attr;         // per instantiation and device
-  V2Plan plan = BN == 192 && DEEP ? v2_middle_plan(a.M, a.N, a.K) : v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, BN);
+  V2Plan plan = BN == 192 && DEEP ? v2_middle_plan(a.M, a.N) : v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, BN);
   v2_set_walk(&plan, v2_window<BN, DEEP>(), a.K);
   if constexpr (JOB) {
     auto kern = gemm_bf16_v2_colsum_kernel<BN, KE, DEEP>;
@@ -874,7 +873,7 @@ hipError_t launch_gemm_bf16_v2_group_ke(const GemmArgs* probs, int n, const V2Gr
   for (int q = 0; q < n; ++q) {
     const GemmArgs& a = probs[!SPLIT ? q : q == n - 1 ? sp.last : q == sp.last ? n - 1 : q];       // (sp.last goes last)
     g.args[q] = a;
-    g.plan[q] = BN == 192 && DEEP ? v2_middle_plan(a.M, a.N, a.K) : v2_plan(a.M, a.N, a.K, false, BN);
+    g.plan[q] = BN == 192 && DEEP ? v2_middle_plan(a.M, a.N) : v2_plan(a.M, a.N, a.K, false, BN);
     g.tile_begin[q] = total;
     total += g.plan[q].full_tiles;
   }
@@ -935,6 +934,44 @@ int v2_pick_bn(int M, int N, int K, bool allow_split) {
   return best;
 }
 
+// Microseconds of a product whose output fits the middle tile: in those, and in the plan's tiles with k-pieces.  Fitted to 963 products of K from 1000
+// to 32000, split-k scratch given, the fix-up included, operands in the caches and not (4 % weight gradients, 9-12 % others), the last term of the pieces to
+// whole steps: their fp32 partial tiles, some 50 MB, push the step's activations out of the memory-side cache, and the launches behind take longer.
+// dhf 3000 x 1536 x 7648 takes 85 us in middle tiles and 80 in pieces, and its step (ragged, split four ways) 541 and 551.
+template <bool A_KC, int EPI>
+double v2_middle_us(int M, int N, int K) {
+  const double nk = v2_slices(K), f = (double)v2_middle_tiles(M, N) / gemm_cu_count(), bytes = ((double)M + N) * K * 2.0 / 5.0e6;
+  if (!A_KC) return 5.3 + (0.29 + 0.121 * f) * nk + 0.075 * bytes;
+  return (EPI == EPI_STORE ? 5.9 : 10.0) + (0.232 + 0.118 * f) * nk + 0.27 * bytes;
+}
+template <bool A_KC>
+double v2_pieces_us(const V2Plan& p, int M, int N, int K) {
+  const double bytes = ((double)M + N) * K * 2.0 / 5.0e6, partial = (double)p.tail_tiles * p.split * p.bm * p.bn * 4.0 / 5.0e6;
+  return (A_KC ? 0.9 * p.cost + 0.5 * bytes : 0.873 * p.cost + 0.23 * bytes) + 1.3 * partial;
+}
+
+// The tiles of a product in a launch of its own: the middle tile or those of the plan, and their price.  The middle one, where it fits:
+//   * Against a plan without k-pieces (short k, or no scratch) from K = 192 on: of 332 products 0.97 of the time at 192 .. 320 k, 0.85 at 450 .. 1000, 0.79
+//     beyond (worst 1.08, 2144 x 2864 x 256 8.6 / 9.1 us); with GeLU or its derivative, whose operands then come behind the last product, from 640 on
+//     (.. 448 1.02, up to 1.11; 640 .. 1000 0.91).  3000 x 1536 x 1536 forward 21.0 / 18.8, 8192 x 768 x 1536 21.8 / 20.9, 2352 x 1792 x 1728 22.9 / 20.5,
+//     7168 x 640 x 2560 31.4 / 28.6, wgrad 992 x 4144 x 1800 29.3 / 26.0, without scratch dgrad 3000 x 1536 x 30592 395 / 305.
+//   * Against k-pieces by price.  Steps with dhf in pieces / in middle tiles, us: 5000 x 1152 x 10944 717 / 706, 2400 x 1920 x 8544 658 / 646, 4000 x 1344 x 9600
+//     781 / 771; 3000 x 1536 x 11264 684 / 690, x 15296 1242 / 1289, 7000 x 640 x 20000 1222 / 1271.
+struct V2Choice { int bn; bool middle; V2Plan plan; double us; };
+template <bool A_KC, bool B_KC, int EPI>
+V2Choice v2_choose(int M, int N, int K, bool allow_split) {
+  V2Choice c = {v2_pick_bn<A_KC, B_KC, EPI>(M, N, K, allow_split), false, {}, 0.0};
+  c.plan = v2_plan(M, N, K, allow_split, c.bn);
+  c.us = c.plan.cost;
+  if constexpr (v2_has_middle<A_KC, B_KC, EPI>()) {
+    if (K < (EPI == EPI_STORE ? 192 : 640) || !v2_middle_fits(M, N)) return c;
+    const double us = v2_middle_us<A_KC, EPI>(M, N, K);
+    if (c.plan.split > 1 && us >= v2_pieces_us<A_KC>(c.plan, M, N, K)) return c;
+    c = {192, true, v2_middle_plan(M, N), us};
+  }
+  return c;
+}
+
 template <bool A_KC, bool B_KC, int EPI, int BN, bool DEEP, bool JOB>
 hipError_t launch_gemm_bf16_v2_bn(const GemmArgs& a, float* splitk_ws, const ColsumJob* job, hipStream_t st) {
   switch (v2_k_end<BN, DEEP>(a.K)) {
@@ -947,14 +984,14 @@ hipError_t launch_gemm_bf16_v2_bn(const GemmArgs& a, float* splitk_ws, const Col
 
 template <bool A_KC, bool B_KC, int EPI, bool JOB = false>
 hipError_t launch_gemm_bf16_v2(const GemmArgs& a, float* splitk_ws, hipStream_t st, const ColsumJob* job = nullptr) {
-  const int bn = v2_pick_bn<A_KC, B_KC, EPI>(a.M, a.N, a.K, splitk_ws != nullptr);
+  const V2Choice c = v2_choose<A_KC, B_KC, EPI>(a.M, a.N, a.K, splitk_ws != nullptr);
   if constexpr (v2_has_middle<A_KC, B_KC, EPI>())
-    if (v2_middle(a.M, a.N, a.K)) return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, 192, true, JOB>(a, splitk_ws, job, st);
+    if (c.middle) return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, 192, true, JOB>(a, splitk_ws, job, st);
   if constexpr (v2_has_narrow<A_KC, B_KC, EPI>())
-    if (bn == 192) return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, 192, false, JOB>(a, splitk_ws, job, st);
+    if (c.bn == 192) return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, 192, false, JOB>(a, splitk_ws, job, st);
   if constexpr (v2_has_small<EPI>())
-    if (bn == V2_SMALL)
-      return v2_plan(a.M, a.N, a.K, splitk_ws != nullptr, V2_SMALL).deep()
+    if (c.bn == V2_SMALL)
+      return c.plan.deep()
                  ? launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_SMALL, true, JOB>(a, splitk_ws, job, st)
                  : launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_SMALL, false, JOB>(a, splitk_ws, job, st);
   return launch_gemm_bf16_v2_bn<A_KC, B_KC, EPI, V2_B, false, JOB>(a, splitk_ws, job, st);
@@ -962,9 +999,9 @@ hipError_t launch_gemm_bf16_v2(const GemmArgs& a, float* splitk_ws, hipStream_t 
 
 // How n weight gradients (both operands k-major) are launched: together in tiles of bn, `split`: with the last round in k-pieces; apart
 // (bn = 0) where they are no group or the shared last round gains nothing over separate launches with their k-splits.
-struct V2GroupPlan { int bn; V2GroupSplit split; };
+struct V2GroupPlan { int bn; V2GroupSplit split; double alone; };          // alone: microseconds of the launches apart
 inline V2GroupPlan v2_group_plan(const GemmArgs* probs, int n, bool have_ws) {
-  V2GroupPlan p = {0, {0, 0, 0, 1e30}};
+  V2GroupPlan p = {0, {0, 0, 0, 1e30}, 1e30};
   if (gemm_v2_group_off() || n < 2 || n > kMaxGroup) return p;
   double alone = 0.0;
   for (int q = 0; q < n; ++q) {
@@ -972,30 +1009,44 @@ inline V2GroupPlan v2_group_plan(const GemmArgs* probs, int n, bool have_ws) {
     if (probs[q].epi != EPI_STORE || probs[q].bias != nullptr || K != probs[0].K) return p;
     alone += v2_plan(M, N, K, true, v2_pick_bn<false, false, EPI_STORE>(M, N, K, true)).cost + 2.0;   // + launch and drain
   }
+  p.alone = alone;
   const double big = v2_group_cost(probs, n, V2_B), small = v2_group_cost(probs, n, V2_SMALL);
   const int forced = gemm_v2_forced_bn();
   const bool use_small = forced ? forced == V2_SMALL : small < big;
   if ((!forced || forced == V2_B) && have_ws) {
     const V2GroupSplit sp = v2_group_split(probs, n);
     const double whole = use_small ? v2_group_cost(probs, n, V2_SMALL, true) : big;
-    if (sp.split && sp.cost < 0.97 * whole && sp.cost + 2.0 < alone) return {V2_B, sp};
+    if (sp.split && sp.cost < 0.97 * whole && sp.cost + 2.0 < alone) return {V2_B, sp, alone};
   }
   if ((use_small ? small : big) + 2.0 < alone) p.bn = use_small ? V2_SMALL : V2_B;
   return p;
 }
 
-// n weight gradients in one launch of middle tiles, by the rule of a single product (v2_middle).
-// Gradients of a layer shard, T x H split p ways, as it was / so, us: 432 x 576 14.0 / 12.6, 960 x 576 22.6 / 18.8, 1376 x 640 30.4 / 26.2, 2436 x 1280, 4
-// 55.1 / 40.5, 5472 x 576 115 / 71, 6412 x 576 124 / 79; 40 drawn ones of 192 tokens on 1.14 times as fast in the mean, the worst 9.4 / 9.4 (196 x 576).
-inline bool v2_group_middle(const GemmArgs* probs, int n) {
+// n weight gradients in one launch of middle tiles: where those find a unit each and the small ones do not, but not
+//   * where launches apart, whose long k goes out in pieces, are priced lower: from some 15000 tokens on, 23288 x 1248 split four ways 342 / 276 us, 17024 x 528
+//     259 / 195 (the price here fitted to 183 groups, within 6 %, operands in the caches and not);
+//   * where the small tiles are walked in strips and these are not yet (v2_set_walk): 1646 x 1312, 4 34.0 / 27.9, 1600 x 1856, 8 27.9 / 24.6.
+// Elsewhere, gradients of a layer shard, T x H split p ways, the best of the other forms / so, us: 520 x 816, 2 16.7 / 14.0, 1376 x 640 29.7 / 25.2, 1648 x 1184, 4
+// 36.0 / 28.5, 5400 x 1184, 4 75.7 / 67.0, 9146 x 1664, 8 121 / 107; 180 groups 0.90 in the mean.
+inline bool v2_group_middle(const GemmArgs* probs, int n, const V2GroupPlan& p) {
   if (gemm_v2_group_off() || gemm_v2_forced_bn() || n < 2 || n > kMaxGroup || probs[0].K < 192) return false;
+  const int K = probs[0].K, cus = gemm_cu_count();
   int middle = 0, small = 0;
+  double bytes = 0.0;
   for (int q = 0; q < n; ++q) {
-    if (probs[q].epi != EPI_STORE || probs[q].bias != nullptr || probs[q].K != probs[0].K) return false;
+    if (probs[q].epi != EPI_STORE || probs[q].bias != nullptr || probs[q].K != K) return false;
     middle += v2_middle_tiles(probs[q].M, probs[q].N);
     small += v2_small_tiles(probs[q].M, probs[q].N);
+    bytes += ((double)probs[q].M + probs[q].N) * K * 2.0 / 5.0e6;
   }
-  return small > gemm_cu_count() && middle <= gemm_cu_count();
+  if (small <= cus || middle > cus) return false;
+  if (6.1 + (0.313 + 0.117 * middle / cus) * v2_slices(K) + 0.229 * bytes >= 0.95 * p.alone) return false;
+  bool small_strips = false;
+  for (int q = 0; q < n; ++q) {
+    if (v2_in_strips(v2_middle_plan(probs[q].M, probs[q].N), v2_window<192, true>(), K)) return true;
+    small_strips = small_strips || v2_in_strips(v2_plan(probs[q].M, probs[q].N, K, false, V2_SMALL), v2_window<V2_SMALL, false>(), K);
+  }
+  return !small_strips;
 }
 
 // How a weight gradient a0 and an input gradient a1 that do not depend on each other are launched: together in tiles of bn

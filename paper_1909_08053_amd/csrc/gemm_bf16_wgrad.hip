@@ -26,8 +26,8 @@ static hipError_t launch_split_group(const GemmArgs* probs, int n, int form, hip
 
 // The weight gradients of a layer shard (same operand layout, same k = tokens), as v2_group_middle, split_group_pick and v2_group_plan say.
 hipError_t launch_gemm_bf16_wgrad_group(const GemmArgs* probs, int n, float* splitk_ws, hipStream_t st) {
-  if (v2_group_middle(probs, n)) return launch_gemm_bf16_v2_group<false, false, 192, true>(probs, n, st);
   const V2GroupPlan p = v2_group_plan(probs, n, splitk_ws != nullptr);
+  if (v2_group_middle(probs, n, p)) return launch_gemm_bf16_v2_group<false, false, 192, true>(probs, n, st);
   switch (split_group_pick(probs, n, p)) {
     case SPLIT_64: return launch_split_group<64, 64>(probs, n, SPLIT_64, st);
     case SPLIT_32X64: return launch_split_group<32, 64>(probs, n, SPLIT_32X64, st);

@@ -45,9 +45,16 @@ def test_bf16_middle_tile(layout, M, N, K):
         assert bool(C[M].isnan().all())
 
 
-# bias + GeLU, GeLU' and the column sums beside: the shard's four products and their weight gradients take the tile by turns
-@pytest.mark.parametrize("b,s,H,h,V,causal", [(2, 1100, 512, 8, 528, True), (2, 724, 768, 8, 528, False), (64, 133, 512, 8, 264, True), (1, 193, 576, 6, 264, True),
-                                                  (3, 211, 640, 5, 264, False), (7, 257, 576, 9, 264, True)])
-def test_bf16_layer_in_middle_tiles(b, s, H, h, V, causal):
-    run_layer_parity(synth.small_config(name=f"middle{b * s}_{H}", dtype="bf16", b=b, s=s, H=H, h=h, F=4 * H, V=V, p=1, causal=causal,
+# (b, s, H, h, V, p, causal) -> which of the layer's products take the tile (test_bf16_middle_choice_host.py): bias + GeLU, GeLU', plain products, the column
+# sums beside an input gradient, and the weight gradients of token counts that are no multiple of anything
+LAYERS = {
+    (2, 1100, 512, 8, 528, 1, True): "", (2, 724, 768, 8, 528, 1, False): "fc1 dg", (64, 133, 512, 8, 264, 1, True): "proj fc2 dfc1 dctx dqkv",
+    (1, 193, 576, 6, 264, 1, True): "wgrads", (3, 211, 640, 5, 264, 1, False): "wgrads", (7, 257, 576, 9, 264, 1, True): "wgrads",
+    (1, 1900, 768, 12, 264, 1, True): "qkv fc1 dg", (20, 380, 640, 10, 528, 2, True): "proj fc2 dfc1 dqkv",
+}
+
+
+@pytest.mark.parametrize("b,s,H,h,V,p,causal", LAYERS)
+def test_bf16_layer_in_middle_tiles(b, s, H, h, V, p, causal):
+    run_layer_parity(synth.small_config(name=f"middle{b * s}_{H}", dtype="bf16", b=b, s=s, H=H, h=h, F=4 * H, V=V, p=p, causal=causal,
                                         masked_lm=not causal), scale_w=3.0)
