@@ -342,23 +342,26 @@ inline int split_tiles(int form, int M, int N) {
   return ((M + kSplitTm[form] - 1) / kSplitTm[form]) * ((N + kSplitTn[form] - 1) / kSplitTn[form]);
 }
 // Microseconds of a launch of `tiles` tiles, the longest of `nk` slices and all together of `work` = sum of tiles x slices: a start, the
-// longest wave's slices, further rounds of the chip (a workgroup of the larger two forms a compute unit, two of the smallest), and the
-// operands' way through the caches.  Fitted to 1000 products of the three layouts (64 .. 8192 x 16 .. 6600 x 24 .. 8352), 300 groups of the
-// weight gradients of a layer shard and 290 pairs of the logits' gradients; standard deviation 7-10 %.
-enum { SPLIT_ALONE = 0, SPLIT_GROUP, SPLIT_DUAL };
+// longest wave's slices, further rounds of the chip (a workgroup of the larger two forms a compute unit, two of the smallest), the operands' way through
+// the caches, and the wait of two workgroups of the smallest form for each other.  Fitted to 1500 products of the three layouts (16 .. 8192 x 16 .. 6600 x 24
+// .. 20000), 300 groups of the weight gradients of a layer shard and 290 pairs of the logits' gradients; standard deviation 7-11 %.
+enum { SPLIT_ALONE = 0, SPLIT_WGRAD, SPLIT_GROUP, SPLIT_DUAL };      // (a product by itself: forward or input gradient, weight gradient)
 inline double split_us(int kind, int form, int tiles, int nk, double work) {
-  static const double c[3][3][5] = {            // start, per serial slice, per serial slice of a further round, per further round, work
-      {{2.59, 0.80, 0.42, 1.94, 0.065}, {2.20, 0.59, 0.24, 1.41, 0.051}, {2.10, 0.38, 0.00, 1.06, 0.052}},
-      {{2.79, 0.88, 0.33, 2.57, 0.063}, {2.45, 0.75, 0.22, 1.66, 0.054}, {2.50, 0.41, 0.00, 1.10, 0.073}},
-      {{2.73, 0.67, 0.13, 0.63, 0.093}, {2.49, 0.40, 0.00, 0.85, 0.091}, {2.30, 0.31, 0.00, 0.57, 0.058}}};
+  // start, per serial slice, per serial slice of a further round, per further round, work, per serial slice of a second workgroup a unit
+  static const double c[4][3][6] = {
+      {{2.59, 0.80, 0.42, 1.94, 0.065, 0.0}, {2.20, 0.59, 0.24, 1.41, 0.051, 0.0}, {2.10, 0.38, 0.00, 1.06, 0.052, 0.2}},
+      {{2.55, 0.706, 0.484, 1.80, 0.079, 0.0}, {2.27, 0.517, 0.495, 0.89, 0.063, 0.0}, {2.06, 0.360, 0.148, 0.50, 0.069, 0.152}},
+      {{2.79, 0.88, 0.33, 2.57, 0.063, 0.0}, {2.45, 0.75, 0.22, 1.66, 0.054, 0.0}, {2.50, 0.41, 0.00, 1.10, 0.073, 0.0}},
+      {{2.73, 0.67, 0.13, 0.63, 0.093, 0.0}, {2.49, 0.40, 0.00, 0.85, 0.091, 0.0}, {2.30, 0.31, 0.00, 0.57, 0.058, 0.0}}};
   const double* q = c[kind][form - SPLIT_64];
   const int cus = gemm_cu_count(), per = form == SPLIT_32 ? 2 * cus : cus, serial = (nk + kSplitWaves - 1) / kSplitWaves;
   const int more = (tiles + per - 1) / per - 1;
-  return q[0] + q[1] * serial + (q[2] * serial + q[3]) * more + q[4] * work / cus;
+  const double over = tiles <= cus ? 0.0 : tiles >= 2 * cus ? 1.0 : (double)tiles / cus - 1.0;
+  return q[0] + q[1] * serial + (q[2] * serial + q[3]) * more + q[4] * work / cus + q[5] * serial * over;
 }
-inline double split_us(int form, int M, int N, int K) {
+inline double split_us(int kind, int form, int M, int N, int K) {
   const int t = split_tiles(form, M, N), nk = (K + 31) / 32;
-  return split_us(SPLIT_ALONE, form, t, nk, (double)t * nk);
+  return split_us(kind, form, t, nk, (double)t * nk);
 }
 // Microseconds of t 128-wide tiles of all problems of a launch, at most one a compute unit, the longest of nk slices
 inline double v2_few_us(int t, int nk) { return 3.0 + 0.245 * nk + 3.2 * t / gemm_cu_count(); }
@@ -374,17 +377,17 @@ inline double v2_few_us(const V2Plan& p, int K) {
 // 64 columns (the cross-entropy partials' column tiles).  Large tiles / 64 x 64 / 32 x 64 / 32 x 32, us: fwd 400 x 288 x 192 4.5 / 3.6 / 3.1 / 2.8, 123 x 1888 x
 // 1920 15.4 / 10.2 / 8.2 / 6.8, 273 x 2776 x 2776 22.0 / 16.4 / 22.5 / 28; dgrad 400 x 192 x 512 6.0 / 4.3 / 3.4 / 2.9, 915 x 928 x 448 6.4 / 5.4 / 6.7 / 6.9,
 // 2048 x 512 x 512 6.7 / 5.4 / 6.8 / 7.0; wgrad 192 x 512 x 400 6.1 / 4.3 / 3.6 / 3.1, 688 x 168 x 2166 15.5 / 12 / 10 / 8.5; fwd 1024 x 1920 x 960 stays, 10.3 / 12.2.
-// Of 1000 drawn products 742 take one of these and the mean time falls to 0.642 (0.635 with the best choice every time); five are more than 3 %
-// slower, 624 x 416 x 4059 most, 19.5 / 23.7.
+// wgrad 624 x 416 x 4059 19.0 / 18.9 / 15.5 / 22.5.  Of 818 drawn products of 7.5 us and more the mean time falls to 0.575 (0.559 with the best choice every
+// time); six are more than 3 % slower, dgrad 40 x 4112 x 4904 most, 21.0 / 26.4.
 constexpr double kSplitMargin = 0.92;
 constexpr int kSplitMaxTiles = 4096;
 struct SplitPick { int form; double us; };
-inline SplitPick split_pick(int M, int N, int K, double than, bool wide = false) {
+inline SplitPick split_pick(int kind, int M, int N, int K, double than, bool wide = false) {
   SplitPick best = {SPLIT_NONE, kSplitMargin * than};
   if (gemm_v2_forced_bn()) return {SPLIT_NONE, than};
   for (int form = SPLIT_64; form <= (wide ? SPLIT_32X64 : SPLIT_32); ++form) {
     if (split_tiles(form, M, N) > kSplitMaxTiles) continue;
-    const double us = split_us(form, M, N, K);
+    const double us = split_us(kind, form, M, N, K);
     if (us < best.us) best = {form, us};
   }
   if (best.form == SPLIT_NONE) best.us = than;
@@ -395,7 +398,7 @@ template <bool A_KC, bool B_KC, int EPI>
 SplitPick split_pick_alone(int M, int N, int K, bool allow_split) {
   const V2Choice c = v2_choose<A_KC, B_KC, EPI>(M, N, K, allow_split);
   const double us = c.middle ? c.us : v2_few_us(c.plan, K);
-  return split_pick(M, N, K, us, EPI == EPI_CE);
+  return split_pick(A_KC ? SPLIT_ALONE : SPLIT_WGRAD, M, N, K, us, EPI == EPI_CE);
 }
 
 // Weight gradients of one K in one launch of these tiles, against the launch or launches of the plan p.  (Only where 128-wide tiles would
@@ -428,7 +431,8 @@ inline int split_group_pick(const GemmArgs* probs, int n, const V2GroupPlan& p) 
 
 // A weight gradient a0 and an input gradient a1 in one launch of these tiles, against the launch or launches of d.  T x H x V, as they were / the
 // three forms, us: 176 x 896 x 656 8.6 / 5.0 / 5.7 / 5.8, 3218 x 768 x 392 24 / 16 / 22 / 24, 338 x 560 x 3728 25 / 21 / 19 / 19; 442 x 768 x 6384 35 / 37 / 46 /
-// 47 stays.
+// 47 stays.  Of 622 drawn pairs 0.904 of the time in the mean (0.882 with the best choice every time), 34 more than 3 % slower (225 x 2592 x 640 8.1 / 10.0); at
+// a margin of a tenth 15, but 1300 x 512 x 4000, which gains 4 us, too, stays in large tiles.
 inline int split_dual_pick(const GemmArgs& a0, const GemmArgs& a1, const V2Dual& d) {
   if (gemm_v2_forced_bn() || d.bn == V2_B) return SPLIT_NONE;
   const int nk0 = (a0.K + 31) / 32, nk1 = (a1.K + 31) / 32, nk = nk0 > nk1 ? nk0 : nk1;

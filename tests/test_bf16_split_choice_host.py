@@ -53,6 +53,7 @@ MEASURED = [
     ("dgrads", 355, 1464, 2928, 18.8, 16.0, 20.3, 18.9), ("fwds", 8056, 96, 784, 10.7, 7.1, 8.9, 8.4), ("dgrads", 841, 472, 1888, 17.4, 10.8, 8.4, 9.3),
     ("wgrads", 1104, 368, 1415, 14.8, 9.6, 8.1, 10.7), ("dgrads", 70, 4680, 1560, 16.9, 9.8, 8.7, 9.6), ("wgrads", 80, 672, 301, 5.2, 3.8, 3.2, 2.8),
     ("dgrads", 1058, 192, 192, 4.4, 3.6, 3.0, 2.7), ("fwds", 70, 2312, 3464, 19.2, 17.9, 14.6, 12.2), ("wgrads", 624, 416, 4059, 19.5, 19.1, 16.1, 23.7),
+    ("wgrads", 1272, 216, 4916, 21.7, 23.5, 18.5, 29.3), ("wgrads", 264, 976, 3443, 16.5, 14.6, 12.7, 19.6), ("wgrads", 184, 1432, 3288, 17.2, 15.7, 14.1, 20.3),
 ]
 
 
@@ -69,9 +70,9 @@ def picks(tmp_path_factory):
     return ask
 
 
-def test_chosen_form_is_within_a_seventh_of_the_best_but_once(picks):
+def test_chosen_form_is_within_a_seventh_of_the_best(picks):
     for m, form in zip(MEASURED, picks([f"{m[0]} {m[1]} {m[2]} {m[3]}" for m in MEASURED])):
-        assert m[4 + form] <= (1.5 if m[3] == 4059 else 1.15) * min(m[4:]), (m, form)     # (the worst of 1000 measured choices)
+        assert m[4 + form] <= 1.15 * min(m[4:]), (m, form)
 
 
 def test_shapes_of_the_gpu_tests_take_their_form(picks):
