@@ -15,8 +15,8 @@
 //     most: with more, products of so many tiles are faster in pieces (at 4096^3 it kept the matrix cores busy 86 % of their cycles).
 //   * 64 x 64 tile, 8 waves: 2 x 2 waves of 32 x 32 in two groups that take the two halves of every 64-deep operand tile,
 //     so a CU that holds one tile still has two waves per SIMD to cover LDS and global latency.
-//   * 32 x 32 or 16 x 16 tile, 8 waves that split k and read their operands straight from the caches (no LDS, no barrier in the
-//     loop): for outputs of so few tiles that the serial k loop of one wave, not the matrix rate, is the time.
+//   * 32 x 32 or 16 x 16 tile, 8 waves that split k, each copying its share of the operands into LDS that only it reads (no barrier in
+//     the loop): for outputs of so few tiles that the serial k loop of one wave, not the matrix rate, is the time.
 #include <string.h>
 #include <type_traits>
 #include <utility>
@@ -249,7 +249,8 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_kernel(Gem
 // What bounds it is the intake of operands (a 32 x 32 tile asks for 16 flops a byte), and at few tiles the serial eighth of k.  A copy takes
 // 16 rows of 64 bytes, or whole k-rows: fragments loaded straight to registers have neighbouring lanes in different rows of a k-contiguous
 // operand, one cache line each (us, registers / LDS: 408 x 56 x 7744 with both k-contiguous 29.4 / 21.4, 256 x 512 x 2048 16.6 / 12.0; with one 15.2 /
-// 14.4; k-major 752 x 168 x 4504 34.5 / 26.6, 256 x 512 x 256 3.6 / 3.9; 69 products of 32 .. 32112 wide 8 % less in the mean, no sum changed).
+// 14.4; k-major 752 x 168 x 4504 34.5 / 26.6, but 256 x 512 x 256 4.05 / 4.1 and, in 16 x 16 tiles, 256 x 256 x 2048 8.6 / 9.2; of 278 products
+// with both k-contiguous 0.85 of the time in the mean, with one 0.94, k-major 0.965, no sum changed).
 // Stages: two of a 32 x 32 tile leave room for two workgroups a unit; three or four, one workgroup, 2-6 % slower in the mean (504 x 1072 x 48
 // 4.8 / 6.3 / 6.2, 792 x 72 x 552 6.6 / 7.4 / 7.5, at best 5 % faster at 744 x 1040 x 696).  Four of a 16 x 16 tile: two cost 13 % at 160 x 104 x 7176.
 constexpr int kF32SplitWaves = 8;
@@ -461,28 +462,24 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_f32_tile_colsum_ker
   else colsum_block<float, 64 * WM * WN * KS>(job, id - tiles, lds_f32);
 }
 
-// Launch of a kernel of f32_split_tile
+// Launch of a kernel of f32_split_tile.  (64 KB of LDS in either form: what a launch may ask for as it is.)
+static_assert(f32_split_lds<32>() <= 64 * 1024 && f32_split_lds<16>() <= 64 * 1024, "more LDS is an attribute of the kernel");
 template <int TS, typename Kernel, typename... Args>
-static hipError_t launch_f32_split(LdsAttrOnce* attr, Kernel kern, dim3 grid, hipStream_t st, const Args&... args) {
-  if (f32_split_lds<TS>() > 64 * 1024)
-    if (hipError_t e = attr->ensure((const void*)kern, (int)f32_split_lds<TS>()); e != hipSuccess) return e;
+static hipError_t launch_f32_split(Kernel kern, dim3 grid, hipStream_t st, const Args&... args) {
   hipLaunchKernelGGL(kern, grid, dim3(64 * kF32SplitWaves), (f32_split_lds<TS>()), st, args...);
   return hipGetLastError();
 }
 template <bool A_KC, bool B_KC, int EPI, int TS>
 static hipError_t launch_f32_split_alone(const GemmArgs& a, hipStream_t st) {
-  static LdsAttrOnce attr;
-  return launch_f32_split<TS>(&attr, gemm_f32_split_kernel<A_KC, B_KC, EPI, TS>, dim3(((a.M + TS - 1) / TS) * ((a.N + TS - 1) / TS)), st, a);
+  return launch_f32_split<TS>(gemm_f32_split_kernel<A_KC, B_KC, EPI, TS>, dim3(((a.M + TS - 1) / TS) * ((a.N + TS - 1) / TS)), st, a);
 }
 template <int TS>
 static hipError_t launch_f32_split_colsum(const GemmArgs& a, const ColsumJob& j, hipStream_t st) {
-  static LdsAttrOnce attr;
-  return launch_f32_split<TS>(&attr, gemm_f32_split_colsum_kernel<TS>, dim3(((a.M + TS - 1) / TS) * ((a.N + TS - 1) / TS) + j.blocks), st, a, j);
+  return launch_f32_split<TS>(gemm_f32_split_colsum_kernel<TS>, dim3(((a.M + TS - 1) / TS) * ((a.N + TS - 1) / TS) + j.blocks), st, a, j);
 }
 template <int TS>
 static hipError_t launch_f32_split_dual(const GemmArgs& w, const GemmArgs& x, int tiles_w, hipStream_t st) {
-  static LdsAttrOnce attr;
-  return launch_f32_split<32>(&attr, gemm_f32_split_dual_kernel<TS>, dim3(tiles_w + ((x.M + TS - 1) / TS) * ((x.N + TS - 1) / TS)), st, w, x);
+  return launch_f32_split<32>(gemm_f32_split_dual_kernel<TS>, dim3(tiles_w + ((x.M + TS - 1) / TS) * ((x.N + TS - 1) / TS)), st, w, x);
 }
 
 // LDS of a workgroup of f32_tile
@@ -592,8 +589,7 @@ hipError_t launch_gemm_f32_wgrads(const GemmArgs* all, int n_all, hipStream_t st
     if (b == 128) return launch_f32_tile_group<128, 128, 2, 2, 1, 32, 1>(g, total, st);
     if (b == 64) return chains == 8 ? launch_f32_tile_group<64, 64, 2, 2, 2, 64, 4>(g, total, st)
                                     : launch_f32_tile_group<64, 64, 2, 2, 2, 64, 1>(g, total, st);
-    static LdsAttrOnce attr;
-    return launch_f32_split<32>(&attr, gemm_f32_split_group_kernel, dim3(total), st, g);
+    return launch_f32_split<32>(gemm_f32_split_group_kernel, dim3(total), st, g);
   };
   if (p.wide_apart)
     if (hipError_t e = launch(128, 1, true, false); e != hipSuccess) return e;

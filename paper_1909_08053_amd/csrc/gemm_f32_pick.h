@@ -29,10 +29,11 @@ inline double f32_tile_us(int b, double t, int K) {
 }
 inline double f32_split_us(int M, int N, int K) { return 3.0 + 6.0 * (K / 1024.0) + 2.0 * M * N * K / 52e6; }
 // Tile of the split kernel.  The matrix operations of a 32 x 32 tile take one compute unit 3.7 us per 1024 k, and few such tiles leave units
-// idle: 16 x 16 where those find a unit each (256 x 256, 32 / 16: K = 128 3.1 / 2.5 us, 1024 9.5 / 5.4; below 128 k nothing to
-// gain), or, at longer k, two a unit (256 x 512: K = 512 6.3 / 5.2 us, 1024 9.7 / 8.0, 2048 15.9 / 13.2, 256 3.8 / 3.8: twice the
-// operands are fetched).  A 16 x 16 tile sums in chunks of 16 k, in eight chains like the other; short k only where they are of one
-// length (a longest chain of 32 k in place of 24 at K = 192 is 4 % further off; from 512 k on uneven ones differ by 0.4 % at most).
+// idle: 16 x 16 where those find a unit each (256 x 256, 32 / 16, us, A and B k-contiguous and k-major: K = 128 3.0 / 2.6 and 3.0 / 2.7, 1024 8.9 / 4.1 and 8.3 / 4.6;
+// below 128 k nothing to gain), or, at longer k, two a unit (256 x 512: K = 512 5.4 / 4.2 and 5.6 / 4.5, 1024 9.4 / 6.9 and 8.6 / 8.4, 2048 15.8 / 11.8 and 13.6 / 14.6).
+// A 16 x 16 tile sums in chunks of 16 k, in eight chains like the other; short k only where they are of one
+// length (a longest chain of 32 k in place of 24 at K = 192 is 4 % further off; from 512 k on uneven ones differ by 0.4 % at most).  The line at
+// 512 k is cautious (256 x 512 x 256 3.7 / 3.3).
 inline int f32_split_tile_of(int M, int N, int K) {
   const double t16 = f32_tiles(16, M, N);
   return (K % 128 == 0 && K > 0 && t16 <= gemm_cu_count()) || (K % 16 == 0 && K >= 512 && t16 <= 2 * gemm_cu_count()) ? 16 : 32;
