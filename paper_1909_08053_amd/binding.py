@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional, Sequence
 
 import torch
@@ -60,10 +61,6 @@ class Dropout(ctypes.Structure):
 
 def make_dropout(p: float, seed: int, offset: int) -> Dropout:
     return Dropout(float(p), int(seed) & 0xFFFFFFFFFFFFFFFF, int(offset) & 0xFFFFFFFFFFFFFFFF)
-
-
-def _d(drop: Optional[Dropout]):
-    return ctypes.byref(drop) if drop is not None else None
 
 
 _lib = None
@@ -161,14 +158,20 @@ class _Marshalled:
         return f
 
 
+def _load():
+    """What marshals the calls: the native module or, with a warning that says why, ctypes."""
+    try:
+        from . import _mlm_call
+        return _mlm_call
+    except ImportError as e:
+        if os.path.exists(LIB_PATH):     # (else nothing is built yet: lib() says so)
+            warnings.warn(f"arguments are marshalled through ctypes, not by the native module: {e}", RuntimeWarning, stacklevel=2)
+        return _Marshalled()
+
+
 # Arguments are marshalled natively (csrc/py_call.cpp): in Python that was 69 of 178 us of the host time of a step of 40 launches, now 149 us in
 # all (bf16, 400 tokens x 192, two shards; the GPU needs 161).
-try:
-    if not os.path.exists(LIB_PATH):
-        raise ImportError(LIB_PATH)
-    from . import _mlm_call as _call
-except ImportError:
-    _call = _Marshalled()
+_call = _load()
 
 
 def mlm_shard_range(n: int, p: int, r: int):
