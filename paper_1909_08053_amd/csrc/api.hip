@@ -67,7 +67,7 @@ size_t ws_bytes_for(const mlm_dims* dm, const Local& L, int which) {
     case MLM_WS_COLSUM: return align256(cs_rows * (size_t)dm->H * 4);
     case MLM_WS_VOCAB_CE_FWD:
       if (dm->dtype == MLM_BF16) {
-        const size_t ntile = ((size_t)L.Vl + 127) / 128;   // upper bound over the tile configurations
+        const size_t ntile = ((size_t)L.Vl + 127) / 128;   // (tiles of 64 columns write more: those take a part of sk)
         return 2 * align256(ntile * T * 4) + align256(T * 4) + sk;
       }
       return align256(T * L.Vl * 4);

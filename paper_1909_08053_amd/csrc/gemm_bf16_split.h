@@ -35,7 +35,7 @@ template <int ROWS> struct SplitOperand<true, ROWS> {
 #pragma unroll
     for (int c = 0; c < NC; ++c) off[c] = (uint32_t)(min(row0 + 16 * c + (lane >> 2), nrows - 1) - row0) * (uint32_t)ld * 2 + unit * 2;
   }
-  __device__ __forceinline__ const char* at(int s, int c, int) const { return base + (size_t)s * 64 + off[c]; }
+  __device__ __forceinline__ const char* at(int s, int c) const { return base + (size_t)s * 64 + off[c]; }
   __device__ __forceinline__ int k_of(int) const { return unit; }
   static __device__ __forceinline__ bf16x8 frag(const unsigned char* ring, int f, int lane) {
     const int row = lane & 15;
@@ -60,7 +60,7 @@ template <int ROWS> struct SplitOperand<false, ROWS> {
       off[c] = (uint32_t)row * (uint32_t)ld * 2 + (uint32_t)(min(row0 + u * 8, nrows - 8) - row0) * 2;
     }
   }
-  __device__ __forceinline__ const char* at(int s, int c, int) const { return base + (size_t)(s * 32 + c * KR) * 2 * ld + off[c & 1]; }
+  __device__ __forceinline__ const char* at(int s, int c) const { return base + (size_t)(s * 32 + c * KR) * 2 * ld + off[c & 1]; }
   __device__ __forceinline__ int k_of(int c) const { return c * KR + row; }
   static __device__ __forceinline__ bf16x8 frag(const unsigned char* ring, int f, int lane) {
     const int l16 = lane & 15, lg = lane >> 4, u = 2 * f + ((l16 & 3) >> 1);
@@ -140,7 +140,7 @@ __device__ __forceinline__ void gemm_split_tile(const GemmArgs& a, int tile_m, i
     auto copies = [&](const auto& op, uint32_t to) {
 #pragma unroll
       for (int c = 0; c < std::decay_t<decltype(op)>::NC; ++c) {
-        const bf16* src = reinterpret_cast<const bf16*>(op.at(s, c, 0));
+        const bf16* src = reinterpret_cast<const bf16*>(op.at(s, c));
         if (end) src = op.k_of(c) < kleft ? src : reinterpret_cast<const bf16*>(&v2_zero16);
         dma16(src, to + c * 1024);
       }
