@@ -47,7 +47,8 @@ template <int BN, bool DEEP> constexpr int v2_waves_m() { return BN == 192 || DE
 template <int BN, bool DEEP> constexpr int v2_nw() { return BN == V2_SMALL && !DEEP ? 4 : 8; }
 inline int v2_slices(int K) { return 2 * ((K + 2 * V2_BK - 1) / (2 * V2_BK)); }   // 32-deep slices walked: whole pairs
 // How K ends: KE_PAIR on a whole pair of slices; KE_SLICE on the first slice of a pair (K an odd multiple of 32; the large tiles'
-// kernels: with KE_ANY they are 4-8 % slower at 8192 x 3072 x 1568, and KE_PAIR's with this form's arithmetic 0.7-1 %); KE_ANY.
+// kernels: with KE_ANY they are 4-8 % slower at 8192 x 3072 x 1568, and KE_PAIR's with this form's arithmetic 0.7-1 %); KE_ANY.  (The middle tile has no KE_SLICE: of 499
+// such K its forward products and input gradients are 1.7 % slower in it in the mean, weight gradients 0.6 % faster.)
 enum { KE_PAIR, KE_SLICE, KE_ANY };
 template <int BN, bool DEEP = false> int v2_k_end(int K) {
   if (K % (2 * V2_BK) == 0) return KE_PAIR;
